@@ -151,9 +151,30 @@ FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len)
     FcAttnPlan p;
     memset(&p, 0, sizeof p);
     p.splits = p.splits_bound = 1;
-    if (cfg.dtype != FC_BF16 || cfg.head_dim != 128) return p;  // kind 0: generic kernel
-    p.kind = 1;
     const int g = cfg.n_q_heads / cfg.n_kv_heads;
+    if (cfg.dtype != FC_BF16 || cfg.head_dim != 128) {
+        // kind 0: one workgroup per (sequence, kv head, one or two 16-row tiles); two tiles share the key
+        // and value loads and are taken once they still fill half the chip (head_dim 64 only: with fp32 rows
+        // of 128 the operands of two tiles do not fit in registers).  A workgroup pulls keys and
+        // values at some 50..80 KB per us, so with fewer workgroups than compute units the keys are also
+        // cut into ranges of at least 128 KB; the second launch that merges them costs about 3 us.
+        const int64_t rows = (int64_t)g * A, pairs = (int64_t)cfg.batch * cfg.n_kv_heads;
+        p.row_tiles = (int)((rows + 15) / 16);
+        p.waves = 8;
+        p.tiles_per_wg = cfg.head_dim == 64 && pairs * ((rows + 31) / 32) >= 128 ? 2 : 1;
+        const int64_t base = pairs * ((p.row_tiles + p.tiles_per_wg - 1) / p.tiles_per_wg);
+        const int64_t groups = ((int64_t)kv_len + 31) / 32;
+        const int64_t group_bytes = 64 * (int64_t)cfg.head_dim * (int64_t)esize_of(cfg.dtype);
+        int64_t splits = groups * group_bytes / (128 * 1024);
+        if (splits > 256 / base) splits = 256 / base;
+        if (splits < 1) splits = 1;
+        p.splits_bound = (int)splits;
+        const int64_t per = (groups + splits - 1) / splits;
+        p.keys_per_split = (int)(32 * per);
+        p.splits = (int)((groups + per - 1) / per);
+        return p;
+    }
+    p.kind = 1;
     p.row_tiles = (int)(((int64_t)g * A + 31) / 32);
     // Row tiles per workgroup: 2 (four waves share one tile pair), 4 or 8 (each wave its own pair).
     // One workgroup per compute unit (its LDS ring takes 128 KB), so aim for one wave of them.
@@ -209,11 +230,26 @@ FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len)
 
 size_t fc_plan_workspace(const fc_config &cfg, const FcAttnPlan &p, int A)
 {
-    if (p.kind == 0 || p.splits_bound <= 1) return 0;
-    // per (32-row tile, split): 32 x Dh partial outputs as half floats + 32 x 4 floats of row state
     (void)A;
+    if (p.splits_bound <= 1) return 0;
+    if (p.kind == 0)  // per (workgroup tile, split): rows x Dh partial outputs + rows x 2 floats of row state
+        return (size_t)cfg.batch * cfg.n_kv_heads * ((p.row_tiles + p.tiles_per_wg - 1) / p.tiles_per_wg) * p.splits_bound *
+               (16 * p.tiles_per_wg) * (cfg.head_dim + 2) * sizeof(float);
+    // per (32-row tile, split): 32 x Dh partial outputs as half floats + 32 x 4 floats of row state
     return (size_t)cfg.batch * cfg.n_kv_heads * p.row_tiles * p.splits_bound * 32 *
            (cfg.head_dim * 2 + 4 * sizeof(float));
+}
+
+// The plan of one call that brings `bytes` of workspace.  The kernel of kind 0 cuts the keys only to fill the
+// chip; without the space for it it runs uncut.
+static FcAttnPlan plan_with_workspace(const fc_config &cfg, int A, int kv_len, size_t bytes)
+{
+    FcAttnPlan p = fc_plan_attention(cfg, A, kv_len);
+    if (p.kind == 0 && fc_plan_workspace(cfg, p, A) > bytes) {
+        p.splits = p.splits_bound = 1;
+        p.keys_per_split = (kv_len + 31) / 32 * 32;
+    }
+    return p;
 }
 
 extern "C" {
@@ -405,7 +441,7 @@ fc_status fc_qkv_project_scatter(fc_cache *cache, int32_t layer, const void *x, 
                     A, cache->cfg.max_seq);
     const FcGeom G = geom_of(cache);
     void *kl = layer_ptr(cache, cache->k, layer), *vl = layer_ptr(cache, cache->v, layer);
-    // wide windows: tiled GEMM; short windows: weight-streaming kernels; other shapes: plain ALU kernel
+    // wide windows: tiled GEMM; short windows: weight-streaming kernels; other shapes and fp32: tile kernel
     hipError_t e;
     if (fc_project_gemm_supported(cache->cfg, cache->cfg.batch * A))
         e = fc_launch_project_gemm(G, x, w_qkv, b_qkv, pos, win_start, A, q_out, kl, vl, (hipStream_t)stream);
@@ -413,8 +449,8 @@ fc_status fc_qkv_project_scatter(fc_cache *cache, int32_t layer, const void *x, 
         e = fc_launch_project_mfma(G, cache->inv_freq, x, w_qkv, b_qkv, pos, win_start, A, q_out, kl, vl,
                                    cache->scratch, (hipStream_t)stream);
     else
-        e = fc_launch_project_generic(G, cache->cfg.dtype, x, w_qkv, b_qkv, pos, win_start, A, q_out, kl, vl,
-                                      (hipStream_t)stream);
+        e = fc_launch_project_tile(G, cache->inv_freq, cache->cfg.dtype, x, w_qkv, b_qkv, pos, win_start, A, q_out, kl,
+                                   vl, (hipStream_t)stream);
     return e == hipSuccess ? FC_OK : hip_fail(e, "projection launch");
 }
 
@@ -442,7 +478,7 @@ fc_status fc_active_attention(fc_cache *cache, int32_t layer, const void *q, int
         return fail(FC_ERR_UNSUPPORTED, "batch * A exceeds 2^24 rows");
     if (kv_len < 1 || kv_len > cache->cfg.max_seq)
         return fail(FC_ERR_BOUNDS, "kv_len %d outside [1, %d]", kv_len, cache->cfg.max_seq);
-    const FcAttnPlan plan = fc_plan_attention(cache->cfg, A, kv_len);
+    const FcAttnPlan plan = plan_with_workspace(cache->cfg, A, kv_len, workspace ? workspace_bytes : 0);
     const size_t need = fc_plan_workspace(cache->cfg, plan, A);
     if (need > 0 && (!workspace || workspace_bytes < need))
         return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need,
@@ -452,8 +488,8 @@ fc_status fc_active_attention(fc_cache *cache, int32_t layer, const void *q, int
     hipError_t e = plan.kind == 1
                        ? fc_launch_attention_mfma(G, plan, q, kl, vl, pos, A, kv_len, out, workspace,
                                                   (hipStream_t)stream)
-                       : fc_launch_attention_generic(G, cache->cfg.dtype, q, kl, vl, pos, A, kv_len, out,
-                                                     (hipStream_t)stream);
+                       : fc_launch_attention_tile(G, plan, cache->cfg.dtype, q, kl, vl, pos, A, kv_len, out, workspace,
+                                                  (hipStream_t)stream);
     return e == hipSuccess ? FC_OK : hip_fail(e, "attention launch");
 }
 
@@ -508,7 +544,7 @@ fc_status fc_active_attention_static(fc_cache *cache, int32_t layer, const void 
         return fail(FC_ERR_UNSUPPORTED, "batch * A exceeds 2^24 rows");
     if (kv_len < 1 || kv_len > cache->cfg.max_seq)
         return fail(FC_ERR_BOUNDS, "kv_len %d outside [1, %d]", kv_len, cache->cfg.max_seq);
-    const FcAttnPlan plan = fc_plan_attention(cache->cfg, A, kv_len);
+    const FcAttnPlan plan = plan_with_workspace(cache->cfg, A, kv_len, FC_STATIC_SCRATCH_BYTES);
     const size_t need = fc_plan_workspace(cache->cfg, plan, A);
     if (need > FC_STATIC_SCRATCH_BYTES)
         return fail(FC_ERR_WORKSPACE, "this shape needs %zu bytes of partial results, the static scratch holds %u",
@@ -540,7 +576,7 @@ fc_status fc_refresh(fc_cache *cache, int32_t layer, const void *x, const void *
             return fail(FC_ERR_BOUNDS, "kv_len %d outside [1, %d]", kv_len, cache->cfg.max_seq);
         if (start + R > kv_len)
             return fail(FC_ERR_BOUNDS, "refreshed rows end at %d, beyond kv_len %d", start + R, kv_len);
-        const FcAttnPlan plan = fc_plan_attention(cache->cfg, R, kv_len);
+        const FcAttnPlan plan = plan_with_workspace(cache->cfg, R, kv_len, workspace ? workspace_bytes : 0);
         const size_t need = fc_plan_workspace(cache->cfg, plan, R);
         if (need > 0 && (!workspace || workspace_bytes < need))
             return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need,
@@ -624,8 +660,8 @@ static fc_status linear_common(int32_t dtype, int mode, const void *x, const voi
     else if (plan.kind >= 1)
         e = fc_launch_linear_skinny(plan, mode, x, w, w2, res, M, K, N, out, workspace, (hipStream_t)stream);
     else
-        e = fc_launch_linear_generic(dtype, mode, x, w, mode == FC_LIN_GATE_UP ? w2 : res, M, K, N, out,
-                                     (hipStream_t)stream);
+        e = fc_launch_linear_tile(dtype, mode, x, w, mode == FC_LIN_GATE_UP ? w2 : res, M, K, N, out,
+                                  (hipStream_t)stream);
     return e == hipSuccess ? FC_OK : hip_fail(e, "linear launch");
 }
 
@@ -763,7 +799,7 @@ LmHeadWs lm_head_ws(int dtype, int M, int K, int V)
     w.parts = w.wide.kind == 1 ? V / 128
                                : (w.plan.kind == 1 ? w.plan.slabs
                                                    : (w.plan.kind == 2 ? w.plan.G  // one running triple per workgroup
-                                                                       : (V + FC_LMHEAD_GENERIC_CHUNK - 1) / FC_LMHEAD_GENERIC_CHUNK));
+                                                                       : (V + FC_LMHEAD_TILE_PART - 1) / FC_LMHEAD_TILE_PART));
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t at = off;
@@ -814,7 +850,7 @@ fc_status fc_lm_head_argmax(int32_t dtype, const void *x, const void *w_vocab, i
         e = fc_launch_linear_skinny(w.plan, FC_LIN_VOCAB, x, w_vocab, nullptr, nullptr, M, K, V, nullptr, ws + w.tiles,
                                     (hipStream_t)stream, &am);
     else
-        e = fc_launch_lmhead_generic(dtype, x, w_vocab, M, K, V, am, (hipStream_t)stream);
+        e = fc_launch_lmhead_tile(dtype, x, w_vocab, M, K, V, am, (hipStream_t)stream);
     if (e == hipSuccess) e = fc_launch_lmhead_reduce(am, w.parts, M, tok, conf, (hipStream_t)stream);
     return e == hipSuccess ? FC_OK : hip_fail(e, "lm-head launch");
 }

@@ -1,8 +1,10 @@
-// Plain-ALU kernels of the cached layer-step for any supported dtype / head_dim.
-//
-// They are the whole path for fp32 caches (the small full-precision configuration) and for bf16
-// shapes the matrix-core kernels do not cover.  Arithmetic: fp32 accumulation everywhere, rotary
-// angles reduced in double, results rounded once to the storage dtype.
+// Kernels for fp32 caches (the small full-precision configuration) and for the bf16 shapes that the
+// weight-streaming and tiled-GEMM kernels do not cover (head_dim 64, hidden sizes and widths that are
+// not whole stages or slabs), plus row copies, RMS normalisation and the drift diagnostic.
+// Arithmetic: products on the matrix cores with fp32 accumulation (fp32 operands use the fp32 MFMA:
+// full-precision products), rotary angles reduced in double, results rounded once to the storage dtype.
+#include <string.h>
+
 #include "fc_device.h"
 #include "fc_internal.h"
 
@@ -11,11 +13,6 @@ namespace {
 __device__ __forceinline__ float wave_sum(float v)
 {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-__device__ __forceinline__ float wave_max(float v)
-{
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
     return v;
 }
 
@@ -48,140 +45,536 @@ __global__ __launch_bounds__(256) void k_copy_rows(FcGeom G, T *__restrict__ kc,
 }
 
 // ---------------------------------------------------------------------------------------------
-// Projection + RoPE + scatter.  Block = (4 rows, one head slot); each wave owns every 4th output
-// column of the head and runs the dot product with lanes along the hidden dimension.
-constexpr int PG_ROWS = 4;
+// Operand fragments of the 16x16 matrix instructions: a lane (rho = lane & 15, q = lane >> 4) holds 16
+// bytes of row rho, the hidden elements KB q .. KB q + KB - 1 of a block of 4 KB.  For fp32 the four
+// elements feed four v_mfma_f32_16x16x4_f32 (each takes one element per lane, so the hidden index is
+// permuted, the same way in both operands); for bf16 the eight feed one v_mfma_f32_16x16x32_bf16.
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_project_generic(FcGeom G, const T *__restrict__ X,
-                                                         const T *__restrict__ W,
-                                                         const T *__restrict__ bias,
-                                                         const int32_t *__restrict__ pos, int win_start,
-                                                         int A, T *__restrict__ Q, T *__restrict__ Kc,
-                                                         T *__restrict__ Vc)
-{
-    __shared__ float y[PG_ROWS][128];
-    const int hs = blockIdx.y;  // head slot: q heads, then k heads, then v heads
-    const int m0 = blockIdx.x * PG_ROWS;
-    const int M = G.B * A;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+struct Op;
+template <>
+struct Op<float> {
+    static constexpr int KB = 4;
+    typedef f32x4 frag;
+    static __device__ __forceinline__ f32x4 mfma(const frag &a, const frag &b, f32x4 acc)
+    {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc, 0, 0, 0);
+        return acc;
+    }
+};
+template <>
+struct Op<bf16_t> {
+    static constexpr int KB = 8;
+    typedef bf16x8 frag;
+    static __device__ __forceinline__ f32x4 mfma(const frag &a, const frag &b, f32x4 acc)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
+    }
+};
 
-    for (int i = wave; i < G.Dh; i += 4) {
-        const int n = hs * G.Dh + i;
-        const T *w = W + (size_t)n * G.d;
-        float acc[PG_ROWS];
+__device__ __forceinline__ float partner32(float v)  // the value of lane ^ 32
+{
+    const unsigned u = __float_as_uint(v);
+    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return (threadIdx.x & 32) ? __uint_as_float(r[0]) : __uint_as_float(r[1]);
+}
+
+__device__ __forceinline__ void store4(float *p, const float (&y)[4]) { *(float4 *)p = make_float4(y[0], y[1], y[2], y[3]); }
+__device__ __forceinline__ void store4(bf16_t *p, const float (&y)[4])
+{
+    uint2 w;
+    w.x = (uint32_t)fc_bf16_bits(y[0]) | ((uint32_t)fc_bf16_bits(y[1]) << 16);
+    w.y = (uint32_t)fc_bf16_bits(y[2]) | ((uint32_t)fc_bf16_bits(y[3]) << 16);
+    *(uint2 *)p = w;
+}
+
+// ---------------------------------------------------------------------------------------------
+// Linear layers of any shape: Y^T = W X^T for a block of 16 NT weight rows and 16 MT window rows per
+// workgroup.  These problems are small (a few MB of weights at most), so what bounds them is latency:
+// the eight waves cut the hidden dimension, each streams its part of both operands from global memory
+// straight into operand registers (the next pair of blocks in flight behind the multiplies of this one),
+// and the partial tiles are summed through LDS, tile t by wave t mod 8, which applies the epilogue.
+// Plain-ALU kernels with one dot product per wave took 36 us for the tiny configuration's projection (32
+// rows, hidden 256, 768 outputs; 0.3 TFLOP/s); this one takes about 5.
+//   EPI_QKV       bias, rotary embedding, scatter: a 16-row weight tile is the rotary indices i0 .. i0 + 7
+//                 of a head and their partners, so the two members of a pair sit 32 lanes apart
+//   EPI_RESIDUAL  out = aux + x w^T (aux may be nullptr)
+//   EPI_GATE_UP   out = silu(x w^T) * (x w2^T): a tile is eight gate rows and the same eight up rows
+//   EPI_VOCAB     per (workgroup of weight rows, window row): largest logit, its index, sum of exponentials
+enum { EPI_QKV, EPI_RESIDUAL, EPI_GATE_UP, EPI_VOCAB };
+
+struct TileArgs {
+    const void *X, *W, *W2, *aux;  // aux: bias [N] (EPI_QKV) or residual [M][N]
+    void *out;                     // [M][N], or q
+    int M, K, N, n_blocks;         // n_blocks: workgroups along the weight rows
+    // EPI_QKV
+    FcGeom G;
+    const int32_t *pos;
+    int win_start, A;
+    void *Kc, *Vc;
+    double inv_freq[64];
+    FcArgmaxPart am;               // EPI_VOCAB
+};
+
+constexpr int TW = 8;  // waves per workgroup
+constexpr size_t tile_lds(int NT, int MT) { return (size_t)TW * NT * MT * 1024 + (size_t)MT * 16 * NT * 8 * sizeof(float2); }
+
+template <typename T, int NT, int MT, int EPI>
+__global__ __launch_bounds__(TW * 64) void k_linear_tile(TileArgs p)
+{
+    typedef Op<T> O;
+    typedef typename O::frag frag;
+    constexpr int KB = O::KB, U = 2;  // blocks of 4 KB hidden elements per load step
+    extern __shared__ __align__(16) unsigned char tile_smem[];
+    float *red = (float *)tile_smem;                               // [wave][tile][reg][lane]
+    float2 *cs = (float2 *)(tile_smem + (size_t)TW * NT * MT * 1024);  // EPI_QKV: [window row][8 NT rotary indices]
+    const FcGeom &G = p.G;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rho = lane & 15, q = lane >> 4;
+    const int n_blk = blockIdx.x % p.n_blocks, m0 = blockIdx.x / p.n_blocks * (16 * MT);
+    const int half = G.Dh / 2;
+    // EPI_QKV: tiles per head = Dh / 16
+    auto head_of = [&](int tile) { return tile / (G.Dh / 16); };
+    auto i0_of = [&](int tile) { return (tile % (G.Dh / 16)) * 8; };
+
+    const T *wrow[NT], *xrow[MT];
 #pragma unroll
-        for (int r = 0; r < PG_ROWS; ++r) acc[r] = 0.f;
-        for (int k = lane; k < G.d; k += 64) {
-            const float wv = fc_to_float(w[k]);
-#pragma unroll
-            for (int r = 0; r < PG_ROWS; ++r)
-                if (m0 + r < M) acc[r] += wv * fc_to_float(X[(size_t)(m0 + r) * G.d + k]);
+    for (int t = 0; t < NT; ++t) {
+        const int tile = n_blk * NT + t;
+        if (EPI == EPI_QKV) {
+            const int hs = min(head_of(tile), G.Hq + 2 * G.Hkv - 1), i0 = i0_of(tile);
+            wrow[t] = (const T *)p.W + (size_t)(hs * G.Dh + (rho < 8 ? i0 + rho : half + i0 + rho - 8)) * p.K;
+        } else if (EPI == EPI_GATE_UP) {
+            wrow[t] = (const T *)(rho < 8 ? p.W : p.W2) + (size_t)min(tile * 8 + (rho & 7), p.N - 1) * p.K;
+        } else {
+            wrow[t] = (const T *)p.W + (size_t)min(tile * 16 + rho, p.N - 1) * p.K;
         }
+        wrow[t] += KB * q;
+    }
 #pragma unroll
-        for (int r = 0; r < PG_ROWS; ++r) {
-            const float s = wave_sum(acc[r]);
-            if (lane == 0) y[r][i] = s + (bias ? fc_to_float(bias[n]) : 0.f);
+    for (int t = 0; t < MT; ++t) xrow[t] = (const T *)p.X + (size_t)min(m0 + 16 * t + rho, p.M - 1) * p.K + KB * q;
+
+    // this wave's blocks of the hidden dimension
+    const int n_kb = (p.K + 4 * KB - 1) / (4 * KB);
+    const int b0 = wave * n_kb / TW, b1 = (wave + 1) * n_kb / TW;
+    auto load = [&](int b, frag(&wf)[U][NT], frag(&xf)[U][MT]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            // past this wave's blocks or past the hidden dimension (K is a multiple of 8, a block 16 or 32):
+            // read the row's first elements and drop them
+            const int k = (b + u) * 4 * KB;
+            const bool ok = b + u < b1 && k + KB * q < p.K;
+            const int at = ok ? k : -KB * q;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) wf[u][t] = *(const frag *)(wrow[t] + at);
+#pragma unroll
+            for (int t = 0; t < MT; ++t) xf[u][t] = *(const frag *)(xrow[t] + at);
+            if (!ok) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t) wf[u][t] = frag{};
+#pragma unroll
+                for (int t = 0; t < MT; ++t) xf[u][t] = frag{};
+            }
+        }
+    };
+    f32x4 acc[NT][MT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int m = 0; m < MT; ++m) acc[t][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](const frag(&wf)[U][NT], const frag(&xf)[U][MT]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int m = 0; m < MT; ++m) acc[t][m] = O::mfma(wf[u][t], xf[u][m], acc[t][m]);
+    };
+
+    frag wa[U][NT], xa[U][MT], wb[U][NT], xb[U][MT];
+    load(b0, wa, xa);
+    if (EPI == EPI_QKV) {
+        // rotary factors of this workgroup's rows and indices, while the first loads are in flight
+        const int hs0 = head_of(n_blk * NT);
+        if (hs0 < G.Hq + G.Hkv) {
+            for (int idx = tid; idx < 16 * MT * 8 * NT; idx += TW * 64) {
+                const int lr = idx / (8 * NT), e = idx % (8 * NT);
+                const int m = min(m0 + lr, p.M - 1);
+                const int pp = p.pos ? p.pos[m] : p.win_start + m % p.A;
+                double turns = (double)pp * p.inv_freq[i0_of(n_blk * NT + e / 8) + e % 8] * 0.15915494309189533576888;
+                turns -= rint(turns);
+                float c, s;
+                sincosf((float)(turns * 6.283185307179586476925286766559), &s, &c);
+                cs[idx] = make_float2(c, s);
+            }
         }
     }
+    for (int b = b0; b < b1; b += 2 * U) {
+        load(b + U, wb, xb);
+        multiply(wa, xa);
+        if (b + U >= b1) break;
+        load(b + 2 * U, wa, xa);
+        multiply(wb, xb);
+    }
+
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) red[((wave * NT * MT + t * MT + m) * 4 + r) * 64 + lane] = acc[t][m][r];
     __syncthreads();
 
-    const int half = G.Dh / 2;
-    for (int idx = threadIdx.x; idx < PG_ROWS * half; idx += 256) {
-        const int r = idx / half, i = idx % half;
-        const int m = m0 + r;
-        if (m >= M) continue;
-        const int b = m / A, a = m % A;
-        const int p = pos ? pos[m] : win_start + a;
-        const bool valid = p >= 0 && p < G.max_seq;
-        float y0 = y[r][i], y1 = y[r][i + half];
-        if (hs < G.Hq + G.Hkv && valid) {
-            float c, s;
-            fc_rope_cs(p, i, G.Dh, G.log_base, &c, &s);
-            const float r0 = y0 * c - y1 * s;
-            const float r1 = y1 * c + y0 * s;
-            y0 = r0;
-            y1 = r1;
-        }
-        if (hs < G.Hq) {
-            T *q = Q + (((size_t)b * G.Hq + hs) * A + a) * G.Dh;
-            q[i] = fc_from_float<T>(valid ? y0 : 0.f);
-            q[i + half] = fc_from_float<T>(valid ? y1 : 0.f);
-        } else if (valid) {
-            if (hs < G.Hq + G.Hkv) {
-                const int j = hs - G.Hq;
-                Kc[fc_k_index(G, b, j, p, i)] = fc_from_float<T>(y0);
-                Kc[fc_k_index(G, b, j, p, i + half)] = fc_from_float<T>(y1);
+    float run_mx = -INFINITY, run_sm = 0.f;
+    int run_arg = 0x7fffffff;
+    // EPI_VOCAB: the NT tiles of a window-row tile are merged by one wave
+    for (int ti = wave; ti < (EPI == EPI_VOCAB ? MT : NT * MT); ti += TW) {
+#pragma unroll
+        for (int tv = 0; tv < (EPI == EPI_VOCAB ? NT : 1); ++tv) {
+            const int t = EPI == EPI_VOCAB ? tv : ti / MT, mt = EPI == EPI_VOCAB ? ti : ti % MT;
+            float y[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w2 = 0; w2 < TW; ++w2)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) y[r] += red[((w2 * NT * MT + t * MT + mt) * 4 + r) * 64 + lane];
+            // lane (rho, q) holds weight rows 4 q .. 4 q + 3 of the tile for window row rho
+            const int m = m0 + 16 * mt + rho, tile = n_blk * NT + t;
+            const bool mvalid = m < p.M;
+            if constexpr (EPI == EPI_QKV) {
+                const int hs = head_of(tile), i0 = i0_of(tile);
+                if (hs >= G.Hq + 2 * G.Hkv) continue;
+                const int d0 = (q >= 2 ? half : 0) + i0 + 4 * (q & 1);
+                const int mm = mvalid ? m : 0;
+                const int b = mm / p.A, a = mm - b * p.A;
+                const int pp = p.pos ? p.pos[mm] : p.win_start + a;
+                const bool valid = mvalid && pp >= 0 && pp < G.max_seq;
+                if (p.aux) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) y[r] += fc_to_float(((const T *)p.aux)[hs * G.Dh + d0 + r]);
+                }
+                if (hs < G.Hq + G.Hkv) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float other = partner32(y[r]);
+                        const float2 f = cs[(16 * mt + rho) * (8 * NT) + 8 * t + 4 * (q & 1) + r];
+                        y[r] = q >= 2 ? y[r] * f.x + other * f.y : y[r] * f.x - other * f.y;
+                    }
+                }
+                if (hs < G.Hq) {
+                    if (!valid) y[0] = y[1] = y[2] = y[3] = 0.f;
+                    if (mvalid) store4((T *)p.out + (((size_t)b * G.Hq + hs) * p.A + a) * G.Dh + d0, y);
+                } else if (valid) {
+                    if (hs < G.Hq + G.Hkv) {
+                        store4((T *)p.Kc + fc_k_index(G, b, hs - G.Hq, pp, d0), y);
+                    } else {
+                        T *v = (T *)p.Vc + fc_v_index(G, b, hs - G.Hq - G.Hkv, pp, d0);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) v[r * FC_VTILE] = fc_from_float<T>(y[r]);
+                    }
+                }
+            } else if constexpr (EPI == EPI_GATE_UP) {
+                // lanes q = 0, 1 hold the gate products of features 4 q + r, lanes q = 2, 3 the up products
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float up = partner32(y[r]);
+                    y[r] = y[r] / (1.0f + expf(-y[r])) * up;
+                }
+                const int f0 = tile * 8 + 4 * q;
+                if (!mvalid || q >= 2) continue;
+                T *o = (T *)p.out + (size_t)m * p.N + f0;
+                if ((p.N & 3) == 0) {
+                    if (f0 < p.N) store4(o, y);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (f0 + r < p.N) o[r] = fc_from_float<T>(y[r]);
+                }
+            } else if constexpr (EPI == EPI_RESIDUAL) {
+                const int n0 = tile * 16 + 4 * q;
+                if (!mvalid) continue;
+                T *o = (T *)p.out + (size_t)m * p.N + n0;
+                if (p.aux) {
+                    const T *res = (const T *)p.aux + (size_t)m * p.N + n0;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (n0 + r < p.N) y[r] += fc_to_float(res[r]);
+                }
+                if ((p.N & 3) == 0) {
+                    if (n0 < p.N) store4(o, y);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (n0 + r < p.N) o[r] = fc_from_float<T>(y[r]);
+                }
             } else {
-                const int j = hs - G.Hq - G.Hkv;
-                Vc[fc_v_index(G, b, j, p, i)] = fc_from_float<T>(y0);
-                Vc[fc_v_index(G, b, j, p, i + half)] = fc_from_float<T>(y1);
+                const int n0 = tile * 16 + 4 * q;
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (n0 + r < p.N) fc_argmax_merge(run_mx, run_arg, run_sm, y[r], n0 + r, 1.0f);
+            }
+        }
+        if constexpr (EPI == EPI_VOCAB) {
+#pragma unroll
+            for (int off = 16; off < 64; off <<= 1) {
+                const float mx2 = __shfl_xor(run_mx, off, 64), sm2 = __shfl_xor(run_sm, off, 64);
+                const int arg2 = __shfl_xor(run_arg, off, 64);
+                fc_argmax_merge(run_mx, run_arg, run_sm, mx2, arg2, sm2);
+            }
+            const int m = m0 + 16 * ti + rho;
+            if (q == 0 && m < p.M) {
+                const size_t at = (size_t)n_blk * p.M + m;
+                p.am.mx[at] = run_mx;
+                p.am.arg[at] = run_arg;
+                p.am.sm[at] = run_sm;
             }
         }
     }
 }
 
 // ---------------------------------------------------------------------------------------------
-// Attention, one block per (query row, head, sequence); keys in chunks of 256 with an online
-// softmax (running max m, running sum l, rescaled accumulator).
-template <typename T>
-__global__ __launch_bounds__(256) void k_attention_generic(FcGeom G, const T *__restrict__ Q,
-                                                           const T *__restrict__ Kc,
-                                                           const T *__restrict__ Vc,
-                                                           const int32_t *__restrict__ pos, int A,
-                                                           int kv_len, T *__restrict__ O)
-{
-    __shared__ float qs[128];
-    __shared__ float ps[256];
-    __shared__ float red[4];
-    const int a = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    T *o = O + ((size_t)b * A + a) * ((size_t)G.Hq * G.Dh) + (size_t)h * G.Dh;
-    if (pos) {  // padded row: same rule as the projection (negative or beyond the cache)
-        const int p = pos[b * A + a];
-        if (p < 0 || p >= G.max_seq) {
-            if (tid < G.Dh) o[tid] = fc_from_float<T>(0.f);
-            return;
-        }
-    }
-    const int j = h / G.g;
-    if (tid < G.Dh) qs[tid] = fc_to_float(Q[(((size_t)b * G.Hq + h) * A + a) * G.Dh + tid]);
-    __syncthreads();
+// Attention of any supported shape: 16 QT query rows of a (sequence, kv head) per workgroup, its eight
+// waves take the 32-key groups of the workgroup's key range in turn and are merged through LDS.
+//
+// S^T = K Q^T and O^T += V^T P^T on the 16x16 matrix instructions, operands straight from global memory
+// (K rows and transposed V tiles are both in operand order, 16 bytes per lane).  The accumulator of S^T
+// puts keys 4 q + r of a 16-key group into register r of lane (query, q): for fp32 that is the operand
+// layout of P^T (four 16x16x4 instructions, keys 4 q + j); for bf16 the K rows of the two groups are read
+// permuted, so that the eight probabilities of a lane are the keys 8 q .. 8 q + 7.  No exchange for P.
+//
+// These caches are small: the kernel is bound by latency with few query rows and by L2 and the fp32 matrix
+// rate with many.  A short cache with a single workgroup per (head, tile) is cut into key ranges ("splits",
+// planned on the host) whose partial states k_attn_tile_merge combines.  The plain-ALU kernel it replaces
+// (a thread per key, then a thread per output column) took 22 us for the tiny configuration.
+struct AttnTileArgs {
+    const void *Q, *Kc, *Vc;
+    const int32_t *pos;
+    void *out;
+    float *part_o, *part_ml;  // splits > 1: [bj][tile][split][16 QT][Dh], [bj][tile][split][16 QT][2]
+    FcGeom G;
+    int A, kv_len, tiles, splits, groups_per_split;
+    float c;                  // softmax scale * log2(e)
+};
 
-    float m = -INFINITY, l = 0.f, acc = 0.f;
-    for (int c0 = 0; c0 < kv_len; c0 += 256) {
-        const int t = c0 + tid;
-        float s = -INFINITY;
-        if (t < kv_len) {
-            const T *k = Kc + fc_k_index(G, b, j, t, 0);
-            float dot = 0.f;
-            for (int i = 0; i < G.Dh; ++i) dot += qs[i] * fc_to_float(k[i]);
-            s = dot * G.scale;
-        }
-        float mx = wave_max(s);
-        if (lane == 0) red[wave] = mx;
-        __syncthreads();
-        mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-        const float m_new = fmaxf(m, mx);
-        const float p = (t < kv_len) ? expf(s - m_new) : 0.f;
-        ps[tid] = p;
-        float sum = wave_sum(p);
-        __syncthreads();  // everyone has read red[] for the max; ps[] is complete after this
-        if (lane == 0) red[wave] = sum;
-        __syncthreads();
-        sum = red[0] + red[1] + red[2] + red[3];
-        const float alpha = (m == -INFINITY) ? 0.f : expf(m - m_new);
-        l = l * alpha + sum;
-        m = m_new;
-        if (tid < G.Dh) {
-            const int n = min(256, kv_len - c0);
-            float part = 0.f;
-            for (int u = 0; u < n; ++u) part += ps[u] * fc_to_float(Vc[fc_v_index(G, b, j, c0 + u, tid)]);
-            acc = acc * alpha + part;
-        }
-        __syncthreads();  // ps[] and red[] are rewritten by the next chunk
+constexpr int AT_STRIDE = 4;  // padding floats per row of the exchange area
+
+template <typename T>
+__device__ __forceinline__ void attn_store_row4(const AttnTileArgs &p, int bj, int row, int d0, float4 v)
+{
+    const FcGeom &G = p.G;
+    if (row >= G.g * p.A) return;
+    const int b = bj / G.Hkv, j = bj % G.Hkv, hg = row / p.A, a = row - hg * p.A;
+    if (p.pos) {  // padded row: same rule as the projection (negative or beyond the cache)
+        const int pp = p.pos[b * p.A + a];
+        if (pp < 0 || pp >= G.max_seq) v = make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    if (tid < G.Dh) o[tid] = fc_from_float<T>(acc / l);
+    const float y[4] = {v.x, v.y, v.z, v.w};
+    store4((T *)p.out + ((size_t)b * p.A + a) * ((size_t)G.Hq * G.Dh) + (size_t)(j * G.g + hg) * G.Dh + d0, y);
+}
+
+template <typename T, int DH, int QT>
+__global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
+{
+    typedef Op<T> O;
+    typedef typename O::frag frag;
+    constexpr int KB = O::KB, NKB = DH / (4 * KB), ND = DH / 16, ROW = DH + AT_STRIDE;
+    constexpr bool F32 = KB == 4;
+    constexpr int NV = F32 ? 2 : 1;  // V fragments per 16 head-dim rows and 32 keys
+    extern __shared__ __align__(16) unsigned char attn_smem[];
+    float *xo = (float *)attn_smem;                  // [wave][16 QT][ROW]
+    float *xml = xo + TW * QT * 16 * ROW;            // [wave][16 QT][2]
+    const FcGeom &G = p.G;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rho = lane & 15, q = lane >> 4;
+    const int split = blockIdx.x % p.splits, bt = blockIdx.x / p.splits;
+    const int tile = bt % p.tiles, bj = bt / p.tiles;
+    const int b = bj / G.Hkv, j = bj % G.Hkv;
+    const T *kc = (const T *)p.Kc + (size_t)bj * G.spad * DH, *vc = (const T *)p.Vc + (size_t)bj * G.spad * DH;
+
+    frag qf[QT][NKB];
+#pragma unroll
+    for (int u = 0; u < QT; ++u) {
+        const int row = tile * (16 * QT) + 16 * u + rho;
+        const bool ok = row < G.g * p.A;
+        const int hg = ok ? row / p.A : 0, a = ok ? row - hg * p.A : 0;
+        const T *qr = (const T *)p.Q + (((size_t)b * G.Hq + j * G.g + hg) * p.A + a) * DH + KB * q;
+#pragma unroll
+        for (int s = 0; s < NKB; ++s) qf[u][s] = ok ? *(const frag *)(qr + 4 * KB * s) : frag{};
+    }
+    f32x4 o[QT][ND];
+    float m[QT], l[QT];
+#pragma unroll
+    for (int u = 0; u < QT; ++u) {
+#pragma unroll
+        for (int d = 0; d < ND; ++d) o[u][d] = f32x4{0.f, 0.f, 0.f, 0.f};
+        m[u] = -INFINITY;
+        l[u] = 0.f;
+    }
+
+    const int n_groups = (p.kv_len + 31) / 32;
+    const int g0 = split * p.groups_per_split, g1 = min(n_groups, g0 + p.groups_per_split);
+    // key of row i of 16-key group h: fp32 in order; bf16 so that register pairs of the two groups are 8 keys in a row
+    auto key_of = [&](int h, int i) { return F32 ? 16 * h + i : 8 * (i >> 2) + 4 * h + (i & 3); };
+    frag kf[2][NKB];
+    auto load_k = [&](int g) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int s = 0; s < NKB; ++s)
+                kf[h][s] = *(const frag *)(kc + (size_t)(32 * g + key_of(h, rho)) * DH + 4 * KB * s + KB * q);
+    };
+    if (g0 + wave < g1) load_k(g0 + wave);
+    for (int g = g0 + wave; g < g1; g += TW) {
+        frag vf[ND][NV];
+        const T *vt = vc + (size_t)(g >> 1) * (FC_VTILE * DH) + 32 * (g & 1);
+#pragma unroll
+        for (int d = 0; d < ND; ++d)
+#pragma unroll
+            for (int h = 0; h < NV; ++h)
+                vf[d][h] = *(const frag *)(vt + (16 * d + rho) * FC_VTILE + (F32 ? 16 * h : 0) + KB * q);
+        f32x4 s[QT][2];
+#pragma unroll
+        for (int u = 0; u < QT; ++u)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                s[u][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int k = 0; k < NKB; ++k) s[u][h] = O::mfma(kf[h][k], qf[u][k], s[u][h]);
+            }
+        if (g + TW < g1) load_k(g + TW);  // the next group's keys travel behind the softmax and the output products
+        if (32 * g + 32 > p.kv_len) {
+            // keys past the end may hold anything: no score, and zero values so that 0 * V stays 0
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (32 * g + key_of(h, 4 * q + r) >= p.kv_len) {
+#pragma unroll
+                        for (int u = 0; u < QT; ++u) s[u][h][r] = -INFINITY;
+                    }
+#pragma unroll
+            for (int d = 0; d < ND; ++d)
+#pragma unroll
+                for (int h = 0; h < NV; ++h)
+#pragma unroll
+                    for (int e = 0; e < KB; ++e)
+                        if (32 * g + (F32 ? 16 * h : 0) + KB * q + e >= p.kv_len) vf[d][h][e] = {};
+        }
+#pragma unroll
+        for (int u = 0; u < QT; ++u) {
+            float mx = s[u][0][0];
+#pragma unroll
+            for (int r = 1; r < 8; ++r) mx = fmaxf(mx, s[u][r >> 2][r & 3]);
+            mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+            const float m_new = fmaxf(m[u], mx);
+            const float alpha = __builtin_amdgcn_exp2f((m[u] - m_new) * p.c);
+            m[u] = m_new;
+            l[u] *= alpha;
+            float pr[8];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                pr[r] = __builtin_amdgcn_exp2f((s[u][r >> 2][r & 3] - m_new) * p.c);
+                l[u] += pr[r];
+            }
+#pragma unroll
+            for (int d = 0; d < ND; ++d)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o[u][d][r] *= alpha;
+            frag pf[NV];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                if constexpr (F32) pf[r >> 2][r & 3] = pr[r];
+                else pf[0][r] = (__bf16)pr[r];
+            }
+#pragma unroll
+            for (int d = 0; d < ND; ++d)
+#pragma unroll
+                for (int h = 0; h < NV; ++h) o[u][d] = O::mfma(vf[d][h], pf[h], o[u][d]);
+        }
+    }
+
+    // ---- merge the eight waves through LDS
+#pragma unroll
+    for (int u = 0; u < QT; ++u) {
+        float lu = l[u];
+        lu += __shfl_xor(lu, 16, 64);
+        lu += __shfl_xor(lu, 32, 64);
+        float *row = xo + ((size_t)wave * QT * 16 + 16 * u + rho) * ROW + 4 * q;
+#pragma unroll
+        for (int d = 0; d < ND; ++d) *(f32x4 *)(row + 16 * d) = o[u][d];
+        if (q == 0) {
+            float *ml = xml + ((size_t)wave * QT * 16 + 16 * u + rho) * 2;
+            ml[0] = m[u];
+            ml[1] = lu;
+        }
+    }
+    __syncthreads();
+    for (int idx = tid; idx < QT * 16 * (DH / 4); idx += TW * 64) {
+        const int row = idx / (DH / 4), d0 = 4 * (idx % (DH / 4));
+        float mm = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < TW; ++w) mm = fmaxf(mm, xml[(w * QT * 16 + row) * 2]);
+        float den = 0.f;
+        float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int w = 0; w < TW; ++w) {
+            const float *ml = xml + (w * QT * 16 + row) * 2;
+            const float k = __builtin_amdgcn_exp2f((ml[0] - mm) * p.c);
+            const float4 v = *(const float4 *)(xo + ((size_t)w * QT * 16 + row) * ROW + d0);
+            den += k * ml[1];
+            num.x += k * v.x;
+            num.y += k * v.y;
+            num.z += k * v.z;
+            num.w += k * v.w;
+        }
+        if (p.splits > 1) {
+            const size_t at = ((size_t)bt * p.splits + split) * (QT * 16) + row;
+            *(float4 *)(p.part_o + at * DH + d0) = num;
+            if (d0 == 0) *(float2 *)(p.part_ml + at * 2) = make_float2(mm, den);
+        } else {
+            attn_store_row4<T>(p, bj, tile * (16 * QT) + row, d0, make_float4(num.x / den, num.y / den, num.z / den, num.w / den));
+        }
+    }
+}
+
+// Merge of the key ranges: one workgroup per (sequence, kv head, tile), a thread per four output values.
+template <typename T, int DH, int QT>
+__global__ __launch_bounds__(256) void k_attn_tile_merge(AttnTileArgs p)
+{
+    const int bt = blockIdx.x / (QT * DH / 64), idx = (blockIdx.x % (QT * DH / 64)) * 256 + threadIdx.x;
+    const int row = idx / (DH / 4), d0 = 4 * (idx % (DH / 4));
+    const size_t at = (size_t)bt * p.splits * (QT * 16) + row;
+    float mm = -INFINITY, den = 0.f;
+    float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int s0 = 0; s0 < p.splits; s0 += 4) {  // four ranges' loads in flight together
+        float2 ml[4];
+        float4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const size_t as = at + (size_t)min(s0 + u, p.splits - 1) * (QT * 16);
+            ml[u] = *(const float2 *)(p.part_ml + as * 2);
+            v[u] = *(const float4 *)(p.part_o + as * DH + d0);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (s0 + u >= p.splits) break;
+            const float m_new = fmaxf(mm, ml[u].x);
+            const float k0 = __builtin_amdgcn_exp2f((mm - m_new) * p.c), k1 = __builtin_amdgcn_exp2f((ml[u].x - m_new) * p.c);
+            mm = m_new;
+            den = den * k0 + ml[u].y * k1;
+            num.x = num.x * k0 + v[u].x * k1;
+            num.y = num.y * k0 + v[u].y * k1;
+            num.z = num.z * k0 + v[u].z * k1;
+            num.w = num.w * k0 + v[u].w * k1;
+        }
+    }
+    attn_store_row4<T>(p, bt / p.tiles, (bt % p.tiles) * (16 * QT) + row, d0,
+                       make_float4(num.x / den, num.y / den, num.z / den, num.w / den));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -256,54 +649,6 @@ __global__ __launch_bounds__(256) void k_rmsnorm_bf16_row(const uint16_t *X, con
 }
 
 // ---------------------------------------------------------------------------------------------
-// Linear layer, block = (4 rows, 64 output columns); each wave owns every 4th column of the block and
-// runs the dot products with lanes along the hidden dimension.  MODE 0: out = aux + x w^T
-// (aux = residual or nullptr); MODE 1: out = silu(x w^T) * (x aux^T) (aux = second weight matrix).
-constexpr int LG_ROWS = 4;
-
-template <typename T, int MODE>
-__global__ __launch_bounds__(256) void k_linear_generic(const T *__restrict__ X, const T *__restrict__ W,
-                                                        const T *aux, int M, int K, int N, T *out)
-{
-    const int m0 = blockIdx.x * LG_ROWS, n0 = blockIdx.y * 64;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int c = wave; c < 64; c += 4) {
-        const int n = n0 + c;
-        if (n >= N) break;
-        const T *w = W + (size_t)n * K;
-        const T *w2 = MODE == 1 ? aux + (size_t)n * K : nullptr;
-        float acc[LG_ROWS], acc2[LG_ROWS];
-#pragma unroll
-        for (int r = 0; r < LG_ROWS; ++r) acc[r] = acc2[r] = 0.f;
-        for (int k = lane; k < K; k += 64) {
-            const float wv = fc_to_float(w[k]);
-            const float wv2 = MODE == 1 ? fc_to_float(w2[k]) : 0.f;
-#pragma unroll
-            for (int r = 0; r < LG_ROWS; ++r)
-                if (m0 + r < M) {
-                    const float xv = fc_to_float(X[(size_t)(m0 + r) * K + k]);
-                    acc[r] += wv * xv;
-                    if (MODE == 1) acc2[r] += wv2 * xv;
-                }
-        }
-#pragma unroll
-        for (int r = 0; r < LG_ROWS; ++r) {
-            const float a = wave_sum(acc[r]);
-            const float b = MODE == 1 ? wave_sum(acc2[r]) : 0.f;
-            if (lane == 0 && m0 + r < M) {
-                const size_t o = (size_t)(m0 + r) * N + n;
-                float y;
-                if (MODE == 1)
-                    y = a / (1.0f + expf(-a)) * b;
-                else
-                    y = aux ? a + fc_to_float(aux[o]) : a;
-                out[o] = fc_from_float<T>(y);
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------------------------
 // KV drift diagnostic: cosine similarity over the head dimension between rows of the cache and an
 // earlier snapshot of the same rows in the plain [B][Hkv][rows][Dh] layout.  One wave per
 // (sequence, kv head, row); lanes run along the head dimension.
@@ -373,42 +718,6 @@ hipError_t fc_launch_copy_rows(const FcGeom &G, int dtype, void *k_layer, void *
     return hipGetLastError();
 }
 
-hipError_t fc_launch_project_generic(const FcGeom &G, int dtype, const void *x, const void *w,
-                                     const void *bias, const int32_t *pos, int win_start, int A,
-                                     void *q_out, void *k_layer, void *v_layer, hipStream_t s)
-{
-    const int M = G.B * A;
-    dim3 grid((M + PG_ROWS - 1) / PG_ROWS, G.Hq + 2 * G.Hkv);
-    if (dtype == FC_F32)
-        k_project_generic<float><<<grid, dim3(256), 0, s>>>(G, (const float *)x, (const float *)w,
-                                                            (const float *)bias, pos, win_start, A,
-                                                            (float *)q_out, (float *)k_layer,
-                                                            (float *)v_layer);
-    else
-        k_project_generic<bf16_t><<<grid, dim3(256), 0, s>>>(G, (const bf16_t *)x, (const bf16_t *)w,
-                                                             (const bf16_t *)bias, pos, win_start, A,
-                                                             (bf16_t *)q_out, (bf16_t *)k_layer,
-                                                             (bf16_t *)v_layer);
-    return hipGetLastError();
-}
-
-hipError_t fc_launch_attention_generic(const FcGeom &G, int dtype, const void *q, const void *k_layer,
-                                       const void *v_layer, const int32_t *pos, int A, int kv_len,
-                                       void *out, hipStream_t s)
-{
-    dim3 grid(A, G.Hq, G.B);
-    if (dtype == FC_F32)
-        k_attention_generic<float><<<grid, dim3(256), 0, s>>>(G, (const float *)q, (const float *)k_layer,
-                                                              (const float *)v_layer, pos, A, kv_len,
-                                                              (float *)out);
-    else
-        k_attention_generic<bf16_t><<<grid, dim3(256), 0, s>>>(G, (const bf16_t *)q,
-                                                               (const bf16_t *)k_layer,
-                                                               (const bf16_t *)v_layer, pos, A, kv_len,
-                                                               (bf16_t *)out);
-    return hipGetLastError();
-}
-
 hipError_t fc_launch_rmsnorm(int dtype, const void *x, const void *weight, float eps, int rows, int d,
                              void *out, hipStream_t s)
 {
@@ -429,23 +738,146 @@ hipError_t fc_launch_rmsnorm(int dtype, const void *x, const void *weight, float
     return hipGetLastError();
 }
 
-template <typename T>
-static void launch_linear_t(int mode, const void *x, const void *w, const void *aux, int M, int K, int N,
-                            void *out, hipStream_t s)
+namespace {
+
+template <typename T, int NT, int MT, int EPI>
+hipError_t launch_tile_shape(TileArgs a, int n_tiles, hipStream_t s)
 {
-    const dim3 grid((unsigned)((M + LG_ROWS - 1) / LG_ROWS), (unsigned)((N + 63) / 64));
-    if (mode == FC_LIN_GATE_UP)
-        k_linear_generic<T, 1><<<grid, dim3(256), 0, s>>>((const T *)x, (const T *)w, (const T *)aux, M, K, N, (T *)out);
-    else
-        k_linear_generic<T, 0><<<grid, dim3(256), 0, s>>>((const T *)x, (const T *)w, (const T *)aux, M, K, N, (T *)out);
+    constexpr size_t LDS = tile_lds(NT, MT);
+    static hipError_t attr = hipFuncSetAttribute((const void *)k_linear_tile<T, NT, MT, EPI>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
+    if (attr != hipSuccess) return attr;
+    a.n_blocks = (n_tiles + NT - 1) / NT;
+    const int64_t grid = (int64_t)a.n_blocks * ((a.M + 16 * MT - 1) / (16 * MT));
+    if (grid > INT32_MAX) return hipErrorInvalidValue;
+    k_linear_tile<T, NT, MT, EPI><<<dim3((unsigned)grid), dim3(TW * 64), LDS, s>>>(a);
+    return hipGetLastError();
 }
 
-hipError_t fc_launch_linear_generic(int dtype, int mode, const void *x, const void *w, const void *aux,
-                                    int M, int K, int N, void *out, hipStream_t s)
+// Tile choice: as many window rows per workgroup as there are (up to 64: the weights are then read once per
+// 64 rows), and two weight tiles once that still leaves a workgroup for every compute unit.  The
+// vocabulary takes two always: its parts are workspace.
+template <typename T, int EPI>
+hipError_t launch_tile_t(const TileArgs &a, int n_tiles, hipStream_t s)
 {
-    if (dtype == FC_F32)
-        launch_linear_t<float>(mode, x, w, aux, M, K, N, out, s);
-    else
-        launch_linear_t<bf16_t>(mode, x, w, aux, M, K, N, out, s);
+    const int64_t mc = a.M <= 32 ? 1 : (a.M + 63) / 64;
+    const bool two = EPI == EPI_VOCAB || (n_tiles + 1) / 2 * mc >= 256;
+    if (a.M <= 16) return two ? launch_tile_shape<T, 2, 1, EPI>(a, n_tiles, s) : launch_tile_shape<T, 1, 1, EPI>(a, n_tiles, s);
+    if (a.M <= 32) return two ? launch_tile_shape<T, 2, 2, EPI>(a, n_tiles, s) : launch_tile_shape<T, 1, 2, EPI>(a, n_tiles, s);
+    return two ? launch_tile_shape<T, 2, 4, EPI>(a, n_tiles, s) : launch_tile_shape<T, 1, 4, EPI>(a, n_tiles, s);
+}
+
+template <int EPI>
+hipError_t launch_tile(int dtype, const TileArgs &a, int n_tiles, hipStream_t s)
+{
+    return dtype == FC_F32 ? launch_tile_t<float, EPI>(a, n_tiles, s) : launch_tile_t<bf16_t, EPI>(a, n_tiles, s);
+}
+
+template <typename T, int DH, int QT>
+hipError_t launch_attn_tile(const AttnTileArgs &a, hipStream_t s)
+{
+    constexpr size_t LDS = (size_t)TW * QT * 16 * (DH + AT_STRIDE + 2) * sizeof(float);
+    static hipError_t attr = hipFuncSetAttribute((const void *)k_attn_tile<T, DH, QT>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
+    if (attr != hipSuccess) return attr;
+    const int64_t bt = (int64_t)a.G.B * a.G.Hkv * a.tiles;
+    if (bt * a.splits > (1 << 30) || bt * (QT * DH / 64) > (1 << 30)) return hipErrorInvalidValue;
+    k_attn_tile<T, DH, QT><<<dim3((unsigned)(bt * a.splits)), dim3(TW * 64), LDS, s>>>(a);
+    if (a.splits > 1) k_attn_tile_merge<T, DH, QT><<<dim3((unsigned)(bt * (QT * DH / 64))), dim3(256), 0, s>>>(a);
     return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_attn_tile_t(int qt, const AttnTileArgs &a, hipStream_t s)
+{
+    if (a.G.Dh == 64) return qt == 2 ? launch_attn_tile<T, 64, 2>(a, s) : launch_attn_tile<T, 64, 1>(a, s);
+    if constexpr (sizeof(T) == 4) return qt == 1 ? launch_attn_tile<T, 128, 1>(a, s) : hipErrorInvalidValue;
+    return hipErrorInvalidValue;  // bf16 with head_dim 128 has its own kernel
+}
+
+}  // namespace
+
+hipError_t fc_launch_project_tile(const FcGeom &G, const double *inv_freq, int dtype, const void *x, const void *w,
+                                  const void *bias, const int32_t *pos, int win_start, int A, void *q_out, void *k_layer,
+                                  void *v_layer, hipStream_t s)
+{
+    TileArgs a;
+    memset(&a, 0, sizeof a);
+    a.X = x;
+    a.W = w;
+    a.aux = bias;
+    a.out = q_out;
+    a.M = G.B * A;
+    a.K = G.d;
+    a.N = (G.Hq + 2 * G.Hkv) * G.Dh;
+    a.G = G;
+    a.pos = pos;
+    a.win_start = win_start;
+    a.A = A;
+    a.Kc = k_layer;
+    a.Vc = v_layer;
+    memcpy(a.inv_freq, inv_freq, sizeof a.inv_freq);
+    return launch_tile<EPI_QKV>(dtype, a, a.N / 16, s);
+}
+
+hipError_t fc_launch_linear_tile(int dtype, int mode, const void *x, const void *w, const void *aux, int M, int K, int N,
+                                 void *out, hipStream_t s)
+{
+    TileArgs a;
+    memset(&a, 0, sizeof a);
+    a.X = x;
+    a.W = w;
+    a.out = out;
+    a.M = M;
+    a.K = K;
+    a.N = N;
+    a.G.Dh = 64;  // not used
+    if (mode == FC_LIN_GATE_UP) {
+        a.W2 = aux;
+        return launch_tile<EPI_GATE_UP>(dtype, a, (N + 7) / 8, s);
+    }
+    a.aux = aux;
+    return launch_tile<EPI_RESIDUAL>(dtype, a, (N + 15) / 16, s);
+}
+
+hipError_t fc_launch_lmhead_tile(int dtype, const void *x, const void *w, int M, int K, int V, const FcArgmaxPart &am,
+                                 hipStream_t s)
+{
+    TileArgs a;
+    memset(&a, 0, sizeof a);
+    a.X = x;
+    a.W = w;
+    a.M = M;
+    a.K = K;
+    a.N = V;
+    a.G.Dh = 64;  // not used
+    a.am = am;
+    return launch_tile<EPI_VOCAB>(dtype, a, (V + 15) / 16, s);
+}
+
+hipError_t fc_launch_attention_tile(const FcGeom &G, const FcAttnPlan &pl, int dtype, const void *q, const void *k_layer,
+                                    const void *v_layer, const int32_t *pos, int A, int kv_len, void *out,
+                                    void *workspace, hipStream_t s)
+{
+    AttnTileArgs a;
+    memset(&a, 0, sizeof a);
+    a.Q = q;
+    a.Kc = k_layer;
+    a.Vc = v_layer;
+    a.pos = pos;
+    a.out = out;
+    a.G = G;
+    a.A = A;
+    a.kv_len = kv_len;
+    a.tiles = (int)(((int64_t)G.g * A + 16 * pl.tiles_per_wg - 1) / (16 * pl.tiles_per_wg));
+    a.splits = pl.splits;
+    a.groups_per_split = pl.keys_per_split / 32;
+    a.c = G.scale * 1.4426950408889634f;
+    if (pl.splits > 1) {
+        if (!workspace) return hipErrorInvalidValue;
+        a.part_o = (float *)workspace;
+        a.part_ml = a.part_o + (size_t)G.B * G.Hkv * a.tiles * pl.splits * 16 * pl.tiles_per_wg * G.Dh;
+    }
+    return dtype == FC_F32 ? launch_attn_tile_t<float>(pl.tiles_per_wg, a, s)
+                           : launch_attn_tile_t<bf16_t>(pl.tiles_per_wg, a, s);
 }

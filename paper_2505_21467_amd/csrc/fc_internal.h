@@ -66,11 +66,11 @@ __host__ __device__ inline size_t fc_v_index(const FcGeom &G, int b, int j, int 
 
 // Launch plan of the split-KV attention (host, pure function of the shape).
 struct FcAttnPlan {
-    int kind;            // 0 = generic kernel (no workspace), 1 = MFMA split-KV
+    int kind;            // 0 = fp32 / head_dim 64 kernel, 1 = bf16 head_dim 128 split-KV
     int splits;          // key ranges per (sequence, kv head); every one is non-empty
     int splits_bound;    // upper bound of `splits` over all kv_len <= the given one (workspace sizing)
-    int keys_per_split;  // multiple of 64
-    int row_tiles;       // 32-row tiles of the flattened (head-in-group, a) rows per (b, kv head)
+    int keys_per_split;  // multiple of 64 (kind 0: of 32)
+    int row_tiles;       // 32-row (kind 0: 16-row) tiles of the flattened (head-in-group, a) rows per (b, kv head)
     int tiles_per_wg;    // row tiles handled by one workgroup
     int waves;           // waves per workgroup (tiles_per_wg or twice that)
 };
@@ -80,12 +80,12 @@ size_t fc_plan_workspace(const fc_config &cfg, const FcAttnPlan &p, int A);
 // Kernel launchers (defined in the .hip kernel files).  All return hipGetLastError() after launch.
 hipError_t fc_launch_copy_rows(const FcGeom &G, int dtype, void *k_layer, void *v_layer, void *k_rows,
                                void *v_rows, int start, int rows, bool to_cache, hipStream_t s);
-hipError_t fc_launch_project_generic(const FcGeom &G, int dtype, const void *x, const void *w,
-                                     const void *bias, const int32_t *pos, int win_start, int A,
-                                     void *q_out, void *k_layer, void *v_layer, hipStream_t s);
-hipError_t fc_launch_attention_generic(const FcGeom &G, int dtype, const void *q, const void *k_layer,
-                                       const void *v_layer, const int32_t *pos, int A, int kv_len,
-                                       void *out, hipStream_t s);
+hipError_t fc_launch_project_tile(const FcGeom &G, const double *inv_freq, int dtype, const void *x, const void *w,
+                                  const void *bias, const int32_t *pos, int win_start, int A,
+                                  void *q_out, void *k_layer, void *v_layer, hipStream_t s);
+hipError_t fc_launch_attention_tile(const FcGeom &G, const FcAttnPlan &p, int dtype, const void *q, const void *k_layer,
+                                    const void *v_layer, const int32_t *pos, int A, int kv_len,
+                                    void *out, void *workspace, hipStream_t s);
 bool fc_project_mfma_supported(const fc_config &cfg, int A);
 hipError_t fc_launch_project_mfma(const FcGeom &G, const double *inv_freq, const void *x, const void *w, const void *bias,
                                   const int32_t *pos, int win_start, int A, void *q_out,
@@ -124,9 +124,9 @@ __host__ __device__ inline void fc_argmax_merge(float &mx, int &arg, float &sm, 
 }
 hipError_t fc_launch_rmsnorm(int dtype, const void *x, const void *weight, float eps, int rows, int d,
                              void *out, hipStream_t s);
-// Plain-ALU linear layer for any dtype and shape.  FC_LIN_RESIDUAL: out = aux + x w^T (aux = residual
+// Linear layer for any dtype and shape.  FC_LIN_RESIDUAL: out = aux + x w^T (aux = residual
 // or nullptr); FC_LIN_GATE_UP: out = silu(x w^T) * (x aux^T) (aux = up matrix).
-hipError_t fc_launch_linear_generic(int dtype, int mode, const void *x, const void *w, const void *aux,
+hipError_t fc_launch_linear_tile(int dtype, int mode, const void *x, const void *w, const void *aux,
                                     int M, int K, int N, void *out, hipStream_t s);
 // Launch plan of the weight-streaming linear kernels (host, pure function of the shape).
 struct FcSkinnyPlan {
@@ -144,11 +144,11 @@ size_t fc_skinny_workspace(const FcSkinnyPlan &p);
 hipError_t fc_launch_linear_skinny(const FcSkinnyPlan &pl, int mode, const void *x, const void *w,
                                    const void *w2, const void *res, int M, int K, int N, void *out,
                                    void *workspace, hipStream_t s, const FcArgmaxPart *am = nullptr);
-// Unmasking step: plain vocabulary projection (any dtype / shape), merge of the vocabulary parts, and
+// Unmasking step: vocabulary projection for any dtype and shape, merge of the vocabulary parts, and
 // the confidence-ranked fill.
-hipError_t fc_launch_lmhead_generic(int dtype, const void *x, const void *w, int M, int K, int V,
-                                    const FcArgmaxPart &am, hipStream_t s);
-#define FC_LMHEAD_GENERIC_CHUNK 256  // vocabulary entries per part of the plain kernel
+hipError_t fc_launch_lmhead_tile(int dtype, const void *x, const void *w, int M, int K, int V,
+                                 const FcArgmaxPart &am, hipStream_t s);
+#define FC_LMHEAD_TILE_PART 32  // vocabulary entries per part of that kernel
 hipError_t fc_launch_lmhead_reduce(const FcArgmaxPart &am, int parts, int M, int32_t *tok, float *conf,
                                    hipStream_t s);
 #define FC_UNMASK_MAX_ROWS 8192

@@ -14,50 +14,6 @@
 
 namespace {
 
-__device__ __forceinline__ float wave_sum_f(float v)
-{
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
-// Plain vocabulary projection, block = (row, FC_LMHEAD_GENERIC_CHUNK vocabulary entries); wave w owns
-// entries w, w + 4, ... of the chunk (ascending), lanes run along the hidden dimension.
-template <typename T>
-__global__ __launch_bounds__(256) void k_lmhead_generic(const T *__restrict__ X, const T *__restrict__ W, int M,
-                                                        int K, int V, FcArgmaxPart am)
-{
-    __shared__ float s_mx[4], s_sm[4];
-    __shared__ int s_arg[4];
-    const int m = blockIdx.x, part = blockIdx.y;
-    const int v0 = part * FC_LMHEAD_GENERIC_CHUNK;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const T *x = X + (size_t)m * K;
-    float mx = -INFINITY, sm = 0.f;
-    int arg = 0;
-    for (int c = wave; c < FC_LMHEAD_GENERIC_CHUNK; c += 4) {
-        const int v = v0 + c;
-        if (v >= V) break;
-        const T *w = W + (size_t)v * K;
-        float acc = 0.f;
-        for (int k = lane; k < K; k += 64) acc += fc_to_float(w[k]) * fc_to_float(x[k]);
-        const float z = wave_sum_f(acc);
-        fc_argmax_merge(mx, arg, sm, z, v, 1.0f);
-    }
-    if (lane == 0) {
-        s_mx[wave] = mx;
-        s_sm[wave] = sm;
-        s_arg[wave] = arg;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w2 = 1; w2 < 4; ++w2) fc_argmax_merge(mx, arg, sm, s_mx[w2], s_arg[w2], s_sm[w2]);
-        const size_t at = (size_t)part * M + m;
-        am.mx[at] = mx;
-        am.arg[at] = arg;
-        am.sm[at] = sm;
-    }
-}
-
 // Merge of the vocabulary parts of one row: one workgroup per row.
 __global__ __launch_bounds__(256) void k_lmhead_reduce(FcArgmaxPart am, int parts, int M, int32_t *tok, float *conf)
 {
@@ -493,17 +449,6 @@ hipError_t fc_launch_gather_rows(const void *table, int64_t R, int row_bytes, co
                                  hipStream_t s)
 {
     k_gather_rows<<<dim3((unsigned)n), dim3(256), 0, s>>>((const uint4 *)table, R, row_bytes / 16, idx, (uint4 *)out);
-    return hipGetLastError();
-}
-
-hipError_t fc_launch_lmhead_generic(int dtype, const void *x, const void *w, int M, int K, int V,
-                                    const FcArgmaxPart &am, hipStream_t s)
-{
-    const dim3 grid((unsigned)M, (unsigned)((V + FC_LMHEAD_GENERIC_CHUNK - 1) / FC_LMHEAD_GENERIC_CHUNK));
-    if (dtype == FC_F32)
-        k_lmhead_generic<float><<<grid, dim3(256), 0, s>>>((const float *)x, (const float *)w, M, K, V, am);
-    else
-        k_lmhead_generic<bf16_t><<<grid, dim3(256), 0, s>>>((const bf16_t *)x, (const bf16_t *)w, M, K, V, am);
     return hipGetLastError();
 }
 

@@ -1,0 +1,70 @@
+"""GPU parity of the kernels for fp32 caches and for the bf16 shapes outside the streaming and tiled-GEMM
+kernels, at the edges of their tiles: against the CPU oracle on the same inputs."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import fc_oracle as orc
+from paper_2505_21467_amd import binding as fc
+from paper_2505_21467_amd import inputs
+from tests.harness import GpuLayerCache, OracleLayerCache, assert_close
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("dtype,B,d,Hq,Hkv,Dh,L,A", [
+    ("f32", 1, 8, 1, 1, 64, 0, 1),          # the smallest call: one key, one row, half a block of the hidden dimension
+    ("f32", 1, 40, 2, 1, 64, 2000, 3),      # one row tile, keys cut into ranges, ragged last group
+    ("f32", 2, 264, 3, 1, 128, 1000, 6),    # the same with rows of 128: 18 query rows in two tiles
+    ("f32", 3, 72, 8, 4, 64, 70, 83),       # 166 rows per kv head: two tiles per workgroup, the last one ragged
+    ("f32", 3, 40, 12, 1, 128, 33, 100),    # 300 window rows: two weight tiles and 64 rows per workgroup
+    ("bf16", 1, 200, 4, 2, 64, 1777, 5),    # bf16: permuted key rows, ranges, ragged last group
+    ("bf16", 4, 136, 8, 8, 64, 31, 33),     # bf16, two tiles per workgroup, 132 rows
+])
+def test_step_matches_oracle(dtype, B, d, Hq, Hkv, Dh, L, A):
+    print("[case]", dtype, B, d, Hq, Hkv, Dh, L, A, flush=True)
+    w = inputs.Workload("t", dtype, B, d, Hq, Hkv, Dh, L, A)
+    S = L + A
+    g = GpuLayerCache(dtype, B, d, Hq, Hkv, Dh, S + 5, max_rows=A, fill=float("nan"))  # keys past kv_len are not numbers
+    o = OracleLayerCache(dtype, B, d, Hq, Hkv, Dh, S + 5)
+    if L:
+        K, V = inputs.kv_fill(w, 3, L)
+        g.write_rows(0, K, V, 0)
+        o.write_rows(K, V, 0)
+    W, b, X = inputs.weights(w, 3), inputs.bias(w, 3), inputs.hidden_states(w, 3, A)
+    pos = inputs.window_positions(B, L, A)
+    if A > 2:
+        pos[:, 1] = -1  # a padded row: nothing stored; its key is then whatever the cache held
+        K1 = torch.zeros((B, Hkv, 1, Dh), dtype=g.tdt)
+        g.write_rows(0, K1, K1, L + 1)
+    Qg, Og = g.step(0, X, W, b, L, S, pos=pos)
+    Qo, Oo = o.step(X, W, b, L, S, pos=pos)
+    assert_close(Qg, Qo, dtype, "Q")
+    assert_close(Og, Oo, dtype, "O")
+    Kg, Vg = g.read_rows(0, 0, S)
+    assert_close(Kg, o.Kc[:, :, :S], dtype, "K")
+    assert_close(Vg, o.Vc[:, :, :S], dtype, "V")
+    # without the space for key ranges the same call runs uncut
+    Qd = torch.from_numpy(Qg).to(g.tdt).to(DEV)
+    out = torch.full((B, A, Hq * Dh), float("nan"), dtype=g.tdt, device=DEV)
+    fc.fc_active_attention(g.handle, 0, Qd, A, S, pos.to(DEV), out, None, 0)
+    torch.cuda.synchronize()
+    assert_close(inputs.as_oracle(out), Oo, dtype, "O uncut")
+    g.close()
+
+
+@pytest.mark.parametrize("dtype,M,K,N", [
+    ("f32", 1, 8, 1), ("f32", 33, 24, 15), ("f32", 300, 40, 1702), ("bf16", 17, 8, 33), ("bf16", 65, 40, 4100),
+])
+def test_linear_layers_match_oracle(dtype, M, K, N):
+    print("[case]", dtype, M, K, N, flush=True)
+    x, r = inputs.normal(2, "x", (M, K), 1.0, dtype), inputs.normal(2, "r", (M, N), 1.0, dtype)
+    w, w2 = inputs.normal(2, "w", (N, K), 0.05, dtype), inputs.normal(2, "w2", (N, K), 0.05, dtype)
+    xd, wd, w2d, rd = (t.to(DEV) for t in (x, w, w2, r))
+    xo, wo, w2o = (inputs.as_oracle(t) for t in (x, w, w2))
+    out = torch.full((M, N), float("nan"), dtype=xd.dtype, device=DEV)
+    fc.fc_linear_residual(dtype, xd, wd, rd, M, K, N, out, None, 0)
+    assert_close(inputs.as_oracle(out), orc.linear_residual(xo, wo, inputs.as_oracle(r), dtype), dtype, "linear")
+    fc.fc_ffn_gate_up(dtype, xd, wd, w2d, M, K, N, out, None, 0)
+    assert_close(inputs.as_oracle(out), orc.ffn_gate_up(xo, wo, w2o, dtype), dtype, "gate_up")
