@@ -9,6 +9,9 @@ import os
 
 import torch
 
+_raw_stream = torch._C._cuda_getCurrentRawStream
+_current_device = torch._C._cuda_getDevice
+
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libfreecache.so")
 
@@ -137,15 +140,18 @@ def _check(status):
 
 def _ptr(t):
     """Device (or raw) pointer of a tensor / int / None."""
-    if t is None:
-        return None
-    if isinstance(t, int):
+    if t is None or isinstance(t, int):
         return t
     return t.data_ptr()
 
 
 def _stream(stream):
+    """hipStream_t of a torch stream / int; None is the current stream of the current device."""
     if stream is None:
+        # The raw handle, without the Stream object that torch.cuda.current_stream() builds on every call
+        # (2.7 us of a 14 us tiny step, twice).
+        if torch.cuda.is_initialized():
+            return _raw_stream(_current_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
