@@ -25,7 +25,7 @@
 // 128-row shapes (four multiplying waves) therefore carry four more waves that do nothing but issue
 // the loads; in the 256-row shapes (two multiplying waves per SIMD) every wave issues its share, a
 // quarter at a time between its multiplies.
-#include <stdlib.h>
+#include <math.h>
 #include <string.h>
 
 #include "fc_device.h"
@@ -54,7 +54,7 @@ struct GemmArgs {
     // The part of the problem this launch covers (a problem may be cut into two launches with different
     // tile shapes, see launch_pieces): slabs [slot_base, slot_base + slots_here), rows [m_base, m_end).
     int slot_base, slots_here, m_base, m_end;
-    double log2_base_64;   // log2(rope_base) / 64
+    double rot1, rot8, rot16, rot32;  // rope_base^(-i/64), i = 1, 8, 16, 32
     // plain linear layers of the rest of the layer (EPI != 0)
     const uint16_t *W2;    // EPI 2: the up matrix [N][K] (W is the gate matrix)
     const uint16_t *res;   // EPI 1: residual [M][N] or nullptr
@@ -87,6 +87,244 @@ __device__ __forceinline__ void wait_stages(int k)
     else if (k == 2) wait_vmg<2 * PER, LGKM0>();
     else if (k == 1) wait_vmg<PER, LGKM0>();
     else wait_vmg<0, LGKM0>();
+}
+
+// silu(g) * u in fp32 (hardware exponential and reciprocal, one ulp each, in front of the rounding to bf16)
+__device__ __forceinline__ float silu_mul(float g, float u)
+{
+    return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(g * -1.4426950408889634f)) * u;
+}
+
+__device__ __forceinline__ uint4 pack8(const float (&y)[8])
+{
+    uint4 w;
+    w.x = (uint32_t)fc_bf16_bits(y[0]) | ((uint32_t)fc_bf16_bits(y[1]) << 16);
+    w.y = (uint32_t)fc_bf16_bits(y[2]) | ((uint32_t)fc_bf16_bits(y[3]) << 16);
+    w.z = (uint32_t)fc_bf16_bits(y[4]) | ((uint32_t)fc_bf16_bits(y[5]) << 16);
+    w.w = (uint32_t)fc_bf16_bits(y[6]) | ((uint32_t)fc_bf16_bits(y[7]) << 16);
+    return w;
+}
+
+// bytes of LDS a wave needs for its epilogue: 32 rows of NT sub-tiles in fp32, 16 bytes of padding each
+__host__ __device__ constexpr int epi_bytes(int NT) { return 32 * (NT * 128 + 16); }
+
+// The workgroup's bias goes to LDS at the very start: nothing else asks for it before the end, and a layer's bias
+// comes from HBM (2.5 us with the matrix core idle when the epilogue fetched it).  NPW pairs: the low values, then
+// the high ones; pairs (2 d, 2 d + 1) of all slabs laid end to end, from pair `first` on.  One wave calls this.
+constexpr int BIAS_LDS = 512;
+__device__ __forceinline__ void load_bias(const GemmArgs &p, unsigned char *dst, int first, int npw, int n_pairs, int lane)
+{
+    if (!p.bias) return;
+    for (int d0 = 0; d0 < npw; d0 += 64) {
+        const int d = d0 + lane;
+        if (d >= npw) break;
+        const bool high = d >= npw / 2;
+        const int pr = min(first + 2 * (high ? d - npw / 2 : d), n_pairs - 2);
+        const uint16_t *src = p.bias + (pr >> 6) * 128 + (pr & 63) + (high ? 64 : 0);
+        __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)src,
+                                         (void __attribute__((address_space(3))) *)(dst + d0 * 4), 4, 0, 0);
+    }
+}
+
+// Epilogue of a wave.  Lane (col, hi) of sub-tile i holds window row m_first + 32 i + col; register r of
+// sub-tile t is row 8 (r >> 2) + 4 hi + (r & 3) of the sub-tile.  Sub-tiles are, in units of 32 features of slab hs:
+// t for a whole slab (NT = 4), {half, half + 2} for a half slab (NT = 2); or (DEALT) 16 pairs each, the low rows in
+// registers 0..7 and the high rows in 8..15, starting with pair pair0 of all slabs laid end to end, nt of them.
+// Either way the tile is a row of "low" and a row of "high" values per window row; the two members of a pair
+// (rotary pair, gate and up product) have the same place in the two.
+//
+// The values go through LDS, 32 window rows at a time in the wave's own area: in the accumulator layout a
+// store instruction covers 16 bytes of 32 different rows (128 KB of a 256 x 256 tile took 7.6 us to leave),
+// read back as rows it covers 128 or 256 contiguous bytes.  The loop over eight-value pieces is not
+// unrolled: this code runs once per tile, and unrolled it costs more in instruction fetches than in work.
+template <int NT, int MW, int EPI, bool DEALT>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x16 (&acc)[MW][NT], unsigned char *area,
+                                              const uint16_t *bias_low, const uint16_t *bias_high, int hs, int half, int pair0,
+                                              int nt, int m_first, int lane, int kpart)
+{
+    constexpr int PITCH = NT * 128 + 16;         // bytes per window row: low values, high values, padding
+    constexpr int HIGH = NT * 64;                // offset of the high values
+    const FcGeom &G = p.G;
+    const int col = lane & 31, hi = lane >> 5;
+    const int first_v = G.Hq + G.Hkv;            // EPI 0: first value slab
+#pragma unroll
+    for (int i = 0; i < MW; ++i) {
+        const int m_i = m_first + 32 * i;
+        // EPI 0: sequence, window row and position of row m_i + col (pp < 0: padded or past the end)
+        int b_l = 0, a_l = 0, pp_l = -1;
+        if (EPI == 0 && m_i + col < p.m_end) {
+            b_l = (m_i + col) / p.A;
+            a_l = m_i + col - b_l * p.A;
+            pp_l = p.pos ? p.pos[m_i + col] : p.win_start + a_l;
+            if (pp_l >= G.max_seq) pp_l = -1;
+        }
+        if (EPI == 0 && (DEALT || hs >= first_v)) {
+            // value rows go to the transposed tiles straight from the accumulators: lanes run along the keys
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const int pr = pair0 + 16 * t, hs_t = DEALT ? pr >> 6 : hs;
+                if (DEALT && (t >= nt || hs_t < first_v || hs_t >= p.n_slots)) continue;
+                if (pp_l < 0) continue;
+#pragma unroll
+                for (int rq = 0; rq < 4; ++rq) {
+                    const int d0 = DEALT ? (pr & 63) + 8 * (rq & 1) + 4 * hi + 64 * (rq >> 1)
+                                         : 32 * (NT == 4 ? t : half + 2 * t) + 8 * rq + 4 * hi;
+                    uint16_t *v = p.Vc + fc_v_index(G, b_l, hs_t - first_v, pp_l, d0);
+                    // (the same place in the wave's low or high values as below)
+                    const uint16_t *bs = DEALT ? (rq >= 2 ? bias_high : bias_low) + 16 * t + 8 * (rq & 1) + 4 * hi
+                                               : (t >= NT / 2 ? bias_high : bias_low) + 32 * (t % (NT / 2 > 0 ? NT / 2 : 1)) + 8 * rq + 4 * hi;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        v[e * FC_VTILE] = fc_bf16_bits(acc[i][t][4 * rq + e] + (p.bias ? fc_to_float(bf16_t{bs[e]}) : 0.f));
+                }
+            }
+            if (!DEALT) continue;
+        }
+        // ---- to LDS
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int rq = 0; rq < 4; ++rq) {
+                const bool high = DEALT ? rq >= 2 : t >= NT / 2;
+                const int at = (DEALT ? 64 * t + 32 * (rq & 1) : 128 * (t % (NT / 2 > 0 ? NT / 2 : 1)) + 32 * rq) + 16 * hi;
+                if (!DEALT || t < nt)
+                    *(float4 *)(area + col * PITCH + (high ? HIGH : 0) + at) =
+                        make_float4(acc[i][t][4 * rq], acc[i][t][4 * rq + 1], acc[i][t][4 * rq + 2], acc[i][t][4 * rq + 3]);
+            }
+        __builtin_amdgcn_wave_barrier();
+        wait_vmg<63, true>();
+        // ---- and back as rows, eight low and eight high values per lane and step
+        const int per_row = DEALT ? 2 * nt : NT * 2;  // pieces of eight pairs per row
+#pragma unroll 1
+        for (int u = lane; u < 32 * per_row; u += 64) {
+            const int row = u / per_row, s = u - row * per_row;
+            const int m = m_i + row;
+            int b = 0, a = 0, pp = 0;
+            if (EPI == 0) {
+                b = __shfl(b_l, row, 64);
+                a = __shfl(a_l, row, 64);
+                pp = __shfl(pp_l, row, 64);
+            }
+            float lo[8], hv[8];
+            const float *src = (const float *)(area + row * PITCH) + 8 * s;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                *(float4 *)(lo + 4 * h) = *(const float4 *)(src + 4 * h);
+                *(float4 *)(hv + 4 * h) = *(const float4 *)(src + HIGH / 4 + 4 * h);
+            }
+            if (m >= p.m_end) continue;
+            const int pr = pair0 + 8 * s;                     // DEALT: pair
+            const int lf = DEALT ? pr & 63 : NT == 4 ? 8 * s : 32 * half + 8 * s;  // first low feature of the slab
+            const int hs_t = DEALT ? pr >> 6 : hs;
+            if (DEALT && hs_t >= p.n_slots) continue;
+            if constexpr (EPI == 0) {
+                if (DEALT && hs_t >= first_v) continue;
+                const bool valid = pp >= 0;
+                if (p.bias) {
+                    union { uint4 u4; uint16_t h[8]; } bl, bh;
+                    bl.u4 = *(const uint4 *)(bias_low + 8 * s);
+                    bh.u4 = *(const uint4 *)(bias_high + 8 * s);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        lo[e] += fc_to_float(bf16_t{bl.h[e]});
+                        hv[e] += fc_to_float(bf16_t{bh.h[e]});
+                    }
+                }
+                // the angle is reduced to a fraction of a turn in double, then hardware sine / cosine
+                // (argument in turns)
+                double f = 0.15915494309189533576888;  // base^(-i/64) / (2 pi): turns per position of pair i
+                if (lf & 8) f *= p.rot8;
+                if (lf & 16) f *= p.rot16;
+                if (lf & 32) f *= p.rot32;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const double turns = (double)pp * f;
+                    const float ph = (float)(turns - rint(turns));
+                    const float c = __builtin_amdgcn_cosf(ph), sn = __builtin_amdgcn_sinf(ph);
+                    const float l = lo[e], h = hv[e];
+                    lo[e] = l * c - h * sn;
+                    hv[e] = h * c + l * sn;
+                    f *= p.rot1;
+                }
+                if (hs_t < G.Hq) {
+                    uint16_t *q = p.Q + (((size_t)b * G.Hq + hs_t) * p.A + a) * 128 + lf;
+                    *(uint4 *)q = valid ? pack8(lo) : make_uint4(0, 0, 0, 0);
+                    *(uint4 *)(q + 64) = valid ? pack8(hv) : make_uint4(0, 0, 0, 0);
+                } else if (valid) {
+                    uint16_t *k = p.Kc + fc_k_index(G, b, hs_t - G.Hq, pp, lf);
+                    *(uint4 *)k = pack8(lo);
+                    *(uint4 *)(k + 64) = pack8(hv);
+                }
+            } else if constexpr (EPI == 2) {
+                float y[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) y[e] = silu_mul(lo[e], hv[e]);
+                *(uint4 *)(p.out + (size_t)m * p.N + hs_t * 64 + lf) = pack8(y);
+            } else {
+                const size_t at = (size_t)m * p.N + (size_t)hs * 128 + lf;  // low features at `at`, high ones 64 on
+                if constexpr (EPI == 3) {
+                    float *o = p.part + (size_t)kpart * p.M * p.N + at;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        *(float4 *)(o + 4 * h) = *(float4 *)(lo + 4 * h);
+                        *(float4 *)(o + 64 + 4 * h) = *(float4 *)(hv + 4 * h);
+                    }
+                } else {
+                    if (p.res) {
+                        union { uint4 u4; uint16_t h[8]; } rl, rh;
+                        rl.u4 = *(const uint4 *)(p.res + at);
+                        rh.u4 = *(const uint4 *)(p.res + at + 64);
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            lo[e] += fc_to_float(bf16_t{rl.h[e]});
+                            hv[e] += fc_to_float(bf16_t{rh.h[e]});
+                        }
+                    }
+                    *(uint4 *)(p.out + at) = pack8(lo);
+                    *(uint4 *)(p.out + at + 64) = pack8(hv);
+                }
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        wait_vmg<63, true>();
+    }
+}
+
+// Vocabulary mode (EPI 4): lane (col, hi) holds, for window row col, the logits 32 t + 8 (r >> 2) + 4 hi + (r & 3)
+// of slab hs, ascending in (t, r), so that ties keep the smaller index; the other half is in lane ^ 32.  First the
+// maximum and its place, then the sum of exponentials against it.
+template <int MW>
+__device__ __forceinline__ void gemm_epilogue_vocab(const GemmArgs &p, const f32x16 (&acc)[MW][4], int hs, int m_first, int lane)
+{
+    const int col = lane & 31, hi = lane >> 5;
+#pragma unroll
+    for (int i = 0; i < MW; ++i) {
+        const int m = m_first + 32 * i + col;
+        float mx = -INFINITY, sm = 0.f;
+        int arg = 0;
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const bool more = acc[i][t][r] > mx;
+                mx = more ? acc[i][t][r] : mx;
+                arg = more ? 32 * t + 8 * (r >> 2) + (r & 3) : arg;
+            }
+        arg += hs * 128 + 4 * hi;
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sm += __builtin_amdgcn_exp2f((acc[i][t][r] - mx) * 1.4426950408889634f);
+        const float mx2 = __shfl_xor(mx, 32, 64), sm2 = __shfl_xor(sm, 32, 64);
+        const int arg2 = __shfl_xor(arg, 32, 64);
+        fc_argmax_merge(mx, arg, sm, mx2, arg2, sm2);
+        if (hi == 0 && m < p.m_end) {
+            const size_t at = (size_t)hs * p.M + m;
+            p.am.mx[at] = mx;
+            p.am.arg[at] = arg;
+            p.am.sm[at] = sm;
+        }
+    }
 }
 
 // Workgroup tile: NG head groups x WM row groups of waves (NW = NG * WM waves).  A wave owns MW
@@ -138,7 +376,6 @@ __global__ __launch_bounds__((NW + NL) * 64) void k_proj_gemm(GemmArgs p)
     static_assert((SLOTS - 1) * LBW < 64 && SLOTS >= 2 && SLOTS <= 4, "vmcnt range");
     static_assert(EPI == 0 || NG == 1 || DEALT, "the plain linear layers use one slab per workgroup");
     extern __shared__ __align__(1024) unsigned char smem[];
-    const FcGeom &G = p.G;
 
     // Workgroup -> (unit, row tile).  Workgroup ids that are equal modulo 8 land on the same XCD; the
     // tiles, ordered unit by unit, are dealt to the eight XCDs in equal contiguous runs, so the
@@ -228,6 +465,13 @@ __global__ __launch_bounds__((NW + NL) * 64) void k_proj_gemm(GemmArgs p)
             load_lds16g(src + goff[i], dst + (lw + NLW * i) * 1024);
         }
     };
+
+    // bias, behind the ring
+    constexpr int NPW = DEALT ? PPU : NSUB == 4 ? 64 * NG : 32;  // pairs per workgroup
+    constexpr int EPI_LDS = NW * epi_bytes(NT);
+    unsigned char *bias_area = smem + (SLOTS * STAGE > EPI_LDS ? SLOTS * STAGE : EPI_LDS);  // behind ring and staging
+    if (EPI == 0 && lw == 0)
+        load_bias(p, bias_area, DEALT ? PPU * unit : NSUB == 4 ? (p.slot_base + unit * NG) * 64 : hs * 64 + 32 * half, NPW, n_pairs, lane);
 
     // ---- operand read offsets inside a stage (bytes): row `col` of a 32-row sub-tile, k-step kk
     uint32_t foff[NKK];
@@ -342,263 +586,15 @@ __global__ __launch_bounds__((NW + NL) * 64) void k_proj_gemm(GemmArgs p)
     }
     }
 
-    // ---- epilogue, in registers.  Lane (col, hi) of sub-tile i holds window row m0 + 32 (wm MW + i) + col;
-    // register r of sub-tile t is feature 32 t' + 8 (r >> 2) + 4 hi + (r & 3) of the head, with t' = t
-    // for a whole head and {half, half + 2} for a half head.
-    if (!head_valid) return;
+    // ---- epilogue; the LDS ring is its staging area, once every wave has left it
     if constexpr (EPI == 4) {
-        // Lane (col, hi) holds, for window row col, the logits 32 t + 8 (r >> 2) + 4 hi + (r & 3) of the
-        // slab: ascending in (t, r), so ties keep the smaller index; the other half is in lane ^ 32.
-        static_assert(EPI != 4 || NSUB == 4, "vocabulary mode uses whole slabs");
-#pragma unroll
-        for (int i = 0; i < MW; ++i) {
-            const int m = m0 + 32 * (wm * MW + i) + col;
-            float mx = -INFINITY, sm = 0.f;
-            int arg = 0;
-#pragma unroll
-            for (int t = 0; t < NSUB; ++t)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float z = acc[i][t][r];
-                    const int v = hs * 128 + 32 * t + 8 * (r >> 2) + 4 * hi + (r & 3);
-                    if (z > mx) {
-                        sm = sm * expf(mx - z) + 1.0f;
-                        mx = z;
-                        arg = v;
-                    } else {
-                        sm += expf(z - mx);
-                    }
-                }
-            const float mx2 = __shfl_xor(mx, 32, 64), sm2 = __shfl_xor(sm, 32, 64);
-            const int arg2 = __shfl_xor(arg, 32, 64);
-            fc_argmax_merge(mx, arg, sm, mx2, arg2, sm2);
-            if (hi == 0 && m < p.m_end) {
-                const size_t at = (size_t)hs * p.M + m;
-                p.am.mx[at] = mx;
-                p.am.arg[at] = arg;
-                p.am.sm[at] = sm;
-            }
-        }
-        return;
-    }
-    if (DEALT && EPI == 2) {
-        // Gated layer, dealt pairs: registers 4 rq + e (gate) and 8 + 4 rq + e (up), rq < 2, of sub-tile t
-        // are output column 80 unit + 16 t + 8 rq + 4 hi + e.
-#pragma unroll
-        for (int i = 0; i < MW; ++i) {
-            const int m = m0 + 32 * (wm * MW + i) + col;
-            if (m >= p.m_end) continue;
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const int base = PPU * unit + 16 * (t0 + t);
-                if (t >= nt_mine || base >= n_pairs) continue;
-#pragma unroll
-                for (int rq = 0; rq < 2; ++rq) {
-                    float y[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float g = acc[i][t][4 * rq + e];
-                        y[e] = g / (1.0f + expf(-g)) * acc[i][t][8 + 4 * rq + e];
-                    }
-                    uint2 w;
-                    w.x = (uint32_t)fc_bf16_bits(y[0]) | ((uint32_t)fc_bf16_bits(y[1]) << 16);
-                    w.y = (uint32_t)fc_bf16_bits(y[2]) | ((uint32_t)fc_bf16_bits(y[3]) << 16);
-                    *(uint2 *)(p.out + (size_t)m * p.N + base + 8 * rq + 4 * hi) = w;
-                }
-            }
-        }
-        return;
-    }
-    if constexpr (EPI != 0 && !DEALT) {
-        // Plain linear layers.  Register r of sub-tile t of lane (col, hi) is output column
-        // 32 t' + 8 (r >> 2) + 4 hi + (r & 3) of the slab (of its 64 outputs for EPI 2, t' < 2).
-#pragma unroll
-        for (int i = 0; i < MW; ++i) {
-            const int m = m0 + 32 * (wm * MW + i) + col;
-            if (m >= p.m_end) continue;
-#pragma unroll
-            for (int t = 0; t < (EPI == 2 ? NSUB / 2 : NSUB); ++t) {
-                const int tq = NSUB == 4 ? t : (EPI == 2 ? half : half + 2 * t);
-#pragma unroll
-                for (int rq = 0; rq < 4; ++rq) {
-                    const size_t at = (size_t)m * p.N + (size_t)hs * (EPI == 2 ? 64 : 128) + 32 * tq + 8 * rq + 4 * hi;
-                    float y[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        y[e] = acc[i][t][4 * rq + e];
-                        if (EPI == 2) y[e] = y[e] / (1.0f + expf(-y[e])) * acc[i][t + NSUB / 2][4 * rq + e];
-                    }
-                    if (EPI == 3) {
-                        *(float4 *)(p.part + (size_t)kpart * p.M * p.N + at) = make_float4(y[0], y[1], y[2], y[3]);
-                        continue;
-                    }
-                    if (EPI == 1 && p.res) {
-                        const uint2 rv = *(const uint2 *)(p.res + at);
-                        y[0] += __uint_as_float(rv.x << 16);
-                        y[1] += __uint_as_float(rv.x & 0xffff0000u);
-                        y[2] += __uint_as_float(rv.y << 16);
-                        y[3] += __uint_as_float(rv.y & 0xffff0000u);
-                    }
-                    uint2 w;
-                    w.x = (uint32_t)fc_bf16_bits(y[0]) | ((uint32_t)fc_bf16_bits(y[1]) << 16);
-                    w.y = (uint32_t)fc_bf16_bits(y[2]) | ((uint32_t)fc_bf16_bits(y[3]) << 16);
-                    *(uint2 *)(p.out + at) = w;
-                }
-            }
-        }
-        return;
-    }
-    // base^(-1/64) and its powers; base^(-i/64) / (2 pi) = turns per position of pair i
-    const double r1 = exp2(-p.log2_base_64);
-    const double r2 = r1 * r1, r4 = r2 * r2, r8 = r4 * r4, r16 = r8 * r8, r32 = r16 * r16;
-    if constexpr (DEALT) {
-        // Dealt pairs: sub-tile t holds the 16 rotary pairs ib .. ib + 15 of head slot hs_t; registers
-        // 4 rq + e (feature ib + 8 rq + 4 hi + e) and 8 + 4 rq + e (the same + 64), rq < 2.
-#pragma unroll
-        for (int i = 0; i < MW; ++i) {
-            const int m = m0 + 32 * (wm * MW + i) + col;
-            const bool mvalid = m < p.m_end;
-            const int mm = mvalid ? m : 0;
-            const int b = mm / p.A, a = mm - b * p.A;
-            const int pp = p.pos ? p.pos[mm] : p.win_start + a;
-            const bool valid = mvalid && pp >= 0 && pp < G.max_seq;
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const int base = PPU * unit + 16 * (t0 + t);
-                if (t >= nt_mine || base >= n_pairs) continue;  // wave-uniform
-                const int hs_t = base >> 6, ib = base & 63;
-                if (p.bias) {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        acc[i][t][r] += fc_to_float(
-                            bf16_t{p.bias[hs_t * 128 + ib + 8 * ((r >> 2) & 1) + 4 * hi + (r & 3) + 64 * (r >> 3)]});
-                }
-                if (hs_t < G.Hq + G.Hkv) {
-                    double f = 0.15915494309189533576888;
-                    if (ib & 16) f *= r16;
-                    if (ib & 32) f *= r32;
-                    if (hi) f *= r4;
-#pragma unroll
-                    for (int rq = 0; rq < 2; ++rq) {
-                        double fr = f;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const int r = 4 * rq + e;
-                            const double turns = (double)pp * fr;
-                            const float ph = (float)(turns - rint(turns));
-                            const float c = __builtin_amdgcn_cosf(ph), sn = __builtin_amdgcn_sinf(ph);
-                            const float lo = acc[i][t][r], hi2 = acc[i][t][r + 8];
-                            acc[i][t][r] = lo * c - hi2 * sn;
-                            acc[i][t][r + 8] = hi2 * c + lo * sn;
-                            fr *= r1;
-                        }
-                        f *= r8;
-                    }
-                }
-                if (!mvalid) continue;
-#pragma unroll
-                for (int rq4 = 0; rq4 < 4; ++rq4) {
-                    const int d0 = ib + 8 * (rq4 & 1) + 4 * hi + 64 * (rq4 >> 1);
-                    uint2 w;
-                    w.x = (uint32_t)fc_bf16_bits(acc[i][t][4 * rq4]) | ((uint32_t)fc_bf16_bits(acc[i][t][4 * rq4 + 1]) << 16);
-                    w.y = (uint32_t)fc_bf16_bits(acc[i][t][4 * rq4 + 2]) | ((uint32_t)fc_bf16_bits(acc[i][t][4 * rq4 + 3]) << 16);
-                    if (hs_t < G.Hq) {
-                        if (!valid) w = make_uint2(0, 0);
-                        *(uint2 *)(p.Q + (((size_t)b * G.Hq + hs_t) * p.A + a) * 128 + d0) = w;
-                    } else if (valid) {
-                        if (hs_t < G.Hq + G.Hkv) {
-                            *(uint2 *)(p.Kc + fc_k_index(G, b, hs_t - G.Hq, pp, d0)) = w;
-                        } else {
-                            uint16_t *v = p.Vc + fc_v_index(G, b, hs_t - G.Hq - G.Hkv, pp, d0);
-                            v[0] = (uint16_t)(w.x & 0xffff);
-                            v[FC_VTILE] = (uint16_t)(w.x >> 16);
-                            v[2 * FC_VTILE] = (uint16_t)(w.y & 0xffff);
-                            v[3 * FC_VTILE] = (uint16_t)(w.y >> 16);
-                        }
-                    }
-                }
-            }
-        }
-        return;
-    }
-    if constexpr (!DEALT) {
-    const bool rotate = hs < G.Hq + G.Hkv;
-    constexpr int NP = NSUB / 2;  // rotary pairs of sub-tiles: (t, t + NP)
-
-#pragma unroll
-    for (int i = 0; i < MW; ++i) {
-        const int m = m0 + 32 * (wm * MW + i) + col;
-        const bool mvalid = m < p.m_end;
-        const int mm = mvalid ? m : 0;
-        const int b = mm / p.A, a = mm - b * p.A;
-        const int pp = p.pos ? p.pos[mm] : p.win_start + a;
-        const bool valid = mvalid && pp >= 0 && pp < G.max_seq;
-
-        if (p.bias) {
-#pragma unroll
-            for (int t = 0; t < NSUB; ++t) {
-                const int tq = NSUB == 4 ? t : half + 2 * t;
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    acc[i][t][r] += fc_to_float(bf16_t{p.bias[hs * 128 + 32 * tq + 8 * (r >> 2) + 4 * hi + (r & 3)]});
-            }
-        }
-        if (rotate) {
-            // the angle is reduced to a fraction of a turn in double, then hardware sine / cosine
-            // (argument in turns)
-#pragma unroll
-            for (int t = 0; t < NP; ++t) {
-                const int tq = NSUB == 4 ? t : half;  // pair index 32 tq + 8 rq + 4 hi + (r & 3) < 64
-                double f = 0.15915494309189533576888;
-                if (tq) f *= r32;
-                if (hi) f *= r4;
-#pragma unroll
-                for (int rq = 0; rq < 4; ++rq) {
-                    double fr = f;
-#pragma unroll
-                    for (int r3 = 0; r3 < 4; ++r3) {
-                        const int r = 4 * rq + r3;
-                        const double turns = (double)pp * fr;
-                        const float ph = (float)(turns - rint(turns));
-                        const float c = __builtin_amdgcn_cosf(ph), sn = __builtin_amdgcn_sinf(ph);
-                        const float lo = acc[i][t][r], hi2 = acc[i][t + NP][r];
-                        acc[i][t][r] = lo * c - hi2 * sn;
-                        acc[i][t + NP][r] = hi2 * c + lo * sn;
-                        fr *= r1;
-                    }
-                    f *= r8;
-                }
-            }
-        }
-        if (!mvalid) continue;
-
-#pragma unroll
-        for (int t = 0; t < NSUB; ++t) {
-            const int tq = NSUB == 4 ? t : half + 2 * t;
-#pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
-                const int d0 = 32 * tq + 8 * rq + 4 * hi;
-                uint2 w;
-                w.x = (uint32_t)fc_bf16_bits(acc[i][t][4 * rq]) | ((uint32_t)fc_bf16_bits(acc[i][t][4 * rq + 1]) << 16);
-                w.y = (uint32_t)fc_bf16_bits(acc[i][t][4 * rq + 2]) | ((uint32_t)fc_bf16_bits(acc[i][t][4 * rq + 3]) << 16);
-                if (hs < G.Hq) {
-                    if (!valid) w = make_uint2(0, 0);
-                    *(uint2 *)(p.Q + (((size_t)b * G.Hq + hs) * p.A + a) * 128 + d0) = w;
-                } else if (valid) {
-                    if (hs < G.Hq + G.Hkv) {
-                        *(uint2 *)(p.Kc + fc_k_index(G, b, hs - G.Hq, pp, d0)) = w;
-                    } else {
-                        const int j = hs - G.Hq - G.Hkv;
-                        uint16_t *v = p.Vc + fc_v_index(G, b, j, pp, d0);
-                        v[0] = (uint16_t)(w.x & 0xffff);
-                        v[FC_VTILE] = (uint16_t)(w.x >> 16);
-                        v[2 * FC_VTILE] = (uint16_t)(w.y & 0xffff);
-                        v[3 * FC_VTILE] = (uint16_t)(w.y >> 16);
-                    }
-                }
-            }
-        }
-    }
+        if (head_valid) gemm_epilogue_vocab<MW>(p, acc, hs, m0 + 32 * wm * MW, lane);
+    } else {
+        __builtin_amdgcn_s_barrier();
+        if (!head_valid) return;
+        const uint16_t *bias_low = (const uint16_t *)bias_area + (DEALT ? 16 * t0 : NSUB == 4 ? 64 * wn : 0);
+        gemm_epilogue<NT, MW, EPI, DEALT>(p, acc, smem + wave * epi_bytes(NT), bias_low, bias_low + NPW, hs, half, PPU * unit + 16 * t0, nt_mine,
+                                          m0 + 32 * wm * MW, lane, kpart);
     }
 }
 
@@ -607,7 +603,9 @@ hipError_t launch_gemm(GemmArgs a, hipStream_t s)
 {
     constexpr int XROWS = 32 * MW * (NW / NG);
     constexpr bool DEALT = NSUB == 5 || NSUB == 3;
-    constexpr int LDS = SLOTS * ((DEALT ? 32 * NSUB : 32 * NSUB * NG) + XROWS) * KS * 2;
+    constexpr int RING = SLOTS * ((DEALT ? 32 * NSUB : 32 * NSUB * NG) + XROWS) * KS * 2;
+    constexpr int EPI_LDS = NW * epi_bytes(DEALT && NG == 2 ? (NSUB + 1) / 2 : NSUB);
+    constexpr int LDS = (RING > EPI_LDS ? RING : EPI_LDS) + (EPI == 0 ? BIAS_LDS : 0);
     static_assert(LDS <= 160 * 1024, "LDS ring too large");
     static hipError_t attr = hipFuncSetAttribute((const void *)k_proj_gemm<KS, NW, NSUB, MW, NG, SLOTS, NL, EPI>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
@@ -862,7 +860,10 @@ hipError_t fc_launch_project_gemm(const FcGeom &G, const void *x, const void *w,
     a.part = nullptr;
     a.N = 0;
     a.ksplit = 1;
-    a.log2_base_64 = G.log_base * 1.4426950408889634074 / 64.0;
+    a.rot1 = exp(-G.log_base / 64.0);
+    a.rot8 = exp(-G.log_base / 8.0);
+    a.rot16 = exp(-G.log_base / 4.0);
+    a.rot32 = exp(-G.log_base / 2.0);
     // The two 128-row shapes get four extra waves that only issue the loads (their four multiplying
     // waves are alone on their SIMDs); the half-head shape also takes 128 hidden elements per stage.
     auto launch_shape = [&](int shape, const GemmArgs &g) -> hipError_t {
