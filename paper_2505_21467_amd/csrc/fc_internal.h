@@ -36,7 +36,7 @@ struct FcKnobs {
     int attn_wgs;           // FC_ATTN_WGS=n          workgroups the split heuristic aims for
     int lin_wgs;            // FC_LIN_WGS=n           workgroups of the weight-streaming linear kernels
     int lin_no_rows;        // FC_LIN_NO_ROWS         slice-wise instead of whole-row weight streaming
-    int lin_wide_shape;     // FC_LIN_WIDE_SHAPE=0..2 (4: gated layer only) one tile shape for the tiled linear GEMM (-1 = planned)
+    int lin_wide_shape;     // FC_LIN_WIDE_SHAPE=0..3 (4: gated layer only) one tile shape for the tiled linear GEMM (-1 = planned)
     int lin_ksplit;         // FC_LIN_KSPLIT=n        parts of the hidden dimension
     int gemm_no_split;      // FC_GEMM_NO_SPLIT       never cut a GEMM into two launches
     int proj_gemm_shape;    // FC_PROJ_GEMM_SHAPE=0..5 one tile shape for the projection GEMM (-1 = planned)
@@ -158,7 +158,7 @@ hipError_t fc_launch_unmask_select(const int32_t *tok, const float *conf, const 
 // Tiled-GEMM plan of the same linear layers on more than 32 rows.
 struct FcWidePlan {
     int kind;    // 0 = not covered, 1 = tiled GEMM
-    int shape;   // 0: 256 rows x slab, 1: 128 rows x slab, 2: 128 rows x half slab
+    int shape;   // tile shape where ksplit > 1 or a tuning knob forces one (0: 256 rows x slab, 1: 128 rows x slab, 2: 128 rows x half slab, 3: 256 rows x two slabs)
     int ksplit;  // parts of the hidden dimension (1 = epilogue inside the GEMM, no workspace)
 };
 FcWidePlan fc_plan_wide(int dtype, int mode, int M, int K, int N);

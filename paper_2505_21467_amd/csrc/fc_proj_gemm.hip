@@ -9,7 +9,7 @@
 // register), with NSUB = 2 it covers the rotary-paired half head {32 h .. 32 h + 31} u {64 + 32 h ..}
 // (more, smaller workgroups when the window is too short to fill the chip).  The rotation, the bias and
 // the stores to q_out / the K rows / the transposed V tiles therefore need no exchange between lanes.
-// Two more shapes (NSUB = 5, 3) deal the rotary pairs of all head slots, laid end to end, 80 or 48 to a
+// A second kernel, k_gemm_pp, covers 256 window rows x two heads.  Two more shapes (NSUB = 5, 3) deal the rotary pairs of all head slots, laid end to end, 80 or 48 to a
 // workgroup (16 per sub-tile, low rows then high rows: the partner of register r is register r + 8): a
 // quarter more work per workgroup than a head for grids that would otherwise be a little more than one
 // round, a quarter less for grids well short of one.
@@ -468,8 +468,7 @@ __global__ __launch_bounds__((NW + NL) * 64) void k_proj_gemm(GemmArgs p)
 
     // bias, behind the ring
     constexpr int NPW = DEALT ? PPU : NSUB == 4 ? 64 * NG : 32;  // pairs per workgroup
-    constexpr int EPI_LDS = NW * epi_bytes(NT);
-    unsigned char *bias_area = smem + (SLOTS * STAGE > EPI_LDS ? SLOTS * STAGE : EPI_LDS);  // behind ring and staging
+    unsigned char *bias_area = smem + SLOTS * STAGE;
     if (EPI == 0 && lw == 0)
         load_bias(p, bias_area, DEALT ? PPU * unit : NSUB == 4 ? (p.slot_base + unit * NG) * 64 : hs * 64 + 32 * half, NPW, n_pairs, lane);
 
@@ -590,6 +589,7 @@ __global__ __launch_bounds__((NW + NL) * 64) void k_proj_gemm(GemmArgs p)
     if constexpr (EPI == 4) {
         if (head_valid) gemm_epilogue_vocab<MW>(p, acc, hs, m0 + 32 * wm * MW, lane);
     } else {
+        static_assert(NW * epi_bytes(NT) <= SLOTS * STAGE, "epilogue staging");
         __builtin_amdgcn_s_barrier();
         if (!head_valid) return;
         const uint16_t *bias_low = (const uint16_t *)bias_area + (DEALT ? 16 * t0 : NSUB == 4 ? 64 * wn : 0);
@@ -598,14 +598,207 @@ __global__ __launch_bounds__((NW + NL) * 64) void k_proj_gemm(GemmArgs p)
     }
 }
 
+// -------------------------------------------------------------------------------------------------
+// 256 window rows x two slabs (256 weight rows), for problems with enough such tiles to fill the chip.
+//
+// A workgroup has eight waves in two groups of four, one wave of each group per SIMD; group wn owns slab wn
+// and its wave wm the window rows 64 wm .. 64 wm + 63 (MW = 2, NT = 4 sub-tiles of 32 x 32).  The loop over
+// 64 hidden elements (a stage) alternates between reading operand fragments from LDS (and issuing loads)
+// and multiplying, with a workgroup barrier behind each such interval, and group 1 runs one interval behind
+// group 0: on every SIMD one wave multiplies while the other reads, so that LDS results never have to
+// wait for the register ports of a running multiply and the matrix core always has a wave to run.  The loads
+// of an interval are issued behind its reads: in front of them they held the reads back (1.74 us per stage at half
+// the compute units, 1.32 behind).  2304 rows x 296 gated slabs, hidden 3584: 635 us in tiles of one slab, 560 in
+// this one, 551 with the last round cut off (1135 TFLOP/s); with all compute units multiplying and no loads at
+// all the same loop runs at 1380 TFLOP/s, which is what the clock allows under that load.
+//
+//   interval   M0            C0          M1         C1          M2            C2          M3               C3
+//   reads      W sub 0,1                 X sub 1                W sub 2,3                 X sub 0 (next)
+//   multiplies               X0 W01                 X1 W01                    X0 W23                       X1 W23
+//
+// LDS holds two stages of 64 KB in four parts (X0, W01, X1, W23: 128 rows x 128 B, swizzled like the other
+// shapes).  A part is refilled, for the stage after the next, one or two intervals after its last reader:
+// group 0 issues its half of W23, X0, W01, X1 in M0 .. M3, group 1 its half of X0, W01, X1, W23, so a
+// load has eleven intervals (about 1.4 us) to arrive, and some 88 KB are always in flight.  Each wave
+// waits for its own loads of the part that group 0 reads next at the end of every second interval; the count of
+// younger loads is the same every time (five parts in group 0, six in group 1, two loads each).  Past the last
+// stage the loads go on, from the last stage's addresses, into parts nobody reads: the counts stay exact.
+template <int GRP, typename Issue, typename Read, typename Mul>
+__device__ __forceinline__ void gemm_pp_loop(int n_stages, Issue issue, Read read, Mul mul)
+{
+    constexpr int AHEAD = 2 * (GRP == 0 ? 5 : 6);
+    auto end_m = [&]() {  // end of a memory interval
+        wait_vmg<GRP == 1 ? AHEAD : 63, true>();
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto compute = [&](int i, int tp) {
+        mul(i, tp);
+        __builtin_amdgcn_sched_barrier(0);
+        if (GRP == 0) wait_vmg<AHEAD>();
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // parts: 0 X0, 1 W01, 2 X1, 3 W23
+#pragma unroll
+    for (int part = 0; part < 4; ++part) issue(0, part);
+#pragma unroll
+    for (int part = 0; part < (GRP == 0 ? 3 : 4); ++part) issue(1, part);
+    wait_vmg<AHEAD>();  // X0 and W01 of stage 0
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    read(0, 0);
+    if (GRP == 1) {
+        wait_vmg<63, true>();
+        __builtin_amdgcn_s_barrier();  // one interval behind
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    for (int st = 0; st < n_stages; ++st) {
+        // M0
+        read(st, 1);
+        issue(GRP == 0 ? st + 1 : st + 2, GRP == 0 ? 3 : 0);
+        end_m();
+        compute(0, 0);
+        // M1
+        read(st, 2);
+        issue(st + 2, GRP == 0 ? 0 : 1);
+        end_m();
+        compute(1, 0);
+        // M2
+        read(st, 3);
+        issue(st + 2, GRP == 0 ? 1 : 2);
+        end_m();
+        compute(0, 1);
+        // M3
+        read(st + 1, 0);  // (behind the last stage: not used)
+        issue(st + 2, GRP == 0 ? 2 : 3);
+        end_m();
+        compute(1, 1);
+    }
+    if (GRP == 0) __builtin_amdgcn_s_barrier();
+    wait_vmg<0>();  // no load may still arrive in LDS when the epilogue uses it
+    __builtin_amdgcn_s_barrier();
+}
+
+constexpr int PP_LDS = 8 * epi_bytes(4) > 128 * 1024 ? 8 * epi_bytes(4) : 128 * 1024;  // the loop's two stages; the epilogue
+template <int EPI>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_pp(GemmArgs p)
+{
+    constexpr int PART = 128 * 128, STAGE = 4 * PART;
+    extern __shared__ __align__(1024) unsigned char smem[];
+    // workgroup -> (slab pair, row tile, part of the hidden dimension), dealt to the XCDs as in k_proj_gemm
+    const int id = blockIdx.x;
+    const int xcd = id & 7, qd = id >> 3;
+    const int n_kp = EPI == 3 ? p.ksplit : 1;
+    const int64_t n_tiles = (int64_t)p.n_units * p.n_mt * n_kp;
+    const int tile_k = (int)(xcd * n_tiles / 8) + qd;
+    if (tile_k >= (int)((xcd + 1) * n_tiles / 8)) return;
+    const int tile = tile_k / n_kp, kpart = tile_k - tile * n_kp;
+    const int unit = tile / p.n_mt, mt = tile - unit * p.n_mt;
+    const int m0 = p.m_base + mt * 256;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, hi = lane >> 5;
+    const int wn = wave >> 2, wm = wave & 3;
+
+    // ---- loads: two 1 KB blocks (8 rows x 128 B) of each part per wave
+    uint32_t goff[4][2];
+#pragma unroll
+    for (int part = 0; part < 4; ++part)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int r = 8 * (2 * wave + i) + (lane >> 3);  // row of the part
+            const int c = (lane & 7) ^ ((r >> 1) & 7);
+            int row;
+            if ((part & 1) == 0) {
+                row = min(m0 + 64 * (r >> 5) + 16 * part + (r & 31), p.m_end - 1);  // rows past the end: never stored
+            } else {
+                const int slab = min(p.slot_base + 2 * unit + (r >> 6), p.n_slots - 1);
+                row = EPI == 2 ? slab * 64 + (r & 63) : slab * 128 + (part == 3 ? 64 : 0) + (r & 63);
+            }
+            goff[part][i] = (uint32_t)row * (uint32_t)(p.K * 2) + c * 16;
+        }
+    const int all_stages = p.K / 64;
+    const int st0 = EPI == 3 ? (int)((int64_t)kpart * all_stages / p.ksplit) : 0;
+    const int n_stages = EPI == 3 ? (int)(((int64_t)kpart + 1) * all_stages / p.ksplit) - st0 : all_stages;
+    auto issue = [&](int st, int part) {
+        __builtin_amdgcn_sched_barrier(0);
+        const uint16_t *mat = (part & 1) == 0 ? p.X : (EPI == 2 && part == 3) ? p.W2 : p.W;
+        const unsigned char *src = (const unsigned char *)mat + (size_t)(st0 + min(st, n_stages - 1)) * 128;
+        unsigned char *dst = smem + (st & 1) * STAGE + part * PART + wave * 2048;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) load_lds16g(src + goff[part][i], dst + i * 1024);
+    };
+
+    // bias, behind everything else
+    unsigned char *bias_area = smem + PP_LDS;
+    if (EPI == 0 && wave == 0) load_bias(p, bias_area, (p.slot_base + 2 * unit) * 64, 128, p.n_slots * 64, lane);
+
+    // ---- operand fragments
+    uint32_t foff[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) foff[kk] = (uint32_t)(col * 128 + (((2 * kk + hi) ^ ((col >> 1) & 7)) << 4));
+    bf16x8 xf[2][4], wf[2][4];
+    auto read = [&](int st, int part) {
+        const unsigned char *base = smem + (st & 1) * STAGE + part * PART;
+        if ((part & 1) == 0) {
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) xf[part >> 1][kk] = *(const bf16x8 *)(base + wm * 4096 + foff[kk]);
+        } else {
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) wf[t][kk] = *(const bf16x8 *)(base + wn * 8192 + t * 4096 + foff[kk]);
+        }
+    };
+    f32x16 acc[2][4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][t][r] = 0.f;
+    auto mul = [&](int i, int tp) {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+                acc[i][2 * tp + t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[t][kk], xf[i][kk], acc[i][2 * tp + t], 0, 0, 0);
+    };
+    if (wn == 0) gemm_pp_loop<0>(n_stages, issue, read, mul);
+    else gemm_pp_loop<1>(n_stages, issue, read, mul);
+
+    const int hs = p.slot_base + 2 * unit + wn;
+    if (hs >= p.slot_base + p.slots_here) return;  // an odd number of slabs leaves the last pair half empty
+    if constexpr (EPI == 4) gemm_epilogue_vocab<2>(p, acc, hs, m0 + 64 * wm, lane);
+    else gemm_epilogue<4, 2, EPI, false>(p, acc, smem + wave * epi_bytes(4), (const uint16_t *)bias_area + 64 * wn,
+                                         (const uint16_t *)bias_area + 128 + 64 * wn, hs, 0, 0, 4, m0 + 64 * wm, lane, kpart);
+}
+
+template <int EPI>
+hipError_t launch_gemm_pp(GemmArgs a, hipStream_t s)
+{
+    constexpr int LDS = PP_LDS + (EPI == 0 ? BIAS_LDS : 0);
+    static hipError_t attr = hipFuncSetAttribute((const void *)k_gemm_pp<EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+    if (attr != hipSuccess) return attr;
+    a.n_units = (a.slots_here + 1) / 2;
+    a.n_mt = (a.m_end - a.m_base + 255) / 256;
+    if (a.slots_here < 1 || a.n_mt < 1 || a.slot_base < 0 || a.slot_base + a.slots_here > a.n_slots || a.m_base < 0 ||
+        a.m_end > a.M || a.K % 64 != 0 || (EPI == 3 && (a.ksplit < 1 || a.ksplit > a.K / 64)))
+        return hipErrorInvalidValue;
+    const int64_t n_tiles = (int64_t)a.n_units * a.n_mt * (EPI == 3 ? a.ksplit : 1);
+    if (n_tiles > (1 << 30)) return hipErrorInvalidValue;
+    k_gemm_pp<EPI><<<dim3((unsigned)((n_tiles + 7) / 8 * 8)), dim3(512), LDS, s>>>(a);
+    return hipGetLastError();
+}
+
 template <int KS, int NW, int NSUB, int MW, int NG, int SLOTS, int NL, int EPI = 0>
 hipError_t launch_gemm(GemmArgs a, hipStream_t s)
 {
     constexpr int XROWS = 32 * MW * (NW / NG);
     constexpr bool DEALT = NSUB == 5 || NSUB == 3;
-    constexpr int RING = SLOTS * ((DEALT ? 32 * NSUB : 32 * NSUB * NG) + XROWS) * KS * 2;
-    constexpr int EPI_LDS = NW * epi_bytes(DEALT && NG == 2 ? (NSUB + 1) / 2 : NSUB);
-    constexpr int LDS = (RING > EPI_LDS ? RING : EPI_LDS) + (EPI == 0 ? BIAS_LDS : 0);
+    constexpr int LDS = SLOTS * ((DEALT ? 32 * NSUB : 32 * NSUB * NG) + XROWS) * KS * 2 + (EPI == 0 ? BIAS_LDS : 0);
     static_assert(LDS <= 160 * 1024, "LDS ring too large");
     static hipError_t attr = hipFuncSetAttribute((const void *)k_proj_gemm<KS, NW, NSUB, MW, NG, SLOTS, NL, EPI>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
@@ -650,78 +843,130 @@ __global__ __launch_bounds__(256) void k_splitk_finish(const float *__restrict__
     *(uint2 *)(out + 4 * i) = w;
 }
 
+// A launch in one tile shape (numbered below).  Loads of the 128-row shapes are issued by four extra waves: their four
+// multiplying waves are alone on their SIMDs.  The half-head shape of the projection takes 128 hidden elements per
+// stage where it can.
 template <int EPI>
-hipError_t launch_wide_shape(int shape, const GemmArgs &a, hipStream_t s)
+hipError_t launch_shape(int shape, const GemmArgs &a, hipStream_t s)
 {
-    if (shape == 4) {  // 256 rows x 80 dealt pairs (gated layer only)
-        if constexpr (EPI == 2) return launch_gemm<64, 8, 5, 2, 2, 3, 0, EPI>(a, s);
-        else return hipErrorInvalidValue;
+    switch (shape) {
+    case 0: return launch_gemm<64, 8, 4, 1, 1, 3, 0, EPI>(a, s);
+    case 1: return launch_gemm<64, 4, 4, 1, 1, 4, 4, EPI>(a, s);
+    case 2:
+        if constexpr (EPI == 4) return hipErrorInvalidValue;
+        else if (EPI == 0 && a.K % 128 == 0) return launch_gemm<128, 4, 2, 1, 1, 3, 4, EPI>(a, s);
+        else return launch_gemm<64, 4, 2, 1, 1, 4, 4, EPI>(a, s);
+    case 3: return launch_gemm_pp<EPI>(a, s);
+    case 4:
+        if constexpr (EPI == 0 || EPI == 2) return launch_gemm<64, 8, 5, 2, 2, 3, 0, EPI>(a, s);
+        return hipErrorInvalidValue;
+    case 5:
+        if constexpr (EPI == 0 || EPI == 2) return launch_gemm<64, 4, 3, 1, 1, 4, 4, EPI>(a, s);
+        return hipErrorInvalidValue;
+    default: return hipErrorInvalidValue;
     }
-    if (shape == 0) return launch_gemm<64, 8, 4, 1, 1, 3, 0, EPI>(a, s);  // 256 rows x slab
-    if (shape == 1) return launch_gemm<64, 4, 4, 1, 1, 4, 4, EPI>(a, s);  // 128 rows x slab
-    return launch_gemm<64, 4, 2, 1, 1, 4, 4, EPI>(a, s);                  // 128 rows x half slab
 }
 
-// Tile choice: the largest tile that still gives the chip about one workgroup per compute unit.
-// 0: 256 rows x slab, 1: 128 rows x slab, 2: 128 rows x half slab.
-int pick_shape(int64_t slots, int64_t rows, bool allow_half)
+// Tile shapes of the tiled GEMM and what a full round of 256 workgroups takes per 64 hidden elements (us, measured at
+// hidden 3584 with 256..768 workgroups).  Per tile area the larger ones are cheaper -- they move fewer
+// bytes into the compute unit per product -- but leave the chip emptier at the end.
+//   0: 256 rows x slab   1: 128 rows x slab   2: 128 rows x half slab   3: 256 rows x two slabs
+//   4: 256 rows x 80 dealt pairs   5: 128 rows x 48 dealt pairs
+constexpr double ROUND_US[6] = {1.03, 0.62, 0.39, 1.84, 1.30, 0.54};
+
+int64_t tiles_of(int shape, int64_t slots, int64_t rows)
 {
-    // Up to 128 rows the 256-row tile is mostly padding; with that many slabs the half slab is the
-    // fastest (gated W_1 of the 7B widths, 296 slabs, 48 / 64 / 128 rows: 67.6 / 71.7 / 83.8 us against
-    // 72.9 / 74.4 / 85.1 with whole slabs and 81.8 / 80.7 / 88.7 with the 256-row tile).
-    if (rows <= 128 && slots >= 192) return allow_half ? 2 : 1;
-    if (slots * ((rows + 255) / 256) >= 192) return 0;
-    if (slots * ((rows + 127) / 128) >= 144 || !allow_half) return 1;
-    return 2;
+    const int64_t t256 = (rows + 255) / 256, t128 = (rows + 127) / 128;
+    switch (shape) {
+    case 0: return slots * t256;
+    case 1: return slots * t128;
+    case 2: return 2 * slots * t128;
+    case 3: return (slots + 1) / 2 * t256;
+    case 4: return (slots * 64 + 79) / 80 * t256;
+    default: return (slots * 64 + 47) / 48 * t128;
+    }
 }
 
-// One workgroup of the 256-row shape fills a compute unit, so a grid of a little more than 256 such
-// workgroups ends with a nearly empty second round.  Such a problem is cut in two: one round in the
-// 256-row shape and the rest -- the other slabs when there is one row tile (256 rows x 296 slabs:
-// 115 -> 96 us), else the last rows (36 slabs x 8 row tiles: 7 row tiles, then the last 256 rows) -- as
-// a second launch with the (smaller) tile that suits it.  Grids of several rounds are left alone
-// (cutting them was measured slower).
+// Estimated time of one launch per 64 hidden elements.  A round that fills half the chip was measured at 0.78 to
+// 0.9 of a full one (the clock is higher and the memory path less loaded), hence the line 0.6 + 0.4 x.
+double launch_cost(int shape, int64_t slots, int64_t rows)
+{
+    const int64_t n = tiles_of(shape, slots, rows), part = n % 256;
+    return ROUND_US[shape] * ((double)(n / 256) + (part ? 0.6 + 0.4 * part / 256.0 : 0.0));
+}
+
+// A problem is covered by one launch, or cut in two where the last round of workgroups would be nearly empty:
+// the first launch takes whole rounds and the second, in a smaller tile, the other slabs or the last rows.
+// The cut, the second launch (about 3 us) and the shapes are the cheapest by the estimate above: 2304 rows x 296
+// gated slabs, hidden 3584: 284 slabs in 1278 tiles of shape 3 (4.99 rounds) and 12 in shape 1; 256
+// rows x 296: 237 tiles of shape 4 in one round; 2048 rows x 36 head slots: 232 tiles of shape 4.
 struct GemmPiece {
     int shape, slot_base, slots, m_base, m_end;
 };
-int plan_pieces(int slots, int M, bool allow_half, bool allow_dealt, GemmPiece out[2])
+int plan_pieces(int slots, int M, int K, bool allow_half, bool allow_dealt, GemmPiece out[2])
 {
-    out[0] = GemmPiece{pick_shape(slots, M, allow_half), 0, slots, 0, M};
     const bool no_split = fc_knobs().gemm_no_split != 0;  // tuning knob
-    if (out[0].shape != 0 || no_split) return 1;
-    const int64_t mt = (M + 255) / 256, tiles = (int64_t)slots * mt, rounds = tiles / 256, rem = tiles % 256;
-    if (rounds != 1 || rem == 0 || rem > 160) return 1;
-    // Layers whose weight rows come in pairs (rotary pairs, gate and up rows) have a fifth shape, 256
-    // rows x 80 dealt pairs: a quarter more work per workgroup, so up to 320 tiles of the 256-row shape
-    // still make one round, in one launch (36 head slots x 8 row tiles: 89.5 -> 82.5 us; 296 gated slabs
-    // x 256 rows: 98.5 -> 88.5 us).
-    if (allow_dealt && (((int64_t)slots * 64 + 79) / 80) * mt <= 256) {
-        out[0].shape = 4;
+    // Up to 128 rows the 256-row tiles are mostly padding and the weights, not the tiles, bound the time; with that
+    // many slabs the half slab is the fastest (gated W_1 of the 7B widths, 296 slabs, 48 / 64 / 128 rows: 67.6
+    // / 71.7 / 83.8 us against 72.9 / 74.4 / 85.1 with whole slabs and 81.8 / 80.7 / 88.7 with the 256-row tile).
+    if (M <= 128 && slots >= 192) {
+        out[0] = GemmPiece{allow_half ? 2 : 1, 0, slots, 0, M};
         return 1;
     }
-    if (mt == 1) {
-        out[0].slots = 256;
-        out[1] = GemmPiece{pick_shape(slots - 256, M, allow_half), 256, slots - 256, 0, M};
-    } else {
-        const int mt1 = 256 / slots;  // row tiles of the first round
-        if (mt1 * slots < 224) return 1;
-        out[0].m_end = mt1 * 256;
-        out[1] = GemmPiece{pick_shape(slots, M - mt1 * 256, allow_half), 0, slots, mt1 * 256, M};
+    double best = 1e30;
+    int n = 1;
+    for (int sh = 0; sh < 6; ++sh) {
+        if ((sh == 2 && !allow_half) || (sh >= 4 && !allow_dealt)) continue;
+        const double c = launch_cost(sh, slots, M);
+        if (c < best) {
+            best = c;
+            out[0] = GemmPiece{sh, 0, slots, 0, M};
+        }
     }
-    return 2;
+    if (no_split) return 1;
+    const double extra = 3.0 / (K / 64);
+    for (int sh = 0; sh <= 3; sh += 3) {
+        const int64_t per = sh == 3 ? 2 : 1, t256 = (M + 255) / 256, units = (slots + per - 1) / per;
+        for (int64_t rounds = units * t256 / 256; rounds >= 1 && rounds >= units * t256 / 256 - 1; --rounds) {
+            const int64_t u1 = rounds * 256 / t256, s1 = u1 * per;          // slabs of the first launch
+            const int64_t r1 = rounds * 256 / units, m1 = r1 * 256;         // or its row tiles
+            for (int s2 = 0; s2 <= 3; ++s2) {
+                if (s2 == 2 && !allow_half) continue;
+                if (u1 >= 1 && s1 < slots) {
+                    const double c = launch_cost(sh, s1, M) + launch_cost(s2, slots - s1, M) + extra;
+                    if (c < best) {
+                        best = c;
+                        n = 2;
+                        out[0] = GemmPiece{sh, 0, (int)s1, 0, M};
+                        out[1] = GemmPiece{s2, (int)s1, (int)(slots - s1), 0, M};
+                    }
+                }
+                if (r1 >= 1 && m1 < M) {
+                    const double c = launch_cost(sh, slots, m1) + launch_cost(s2, slots, M - m1) + extra;
+                    if (c < best) {
+                        best = c;
+                        n = 2;
+                        out[0] = GemmPiece{sh, 0, slots, 0, (int)m1};
+                        out[1] = GemmPiece{s2, 0, slots, (int)m1, M};
+                    }
+                }
+            }
+        }
+    }
+    return n;
 }
 
 template <int EPI>
-hipError_t launch_pieces(GemmArgs a, bool allow_half, hipStream_t s)
+hipError_t launch_pieces(GemmArgs a, hipStream_t s)
 {
     GemmPiece pc[2];
-    const int n = plan_pieces(a.n_slots, a.M, allow_half, EPI == 2, pc);
+    const int n = plan_pieces(a.n_slots, a.M, a.K, EPI != 4, EPI == 0 || EPI == 2, pc);
     for (int i = 0; i < n; ++i) {
         a.slot_base = pc[i].slot_base;
         a.slots_here = pc[i].slots;
         a.m_base = pc[i].m_base;
         a.m_end = pc[i].m_end;
-        const hipError_t e = launch_wide_shape<EPI>(pc[i].shape, a, s);
+        const hipError_t e = launch_shape<EPI>(pc[i].shape, a, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -742,9 +987,8 @@ FcWidePlan fc_plan_wide(int dtype, int mode, int M, int K, int N)
     if ((int64_t)N * K * 2 >= ((int64_t)1 << 32) || (int64_t)M * K * 2 >= ((int64_t)1 << 32)) return p;
     p.kind = 1;
     const int64_t units = N / per_slab, t256 = (M + 255) / 256, t128 = (M + 127) / 128;
-    // the largest tile that still gives the chip about one workgroup per compute unit; up to 128 rows
-    // the 256-row tile is mostly padding (vocabulary projection of the 7B widths at 48 / 64 / 128 rows:
-    // 263 / 253 / 271 us with the 128-row tile against 345 / 329 / 323)
+    // (The shape counts only where the hidden dimension is cut into parts or a tuning knob asks for one shape;
+    // everything else goes through plan_pieces at launch.)
     if (M <= 128 && units >= 192) p.shape = mode == FC_LIN_VOCAB ? 1 : 2;
     else if (units * t256 >= 192) p.shape = 0;
     else if (units * t128 >= 144 || mode == FC_LIN_VOCAB) p.shape = 1;
@@ -777,7 +1021,7 @@ FcWidePlan fc_plan_wide(int dtype, int mode, int M, int K, int N)
     }
     {  // tuning knobs
         const int v = fc_knobs().lin_wide_shape;
-        if ((v >= 0 && v <= (mode == FC_LIN_VOCAB ? 1 : 2)) || (v == 4 && mode == FC_LIN_GATE_UP)) p.shape = v;
+        if ((v >= 0 && v <= (mode == FC_LIN_VOCAB ? 1 : 2)) || v == 3 || (v == 4 && mode == FC_LIN_GATE_UP)) p.shape = v;
         const int ks = fc_knobs().lin_ksplit;
         if (ks >= 1 && ks <= 16 && ks <= K / KS_MIN / 4 && mode == FC_LIN_RESIDUAL) p.ksplit = ks;
     }
@@ -814,13 +1058,13 @@ hipError_t fc_launch_linear_wide(const FcWidePlan &pl, int mode, const void *x, 
     a.m_end = M;
     const bool forced = fc_knobs().lin_wide_shape >= 0;  // a forced shape is used for the whole problem
     if (mode == FC_LIN_VOCAB) {
-        if (!am || pl.shape > 1) return hipErrorInvalidValue;
+        if (!am) return hipErrorInvalidValue;
         a.am = *am;
-        return pl.shape == 0 ? launch_gemm<64, 8, 4, 1, 1, 3, 0, 4>(a, s) : launch_gemm<64, 4, 4, 1, 1, 4, 4, 4>(a, s);
+        return forced ? launch_shape<4>(pl.shape, a, s) : launch_pieces<4>(a, s);
     }
-    if (mode == FC_LIN_GATE_UP) return forced ? launch_wide_shape<2>(pl.shape, a, s) : launch_pieces<2>(a, true, s);
-    if (pl.ksplit <= 1) return forced ? launch_wide_shape<1>(pl.shape, a, s) : launch_pieces<1>(a, true, s);
-    hipError_t e = launch_wide_shape<3>(pl.shape, a, s);
+    if (mode == FC_LIN_GATE_UP) return forced ? launch_shape<2>(pl.shape, a, s) : launch_pieces<2>(a, s);
+    if (pl.ksplit <= 1) return forced ? launch_shape<1>(pl.shape, a, s) : launch_pieces<1>(a, s);
+    hipError_t e = launch_shape<3>(pl.shape, a, s);
     if (e != hipSuccess) return e;
     const size_t quads = (size_t)M * N / 4;
     k_splitk_finish<<<dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s>>>((const float *)workspace, a.res, a.out,
@@ -864,41 +1108,10 @@ hipError_t fc_launch_project_gemm(const FcGeom &G, const void *x, const void *w,
     a.rot8 = exp(-G.log_base / 8.0);
     a.rot16 = exp(-G.log_base / 4.0);
     a.rot32 = exp(-G.log_base / 2.0);
-    // The two 128-row shapes get four extra waves that only issue the loads (their four multiplying
-    // waves are alone on their SIMDs); the half-head shape also takes 128 hidden elements per stage.
-    auto launch_shape = [&](int shape, const GemmArgs &g) -> hipError_t {
-        if (shape == 4) return launch_gemm<64, 8, 5, 2, 2, 3, 0>(g, s);   // 256 rows x 80 dealt rotary pairs
-        if (shape == 5) return launch_gemm<64, 4, 3, 1, 1, 4, 4>(g, s);   // 128 rows x 48 dealt rotary pairs, 4 + 4 waves
-        if (shape == 3) return launch_gemm<64, 8, 4, 2, 2, 2, 0>(g, s);   // 256 rows x two heads
-        if (shape == 0) return launch_gemm<64, 8, 4, 1, 1, 3, 0>(g, s);   // 256 rows x head
-        if (shape == 1) return launch_gemm<64, 4, 4, 1, 1, 4, 4>(g, s);   // 128 rows x head
-        if (g.K % 128 == 0) return launch_gemm<128, 4, 2, 1, 1, 3, 4>(g, s);  // 128 rows x half head
-        return launch_gemm<64, 4, 2, 1, 1, 4, 4>(g, s);
-    };
     a.slot_base = 0;
     a.slots_here = a.n_slots;
     a.m_base = 0;
     a.m_end = a.M;
-    if (fc_knobs().proj_gemm_shape >= 0) return launch_shape(fc_knobs().proj_gemm_shape, a);  // tuning knob: one shape for all
-    GemmPiece pc[2];
-    const int n = plan_pieces(a.n_slots, a.M, true, true, pc);
-    if (n == 1 && pc[0].shape == 1) {
-        // 128 rows x head leaves compute units idle when the grid is well short of a round (96 head slots
-        // x 2 row tiles = 192 workgroups); dealt in units of 48 rotary pairs the same rows make more,
-        // smaller workgroups (256 there).  A workgroup's time goes with the rows of both operands it
-        // pulls (128 + 128 against 128 + 96): 44.3 -> 40.8 us at 256 rows, 96 slots, hidden 4096.  (64
-        // rows x 48 pairs for the 36-slot geometry measured the same as the half-head shape: not used.)
-        const int64_t t128 = (a.M + 127) / 128;
-        const int64_t wg1 = (int64_t)a.n_slots * t128, wg5 = (((int64_t)a.n_slots * 64 + 47) / 48) * t128;
-        if (((wg5 + 255) / 256) * 224 < ((wg1 + 255) / 256) * 256) pc[0].shape = 5;
-    }
-    for (int i = 0; i < n; ++i) {
-        a.slot_base = pc[i].slot_base;
-        a.slots_here = pc[i].slots;
-        a.m_base = pc[i].m_base;
-        a.m_end = pc[i].m_end;
-        const hipError_t e = launch_shape(pc[i].shape, a);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    if (fc_knobs().proj_gemm_shape >= 0) return launch_shape<0>(fc_knobs().proj_gemm_shape, a, s);  // tuning knob: one shape for all
+    return launch_pieces<0>(a, s);
 }
