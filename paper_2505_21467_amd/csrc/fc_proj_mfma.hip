@@ -13,7 +13,7 @@
 // 16x16 accumulator layout a lane holds 4 consecutive head-dim indices of one window row, and the
 // rotary partner of every value sits in the lane 32 away, so the rotation needs one cross-lane swap.
 // The rotated q goes to q_out; k and v go directly to their cache rows (v into the transposed tiles).
-#include <stdlib.h>
+#include <math.h>
 
 #include "fc_device.h"
 #include "fc_internal.h"
@@ -34,6 +34,7 @@ struct ProjArgs {
     FcGeom G;
     int M, A, K, win_start, n_tiles;
     double log2_base_64;   // log2(rope_base) / 64
+    double rot[6];         // rope_base^(-i/64), i = 1, 2, 4, .. 32
     float *partials;       // cache scratch: partial tiles of the hidden-dimension slices
 };
 
@@ -283,8 +284,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 // tiles of the hidden-dimension slices (a kernel boundary is the only cross-workgroup ordering used:
 // device-scope fences inside a kernel cost an L2 write-back per workgroup on this multi-die part),
 // then applies bias and rotary embedding and scatters q, k and v.  Rotary factors are computed per
-// lane: base^(-i/64) by binary powering in double, the angle reduced to a fraction of a turn in
-// double, hardware sine/cosine (argument in turns).
+// lane: base^(-i/64) by binary powering in double (the powers come from the host), the angle reduced to a
+// fraction of a turn in double, hardware sine/cosine (argument in turns).  The kernel is one memory round
+// trip long, so all of that runs while the partial tiles are on their way.
 template <int MT>
 __global__ __launch_bounds__(64) void k_proj_finish(ProjArgs p)
 {
@@ -295,11 +297,9 @@ __global__ __launch_bounds__(64) void k_proj_finish(ProjArgs p)
     const int rho = lane & 15, q = lane >> 4;
     const int i0 = wave * 8;
 
-    f32x4 acc[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int kb = 0; kb < S; kb += 8) {  // eight slices' worth of loads in flight at a time
-        float v[8][MT][4];
+    // the first eight slices' loads go out, then everything the epilogue needs besides is fetched and computed
+    float v[8][MT][4];
+    auto load = [&](int kb) {
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const int k2 = min(kb + u, S - 1);
@@ -309,6 +309,47 @@ __global__ __launch_bounds__(64) void k_proj_finish(ProjArgs p)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) v[u][mt][r] = pp2[mt * 256 + r * 64 + lane];
         }
+    };
+    load(0);
+    const bool second = q >= 2, rotate = hs < G.Hq + G.Hkv;
+    const int ib = i0 + 4 * (q & 1);
+    const int d0 = (second ? 64 : 0) + ib;
+    float bs[4] = {0.f, 0.f, 0.f, 0.f};
+    if (p.bias) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) bs[r] = fc_to_float(bf16_t{p.bias[hs * 128 + d0 + r]});
+    }
+    int pos_m[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const int mm = min(16 * mt + rho, p.M - 1);
+        pos_m[mt] = p.pos ? p.pos[mm] : p.win_start + mm % p.A;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    float2 cs[MT][4];
+    if (rotate) {
+        double f = 0.15915494309189533576888;  // base^(-(ib + r)/64) / (2 pi): turns per position
+#pragma unroll
+        for (int bit = 0; bit < 6; ++bit)
+            if (ib & (1 << bit)) f *= p.rot[bit];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                const double turns = (double)pos_m[mt] * f;
+                const float fr = (float)(turns - rint(turns));
+                cs[mt][r] = make_float2(__builtin_amdgcn_cosf(fr), __builtin_amdgcn_sinf(fr));
+            }
+            f *= p.rot[0];
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    f32x4 acc[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int kb = 0; kb < S; kb += 8) {  // eight slices at a time
+        if (kb) load(kb);
 #pragma unroll
         for (int u = 0; u < 8; ++u)
             if (kb + u < S) {
@@ -319,37 +360,13 @@ __global__ __launch_bounds__(64) void k_proj_finish(ProjArgs p)
             }
     }
 
-    const bool second = q >= 2;
-    const int ib = i0 + 4 * (q & 1);
-    const int d0 = (second ? 64 : 0) + ib;
-    const bool rotate = hs < G.Hq + G.Hkv;
-    double freq[4];  // base^(-(ib + r)/64) / (2 pi): turns per position
-    if (rotate) {
-        const double r1 = exp2(-p.log2_base_64);
-        double f = 0.15915494309189533576888, b2 = r1;
-#pragma unroll
-        for (int bit = 0; bit < 6; ++bit) {
-            if (ib & (1 << bit)) f *= b2;
-            b2 *= b2;
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            freq[r] = f;
-            f *= r1;
-        }
-    }
-    float bs[4] = {0.f, 0.f, 0.f, 0.f};
-    if (p.bias) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) bs[r] = fc_to_float(bf16_t{p.bias[hs * 128 + d0 + r]});
-    }
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
         const int m = 16 * mt + rho;
         const bool mvalid = m < p.M;
         const int mm = mvalid ? m : 0;
         const int b = mm / p.A, a = mm - b * p.A;
-        const int pp = p.pos ? p.pos[mm] : p.win_start + a;
+        const int pp = pos_m[mt];
         const bool valid = mvalid && pp >= 0 && pp < G.max_seq;
         float y[4];
 #pragma unroll
@@ -358,10 +375,7 @@ __global__ __launch_bounds__(64) void k_proj_finish(ProjArgs p)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const float other = swap32f(y[r]);
-                const double turns = (double)pp * freq[r];
-                const float fr = (float)(turns - rint(turns));
-                const float c = __builtin_amdgcn_cosf(fr), sn = __builtin_amdgcn_sinf(fr);
-                y[r] = second ? y[r] * c + other * sn : y[r] * c - other * sn;
+                y[r] = second ? y[r] * cs[mt][r].x + other * cs[mt][r].y : y[r] * cs[mt][r].x - other * cs[mt][r].y;
             }
         }
         uint2 w;
@@ -428,6 +442,7 @@ hipError_t fc_launch_project_mfma(const FcGeom &G, const double *inv_freq, const
     (void)inv_freq;
     a.log2_base_64 = G.log_base * 1.4426950408889634074 / 64.0;
     a.partials = (float *)scratch;
+    for (int i = 0; i < 6; ++i) a.rot[i] = exp(-G.log_base * (1 << i) / 64.0);
     const int slots = G.Hq + 2 * G.Hkv;
     const bool no_headsplit = fc_knobs().proj_no_headsplit != 0;  // tuning knob
     if (!no_headsplit && scratch && a.M <= 32 && a.K % HS_K == 0 &&
