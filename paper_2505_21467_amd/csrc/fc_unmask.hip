@@ -117,217 +117,240 @@ __global__ __launch_bounds__(256) void k_unmask_select(const int32_t *__restrict
 
 // -------------------------------------------------------------------------------------------------
 // Guided Diffusion acceptance (paper, section 3.2.2, Algorithm 1; Top-K match and threshold tau from the
-// implementation details).  k_accept_scan: several workgroups per still masked window row, each scans a
-// part of the row's two logit vectors (DLM and AR guide): largest DLM logit, the topk best entries of
-// the AR row (every thread keeps its own best list; the lists are merged by topk rounds of a block-wide
-// arg-max).  k_accept_rowmerge: one wave per row merges the parts the same way and decides whether the
-// row matches.  k_accept_seq: one workgroup per sequence finds the longest matching prefix of the masked
-// rows, fills it (or the first masked row) and lists the rest.
+// implementation details).  A row matches if the DLM's token t is among the topk best AR entries, that is, if fewer than
+// topk AR entries come before (ar[t], t) in the order (larger value first, then smaller id).  No list of the
+// topk best is needed for that:
+//  - k_accept_scan cuts every still masked row's vocabulary into parts, 64 lanes each, and finds each part's best DLM and
+//    best AR entry: two running maxima per lane, so the scan is bound by reading the logits;
+//  - accept_rows (a wave per row) merges the parts, fetches ar[t], and counts.  Only parts whose best AR entry comes
+//    before (ar[t], t) hold any entry that does; with topk of them or more the row does not match, and else
+//    those few parts (usually none or one) are read again and counted exactly.
+// Sorted lists per lane, merged by rounds of arg-max, took 14.8 us for the scan of 32 rows x 2 x 152064 floats (39 MB):
+// some lane of a wave updates its list at almost every step, and the whole wave pays for it.
+// Then the prefix: the longest run of matching masked rows is filled (or the first masked row), the rest listed.
+// Blocks of up to 64 rows do the last two in one kernel, one workgroup per sequence.
 constexpr int ACC_MAXK = 8;
+constexpr int ACC_PARTS = 128;      // at most, per row: two per lane of the merging wave
+constexpr int ACC_FUSED_ROWS = 64;
 
 // (value, id) order: larger value first, then smaller id
 __device__ __forceinline__ bool acc_before(float v1, int i1, float v2, int i2) { return v1 > v2 || (v1 == v2 && i1 < i2); }
 
-// Partial results of one part of a row's vocabulary: DLM (largest, id) and the AR's topk best, best first.
-struct AccPart {
+struct AccPart {  // best entries of one part of a row; (-inf, int max) where there is none
     float dv;
     int di;
-    float tv[ACC_MAXK];
-    int ti[ACC_MAXK];
+    float av;
+    int ai;
 };
 
-// grid (parts, A, B): workgroup (part, a, b) scans entries [part * chunk, (part + 1) * chunk) of row (b, a).
-__global__ __launch_bounds__(256) void k_accept_scan(const float *__restrict__ dlm, const float *__restrict__ ar,
-                                                     const int32_t *__restrict__ pos, int win_start, int A, int V,
-                                                     int chunk, int topk, int mask_id, const int32_t *tokens, int L,
-                                                     AccPart *parts)
+struct AccArgs {
+    const float *dlm, *ar;
+    const int32_t *pos;
+    int32_t *tokens;
+    AccPart *parts;                // [B][A][n_parts]
+    int win_start, A, V, chunk, n_parts, topk, mask_id, L;
+    float tau;
+};
+
+__device__ __forceinline__ int acc_position(const AccArgs &p, int b, int a)
 {
-    __shared__ float s_v[256];
-    __shared__ int s_i[256];
-    __shared__ int s_who;
-    const int part = blockIdx.x, a = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
-    const int p = pos ? pos[(size_t)b * A + a] : win_start + a;
-    const size_t at = (size_t)b * A + a;
-    if (!(p >= 0 && p < L && tokens[(size_t)b * L + p] == mask_id)) return;  // not a candidate: nothing to scan
-    const float *zd = dlm + at * V, *za = ar + at * V;
-    const int v0 = part * chunk, v1 = min(V, v0 + chunk);
-    // DLM arg-max and this thread's topk best AR entries (sorted best first)
-    float dv = -INFINITY;
-    int di = 0x7fffffff;
-    float tv[ACC_MAXK];
-    int ti[ACC_MAXK];
-#pragma unroll
-    for (int r = 0; r < ACC_MAXK; ++r) {
-        tv[r] = -INFINITY;
-        ti[r] = 0x7fffffff;
-    }
-    float worst_v = -INFINITY;  // the list's last kept entry: most elements fail against it and cost two compares
-    int worst_i = 0x7fffffff;
-    auto visit = [&](float d, float x, int v) {
-        if (acc_before(d, v, dv, di)) {
-            dv = d;
-            di = v;
-        }
-        if (!acc_before(x, v, worst_v, worst_i)) return;
-        int xi = v;
-#pragma unroll
-        for (int r = 0; r < ACC_MAXK; ++r) {  // insertion into the sorted list
-            if (r < topk && acc_before(x, xi, tv[r], ti[r])) {
-                const float t0 = tv[r];
-                const int t1 = ti[r];
-                tv[r] = x;
-                ti[r] = xi;
-                x = t0;
-                xi = t1;
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < ACC_MAXK; ++r)
-            if (r == topk - 1) {
-                worst_v = tv[r];
-                worst_i = ti[r];
-            }
-    };
-    // rows of V floats are 16-byte aligned when V is a multiple of 4 (chunk always is): four entries per load
-    if ((V & 3) == 0) {
-        for (int v = v0 + 4 * tid; v < v1; v += 1024) {
-            const float4 d4 = *(const float4 *)(zd + v), x4 = *(const float4 *)(za + v);
-            visit(d4.x, x4.x, v);
-            visit(d4.y, x4.y, v + 1);
-            visit(d4.z, x4.z, v + 2);
-            visit(d4.w, x4.w, v + 3);
-        }
-    } else {
-        for (int v = v0 + tid; v < v1; v += 256) visit(zd[v], za[v], v);
-    }
-    // block arg-max of the DLM part
-    s_v[tid] = dv;
-    s_i[tid] = di;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if (tid < off && acc_before(s_v[tid + off], s_i[tid + off], s_v[tid], s_i[tid])) {
-            s_v[tid] = s_v[tid + off];
-            s_i[tid] = s_i[tid + off];
-        }
-        __syncthreads();
-    }
-    AccPart *out = parts + at * gridDim.x + part;
-    if (tid == 0) {
-        out->dv = s_v[0];
-        out->di = s_i[0];
-    }
-    __syncthreads();
-    // topk rounds: the best head among the threads' lists is the next entry of the part's list
-    for (int r = 0; r < topk; ++r) {
-        s_v[tid] = tv[0];
-        s_i[tid] = ti[0];
-        __syncthreads();
-        for (int off = 128; off > 0; off >>= 1) {
-            if (tid < off && acc_before(s_v[tid + off], s_i[tid + off], s_v[tid], s_i[tid])) {
-                s_v[tid] = s_v[tid + off];
-                s_i[tid] = s_i[tid + off];
-            }
-            __syncthreads();
-        }
-        const float bv = s_v[0];
-        const int bi = s_i[0];
-        if (tid == 0) {
-            out->tv[r] = bv;  // (-inf, int max) once the part is exhausted
-            out->ti[r] = bi;
-            s_who = -1;
-        }
-        __syncthreads();
-        if (ti[0] == bi && bi != 0x7fffffff) s_who = tid;  // ids are unique: one thread owns the winner
-        __syncthreads();
-        if (s_who == tid) {  // pop the head
-#pragma unroll
-            for (int q = 0; q + 1 < ACC_MAXK; ++q) {
-                tv[q] = tv[q + 1];
-                ti[q] = ti[q + 1];
-            }
-            tv[ACC_MAXK - 1] = -INFINITY;
-            ti[ACC_MAXK - 1] = 0x7fffffff;
-        }
-        __syncthreads();
-    }
+    return p.pos ? p.pos[(size_t)b * p.A + a] : p.win_start + a;
 }
 
-// One wave per row merges the parts (at most 64, one per lane) and decides whether the row matches.
-__global__ __launch_bounds__(64) void k_accept_rowmerge(const AccPart *__restrict__ parts, int n_parts,
-                                                        const int32_t *__restrict__ pos, int win_start, int A, int topk,
-                                                        float tau, int mask_id, const int32_t *tokens, int L,
-                                                        int32_t *row_tok, int32_t *row_match)
+// grid (parts / 4, A, B): 64 lanes scan entries [part * chunk, (part + 1) * chunk) of row (b, a), normally in one step
+// with every load in flight at once.
+constexpr int ACC_LANES = 64, ACC_VEC_LOADS = 5;
+constexpr int ACC_STEP = ACC_LANES * 4 * ACC_VEC_LOADS;  // entries per step with 16-byte loads
+template <bool VEC>
+__global__ __launch_bounds__(256) void k_accept_scan(AccArgs p)
 {
-    const int a = blockIdx.x, b = blockIdx.y, lane = threadIdx.x;
-    const int p = pos ? pos[(size_t)b * A + a] : win_start + a;
-    const size_t at = (size_t)b * A + a;
-    if (!(p >= 0 && p < L && tokens[(size_t)b * L + p] == mask_id)) {
-        if (lane == 0) {
-            row_tok[at] = -1;
-            row_match[at] = -1;
+    const int a = blockIdx.y, b = blockIdx.z, l = threadIdx.x % ACC_LANES;
+    const int part = blockIdx.x * (256 / ACC_LANES) + threadIdx.x / ACC_LANES;
+    const size_t at = (size_t)b * p.A + a;
+    const int ps = acc_position(p, b, a);
+    if (!(ps >= 0 && ps < p.L && p.tokens[(size_t)b * p.L + ps] == p.mask_id)) return;  // not a candidate: nothing to scan
+    const float *zd = p.dlm + at * p.V, *za = p.ar + at * p.V;
+    const int v0 = min(part, p.n_parts) * p.chunk, v1 = min(p.V, v0 + p.chunk);
+    constexpr int W = VEC ? 4 : 1, U = VEC ? ACC_VEC_LOADS : 10;  // entries per lane and load; loads of each array in flight
+    float dv = -INFINITY, av = -INFINITY;
+    int di = 0x7fffffff, ai = 0x7fffffff;
+    for (int s0 = v0 + l * W; s0 < v1; s0 += ACC_LANES * W * U) {
+        float d[U][W], x[U][W];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int v = min(s0 + u * ACC_LANES * W, p.V - W);  // (past the end: re-read and dropped)
+            if constexpr (VEC) {
+                *(float4 *)d[u] = *(const float4 *)(zd + v);
+                *(float4 *)x[u] = *(const float4 *)(za + v);
+            } else {
+                d[u][0] = zd[v];
+                x[u][0] = za[v];
+            }
         }
-        return;
-    }
-    float dv = -INFINITY;
-    int di = 0x7fffffff;
-    float tv[ACC_MAXK];
-    int ti[ACC_MAXK];
 #pragma unroll
-    for (int r = 0; r < ACC_MAXK; ++r) {
-        tv[r] = -INFINITY;
-        ti[r] = 0x7fffffff;
-    }
-    if (lane < n_parts) {
-        const AccPart *pt = parts + at * n_parts + lane;
-        dv = pt->dv;
-        di = pt->di;
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int r = 0; r < ACC_MAXK; ++r)
-            if (r < topk) {
-                tv[r] = pt->tv[r];
-                ti[r] = pt->ti[r];
+            for (int e = 0; e < W; ++e) {
+                const int v = s0 + u * ACC_LANES * W + e;
+                if (v < v1 && acc_before(d[u][e], v, dv, di)) {
+                    dv = d[u][e];
+                    di = v;
+                }
+                if (v < v1 && acc_before(x[u][e], v, av, ai)) {
+                    av = x[u][e];
+                    ai = v;
+                }
             }
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        const float v2 = __shfl_xor(dv, off, 64);
-        const int i2 = __shfl_xor(di, off, 64);
-        if (acc_before(v2, i2, dv, di)) {
-            dv = v2;
+#pragma unroll
+    for (int off = ACC_LANES / 2; off > 0; off >>= 1) {
+        const float d2 = __shfl_xor(dv, off, 64), a2 = __shfl_xor(av, off, 64);
+        const int i2 = __shfl_xor(di, off, 64), j2 = __shfl_xor(ai, off, 64);
+        if (acc_before(d2, i2, dv, di)) {
+            dv = d2;
             di = i2;
         }
-    }
-    bool in_top = false;
-    float za_max = 0.f;
-    for (int r = 0; r < topk; ++r) {
-        float bv = tv[0];
-        int bi = ti[0];
-        for (int off = 32; off > 0; off >>= 1) {
-            const float v2 = __shfl_xor(bv, off, 64);
-            const int i2 = __shfl_xor(bi, off, 64);
-            if (acc_before(v2, i2, bv, bi)) {
-                bv = v2;
-                bi = i2;
-            }
+        if (acc_before(a2, j2, av, ai)) {
+            av = a2;
+            ai = j2;
         }
-        if (r == 0) za_max = bv;
-        if (bi == di) in_top = true;
-        if (ti[0] == bi && bi != 0x7fffffff) {  // this lane owns the winner: pop
+    }
+    if (l == 0 && part < p.n_parts) p.parts[at * p.n_parts + part] = AccPart{dv, di, av, ai};
+}
+
+// One wave decides rows a0, a0 + step, .. (N of them at most) of sequence b: the DLM's token, and 1 / 0 for a match or
+// none, -1 for a row that is not a candidate.  The rows' memory round trips run together.
+template <int N>
+__device__ __forceinline__ void accept_rows(const AccArgs &p, int b, int a0, int step, int lane, int (&tok)[N], int (&match)[N])
+{
+    AccPart pt[N][ACC_PARTS / 64];
+    float z[N], zmax[N];
+    bool cand[N];
 #pragma unroll
-            for (int q = 0; q + 1 < ACC_MAXK; ++q) {
-                tv[q] = tv[q + 1];
-                ti[q] = ti[q + 1];
-            }
-            tv[ACC_MAXK - 1] = -INFINITY;
-            ti[ACC_MAXK - 1] = 0x7fffffff;
-        }
+    for (int n = 0; n < N; ++n) {
+        const int a = min(a0 + n * step, p.A - 1);
+        const int ps = acc_position(p, b, a);
+        const bool in = ps >= 0 && ps < p.L;
+        cand[n] = p.tokens[(size_t)b * p.L + (in ? ps : 0)] == p.mask_id && in && a0 + n * step < p.A;
+#pragma unroll
+        for (int g = 0; g < ACC_PARTS / 64; ++g)
+            pt[n][g] = 64 * g + lane < p.n_parts ? p.parts[((size_t)b * p.A + a) * p.n_parts + 64 * g + lane]
+                                                 : AccPart{-INFINITY, 0x7fffffff, -INFINITY, 0x7fffffff};
     }
-    if (lane == 0) {
-        const float thr = tau * za_max;
-        row_tok[at] = di;
-        row_match[at] = (in_top && (!(tau > 0.0f) || dv > thr)) ? 1 : 0;
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        float dv = pt[n][0].dv;
+        int di = pt[n][0].di;
+        float am = pt[n][0].av;
+#pragma unroll
+        for (int g = 1; g < ACC_PARTS / 64; ++g) {
+            if (acc_before(pt[n][g].dv, pt[n][g].di, dv, di)) {
+                dv = pt[n][g].dv;
+                di = pt[n][g].di;
+            }
+            am = fmaxf(am, pt[n][g].av);
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const float v2 = __shfl_xor(dv, off, 64);
+            const int i2 = __shfl_xor(di, off, 64);
+            am = fmaxf(am, __shfl_xor(am, off, 64));
+            if (acc_before(v2, i2, dv, di)) {
+                dv = v2;
+                di = i2;
+            }
+        }
+        tok[n] = di;
+        zmax[n] = am;
+        match[n] = !cand[n] ? -1 : (!(p.tau > 0.0f) || dv > p.tau * am) ? 1 : 0;
+        // the AR's value of the DLM's token (rows that are no candidates hold anything: stay inside the row)
+        z[n] = p.ar[((size_t)b * p.A + min(a0 + n * step, p.A - 1)) * p.V + (di >= 0 && di < p.V ? di : 0)];
+    }
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        if (match[n] != 1) continue;  // wave-uniform
+        uint64_t ahead[ACC_PARTS / 64];
+        int count = 0;
+#pragma unroll
+        for (int g = 0; g < ACC_PARTS / 64; ++g) {
+            ahead[g] = __ballot(acc_before(pt[n][g].av, pt[n][g].ai, z[n], tok[n]));
+            count += __builtin_popcountll(ahead[g]);
+        }
+        if (count > 0 && count < p.topk) {
+            // at least one entry in each of these parts: count them all
+            const float *za = p.ar + ((size_t)b * p.A + a0 + n * step) * p.V;
+            count = 0;
+#pragma unroll
+            for (int g = 0; g < ACC_PARTS / 64; ++g)
+                for (uint64_t w = ahead[g]; w && count < p.topk; w &= w - 1) {
+                    const int v0 = (64 * g + __builtin_ctzll(w)) * p.chunk, v1 = min(p.V, v0 + p.chunk);
+                    for (int v = v0; v < v1; v += ACC_STEP) {  // a part is one step: every load in flight at once
+                        float x[ACC_STEP / 64];
+#pragma unroll
+                        for (int u = 0; u < ACC_STEP / 64; ++u) x[u] = za[min(v + 64 * u + lane, p.V - 1)];
+#pragma unroll
+                        for (int u = 0; u < ACC_STEP / 64; ++u) {
+                            const int vv = v + 64 * u + lane;
+                            count += __builtin_popcountll(__ballot(vv < v1 && acc_before(x[u], vv, z[n], tok[n])));
+                        }
+                    }
+                }
+        }
+        if (count >= p.topk) match[n] = 0;
     }
 }
 
+// Rows of a block that is too long for the fused kernel: one wave per row.
+__global__ __launch_bounds__(64) void k_accept_rowmerge(AccArgs p, int32_t *row_tok, int32_t *row_match)
+{
+    const int a = blockIdx.x, b = blockIdx.y;
+    int tok[1], match[1];
+    accept_rows<1>(p, b, a, 1, threadIdx.x, tok, match);
+    if (threadIdx.x == 0) {
+        row_tok[(size_t)b * p.A + a] = tok[0];
+        row_match[(size_t)b * p.A + a] = match[0];
+    }
+}
+
+// Blocks of at most 64 rows: one workgroup per sequence, N rows per wave; its first wave, a lane per row, finds the prefix.
+template <int N>
+__global__ __launch_bounds__(1024) void k_accept_block(AccArgs p, int32_t *n_accept, int32_t *pos_next, int32_t *count_next)
+{
+    __shared__ int s_tok[ACC_FUSED_ROWS], s_match[ACC_FUSED_ROWS];
+    const int b = blockIdx.x, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = blockDim.x >> 6;
+    int tok[N], match[N];
+    accept_rows<N>(p, b, wave, n_waves, lane, tok, match);
+    if (lane == 0) {
+#pragma unroll
+        for (int n = 0; n < N; ++n)
+            if (wave + n * n_waves < p.A) {
+                s_tok[wave + n * n_waves] = tok[n];
+                s_match[wave + n * n_waves] = match[n];
+            }
+    }
+    __syncthreads();
+    if (wave) return;
+    const bool row = lane < p.A;
+    const int mt = row ? s_match[lane] : -1;
+    const uint64_t masked = __ballot(mt >= 0), missed = __ballot(mt == 0);
+    const int m = __builtin_popcountll(masked);
+    const int k = missed ? __builtin_popcountll(masked & ((missed & -missed) - 1)) : m;  // longest matching prefix
+    const int n = m == 0 ? 0 : (k > 0 ? k : 1);
+    const int j = __builtin_popcountll(masked & (((uint64_t)1 << lane) - 1));           // index among the masked rows
+    if (mt >= 0) {
+        const int ps = acc_position(p, b, lane);
+        if (j < n) p.tokens[(size_t)b * p.L + ps] = s_tok[lane];
+        else pos_next[(size_t)b * p.A + (j - n)] = ps;
+    }
+    if (row && lane >= m - n) pos_next[(size_t)b * p.A + lane] = -1;
+    if (lane == 0) {
+        n_accept[b] = n;
+        count_next[b] = m - n;
+    }
+}
+
+// Prefix of a longer block, one workgroup per sequence over the rows' results.
 __global__ __launch_bounds__(256) void k_accept_seq(const int32_t *__restrict__ row_tok, const int32_t *__restrict__ row_match,
                                                     const int32_t *__restrict__ pos, int win_start, int A,
                                                     int32_t *tokens, int L, int32_t *n_accept, int32_t *pos_next,
@@ -409,14 +432,14 @@ __global__ __launch_bounds__(256) void k_gather_rows(const uint4 *__restrict__ t
 
 }  // namespace
 
-// Parts a row's vocabulary is cut into: several workgroups per compute unit (measured: 20.7 us with 2048
-// workgroups, 26.6 with 512, 37.5 with 256 for a 32-row block at vocabulary 152064), chunks of whole float4s.
+// Parts a row's vocabulary is cut into: one step of the scan each (32 rows x 152064: 11 us for 39 MB),
+// at most two per lane of the merging wave; chunks of whole float4s.
 int fc_accept_parts(int B, int A, int V)
 {
-    const int target = fc_knobs().accept_wgs > 0 ? fc_knobs().accept_wgs : 2048;  // tuning knob
-    int64_t parts = (target > 0 ? target : 2048) / ((int64_t)B * A);
-    if (parts > 64) parts = 64;
-    if (parts > (V + 2047) / 2048) parts = (V + 2047) / 2048;  // at least 2048 entries per part
+    int64_t parts = (V + ACC_STEP - 1) / ACC_STEP;
+    if (fc_knobs().accept_wgs > 0) parts = fc_knobs().accept_wgs / ((int64_t)B * A);  // tuning knob
+    if (parts > ACC_PARTS) parts = ACC_PARTS;
+    if (parts > V) parts = V;
     if (parts < 1) parts = 1;
     return (int)parts;
 }
@@ -431,17 +454,34 @@ hipError_t fc_launch_guided_accept(const float *dlm, const float *ar, const int3
                                    int32_t *pos_next, int32_t *count_next, void *workspace, hipStream_t s)
 {
     if (topk < 1 || topk > ACC_MAXK || !workspace) return hipErrorInvalidValue;
-    const int n_parts = fc_accept_parts(B, A, V);
-    const int chunk = (((V + n_parts - 1) / n_parts) + 3) & ~3;
-    int32_t *row_tok = (int32_t *)workspace, *row_match = row_tok + (size_t)B * A;
-    AccPart *parts = (AccPart *)(row_match + (size_t)B * A);
-    k_accept_scan<<<dim3((unsigned)n_parts, (unsigned)A, (unsigned)B), dim3(256), 0, s>>>(dlm, ar, pos, win_start, A, V,
-                                                                                          chunk, topk, mask_id, tokens, L,
-                                                                                          parts);
-    k_accept_rowmerge<<<dim3((unsigned)A, (unsigned)B), dim3(64), 0, s>>>(parts, n_parts, pos, win_start, A, topk, tau,
-                                                                          mask_id, tokens, L, row_tok, row_match);
-    k_accept_seq<<<dim3((unsigned)B), dim3(256), 0, s>>>(row_tok, row_match, pos, win_start, A, tokens, L, n_accept,
-                                                         pos_next, count_next);
+    AccArgs p;
+    p.dlm = dlm;
+    p.ar = ar;
+    p.pos = pos;
+    p.tokens = tokens;
+    p.win_start = win_start;
+    p.A = A;
+    p.V = V;
+    p.n_parts = fc_accept_parts(B, A, V);
+    p.chunk = (((V + p.n_parts - 1) / p.n_parts) + 3) & ~3;
+    p.topk = topk;
+    p.mask_id = mask_id;
+    p.L = L;
+    p.tau = tau;
+    p.parts = (AccPart *)workspace;
+    int32_t *row_tok = (int32_t *)(p.parts + (size_t)B * A * p.n_parts), *row_match = row_tok + (size_t)B * A;
+    const dim3 grid((unsigned)((p.n_parts + 256 / ACC_LANES - 1) / (256 / ACC_LANES)), (unsigned)A, (unsigned)B);
+    // rows of V floats are 16-byte aligned when V is a multiple of 4
+    if ((V & 3) == 0) k_accept_scan<true><<<grid, dim3(256), 0, s>>>(p);
+    else k_accept_scan<false><<<grid, dim3(256), 0, s>>>(p);
+    if (A <= 16) k_accept_block<1><<<dim3((unsigned)B), dim3((unsigned)A * 64), 0, s>>>(p, n_accept, pos_next, count_next);
+    else if (A <= 32) k_accept_block<2><<<dim3((unsigned)B), dim3(1024), 0, s>>>(p, n_accept, pos_next, count_next);
+    else if (A <= ACC_FUSED_ROWS) k_accept_block<4><<<dim3((unsigned)B), dim3(1024), 0, s>>>(p, n_accept, pos_next, count_next);
+    else {
+        k_accept_rowmerge<<<dim3((unsigned)A, (unsigned)B), dim3(64), 0, s>>>(p, row_tok, row_match);
+        k_accept_seq<<<dim3((unsigned)B), dim3(256), 0, s>>>(row_tok, row_match, pos, win_start, A, tokens, L, n_accept,
+                                                             pos_next, count_next);
+    }
     return hipGetLastError();
 }
 

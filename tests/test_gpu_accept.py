@@ -1,0 +1,31 @@
+"""GPU parity of the guided acceptance where its parts and its row counts have edges: vocabularies of one part, of
+several and of many steps per part, one to four rows per wave and the kernel for longer blocks; ties, ranks
+around topk, and a guide that agrees almost everywhere, so that long prefixes are decided by every part."""
+import numpy as np
+import pytest
+
+from oracle import fc_oracle as orc
+from tests.test_gpu_unmask import _gpu_accept
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,A,V", [(1, 1, 1), (2, 16, 1279), (1, 17, 1281), (2, 33, 6429), (1, 64, 5120), (1, 65, 2563), (1, 3, 200001)])
+def test_long_prefixes_are_bit_exact(B, A, V):
+    print("[case]", B, A, V, flush=True)
+    rng = np.random.default_rng(A * 131 + V)
+    MASK, L = 300000, 2 * A
+    for topk, tau, noise, ties in ((1, 0.0, 0.02, False), (2, 0.5, 0.1, True), (8, 0.0, 0.4, False), (3, 1.0, 0.1, True)):
+        topk = min(topk, V)
+        dlm = rng.normal(0, 3, (B, A, V)).astype(np.float32)
+        ar = (dlm + rng.normal(0, noise, (B, A, V))).astype(np.float32)
+        if ties:
+            dlm, ar = np.round(dlm), np.round(ar)
+        pos = np.stack([np.sort(rng.choice(L, A, replace=False)) for _ in range(B)]).astype(np.int32)
+        tokens = np.full((B, L), MASK, np.int32)
+        tokens[rng.random((B, L)) < 0.2] = 0
+        want_t = tokens.copy()
+        want = orc.guided_accept(dlm, ar, pos, topk, tau, MASK, want_t)
+        got_t, n, pn, cn = _gpu_accept(dlm, ar, pos, 0, topk, tau, MASK, tokens)
+        assert np.array_equal(n, want[0]) and np.array_equal(got_t, want_t)
+        assert np.array_equal(pn, want[1]) and np.array_equal(cn, want[2])
