@@ -146,7 +146,87 @@ FcKnobs &knobs_mut()
 
 const FcKnobs &fc_knobs() { return knobs_mut(); }
 
-FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len)
+namespace {
+
+// Row tiles and waves per attention workgroup, with the measured time of one 64-key stage (us).  Eight-wave
+// workgroups fill a compute unit; two of four waves share one, a stage of each then taking 1.476 times as long.
+struct AttnShape {
+    int R, W;
+    double stage;
+};
+const AttnShape ATTN_SHAPES[] = {{8, 8, 1.174}, {4, 8, 0.826}, {2, 8, 0.706}, {4, 4, 1.179}, {2, 4, 0.939}};
+
+// Estimated time of the attention call (us), fitted to 2600 measured (shape, plan) pairs (1..8 sequences, 2..1000
+// window rows, 100..17000 keys from HBM; rms error 9 %): a fixed part and a workgroup's start and stages per round,
+// the bandwidth of the stream (5.9 TB/s) and of its copies into the compute units (16 TB/s), joined by a
+// 5-norm, and the merge kernel.  The plans it picks are within 3 % of the best measured ones in the mean; choosing
+// tiles by the row count and splits by "nearest to 256 workgroups" was 14 % off, mostly through grids a little over
+// one round.
+double attn_cost(const AttnShape &sh, int64_t pairs, int row_tiles, int kv_len, int64_t splits, int64_t stages)
+{
+    const int64_t n = pairs * ((row_tiles + sh.R - 1) / sh.R) * splits, at_once = sh.W == 8 ? 256 : 512;
+    const int64_t rounds = n / at_once, rest = n % at_once;
+    const double start = sh.W == 8 ? 4.013 : 2.418;
+    const double one = start + stages * sh.stage;                               // a workgroup alone on its compute unit
+    const double full = sh.W == 8 ? one : start + stages * sh.stage * 1.476;
+    double wg = rounds * full;
+    if (rest) {
+        const double last = sh.W == 8 || rest <= 256 ? one : one + (full - one) * (double)(rest - 256) / 256.0;
+        wg += last * (rounds ? 0.966 : 1.0);
+    }
+    const double hbm = (double)pairs * kv_len * 512.0 / 5.916e6, fill = (double)n * stages * 32768.0 / 16.2e6;
+    auto p5 = [](double v) { return v * v * v * v * v; };
+    double t = 3.6 + pow(p5(wg) + p5(hbm) + p5(fill), 0.2);
+    if (splits > 1) t += 0.044 * splits + (double)pairs * row_tiles * splits * 8704.0 / 1.52e6;
+    return t > 7.4 ? t : 7.4;
+}
+
+// Most key ranges any plan for this many row tiles may use, whatever the length up to by_len (the workspace is sized by
+// it): one round of workgroups in some shape, or about 32 MB of partial results where a
+// round has few ranges.
+int64_t attn_splits_bound(int64_t pairs, int row_tiles, int64_t by_len)
+{
+    int64_t bound = 1;
+    for (const AttnShape &sh : ATTN_SHAPES) {
+        const int64_t b = (sh.W == 8 ? 256 : 512) / (pairs * ((row_tiles + sh.R - 1) / sh.R));
+        if (b > bound) bound = b;
+    }
+    if (pairs * row_tiles >= 200 && 3800 / (pairs * row_tiles) > bound) bound = 3800 / (pairs * row_tiles);
+    if (bound > 96) bound = 96;  // (more never came out best)
+    return bound < by_len ? bound : by_len;
+}
+
+void set_attn_plan(FcAttnPlan &p, int R, int W, int64_t splits, int64_t n_stages)
+{
+    p.tiles_per_wg = R;
+    p.waves = W;
+    const int64_t stages = (n_stages + splits - 1) / splits;
+    p.keys_per_split = (int)(stages * 64);
+    p.splits = (int)((n_stages + stages - 1) / stages);
+}
+
+// Given tiles and the split that comes nearest to a given number of workgroups (0 = by the row count; one round).
+FcAttnPlan plan_fixed_tiles(FcAttnPlan p, int R, int W, int64_t target, int64_t pairs, int64_t n_stages, int64_t by_len)
+{
+    if (W != 4) W = 8;
+    if (R != 2 && R != 4 && R != 8) R = p.row_tiles <= 2 ? 2 : (p.row_tiles <= 7 ? 4 : 8);
+    if (W == 4 && R == 8) R = 4;
+    if (target <= 0) target = W == 4 ? 512 : 256;
+    const int64_t base = pairs * ((p.row_tiles + R - 1) / R);
+    int64_t splits = (target + base / 2) / base;
+    if (splits > by_len) splits = by_len;
+    if (splits < 1) splits = 1;
+    set_attn_plan(p, R, W, splits, n_stages);
+    if (p.splits_bound < (int)splits) p.splits_bound = (int)splits;
+    return p;
+}
+
+// Bytes of partial results per row tile and key range: 32 x 128 half floats and 32 x 4 floats of row state.
+constexpr size_t ATTN_PART_BYTES = 32 * (128 * 2 + 4 * sizeof(float));
+
+}  // namespace
+
+FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len, size_t cap)
 {
     FcAttnPlan p;
     memset(&p, 0, sizeof p);
@@ -176,56 +256,46 @@ FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len)
     }
     p.kind = 1;
     p.row_tiles = (int)(((int64_t)g * A + 31) / 32);
-    // Row tiles per workgroup: 2 (four waves share one tile pair), 4 or 8 (each wave its own pair).
-    // One workgroup per compute unit (its LDS ring takes 128 KB), so aim for one wave of them.
-    const int r_default = p.row_tiles <= 2 ? 2 : (p.row_tiles <= 7 ? 4 : 8);
-    int R = r_default, W = 8, target = 256;
-    {
-        // A short cache cannot give 256 eight-wave workgroups (a split takes at least 128 keys): with
-        // 3..7 row tiles, four-wave workgroups of two tiles, two per compute unit, then fill the chip
-        // better (one sequence, 28/4 heads, 32 rows: 10.7 against 12.7 us at 1056 keys, 11.4 against
-        // 13.9 at 2112; from about 4000 keys on the eight-wave shape is as fast or faster).
-        const int64_t n_rg8 = (p.row_tiles + r_default - 1) / r_default;
-        const int64_t base8 = (int64_t)cfg.batch * cfg.n_kv_heads * n_rg8;
-        const int64_t st = (kv_len + 63) / 64, by_len8 = st / 2 > 1 ? st / 2 : 1;
-        int64_t sp8 = (256 + base8 / 2) / base8;
-        if (sp8 > by_len8) sp8 = by_len8;
-        if (sp8 < 1) sp8 = 1;
-        if (r_default == 4 && base8 * sp8 < 256) {
-            R = 2;
-            W = 4;
-        }
-    }
-    {
-        const FcKnobs &kn = fc_knobs();
-        if (kn.attn_r > 0 && kn.attn_w > 0) {
-            R = kn.attn_r;
-            W = kn.attn_w;
-        }
-        if (kn.attn_wgs > 0) target = kn.attn_wgs;
-    }
-    if (R != 2 && R != 4 && R != 8) R = r_default;
-    if (W != 4 && W != 8) W = 8;
-    if (W == 4) {  // four-wave workgroups: two or four tiles, two workgroups per compute unit
-        if (R == 8) R = 4;
-        if (target == 256) target = 512;
-    }
-    p.tiles_per_wg = R;
-    p.waves = W;  // one row tile per wave group either way
-    const int64_t n_rg = (p.row_tiles + R - 1) / R;
-    const int64_t base = (int64_t)cfg.batch * cfg.n_kv_heads * n_rg;
-    const int n_stages = (kv_len + 63) / 64;
-    // enough workgroups to fill the chip; rounded to nearest, so that a grid that nearly fills it
-    // already is not doubled (the partial results of a split are extra traffic)
-    int64_t splits = (target + base / 2) / base;
+    const int64_t pairs = (int64_t)cfg.batch * cfg.n_kv_heads;
+    const int64_t n_stages = ((int64_t)kv_len + 63) / 64;
     const int64_t by_len = n_stages / 2 > 1 ? n_stages / 2 : 1;  // at least 128 keys per split
-    if (splits > by_len) splits = by_len;
-    if (splits < 1) splits = 1;
-    p.splits_bound = (int)splits;
-    const int stages_per_split = (int)((n_stages + splits - 1) / splits);
-    p.keys_per_split = stages_per_split * 64;
-    p.splits = (n_stages + stages_per_split - 1) / stages_per_split;
+    const FcKnobs &kn = fc_knobs();
+    int64_t bound = attn_splits_bound(pairs, p.row_tiles, by_len);
+    const int64_t within = (int64_t)(cap / ((size_t)pairs * p.row_tiles * ATTN_PART_BYTES));
+    if (bound > within) bound = within > 1 ? within : 1;
+    p.splits_bound = (int)bound;
+    if (kn.attn_r > 0 || kn.attn_wgs > 0) return plan_fixed_tiles(p, kn.attn_r, kn.attn_w, kn.attn_wgs, pairs, n_stages, by_len);
+    double best = 1e30;
+    for (const AttnShape &sh : ATTN_SHAPES) {
+        const int64_t base = pairs * ((p.row_tiles + sh.R - 1) / sh.R), at_once = sh.W == 8 ? 256 : 512;
+        // the first few splits, whole rounds of workgroups, and steps of a third between
+        static const int STEPS[] = {1, 2, 3, 4, 5, 6, 7, 8, 12, 16, 24, 32, 48, 64, 96};
+        constexpr int NS = sizeof STEPS / sizeof STEPS[0];
+        for (int c = 0; c < NS + 3; ++c) {
+            const int64_t splits = c < NS ? STEPS[c] : at_once * (c - NS + 1) / base;
+            if (splits < 1 || splits > p.splits_bound) continue;
+            const int64_t stages = (n_stages + splits - 1) / splits;
+            const double t = attn_cost(sh, pairs, p.row_tiles, kv_len, (n_stages + stages - 1) / stages, stages);
+            if (t < best * (1 - 1e-9)) {
+                best = t;
+                set_attn_plan(p, sh.R, sh.W, splits, n_stages);
+            }
+        }
+    }
     return p;
+}
+
+// One round of eight-wave workgroups, tiles by the row count.
+static FcAttnPlan fc_plan_attention_default(const fc_config &cfg, int A, int kv_len)
+{
+    FcAttnPlan p;
+    memset(&p, 0, sizeof p);
+    p.splits = p.splits_bound = 1;
+    if (cfg.dtype != FC_BF16 || cfg.head_dim != 128) return p;
+    p.kind = 1;
+    p.row_tiles = (int)(((int64_t)(cfg.n_q_heads / cfg.n_kv_heads) * A + 31) / 32);
+    const int64_t n_stages = ((int64_t)kv_len + 63) / 64;
+    return plan_fixed_tiles(p, 0, 8, 0, (int64_t)cfg.batch * cfg.n_kv_heads, n_stages, n_stages / 2 > 1 ? n_stages / 2 : 1);
 }
 
 size_t fc_plan_workspace(const fc_config &cfg, const FcAttnPlan &p, int A)
@@ -235,16 +305,22 @@ size_t fc_plan_workspace(const fc_config &cfg, const FcAttnPlan &p, int A)
     if (p.kind == 0)  // per (workgroup tile, split): rows x Dh partial outputs + rows x 2 floats of row state
         return (size_t)cfg.batch * cfg.n_kv_heads * ((p.row_tiles + p.tiles_per_wg - 1) / p.tiles_per_wg) * p.splits_bound *
                (16 * p.tiles_per_wg) * (cfg.head_dim + 2) * sizeof(float);
-    // per (32-row tile, split): 32 x Dh partial outputs as half floats + 32 x 4 floats of row state
-    return (size_t)cfg.batch * cfg.n_kv_heads * p.row_tiles * p.splits_bound * 32 *
-           (cfg.head_dim * 2 + 4 * sizeof(float));
+    return (size_t)cfg.batch * cfg.n_kv_heads * p.row_tiles * p.splits_bound * ATTN_PART_BYTES;
 }
 
 // The plan of one call that brings `bytes` of workspace.  The kernel of kind 0 cuts the keys only to fill the
 // chip; without the space for it it runs uncut.
-static FcAttnPlan plan_with_workspace(const fc_config &cfg, int A, int kv_len, size_t bytes)
+// `last` (of a cache handle) keeps the plan of the last shape: a step asks for the same one in every layer.
+static FcAttnPlan plan_with_workspace(const fc_config &cfg, FcLastPlan &last, int A, int kv_len, size_t bytes,
+                                      size_t cap = SIZE_MAX)
 {
-    FcAttnPlan p = fc_plan_attention(cfg, A, kv_len);
+    if (last.A != A || last.kv_len != kv_len || last.knobs != fc_knobs().version) {
+        last.plan = fc_plan_attention(cfg, A, kv_len, cap);
+        last.A = A;
+        last.kv_len = kv_len;
+        last.knobs = fc_knobs().version;
+    }
+    FcAttnPlan p = last.plan;
     if (p.kind == 0 && fc_plan_workspace(cfg, p, A) > bytes) {
         p.splits = p.splits_bound = 1;
         p.keys_per_split = (kv_len + 31) / 32 * 32;
@@ -260,6 +336,7 @@ fc_status fc_tuning_set(const char *name, const char *value)
 {
     if (!name) return fail(FC_ERR_INVALID_ARG, "name is NULL");
     if (!knob_apply(knobs_mut(), name, value)) return fail(FC_ERR_INVALID_ARG, "unknown tuning knob %s", name);
+    ++knobs_mut().version;
     return FC_OK;
 }
 
@@ -307,6 +384,8 @@ fc_status fc_cache_alloc(const fc_config *cfg, void *k_storage, void *v_storage,
     c->v = v_storage;
     c->owned = false;
     c->ws_A = c->ws_d_ff = 0;
+    memset(&c->last_plan, 0, sizeof c->last_plan);
+    memset(&c->last_static, 0, sizeof c->last_static);
     for (int i = 0; i < 64; ++i)
         c->inv_freq[i] = i < cfg->head_dim / 2 ? pow((double)cfg->rope_base, -2.0 * i / cfg->head_dim) : 0.0;
     if (!k_storage) {
@@ -458,12 +537,36 @@ size_t fc_workspace_bytes(const fc_config *cfg, int32_t max_rows)
 {
     if (check_config(cfg) != FC_OK || max_rows < 1) return 0;
     size_t best = 0;
+    const bool direct = cfg->dtype == FC_BF16 && cfg->head_dim == 128 && fc_knobs().attn_r <= 0 && fc_knobs().attn_wgs <= 0;
+    const int64_t pairs = (int64_t)cfg->batch * cfg->n_kv_heads, g = cfg->n_q_heads / cfg->n_kv_heads;
+    const int64_t n_stages = ((int64_t)cfg->max_seq + 63) / 64;
     for (int a = 1; a <= max_rows; ++a) {
-        const FcAttnPlan p = fc_plan_attention(*cfg, a, cfg->max_seq);
+        FcAttnPlan p;
+        if (direct) {  // all that counts is the bound on the key ranges
+            memset(&p, 0, sizeof p);
+            p.kind = 1;
+            p.row_tiles = (int)((g * a + 31) / 32);
+            p.splits_bound = (int)attn_splits_bound(pairs, p.row_tiles, n_stages / 2 > 1 ? n_stages / 2 : 1);
+        } else {
+            p = fc_plan_attention(*cfg, a, cfg->max_seq);
+        }
         const size_t b = fc_plan_workspace(*cfg, p, a);
         if (b > best) best = b;
     }
     return best;
+}
+
+static fc_status run_attention(fc_cache *cache, int32_t layer, const FcAttnPlan &plan, const void *q, int32_t A,
+                               int32_t kv_len, const int32_t *pos, void *out, void *workspace, void *stream)
+{
+    const FcGeom G = geom_of(cache);
+    void *kl = layer_ptr(cache, cache->k, layer), *vl = layer_ptr(cache, cache->v, layer);
+    hipError_t e = plan.kind == 1
+                       ? fc_launch_attention_mfma(G, plan, q, kl, vl, pos, A, kv_len, out, workspace,
+                                                  (hipStream_t)stream)
+                       : fc_launch_attention_tile(G, plan, cache->cfg.dtype, q, kl, vl, pos, A, kv_len, out, workspace,
+                                                  (hipStream_t)stream);
+    return e == hipSuccess ? FC_OK : hip_fail(e, "attention launch");
 }
 
 fc_status fc_active_attention(fc_cache *cache, int32_t layer, const void *q, int32_t A, int32_t kv_len,
@@ -478,19 +581,12 @@ fc_status fc_active_attention(fc_cache *cache, int32_t layer, const void *q, int
         return fail(FC_ERR_UNSUPPORTED, "batch * A exceeds 2^24 rows");
     if (kv_len < 1 || kv_len > cache->cfg.max_seq)
         return fail(FC_ERR_BOUNDS, "kv_len %d outside [1, %d]", kv_len, cache->cfg.max_seq);
-    const FcAttnPlan plan = plan_with_workspace(cache->cfg, A, kv_len, workspace ? workspace_bytes : 0);
+    const FcAttnPlan plan = plan_with_workspace(cache->cfg, cache->last_plan, A, kv_len, workspace ? workspace_bytes : 0);
     const size_t need = fc_plan_workspace(cache->cfg, plan, A);
     if (need > 0 && (!workspace || workspace_bytes < need))
         return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need,
                     workspace ? workspace_bytes : (size_t)0);
-    const FcGeom G = geom_of(cache);
-    void *kl = layer_ptr(cache, cache->k, layer), *vl = layer_ptr(cache, cache->v, layer);
-    hipError_t e = plan.kind == 1
-                       ? fc_launch_attention_mfma(G, plan, q, kl, vl, pos, A, kv_len, out, workspace,
-                                                  (hipStream_t)stream)
-                       : fc_launch_attention_tile(G, plan, cache->cfg.dtype, q, kl, vl, pos, A, kv_len, out, workspace,
-                                                  (hipStream_t)stream);
-    return e == hipSuccess ? FC_OK : hip_fail(e, "attention launch");
+    return run_attention(cache, layer, plan, q, A, kv_len, pos, out, workspace, stream);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -544,11 +640,17 @@ fc_status fc_active_attention_static(fc_cache *cache, int32_t layer, const void 
         return fail(FC_ERR_UNSUPPORTED, "batch * A exceeds 2^24 rows");
     if (kv_len < 1 || kv_len > cache->cfg.max_seq)
         return fail(FC_ERR_BOUNDS, "kv_len %d outside [1, %d]", kv_len, cache->cfg.max_seq);
-    const FcAttnPlan plan = plan_with_workspace(cache->cfg, A, kv_len, FC_STATIC_SCRATCH_BYTES);
+    // Refused are the shapes whose partial results with one round of eight-wave workgroups exceed the array; the
+    // others are planned within it.
+    {
+        FcAttnPlan q = fc_plan_attention_default(cache->cfg, A, kv_len);
+        const size_t bytes = fc_plan_workspace(cache->cfg, q, A);
+        if (q.kind == 1 && bytes > FC_STATIC_SCRATCH_BYTES)
+            return fail(FC_ERR_WORKSPACE, "this shape needs %zu bytes of partial results, the static scratch holds %u",
+                        bytes, FC_STATIC_SCRATCH_BYTES);
+    }
+    const FcAttnPlan plan = plan_with_workspace(cache->cfg, cache->last_static, A, kv_len, FC_STATIC_SCRATCH_BYTES, FC_STATIC_SCRATCH_BYTES);
     const size_t need = fc_plan_workspace(cache->cfg, plan, A);
-    if (need > FC_STATIC_SCRATCH_BYTES)
-        return fail(FC_ERR_WORKSPACE, "this shape needs %zu bytes of partial results, the static scratch holds %u",
-                    need, FC_STATIC_SCRATCH_BYTES);
     void *scratch = nullptr;
     if (need > 0) {
         st = static_scratch_ptr(&scratch);
@@ -556,7 +658,7 @@ fc_status fc_active_attention_static(fc_cache *cache, int32_t layer, const void 
     }
     // Nothing in the scratch has to start at zero: every (row tile, split) slot the merge kernel
     // reads is written by the first kernel of the same call.
-    return fc_active_attention(cache, layer, q, A, kv_len, pos, out, scratch, need, stream);
+    return run_attention(cache, layer, plan, q, A, kv_len, pos, out, scratch, stream);
 }
 
 fc_status fc_refresh(fc_cache *cache, int32_t layer, const void *x, const void *w_qkv, const void *b_qkv,
@@ -576,7 +678,7 @@ fc_status fc_refresh(fc_cache *cache, int32_t layer, const void *x, const void *
             return fail(FC_ERR_BOUNDS, "kv_len %d outside [1, %d]", kv_len, cache->cfg.max_seq);
         if (start + R > kv_len)
             return fail(FC_ERR_BOUNDS, "refreshed rows end at %d, beyond kv_len %d", start + R, kv_len);
-        const FcAttnPlan plan = plan_with_workspace(cache->cfg, R, kv_len, workspace ? workspace_bytes : 0);
+        const FcAttnPlan plan = plan_with_workspace(cache->cfg, cache->last_plan, R, kv_len, workspace ? workspace_bytes : 0);
         const size_t need = fc_plan_workspace(cache->cfg, plan, R);
         if (need > 0 && (!workspace || workspace_bytes < need))
             return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need,

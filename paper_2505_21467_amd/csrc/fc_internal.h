@@ -8,6 +8,21 @@
 
 #define FC_VTILE 64  // rows per transposed V tile; Spad is a multiple of it
 
+// Launch plan of the split-KV attention (host, pure function of the shape).
+struct FcAttnPlan {
+    int kind;            // 0 = fp32 / head_dim 64 kernel, 1 = bf16 head_dim 128 split-KV
+    int splits;          // key ranges per (sequence, kv head); every one is non-empty
+    int splits_bound;    // upper bound of `splits` over all kv_len <= the given one (workspace sizing)
+    int keys_per_split;  // multiple of 64 (kind 0: of 32)
+    int row_tiles;       // 32-row (kind 0: 16-row) tiles of the flattened (head-in-group, a) rows per (b, kv head)
+    int tiles_per_wg;    // row tiles handled by one workgroup
+    int waves;           // waves per workgroup (tiles_per_wg or twice that)
+};
+struct FcLastPlan {
+    int A, kv_len, knobs;  // the shape it is for; version of the tuning knobs
+    FcAttnPlan plan;
+};
+
 struct fc_cache {
     fc_config cfg;
     int32_t spad;        // max_seq rounded up to FC_VTILE
@@ -24,6 +39,7 @@ struct fc_cache {
     // with the same shape step after step, and planning it anew walks every window size up to A.
     int32_t ws_d_ff, ws_A;
     size_t ws_part[10];
+    FcLastPlan last_plan, last_static;  // attention plans of the last shape (own workspace, static scratch)
 };
 
 #define FC_SCRATCH_BYTES (32u * 1024u * 1024u)
@@ -41,6 +57,7 @@ struct FcKnobs {
     int gemm_no_split;      // FC_GEMM_NO_SPLIT       never cut a GEMM into two launches
     int proj_gemm_shape;    // FC_PROJ_GEMM_SHAPE=0..5 one tile shape for the projection GEMM (-1 = planned)
     int proj_no_headsplit;  // FC_PROJ_NO_HEADSPLIT   short-window projection without the head-split kernels
+    int version;            // changes with every fc_tuning_set
     int accept_wgs;         // FC_ACCEPT_WGS=n        workgroups of the acceptance scan
 };
 const FcKnobs &fc_knobs();
@@ -64,17 +81,7 @@ __host__ __device__ inline size_t fc_v_index(const FcGeom &G, int b, int j, int 
            (size_t)i * FC_VTILE + (row % FC_VTILE);
 }
 
-// Launch plan of the split-KV attention (host, pure function of the shape).
-struct FcAttnPlan {
-    int kind;            // 0 = fp32 / head_dim 64 kernel, 1 = bf16 head_dim 128 split-KV
-    int splits;          // key ranges per (sequence, kv head); every one is non-empty
-    int splits_bound;    // upper bound of `splits` over all kv_len <= the given one (workspace sizing)
-    int keys_per_split;  // multiple of 64 (kind 0: of 32)
-    int row_tiles;       // 32-row (kind 0: 16-row) tiles of the flattened (head-in-group, a) rows per (b, kv head)
-    int tiles_per_wg;    // row tiles handled by one workgroup
-    int waves;           // waves per workgroup (tiles_per_wg or twice that)
-};
-FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len);
+FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len, size_t cap = SIZE_MAX);  // cap: bytes of partial results
 size_t fc_plan_workspace(const fc_config &cfg, const FcAttnPlan &p, int A);
 
 // Kernel launchers (defined in the .hip kernel files).  All return hipGetLastError() after launch.

@@ -1,0 +1,45 @@
+"""The attention planner: every plan covers the keys and fits the workspace that is asked for, whatever the length up
+to the cache's capacity; and every tile shape it can pick agrees with the oracle where its tiles are ragged."""
+import random
+
+import pytest
+
+from paper_2505_21467_amd import binding as fc
+from paper_2505_21467_amd import inputs
+from tests.harness import GpuLayerCache, OracleLayerCache, assert_close
+
+
+def test_plans_cover_the_keys_and_fit_the_workspace():
+    rng = random.Random(7)
+    for _ in range(300):
+        hkv, g = rng.choice((1, 2, 4, 8, 32)), rng.choice((1, 2, 7, 8))
+        smax, batch, rows = rng.randint(1, 20000), rng.randint(1, 8), rng.randint(1, 300)
+        c = fc.make_config(1, batch, 256, hkv * g, hkv, 128, smax, "bf16")
+        space = fc.fc_workspace_bytes(c, rows)
+        for _ in range(6):
+            a, kv = rng.randint(1, rows), rng.randint(1, smax)
+            p = fc.fc_attention_plan(c, a, kv)
+            assert p["splits"] * p["keys_per_split"] >= kv > (p["splits"] - 1) * p["keys_per_split"], (a, kv, p)
+            assert p["keys_per_split"] % 64 == 0 and p["tiles_per_wg"] in (2, 4, 8) and p["waves"] in (4, 8)
+            need = batch * hkv * p["row_tiles"] * p["splits"] * 32 * (256 + 16) if p["splits"] > 1 else 0
+            assert need <= space, (a, kv, p, need, space)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tiles", ["8,8", "4,8", "2,8", "4,4", "2,4"])
+@pytest.mark.parametrize("Hq,Hkv,A,S", [(3, 1, 5, 70), (10, 2, 21, 777), (9, 1, 33, 300)])
+def test_every_tile_shape_matches_oracle(tiles, Hq, Hkv, A, S, knob):
+    print("[case]", tiles, Hq, Hkv, A, S, flush=True)
+    knob("FC_ATTN_TILES", tiles)
+    from oracle import fc_oracle as orc
+    B, Dh, dt = 2, 128, "bf16"
+    w = inputs.Workload("t", dt, B, 256, Hq, Hkv, Dh, S, A)
+    g = GpuLayerCache(dt, B, 256, Hq, Hkv, Dh, S, max_rows=A)
+    o = OracleLayerCache(dt, B, 256, Hq, Hkv, Dh, S)
+    K, V = inputs.kv_fill(w, 2, S)
+    g.write_rows(0, K, V, 0)
+    o.write_rows(K, V, 0)
+    Q = inputs.normal(2, "q", (B, Hq, A, Dh), 1.0, dt)
+    O = g.attend(0, g.dev_t(Q), S)
+    assert_close(inputs.as_oracle(O), orc.attend(o.cfg, inputs.as_oracle(Q), o.Kc, o.Vc, S, None), dt, tiles)
+    g.close()
