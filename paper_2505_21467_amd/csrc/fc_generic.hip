@@ -95,7 +95,7 @@ __device__ __forceinline__ void store4(bf16_t *p, const float (&y)[4])
 // Linear layers of any shape: Y^T = W X^T for a block of 16 NT weight rows and 16 MT window rows per
 // workgroup.  These problems are small (a few MB of weights at most), so what bounds them is latency:
 // the eight waves cut the hidden dimension, each streams its part of both operands from global memory
-// straight into operand registers (the next pair of blocks in flight behind the multiplies of this one),
+// straight into operand registers (U blocks at a time, the next U in flight behind the multiplies of these),
 // and the partial tiles are summed through LDS, tile t by wave t mod 8, which applies the epilogue.
 // Plain-ALU kernels with one dot product per wave took 36 us for the tiny configuration's projection (32
 // rows, hidden 256, 768 outputs; 0.3 TFLOP/s); this one takes about 5.
@@ -122,12 +122,12 @@ struct TileArgs {
 constexpr int TW = 8;  // waves per workgroup
 constexpr size_t tile_lds(int NT, int MT) { return (size_t)TW * NT * MT * 1024 + (size_t)MT * 16 * NT * 8 * sizeof(float2); }
 
-template <typename T, int NT, int MT, int EPI>
+template <typename T, int NT, int MT, int U, int EPI>
 __global__ __launch_bounds__(TW * 64) void k_linear_tile(TileArgs p)
 {
     typedef Op<T> O;
     typedef typename O::frag frag;
-    constexpr int KB = O::KB, U = 2;  // blocks of 4 KB hidden elements per load step
+    constexpr int KB = O::KB;  // U blocks of 4 KB hidden elements per load step
     extern __shared__ __align__(16) unsigned char tile_smem[];
     float *red = (float *)tile_smem;                               // [wave][tile][reg][lane]
     float2 *cs = (float2 *)(tile_smem + (size_t)TW * NT * MT * 1024);  // EPI_QKV: [window row][8 NT rotary indices]
@@ -213,10 +213,17 @@ __global__ __launch_bounds__(TW * 64) void k_linear_tile(TileArgs p)
             }
         }
     }
-    for (int b = b0; b < b1; b += 2 * U) {
+    for (int b = b0;; b += 2 * U) {  // (a wave without blocks multiplies zeros once)
+        if (b + U >= b1) {
+            multiply(wa, xa);
+            break;
+        }
         load(b + U, wb, xb);
         multiply(wa, xa);
-        if (b + U >= b1) break;
+        if (b + 2 * U >= b1) {
+            multiply(wb, xb);
+            break;
+        }
         load(b + 2 * U, wa, xa);
         multiply(wb, xb);
     }
@@ -740,31 +747,38 @@ hipError_t fc_launch_rmsnorm(int dtype, const void *x, const void *weight, float
 
 namespace {
 
-template <typename T, int NT, int MT, int EPI>
-hipError_t launch_tile_shape(TileArgs a, int n_tiles, hipStream_t s)
+template <typename T, int NT, int MT, int U, int EPI>
+hipError_t launch_tile_u(TileArgs a, int n_tiles, hipStream_t s)
 {
     constexpr size_t LDS = tile_lds(NT, MT);
-    static hipError_t attr = hipFuncSetAttribute((const void *)k_linear_tile<T, NT, MT, EPI>,
+    static hipError_t attr = hipFuncSetAttribute((const void *)k_linear_tile<T, NT, MT, U, EPI>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
     if (attr != hipSuccess) return attr;
     a.n_blocks = (n_tiles + NT - 1) / NT;
     const int64_t grid = (int64_t)a.n_blocks * ((a.M + 16 * MT - 1) / (16 * MT));
     if (grid > INT32_MAX) return hipErrorInvalidValue;
-    k_linear_tile<T, NT, MT, EPI><<<dim3((unsigned)grid), dim3(TW * 64), LDS, s>>>(a);
+    k_linear_tile<T, NT, MT, U, EPI><<<dim3((unsigned)grid), dim3(TW * 64), LDS, s>>>(a);
     return hipGetLastError();
 }
 
-// Tile choice: as many window rows per workgroup as there are (up to 64: the weights are then read once per
-// 64 rows), and two weight tiles once that still leaves a workgroup for every compute unit.  The
-// vocabulary takes two always: its parts are workspace.
+// Tile choice.  These problems are bound by the latency of a wave's chain of loads and multiplies, so what counts is
+// that every compute unit has a workgroup and that several share one: 16 or 32 window rows per workgroup (about 60
+// registers: four workgroups per compute unit; 138 rows x 3072 x 512 took 28 us in tiles of 64 rows, 200 registers),
+// and 64 rows x two weight tiles, which halve the traffic, only for many rounds of workgroups.  A long hidden dimension
+// with few workgroups keeps four blocks in flight per wave instead of two (with two weight tiles as well that costs more
+// than it brings: 20 x 3584 x 9001 in bf16 27.1 us with two, 32.3 with four).  The vocabulary takes two weight tiles
+// always: its parts are workspace.
 template <typename T, int EPI>
 hipError_t launch_tile_t(const TileArgs &a, int n_tiles, hipStream_t s)
 {
-    const int64_t mc = a.M <= 32 ? 1 : (a.M + 63) / 64;
-    const bool two = EPI == EPI_VOCAB || (n_tiles + 1) / 2 * mc >= 256;
-    if (a.M <= 16) return two ? launch_tile_shape<T, 2, 1, EPI>(a, n_tiles, s) : launch_tile_shape<T, 1, 1, EPI>(a, n_tiles, s);
-    if (a.M <= 32) return two ? launch_tile_shape<T, 2, 2, EPI>(a, n_tiles, s) : launch_tile_shape<T, 1, 2, EPI>(a, n_tiles, s);
-    return two ? launch_tile_shape<T, 2, 4, EPI>(a, n_tiles, s) : launch_tile_shape<T, 1, 4, EPI>(a, n_tiles, s);
+    constexpr int NT = EPI == EPI_VOCAB ? 2 : 1;
+    const int64_t blocks = (n_tiles + NT - 1) / NT;
+    auto wgs = [&](int mt) { return blocks * ((a.M + 16 * mt - 1) / (16 * mt)); };
+    const bool deep = NT == 1 && (a.K + 4 * Op<T>::KB - 1) / (4 * Op<T>::KB) >= 8 * TW;
+    if (a.M > 32 && wgs(2) >= 4096) return launch_tile_u<T, 2, 4, 2, EPI>(a, n_tiles, s);
+    if (a.M > 16 && wgs(2) >= 256)
+        return deep && wgs(2) <= 512 ? launch_tile_u<T, NT, 2, 4, EPI>(a, n_tiles, s) : launch_tile_u<T, NT, 2, 2, EPI>(a, n_tiles, s);
+    return deep && wgs(1) <= 512 ? launch_tile_u<T, NT, 1, 4, EPI>(a, n_tiles, s) : launch_tile_u<T, NT, 1, 2, EPI>(a, n_tiles, s);
 }
 
 template <int EPI>
