@@ -522,7 +522,7 @@ fc_status fc_qkv_project_scatter(fc_cache *cache, int32_t layer, const void *x, 
     void *kl = layer_ptr(cache, cache->k, layer), *vl = layer_ptr(cache, cache->v, layer);
     // wide windows: tiled GEMM; short windows: weight-streaming kernels; other shapes and fp32: tile kernel
     hipError_t e;
-    if (fc_project_gemm_supported(cache->cfg, cache->cfg.batch * A))
+    if (fc_project_prefers_gemm(cache->cfg, cache->cfg.batch * A, cache->scratch != nullptr))
         e = fc_launch_project_gemm(G, x, w_qkv, b_qkv, pos, win_start, A, q_out, kl, vl, (hipStream_t)stream);
     else if (fc_project_mfma_supported(cache->cfg, A))
         e = fc_launch_project_mfma(G, cache->inv_freq, x, w_qkv, b_qkv, pos, win_start, A, q_out, kl, vl,

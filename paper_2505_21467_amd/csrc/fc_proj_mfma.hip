@@ -36,6 +36,7 @@ struct ProjArgs {
     double log2_base_64;   // log2(rope_base) / 64
     double rot[6];         // rope_base^(-i/64), i = 1, 2, 4, .. 32
     float *partials;       // cache scratch: partial tiles of the hidden-dimension slices
+    int mt;                // 16-row window tiles of a partial
 };
 
 
@@ -216,13 +217,15 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
 }
 
 // -------------------------------------------------------------------------------------------------
-// Head-split kernel for windows of at most 32 rows and hidden sizes that are multiples of 512.
+// Head-split kernel for windows of at most 128 rows and hidden sizes that are multiples of 512.
 //
 // A workgroup owns one whole head slot (128 rows of W: 8 waves x 16 rows) and one 512-wide slice of
-// the hidden dimension, so the 32 x 512 slice of X is fetched once per workgroup (direct-to-LDS,
+// the hidden dimension, so the 512-wide slice of X is fetched once per workgroup (direct-to-LDS,
 // swizzled) and shared by the 8 waves instead of being re-read by every 16-row tile.  The partial
 // tiles of the hidden-dimension slices of a head go to the cache's device scratch and are summed
-// by k_proj_finish.
+// by k_proj_finish.  Bound by one pass over the weights and its first latency: at 36 head slots and hidden 3584
+// (252 workgroups, one per compute unit) 9.2 us for 33 MB.  A whole-row kernel without partial tiles (18 rows
+// per compute unit) was slower, 15.3 us at 32 rows: every compute unit then reads all of X.
 constexpr int HS_K = 512;  // hidden elements per workgroup
 
 __device__ __forceinline__ void load_lds16p(const void *g, void *l)
@@ -234,7 +237,7 @@ __device__ __forceinline__ void load_lds16p(const void *g, void *l)
 template <int MT>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_proj_headsplit(ProjArgs p)
 {
-    __shared__ __align__(1024) unsigned char xs[16 * MT * 1024];  // X slice: [row][64 chunks of 16 B]
+    extern __shared__ __align__(1024) unsigned char xs[];  // X slice: [16 MT rows][64 chunks of 16 B]
     const int S = p.K / HS_K;
     const int hs = blockIdx.x / S, ks = blockIdx.x % S;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -280,14 +283,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
         for (int r = 0; r < 4; ++r) part[mt * 256 + r * 64 + lane] = acc[mt][r];
 }
 
-// Second half of the head-split projection: one wave per (head slot, 16-row tile) sums the partial
+// Second half of the head-split projection: one wave per (head slot, 16-row tile, 16 window rows) sums the partial
 // tiles of the hidden-dimension slices (a kernel boundary is the only cross-workgroup ordering used:
 // device-scope fences inside a kernel cost an L2 write-back per workgroup on this multi-die part),
 // then applies bias and rotary embedding and scatters q, k and v.  Rotary factors are computed per
 // lane: base^(-i/64) by binary powering in double (the powers come from the host), the angle reduced to a
 // fraction of a turn in double, hardware sine/cosine (argument in turns).  The kernel is one memory round
 // trip long, so all of that runs while the partial tiles are on their way.
-template <int MT>
 __global__ __launch_bounds__(64) void k_proj_finish(ProjArgs p)
 {
     const FcGeom &G = p.G;
@@ -296,18 +298,19 @@ __global__ __launch_bounds__(64) void k_proj_finish(ProjArgs p)
     const int lane = threadIdx.x;
     const int rho = lane & 15, q = lane >> 4;
     const int i0 = wave * 8;
+    const int m = 16 * blockIdx.y + rho;
+    const bool mvalid = m < p.M;
+    const int mm = mvalid ? m : p.M - 1;
 
     // the first eight slices' loads go out, then everything the epilogue needs besides is fetched and computed
-    float v[8][MT][4];
+    float v[8][4];
     auto load = [&](int kb) {
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const int k2 = min(kb + u, S - 1);
-            const float *pp2 = p.partials + ((((size_t)hs * S + k2) * 8 + wave) * MT) * 256;
+            const float *pp2 = p.partials + ((((size_t)hs * S + k2) * 8 + wave) * p.mt + blockIdx.y) * 256;
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[u][mt][r] = pp2[mt * 256 + r * 64 + lane];
+            for (int r = 0; r < 4; ++r) v[u][r] = pp2[r * 64 + lane];
         }
     };
     load(0);
@@ -319,14 +322,9 @@ __global__ __launch_bounds__(64) void k_proj_finish(ProjArgs p)
 #pragma unroll
         for (int r = 0; r < 4; ++r) bs[r] = fc_to_float(bf16_t{p.bias[hs * 128 + d0 + r]});
     }
-    int pos_m[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const int mm = min(16 * mt + rho, p.M - 1);
-        pos_m[mt] = p.pos ? p.pos[mm] : p.win_start + mm % p.A;
-    }
+    const int pp = p.pos ? p.pos[mm] : p.win_start + mm % p.A;
     __builtin_amdgcn_sched_barrier(0);
-    float2 cs[MT][4];
+    float2 cs[4];
     if (rotate) {
         double f = 0.15915494309189533576888;  // base^(-(ib + r)/64) / (2 pi): turns per position
 #pragma unroll
@@ -334,68 +332,75 @@ __global__ __launch_bounds__(64) void k_proj_finish(ProjArgs p)
             if (ib & (1 << bit)) f *= p.rot[bit];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const double turns = (double)pos_m[mt] * f;
-                const float fr = (float)(turns - rint(turns));
-                cs[mt][r] = make_float2(__builtin_amdgcn_cosf(fr), __builtin_amdgcn_sinf(fr));
-            }
+            const double turns = (double)pp * f;
+            const float fr = (float)(turns - rint(turns));
+            cs[r] = make_float2(__builtin_amdgcn_cosf(fr), __builtin_amdgcn_sinf(fr));
             f *= p.rot[0];
         }
     }
     __builtin_amdgcn_sched_barrier(0);
 
-    f32x4 acc[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
     for (int kb = 0; kb < S; kb += 8) {  // eight slices at a time
         if (kb) load(kb);
 #pragma unroll
         for (int u = 0; u < 8; ++u)
             if (kb + u < S) {
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[mt][r] += v[u][mt][r];
+                for (int r = 0; r < 4; ++r) acc[r] += v[u][r];
             }
     }
 
+    const int b = mm / p.A, a = mm - b * p.A;
+    const bool valid = mvalid && pp >= 0 && pp < G.max_seq;
+    float y[4];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const int m = 16 * mt + rho;
-        const bool mvalid = m < p.M;
-        const int mm = mvalid ? m : 0;
-        const int b = mm / p.A, a = mm - b * p.A;
-        const int pp = pos_m[mt];
-        const bool valid = mvalid && pp >= 0 && pp < G.max_seq;
-        float y[4];
+    for (int r = 0; r < 4; ++r) y[r] = acc[r] + bs[r];
+    if (rotate) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) y[r] = acc[mt][r] + bs[r];
-        if (rotate) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float other = swap32f(y[r]);
-                y[r] = second ? y[r] * cs[mt][r].x + other * cs[mt][r].y : y[r] * cs[mt][r].x - other * cs[mt][r].y;
-            }
-        }
-        uint2 w;
-        w.x = (uint32_t)fc_bf16_bits(y[0]) | ((uint32_t)fc_bf16_bits(y[1]) << 16);
-        w.y = (uint32_t)fc_bf16_bits(y[2]) | ((uint32_t)fc_bf16_bits(y[3]) << 16);
-        if (hs < G.Hq) {
-            if (mvalid) {
-                if (!valid) w = make_uint2(0, 0);
-                *(uint2 *)(p.Q + (((size_t)b * G.Hq + hs) * p.A + a) * 128 + d0) = w;
-            }
-        } else if (valid) {
-            if (hs < G.Hq + G.Hkv) {
-                *(uint2 *)(p.Kc + fc_k_index(G, b, hs - G.Hq, pp, d0)) = w;
-            } else {
-                const int j = hs - G.Hq - G.Hkv;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) p.Vc[fc_v_index(G, b, j, pp, d0 + r)] = fc_bf16_bits(y[r]);
-            }
+        for (int r = 0; r < 4; ++r) {
+            const float other = swap32f(y[r]);
+            y[r] = second ? y[r] * cs[r].x + other * cs[r].y : y[r] * cs[r].x - other * cs[r].y;
         }
     }
+    uint2 w;
+    w.x = (uint32_t)fc_bf16_bits(y[0]) | ((uint32_t)fc_bf16_bits(y[1]) << 16);
+    w.y = (uint32_t)fc_bf16_bits(y[2]) | ((uint32_t)fc_bf16_bits(y[3]) << 16);
+    if (hs < G.Hq) {
+        if (mvalid) {
+            if (!valid) w = make_uint2(0, 0);
+            *(uint2 *)(p.Q + (((size_t)b * G.Hq + hs) * p.A + a) * 128 + d0) = w;
+        }
+    } else if (valid) {
+        if (hs < G.Hq + G.Hkv) {
+            *(uint2 *)(p.Kc + fc_k_index(G, b, hs - G.Hq, pp, d0)) = w;
+        } else {
+            const int j = hs - G.Hq - G.Hkv;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) p.Vc[fc_v_index(G, b, j, pp, d0 + r)] = fc_bf16_bits(y[r]);
+        }
+    }
+}
+
+size_t headsplit_bytes(int slots, int M, int K)
+{
+    return (size_t)slots * (K / HS_K) * 8 * ((M + 15) / 16) * 256 * sizeof(float);
+}
+
+bool headsplit_covers(int slots, int M, int K)
+{
+    return !fc_knobs().proj_no_headsplit && M <= 128 && K % HS_K == 0 && headsplit_bytes(slots, M, K) <= FC_SCRATCH_BYTES;
+}
+
+template <int MT>
+hipError_t launch_headsplit(const ProjArgs &a, int slots, hipStream_t s)
+{
+    constexpr int LDS = 16 * MT * 2 * HS_K;
+    static hipError_t attr = hipFuncSetAttribute((const void *)k_proj_headsplit<MT>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+    if (attr != hipSuccess) return attr;
+    k_proj_headsplit<MT><<<dim3((unsigned)(slots * (a.K / HS_K))), dim3(512), LDS, s>>>(a);
+    k_proj_finish<<<dim3((unsigned)slots * 8, (unsigned)MT), dim3(64), 0, s>>>(a);
+    return hipGetLastError();
 }
 
 template <int MT>
@@ -421,6 +426,23 @@ bool fc_project_mfma_supported(const fc_config &cfg, int A)
     return cfg.dtype == FC_BF16 && cfg.head_dim == 128 && cfg.hidden % 128 == 0;
 }
 
+// The head-split kernels against the tiled GEMM, by estimate (us): weights at 5 TB/s after 4 us of launch and first
+// latency, but no less than two short kernels; for every 16 rows the partial tiles, written and read back at 5.5 TB/s,
+// and the window rows.  Measured at 16 / 32 / 64 / 96 / 128 rows: 36 head slots, hidden 3584: 11.5 / 12.7 / 15.3 / 17.8 /
+// 19.6, the GEMM, whose 72 half-slab tiles leave most of the chip idle, 19.5 / 20.6 / 21.6 / 22.8 / 23.6.  96 slots,
+// hidden 4096 (three workgroups per compute unit): 27.4 / 29.9 / 38.4 at 16 / 32 / 64 rows against 25.8 / 26.5 / 27.9.
+// 12 slots, hidden 512: 9.1 / 9.5 / 10.8 against 6.2 / 6.6 / 6.8.
+bool fc_project_prefers_gemm(const fc_config &cfg, int M, bool scratch)
+{
+    if (!fc_project_gemm_supported(cfg, M)) return false;
+    if (fc_knobs().proj_gemm_shape >= 0 && M > 32) return true;  // tuning knob
+    const int slots = cfg.n_q_heads + 2 * cfg.n_kv_heads, mt = (M + 15) / 16;
+    if (!scratch || !headsplit_covers(slots, M, cfg.hidden)) return M > 32;
+    const double weights = 256.0 * slots * cfg.hidden, part = (double)headsplit_bytes(slots, 16, cfg.hidden);
+    const double us = fmax(8.5, 4.0 + weights / 5.0e6) + mt * (0.5 + 2.0 * part / 5.5e6);
+    return us > fc_project_gemm_us(slots, M, cfg.hidden);
+}
+
 hipError_t fc_launch_project_mfma(const FcGeom &G, const double *inv_freq, const void *x, const void *w, const void *bias,
                                   const int32_t *pos, int win_start, int A, void *q_out, void *k_layer,
                                   void *v_layer, void *scratch, hipStream_t s)
@@ -443,19 +465,19 @@ hipError_t fc_launch_project_mfma(const FcGeom &G, const double *inv_freq, const
     a.log2_base_64 = G.log_base * 1.4426950408889634074 / 64.0;
     a.partials = (float *)scratch;
     for (int i = 0; i < 6; ++i) a.rot[i] = exp(-G.log_base * (1 << i) / 64.0);
-    const int slots = G.Hq + 2 * G.Hkv;
-    const bool no_headsplit = fc_knobs().proj_no_headsplit != 0;  // tuning knob
-    if (!no_headsplit && scratch && a.M <= 32 && a.K % HS_K == 0 &&
-        (size_t)slots * (a.K / HS_K) * 8 * 2 * 256 * sizeof(float) <= FC_SCRATCH_BYTES) {
-        const unsigned grid = (unsigned)(slots * (a.K / HS_K));
-        if (a.M <= 16) {
-            k_proj_headsplit<1><<<dim3(grid), dim3(512), 0, s>>>(a);
-            k_proj_finish<1><<<dim3((unsigned)slots * 8), dim3(64), 0, s>>>(a);
-        } else {
-            k_proj_headsplit<2><<<dim3(grid), dim3(512), 0, s>>>(a);
-            k_proj_finish<2><<<dim3((unsigned)slots * 8), dim3(64), 0, s>>>(a);
+    const int slots = G.Hq + 2 * G.Hkv, mt = (a.M + 15) / 16;
+    if (scratch && headsplit_covers(slots, a.M, a.K)) {
+        a.mt = mt;
+        switch (mt) {
+        case 1: return launch_headsplit<1>(a, slots, s);
+        case 2: return launch_headsplit<2>(a, slots, s);
+        case 3: return launch_headsplit<3>(a, slots, s);
+        case 4: return launch_headsplit<4>(a, slots, s);
+        case 5: return launch_headsplit<5>(a, slots, s);
+        case 6: return launch_headsplit<6>(a, slots, s);
+        case 7: return launch_headsplit<7>(a, slots, s);
+        default: return launch_headsplit<8>(a, slots, s);
         }
-        return hipGetLastError();
     }
     if (a.M <= 16) return launch_mt<1>(a, 1, s);
     return launch_mt<2>(a, (a.M + 31) / 32, s);
