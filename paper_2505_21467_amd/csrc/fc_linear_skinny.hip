@@ -22,6 +22,8 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <type_traits>
+
 #include "fc_device.h"
 #include "fc_internal.h"
 
@@ -54,6 +56,13 @@ __device__ __forceinline__ void load_lds16(const void *g, void *l)
 {
     __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)g,
                                      (void __attribute__((address_space(3))) *)l, 16, 0, 0);
+}
+
+// wait until at most N of this wave's vector-memory operations are outstanding
+template <int N>
+__device__ __forceinline__ void wait_vm()
+{
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
 __device__ __forceinline__ float swap32(float v)
@@ -308,7 +317,10 @@ __global__ __launch_bounds__(512) void k_lmhead_finish(LinArgs p)
 // A work item is 16 rows of W over the whole hidden dimension (16 x 2K bytes, contiguous in memory);
 // the eight waves of a workgroup cut the hidden dimension in eight, and every wave keeps its part of
 // the X block (at most 32 rows) in operand registers for the whole kernel, so X is read once per
-// workgroup and never again.  The weight fragments of a wave are refilled one by one, right behind
+// workgroup and never again.  It comes by way of LDS, 16 rows at a time, in whole cache lines (direct loads,
+// chunks permuted against bank conflicts), with the first item's weights behind it: loaded straight into
+// operand registers, half a line per row and load, X cost 3.6 us per 16 rows, none of it hidden (gated W_1 at
+// hidden 3584, 18944 outputs, 32 rows: 54.5 us, now 51.2; 4096 x 4096: 16.4, now 11.5).  The weight fragments of a wave are refilled one by one, right behind
 // the multiply that consumed them, with the same fragment of the next item: a full item of loads
 // stays in flight and the wave never drains its queue.  The eight partial 16 x 32 tiles of an item
 // are summed through LDS (double-buffered: one barrier per item) by the first MT waves, which apply
@@ -317,11 +329,16 @@ __global__ __launch_bounds__(512) void k_lmhead_finish(LinArgs p)
 // No partial sums leave the workgroup and there is no second kernel.  Items are dealt in contiguous
 // runs measured in half items (8 rows, or 4 gated features), so runs differ by at most half an item;
 // a lane whose half of an item belongs to the neighbouring run re-reads the row of the other half
-// (same cache lines: no extra traffic) and its results are dropped.
+// (same cache lines: no extra traffic) and its results are dropped.  A vocabulary may have any size: rows past its
+// end re-read the last one.  Bound by the weights: 5.9 TB/s and about 6 us of launch, X and last items.
 template <int MT, int NKW, int MODE>
 __global__ __launch_bounds__(512) void k_linear_rows(LinArgs p)
 {
-    __shared__ __align__(16) float red[2][8][MT * 4][64];
+    extern __shared__ __align__(1024) unsigned char lds[];
+    float(*red)[8][MT * 4][64] = (float(*)[8][MT * 4][64])lds;  // [2]
+    constexpr int XROW = NKW * 64;  // bytes of a wave's part of an X row
+    // The 16-byte chunks of a row are permuted so that 16 rows' chunks of one column fall into 16 different bank groups.
+    auto xswz = [](int r) { return NKW % 4 == 0 ? r & 15 : (r >> 1) & 7; };
     const int wg = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -332,15 +349,7 @@ __global__ __launch_bounds__(512) void k_linear_rows(LinArgs p)
     const int it0 = u0 >> 1, it1 = (u1 + 1) >> 1;
     const size_t kw0 = (size_t)wave * (NKW * 32) + 8 * q;  // this lane's first hidden element
 
-    bf16x8 xr[NKW][MT];
-#pragma unroll
-    for (int s = 0; s < NKW; ++s)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            const int m = min(16 * mt + rho, p.M - 1);  // padding rows read a valid row
-            xr[s][mt] = ld8(p.X + (size_t)m * p.K + kw0 + 32 * s);
-        }
-    __builtin_amdgcn_sched_barrier(0);
+    bf16x8 xr[NKW][MT], wf[NKW];
 
     // this lane's weight row of item `it`
     auto wrow_of = [&](int it) -> const uint16_t * {
@@ -353,15 +362,39 @@ __global__ __launch_bounds__(512) void k_linear_rows(LinArgs p)
         int r = rho;  // row of the item; half item = 8 rows
         const int uu = 2 * it + (r >> 3);
         if (uu < u0 || uu >= u1) r ^= 8;
-        return p.W + (size_t)(16 * it + r) * p.K + kw0;
+        const int n = MODE == FC_LIN_VOCAB ? min(16 * it + r, p.N - 1) : 16 * it + r;
+        return p.W + (size_t)n * p.K + kw0;
     };
 
-    bf16x8 wf[NKW];
-    {
-        const uint16_t *cur = wrow_of(it0);
+    // X block -> operand registers, 16 rows at a time by way of LDS
+    unsigned char *xw = lds + wave * (16 * XROW);
 #pragma unroll
-        for (int s = 0; s < NKW; ++s) wf[s] = ld8(cur + 32 * s);
+    for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+        for (int i = 0; i < NKW; ++i) {
+            const int byte = 1024 * i + 16 * lane, r = byte / XROW, c = (byte - r * XROW) >> 4;
+            const int m = min(16 * mt + r, p.M - 1);  // padding rows read a valid row
+            load_lds16(p.X + (size_t)m * p.K + wave * (NKW * 32) + 8 * (c ^ xswz(r)), xw + 1024 * i);
+        }
+        if (mt == MT - 1) {
+            __builtin_amdgcn_sched_barrier(0);
+            const uint16_t *cur = wrow_of(it0);
+#pragma unroll
+            for (int s = 0; s < NKW; ++s) wf[s] = ld8(cur + 32 * s);
+            __builtin_amdgcn_sched_barrier(0);
+            wait_vm<NKW>();  // everything before the weights
+        } else {
+            wait_vm<0>();
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < NKW; ++s)
+            xr[s][mt] = *(const bf16x8 *)(xw + rho * XROW + (((4 * s + q) ^ xswz(rho)) << 4));
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the LDS rows may be overwritten
+        __builtin_amdgcn_sched_barrier(0);
     }
+    __builtin_amdgcn_s_barrier();  // the partial tiles reuse the area
     f32x4 acc[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -376,7 +409,7 @@ __global__ __launch_bounds__(512) void k_linear_rows(LinArgs p)
     constexpr int HALF_EL = MODE == FC_LIN_GATE_UP ? 4 : 8;  // output columns of a half item
     constexpr int STG_ITEMS = 16;                            // items staged between two flushes
     constexpr int STG_CH = STG_ITEMS * 2 * HALF_EL / 4;      // 8-byte pieces of a staged row (at most 64)
-    __shared__ uint2 stage[MODE == FC_LIN_VOCAB ? 1 : MT * 16][STG_CH + 1];
+    uint2(*stage)[STG_CH + 1] = (uint2(*)[STG_CH + 1])(lds + 2 * 8 * MT * 4 * 64 * sizeof(float));  // [16 MT]
     int stage_it0 = it0;  // item in the first staging slot
     auto flush = [&](int it_end) {  // items stage_it0 .. it_end - 1 are staged
         const int c0 = max(u0 * HALF_EL, stage_it0 * 2 * HALF_EL), c1 = min(u1 * HALF_EL, it_end * 2 * HALF_EL);
@@ -438,7 +471,8 @@ __global__ __launch_bounds__(512) void k_linear_rows(LinArgs p)
             int arg = 0x7fffffff;
             if (uu >= u0 && uu < u1) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) fc_argmax_merge(mx, arg, sm, sum[r], 16 * it + 4 * q + r, 1.0f);
+                for (int r = 0; r < 4; ++r)
+                    if (16 * it + 4 * q + r < p.N) fc_argmax_merge(mx, arg, sm, sum[r], 16 * it + 4 * q + r, 1.0f);
             }
 #pragma unroll
             for (int off = 16; off < 64; off <<= 1) {
@@ -450,7 +484,8 @@ __global__ __launch_bounds__(512) void k_linear_rows(LinArgs p)
         }
     };
 
-    for (int it = it0; it < it1; ++it) {
+    auto item = [&](int it, auto more) {
+        constexpr bool MORE = decltype(more)::value;
         // The previous item is finished here, one iteration late: what it loads or stores is then issued
         // behind the wait for this item's fragments and never part of it.
         __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8) | (0 << 14));  // vmcnt(0): this item's fragments have landed
@@ -458,17 +493,14 @@ __global__ __launch_bounds__(512) void k_linear_rows(LinArgs p)
         if (it > it0 && wave < MT) finish_item(it - 1, buf ^ 1);
         __builtin_amdgcn_sched_barrier(0);
         // Fragment s of the next item goes into its register as soon as the multiplies of fragment s are
-        // issued.  After the last item every lane re-reads the first 16 bytes of W instead (never used):
-        // unconditional loads keep the compiler's wait counts exact.
-        const bool has_next = it + 1 < it1;
-        const uint16_t *nxt = has_next ? wrow_of(it + 1) : p.W;
-        const int nstep = has_next ? 32 : 0;
+        // issued.
+        const uint16_t *nxt = MORE ? wrow_of(it + 1) : nullptr;
 #pragma unroll
         for (int s = 0; s < NKW; ++s) {
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
                 acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[s], xr[s][mt], acc[mt], 0, 0, 0);
-            wf[s] = ld8(nxt + nstep * s);
+            if (MORE) wf[s] = ld8(nxt + 32 * s);
         }
         float *mine = &red[buf][wave][0][lane];
 #pragma unroll
@@ -481,7 +513,9 @@ __global__ __launch_bounds__(512) void k_linear_rows(LinArgs p)
         __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));  // lgkmcnt(0): the tile is in LDS
         __builtin_amdgcn_s_barrier();
         buf ^= 1;
-    }
+    };
+    for (int it = it0; it < it1 - 1; ++it) item(it, std::true_type());
+    item(it1 - 1, std::false_type());
     if (wave < MT) {
         finish_item(it1 - 1, buf ^ 1);
         if (MODE != FC_LIN_VOCAB) flush(it1);
@@ -492,6 +526,17 @@ __global__ __launch_bounds__(512) void k_linear_rows(LinArgs p)
         p.am.arg[at] = run_arg;
         p.am.sm[at] = run_sm;
     }
+}
+
+template <int MT, int NKW, int MODE>
+hipError_t launch_rows_mode(const dim3 &g, const LinArgs &a, hipStream_t s)
+{
+    constexpr int X = 8 * 16 * NKW * 64, OUT = 2 * 8 * MT * 4 * 64 * 4 + (MODE == FC_LIN_VOCAB ? 0 : MT * 16 * 65 * 8);
+    constexpr int LDS = X > OUT ? X : OUT;
+    static hipError_t attr = hipFuncSetAttribute((const void *)k_linear_rows<MT, NKW, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+    if (attr != hipSuccess) return attr;
+    k_linear_rows<MT, NKW, MODE><<<g, dim3(512), LDS, s>>>(a);
+    return hipGetLastError();
 }
 
 #ifndef FC_LIN_KSL
@@ -516,11 +561,10 @@ hipError_t launch_mode(const FcSkinnyPlan &pl, const LinArgs &a, hipStream_t s)
 template <int MT, int NKW>
 hipError_t launch_rows(int mode, const FcSkinnyPlan &pl, const LinArgs &a, hipStream_t s)
 {
-    const dim3 g((unsigned)pl.G), b(512);
-    if (mode == FC_LIN_GATE_UP) k_linear_rows<MT, NKW, FC_LIN_GATE_UP><<<g, b, 0, s>>>(a);
-    else if (mode == FC_LIN_VOCAB) k_linear_rows<MT, NKW, FC_LIN_VOCAB><<<g, b, 0, s>>>(a);
-    else k_linear_rows<MT, NKW, FC_LIN_RESIDUAL><<<g, b, 0, s>>>(a);
-    return hipGetLastError();
+    const dim3 g((unsigned)pl.G);
+    if (mode == FC_LIN_GATE_UP) return launch_rows_mode<MT, NKW, FC_LIN_GATE_UP>(g, a, s);
+    if (mode == FC_LIN_VOCAB) return launch_rows_mode<MT, NKW, FC_LIN_VOCAB>(g, a, s);
+    return launch_rows_mode<MT, NKW, FC_LIN_RESIDUAL>(g, a, s);
 }
 
 // hidden sizes the whole-row kernel is built for (256 x the fragments per wave)
@@ -535,19 +579,18 @@ FcSkinnyPlan fc_plan_skinny(int dtype, int mode, int M, int K, int N)
     int target = 256;  // one workgroup per compute unit
     if (fc_knobs().lin_wgs > 0) target = fc_knobs().lin_wgs;  // tuning and test knob: runs of any length
     {
-        // whole-row kernel: at most 32 rows, a hidden size it is built for, whole half items
+        // whole-row kernel: at most 32 rows, a hidden size it is built for, whole half items (a vocabulary of any size)
         const bool off = fc_knobs().lin_no_rows != 0;  // tuning knob
         const int per_half = mode == FC_LIN_GATE_UP ? 4 : 8;
-        // With less than one item per compute unit at a long hidden size (W_out of the 7B geometry: 224
-        // items) the X block, K x 64 bytes per workgroup, is a third of what a workgroup reads, and the
-        // slice-wise kernel below, which reads only the slices it needs, is as fast (12.2 against 12.8 us).
-        const int items = N >= per_half && N % per_half == 0 ? (N / per_half + 1) / 2 : 0;
-        if (!off && dtype == FC_BF16 && M >= 1 && M <= 32 && rows_kernel_covers(K) && items >= 1 &&
-            (items >= 256 || K < 2048)) {
+        // (Fewer items than compute units are no reason for the slice-wise kernel: hidden 3584, 224 / 64 items
+        // 10.0 / 9.3 us against 12.6 / 11.4, its second launch included.)
+        const int halves = mode == FC_LIN_VOCAB || N % per_half == 0 ? (N + per_half - 1) / per_half : 0;
+        const int items = N >= per_half ? (halves + 1) / 2 : 0;
+        if (!off && dtype == FC_BF16 && M >= 1 && M <= 32 && rows_kernel_covers(K) && items >= 1) {
             p.kind = 2;
             p.mt = M <= 16 ? 1 : 2;
             p.chunks = 1;
-            p.T = N / per_half;               // half items
+            p.T = halves;
             p.G = items < target ? items : target;  // at least one item each
             return p;
         }

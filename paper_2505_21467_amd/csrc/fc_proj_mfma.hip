@@ -3,17 +3,20 @@
 //
 // The window is short (tens to a few hundred rows), so the product Y^T = W X^T is bound by streaming
 // the weight matrix once from HBM.  Both operands are contiguous along the hidden dimension, which is
-// exactly the per-lane operand layout of v_mfma_f32_16x16x32_bf16 (8 consecutive k per lane), so W and
-// X fragments are loaded straight from global memory into operand registers: no LDS, no transposes.
+// exactly the per-lane operand layout of v_mfma_f32_16x16x32_bf16 (8 consecutive k per lane), so W
+// fragments are loaded straight from global memory into operand registers.  Three kernels: whole rows for at most 32
+// window rows at the hidden sizes it is built for (k_proj_rows), head slots cut along the hidden dimension for
+// at most 128 rows (k_proj_headsplit), and the one described here for what is left.
 //
 // A workgroup owns 16 rows of W -- 8 rows i0..i0+7 of one head and their rotary partners
-// i0+64..i0+71 -- and up to 32 rows of X.  Its eight waves split the hidden dimension; every wave
-// issues all loads of its slice (weights from HBM, activations from L2) before the first multiply, so
-// there is no dependent chain of memory latencies, and the partial tiles are summed through LDS.  In the
+// i0+64..i0+71 -- and up to 32 rows of X.  Its waves split the hidden dimension, load both operands straight into
+// registers, and the partial tiles are summed through LDS.  In the
 // 16x16 accumulator layout a lane holds 4 consecutive head-dim indices of one window row, and the
 // rotary partner of every value sits in the lane 32 away, so the rotation needs one cross-lane swap.
 // The rotated q goes to q_out; k and v go directly to their cache rows (v into the transposed tiles).
 #include <math.h>
+
+#include <type_traits>
 
 #include "fc_device.h"
 #include "fc_internal.h"
@@ -40,9 +43,6 @@ struct ProjArgs {
 };
 
 
-#ifndef FC_PROJ_VARIANT
-#define FC_PROJ_VARIANT 0  // tuning builds: 1 = no activation loads, 2 = no weight loads
-#endif
 __device__ __forceinline__ bf16x8 ld8(const uint16_t *p)
 {
     union { uint4 u; bf16x8 v; } x;
@@ -58,9 +58,8 @@ __device__ __forceinline__ float swap32f(float v)
     return (threadIdx.x & 32) ? __uint_as_float(r[0]) : __uint_as_float(r[1]);
 }
 
-// NW = waves per workgroup (they split the hidden dimension), KS = k-steps (of 32) per wave when
-// known at compile time (then every load of the wave is issued before the first multiply), 0 = loop.
-template <int MT, int NW, int KS>
+// NW = waves per workgroup (they split the hidden dimension).
+template <int MT, int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_proj_skinny(ProjArgs p)
 {
     __shared__ float red[NW - 1][MT][4][64];
@@ -109,46 +108,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    if (KS > 0) {
-        // All weight loads of the wave and the first half of its activation loads are issued before
-        // the first multiply; the second half follows once the first has been consumed, which keeps
-        // the kernel within 128 registers so that two workgroups share a compute unit.
-        constexpr int H = KS / 2;
-        bf16x8 wf[KS > 0 ? KS : 1], xf[MT][H > 0 ? H : 1];
+    const int ks = kq >> 5;
+    rope_table();
+    for (int s = 0; s < ks; ++s) {
+        const bf16x8 wfrag = ld8(wrow + 32 * s);
 #pragma unroll
-        for (int s = 0; s < KS; ++s) wf[s] = (FC_PROJ_VARIANT == 2) ? bf16x8{} : ld8(wrow + 32 * s);
-#pragma unroll
-        for (int s = 0; s < H; ++s)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) xf[mt][s] = (FC_PROJ_VARIANT == 1) ? wf[s] : ld8(xrow[mt] + 32 * s);
-        __builtin_amdgcn_sched_barrier(0);
-        rope_table();
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int s = 0; s < H; ++s)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[s], xf[mt][s], acc[mt], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int s = 0; s < H; ++s)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) xf[mt][s] = (FC_PROJ_VARIANT == 1) ? wf[H + s] : ld8(xrow[mt] + 32 * (H + s));
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int s = 0; s < H; ++s)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[H + s], xf[mt][s], acc[mt], 0, 0, 0);
-    } else {
-        const int ks = kq >> 5;
-        rope_table();
-        for (int s = 0; s < ks; ++s) {
-            const bf16x8 wfrag = ld8(wrow + 32 * s);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wfrag, ld8(xrow[mt] + 32 * s), acc[mt], 0, 0, 0);
-        }
+        for (int mt = 0; mt < MT; ++mt)
+            acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wfrag, ld8(xrow[mt] + 32 * s), acc[mt], 0, 0, 0);
     }
 
     // sum the partial tiles of the NW waves in wave 0
@@ -224,8 +190,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
 // swizzled) and shared by the 8 waves instead of being re-read by every 16-row tile.  The partial
 // tiles of the hidden-dimension slices of a head go to the cache's device scratch and are summed
 // by k_proj_finish.  Bound by one pass over the weights and its first latency: at 36 head slots and hidden 3584
-// (252 workgroups, one per compute unit) 9.2 us for 33 MB.  A whole-row kernel without partial tiles (18 rows
-// per compute unit) was slower, 15.3 us at 32 rows: every compute unit then reads all of X.
+// (252 workgroups, one per compute unit) 9.2 us for 33 MB.
 constexpr int HS_K = 512;  // hidden elements per workgroup
 
 __device__ __forceinline__ void load_lds16p(const void *g, void *l)
@@ -382,6 +347,196 @@ __global__ __launch_bounds__(64) void k_proj_finish(ProjArgs p)
     }
 }
 
+// -------------------------------------------------------------------------------------------------
+// Whole-row kernel for windows of at most 32 rows and hidden sizes of 512, 3584 and 4096 (the window rows fit in registers).
+//
+// Every workgroup owns an equal run of rotary pairs (rows i and i + 64 of a head; 9 pairs at 36 head slots) and takes
+// them in items of 8 NF pairs over the whole hidden dimension, so no partial tiles leave the workgroup: its eight
+// waves cut the hidden dimension, keep their part of X in operand registers, and sum their tiles through LDS.
+//   NF = 1: one operand of 16 weight rows, lanes 0 .. 7 the first rows of 8 pairs, 8 .. 15 their partners
+//   NF = 2: two operands, the first rows of up to 16 pairs and their partners
+// X comes by way of LDS in whole cache lines (direct-to-LDS, 16 rows at a time, chunks permuted against bank conflicts):
+// loaded straight into operand registers, half a line per row and load, it was 7 us of the kernel at 32 rows.  One launch:
+// 36 head slots, hidden 3584, 16 / 32 rows 9.9 / 11.3 us (head-split and its finish 11.5 / 12.6); 96 slots, hidden 4096,
+// 32 rows 22.8 us (26.7 in the tiled GEMM); 12 slots, hidden 512, 4.2 (6.6).
+template <int N>
+__device__ __forceinline__ void wait_vm()
+{
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+
+template <int MT, int NKW, int NF>
+__global__ __launch_bounds__(512) void k_proj_rows(ProjArgs p)
+{
+    extern __shared__ __align__(1024) unsigned char lds[];
+    float(*red)[8][NF][MT * 4][64] = (float(*)[8][NF][MT * 4][64])lds;  // [2]
+    constexpr int XROW = NKW * 64;  // bytes of a wave's part of an X row
+    auto xswz = [](int r) { return NKW % 4 == 0 ? r & 15 : (r >> 1) & 7; };
+    const FcGeom &G = p.G;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rho = lane & 15, q = lane >> 4;
+    const int n_pairs = p.n_tiles * 8;
+    int g0 = (int)((int64_t)blockIdx.x * n_pairs / gridDim.x);
+    const int g1 = (int)(((int64_t)blockIdx.x + 1) * n_pairs / gridDim.x);
+    const int kw0 = wave * (NKW * 32) + 8 * q;
+
+    // weight row of this lane in operand f of the item that starts at pair g (past the end: the run's last pair)
+    auto wrow_of = [&](int g, int f) -> const uint16_t * {
+        const int gp = min(g + (NF == 1 ? rho & 7 : rho), g1 - 1);
+        const bool partner = NF == 1 ? rho >= 8 : f == 1;
+        return p.W + ((size_t)(gp >> 6) * 128 + (gp & 63) + (partner ? 64 : 0)) * p.K + kw0;
+    };
+    bf16x8 xr[NKW][MT], wf[NKW][NF];
+    unsigned char *xw = lds + wave * (16 * XROW);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+        for (int i = 0; i < NKW; ++i) {
+            const int byte = 1024 * i + 16 * lane, r = byte / XROW, c = (byte - r * XROW) >> 4;
+            const int m = min(16 * mt + r, p.M - 1);  // padding rows read a valid row
+            load_lds16p(p.X + (size_t)m * p.K + wave * (NKW * 32) + 8 * (c ^ xswz(r)), xw + 1024 * i);
+        }
+        if (mt == MT - 1) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                const uint16_t *w = wrow_of(g0, f);
+#pragma unroll
+                for (int s = 0; s < NKW; ++s) wf[s][f] = ld8(w + 32 * s);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            wait_vm<NKW * NF>();  // everything before the weights
+        } else {
+            wait_vm<0>();
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < NKW; ++s)
+            xr[s][mt] = *(const bf16x8 *)(xw + rho * XROW + (((4 * s + q) ^ xswz(rho)) << 4));
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the LDS rows may be overwritten
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __builtin_amdgcn_s_barrier();  // the partial tiles reuse the area
+
+    // In the epilogue wave e < 4 MT finishes register r = e & 3 of window tile e >> 2; its lanes hold pair 4 q + r of an
+    // item (NF = 1: pair 4 (q & 1) + r, lanes q >= 2 the partner).
+    const int mt_e = wave >> 2, r_e = wave & 3;
+    const int m = 16 * mt_e + rho, mm = min(m, p.M - 1);
+    const int b = mm / p.A, a = mm - b * p.A;
+    const int pp = p.pos ? p.pos[mm] : p.win_start + a;
+    const bool valid = pp >= 0 && pp < G.max_seq;
+    const int pair_e = NF == 1 ? 4 * (q & 1) + r_e : 4 * q + r_e;
+
+    f32x4 acc[NF][MT];
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[f][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int buf = 0;
+    auto item = [&](int g, auto more) {
+        constexpr bool MORE = decltype(more)::value;
+        // what the epilogue needs besides, while the weights are on their way
+        const int gp = min(g + pair_e, g1 - 1), hs = gp >> 6, i = gp & 63;
+        float bs[2] = {0.f, 0.f};
+        if (p.bias) {
+            bs[0] = fc_to_float(bf16_t{p.bias[hs * 128 + i]});
+            bs[1] = fc_to_float(bf16_t{p.bias[hs * 128 + i + 64]});
+        }
+        double f = 0.15915494309189533576888;  // base^(-i/64) / (2 pi): turns per position
+#pragma unroll
+        for (int bit = 0; bit < 6; ++bit)
+            if (i & (1 << bit)) f *= p.rot[bit];
+        const double turns = (double)pp * f;
+        const float fr = (float)(turns - rint(turns));
+        const bool rotate = hs < G.Hq + G.Hkv;
+        const float cs = rotate ? __builtin_amdgcn_cosf(fr) : 1.f, sn = rotate ? __builtin_amdgcn_sinf(fr) : 0.f;
+        __builtin_amdgcn_sched_barrier(0);
+
+        const uint16_t *nxt[NF];
+#pragma unroll
+        for (int f2 = 0; f2 < NF; ++f2)
+            if (MORE) nxt[f2] = wrow_of(g + 8 * NF, f2);
+#pragma unroll
+        for (int s = 0; s < NKW; ++s)
+#pragma unroll
+            for (int f2 = 0; f2 < NF; ++f2) {
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    acc[f2][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[s][f2], xr[s][mt], acc[f2][mt], 0, 0, 0);
+                if (MORE) wf[s][f2] = ld8(nxt[f2] + 32 * s);
+            }
+#pragma unroll
+        for (int f2 = 0; f2 < NF; ++f2)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    red[buf][wave][f2][mt * 4 + r][lane] = acc[f2][mt][r];
+                    acc[f2][mt][r] = 0.f;
+                }
+        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the tile is in LDS
+        __builtin_amdgcn_s_barrier();
+        if (wave < 4 * MT) {
+            float y0 = 0.f, y1 = 0.f;  // NF = 1: own value and partner's; NF = 2: first row and partner
+#pragma unroll
+            for (int w2 = 0; w2 < 8; ++w2) {
+                y0 += red[buf][w2][0][wave][lane];
+                y1 += NF == 1 ? red[buf][w2][0][wave][lane ^ 32] : red[buf][w2][NF - 1][wave][lane];
+            }
+            const bool second = NF == 1 && q >= 2;
+            y0 += second ? bs[1] : bs[0];
+            y1 += second ? bs[0] : bs[1];
+            const uint16_t o0 = fc_bf16_bits(second ? y0 * cs + y1 * sn : y0 * cs - y1 * sn);
+            const uint16_t o1 = fc_bf16_bits(y1 * cs + y0 * sn);
+            const int d0 = i + (second ? 64 : 0);
+            if (m < p.M && g + pair_e < g1) {
+                if (hs < G.Hq) {
+                    uint16_t *d = p.Q + (((size_t)b * G.Hq + hs) * p.A + a) * 128;
+                    d[d0] = valid ? o0 : 0;
+                    if (NF == 2) d[i + 64] = valid ? o1 : 0;
+                } else if (valid) {
+                    const bool is_k = hs < G.Hq + G.Hkv;
+                    const int j = hs - G.Hq - (is_k ? 0 : G.Hkv);
+                    uint16_t *base = is_k ? p.Kc : p.Vc;
+                    base[is_k ? fc_k_index(G, b, j, pp, d0) : fc_v_index(G, b, j, pp, d0)] = o0;
+                    if (NF == 2) base[is_k ? fc_k_index(G, b, j, pp, i + 64) : fc_v_index(G, b, j, pp, i + 64)] = o1;
+                }
+            }
+        }
+        buf ^= 1;
+    };
+    if constexpr (NF == 1)
+        for (; g0 + 8 < g1; g0 += 8) item(g0, std::true_type());
+    item(g0, std::false_type());
+}
+
+template <int MT, int NKW, int NF>
+hipError_t launch_rows(const ProjArgs &a, hipStream_t s)
+{
+    constexpr int X = 8 * 16 * NKW * 64, RED = 2 * 8 * NF * MT * 4 * 64 * 4, LDS = X > RED ? X : RED;
+    static hipError_t attr = hipFuncSetAttribute((const void *)k_proj_rows<MT, NKW, NF>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+    if (attr != hipSuccess) return attr;
+    const int groups = a.n_tiles;  // of eight pairs
+    k_proj_rows<MT, NKW, NF><<<dim3((unsigned)(groups < 256 ? groups : 256)), dim3(512), LDS, s>>>(a);
+    return hipGetLastError();
+}
+
+// Two operands (one item of up to 16 pairs) where the runs are of 9 .. 16 pairs: with one they would be two items, the
+// second nearly empty (36 head slots, hidden 3584, 32 rows: 11.3 against 11.9 us).  At hidden 4096 they do not fit in
+// registers.
+template <int MT>
+hipError_t launch_rows_mt(const ProjArgs &a, hipStream_t s)
+{
+    const int run = (a.n_tiles * 8 + 255) / 256;
+    if (a.K == 512) return launch_rows<MT, 2, 1>(a, s);
+    if (a.K == 4096) return launch_rows<MT, 16, 1>(a, s);
+    return run > 8 && run <= 16 ? launch_rows<MT, 14, 2>(a, s) : launch_rows<MT, 14, 1>(a, s);
+}
+
+bool rows_covers(int M, int K) { return M <= 32 && (K == 512 || K == 3584 || K == 4096); }
+
 size_t headsplit_bytes(int slots, int M, int K)
 {
     return (size_t)slots * (K / HS_K) * 8 * ((M + 15) / 16) * 256 * sizeof(float);
@@ -407,14 +562,8 @@ template <int MT>
 hipError_t launch_mt(const ProjArgs &a, int m_chunks, hipStream_t s)
 {
     const unsigned grid = (unsigned)(((a.n_tiles + 7) & ~7) * m_chunks);
-    if (a.K % 256 == 0) {  // eight waves split the hidden dimension
-        const int ks = a.K / 256;
-        if (ks == 14) k_proj_skinny<MT, 8, 14><<<dim3(grid), dim3(512), 0, s>>>(a);
-        else if (ks == 16) k_proj_skinny<MT, 8, 16><<<dim3(grid), dim3(512), 0, s>>>(a);
-        else k_proj_skinny<MT, 8, 0><<<dim3(grid), dim3(512), 0, s>>>(a);
-    } else {
-        k_proj_skinny<MT, 4, 0><<<dim3(grid), dim3(256), 0, s>>>(a);
-    }
+    if (a.K % 256 == 0) k_proj_skinny<MT, 8><<<dim3(grid), dim3(512), 0, s>>>(a);  // eight waves split the hidden dimension
+    else k_proj_skinny<MT, 4><<<dim3(grid), dim3(256), 0, s>>>(a);
     return hipGetLastError();
 }
 
@@ -436,6 +585,7 @@ bool fc_project_prefers_gemm(const fc_config &cfg, int M, bool scratch)
 {
     if (!fc_project_gemm_supported(cfg, M)) return false;
     if (fc_knobs().proj_gemm_shape >= 0 && M > 32) return true;  // tuning knob
+    if (rows_covers(M, cfg.hidden)) return false;
     const int slots = cfg.n_q_heads + 2 * cfg.n_kv_heads, mt = (M + 15) / 16;
     if (!scratch || !headsplit_covers(slots, M, cfg.hidden)) return M > 32;
     const double weights = 256.0 * slots * cfg.hidden, part = (double)headsplit_bytes(slots, 16, cfg.hidden);
@@ -466,6 +616,7 @@ hipError_t fc_launch_project_mfma(const FcGeom &G, const double *inv_freq, const
     a.partials = (float *)scratch;
     for (int i = 0; i < 6; ++i) a.rot[i] = exp(-G.log_base * (1 << i) / 64.0);
     const int slots = G.Hq + 2 * G.Hkv, mt = (a.M + 15) / 16;
+    if (rows_covers(a.M, a.K)) return mt == 1 ? launch_rows_mt<1>(a, s) : launch_rows_mt<2>(a, s);
     if (scratch && headsplit_covers(slots, a.M, a.K)) {
         a.mt = mt;
         switch (mt) {

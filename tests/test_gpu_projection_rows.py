@@ -1,5 +1,6 @@
-"""GPU parity of the head-split projection at 33 .. 128 window rows (each number of 16-row tiles, ragged last tiles) and
-at the sizes where the tiled GEMM takes over, with bias and with padded and out-of-range positions."""
+"""GPU parity of the projection kernels at the edges of their ranges, with bias and with padded and out-of-range
+positions: whole rows up to 32 window rows (runs of less than an item, of one and of several), head-split at 33 .. 128
+(each number of 16-row tiles, ragged last tiles), and the sizes where the tiled GEMM takes over."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +15,10 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("B,d,Hq,Hkv,A", [
     (1, 3584, 4, 1, 33), (1, 3584, 2, 1, 48), (3, 3584, 4, 2, 19), (1, 4096, 3, 1, 65), (4, 3584, 2, 2, 24),
     (2, 4096, 2, 1, 50), (1, 3584, 2, 1, 127), (1, 3584, 2, 1, 128),  # head-split, three to eight tiles
-    (1, 3584, 2, 1, 129), (1, 512, 4, 2, 5), (2, 512, 2, 1, 15),      # tiled GEMM: more rows; few rows of a small matrix
+    (1, 3584, 2, 1, 129), (1, 768, 4, 2, 33), (1, 1024, 2, 1, 20),    # tiled GEMM: more rows; few rows of a small matrix
+    (1, 512, 4, 2, 5), (2, 512, 30, 5, 16), (1, 512, 60, 4, 17),       # whole rows, hidden 512: one item or two per run
+    (1, 3584, 28, 4, 32), (2, 3584, 30, 5, 8), (1, 3584, 3, 1, 9),     # hidden 3584: 9 or 10 pairs in one item; 8 pairs
+    (1, 4096, 33, 3, 18), (3, 4096, 1, 1, 5),                          # hidden 4096: 9 or 10 pairs in two items; few
 ])
 def test_projection_rows(B, d, Hq, Hkv, A):
     print("[case] projection rows", B, d, Hq, Hkv, A, flush=True)

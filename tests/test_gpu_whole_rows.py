@@ -1,0 +1,24 @@
+"""GPU parity of the whole-row linear kernels where their ranges end: fewer items than compute units, one item, half
+items, and vocabularies that are no multiple of anything."""
+import pytest
+
+from paper_2505_21467_amd import inputs
+from tests.test_gpu_gemm_shapes import _linear
+from tests.test_gpu_unmask import _check_lm_head
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,K,N,gated", [
+    (32, 3584, 8, False), (17, 3584, 264, False), (1, 4096, 24, False), (16, 3584, 4, True), (31, 4096, 52, True),
+    (32, 512, 4104, False), (5, 512, 2052, True),
+])
+def test_few_items(M, K, N, gated):
+    _linear(M, K, N, gated, "whole rows")
+
+
+@pytest.mark.parametrize("M,K,V", [(20, 3584, 1001), (32, 512, 15999), (1, 4096, 9), (16, 512, 8193)])
+def test_odd_vocabulary(M, K, V):
+    print("[case] odd vocabulary", M, K, V, flush=True)
+    x, w = inputs.normal(31, "x", (M, K), 1.0, "bf16"), inputs.normal(31, "w", (V, K), 0.03, "bf16")
+    _check_lm_head("bf16", x, w, "vocabulary of %d" % V)
