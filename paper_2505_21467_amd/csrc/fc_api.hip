@@ -883,13 +883,12 @@ fc_status fc_full_layer_step(fc_cache *cache, int32_t layer, const fc_layer_weig
 
 namespace {
 
-// Carve-up of the lm-head workspace: [partial tiles of the streaming kernels][mx][arg][sm], each
-// [parts][M].
+// Carve-up of the lm-head workspace: [partial tiles of the streaming kernels][(largest, index, sum) per part and row].
 struct LmHeadWs {
     FcWidePlan wide;
     FcSkinnyPlan plan;
     int parts;
-    size_t tiles, mx, arg, sm, total;
+    size_t tiles, am, total;
 };
 
 LmHeadWs lm_head_ws(int dtype, int M, int K, int V)
@@ -909,9 +908,7 @@ LmHeadWs lm_head_ws(int dtype, int M, int K, int V)
         return at;
     };
     w.tiles = take(fc_skinny_workspace(w.plan));
-    w.mx = take((size_t)w.parts * M * 4);
-    w.arg = take((size_t)w.parts * M * 4);
-    w.sm = take((size_t)w.parts * M * 4);
+    w.am = take((size_t)w.parts * ((M + 7) / 8 * 8) * sizeof(FcArgmax));
     w.total = off;
     return w;
 }
@@ -941,9 +938,8 @@ fc_status fc_lm_head_argmax(int32_t dtype, const void *x, const void *w_vocab, i
                     workspace ? workspace_bytes : (size_t)0);
     char *ws = (char *)workspace;
     FcArgmaxPart am;
-    am.mx = (float *)(ws + w.mx);
-    am.arg = (int32_t *)(ws + w.arg);
-    am.sm = (float *)(ws + w.sm);
+    am.p = (FcArgmax *)(ws + w.am);
+    am.parts = w.parts;
     hipError_t e;
     if (w.wide.kind == 1)
         e = fc_launch_linear_wide(w.wide, FC_LIN_VOCAB, x, w_vocab, nullptr, nullptr, M, K, V, nullptr, nullptr,
@@ -953,7 +949,7 @@ fc_status fc_lm_head_argmax(int32_t dtype, const void *x, const void *w_vocab, i
                                     (hipStream_t)stream, &am);
     else
         e = fc_launch_lmhead_tile(dtype, x, w_vocab, M, K, V, am, (hipStream_t)stream);
-    if (e == hipSuccess) e = fc_launch_lmhead_reduce(am, w.parts, M, tok, conf, (hipStream_t)stream);
+    if (e == hipSuccess) e = fc_launch_lmhead_reduce(am, M, tok, conf, (hipStream_t)stream);
     return e == hipSuccess ? FC_OK : hip_fail(e, "lm-head launch");
 }
 

@@ -332,12 +332,7 @@ __global__ __launch_bounds__(TW * 64) void k_linear_tile(TileArgs p)
                 fc_argmax_merge(run_mx, run_arg, run_sm, mx2, arg2, sm2);
             }
             const int m = m0 + 16 * ti + rho;
-            if (q == 0 && m < p.M) {
-                const size_t at = (size_t)n_blk * p.M + m;
-                p.am.mx[at] = run_mx;
-                p.am.arg[at] = run_arg;
-                p.am.sm[at] = run_sm;
-            }
+            if (q == 0 && m < p.M) p.am.at(n_blk, m) = FcArgmax{run_mx, run_arg, run_sm};
         }
     }
 }
@@ -607,6 +602,38 @@ __global__ __launch_bounds__(256) void k_rmsnorm(const T *X, const T *__restrict
     for (int k = tid; k < d; k += 256) out[row * d + k] = fc_from_float<T>(fc_to_float(x[k]) * inv * fc_to_float(w[k]));
 }
 
+// fp32 rows whose length is a multiple of 4 and at most 1024 NJ: as below.  (Hidden 384, 40 rows: 3.4 us with a second
+// pass over the row and the weight behind the sum, now 2.9.)
+template <int NJ>
+__global__ __launch_bounds__(256) void k_rmsnorm_f32_row(const float *X, const float *__restrict__ w, float eps, int d, float *out)
+{
+    __shared__ float red[4];
+    const size_t row = blockIdx.x;
+    const int tid = threadIdx.x, chunks = d >> 2;
+    float4 v[NJ], g[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int c = tid + 256 * j;
+        v[j] = c < chunks ? *(const float4 *)(X + row * d + 4 * c) : make_float4(0.f, 0.f, 0.f, 0.f);
+        g[j] = c < chunks ? *(const float4 *)(w + 4 * c) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    float ss = 0.f;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) ss += (v[j].x * v[j].x + v[j].y * v[j].y) + (v[j].z * v[j].z + v[j].w * v[j].w);
+    ss = wave_sum(ss);
+    if ((tid & 63) == 0) red[tid >> 6] = ss;
+    __syncthreads();
+    const float tot = (red[0] + red[1]) + (red[2] + red[3]);
+    const float inv = 1.0f / sqrtf(tot / (float)d + eps);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int c = tid + 256 * j;
+        if (c < chunks)
+            *(float4 *)(out + row * d + 4 * c) = make_float4(v[j].x * inv * g[j].x, v[j].y * inv * g[j].y, v[j].z * inv * g[j].z,
+                                                             v[j].w * inv * g[j].w);
+    }
+}
+
 // bf16 rows whose length is a multiple of 8 and at most 2048 * NJ: every thread keeps its NJ 16-byte
 // pieces of the row in registers, so the row is read once.
 template <int NJ>
@@ -728,10 +755,17 @@ hipError_t fc_launch_copy_rows(const FcGeom &G, int dtype, void *k_layer, void *
 hipError_t fc_launch_rmsnorm(int dtype, const void *x, const void *weight, float eps, int rows, int d,
                              void *out, hipStream_t s)
 {
-    if (dtype == FC_F32)
+    const bool aligned = (((uintptr_t)x | (uintptr_t)weight | (uintptr_t)out) & 15) == 0;
+    if (dtype == FC_F32 && d % 4 == 0 && d <= 4096 && aligned) {
+        const float *xf = (const float *)x, *wf = (const float *)weight;
+        if (d <= 1024)
+            k_rmsnorm_f32_row<1><<<dim3((unsigned)rows), dim3(256), 0, s>>>(xf, wf, eps, d, (float *)out);
+        else
+            k_rmsnorm_f32_row<4><<<dim3((unsigned)rows), dim3(256), 0, s>>>(xf, wf, eps, d, (float *)out);
+    } else if (dtype == FC_F32)
         k_rmsnorm<float><<<dim3((unsigned)rows), dim3(256), 0, s>>>((const float *)x, (const float *)weight, eps,
                                                                     d, (float *)out);
-    else if (d % 8 == 0 && d <= 8192 && (((uintptr_t)x | (uintptr_t)weight | (uintptr_t)out) & 15) == 0) {
+    else if (d % 8 == 0 && d <= 8192 && aligned) {
         const uint16_t *xb = (const uint16_t *)x, *wb = (const uint16_t *)weight;
         if (d <= 2048)
             k_rmsnorm_bf16_row<1><<<dim3((unsigned)rows), dim3(256), 0, s>>>(xb, wb, eps, d, (uint16_t *)out);

@@ -110,11 +110,17 @@ hipError_t fc_launch_attention_mfma(const FcGeom &G, const FcAttnPlan &p, const 
 // Rest of the layer on the window rows: RMS normalisation and the linear layers around attention.
 enum { FC_LIN_RESIDUAL = 0, FC_LIN_GATE_UP = 1, FC_LIN_VOCAB = 2 };
 // Vocabulary mode: per (part of the vocabulary, row) the largest logit, its index and the sum of
-// exp(logit - largest) over the part, each array [parts][M].
+// exp(logit - largest) over the part, in groups of eight rows, [ceil(M / 8)][parts][8]: the merge reads a group's parts
+// in one piece.
+struct FcArgmax {
+    float mx;
+    int32_t arg;
+    float sm;
+};
 struct FcArgmaxPart {
-    float *mx;
-    int32_t *arg;
-    float *sm;
+    FcArgmax *p;
+    int parts;
+    __host__ __device__ FcArgmax &at(int part, int m) const { return p[((size_t)(m >> 3) * parts + part) * 8 + (m & 7)]; }
 };
 // (largest, index, sum) of a union of two parts; equal maxima keep the smaller index.
 __host__ __device__ inline void fc_argmax_merge(float &mx, int &arg, float &sm, float mx2, int arg2, float sm2)
@@ -158,7 +164,7 @@ hipError_t fc_launch_linear_skinny(const FcSkinnyPlan &pl, int mode, const void 
 hipError_t fc_launch_lmhead_tile(int dtype, const void *x, const void *w, int M, int K, int V,
                                  const FcArgmaxPart &am, hipStream_t s);
 #define FC_LMHEAD_TILE_PART 32  // vocabulary entries per part of that kernel
-hipError_t fc_launch_lmhead_reduce(const FcArgmaxPart &am, int parts, int M, int32_t *tok, float *conf,
+hipError_t fc_launch_lmhead_reduce(const FcArgmaxPart &am, int M, int32_t *tok, float *conf,
                                    hipStream_t s);
 #define FC_UNMASK_MAX_ROWS 8192
 hipError_t fc_launch_unmask_select(const int32_t *tok, const float *conf, const int32_t *pos, int win_start,

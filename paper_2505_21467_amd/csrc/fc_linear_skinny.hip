@@ -175,80 +175,68 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(KSL >= 512 
     }
 }
 
-// Sum of a slab's partial tiles + epilogue; one wave per (slab, 16-row tile of W), grid.y = m chunk.
+// Sum of a slab's partial tiles + epilogue; one wave per (slab, 16-row tile of W, m chunk, 16 rows of X).  One memory
+// round trip long where a slab met at most twelve runs, whose partial tiles are then all in flight (28 slabs,
+// hidden 18944, 32 rows: 4.6 us with both row tiles in one wave and four in flight, now 4.0).
 template <int MT, int KSL, int MODE>
 __global__ __launch_bounds__(64) void k_linear_finish(LinArgs p)
 {
-    constexpr int KS = KSL / 32;
+    constexpr int KS = KSL / 32, SEGS = 12;
     const int64_t U = (int64_t)p.T * KS;
-    const int slab = blockIdx.x >> 3, wave = blockIdx.x & 7;
-    const int m0 = blockIdx.y * 32;
+    const int slab = blockIdx.x >> 3, wave = blockIdx.x & 7, mt = blockIdx.z;
     const int lane = threadIdx.x, rho = lane & 15, q = lane >> 4;
+    const int m = blockIdx.y * 32 + 16 * mt + rho;
+    const bool mvalid = m < p.M;
     const int first = owner_of((int64_t)slab * p.S * KS, U, p.G);
     const int nseg = owner_of((int64_t)(slab + 1) * p.S * KS - 1, U, p.G) - first + 1;
-    const float *base = p.partials + ((((size_t)blockIdx.y * p.slabs + slab) * p.maxseg) * 8 + wave) * (MT * 256);
+    const float *base = p.partials + ((((size_t)blockIdx.y * p.slabs + slab) * p.maxseg) * 8 + wave) * (MT * 256) + mt * 256 + lane;
     const size_t seg_stride = (size_t)8 * MT * 256;
 
-    f32x4 acc[MT];
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    uint2 rv = make_uint2(0, 0);
+    for (int s0 = 0; s0 < nseg; s0 += SEGS) {
+        float v[SEGS][4];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0; s0 < nseg; s0 += 4) {  // four segments' worth of loads in flight
-        float v[4][MT][4];
+        for (int u = 0; u < SEGS; ++u)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float *pp = base + (size_t)min(s0 + u, nseg - 1) * seg_stride;
+            for (int r = 0; r < 4; ++r) v[u][r] = base[(size_t)min(s0 + u, nseg - 1) * seg_stride + r * 64];
+        if (MODE == FC_LIN_RESIDUAL && s0 == 0 && p.res && mvalid)
+            rv = *(const uint2 *)(p.res + (size_t)m * p.N + slab * 128 + wave * 16 + 4 * q);
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[u][mt][r] = pp[mt * 256 + r * 64 + lane];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < SEGS; ++u)
             if (s0 + u < nseg) {
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[mt][r] += v[u][mt][r];
+                for (int r = 0; r < 4; ++r) acc[r] += v[u][r];
             }
     }
 
+    float y[4];
+    int n;
+    if (MODE == FC_LIN_GATE_UP) {
+        // lanes q = 0, 1 hold the gate products of outputs 4q + r, lanes q = 2, 3 the up products
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const int m = m0 + 16 * mt + rho;
-        const bool mvalid = m < p.M;
-        float y[4];
-        if (MODE == FC_LIN_GATE_UP) {
-            // lanes q = 0, 1 hold the gate products of outputs 4q + r, lanes q = 2, 3 the up products
+        for (int r = 0; r < 4; ++r) {
+            const float other = swap32(acc[r]);
+            y[r] = acc[r] / (1.0f + expf(-acc[r])) * other;
+        }
+        if (!mvalid || q >= 2) return;
+        n = slab * 64 + wave * 8 + 4 * q;
+    } else {
+        if (!mvalid) return;
+        n = slab * 128 + wave * 16 + 4 * q;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float other = swap32(acc[mt][r]);
-                const float g = acc[mt][r];
-                y[r] = g / (1.0f + expf(-g)) * other;
-            }
-            if (!mvalid || q >= 2) continue;
-            const int f = slab * 64 + wave * 8 + 4 * q;
-            uint2 w;
-            w.x = (uint32_t)fc_bf16_bits(y[0]) | ((uint32_t)fc_bf16_bits(y[1]) << 16);
-            w.y = (uint32_t)fc_bf16_bits(y[2]) | ((uint32_t)fc_bf16_bits(y[3]) << 16);
-            *(uint2 *)(p.out + (size_t)m * p.N + f) = w;
-        } else {
-            if (!mvalid) continue;
-            const int n = slab * 128 + wave * 16 + 4 * q;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) y[r] = acc[mt][r];
-            if (p.res) {
-                const uint2 rv = *(const uint2 *)(p.res + (size_t)m * p.N + n);
-                y[0] += __uint_as_float(rv.x << 16);
-                y[1] += __uint_as_float(rv.x & 0xffff0000u);
-                y[2] += __uint_as_float(rv.y << 16);
-                y[3] += __uint_as_float(rv.y & 0xffff0000u);
-            }
-            uint2 w;
-            w.x = (uint32_t)fc_bf16_bits(y[0]) | ((uint32_t)fc_bf16_bits(y[1]) << 16);
-            w.y = (uint32_t)fc_bf16_bits(y[2]) | ((uint32_t)fc_bf16_bits(y[3]) << 16);
-            *(uint2 *)(p.out + (size_t)m * p.N + n) = w;
+        for (int r = 0; r < 4; ++r) y[r] = acc[r];
+        if (p.res) {
+            y[0] += __uint_as_float(rv.x << 16);
+            y[1] += __uint_as_float(rv.x & 0xffff0000u);
+            y[2] += __uint_as_float(rv.y << 16);
+            y[3] += __uint_as_float(rv.y & 0xffff0000u);
         }
     }
+    uint2 w;
+    w.x = (uint32_t)fc_bf16_bits(y[0]) | ((uint32_t)fc_bf16_bits(y[1]) << 16);
+    w.y = (uint32_t)fc_bf16_bits(y[2]) | ((uint32_t)fc_bf16_bits(y[3]) << 16);
+    *(uint2 *)(p.out + (size_t)m * p.N + n) = w;
 }
 
 // Vocabulary mode (the unmasking step, section 3.1): the outputs of a slab are 128 logits per row, of
@@ -303,10 +291,7 @@ __global__ __launch_bounds__(512) void k_lmhead_finish(LinArgs p)
         float mx = s_mx[0][row], sm = s_sm[0][row];
         int arg = s_arg[0][row];
         for (int w2 = 1; w2 < 8; ++w2) fc_argmax_merge(mx, arg, sm, s_mx[w2][row], s_arg[w2][row], s_sm[w2][row]);
-        const size_t at = (size_t)slab * p.M + m0 + row;
-        p.am.mx[at] = mx;
-        p.am.arg[at] = arg;
-        p.am.sm[at] = sm;
+        p.am.at(slab, m0 + row) = FcArgmax{mx, arg, sm};
     }
 }
 
@@ -520,12 +505,8 @@ __global__ __launch_bounds__(512) void k_linear_rows(LinArgs p)
         finish_item(it1 - 1, buf ^ 1);
         if (MODE != FC_LIN_VOCAB) flush(it1);
     }
-    if (MODE == FC_LIN_VOCAB && wave < MT && q == 0 && 16 * wave + rho < p.M) {
-        const size_t at = (size_t)wg * p.M + 16 * wave + rho;
-        p.am.mx[at] = run_mx;
-        p.am.arg[at] = run_arg;
-        p.am.sm[at] = run_sm;
-    }
+    if (MODE == FC_LIN_VOCAB && wave < MT && q == 0 && 16 * wave + rho < p.M)
+        p.am.at(wg, 16 * wave + rho) = FcArgmax{run_mx, run_arg, run_sm};
 }
 
 template <int MT, int NKW, int MODE>
@@ -547,7 +528,7 @@ constexpr int KSL = FC_LIN_KSL;  // hidden elements per work item
 template <int MODE>
 hipError_t launch_mode(const FcSkinnyPlan &pl, const LinArgs &a, hipStream_t s)
 {
-    const dim3 g1((unsigned)pl.G, (unsigned)pl.chunks), g2((unsigned)pl.slabs * 8, (unsigned)pl.chunks);
+    const dim3 g1((unsigned)pl.G, (unsigned)pl.chunks), g2((unsigned)pl.slabs * 8, (unsigned)pl.chunks, (unsigned)pl.mt);
     if (pl.mt == 1) {
         k_linear_stream<1, KSL, MODE><<<g1, dim3(512), 0, s>>>(a);
         k_linear_finish<1, KSL, MODE><<<g2, dim3(64), 0, s>>>(a);

@@ -318,12 +318,7 @@ __device__ __forceinline__ void gemm_epilogue_vocab(const GemmArgs &p, const f32
         const float mx2 = __shfl_xor(mx, 32, 64), sm2 = __shfl_xor(sm, 32, 64);
         const int arg2 = __shfl_xor(arg, 32, 64);
         fc_argmax_merge(mx, arg, sm, mx2, arg2, sm2);
-        if (hi == 0 && m < p.m_end) {
-            const size_t at = (size_t)hs * p.M + m;
-            p.am.mx[at] = mx;
-            p.am.arg[at] = arg;
-            p.am.sm[at] = sm;
-        }
+        if (hi == 0 && m < p.m_end) p.am.at(hs, m) = FcArgmax{mx, arg, sm};
     }
 }
 
