@@ -377,12 +377,12 @@ __device__ __forceinline__ void attn_store_row4(const AttnTileArgs &p, int bj, i
     store4((T *)p.out + ((size_t)b * p.A + a) * ((size_t)G.Hq * G.Dh) + (size_t)(j * G.g + hg) * G.Dh + d0, y);
 }
 
-template <typename T, int DH, int QT>
+template <typename T, int DH, int QT, int DS>
 __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
 {
     typedef Op<T> O;
     typedef typename O::frag frag;
-    constexpr int KB = O::KB, NKB = DH / (4 * KB), ND = DH / 16, ROW = DH + AT_STRIDE;
+    constexpr int KB = O::KB, NKB = DH / (4 * KB), DV = DH / DS, ND = DV / 16, ROW = DV + AT_STRIDE;
     constexpr bool F32 = KB == 4;
     constexpr int NV = F32 ? 2 : 1;  // V fragments per 16 head-dim rows and 32 keys
     extern __shared__ __align__(16) unsigned char attn_smem[];
@@ -392,7 +392,8 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rho = lane & 15, q = lane >> 4;
-    const int split = blockIdx.x % p.splits, bt = blockIdx.x / p.splits;
+    const int dv0 = (int)(blockIdx.x % DS) * DV;  // this workgroup's part of the head dimension of V
+    const int split = blockIdx.x / DS % p.splits, bt = blockIdx.x / DS / p.splits;
     const int tile = bt % p.tiles, bj = bt / p.tiles;
     const int b = bj / G.Hkv, j = bj % G.Hkv;
     const T *kc = (const T *)p.Kc + (size_t)bj * G.spad * DH, *vc = (const T *)p.Vc + (size_t)bj * G.spad * DH;
@@ -437,7 +438,7 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
         for (int d = 0; d < ND; ++d)
 #pragma unroll
             for (int h = 0; h < NV; ++h)
-                vf[d][h] = *(const frag *)(vt + (16 * d + rho) * FC_VTILE + (F32 ? 16 * h : 0) + KB * q);
+                vf[d][h] = *(const frag *)(vt + (dv0 + 16 * d + rho) * FC_VTILE + (F32 ? 16 * h : 0) + KB * q);
         f32x4 s[QT][2];
 #pragma unroll
         for (int u = 0; u < QT; ++u)
@@ -516,8 +517,8 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
         }
     }
     __syncthreads();
-    for (int idx = tid; idx < QT * 16 * (DH / 4); idx += TW * 64) {
-        const int row = idx / (DH / 4), d0 = 4 * (idx % (DH / 4));
+    for (int idx = tid; idx < QT * 16 * (DV / 4); idx += TW * 64) {
+        const int row = idx / (DV / 4), d0 = 4 * (idx % (DV / 4));
         float mm = -INFINITY;
 #pragma unroll
         for (int w = 0; w < TW; ++w) mm = fmaxf(mm, xml[(w * QT * 16 + row) * 2]);
@@ -536,10 +537,10 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
         }
         if (p.splits > 1) {
             const size_t at = ((size_t)bt * p.splits + split) * (QT * 16) + row;
-            *(float4 *)(p.part_o + at * DH + d0) = num;
-            if (d0 == 0) *(float2 *)(p.part_ml + at * 2) = make_float2(mm, den);
+            *(float4 *)(p.part_o + at * DH + dv0 + d0) = num;
+            if (dv0 + d0 == 0) *(float2 *)(p.part_ml + at * 2) = make_float2(mm, den);
         } else {
-            attn_store_row4<T>(p, bj, tile * (16 * QT) + row, d0, make_float4(num.x / den, num.y / den, num.z / den, num.w / den));
+            attn_store_row4<T>(p, bj, tile * (16 * QT) + row, dv0 + d0, make_float4(num.x / den, num.y / den, num.z / den, num.w / den));
         }
     }
 }
@@ -821,26 +822,34 @@ hipError_t launch_tile(int dtype, const TileArgs &a, int n_tiles, hipStream_t s)
     return dtype == FC_F32 ? launch_tile_t<float, EPI>(a, n_tiles, s) : launch_tile_t<bf16_t, EPI>(a, n_tiles, s);
 }
 
-template <typename T, int DH, int QT>
+template <typename T, int DH, int QT, int DS>
 hipError_t launch_attn_tile(const AttnTileArgs &a, hipStream_t s)
 {
-    constexpr size_t LDS = (size_t)TW * QT * 16 * (DH + AT_STRIDE + 2) * sizeof(float);
-    static hipError_t attr = hipFuncSetAttribute((const void *)k_attn_tile<T, DH, QT>,
+    constexpr size_t LDS = (size_t)TW * QT * 16 * (DH / DS + AT_STRIDE + 2) * sizeof(float);
+    static hipError_t attr = hipFuncSetAttribute((const void *)k_attn_tile<T, DH, QT, DS>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
     if (attr != hipSuccess) return attr;
     const int64_t bt = (int64_t)a.G.B * a.G.Hkv * a.tiles;
     if (bt * a.splits > (1 << 30) || bt * (QT * DH / 64) > (1 << 30)) return hipErrorInvalidValue;
-    k_attn_tile<T, DH, QT><<<dim3((unsigned)(bt * a.splits)), dim3(TW * 64), LDS, s>>>(a);
+    k_attn_tile<T, DH, QT, DS><<<dim3((unsigned)(bt * a.splits * DS)), dim3(TW * 64), LDS, s>>>(a);
     if (a.splits > 1) k_attn_tile_merge<T, DH, QT><<<dim3((unsigned)(bt * (QT * DH / 64))), dim3(256), 0, s>>>(a);
     return hipGetLastError();
 }
 
-template <typename T>
+// With a quarter or half of the compute units at most, the head dimension of V is cut in four or two: every part
+// repeats the scores, but the values it loads, its output products and the merge of its waves shrink (fp32, head_dim 64,
+// 8 workgroups, 288 keys: 8.4 us uncut, now 6.5; 861 keys in two ranges, with the merge 11.4, now 9.5).  With more workgroups
+// it costs more than it brings (144 of head_dim 128, 305 keys: 12.3 us, 18.5 in halves).
+template <typename T, int DH>
 hipError_t launch_attn_tile_t(int qt, const AttnTileArgs &a, hipStream_t s)
 {
-    if (a.G.Dh == 64) return qt == 2 ? launch_attn_tile<T, 64, 2>(a, s) : launch_attn_tile<T, 64, 1>(a, s);
-    if constexpr (sizeof(T) == 4) return qt == 1 ? launch_attn_tile<T, 128, 1>(a, s) : hipErrorInvalidValue;
-    return hipErrorInvalidValue;  // bf16 with head_dim 128 has its own kernel
+    if constexpr (DH == 64)
+        if (qt == 2) return launch_attn_tile<T, DH, 2, 1>(a, s);
+    if (qt != 1) return hipErrorInvalidValue;
+    const int64_t wgs = (int64_t)a.G.B * a.G.Hkv * a.tiles * a.splits;
+    if (wgs <= 64) return launch_attn_tile<T, DH, 1, 4>(a, s);
+    if (wgs <= 128) return launch_attn_tile<T, DH, 1, 2>(a, s);
+    return launch_attn_tile<T, DH, 1, 1>(a, s);
 }
 
 }  // namespace
@@ -926,6 +935,7 @@ hipError_t fc_launch_attention_tile(const FcGeom &G, const FcAttnPlan &pl, int d
         a.part_o = (float *)workspace;
         a.part_ml = a.part_o + (size_t)G.B * G.Hkv * a.tiles * pl.splits * 16 * pl.tiles_per_wg * G.Dh;
     }
-    return dtype == FC_F32 ? launch_attn_tile_t<float>(pl.tiles_per_wg, a, s)
-                           : launch_attn_tile_t<bf16_t>(pl.tiles_per_wg, a, s);
+    const int qt = pl.tiles_per_wg;
+    if (dtype == FC_F32) return G.Dh == 64 ? launch_attn_tile_t<float, 64>(qt, a, s) : G.Dh == 128 ? launch_attn_tile_t<float, 128>(qt, a, s) : hipErrorInvalidValue;
+    return G.Dh == 64 ? launch_attn_tile_t<bf16_t, 64>(qt, a, s) : hipErrorInvalidValue;  // (bf16 with head_dim 128 has its own kernel)
 }

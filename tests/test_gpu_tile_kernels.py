@@ -21,6 +21,10 @@ DEV = "cuda:0"
     ("f32", 3, 40, 12, 1, 128, 33, 100),    # 300 window rows: two weight tiles and 64 rows per workgroup
     ("bf16", 1, 200, 4, 2, 64, 1777, 5),    # bf16: permuted key rows, ranges, ragged last group
     ("bf16", 4, 136, 8, 8, 64, 31, 33),     # bf16, two tiles per workgroup, 132 rows
+    ("f32", 2, 40, 16, 4, 64, 50, 30),      # 64 workgroups: the head dimension of V in four parts
+    ("f32", 3, 40, 8, 4, 128, 90, 50),      # 84 workgroups: in two
+    ("bf16", 3, 40, 4, 4, 64, 200, 90),     # the same in bf16
+    ("f32", 5, 24, 4, 4, 128, 20, 100),     # 140: uncut
 ])
 def test_step_matches_oracle(dtype, B, d, Hq, Hkv, Dh, L, A):
     print("[case]", dtype, B, d, Hq, Hkv, Dh, L, A, flush=True)
