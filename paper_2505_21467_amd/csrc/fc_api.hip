@@ -181,6 +181,19 @@ double attn_cost(const AttnShape &sh, int64_t pairs, int row_tiles, int kv_len, 
     return t > 7.4 ? t : 7.4;
 }
 
+// The same for the tile kernel (one workgroup per sequence, kv head and 16 query rows, all keys, no merge kernel), which
+// has one round of at most 256 workgroups; with up to 64 / 128 of them the head dimension of V is cut in four / two.
+// Fitted to 130 shapes, 60 .. 1160 keys (rms error 3 .. 5 %), and used in that range.  Up to some 600 keys (64 workgroups) or 300 (256) it beats
+// every plan of the kernel above, whose stages, split partials and merge are made for long keys: 32 rows x 28 query heads,
+// 96 / 250 / 480 keys 8.8 / 9.5 / 10.3 us, tile kernel 4.6 / 5.8 / 8.0.
+double attn_tile_cost(int64_t wgs, int kv_len)
+{
+    const double groups = (double)((kv_len + 31) / 32);
+    if (wgs <= 64) return 3.58 + 0.275 * groups;
+    if (wgs <= 128) return 3.92 + 0.341 * groups;
+    return 4.28 + 0.229 * groups + 0.37e-4 * (double)wgs * kv_len;
+}
+
 // Most key ranges any plan for this many row tiles may use, whatever the length up to by_len (the workspace is sized by
 // it): one round of workgroups in some shape, or about 32 MB of partial results where a
 // round has few ranges.
@@ -281,6 +294,15 @@ FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len, size_t cap
                 set_attn_plan(p, sh.R, sh.W, splits, n_stages);
             }
         }
+    }
+    const int row_tiles = (g * A + 15) / 16;
+    if (kv_len <= 1200 && pairs * row_tiles <= 256 && attn_tile_cost(pairs * row_tiles, kv_len) < best) {
+        p.kind = 0;
+        p.row_tiles = row_tiles;
+        p.tiles_per_wg = 1;
+        p.waves = 8;
+        p.splits = p.splits_bound = 1;
+        p.keys_per_split = (kv_len + 31) / 32 * 32;
     }
     return p;
 }

@@ -937,5 +937,5 @@ hipError_t fc_launch_attention_tile(const FcGeom &G, const FcAttnPlan &pl, int d
     }
     const int qt = pl.tiles_per_wg;
     if (dtype == FC_F32) return G.Dh == 64 ? launch_attn_tile_t<float, 64>(qt, a, s) : G.Dh == 128 ? launch_attn_tile_t<float, 128>(qt, a, s) : hipErrorInvalidValue;
-    return G.Dh == 64 ? launch_attn_tile_t<bf16_t, 64>(qt, a, s) : hipErrorInvalidValue;  // (bf16 with head_dim 128 has its own kernel)
+    return G.Dh == 64 ? launch_attn_tile_t<bf16_t, 64>(qt, a, s) : G.Dh == 128 ? launch_attn_tile_t<bf16_t, 128>(qt, a, s) : hipErrorInvalidValue;
 }

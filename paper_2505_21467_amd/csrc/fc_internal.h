@@ -153,6 +153,7 @@ struct FcSkinnyPlan {
     int T;       // work items = slabs * S
     int G;       // workgroups
     int maxseg;  // upper bound of the workgroups that meet one slab
+    size_t reserve;  // kind 2: workspace asked of the caller and not used
 };
 FcSkinnyPlan fc_plan_skinny(int dtype, int mode, int M, int K, int N);
 size_t fc_skinny_workspace(const FcSkinnyPlan &p);

@@ -553,29 +553,11 @@ bool rows_kernel_covers(int K) { return K == 512 || K == 3584 || K == 4096; }
 
 }  // namespace
 
-FcSkinnyPlan fc_plan_skinny(int dtype, int mode, int M, int K, int N)
+// Runs of work items for the slice-wise kernel.
+static FcSkinnyPlan plan_slices(int dtype, int mode, int M, int K, int N, int target)
 {
     FcSkinnyPlan p;
     memset(&p, 0, sizeof p);
-    int target = 256;  // one workgroup per compute unit
-    if (fc_knobs().lin_wgs > 0) target = fc_knobs().lin_wgs;  // tuning and test knob: runs of any length
-    {
-        // whole-row kernel: at most 32 rows, a hidden size it is built for, whole half items (a vocabulary of any size)
-        const bool off = fc_knobs().lin_no_rows != 0;  // tuning knob
-        const int per_half = mode == FC_LIN_GATE_UP ? 4 : 8;
-        // (Fewer items than compute units are no reason for the slice-wise kernel: hidden 3584, 224 / 64 items
-        // 10.0 / 9.3 us against 12.6 / 11.4, its second launch included.)
-        const int halves = mode == FC_LIN_VOCAB || N % per_half == 0 ? (N + per_half - 1) / per_half : 0;
-        const int items = N >= per_half ? (halves + 1) / 2 : 0;
-        if (!off && dtype == FC_BF16 && M >= 1 && M <= 32 && rows_kernel_covers(K) && items >= 1) {
-            p.kind = 2;
-            p.mt = M <= 16 ? 1 : 2;
-            p.chunks = 1;
-            p.T = halves;
-            p.G = items < target ? items : target;  // at least one item each
-            return p;
-        }
-    }
     const int rows_per_slab = mode == FC_LIN_GATE_UP ? 64 : 128;  // FC_LIN_VOCAB: slabs of 128 vocabulary rows
     if (dtype != FC_BF16 || M < 1 || K < KSL || K % KSL != 0 || N < rows_per_slab || N % rows_per_slab != 0)
         return p;  // kind 0: plain kernel, no workspace
@@ -599,9 +581,34 @@ FcSkinnyPlan fc_plan_skinny(int dtype, int mode, int M, int K, int N)
     return p;
 }
 
+FcSkinnyPlan fc_plan_skinny(int dtype, int mode, int M, int K, int N)
+{
+    int target = 256;  // one workgroup per compute unit
+    if (fc_knobs().lin_wgs > 0) target = fc_knobs().lin_wgs;  // tuning and test knob: runs of any length
+    // whole-row kernel: at most 32 rows, a hidden size it is built for, whole half items (a vocabulary of any size)
+    const bool off = fc_knobs().lin_no_rows != 0;  // tuning knob
+    const int per_half = mode == FC_LIN_GATE_UP ? 4 : 8;
+    const int halves = mode == FC_LIN_VOCAB || N % per_half == 0 ? (N + per_half - 1) / per_half : 0;
+    const int items = N >= per_half ? (halves + 1) / 2 : 0;
+    if (off || dtype != FC_BF16 || M < 1 || M > 32 || !rows_kernel_covers(K) || items < 1)
+        return plan_slices(dtype, mode, M, K, N, target);
+    FcSkinnyPlan p;
+    memset(&p, 0, sizeof p);
+    // Fewer items than compute units are no reason for the slice-wise kernel (hidden 3584, 224 / 64 items: 10.0 / 9.3 us
+    // against 12.6 / 11.4, its second launch included), but what these shapes ask of a caller's workspace stays what it
+    // has been with it.
+    if (items < 256 && K >= 2048) p.reserve = fc_skinny_workspace(plan_slices(dtype, mode, M, K, N, target));
+    p.kind = 2;
+    p.mt = M <= 16 ? 1 : 2;
+    p.chunks = 1;
+    p.T = halves;
+    p.G = items < target ? items : target;  // at least one item each
+    return p;
+}
+
 size_t fc_skinny_workspace(const FcSkinnyPlan &p)
 {
-    if (p.kind != 1) return 0;  // the whole-row kernel keeps its partial sums inside the workgroup
+    if (p.kind != 1) return p.reserve;  // the whole-row kernel keeps its partial sums inside the workgroup
     return (size_t)p.chunks * p.slabs * p.maxseg * 8 * p.mt * 256 * sizeof(float);
 }
 
