@@ -181,17 +181,19 @@ double attn_cost(const AttnShape &sh, int64_t pairs, int row_tiles, int kv_len, 
     return t > 7.4 ? t : 7.4;
 }
 
-// The same for the tile kernel (one workgroup per sequence, kv head and 16 query rows, all keys, no merge kernel), which
-// has one round of at most 256 workgroups; with up to 64 / 128 of them the head dimension of V is cut in four / two.
-// Fitted to 130 shapes, 60 .. 1160 keys (rms error 3 .. 5 %), and used in that range.  Up to some 600 keys (64 workgroups) or 300 (256) it beats
-// every plan of the kernel above, whose stages, split partials and merge are made for long keys: 32 rows x 28 query heads,
-// 96 / 250 / 480 keys 8.8 / 9.5 / 10.3 us, tile kernel 4.6 / 5.8 / 8.0.
-double attn_tile_cost(int64_t wgs, int kv_len)
+// The same for the tile kernel: `wgs` workgroups (at most 256: one round), one per sequence, kv head, 16 query rows and key
+// range, each over `groups` groups of 32 keys of `group_bytes` bytes.  What counts is what one compute unit can pull from
+// HBM, some 35 B/ns; with up to 64 / 128 workgroups the head dimension of V is cut in four / two (the launch does that).
+// Fitted to 130 bf16 shapes of head_dim 128, 60 .. 1160 keys, one range (rms error 3 .. 5 %), and used for them in that
+// range; fp32 and head_dim 64 follow it by their bytes.  Up to some 600 keys (64 workgroups) or 300 (256) it
+// beats every plan of the kernel above, whose stages, split partials and merge are made for long keys: 32 rows x
+// 28 query heads, 96 / 250 / 480 keys 8.8 / 9.5 / 10.3 us, tile kernel 4.6 / 5.8 / 8.0.
+double attn_tile_cost(int64_t wgs, int64_t groups, int64_t group_bytes)
 {
-    const double groups = (double)((kv_len + 31) / 32);
-    if (wgs <= 64) return 3.58 + 0.275 * groups;
-    if (wgs <= 128) return 3.92 + 0.341 * groups;
-    return 4.28 + 0.229 * groups + 0.37e-4 * (double)wgs * kv_len;
+    const double g = (double)groups * (double)group_bytes / 16384.0;
+    if (wgs <= 64) return 3.58 + 0.275 * g;
+    if (wgs <= 128) return 3.92 + 0.341 * g;
+    return 4.28 + (0.229 + 1.18e-3 * (double)wgs) * g;
 }
 
 // Most key ranges any plan for this many row tiles may use, whatever the length up to by_len (the workspace is sized by
@@ -248,9 +250,8 @@ FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len, size_t cap
     if (cfg.dtype != FC_BF16 || cfg.head_dim != 128) {
         // kind 0: one workgroup per (sequence, kv head, one or two 16-row tiles); two tiles share the key
         // and value loads and are taken once they still fill half the chip (head_dim 64 only: with fp32 rows
-        // of 128 the operands of two tiles do not fit in registers).  A workgroup pulls keys and
-        // values at some 50..80 KB per us, so with fewer workgroups than compute units the keys are also
-        // cut into ranges of at least 128 KB; the second launch that merges them costs about 3 us.
+        // of 128 the operands of two tiles do not fit in registers).  The keys are cut into ranges where the
+        // estimate says that their shorter chains pay for the second launch that merges them (3 to 5 us).
         const int64_t rows = (int64_t)g * A, pairs = (int64_t)cfg.batch * cfg.n_kv_heads;
         p.row_tiles = (int)((rows + 15) / 16);
         p.waves = 8;
@@ -258,13 +259,16 @@ FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len, size_t cap
         const int64_t base = pairs * ((p.row_tiles + p.tiles_per_wg - 1) / p.tiles_per_wg);
         const int64_t groups = ((int64_t)kv_len + 31) / 32;
         const int64_t group_bytes = 64 * (int64_t)cfg.head_dim * (int64_t)esize_of(cfg.dtype);
-        int64_t splits = groups * group_bytes / (128 * 1024);
-        if (splits > 256 / base) splits = 256 / base;
-        if (splits < 1) splits = 1;
-        p.splits_bound = (int)splits;
-        const int64_t per = (groups + splits - 1) / splits;
-        p.keys_per_split = (int)(32 * per);
-        p.splits = (int)((groups + per - 1) / per);
+        double best = 1e30;
+        for (int64_t n = 1; n == 1 || (n <= groups && n * base <= 256); ++n) {
+            const int64_t per = (groups + n - 1) / n, splits = (groups + per - 1) / per;
+            const double t = attn_tile_cost(base * splits, per, group_bytes) + (splits > 1 ? 2.6 + 0.45 * splits : 0.0);
+            if (t < best) {
+                best = t;
+                p.splits = p.splits_bound = (int)splits;
+                p.keys_per_split = (int)(32 * per);
+            }
+        }
         return p;
     }
     p.kind = 1;
@@ -296,7 +300,7 @@ FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len, size_t cap
         }
     }
     const int row_tiles = (g * A + 15) / 16;
-    if (kv_len <= 1200 && pairs * row_tiles <= 256 && attn_tile_cost(pairs * row_tiles, kv_len) < best) {
+    if (kv_len <= 1200 && pairs * row_tiles <= 256 && attn_tile_cost(pairs * row_tiles, ((int64_t)kv_len + 31) / 32, 16384) < best) {
         p.kind = 0;
         p.row_tiles = row_tiles;
         p.tiles_per_wg = 1;
