@@ -546,9 +546,12 @@ fc_status fc_qkv_project_scatter(fc_cache *cache, int32_t layer, const void *x, 
                     A, cache->cfg.max_seq);
     const FcGeom G = geom_of(cache);
     void *kl = layer_ptr(cache, cache->k, layer), *vl = layer_ptr(cache, cache->v, layer);
-    // wide windows: tiled GEMM; short windows: weight-streaming kernels; other shapes and fp32: tile kernel
+    // wide windows: tiled GEMM; short windows: weight-streaming kernels; small problems, other shapes and fp32: tile kernel
     hipError_t e;
-    if (fc_project_prefers_gemm(cache->cfg, cache->cfg.batch * A, cache->scratch != nullptr))
+    if (fc_project_prefers_tile(cache->cfg, cache->cfg.batch * A))
+        e = fc_launch_project_tile(G, cache->inv_freq, cache->cfg.dtype, x, w_qkv, b_qkv, pos, win_start, A, q_out, kl, vl,
+                                   (hipStream_t)stream);
+    else if (fc_project_prefers_gemm(cache->cfg, cache->cfg.batch * A, cache->scratch != nullptr))
         e = fc_launch_project_gemm(G, x, w_qkv, b_qkv, pos, win_start, A, q_out, kl, vl, (hipStream_t)stream);
     else if (fc_project_mfma_supported(cache->cfg, A))
         e = fc_launch_project_mfma(G, cache->inv_freq, x, w_qkv, b_qkv, pos, win_start, A, q_out, kl, vl,
@@ -764,6 +767,22 @@ size_t fc_linear_workspace_bytes(int32_t dtype, int32_t M, int32_t K, int32_t N)
     return a > b ? a : b;
 }
 
+// Small bf16 problems run in the tile kernel: it is one launch, and short as long as the products are few, where the
+// tiled GEMM walks the hidden dimension stage by stage in a few workgroups and cuts it only with a second launch, and
+// the slice-wise kernel always has one.  Estimates (us) from 8 .. 300 rows, hidden 256 .. 2048, 256 .. 2048
+// outputs: 74 rows, hidden 1024, 512 outputs 7.6 against 4.4; 8 rows, 2048 x 1024 9.0 against 5.0; 160 rows, 2048 x 1024
+// 9.5 against 13.3.
+static double tile_us(double mm) { return fmax(4.4, 3.2 + 0.027 * mm); }  // mm: million products
+static bool linear_prefers_tile(int dtype, int mode, int M, int K, int N, const FcWidePlan &wide, const FcSkinnyPlan &skinny)
+{
+    if (dtype != FC_BF16 || fc_knobs().lin_wide_shape >= 0 || fc_knobs().lin_ksplit > 0 || fc_knobs().lin_wgs > 0 ||
+        fc_knobs().lin_no_rows)  // tuning knobs name the kernels
+        return false;
+    const double mm = (mode == FC_LIN_GATE_UP ? 2e-6 : 1e-6) * M * (double)K * N;
+    if (wide.kind == 1) return tile_us(mm) < 0.97 * (3.5 + 0.0034 * (K < 1024 ? K : 1024));
+    return skinny.kind == 1 && tile_us(mm) < 0.9 * (8.5 + mm / M / 2.5);
+}
+
 static fc_status linear_common(int32_t dtype, int mode, const void *x, const void *w, const void *w2,
                                const void *res, int32_t M, int32_t K, int32_t N, void *out, void *workspace,
                                size_t workspace_bytes, void *stream)
@@ -783,9 +802,10 @@ static fc_status linear_common(int32_t dtype, int mode, const void *x, const voi
         return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need,
                     workspace ? workspace_bytes : (size_t)0);
     hipError_t e;
-    if (wide.kind == 1)
+    const bool tile = linear_prefers_tile(dtype, mode, M, K, N, wide, plan);
+    if (wide.kind == 1 && !tile)
         e = fc_launch_linear_wide(wide, mode, x, w, w2, res, M, K, N, out, workspace, (hipStream_t)stream);
-    else if (plan.kind >= 1)
+    else if (plan.kind >= 1 && !tile)
         e = fc_launch_linear_skinny(plan, mode, x, w, w2, res, M, K, N, out, workspace, (hipStream_t)stream);
     else
         e = fc_launch_linear_tile(dtype, mode, x, w, mode == FC_LIN_GATE_UP ? w2 : res, M, K, N, out,

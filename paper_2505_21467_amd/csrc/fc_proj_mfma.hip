@@ -593,6 +593,18 @@ bool fc_project_prefers_gemm(const fc_config &cfg, int M, bool scratch)
     return us > fc_project_gemm_us(slots, M, cfg.hidden);
 }
 
+// Small problems: the tile kernel, by estimate (us; 8 .. 300 rows, hidden 256 .. 1024, 6 .. 12 head slots).  Hidden 512, 12
+// slots, 40 / 74 / 300 rows: tiled GEMM 6.2 / 6.3 / 6.5, tile kernel 4.5 / 5.1 / 9.4; hidden 1024, 20 rows: head-split 8.0,
+// tile kernel 4.5; hidden 256, 8 rows: 3.8 and 3.9.
+bool fc_project_prefers_tile(const fc_config &cfg, int M)
+{
+    if (cfg.dtype != FC_BF16 || cfg.head_dim != 128 || fc_knobs().proj_gemm_shape >= 0 || rows_covers(M, cfg.hidden)) return false;
+    const double mm = 128e-6 * M * (double)cfg.hidden * (cfg.n_q_heads + 2 * cfg.n_kv_heads);  // million products
+    const bool skinny = M <= 32 && cfg.hidden % HS_K != 0;
+    const double other = skinny ? 3.55 + 0.002 * cfg.hidden : 3.9 + 0.0043 * (cfg.hidden < 1024 ? cfg.hidden : 1024);
+    return fmax(4.0, 3.2 + 0.032 * mm) < 0.97 * other;
+}
+
 hipError_t fc_launch_project_mfma(const FcGeom &G, const double *inv_freq, const void *x, const void *w, const void *bias,
                                   const int32_t *pos, int win_start, int A, void *q_out, void *k_layer,
                                   void *v_layer, void *scratch, hipStream_t s)
