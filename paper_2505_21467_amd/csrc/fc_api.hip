@@ -749,7 +749,7 @@ static fc_status check_linear_shape(int32_t M, int32_t K, int32_t N)
     return FC_OK;
 }
 
-// Workspace of one linear call: tiled GEMM for more than 32 rows, streaming kernels otherwise.
+// Workspace of one linear call: tiled GEMM where it is planned, streaming kernels otherwise.
 static size_t linear_need(int dtype, int mode, int M, int K, int N)
 {
     const FcWidePlan wide = fc_plan_wide(dtype, mode, M, K, N);
@@ -940,7 +940,7 @@ struct LmHeadWs {
 LmHeadWs lm_head_ws(int dtype, int M, int K, int V)
 {
     LmHeadWs w;
-    w.wide = fc_plan_wide(dtype, FC_LIN_VOCAB, M, K, V);  // more than 32 rows: tiled GEMM
+    w.wide = fc_plan_wide(dtype, FC_LIN_VOCAB, M, K, V);  // tiled GEMM
     w.plan = fc_plan_skinny(dtype, FC_LIN_VOCAB, M, K, V);
     if (w.wide.kind == 1) w.plan.kind = 0;
     w.parts = w.wide.kind == 1 ? V / 128

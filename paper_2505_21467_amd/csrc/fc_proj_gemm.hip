@@ -858,36 +858,66 @@ hipError_t launch_shape(int shape, const GemmArgs &a, hipStream_t s)
     case 5:
         if constexpr (EPI == 0 || EPI == 2) return launch_gemm<64, 4, 3, 1, 1, 4, 4, EPI>(a, s);
         return hipErrorInvalidValue;
+    case 6:
+        if constexpr (EPI == 0 || EPI == 2) return launch_gemm<64, 2, 5, 1, 1, 4, 4, EPI>(a, s);
+        return hipErrorInvalidValue;
+    case 7:
+        if constexpr (EPI == 0 || EPI == 2) return launch_gemm<64, 2, 3, 1, 1, 4, 4, EPI>(a, s);
+        return hipErrorInvalidValue;
+    case 8:
+        if constexpr (EPI == 0 || EPI == 2) return launch_gemm<64, 4, 5, 1, 1, 4, 4, EPI>(a, s);
+        return hipErrorInvalidValue;
+    case 9: return launch_gemm<64, 2, 4, 1, 1, 3, 2, EPI>(a, s);
+    case 10:
+        if constexpr (EPI == 4) return hipErrorInvalidValue;
+        else return launch_gemm<64, 2, 2, 1, 1, 4, 4, EPI>(a, s);
     default: return hipErrorInvalidValue;
     }
 }
 
 // Tile shapes of the tiled GEMM and what a full round of 256 workgroups takes per 64 hidden elements (us, measured at
-// hidden 3584 with 256..768 workgroups).  Per tile area the larger ones are cheaper -- they move fewer
+// hidden 3584 and 4096 with 150..768 workgroups).  Per tile area the larger ones are cheaper -- they move fewer
 // bytes into the compute unit per product -- but leave the chip emptier at the end.
 //   0: 256 rows x slab   1: 128 rows x slab   2: 128 rows x half slab   3: 256 rows x two slabs
 //   4: 256 rows x 80 dealt pairs   5: 128 rows x 48 dealt pairs
-constexpr double ROUND_US[6] = {1.03, 0.62, 0.39, 1.84, 1.30, 0.54};
+//   6: 64 rows x 80 dealt pairs   7: 64 rows x 48 dealt pairs   8: 128 rows x 80 dealt pairs
+//   9: 64 rows x slab   10: 64 rows x half slab
+// 6 .. 10 are for few rows, where the weights alone should count: in the 128-row half slab, for 40 or 64 rows the shape with
+// the most tiles, the compute units pulled three bytes for every byte of weights (two thirds of them window rows, most
+// of those padding); 64 rows x 160 weight rows pull 1.4.  Gated W_1 of 18944 outputs at hidden 3584, 64 / 128 rows:
+// 67.5 / 81.6 us, now 50.4 / 58.3 (the weights alone 46 at 5.9 TB/s).
+constexpr int N_SHAPES = 11;
+constexpr double ROUND_US[N_SHAPES] = {1.03, 0.62, 0.39, 1.84, 1.30, 0.54, 0.75, 0.53, 0.95, 0.52, 0.34};
+constexpr bool shape_dealt(int shape) { return shape >= 4 && shape <= 8; }
+constexpr bool shape_half(int shape) { return shape == 2 || shape == 10; }
 
 int64_t tiles_of(int shape, int64_t slots, int64_t rows)
 {
-    const int64_t t256 = (rows + 255) / 256, t128 = (rows + 127) / 128;
+    const int64_t t256 = (rows + 255) / 256, t128 = (rows + 127) / 128, t64 = (rows + 63) / 64;
     switch (shape) {
     case 0: return slots * t256;
     case 1: return slots * t128;
     case 2: return 2 * slots * t128;
     case 3: return (slots + 1) / 2 * t256;
     case 4: return (slots * 64 + 79) / 80 * t256;
-    default: return (slots * 64 + 47) / 48 * t128;
+    case 5: return (slots * 64 + 47) / 48 * t128;
+    case 6: return (slots * 64 + 79) / 80 * t64;
+    case 7: return (slots * 64 + 47) / 48 * t64;
+    case 8: return (slots * 64 + 79) / 80 * t128;
+    case 9: return slots * t64;
+    default: return 2 * slots * t64;
     }
 }
 
 // Estimated time of one launch per 64 hidden elements.  A round that fills half the chip was measured at 0.78 to
-// 0.9 of a full one (the clock is higher and the memory path less loaded), hence the line 0.6 + 0.4 x.
+// 0.9 of a full one (the clock is higher and the memory path less loaded), hence the line 0.6 + 0.4 x.  The weights
+// come from HBM at 5.8 TB/s at best.
 double launch_cost(int shape, int64_t slots, int64_t rows)
 {
     const int64_t n = tiles_of(shape, slots, rows), part = n % 256;
-    return ROUND_US[shape] * ((double)(n / 256) + (part ? 0.6 + 0.4 * part / 256.0 : 0.0));
+    const double tiles = ROUND_US[shape] * ((double)(n / 256) + (part ? 0.6 + 0.4 * part / 256.0 : 0.0));
+    const double weights = (double)slots * 128 * 128 / 5.8e6;
+    return (tiles > weights ? tiles : weights) + 0.02 * tiles;  // (equally bound by the weights: the smaller tiles)
 }
 
 // A problem is covered by one launch, or cut in two where the last round of workgroups would be nearly empty:
@@ -901,17 +931,10 @@ struct GemmPiece {
 int plan_pieces(int slots, int M, int K, bool allow_half, bool allow_dealt, GemmPiece out[2])
 {
     const bool no_split = fc_knobs().gemm_no_split != 0;  // tuning knob
-    // Up to 128 rows the 256-row tiles are mostly padding and the weights, not the tiles, bound the time; with that
-    // many slabs the half slab is the fastest (gated W_1 of the 7B widths, 296 slabs, 48 / 64 / 128 rows: 67.6
-    // / 71.7 / 83.8 us against 72.9 / 74.4 / 85.1 with whole slabs and 81.8 / 80.7 / 88.7 with the 256-row tile).
-    if (M <= 128 && slots >= 192) {
-        out[0] = GemmPiece{allow_half ? 2 : 1, 0, slots, 0, M};
-        return 1;
-    }
     double best = 1e30;
     int n = 1;
-    for (int sh = 0; sh < 6; ++sh) {
-        if ((sh == 2 && !allow_half) || (sh >= 4 && !allow_dealt)) continue;
+    for (int sh = 0; sh < N_SHAPES; ++sh) {
+        if ((shape_half(sh) && !allow_half) || (shape_dealt(sh) && !allow_dealt)) continue;
         const double c = launch_cost(sh, slots, M);
         if (c < best) {
             best = c;
@@ -969,7 +992,7 @@ hipError_t launch_pieces(GemmArgs a, hipStream_t s)
 
 }  // namespace
 
-// Tiled-GEMM plan of a plain linear layer on more than 32 rows (host, pure function of the shape).
+// Tiled-GEMM plan of a plain linear layer (host, pure function of the shape); kind 0: not for this kernel.
 FcWidePlan fc_plan_wide(int dtype, int mode, int M, int K, int N)
 {
     FcWidePlan p;
@@ -977,9 +1000,23 @@ FcWidePlan fc_plan_wide(int dtype, int mode, int M, int K, int N)
     p.shape = 0;
     p.ksplit = 1;
     const int per_slab = mode == FC_LIN_GATE_UP ? 64 : 128;  // FC_LIN_VOCAB: slabs of 128 vocabulary rows
-    if (dtype != FC_BF16 || M <= 32 || K < 4 * KS_MIN || K % KS_MIN != 0 || N < per_slab || N % per_slab != 0) return p;
+    if (dtype != FC_BF16 || M < 1 || K < 4 * KS_MIN || K % KS_MIN != 0 || N < per_slab || N % per_slab != 0) return p;
     // 32-bit byte offsets inside X and each weight matrix
     if ((int64_t)N * K * 2 >= ((int64_t)1 << 32) || (int64_t)M * K * 2 >= ((int64_t)1 << 32)) return p;
+    // At most 32 rows: only where the estimate beats the whole-row kernel's (weights at 5.94 TB/s, 6 us of launch, X and
+    // last items and 1.2 more for the second 16 rows): a gated W_1 of 18944 outputs at hidden 3584, 32 rows 52.0 and
+    // 48.2 us, a vocabulary of 32000 51.1 and 45.3, of 152064 189.1 and 191.9.
+    if (M <= 32) {
+        const FcSkinnyPlan rows = fc_plan_skinny(dtype, mode, M, K, N);
+        const bool knob = fc_knobs().lin_wide_shape >= 6;
+        if (!knob && (mode == FC_LIN_RESIDUAL || rows.kind != 2 || K < 2048 || fc_knobs().lin_wgs > 0)) return p;
+        GemmPiece pc[2];
+        const int n = plan_pieces(N / per_slab, M, K, mode != FC_LIN_VOCAB, mode == FC_LIN_GATE_UP, pc);
+        double us = n == 2 ? 7.0 : 4.0;
+        for (int i = 0; i < n; ++i) us += launch_cost(pc[i].shape, pc[i].slots, pc[i].m_end - pc[i].m_base) * (K / 64);
+        const double bytes = (mode == FC_LIN_GATE_UP ? 4.0 : 2.0) * K * (double)N;
+        if (!knob && us > bytes / 5.94e6 + (M > 16 ? 7.2 : 6.0)) return p;
+    }
     p.kind = 1;
     const int64_t units = N / per_slab, t256 = (M + 255) / 256, t128 = (M + 127) / 128;
     // (The shape counts only where the hidden dimension is cut into parts or a tuning knob asks for one shape;
@@ -997,9 +1034,10 @@ FcWidePlan fc_plan_wide(int dtype, int mode, int M, int K, int N)
     if (mode == FC_LIN_RESIDUAL && p.shape == 2 && wgs < 192) {
         const int64_t stages = K / KS_MIN;
         double best = 1e30;
-        for (int sh = 0; sh < 3; ++sh) {
-            const int64_t rows = sh == 0 ? 256 : 128, wrows = sh == 2 ? 64 : 128;
-            const int64_t tiles = units * (sh == 2 ? 2 : 1) * ((M + rows - 1) / rows);
+        for (const int sh : {0, 1, 2, 9, 10}) {
+            const int64_t rows = sh == 0 ? 256 : sh < 3 ? 128 : 64, wrows = shape_half(sh) ? 64 : 128;
+            if (rows == 64 && M > 64) continue;  // (256 rows in four such tiles, uncut: 25.0 us for W_out, 19.8 as chosen here)
+            const int64_t tiles = tiles_of(sh, units, M);
             for (int64_t ks = 1; ks <= 16; ++ks) {
                 if (ks > 1 && ks > stages / 8) break;
                 const int64_t wg = tiles * ks;
@@ -1016,7 +1054,7 @@ FcWidePlan fc_plan_wide(int dtype, int mode, int M, int K, int N)
     }
     {  // tuning knobs
         const int v = fc_knobs().lin_wide_shape;
-        if ((v >= 0 && v <= (mode == FC_LIN_VOCAB ? 1 : 2)) || v == 3 || (v == 4 && mode == FC_LIN_GATE_UP)) p.shape = v;
+        if (v >= 0 && v < N_SHAPES && (!shape_half(v) || mode != FC_LIN_VOCAB) && (!shape_dealt(v) || mode == FC_LIN_GATE_UP)) p.shape = v;
         const int ks = fc_knobs().lin_ksplit;
         if (ks >= 1 && ks <= 16 && ks <= K / KS_MIN / 4 && mode == FC_LIN_RESIDUAL) p.ksplit = ks;
     }

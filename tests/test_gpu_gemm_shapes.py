@@ -1,6 +1,7 @@
 """GPU parity of the tiled GEMM's 256 x 256 tile (two slabs, two wave groups an interval apart) and of problems
 cut into two launches, at the edges: an odd number of slabs, ragged rows, one and few stages, parts of the
 hidden dimension."""
+import numpy as np
 import pytest
 import torch
 
@@ -8,6 +9,7 @@ from oracle import fc_oracle as orc
 from paper_2505_21467_amd import binding as fc
 from paper_2505_21467_amd import inputs
 from tests.harness import assert_close
+from tests.test_gpu_parity import _compare_cache, _pair
 from tests.test_gpu_unmask import _check_lm_head
 
 pytestmark = pytest.mark.gpu
@@ -46,7 +48,46 @@ def test_two_slab_tile_vocabulary(knob):
     _check_lm_head("bf16", x, w, "vocabulary, shape 3")
 
 
+@pytest.mark.parametrize("shape", [6, 7, 8, 9, 10])
+@pytest.mark.parametrize("M,K,N", [(5, 256, 256), (64, 320, 384), (65, 256, 1152), (130, 448, 640)])
+def test_few_row_tiles(shape, M, K, N, knob):
+    """64 or 128 rows per tile: ragged rows, one tile and several, dealt pairs that end inside a tile."""
+    knob("FC_LIN_WIDE_SHAPE", str(shape))
+    _linear(M, K, N, True, "gated, shape %d" % shape)
+    if shape >= 9 and M > 32:
+        _linear(M, K, N, False, "linear, shape %d" % shape)
+        knob("FC_LIN_KSPLIT", "2")
+        if K >= 512 or shape == 9:
+            _linear(M, 512, N, False, "linear in parts, shape %d" % shape)
+    if shape == 9:
+        x, w = inputs.normal(22, "x", (M, K), 1.0, "bf16"), inputs.normal(22, "w", (N, K), 0.03, "bf16")
+        _check_lm_head("bf16", x, w, "vocabulary, shape 9")
+
+
+@pytest.mark.parametrize("shape", [6, 7, 8, 9, 10])
+@pytest.mark.parametrize("B,d,Hq,Hkv,A", [(3, 192, 8, 2, 23), (1, 64, 3, 1, 65), (2, 320, 4, 4, 160)])
+def test_few_row_tiles_projection(shape, B, d, Hq, Hkv, A, knob):
+    print("[case] projection, shape", shape, B, d, Hq, Hkv, A, flush=True)
+    knob("FC_PROJ_GEMM_SHAPE", str(shape))
+    dtype, L = "bf16", 40
+    w, S = inputs.Workload("t", dtype, B, d, Hq, Hkv, 128, L, A), L + A
+    g, o = _pair(dtype, B, d, Hq, Hkv, 128, S + 5, max_rows=A, fill=-0.75)
+    K, V = inputs.kv_fill(w, 11, L)
+    g.write_rows(0, K, V, 0)
+    o.write_rows(K, V, 0)
+    W, b, X = inputs.weights(w, 11), inputs.bias(w, 11), inputs.hidden_states(w, 11, A)
+    Qg, Og = g.step(0, X, W, b, L, S)
+    Qo, Oo = o.step(X, W, b, L, S)
+    assert_close(Qg, Qo, dtype, "Q")
+    assert_close(Og, Oo, dtype, "O")
+    written = np.zeros((B, S + 5), bool)
+    written[:, L:S] = True
+    _compare_cache(g, o, dtype, written=written, what="projection")
+    g.close()
+
+
 @pytest.mark.parametrize("M,N,gated", [
+    (20, 296 * 64, True),      # few rows of a wide layer, where the tiled GEMM takes over from the whole-row kernel
     (1200, 53 * 128, False),   # the last two slabs in a second launch
     (1800, 36 * 128, False),   # the last eight rows in a second launch
     (512, 296 * 64, True),     # 256 gated slabs in the 256 x 256 tile, 40 in a smaller one
