@@ -1009,13 +1009,21 @@ FcWidePlan fc_plan_wide(int dtype, int mode, int M, int K, int N)
     if (M <= 32) {
         const FcSkinnyPlan rows = fc_plan_skinny(dtype, mode, M, K, N);
         const bool knob = fc_knobs().lin_wide_shape >= 6;
-        if (!knob && (mode == FC_LIN_RESIDUAL || rows.kind != 2 || K < 2048 || fc_knobs().lin_wgs > 0)) return p;
-        GemmPiece pc[2];
-        const int n = plan_pieces(N / per_slab, M, K, mode != FC_LIN_VOCAB, mode == FC_LIN_GATE_UP, pc);
-        double us = n == 2 ? 7.0 : 4.0;
-        for (int i = 0; i < n; ++i) us += launch_cost(pc[i].shape, pc[i].slots, pc[i].m_end - pc[i].m_base) * (K / 64);
-        const double bytes = (mode == FC_LIN_GATE_UP ? 4.0 : 2.0) * K * (double)N;
-        if (!knob && us > bytes / 5.94e6 + (M > 16 ? 7.2 : 6.0)) return p;
+        if (!knob && (fc_knobs().lin_wgs > 0 || fc_knobs().lin_no_rows)) return p;  // tuning knobs of the streaming kernels
+        if (mode == FC_LIN_RESIDUAL) {
+            // In parts against the slice-wise kernel, which has a second launch too and pulls a window slice per 128 rows: a
+            // large matrix, more than 16 rows (32 x 18944 x 3584 32.5 and 30.2 us, 16 rows 29.9 and 29.7; half the
+            // matrix: equal).
+            if (!knob && !(rows.kind == 1 && M > 16 && (double)K * N >= 60e6)) return p;
+        } else {
+            if (!knob && (rows.kind != 2 || K < 2048)) return p;
+            GemmPiece pc[2];
+            const int n = plan_pieces(N / per_slab, M, K, mode != FC_LIN_VOCAB, mode == FC_LIN_GATE_UP, pc);
+            double us = n == 2 ? 7.0 : 4.0;
+            for (int i = 0; i < n; ++i) us += launch_cost(pc[i].shape, pc[i].slots, pc[i].m_end - pc[i].m_base) * (K / 64);
+            const double bytes = (mode == FC_LIN_GATE_UP ? 4.0 : 2.0) * K * (double)N;
+            if (!knob && us > bytes / 5.94e6 + (M > 16 ? 7.2 : 6.0)) return p;
+        }
     }
     p.kind = 1;
     const int64_t units = N / per_slab, t256 = (M + 255) / 256, t128 = (M + 127) / 128;
