@@ -680,6 +680,9 @@ fc_status fc_active_attention_static(fc_cache *cache, int32_t layer, const void 
     }
     const FcAttnPlan plan = plan_with_workspace(cache->cfg, cache->last_static, A, kv_len, FC_STATIC_SCRATCH_BYTES, FC_STATIC_SCRATCH_BYTES);
     const size_t need = fc_plan_workspace(cache->cfg, plan, A);
+    if (need > FC_STATIC_SCRATCH_BYTES)  // a plan that a tuning knob forces is not bounded by the array
+        return fail(FC_ERR_WORKSPACE, "this shape needs %zu bytes of partial results, the static scratch holds %u", need,
+                    FC_STATIC_SCRATCH_BYTES);
     void *scratch = nullptr;
     if (need > 0) {
         st = static_scratch_ptr(&scratch);

@@ -182,6 +182,19 @@ def test_static_scratch_attention_validates_on_the_host():
         fc.fc_cache_free(h)
 
 
+def test_static_scratch_refuses_a_forced_plan_beyond_its_array(knob):
+    """A tuning knob forces the plan whatever the space, so its partial results are held against the static array, too."""
+    c, A, kv = fc.make_config(1, 1, 3584, 28, 4, 128, 16800, "bf16"), 32, 16800
+    knob("FC_ATTN_WGS", 2000)
+    p = fc.fc_attention_plan(c, A, kv)
+    assert 4 * p["row_tiles"] * p["splits"] * 32 * (256 + 16) > fc.fc_active_attention_static_max_bytes()
+    h = fc.fc_cache_alloc(c, FAKE, FAKE)
+    try:
+        _raises(fc.FC_ERR_WORKSPACE, fc.fc_active_attention_static, h, 0, FAKE, A, kv, None, FAKE, 0)
+    finally:
+        fc.fc_cache_free(h)
+
+
 @pytest.mark.parametrize("mode", [0, 1])
 def test_window_schedule_equals_oracle(mode):
     cases = [(16384, 416, 32, 8, 0), (2048, 256, 32, 8, 8), (0, 70, 32, 1, 3), (5, 64, 64, 4, 2), (9, 1, 1, 1, 1)]
