@@ -334,7 +334,9 @@ fc_status fc_gather_rows(int32_t dtype, const void *table, int32_t rows, int32_t
  * tokens[b][p] == mask_id):  t_j = argmax_v dlm[b][i_j][v] (smallest v on ties);  row j matches when
  * t_j is among the topk largest entries of ar[b][i_j][.] (ties: smaller id first) and, if tau > 0,
  * max_v dlm[b][i_j][v] > tau * max_v ar[b][i_j][v] (float product).  With k = the longest prefix of
- * matching rows, the first max(k, 1) masked rows get tokens[b][p] = t_j.
+ * matching rows, the first max(k, 1) masked rows get tokens[b][p] = t_j.  NaN entries are passed over: they are
+ * neither t_j nor among the topk, so a row whose ar[t_j] is NaN does not match (nor does a dlm row of nothing but
+ * NaN, whose t_j is INT32_MAX).
  *   dlm, ar  device float [B][A][V] logits;  pos  device int32 [B][A] or NULL = win_start + a;
  *   tokens  device int32 [B][L], updated in place;  n_accept  device int32 [B] (0 if nothing was masked);
  *   pos_next  device int32 [B][A], count_next  device int32 [B]: the rows that stay masked (as for

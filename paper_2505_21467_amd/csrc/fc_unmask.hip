@@ -144,8 +144,8 @@ __global__ __launch_bounds__(NW * 64) void k_unmask_select(const int32_t *__rest
 
 // -------------------------------------------------------------------------------------------------
 // Guided Diffusion acceptance (paper, section 3.2.2, Algorithm 1; Top-K match and threshold tau from the
-// implementation details).  A row matches if the DLM's token t is among the topk best AR entries, that is, if fewer than
-// topk AR entries come before (ar[t], t) in the order (larger value first, then smaller id).  No list of the
+// implementation details).  A row matches if the DLM's token t is among the topk best AR entries, that is, if ar[t] is a number and
+// fewer than topk AR entries come before (ar[t], t) in the order (larger value first, then smaller id).  No list of the
 // topk best is needed for that:
 //  - k_accept_scan cuts every still masked row's vocabulary into parts, 64 lanes each, and finds each part's best DLM and
 //    best AR entry: two running maxima per lane, so the scan is bound by reading the logits;
@@ -323,7 +323,9 @@ __device__ __forceinline__ void accept_rows(const AccArgs &p, int b, int a0, int
                     }
                 }
         }
-        if (count >= p.topk) match[n] = 0;
+        // A NaN comes before nothing and nothing before it: counting alone would let it match.  (Token V and beyond: a DLM
+        // row of NaNs, no arg-max.)  Not an early `continue` at the top: hipcc 7.2 then dropped the assignment here.
+        if (count >= p.topk || !(z[n] == z[n]) || tok[n] >= p.V) match[n] = 0;
     }
 }
 

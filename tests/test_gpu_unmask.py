@@ -247,6 +247,55 @@ def test_guided_accept_on_probabilities_is_bit_exact():
         assert np.array_equal(pn, want[1]) and np.array_equal(cn, want[2])
 
 
+@pytest.mark.parametrize("A,V", [(7, 33), (32, 1000), (40, 6002), (70, 500)])
+def test_guided_accept_passes_over_nan(A, V):
+    """NaN and infinite logits, one kind per row.  The oracle gets every NaN as -inf, below all that counts in these
+    rows; where the guide has nothing to say about the proposed token, it gets a guide that ranks the token last."""
+    print("[case] guided acceptance with NaN", A, V, flush=True)
+    rng = np.random.default_rng(A + V)
+    MASK, L = 200000, A + 3
+    pos = np.arange(A, dtype=np.int32)[None].repeat(2, 0)
+    for topk, tau in ((1, 0.0), (3, 0.5), (3, 0.0)):
+        for broken in range(5):
+            dlm = np.abs(rng.normal(0, 3, (2, A, V))).astype(np.float32)
+            ar = dlm.copy()  # agrees everywhere
+            row = min(A - 1, 2 + broken)
+            t = int(np.argmax(dlm[1, row]))
+            want_dlm, want_ar = dlm.copy(), ar.copy()
+            if broken == 0:    # the guide has no number at all
+                ar[1, row] = np.nan
+                want_ar[1, row], want_ar[1, row, t] = 0.0, -np.inf
+            elif broken == 1:  # none for the proposed token
+                ar[1, row, t] = np.nan
+                want_ar[1, row, t] = -np.inf
+            elif broken == 2:  # NaN around the proposed token on both sides: passed over
+                at = rng.permutation(V)[: V // 2]
+                at = at[at != t]
+                ar[1, row, at] = dlm[1, row, at] = np.nan
+                want_ar[1, row, at] = want_dlm[1, row, at] = -np.inf
+            elif broken == 3:  # infinities are numbers
+                dlm[1, row, t] = want_dlm[1, row, t] = np.inf
+                ar[1, row, t] = want_ar[1, row, t] = -np.inf
+            else:              # the proposal's row has NaN in front, and the guide's best is infinite
+                dlm[1, row, 0] = np.nan
+                want_dlm[1, row, 0] = -np.inf
+                ar[1, row, V - 1] = want_ar[1, row, V - 1] = np.inf
+            tokens = np.full((2, L), MASK, np.int32)
+            want_t = tokens.copy()
+            want = orc.guided_accept(want_dlm, want_ar, pos, topk, tau, MASK, want_t)
+            got_t, n, pn, cn = _gpu_accept(dlm, ar, pos, 0, topk, tau, MASK, tokens)
+            assert np.array_equal(n, want[0]), (broken, topk, tau, n, want[0])
+            assert np.array_equal(got_t, want_t) and np.array_equal(pn, want[1]) and np.array_equal(cn, want[2])
+    # a proposal of nothing but NaN matches nothing, whatever the guide says
+    dlm = np.abs(rng.normal(0, 3, (2, A, V))).astype(np.float32)
+    ar = dlm.copy()
+    ar[0, 3, 0] = 100.0
+    dlm[0, 3] = np.nan
+    for topk in (1, 3):
+        _, n, _, cn = _gpu_accept(dlm, ar, pos, 0, topk, 0.0, MASK, np.full((2, L), MASK, np.int32))
+        assert list(n) == [3, A] and list(cn) == [A - 3, 0]
+
+
 def test_guided_accept_until_everything_is_unmasked():
     # Algorithm 1's loop: proposals and guide logits are redrawn each round; every round makes progress
     rng = np.random.default_rng(3)
