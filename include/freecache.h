@@ -42,7 +42,7 @@ typedef enum {
     FC_ERR_BOUNDS = 2,      /* layer, window or kv_len outside the cache */
     FC_ERR_UNSUPPORTED = 3, /* shape the kernels do not cover (see fc_config) */
     FC_ERR_OOM = 4,         /* the library could not allocate cache storage */
-    FC_ERR_WORKSPACE = 5,   /* workspace missing or smaller than fc_workspace_bytes() */
+    FC_ERR_WORKSPACE = 5,   /* workspace missing or smaller than the call requires */
     FC_ERR_HIP = 6          /* a HIP call or kernel launch failed */
 } fc_status;
 
@@ -155,12 +155,16 @@ fc_status fc_qkv_project_scatter(fc_cache *cache, int32_t layer, const void *x, 
                                  const void *b_qkv, int32_t win_start, int32_t A,
                                  const int32_t *pos, void *q_out, void *stream);
 
-/* Workspace bytes fc_active_attention / fc_refresh need for windows of up to max_rows rows
- * (split-KV partial results).  0 on bad arguments. */
+/* Workspace bytes of fc_active_attention / fc_refresh for windows of up to max_rows rows (split-KV
+ * partial results): enough for any of them, and all that the plan for the full max_seq rows can use.
+ * 0 on bad arguments.  What a single call requires may be less: bf16 with head_dim 128, the partial
+ * results of about one round of workgroups at its own row count and kv_len; else nothing.  With
+ * less than it can use a call cuts the keys into fewer ranges, so the roundings of its
+ * result may depend on workspace_bytes. */
 size_t fc_workspace_bytes(const fc_config *cfg, int32_t max_rows);
 
-/* The launch plan fc_active_attention would use for a window of A rows over kv_len cached rows
- * (host, pure function of the shape and the tuning knobs; for reports and for tying a measured HBM
+/* The launch plan fc_active_attention would use for a window of A rows over kv_len cached rows with
+ * fc_workspace_bytes(cfg, A) bytes of workspace (host, pure function of the shape and the tuning knobs; for reports and for tying a measured HBM
  * traffic figure to the plan it was measured with):
  *   plan[0] kind (0 fp32 / head_dim 64 kernel, 1 bf16 head_dim 128 kernel)   plan[1] key ranges (splits)
  *   plan[2] keys per split   plan[3] 32-row (kind 0: 16-row) tiles per (sequence, kv head)
@@ -174,8 +178,8 @@ fc_status fc_attention_plan(const fc_config *cfg, int32_t A, int32_t kv_len, int
  *   q      device [B][Hq][A][Dh] (as written by fc_qkv_project_scatter)
  *   pos    device int32 [B][A] or NULL; rows with a negative entry produce zeros
  *   out    device [B][A][Hq*Dh]
- *   workspace  device, >= fc_workspace_bytes(cfg, A) bytes, contents irrelevant; may be NULL only
- *          if that size is 0.  Two calls that overlap in time must not share a workspace.
+ *   workspace  device, fc_workspace_bytes(cfg, A) bytes (see there), contents irrelevant; may be NULL
+ *          if none is required.  Two calls that overlap in time must not share a workspace.
  * Errors: INVALID_ARG, BOUNDS (layer; kv_len < 1 or > max_seq), WORKSPACE, HIP. */
 fc_status fc_active_attention(fc_cache *cache, int32_t layer, const void *q, int32_t A,
                               int32_t kv_len, const int32_t *pos, void *out, void *workspace,
@@ -186,7 +190,7 @@ fc_status fc_active_attention(fc_cache *cache, int32_t layer, const void *q, int
  * and errors as fc_active_attention, except that the split-KV partial results go to a static device
  * array inside the library (16 MiB per GPU, held until the process ends; its address on the current
  * device is looked up on the first call there, with that device current).  The call allocates
- * nothing.  A shape whose partial results exceed fc_active_attention_static_max_bytes() (compare
+ * nothing.  A shape that requires more than fc_active_attention_static_max_bytes() (compare
  * fc_workspace_bytes) is rejected with FC_ERR_WORKSPACE.  All calls on one GPU share the one array:
  * calls that overlap in time on the same GPU (two streams, two threads) race; calls on one stream
  * are ordered and safe.  Nothing in the array has to be cleared between calls. */
@@ -260,7 +264,8 @@ typedef struct {
 } fc_layer_weights;
 
 /* Workspace bytes of fc_full_layer_step for windows of up to max_rows rows per sequence
- * (intermediate activations of B * max_rows rows, the attention workspace, partial sums). */
+ * (intermediate activations of B * max_rows rows, partial sums, the attention workspace; of the last a
+ * call requires no more than fc_active_attention does). */
 size_t fc_full_layer_workspace_bytes(const fc_config *cfg, int32_t d_ff, int32_t max_rows);
 
 /* One cached step of the whole layer on the window rows (section 3.2.1 applied to every module of

@@ -161,8 +161,8 @@ const AttnShape ATTN_SHAPES[] = {{8, 8, 1.174}, {4, 8, 0.826}, {2, 8, 0.706}, {4
 // the bandwidth of the stream (5.9 TB/s) and of its copies into the compute units (16 TB/s), joined by a
 // 5-norm, and the merge kernel.  The plans it picks are within 3 % of the best measured ones in the mean; choosing
 // tiles by the row count and splits by "nearest to 256 workgroups" was 14 % off, mostly through grids a little over
-// one round.
-double attn_cost(const AttnShape &sh, int64_t pairs, int row_tiles, int kv_len, int64_t splits, int64_t stages)
+// one round.  (Returns some value >= limit where the largest of the joined terms alone reaches it.)
+double attn_cost(const AttnShape &sh, int64_t pairs, int row_tiles, int kv_len, int64_t splits, int64_t stages, double limit)
 {
     const int64_t n = pairs * ((row_tiles + sh.R - 1) / sh.R) * splits, at_once = sh.W == 8 ? 256 : 512;
     const int64_t rounds = n / at_once, rest = n % at_once;
@@ -176,8 +176,10 @@ double attn_cost(const AttnShape &sh, int64_t pairs, int row_tiles, int kv_len, 
     }
     const double hbm = (double)pairs * kv_len * 512.0 / 5.916e6, fill = (double)n * stages * 32768.0 / 16.2e6;
     auto p5 = [](double v) { return v * v * v * v * v; };
-    double t = 3.6 + pow(p5(wg) + p5(hbm) + p5(fill), 0.2);
-    if (splits > 1) t += 0.044 * splits + (double)pairs * row_tiles * splits * 8704.0 / 1.52e6;
+    const double rest_us = 3.6 + (splits > 1 ? 0.044 * splits + (double)pairs * row_tiles * splits * 8704.0 / 1.52e6 : 0.0);
+    const double least = rest_us + fmax(wg, fmax(hbm, fill));
+    if (least >= limit) return least;
+    const double t = rest_us + pow(p5(wg) + p5(hbm) + p5(fill), 0.2);
     return t > 7.4 ? t : 7.4;
 }
 
@@ -196,9 +198,8 @@ double attn_tile_cost(int64_t wgs, int64_t groups, int64_t group_bytes)
     return 4.28 + (0.229 + 1.18e-3 * (double)wgs) * g;
 }
 
-// Most key ranges any plan for this many row tiles may use, whatever the length up to by_len (the workspace is sized by
-// it): one round of workgroups in some shape, or about 32 MB of partial results where a
-// round has few ranges.
+// Most key ranges the planner considers for this many row tiles: one round of workgroups in some shape, or about 32 MB
+// of partial results where a round has few ranges.
 int64_t attn_splits_bound(int64_t pairs, int row_tiles, int64_t by_len)
 {
     int64_t bound = 1;
@@ -220,24 +221,61 @@ void set_attn_plan(FcAttnPlan &p, int R, int W, int64_t splits, int64_t n_stages
     p.splits = (int)((n_stages + stages - 1) / stages);
 }
 
-// Given tiles and the split that comes nearest to a given number of workgroups (0 = by the row count; one round).
-FcAttnPlan plan_fixed_tiles(FcAttnPlan p, int R, int W, int64_t target, int64_t pairs, int64_t n_stages, int64_t by_len)
+// Key ranges with which `base` (sequence, kv head, tile group) triples come nearest to `target` workgroups.
+int64_t nearest_splits(int64_t target, int64_t base, int64_t by_len)
 {
-    if (W != 4) W = 8;
-    if (R != 2 && R != 4 && R != 8) R = p.row_tiles <= 2 ? 2 : (p.row_tiles <= 7 ? 4 : 8);
-    if (W == 4 && R == 8) R = 4;
-    if (target <= 0) target = W == 4 ? 512 : 256;
-    const int64_t base = pairs * ((p.row_tiles + R - 1) / R);
     int64_t splits = (target + base / 2) / base;
     if (splits > by_len) splits = by_len;
-    if (splits < 1) splits = 1;
-    set_attn_plan(p, R, W, splits, n_stages);
-    if (p.splits_bound < (int)splits) p.splits_bound = (int)splits;
-    return p;
+    return splits < 1 ? 1 : splits;
+}
+
+// At least 128 keys per range.
+int64_t splits_by_len(int kv_len)
+{
+    const int64_t n_stages = ((int64_t)kv_len + 63) / 64;
+    return n_stages / 2 > 1 ? n_stages / 2 : 1;
+}
+
+// Tiles and number of ranges the tuning knobs ask for (FC_ATTN_TILES, FC_ATTN_WGS).
+struct ForcedTiles {
+    int R, W;
+    int64_t splits;
+};
+bool attn_forced() { return fc_knobs().attn_r > 0 || fc_knobs().attn_wgs > 0; }
+ForcedTiles forced_tiles(int64_t pairs, int row_tiles, int64_t by_len)
+{
+    int R = fc_knobs().attn_r, W = fc_knobs().attn_w;
+    int64_t target = fc_knobs().attn_wgs;
+    if (W != 4) W = 8;
+    if (R != 2 && R != 4 && R != 8) R = row_tiles <= 2 ? 2 : (row_tiles <= 7 ? 4 : 8);
+    if (W == 4 && R == 8) R = 4;
+    if (target <= 0) target = W == 4 ? 512 : 256;
+    return ForcedTiles{R, W, nearest_splits(target, pairs * ((row_tiles + R - 1) / R), by_len)};
 }
 
 // Bytes of partial results per row tile and key range: 32 x 128 half floats and 32 x 4 floats of row state.
 constexpr size_t ATTN_PART_BYTES = 32 * (128 * 2 + 4 * sizeof(float));
+
+// Workspace a call must bring (bytes): the partial results of one round of workgroups with the tiles by the row count
+// (a cache too short for 256 eight-wave workgroups of four tiles: 512 four-wave workgroups of two), or those of the plan
+// that a tuning knob forces.  What the planner does with it is its own affair: it often takes fewer ranges, and more only
+// where the caller brings more (fc_workspace_bytes says how much is of use).
+size_t attn_required(const fc_config &cfg, int A, int kv_len)
+{
+    if (cfg.dtype != FC_BF16 || cfg.head_dim != 128) return 0;  // those cut the keys only where there is space for it
+    const int64_t pairs = (int64_t)cfg.batch * cfg.n_kv_heads, by_len = splits_by_len(kv_len);
+    const int row_tiles = (int)(((int64_t)(cfg.n_q_heads / cfg.n_kv_heads) * A + 31) / 32);
+    int64_t splits;
+    if (attn_forced()) {
+        splits = forced_tiles(pairs, row_tiles, by_len).splits;
+    } else {
+        const int R = row_tiles <= 2 ? 2 : (row_tiles <= 7 ? 4 : 8);
+        const int64_t base = pairs * ((row_tiles + R - 1) / R);
+        splits = nearest_splits(256, base, by_len);
+        if (R == 4 && base * splits < 256) splits = nearest_splits(512, pairs * ((row_tiles + 1) / 2), by_len);
+    }
+    return splits > 1 ? (size_t)pairs * row_tiles * splits * ATTN_PART_BYTES : 0;
+}
 
 }  // namespace
 
@@ -245,7 +283,7 @@ FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len, size_t cap
 {
     FcAttnPlan p;
     memset(&p, 0, sizeof p);
-    p.splits = p.splits_bound = 1;
+    p.splits = 1;
     const int g = cfg.n_q_heads / cfg.n_kv_heads;
     if (cfg.dtype != FC_BF16 || cfg.head_dim != 128) {
         // kind 0: one workgroup per (sequence, kv head, one or two 16-row tiles); two tiles share the key
@@ -260,28 +298,32 @@ FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len, size_t cap
         const int64_t groups = ((int64_t)kv_len + 31) / 32;
         const int64_t group_bytes = 64 * (int64_t)cfg.head_dim * (int64_t)esize_of(cfg.dtype);
         double best = 1e30;
+        FcAttnPlan chosen = p;
         for (int64_t n = 1; n == 1 || (n <= groups && n * base <= 256); ++n) {
             const int64_t per = (groups + n - 1) / n, splits = (groups + per - 1) / per;
             const double t = attn_tile_cost(base * splits, per, group_bytes) + (splits > 1 ? 2.6 + 0.45 * splits : 0.0);
-            if (t < best) {
+            FcAttnPlan cut = p;
+            cut.splits = (int)splits;
+            cut.keys_per_split = (int)(32 * per);
+            if (t < best && fc_plan_workspace(cfg, cut) <= cap) {
                 best = t;
-                p.splits = p.splits_bound = (int)splits;
-                p.keys_per_split = (int)(32 * per);
+                chosen = cut;
             }
         }
-        return p;
+        return chosen;
     }
     p.kind = 1;
     p.row_tiles = (int)(((int64_t)g * A + 31) / 32);
     const int64_t pairs = (int64_t)cfg.batch * cfg.n_kv_heads;
     const int64_t n_stages = ((int64_t)kv_len + 63) / 64;
-    const int64_t by_len = n_stages / 2 > 1 ? n_stages / 2 : 1;  // at least 128 keys per split
-    const FcKnobs &kn = fc_knobs();
-    int64_t bound = attn_splits_bound(pairs, p.row_tiles, by_len);
+    const int64_t by_len = splits_by_len(kv_len);
+    if (attn_forced()) {  // (whatever the space: the caller checks)
+        const ForcedTiles f = forced_tiles(pairs, p.row_tiles, by_len);
+        set_attn_plan(p, f.R, f.W, f.splits, n_stages);
+        return p;
+    }
+    const int64_t bound = attn_splits_bound(pairs, p.row_tiles, by_len);
     const int64_t within = (int64_t)(cap / ((size_t)pairs * p.row_tiles * ATTN_PART_BYTES));
-    if (bound > within) bound = within > 1 ? within : 1;
-    p.splits_bound = (int)bound;
-    if (kn.attn_r > 0 || kn.attn_wgs > 0) return plan_fixed_tiles(p, kn.attn_r, kn.attn_w, kn.attn_wgs, pairs, n_stages, by_len);
     double best = 1e30;
     for (const AttnShape &sh : ATTN_SHAPES) {
         const int64_t base = pairs * ((p.row_tiles + sh.R - 1) / sh.R), at_once = sh.W == 8 ? 256 : 512;
@@ -290,10 +332,12 @@ FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len, size_t cap
         constexpr int NS = sizeof STEPS / sizeof STEPS[0];
         for (int c = 0; c < NS + 3; ++c) {
             const int64_t splits = c < NS ? STEPS[c] : at_once * (c - NS + 1) / base;
-            if (splits < 1 || splits > p.splits_bound) continue;
-            const int64_t stages = (n_stages + splits - 1) / splits;
-            const double t = attn_cost(sh, pairs, p.row_tiles, kv_len, (n_stages + stages - 1) / stages, stages);
-            if (t < best * (1 - 1e-9)) {
+            if (splits < 1 || splits > bound) continue;
+            const int64_t stages = (n_stages + splits - 1) / splits, ranges = (n_stages + stages - 1) / stages;
+            if (ranges > 1 && ranges > within) continue;
+            const double limit = best * (1 - 1e-9);
+            const double t = attn_cost(sh, pairs, p.row_tiles, kv_len, ranges, stages, limit);
+            if (t < limit) {
                 best = t;
                 set_attn_plan(p, sh.R, sh.W, splits, n_stages);
             }
@@ -305,53 +349,54 @@ FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len, size_t cap
         p.row_tiles = row_tiles;
         p.tiles_per_wg = 1;
         p.waves = 8;
-        p.splits = p.splits_bound = 1;
+        p.splits = 1;
         p.keys_per_split = (kv_len + 31) / 32 * 32;
     }
     return p;
 }
 
-// One round of eight-wave workgroups, tiles by the row count.
-static FcAttnPlan fc_plan_attention_default(const fc_config &cfg, int A, int kv_len)
+size_t fc_plan_workspace(const fc_config &cfg, const FcAttnPlan &p)
 {
-    FcAttnPlan p;
-    memset(&p, 0, sizeof p);
-    p.splits = p.splits_bound = 1;
-    if (cfg.dtype != FC_BF16 || cfg.head_dim != 128) return p;
-    p.kind = 1;
-    p.row_tiles = (int)(((int64_t)(cfg.n_q_heads / cfg.n_kv_heads) * A + 31) / 32);
-    const int64_t n_stages = ((int64_t)kv_len + 63) / 64;
-    return plan_fixed_tiles(p, 0, 8, 0, (int64_t)cfg.batch * cfg.n_kv_heads, n_stages, n_stages / 2 > 1 ? n_stages / 2 : 1);
-}
-
-size_t fc_plan_workspace(const fc_config &cfg, const FcAttnPlan &p, int A)
-{
-    (void)A;
-    if (p.splits_bound <= 1) return 0;
+    if (p.splits <= 1) return 0;
     if (p.kind == 0)  // per (workgroup tile, split): rows x Dh partial outputs + rows x 2 floats of row state
-        return (size_t)cfg.batch * cfg.n_kv_heads * ((p.row_tiles + p.tiles_per_wg - 1) / p.tiles_per_wg) * p.splits_bound *
+        return (size_t)cfg.batch * cfg.n_kv_heads * ((p.row_tiles + p.tiles_per_wg - 1) / p.tiles_per_wg) * p.splits *
                (16 * p.tiles_per_wg) * (cfg.head_dim + 2) * sizeof(float);
-    return (size_t)cfg.batch * cfg.n_kv_heads * p.row_tiles * p.splits_bound * ATTN_PART_BYTES;
+    return (size_t)cfg.batch * cfg.n_kv_heads * p.row_tiles * p.splits * ATTN_PART_BYTES;
 }
 
-// The plan of one call that brings `bytes` of workspace.  The kernel of kind 0 cuts the keys only to fill the
-// chip; without the space for it it runs uncut.
+// The plan of one call that brings `bytes` of workspace.
 // `last` (of a cache handle) keeps the plan of the last shape: a step asks for the same one in every layer.
-static FcAttnPlan plan_with_workspace(const fc_config &cfg, FcLastPlan &last, int A, int kv_len, size_t bytes,
-                                      size_t cap = SIZE_MAX)
+static FcAttnPlan plan_with_workspace(const fc_config &cfg, FcLastPlan &last, int A, int kv_len, size_t bytes)
 {
-    if (last.A != A || last.kv_len != kv_len || last.knobs != fc_knobs().version) {
-        last.plan = fc_plan_attention(cfg, A, kv_len, cap);
+    if (last.A != A || last.kv_len != kv_len || last.bytes != bytes || last.knobs != fc_knobs().version) {
+        last.plan = fc_plan_attention(cfg, A, kv_len, bytes);
         last.A = A;
         last.kv_len = kv_len;
+        last.bytes = bytes;
         last.knobs = fc_knobs().version;
     }
-    FcAttnPlan p = last.plan;
-    if (p.kind == 0 && fc_plan_workspace(cfg, p, A) > bytes) {
-        p.splits = p.splits_bound = 1;
-        p.keys_per_split = (kv_len + 31) / 32 * 32;
+    return last.plan;
+}
+
+// Workspace (bytes) of the attention of windows of up to max_rows rows over up to max_seq keys: what a call must bring,
+// and (`useful`) what the plan for the full length takes where that is more.  Shorter caches make do with as much.
+static size_t attn_workspace(const fc_config &cfg, int max_rows, bool useful)
+{
+    const int64_t pairs = (int64_t)cfg.batch * cfg.n_kv_heads, g = cfg.n_q_heads / cfg.n_kv_heads;
+    size_t most = 0;
+    int64_t tiles = 0;
+    for (int a = 1; a <= max_rows; ++a) {
+        const int64_t t = (g * a + 15) / 16;
+        if (t == tiles) continue;  // plans depend on the 16-row tiles only
+        tiles = t;
+        size_t b = attn_required(cfg, a, cfg.max_seq);
+        if (useful && pairs * t <= 4000) {  // (beyond 1900 32-row tiles no plan cuts the keys)
+            const size_t u = fc_plan_workspace(cfg, fc_plan_attention(cfg, a, cfg.max_seq));
+            if (u > b) b = u;
+        }
+        if (b > most) most = b;
     }
-    return p;
+    return most;
 }
 
 extern "C" {
@@ -373,7 +418,7 @@ fc_status fc_attention_plan(const fc_config *cfg, int32_t A, int32_t kv_len, int
     if (!plan) return fail(FC_ERR_INVALID_ARG, "plan is NULL");
     if (A < 1) return fail(FC_ERR_INVALID_ARG, "A %d must be >= 1", A);
     if (kv_len < 1 || kv_len > cfg->max_seq) return fail(FC_ERR_BOUNDS, "kv_len %d outside [1, %d]", kv_len, cfg->max_seq);
-    const FcAttnPlan p = fc_plan_attention(*cfg, A, kv_len);
+    const FcAttnPlan p = fc_plan_attention(*cfg, A, kv_len, attn_workspace(*cfg, A, true));
     plan[0] = p.kind;
     plan[1] = p.splits;
     plan[2] = p.keys_per_split;
@@ -565,29 +610,15 @@ fc_status fc_qkv_project_scatter(fc_cache *cache, int32_t layer, const void *x, 
 size_t fc_workspace_bytes(const fc_config *cfg, int32_t max_rows)
 {
     if (check_config(cfg) != FC_OK || max_rows < 1) return 0;
-    size_t best = 0;
-    const bool direct = cfg->dtype == FC_BF16 && cfg->head_dim == 128 && fc_knobs().attn_r <= 0 && fc_knobs().attn_wgs <= 0;
-    const int64_t pairs = (int64_t)cfg->batch * cfg->n_kv_heads, g = cfg->n_q_heads / cfg->n_kv_heads;
-    const int64_t n_stages = ((int64_t)cfg->max_seq + 63) / 64;
-    for (int a = 1; a <= max_rows; ++a) {
-        FcAttnPlan p;
-        if (direct) {  // all that counts is the bound on the key ranges
-            memset(&p, 0, sizeof p);
-            p.kind = 1;
-            p.row_tiles = (int)((g * a + 31) / 32);
-            p.splits_bound = (int)attn_splits_bound(pairs, p.row_tiles, n_stages / 2 > 1 ? n_stages / 2 : 1);
-        } else {
-            p = fc_plan_attention(*cfg, a, cfg->max_seq);
-        }
-        const size_t b = fc_plan_workspace(*cfg, p, a);
-        if (b > best) best = b;
-    }
-    return best;
+    return attn_workspace(*cfg, max_rows, true);
 }
 
 static fc_status run_attention(fc_cache *cache, int32_t layer, const FcAttnPlan &plan, const void *q, int32_t A,
-                               int32_t kv_len, const int32_t *pos, void *out, void *workspace, void *stream)
+                               int32_t kv_len, const int32_t *pos, void *out, void *workspace, size_t space, void *stream)
 {
+    const size_t bytes = fc_plan_workspace(cache->cfg, plan);
+    if (bytes > space)  // (not reached: the planner keeps within the space, and the plan of a tuning knob is required space)
+        return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", bytes, space);
     const FcGeom G = geom_of(cache);
     void *kl = layer_ptr(cache, cache->k, layer), *vl = layer_ptr(cache, cache->v, layer);
     hipError_t e = plan.kind == 1
@@ -610,12 +641,10 @@ fc_status fc_active_attention(fc_cache *cache, int32_t layer, const void *q, int
         return fail(FC_ERR_UNSUPPORTED, "batch * A exceeds 2^24 rows");
     if (kv_len < 1 || kv_len > cache->cfg.max_seq)
         return fail(FC_ERR_BOUNDS, "kv_len %d outside [1, %d]", kv_len, cache->cfg.max_seq);
-    const FcAttnPlan plan = plan_with_workspace(cache->cfg, cache->last_plan, A, kv_len, workspace ? workspace_bytes : 0);
-    const size_t need = fc_plan_workspace(cache->cfg, plan, A);
-    if (need > 0 && (!workspace || workspace_bytes < need))
-        return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need,
-                    workspace ? workspace_bytes : (size_t)0);
-    return run_attention(cache, layer, plan, q, A, kv_len, pos, out, workspace, stream);
+    const size_t need = attn_required(cache->cfg, A, kv_len), given = workspace ? workspace_bytes : 0;
+    if (given < need) return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, given);
+    const FcAttnPlan plan = plan_with_workspace(cache->cfg, cache->last_plan, A, kv_len, given);
+    return run_attention(cache, layer, plan, q, A, kv_len, pos, out, workspace, given, stream);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -669,28 +698,19 @@ fc_status fc_active_attention_static(fc_cache *cache, int32_t layer, const void 
         return fail(FC_ERR_UNSUPPORTED, "batch * A exceeds 2^24 rows");
     if (kv_len < 1 || kv_len > cache->cfg.max_seq)
         return fail(FC_ERR_BOUNDS, "kv_len %d outside [1, %d]", kv_len, cache->cfg.max_seq);
-    // Refused are the shapes whose partial results with one round of eight-wave workgroups exceed the array; the
-    // others are planned within it.
-    {
-        FcAttnPlan q = fc_plan_attention_default(cache->cfg, A, kv_len);
-        const size_t bytes = fc_plan_workspace(cache->cfg, q, A);
-        if (q.kind == 1 && bytes > FC_STATIC_SCRATCH_BYTES)
-            return fail(FC_ERR_WORKSPACE, "this shape needs %zu bytes of partial results, the static scratch holds %u",
-                        bytes, FC_STATIC_SCRATCH_BYTES);
-    }
-    const FcAttnPlan plan = plan_with_workspace(cache->cfg, cache->last_static, A, kv_len, FC_STATIC_SCRATCH_BYTES, FC_STATIC_SCRATCH_BYTES);
-    const size_t need = fc_plan_workspace(cache->cfg, plan, A);
-    if (need > FC_STATIC_SCRATCH_BYTES)  // a plan that a tuning knob forces is not bounded by the array
+    const size_t need = attn_required(cache->cfg, A, kv_len);
+    if (need > FC_STATIC_SCRATCH_BYTES)
         return fail(FC_ERR_WORKSPACE, "this shape needs %zu bytes of partial results, the static scratch holds %u", need,
                     FC_STATIC_SCRATCH_BYTES);
+    const FcAttnPlan plan = plan_with_workspace(cache->cfg, cache->last_static, A, kv_len, FC_STATIC_SCRATCH_BYTES);
     void *scratch = nullptr;
-    if (need > 0) {
+    if (plan.splits > 1) {
         st = static_scratch_ptr(&scratch);
         if (st != FC_OK) return st;
     }
     // Nothing in the scratch has to start at zero: every (row tile, split) slot the merge kernel
     // reads is written by the first kernel of the same call.
-    return run_attention(cache, layer, plan, q, A, kv_len, pos, out, scratch, stream);
+    return run_attention(cache, layer, plan, q, A, kv_len, pos, out, scratch, FC_STATIC_SCRATCH_BYTES, stream);
 }
 
 fc_status fc_refresh(fc_cache *cache, int32_t layer, const void *x, const void *w_qkv, const void *b_qkv,
@@ -710,11 +730,8 @@ fc_status fc_refresh(fc_cache *cache, int32_t layer, const void *x, const void *
             return fail(FC_ERR_BOUNDS, "kv_len %d outside [1, %d]", kv_len, cache->cfg.max_seq);
         if (start + R > kv_len)
             return fail(FC_ERR_BOUNDS, "refreshed rows end at %d, beyond kv_len %d", start + R, kv_len);
-        const FcAttnPlan plan = plan_with_workspace(cache->cfg, cache->last_plan, R, kv_len, workspace ? workspace_bytes : 0);
-        const size_t need = fc_plan_workspace(cache->cfg, plan, R);
-        if (need > 0 && (!workspace || workspace_bytes < need))
-            return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need,
-                        workspace ? workspace_bytes : (size_t)0);
+        const size_t need = attn_required(cache->cfg, R, kv_len), given = workspace ? workspace_bytes : 0;
+        if (given < need) return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, given);
     }
     st = fc_qkv_project_scatter(cache, layer, x, w_qkv, b_qkv, start, R, nullptr, q_scratch, stream);
     if (st != FC_OK || !out) return st;
@@ -835,8 +852,9 @@ namespace {
 
 // Carve-up of the whole-layer workspace for M = B * A rows (every part 256-byte aligned).
 struct LayerWs {
-    size_t h, q, o, x2, act, attn, lin, total;
-    size_t attn_bytes, lin_bytes;
+    size_t h, q, o, x2, act, lin, attn;  // attn: last, the attention takes what is left
+    size_t least;                        // bytes a call must bring
+    size_t lin_bytes;
 };
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -857,8 +875,6 @@ LayerWs layer_ws(const fc_config &c, int32_t d_ff, int32_t A)
     w.o = take(M * E * es);
     w.x2 = take(M * d * es);
     w.act = take(M * (size_t)d_ff * es);
-    w.attn_bytes = fc_workspace_bytes(&c, A);
-    w.attn = take(w.attn_bytes);
     size_t lin = fc_linear_workspace_bytes(c.dtype, (int)M, (int)E, c.hidden);
     const size_t l2 = fc_linear_workspace_bytes(c.dtype, (int)M, c.hidden, 2 * d_ff);
     const size_t l3 = fc_linear_workspace_bytes(c.dtype, (int)M, d_ff, c.hidden);
@@ -866,7 +882,8 @@ LayerWs layer_ws(const fc_config &c, int32_t d_ff, int32_t A)
     if (l3 > lin) lin = l3;
     w.lin_bytes = lin;
     w.lin = take(lin);
-    w.total = off;
+    w.attn = off;
+    w.least = off + align256(attn_workspace(c, A, false));
     return w;
 }
 
@@ -876,7 +893,7 @@ size_t fc_full_layer_workspace_bytes(const fc_config *cfg, int32_t d_ff, int32_t
 {
     if (check_config(cfg) != FC_OK || d_ff < 1 || max_rows < 1 || (int64_t)max_rows * cfg->batch > (1 << 24))
         return 0;
-    return layer_ws(*cfg, d_ff, max_rows).total;
+    return layer_ws(*cfg, d_ff, max_rows).attn + align256(attn_workspace(*cfg, max_rows, true));
 }
 
 fc_status fc_full_layer_step(fc_cache *cache, int32_t layer, const fc_layer_weights *wt, const void *x,
@@ -908,18 +925,19 @@ fc_status fc_full_layer_step(fc_cache *cache, int32_t layer, const fc_layer_weig
         cache->ws_A = A;
         cache->ws_d_ff = wt->d_ff;
     }
-    if (!workspace || workspace_bytes < w.total)
-        return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", w.total,
+    if (!workspace || workspace_bytes < w.least)
+        return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", w.least,
                     workspace ? workspace_bytes : (size_t)0);
     if ((uintptr_t)workspace & 15) return fail(FC_ERR_INVALID_ARG, "workspace must be 16-byte aligned");
     char *ws = (char *)workspace;
     const int M = c.batch * A, d = c.hidden, E = c.n_q_heads * c.head_dim;
     void *h = ws + w.h, *q = ws + w.q, *o = ws + w.o, *x2 = ws + w.x2, *act = ws + w.act;
-    void *lin = w.lin_bytes ? ws + w.lin : nullptr, *attn = w.attn_bytes ? ws + w.attn : nullptr;
+    const size_t attn_bytes = workspace_bytes - w.attn;
+    void *lin = w.lin_bytes ? ws + w.lin : nullptr, *attn = attn_bytes ? ws + w.attn : nullptr;
 
     st = fc_rmsnorm(c.dtype, x, wt->norm1, wt->eps, M, d, h, stream);
     if (st == FC_OK) st = fc_qkv_project_scatter(cache, layer, h, wt->w_qkv, wt->b_qkv, win_start, A, pos, q, stream);
-    if (st == FC_OK) st = fc_active_attention(cache, layer, q, A, kv_len, pos, o, attn, w.attn_bytes, stream);
+    if (st == FC_OK) st = fc_active_attention(cache, layer, q, A, kv_len, pos, o, attn, attn_bytes, stream);
     if (st == FC_OK) st = fc_linear_residual(c.dtype, o, wt->w_out, x, M, E, d, x2, lin, w.lin_bytes, stream);
     if (st == FC_OK) st = fc_rmsnorm(c.dtype, x2, wt->norm2, wt->eps, M, d, h, stream);
     if (st == FC_OK) st = fc_ffn_gate_up(c.dtype, h, wt->w_gate, wt->w_up, M, d, wt->d_ff, act, lin, w.lin_bytes, stream);

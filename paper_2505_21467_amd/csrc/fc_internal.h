@@ -12,7 +12,6 @@
 struct FcAttnPlan {
     int kind;            // 0 = fp32 / head_dim 64 kernel, 1 = bf16 head_dim 128 split-KV
     int splits;          // key ranges per (sequence, kv head); every one is non-empty
-    int splits_bound;    // upper bound of `splits` over all kv_len <= the given one (workspace sizing)
     int keys_per_split;  // multiple of 64 (kind 0: of 32)
     int row_tiles;       // 32-row (kind 0: 16-row) tiles of the flattened (head-in-group, a) rows per (b, kv head)
     int tiles_per_wg;    // row tiles handled by one workgroup
@@ -20,6 +19,7 @@ struct FcAttnPlan {
 };
 struct FcLastPlan {
     int A, kv_len, knobs;  // the shape it is for; version of the tuning knobs
+    size_t bytes;          // and the space
     FcAttnPlan plan;
 };
 
@@ -38,7 +38,7 @@ struct fc_cache {
     // Carve-up of the whole-layer workspace for the last (d_ff, A) seen: fc_full_layer_step is called
     // with the same shape step after step, and planning it anew walks every window size up to A.
     int32_t ws_d_ff, ws_A;
-    size_t ws_part[10];
+    size_t ws_part[9];
     FcLastPlan last_plan, last_static;  // attention plans of the last shape (own workspace, static scratch)
 };
 
@@ -82,7 +82,7 @@ __host__ __device__ inline size_t fc_v_index(const FcGeom &G, int b, int j, int 
 }
 
 FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len, size_t cap = SIZE_MAX);  // cap: bytes of partial results
-size_t fc_plan_workspace(const fc_config &cfg, const FcAttnPlan &p, int A);
+size_t fc_plan_workspace(const fc_config &cfg, const FcAttnPlan &p);
 
 // Kernel launchers (defined in the .hip kernel files).  All return hipGetLastError() after launch.
 hipError_t fc_launch_copy_rows(const FcGeom &G, int dtype, void *k_layer, void *v_layer, void *k_rows,

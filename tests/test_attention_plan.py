@@ -3,6 +3,7 @@ to the cache's capacity; and every tile shape it can pick agrees with the oracle
 import random
 
 import pytest
+import torch
 
 from paper_2505_21467_amd import binding as fc
 from paper_2505_21467_amd import inputs
@@ -26,6 +27,75 @@ def test_plans_cover_the_keys_and_fit_the_workspace():
             assert p["keys_per_split"] % 64 == 0 and p["tiles_per_wg"] in (2, 4, 8) and p["waves"] in (4, 8)
             need = batch * hkv * p["row_tiles"] * p["splits"] * 32 * (256 + 16) if p["splits"] > 1 else 0
             assert need <= space, (a, kv, p, need, space)
+
+
+def _required(pairs, g, A, kv):
+    """Partial results (bytes) of one round of workgroups, tiles by the row count: what a bf16 call must bring."""
+    tiles, by_len = -(-g * A // 32), max(1, -(-kv // 64) // 2)
+    R = 2 if tiles <= 2 else 4 if tiles <= 7 else 8
+
+    def nearest(target, base):
+        return max(1, min((target + base // 2) // base, by_len))
+    splits = nearest(256, pairs * -(-tiles // R))
+    if R == 4 and pairs * -(-tiles // R) * splits < 256:
+        splits = nearest(512, pairs * -(-tiles // 2))
+    return pairs * tiles * splits * 32 * (256 + 16) if splits > 1 else 0
+
+
+def test_calls_require_one_round_of_partial_results():
+    rng = random.Random(11)
+    for _ in range(300):
+        hkv, g = rng.choice((1, 2, 4, 8, 32)), rng.choice((1, 2, 7, 8))
+        smax, batch, rows = rng.randint(1, 20000), rng.randint(1, 8), rng.randint(1, 300)
+        c = fc.make_config(1, batch, 256, hkv * g, hkv, 128, smax, "bf16")
+        space = fc.fc_workspace_bytes(c, rows)
+        h = fc.fc_cache_alloc(c, 0x10000, 0x10000)
+        for _ in range(4):
+            a, kv = rng.randint(1, rows), rng.randint(1, smax)
+            need = _required(batch * hkv, g, a, kv)
+            assert need <= space, (a, kv, need, space)
+            if need == 0:
+                continue  # (a call without workspace is accepted)
+            for given in (0, need - 1):
+                with pytest.raises(fc.FreeCacheError) as e:
+                    fc.fc_active_attention(h, 0, 0x10000, a, kv, None, 0x10000, 0x10000 if given else None, given, 0)
+                assert e.value.status == fc.FC_ERR_WORKSPACE and "%d bytes needed" % need in str(e.value)
+        fc.fc_cache_free(h)
+    # 28/4 heads x 16800 keys: 7 row tiles x 32 ranges at 32 rows; the most, 4 tiles x 64 ranges, at 15 .. 18 rows
+    c4 = fc.make_config(1, 1, 3584, 28, 4, 128, 16800, "bf16")
+    assert _required(4, 7, 32, 16800) == 4 * 7 * 32 * 8704 and fc.fc_workspace_bytes(c4, 32) == 4 * 4 * 64 * 8704
+    # a workgroup per (sequence, head): nothing to merge, nothing asked for
+    assert fc.fc_workspace_bytes(fc.make_config(1, 8, 4096, 32, 32, 128, 2304, "bf16"), 32) == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt,B,Hq,Hkv,Dh,A,S", [
+    ("bf16", 8, 32, 32, 128, 3, 1300),   # required: nothing
+    ("bf16", 1, 32, 32, 128, 14, 1563),  # one range more than required is of use
+    ("f32", 1, 4, 1, 64, 8, 2000), ("bf16", 1, 6, 2, 64, 9, 3001), ("f32", 2, 2, 1, 128, 5, 700),  # no call requires any
+])
+def test_less_workspace_means_fewer_key_ranges(dt, B, Hq, Hkv, Dh, A, S):
+    print("[case] workspace", dt, B, Hq, Hkv, Dh, A, S, flush=True)
+    from oracle import fc_oracle as orc
+    w = inputs.Workload("t", dt, B, 256, Hq, Hkv, Dh, S, A)
+    g = GpuLayerCache(dt, B, 256, Hq, Hkv, Dh, S, max_rows=A)
+    o = OracleLayerCache(dt, B, 256, Hq, Hkv, Dh, S)
+    K, V = inputs.kv_fill(w, 2, S)
+    g.write_rows(0, K, V, 0)
+    o.write_rows(K, V, 0)
+    Q = inputs.normal(2, "q", (B, Hq, A, Dh), 1.0, dt)
+    ref = orc.attend(o.cfg, inputs.as_oracle(Q), o.Kc, o.Vc, S, None)
+    least = _required(B * Hkv, Hq // Hkv, A, S) if (dt, Dh) == ("bf16", 128) else 0
+    full = g.ws_bytes
+    for space in sorted({least, (least + full) // 2, max(least, full - 1), full, 2 * full}):
+        # nothing beyond the given bytes may be written
+        ws = torch.full((space + 256,), 0x5A, dtype=torch.uint8, device="cuda:0")
+        O = torch.full((B, A, Hq * Dh), float("nan"), dtype=g.tdt, device="cuda:0")
+        fc.fc_active_attention(g.handle, 0, g.dev_t(Q), A, S, None, O, ws if space else None, space)
+        torch.cuda.synchronize()
+        assert_close(inputs.as_oracle(O), ref, dt, "workspace of %d bytes" % space)
+        assert bool((ws[space:] == 0x5A).all())
+    g.close()
 
 
 @pytest.mark.gpu

@@ -362,6 +362,32 @@ def test_full_layer_step_tiny_f32():
     _run_full_layer(inputs.C1.scaled(cached_len=100), 100, 32, seed=5, with_bias=True, std=0.06)
 
 
+def test_full_layer_step_takes_what_it_requires():
+    """fp32: no call requires space for partial results of the attention; with less the keys are cut into fewer ranges."""
+    w = inputs.C1.scaled(cached_len=700)
+    L, A, S = 700, 8, 708
+    layer, X = FullLayer(w, 3, std=0.06), inputs.hidden_states(w, 3, A)
+    y = []
+    for less in (False, True):
+        g = GpuLayerCache(w.dtype, w.batch, w.hidden, w.n_q_heads, w.n_kv_heads, w.head_dim, S, max_rows=A)
+        K, V = inputs.kv_fill(w, 3, L)
+        g.write_rows(0, K, V, 0)
+        assert g.ws_bytes > 256
+        need = fc.fc_full_layer_workspace_bytes(g.cfg, w.d_ff, A)
+        least = need - -(-g.ws_bytes // 256) * 256
+        given = least if less else need
+        ws, xd = torch.full((need,), 0x5A, dtype=torch.uint8, device=DEV), _dev(X)
+        out = torch.full_like(xd, float("nan"))
+        fc.fc_full_layer_step(g.handle, 0, layer.handle, xd, L, A, None, S, out, ws, given)
+        torch.cuda.synchronize()
+        assert bool((ws[given:] == 0x5A).all())
+        with pytest.raises(fc.FreeCacheError):
+            fc.fc_full_layer_step(g.handle, 0, layer.handle, xd, L, A, None, S, out, ws, least - 1)
+        y.append(inputs.as_oracle(out))
+        g.close()
+    assert_close(y[1], y[0], "f32", "layer output with less workspace")
+
+
 def test_full_layer_step_small_bf16_generic_shapes():
     # shapes none of the matrix-core kernels cover: every module runs on the plain kernels
     w = inputs.Workload("small", "bf16", 2, 136, 6, 2, 64, 0, 0, d_ff=200)
