@@ -24,7 +24,10 @@
  *    returned, nothing has been enqueued, and fc_last_error() describes the problem.  No entry
  *    point aborts or throws across the ABI.
  *  - Calls on distinct caches are independent.  One cache must not be used from two streams at
- *    the same time.
+ *    the same time.  Host threads that share a cache take turns too, since a call may enqueue
+ *    several kernels that belong together (the projection hands partial sums over in the handle's
+ *    scratch); only fc_active_attention keeps nothing in the handle, so that threads with workspaces of
+ *    their own may call it at the same time on one stream.
  */
 #ifndef FREECACHE_H
 #define FREECACHE_H

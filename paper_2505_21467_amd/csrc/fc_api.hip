@@ -95,9 +95,6 @@ fc_status hip_fail(hipError_t e, const char *what)
 // Tuning knobs (see FcKnobs): read from the environment once, then changed only by fc_tuning_set.
 namespace {
 
-FcKnobs g_knobs;
-bool g_knobs_init = false;
-
 void knobs_defaults(FcKnobs &k)
 {
     memset(&k, 0, sizeof k);
@@ -131,15 +128,19 @@ const char *const KNOB_NAMES[] = {"FC_ATTN_TILES", "FC_ATTN_WGS", "FC_LIN_WGS", 
                                   "FC_LIN_KSPLIT", "FC_GEMM_NO_SPLIT", "FC_PROJ_GEMM_SHAPE", "FC_PROJ_NO_HEADSPLIT",
                                   "FC_ACCEPT_WGS"};
 
+FcKnobs knobs_from_environment()
+{
+    FcKnobs k;
+    knobs_defaults(k);
+    for (const char *n : KNOB_NAMES)
+        if (const char *e = getenv(n)) knob_apply(k, n, e);
+    return k;
+}
+
 FcKnobs &knobs_mut()
 {
-    if (!g_knobs_init) {
-        knobs_defaults(g_knobs);
-        for (const char *n : KNOB_NAMES)
-            if (const char *e = getenv(n)) knob_apply(g_knobs, n, e);
-        g_knobs_init = true;
-    }
-    return g_knobs;
+    static FcKnobs k = knobs_from_environment();  // (once, whichever thread comes first)
+    return k;
 }
 
 }  // namespace
@@ -364,19 +365,45 @@ size_t fc_plan_workspace(const fc_config &cfg, const FcAttnPlan &p)
     return (size_t)cfg.batch * cfg.n_kv_heads * p.row_tiles * p.splits * ATTN_PART_BYTES;
 }
 
-// The plan of one call that brings `bytes` of workspace.
-// `last` (of a cache handle) keeps the plan of the last shape: a step asks for the same one in every layer.
-static FcAttnPlan plan_with_workspace(const fc_config &cfg, FcLastPlan &last, int A, int kv_len, size_t bytes)
-{
-    if (last.A != A || last.kv_len != kv_len || last.bytes != bytes || last.knobs != fc_knobs().version) {
-        last.plan = fc_plan_attention(cfg, A, kv_len, bytes);
-        last.A = A;
-        last.kv_len = kv_len;
-        last.bytes = bytes;
-        last.knobs = fc_knobs().version;
+namespace {
+
+// The last few results of a pure planning function, per host thread: a step asks for the same shapes in every layer, and
+// a plan takes a microsecond or two.  Keys are plain values without padding.
+template <typename Key, typename Value>
+struct Memo {
+    static constexpr int N = 4;
+    Key key[N];
+    Value value[N];
+    int used = 0, next = 0;
+    template <typename Make>
+    const Value &get(const Key &k, Make make)
+    {
+        for (int i = 0; i < used; ++i)
+            if (!memcmp(&key[i], &k, sizeof k)) return value[i];
+        const int at = next;
+        next = (next + 1) % N;
+        value[at] = make();
+        key[at] = k;
+        if (used < N) ++used;
+        return value[at];
     }
-    return last.plan;
+};
+
+struct AttnPlanKey {
+    size_t bytes;
+    int32_t batch, n_q_heads, n_kv_heads, head_dim, dtype, A, kv_len, knobs;
+};
+static_assert(sizeof(AttnPlanKey) == sizeof(size_t) + 8 * sizeof(int32_t), "no padding");
+
+// The plan of one call that brings `bytes` of workspace.
+FcAttnPlan plan_with_workspace(const fc_config &c, int A, int kv_len, size_t bytes)
+{
+    static thread_local Memo<AttnPlanKey, FcAttnPlan> memo;
+    const AttnPlanKey k = {bytes, c.batch, c.n_q_heads, c.n_kv_heads, c.head_dim, c.dtype, A, kv_len, fc_knobs().version};
+    return memo.get(k, [&] { return fc_plan_attention(c, A, kv_len, bytes); });
 }
+
+}  // namespace
 
 // Workspace (bytes) of the attention of windows of up to max_rows rows over up to max_seq keys: what a call must bring,
 // and (`useful`) what the plan for the full length takes where that is more.  Shorter caches make do with as much.
@@ -454,9 +481,6 @@ fc_status fc_cache_alloc(const fc_config *cfg, void *k_storage, void *v_storage,
     c->k = k_storage;
     c->v = v_storage;
     c->owned = false;
-    c->ws_A = c->ws_d_ff = 0;
-    memset(&c->last_plan, 0, sizeof c->last_plan);
-    memset(&c->last_static, 0, sizeof c->last_static);
     for (int i = 0; i < 64; ++i)
         c->inv_freq[i] = i < cfg->head_dim / 2 ? pow((double)cfg->rope_base, -2.0 * i / cfg->head_dim) : 0.0;
     if (!k_storage) {
@@ -643,7 +667,7 @@ fc_status fc_active_attention(fc_cache *cache, int32_t layer, const void *q, int
         return fail(FC_ERR_BOUNDS, "kv_len %d outside [1, %d]", kv_len, cache->cfg.max_seq);
     const size_t need = attn_required(cache->cfg, A, kv_len), given = workspace ? workspace_bytes : 0;
     if (given < need) return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, given);
-    const FcAttnPlan plan = plan_with_workspace(cache->cfg, cache->last_plan, A, kv_len, given);
+    const FcAttnPlan plan = plan_with_workspace(cache->cfg, A, kv_len, given);
     return run_attention(cache, layer, plan, q, A, kv_len, pos, out, workspace, given, stream);
 }
 
@@ -702,7 +726,7 @@ fc_status fc_active_attention_static(fc_cache *cache, int32_t layer, const void 
     if (need > FC_STATIC_SCRATCH_BYTES)
         return fail(FC_ERR_WORKSPACE, "this shape needs %zu bytes of partial results, the static scratch holds %u", need,
                     FC_STATIC_SCRATCH_BYTES);
-    const FcAttnPlan plan = plan_with_workspace(cache->cfg, cache->last_static, A, kv_len, FC_STATIC_SCRATCH_BYTES);
+    const FcAttnPlan plan = plan_with_workspace(cache->cfg, A, kv_len, FC_STATIC_SCRATCH_BYTES);
     void *scratch = nullptr;
     if (plan.splits > 1) {
         st = static_scratch_ptr(&scratch);
@@ -857,6 +881,10 @@ struct LayerWs {
     size_t lin_bytes;
 };
 
+struct LayerWsKey {
+    int32_t batch, hidden, n_q_heads, n_kv_heads, head_dim, max_seq, dtype, d_ff, A, knobs;
+};
+
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 LayerWs layer_ws(const fc_config &c, int32_t d_ff, int32_t A)
@@ -915,16 +943,9 @@ fc_status fc_full_layer_step(fc_cache *cache, int32_t layer, const fc_layer_weig
         return fail(FC_ERR_BOUNDS, "window [%d, %d+%d) outside the cache of %d rows", win_start, win_start, A,
                     c.max_seq);
     if (kv_len < 1 || kv_len > c.max_seq) return fail(FC_ERR_BOUNDS, "kv_len %d outside [1, %d]", kv_len, c.max_seq);
-    LayerWs w;
-    static_assert(sizeof(LayerWs) == sizeof(cache->ws_part), "cached carve-up");
-    if (cache->ws_A == A && cache->ws_d_ff == wt->d_ff) {
-        memcpy(&w, cache->ws_part, sizeof w);
-    } else {
-        w = layer_ws(c, wt->d_ff, A);
-        memcpy(cache->ws_part, &w, sizeof w);
-        cache->ws_A = A;
-        cache->ws_d_ff = wt->d_ff;
-    }
+    static thread_local Memo<LayerWsKey, LayerWs> memo;  // (planning it walks every window size up to A)
+    const LayerWsKey key = {c.batch, c.hidden, c.n_q_heads, c.n_kv_heads, c.head_dim, c.max_seq, c.dtype, wt->d_ff, A, fc_knobs().version};
+    const LayerWs w = memo.get(key, [&] { return layer_ws(c, wt->d_ff, A); });
     if (!workspace || workspace_bytes < w.least)
         return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", w.least,
                     workspace ? workspace_bytes : (size_t)0);

@@ -17,12 +17,8 @@ struct FcAttnPlan {
     int tiles_per_wg;    // row tiles handled by one workgroup
     int waves;           // waves per workgroup (tiles_per_wg or twice that)
 };
-struct FcLastPlan {
-    int A, kv_len, knobs;  // the shape it is for; version of the tuning knobs
-    size_t bytes;          // and the space
-    FcAttnPlan plan;
-};
 
+// A cache handle: written by fc_cache_alloc only.
 struct fc_cache {
     fc_config cfg;
     int32_t spad;        // max_seq rounded up to FC_VTILE
@@ -35,11 +31,6 @@ struct fc_cache {
     // Device scratch owned by the handle (nullptr when no GPU was present at creation): space for the
     // partial sums that the short-window projection hands from its first kernel to its second.
     void *scratch;
-    // Carve-up of the whole-layer workspace for the last (d_ff, A) seen: fc_full_layer_step is called
-    // with the same shape step after step, and planning it anew walks every window size up to A.
-    int32_t ws_d_ff, ws_A;
-    size_t ws_part[9];
-    FcLastPlan last_plan, last_static;  // attention plans of the last shape (own workspace, static scratch)
 };
 
 #define FC_SCRATCH_BYTES (32u * 1024u * 1024u)

@@ -138,3 +138,42 @@ def test_every_tile_shape_matches_oracle(tiles, Hq, Hkv, A, S, knob):
     O = g.attend(0, g.dev_t(Q), S)
     assert_close(inputs.as_oracle(O), orc.attend(o.cfg, inputs.as_oracle(Q), o.Kc, o.Vc, S, None), dt, tiles)
     g.close()
+
+
+@pytest.mark.gpu
+def test_host_threads_with_two_shapes_share_a_cache():
+    """Two threads plan and launch two shapes on one handle and stream, each with its own buffers."""
+    import threading
+    print("[case] two threads", flush=True)
+    dt, B, Hq, Hkv, Dh, S = "bf16", 1, 14, 2, 128, 1500
+    w = inputs.Workload("t", dt, B, 256, Hq, Hkv, Dh, S, 32)
+    g = GpuLayerCache(dt, B, 256, Hq, Hkv, Dh, S, max_rows=32)
+    g.write_rows(0, *inputs.kv_fill(w, 2, S), 0)
+    stream = torch.cuda.current_stream().cuda_stream
+    jobs = []
+    for A, kv in ((32, S), (5, 300)):
+        Q = g.dev_t(inputs.normal(A, "q", (B, Hq, A, Dh), 1.0, dt))
+        O = [torch.full((B, A, Hq * Dh), float("nan"), dtype=g.tdt, device="cuda:0") for _ in range(2)]
+        ws = torch.empty(max(16, fc.fc_workspace_bytes(g.cfg, A)), dtype=torch.uint8, device="cuda:0")
+        fc.fc_active_attention(g.handle, 0, Q, A, kv, None, O[0], ws, ws.numel(), stream)
+        jobs.append((Q, A, kv, O, ws))
+    torch.cuda.synchronize()
+    assert fc.fc_attention_plan(g.cfg, 32, S) != fc.fc_attention_plan(g.cfg, 5, 300)
+    wrong = []
+
+    def work(Q, A, kv, O, ws):
+        try:
+            for _ in range(300):
+                fc.fc_active_attention(g.handle, 0, Q, A, kv, None, O[1], ws, ws.numel(), stream)
+        except Exception as e:
+            wrong.append(e)
+    threads = [threading.Thread(target=work, args=j) for j in jobs]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not wrong
+    for _, _, _, O, _ in jobs:
+        assert torch.equal(O[0].view(torch.int16), O[1].view(torch.int16))
+    g.close()
