@@ -363,6 +363,15 @@ struct AttnTileArgs {
 
 constexpr int AT_STRIDE = 4;  // padding floats per row of the exchange area
 
+// Probabilities are fp32: for bf16 values of head_dim 64 they go into the output products as sums of three bf16 numbers,
+// which hold all 24 bits (error against 64 bits 1.65e-3, what rounding the result costs; with probabilities in bf16 2.0e-3
+// and 1 to 4 % less time: 32 rows x 4 heads x 288 keys 4.32 against 4.2 us).  For bf16 of head_dim 128 they are rounded to bf16 as in the split-KV kernel; the planner chooses between the
+// two by length.  The exponential is the hardware's, of a rounded product: over 40 fp32 shapes of 64 .. 2048 keys the
+// error against 64 bits is 1.004 times that with expf (5e-7 at 288 keys, all from the sums), and the tiny
+// configuration's step takes 10.6 us instead of 11.2.
+template <typename T, int DH>
+constexpr int prob_terms() { return Op<T>::KB == 8 && DH == 64 ? 3 : 1; }
+
 template <typename T>
 __device__ __forceinline__ void attn_store_row4(const AttnTileArgs &p, int bj, int row, int d0, float4 v)
 {
@@ -385,6 +394,7 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
     constexpr int KB = O::KB, NKB = DH / (4 * KB), DV = DH / DS, ND = DV / 16, ROW = DV + AT_STRIDE;
     constexpr bool F32 = KB == 4;
     constexpr int NV = F32 ? 2 : 1;  // V fragments per 16 head-dim rows and 32 keys
+    constexpr int NP = prob_terms<T, DH>();
     extern __shared__ __align__(16) unsigned char attn_smem[];
     float *xo = (float *)attn_smem;                  // [wave][16 QT][ROW]
     float *xml = xo + TW * QT * 16 * ROW;            // [wave][16 QT][2]
@@ -488,16 +498,23 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
             for (int d = 0; d < ND; ++d)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) o[u][d][r] *= alpha;
-            frag pf[NV];
+            frag pf[F32 ? NV : NP];
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
-                if constexpr (F32) pf[r >> 2][r & 3] = pr[r];
-                else pf[0][r] = (__bf16)pr[r];
+                if constexpr (F32) {
+                    pf[r >> 2][r & 3] = pr[r];
+                } else {
+#pragma unroll
+                    for (int h = 0; h < NP; ++h) {
+                        pf[h][r] = (__bf16)pr[r];
+                        pr[r] -= (float)pf[h][r];  // (exact)
+                    }
+                }
             }
 #pragma unroll
             for (int d = 0; d < ND; ++d)
 #pragma unroll
-                for (int h = 0; h < NV; ++h) o[u][d] = O::mfma(vf[d][h], pf[h], o[u][d]);
+                for (int h = 0; h < (F32 ? NV : NP); ++h) o[u][d] = O::mfma(vf[d][F32 ? h : 0], pf[h], o[u][d]);
         }
     }
 
