@@ -364,11 +364,11 @@ struct AttnTileArgs {
 constexpr int AT_STRIDE = 4;  // padding floats per row of the exchange area
 
 // Probabilities are fp32: for bf16 values of head_dim 64 they go into the output products as sums of three bf16 numbers,
-// which hold all 24 bits (error against 64 bits 1.65e-3, what rounding the result costs; with probabilities in bf16 2.0e-3
-// and 1 to 4 % less time: 32 rows x 4 heads x 288 keys 4.32 against 4.2 us).  For bf16 of head_dim 128 they are rounded to bf16 as in the split-KV kernel; the planner chooses between the
-// two by length.  The exponential is the hardware's, of a rounded product: over 40 fp32 shapes of 64 .. 2048 keys the
-// error against 64 bits is 1.004 times that with expf (5e-7 at 288 keys, all from the sums), and the tiny
-// configuration's step takes 10.6 us instead of 11.2.
+// which hold all 24 bits (error against 64 bits 1.65e-3, what rounding the result costs; with probabilities in bf16
+// 2.0e-3 and 1 to 4 % less time: 32 rows x 4 heads x 288 keys 4.32 against 4.2 us).  For bf16 of head_dim 128 they are
+// rounded to bf16 as in the split-KV kernel; the planner chooses between the two by length.  The exponential is the
+// hardware's, of a rounded product: over 40 fp32 shapes of 64 .. 2048 keys the error against 64 bits is 1.004 times
+// that with expf (5e-7 at 288 keys, all from the sums), and the tiny configuration's step takes 10.6 us instead of 11.2.
 template <typename T, int DH>
 constexpr int prob_terms() { return Op<T>::KB == 8 && DH == 64 ? 3 : 1; }
 

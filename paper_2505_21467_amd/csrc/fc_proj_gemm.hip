@@ -89,7 +89,10 @@ __device__ __forceinline__ void wait_stages(int k)
     else wait_vmg<0, LGKM0>();
 }
 
-// silu(g) * u in fp32 (hardware exponential and reciprocal, one ulp each, in front of the rounding to bf16)
+// silu(g) * u in fp32, in front of the rounding to bf16, with the hardware's exponential and reciprocal (gates below
+// -87 give 0 instead of some 1e-36).  Against expf and a division, which the kernels for few rows use: over 16 shapes of 33 ..
+// 600 rows the same error against 64 bits (1.66e-3, the rounding), 2 results in 10000 off by a rounding either way;
+// 2304 rows of a layer 2122 us per two layers instead of 2164, 256 rows 425.5 instead of 428.5.
 __device__ __forceinline__ float silu_mul(float g, float u)
 {
     return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(g * -1.4426950408889634f)) * u;
@@ -292,7 +295,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x16 (&acc)[M
 
 // Vocabulary mode (EPI 4): lane (col, hi) holds, for window row col, the logits 32 t + 8 (r >> 2) + 4 hi + (r & 3)
 // of slab hs, ascending in (t, r), so that ties keep the smaller index; the other half is in lane ^ 32.  First the
-// maximum and its place, then the sum of exponentials against it.
+// maximum and its place, then the sum of exponentials against it, by the hardware's exponential of a rounded product.
+// On logits that are exact in fp32 the error of the confidences against 64 bits is 5 .. 10e-8, 0.87 times that of a running
+// maximum with expf and 0.89 times that of expf in this form, which also takes longer (256 rows x 152064: 309.0 us, this
+// 303.9); on others the logits' own error covers it.
 template <int MW>
 __device__ __forceinline__ void gemm_epilogue_vocab(const GemmArgs &p, const f32x16 (&acc)[MW][4], int hs, int m_first, int lane)
 {
