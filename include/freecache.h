@@ -14,6 +14,9 @@
  *    library keeps no reference after the enqueued work has run.
  *  - Element type of all tensors is fc_config.dtype (float or bfloat16, the latter as raw 16-bit
  *    words), except pos (int32) and the workspace (opaque bytes).
+ *  - Tensors need the alignment of their elements, with these exceptions: cache storage, the tensors of
+ *    the linear layers, of the vocabulary projection and of fc_gather_rows, dlm and ar are 16-byte
+ *    aligned (checked), and so are x and w_qkv of bf16 caches with head_dim 128, and every workspace.
  *  - Compute entry points only enqueue work on `stream` (a hipStream_t passed as void*; NULL is the
  *    default stream).  They never synchronise, never allocate and clear no memory with a memset
  *    node, so a caller may record them into a HIP graph on a capturing stream and replay it; what

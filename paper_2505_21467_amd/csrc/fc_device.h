@@ -18,6 +18,28 @@ __device__ __forceinline__ uint16_t fc_bf16_bits(float f)
     return x.u;
 }
 
+// 16- and 8-byte pieces of a caller's tensor that need only be aligned to its elements (views may start anywhere): the
+// compiler emits the same single loads and stores for them as for aligned pieces, the hardware takes any address.
+struct __attribute__((packed, aligned(2))) fc_any16 {
+    uint32_t w[4];
+};
+struct __attribute__((packed, aligned(2))) fc_any8 {
+    uint32_t w[2];
+};
+template <typename V>
+__device__ __forceinline__ V fc_load_any(const void *p)
+{
+    static_assert(sizeof(V) == 16, "16 bytes");
+    return __builtin_bit_cast(V, *(const fc_any16 *)p);
+}
+template <typename V>
+__device__ __forceinline__ void fc_store_any(void *p, V v)
+{
+    static_assert(sizeof(V) == 16 || sizeof(V) == 8, "16 or 8 bytes");
+    if constexpr (sizeof(V) == 16) *(fc_any16 *)p = __builtin_bit_cast(fc_any16, v);
+    else *(fc_any8 *)p = __builtin_bit_cast(fc_any8, v);
+}
+
 template <typename T>
 __device__ __forceinline__ T fc_from_float(float f);
 template <>

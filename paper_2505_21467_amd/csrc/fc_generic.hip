@@ -82,13 +82,13 @@ __device__ __forceinline__ float partner32(float v)  // the value of lane ^ 32
     return (threadIdx.x & 32) ? __uint_as_float(r[0]) : __uint_as_float(r[1]);
 }
 
-__device__ __forceinline__ void store4(float *p, const float (&y)[4]) { *(float4 *)p = make_float4(y[0], y[1], y[2], y[3]); }
+__device__ __forceinline__ void store4(float *p, const float (&y)[4]) { fc_store_any(p, make_float4(y[0], y[1], y[2], y[3])); }
 __device__ __forceinline__ void store4(bf16_t *p, const float (&y)[4])
 {
     uint2 w;
     w.x = (uint32_t)fc_bf16_bits(y[0]) | ((uint32_t)fc_bf16_bits(y[1]) << 16);
     w.y = (uint32_t)fc_bf16_bits(y[2]) | ((uint32_t)fc_bf16_bits(y[3]) << 16);
-    *(uint2 *)p = w;
+    fc_store_any(p, w);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -170,9 +170,9 @@ __global__ __launch_bounds__(TW * 64) void k_linear_tile(TileArgs p)
             const bool ok = b + u < b1 && k + KB * q < p.K;
             const int at = ok ? k : -KB * q;
 #pragma unroll
-            for (int t = 0; t < NT; ++t) wf[u][t] = *(const frag *)(wrow[t] + at);
+            for (int t = 0; t < NT; ++t) wf[u][t] = fc_load_any<frag>(wrow[t] + at);
 #pragma unroll
-            for (int t = 0; t < MT; ++t) xf[u][t] = *(const frag *)(xrow[t] + at);
+            for (int t = 0; t < MT; ++t) xf[u][t] = fc_load_any<frag>(xrow[t] + at);
             if (!ok) {
 #pragma unroll
                 for (int t = 0; t < NT; ++t) wf[u][t] = frag{};
@@ -416,7 +416,7 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
         const int hg = ok ? row / p.A : 0, a = ok ? row - hg * p.A : 0;
         const T *qr = (const T *)p.Q + (((size_t)b * G.Hq + j * G.g + hg) * p.A + a) * DH + KB * q;
 #pragma unroll
-        for (int s = 0; s < NKB; ++s) qf[u][s] = ok ? *(const frag *)(qr + 4 * KB * s) : frag{};
+        for (int s = 0; s < NKB; ++s) qf[u][s] = ok ? fc_load_any<frag>(qr + 4 * KB * s) : frag{};
     }
     f32x4 o[QT][ND];
     float m[QT], l[QT];

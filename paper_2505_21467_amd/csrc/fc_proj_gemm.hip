@@ -114,6 +114,7 @@ __host__ __device__ constexpr int epi_bytes(int NT) { return 32 * (NT * 128 + 16
 // The workgroup's bias goes to LDS at the very start: nothing else asks for it before the end, and a layer's bias
 // comes from HBM (2.5 us with the matrix core idle when the epilogue fetched it).  NPW pairs: the low values, then
 // the high ones; pairs (2 d, 2 d + 1) of all slabs laid end to end, from pair `first` on.  One wave calls this.
+// A direct load takes two values from a 4-byte address; a bias that starts at an odd element goes through registers.
 constexpr int BIAS_LDS = 512;
 __device__ __forceinline__ void load_bias(const GemmArgs &p, unsigned char *dst, int first, int npw, int n_pairs, int lane)
 {
@@ -124,9 +125,13 @@ __device__ __forceinline__ void load_bias(const GemmArgs &p, unsigned char *dst,
         const bool high = d >= npw / 2;
         const int pr = min(first + 2 * (high ? d - npw / 2 : d), n_pairs - 2);
         const uint16_t *src = p.bias + (pr >> 6) * 128 + (pr & 63) + (high ? 64 : 0);
-        __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)src,
-                                         (void __attribute__((address_space(3))) *)(dst + d0 * 4), 4, 0, 0);
+        if (((uintptr_t)p.bias & 3) == 0)
+            __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)src,
+                                             (void __attribute__((address_space(3))) *)(dst + d0 * 4), 4, 0, 0);
+        else
+            *(uint32_t *)(dst + d * 4) = (uint32_t)src[0] | ((uint32_t)src[1] << 16);
     }
+    wait_vmg<63, true>();  // LDS writes done, if any
 }
 
 // Epilogue of a wave.  Lane (col, hi) of sub-tile i holds window row m_first + 32 i + col; register r of
@@ -251,8 +256,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x16 (&acc)[M
                 }
                 if (hs_t < G.Hq) {
                     uint16_t *q = p.Q + (((size_t)b * G.Hq + hs_t) * p.A + a) * 128 + lf;
-                    *(uint4 *)q = valid ? pack8(lo) : make_uint4(0, 0, 0, 0);
-                    *(uint4 *)(q + 64) = valid ? pack8(hv) : make_uint4(0, 0, 0, 0);
+                    const uint4 ql = valid ? pack8(lo) : make_uint4(0, 0, 0, 0), qh = valid ? pack8(hv) : make_uint4(0, 0, 0, 0);
+                    fc_store_any(q, ql);
+                    fc_store_any(q + 64, qh);
                 } else if (valid) {
                     uint16_t *k = p.Kc + fc_k_index(G, b, hs_t - G.Hq, pp, lf);
                     *(uint4 *)k = pack8(lo);
