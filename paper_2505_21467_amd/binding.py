@@ -9,8 +9,9 @@ import os
 
 import torch
 
-_raw_stream = torch._C._cuda_getCurrentRawStream
-_current_device = torch._C._cuda_getDevice
+# Private to torch; without them (another build of torch) the public lookup below serves.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libfreecache.so")
@@ -150,7 +151,7 @@ def _stream(stream):
     if stream is None:
         # The raw handle, without the Stream object that torch.cuda.current_stream() builds on every call
         # (2.7 us of a 14 us tiny step, twice).
-        if torch.cuda.is_initialized():
+        if _raw_stream and _current_device and torch.cuda.is_initialized():
             return _raw_stream(_current_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):

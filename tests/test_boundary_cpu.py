@@ -43,6 +43,22 @@ def test_library_exports_every_declared_symbol():
     assert declared == set(fc.EXPORTS)
 
 
+def test_binding_imports_without_torchs_private_stream_lookup(monkeypatch):
+    import importlib.util
+    import torch
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.delattr(torch._C, name, raising=False)
+    spec = importlib.util.spec_from_file_location("binding_of_another_torch", fc.__file__)
+    m = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(m)
+    assert m.fc_window(0, 4, 8, 4, 1) == fc.fc_window(0, 4, 8, 4, 1)
+    # a stream given by the caller needs no lookup, the current one goes through the public interface
+    assert m._stream(17) == 17
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("S", (), {"cuda_stream": 23}))
+    assert m._stream(None) == 23
+
+
 def test_storage_bytes_and_layout_padding():
     c = _cfg()
     spad = 320  # 300 rounded up to a multiple of 64
