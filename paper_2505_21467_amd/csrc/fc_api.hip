@@ -622,8 +622,8 @@ fc_status fc_qkv_project_scatter(fc_cache *cache, int32_t layer, const void *x, 
                                    (hipStream_t)stream);
     else if (fc_project_prefers_gemm(cache->cfg, cache->cfg.batch * A, cache->scratch != nullptr))
         e = fc_launch_project_gemm(G, x, w_qkv, b_qkv, pos, win_start, A, q_out, kl, vl, (hipStream_t)stream);
-    else if (fc_project_mfma_supported(cache->cfg, A))
-        e = fc_launch_project_mfma(G, cache->inv_freq, x, w_qkv, b_qkv, pos, win_start, A, q_out, kl, vl,
+    else if (fc_project_mfma_supported(cache->cfg))
+        e = fc_launch_project_mfma(G, x, w_qkv, b_qkv, pos, win_start, A, q_out, kl, vl,
                                    cache->scratch, (hipStream_t)stream);
     else
         e = fc_launch_project_tile(G, cache->inv_freq, cache->cfg.dtype, x, w_qkv, b_qkv, pos, win_start, A, q_out, kl,

@@ -1,4 +1,4 @@
-// Device-side helpers shared by the kernel files: storage-type conversion and rotary angles.
+// Device-side helpers shared by the kernel files: storage-type conversion, pieces of tensors at any element.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -50,15 +50,4 @@ __device__ __forceinline__ bf16_t fc_from_float<bf16_t>(float f)
     bf16_t r;
     r.bits = fc_bf16_bits(f);
     return r;
-}
-
-// cos and sin of pos * base^(-2 i / Dh).  The angle is formed and reduced to [-pi, pi] in double
-// so that long contexts (pos ~ 1e5 and beyond) lose no accuracy; sin/cos themselves run in float.
-__device__ __forceinline__ void fc_rope_cs(int pos, int i, int Dh, double log_base, float *c, float *s)
-{
-    const double theta = exp(-(2.0 * (double)i / (double)Dh) * log_base);
-    double ang = (double)pos * theta;
-    const double two_pi = 6.283185307179586476925286766559;
-    ang -= two_pi * rint(ang / two_pi);
-    sincosf((float)ang, s, c);
 }

@@ -84,10 +84,10 @@ hipError_t fc_launch_project_tile(const FcGeom &G, const double *inv_freq, int d
 hipError_t fc_launch_attention_tile(const FcGeom &G, const FcAttnPlan &p, int dtype, const void *q, const void *k_layer,
                                     const void *v_layer, const int32_t *pos, int A, int kv_len,
                                     void *out, void *workspace, hipStream_t s);
-bool fc_project_mfma_supported(const fc_config &cfg, int A);
+bool fc_project_mfma_supported(const fc_config &cfg);
 bool fc_project_prefers_gemm(const fc_config &cfg, int M, bool scratch);
 bool fc_project_prefers_tile(const fc_config &cfg, int M);
-hipError_t fc_launch_project_mfma(const FcGeom &G, const double *inv_freq, const void *x, const void *w, const void *bias,
+hipError_t fc_launch_project_mfma(const FcGeom &G, const void *x, const void *w, const void *bias,
                                   const int32_t *pos, int win_start, int A, void *q_out,
                                   void *k_layer, void *v_layer, void *scratch, hipStream_t s);
 bool fc_project_gemm_supported(const fc_config &cfg, int M);

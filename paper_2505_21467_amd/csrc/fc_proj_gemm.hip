@@ -693,14 +693,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 {
     constexpr int PART = 128 * 128, STAGE = 4 * PART;
     extern __shared__ __align__(1024) unsigned char smem[];
-    // workgroup -> (slab pair, row tile, part of the hidden dimension), dealt to the XCDs as in k_proj_gemm
+    // workgroup -> (slab pair, row tile), dealt to the XCDs as in k_proj_gemm
     const int id = blockIdx.x;
     const int xcd = id & 7, qd = id >> 3;
-    const int n_kp = EPI == 3 ? p.ksplit : 1;
-    const int64_t n_tiles = (int64_t)p.n_units * p.n_mt * n_kp;
-    const int tile_k = (int)(xcd * n_tiles / 8) + qd;
-    if (tile_k >= (int)((xcd + 1) * n_tiles / 8)) return;
-    const int tile = tile_k / n_kp, kpart = tile_k - tile * n_kp;
+    const int64_t n_tiles = (int64_t)p.n_units * p.n_mt;
+    const int tile = (int)(xcd * n_tiles / 8) + qd;
+    if (tile >= (int)((xcd + 1) * n_tiles / 8)) return;
     const int unit = tile / p.n_mt, mt = tile - unit * p.n_mt;
     const int m0 = p.m_base + mt * 256;
 
@@ -726,13 +724,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             }
             goff[part][i] = (uint32_t)row * (uint32_t)(p.K * 2) + c * 16;
         }
-    const int all_stages = p.K / 64;
-    const int st0 = EPI == 3 ? (int)((int64_t)kpart * all_stages / p.ksplit) : 0;
-    const int n_stages = EPI == 3 ? (int)(((int64_t)kpart + 1) * all_stages / p.ksplit) - st0 : all_stages;
+    const int n_stages = p.K / 64;
     auto issue = [&](int st, int part) {
         __builtin_amdgcn_sched_barrier(0);
         const uint16_t *mat = (part & 1) == 0 ? p.X : (EPI == 2 && part == 3) ? p.W2 : p.W;
-        const unsigned char *src = (const unsigned char *)mat + (size_t)(st0 + min(st, n_stages - 1)) * 128;
+        const unsigned char *src = (const unsigned char *)mat + (size_t)min(st, n_stages - 1) * 128;
         unsigned char *dst = smem + (st & 1) * STAGE + part * PART + wave * 2048;
 #pragma unroll
         for (int i = 0; i < 2; ++i) load_lds16g(src + goff[part][i], dst + i * 1024);
@@ -780,7 +776,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (hs >= p.slot_base + p.slots_here) return;  // an odd number of slabs leaves the last pair half empty
     if constexpr (EPI == 4) gemm_epilogue_vocab<2>(p, acc, hs, m0 + 64 * wm, lane);
     else gemm_epilogue<4, 2, EPI, false>(p, acc, smem + wave * epi_bytes(4), (const uint16_t *)bias_area + 64 * wn,
-                                         (const uint16_t *)bias_area + 128 + 64 * wn, hs, 0, 0, 4, m0 + 64 * wm, lane, kpart);
+                                         (const uint16_t *)bias_area + 128 + 64 * wn, hs, 0, 0, 4, m0 + 64 * wm, lane, 0);
 }
 
 template <int EPI>
@@ -792,9 +788,9 @@ hipError_t launch_gemm_pp(GemmArgs a, hipStream_t s)
     a.n_units = (a.slots_here + 1) / 2;
     a.n_mt = (a.m_end - a.m_base + 255) / 256;
     if (a.slots_here < 1 || a.n_mt < 1 || a.slot_base < 0 || a.slot_base + a.slots_here > a.n_slots || a.m_base < 0 ||
-        a.m_end > a.M || a.K % 64 != 0 || (EPI == 3 && (a.ksplit < 1 || a.ksplit > a.K / 64)))
+        a.m_end > a.M || a.K % 64 != 0)
         return hipErrorInvalidValue;
-    const int64_t n_tiles = (int64_t)a.n_units * a.n_mt * (EPI == 3 ? a.ksplit : 1);
+    const int64_t n_tiles = (int64_t)a.n_units * a.n_mt;
     if (n_tiles > (1 << 30)) return hipErrorInvalidValue;
     k_gemm_pp<EPI><<<dim3((unsigned)((n_tiles + 7) / 8 * 8)), dim3(512), LDS, s>>>(a);
     return hipGetLastError();
@@ -863,7 +859,9 @@ hipError_t launch_shape(int shape, const GemmArgs &a, hipStream_t s)
         if constexpr (EPI == 4) return hipErrorInvalidValue;
         else if (EPI == 0 && a.K % 128 == 0) return launch_gemm<128, 4, 2, 1, 1, 3, 4, EPI>(a, s);
         else return launch_gemm<64, 4, 2, 1, 1, 4, 4, EPI>(a, s);
-    case 3: return launch_gemm_pp<EPI>(a, s);
+    case 3:
+        if constexpr (EPI == 3) return hipErrorInvalidValue;
+        else return launch_gemm_pp<EPI>(a, s);
     case 4:
         if constexpr (EPI == 0 || EPI == 2) return launch_gemm<64, 8, 5, 2, 2, 3, 0, EPI>(a, s);
         return hipErrorInvalidValue;
@@ -1077,6 +1075,7 @@ FcWidePlan fc_plan_wide(int dtype, int mode, int M, int K, int N)
         if (v >= 0 && v < N_SHAPES && (!shape_half(v) || mode != FC_LIN_VOCAB) && (!shape_dealt(v) || mode == FC_LIN_GATE_UP)) p.shape = v;
         const int ks = fc_knobs().lin_ksplit;
         if (ks >= 1 && ks <= 16 && ks <= K / KS_MIN / 4 && mode == FC_LIN_RESIDUAL) p.ksplit = ks;
+        if (p.shape == 3) p.ksplit = 1;  // (forced: 256 rows x two slabs come in one piece only)
     }
     return p;
 }

@@ -569,9 +569,8 @@ hipError_t launch_mt(const ProjArgs &a, int m_chunks, hipStream_t s)
 
 }  // namespace
 
-bool fc_project_mfma_supported(const fc_config &cfg, int A)
+bool fc_project_mfma_supported(const fc_config &cfg)
 {
-    (void)A;
     return cfg.dtype == FC_BF16 && cfg.head_dim == 128 && cfg.hidden % 128 == 0;
 }
 
@@ -605,7 +604,7 @@ bool fc_project_prefers_tile(const fc_config &cfg, int M)
     return fmax(4.0, 3.2 + 0.032 * mm) < 0.97 * other;
 }
 
-hipError_t fc_launch_project_mfma(const FcGeom &G, const double *inv_freq, const void *x, const void *w, const void *bias,
+hipError_t fc_launch_project_mfma(const FcGeom &G, const void *x, const void *w, const void *bias,
                                   const int32_t *pos, int win_start, int A, void *q_out, void *k_layer,
                                   void *v_layer, void *scratch, hipStream_t s)
 {
@@ -623,7 +622,6 @@ hipError_t fc_launch_project_mfma(const FcGeom &G, const double *inv_freq, const
     a.K = G.d;
     a.win_start = win_start;
     a.n_tiles = (G.Hq + 2 * G.Hkv) * 8;
-    (void)inv_freq;
     a.log2_base_64 = G.log_base * 1.4426950408889634074 / 64.0;
     a.partials = (float *)scratch;
     for (int i = 0; i < 6; ++i) a.rot[i] = exp(-G.log_base * (1 << i) / 64.0);
