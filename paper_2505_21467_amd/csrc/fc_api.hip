@@ -813,18 +813,30 @@ size_t fc_linear_workspace_bytes(int32_t dtype, int32_t M, int32_t K, int32_t N)
 
 // Small bf16 problems run in the tile kernel: it is one launch, and short as long as the products are few, where the
 // tiled GEMM walks the hidden dimension stage by stage in a few workgroups and cuts it only with a second launch, and
-// the slice-wise kernel always has one.  Estimates (us) from 8 .. 300 rows, hidden 256 .. 2048, 256 .. 2048
-// outputs: 74 rows, hidden 1024, 512 outputs 7.6 against 4.4; 8 rows, 2048 x 1024 9.0 against 5.0; 160 rows, 2048 x 1024
-// 9.5 against 13.3.
-static double tile_us(double mm) { return fmax(4.4, 3.2 + 0.027 * mm); }  // mm: million products
+// the slice-wise kernel always has one.  But its waves walk the hidden dimension as a chain, and its workgroups pull X for 16
+// weight rows each.  Both sides measured, weights from HBM (us, tile kernel first):
+//   against the tiled GEMM, 33 .. 256 rows: 1024 x 1024 outputs, 64 rows 4.4 and 6.9, 128 rows 5.4 and 8.1; 2048 x 1024, 64 rows
+//   6.4 and 8.3, 74 rows 9.2 and 8.8; 4096 x 256, 33 rows 9.2 and 8.3; 8192 x 256 16.4 and 11.1: up to hidden 2048, by
+//   products;
+//   against the slice-wise kernel, 1 .. 32 rows, 30 matrices of 0.5 to 68 million weights: 1024 x 512 4.9 and 9.1 at any row
+//   count; 2048 x 8192, 8 / 16 / 32 rows 11.0 and 13.5 / 12.9 and 13.6 / 17.2 and 14.8; 8192 x 1024 12.8 and 10.9 at 4 rows;
+//   18944 x 3584 28.1 and 29.4 at 4 rows, 36 and 30 at 12.  The estimate is wrong by more than 3 % (at most 8) in 4 of 386 measured
+//   cases (by products alone it was wrong in 94, by up to a factor of two).
 static bool linear_prefers_tile(int dtype, int mode, int M, int K, int N, const FcWidePlan &wide, const FcSkinnyPlan &skinny)
 {
     if (dtype != FC_BF16 || fc_knobs().lin_wide_shape >= 0 || fc_knobs().lin_ksplit > 0 || fc_knobs().lin_wgs > 0 ||
         fc_knobs().lin_no_rows)  // tuning knobs name the kernels
         return false;
-    const double mm = (mode == FC_LIN_GATE_UP ? 2e-6 : 1e-6) * M * (double)K * N;
-    if (wide.kind == 1) return tile_us(mm) < 0.97 * (3.5 + 0.0034 * (K < 1024 ? K : 1024));
-    return skinny.kind == 1 && tile_us(mm) < 0.9 * (8.5 + mm / M / 2.5);
+    const bool gated = mode == FC_LIN_GATE_UP;
+    const double weights = (gated ? 2e-6 : 1e-6) * K * (double)N;  // millions
+    if (wide.kind == 1)
+        return K <= 2048 && fmax(4.4, 3.2 + 0.027 * M * weights) < 0.97 * (3.5 + 0.0034 * (K < 1024 ? K : 1024));
+    if (skinny.kind != 1) return false;
+    const int tiles = gated ? (N + 7) / 8 : (N + 15) / 16, passes = M > 16 && tiles < 256 ? 2 : 1;  // over the weights
+    const int wgs = tiles * passes;
+    const double uneven = wgs > 256 ? (double)((wgs + 255) / 256 * 256) / wgs : 1.0, chain = K / 1024.0;
+    const double tile = 3.5 + fmax(1.1 * chain, 0.31 * weights * passes * uneven) + (M - 1) * fmax(0.052 * chain, 0.0125 * weights * uneven);
+    return fmax(4.7, tile) < 0.97 * (8.3 + 0.31 * weights + (M > 16 ? 0.5 : 0.0));
 }
 
 static fc_status linear_common(int32_t dtype, int mode, const void *x, const void *w, const void *w2,

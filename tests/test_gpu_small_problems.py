@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("M,K,N,gated", [
     (8, 1024, 512, False), (32, 2048, 1024, True), (33, 768, 384, False), (74, 512, 520, False), (160, 512, 512, True),
     (75, 1024, 1024, True), (74, 1024, 1024, False), (300, 1024, 1024, False),
+    (4, 2048, 2048, False), (12, 6144, 256, False), (33, 4096, 128, False),  # long chains: the tile kernel only for the first
 ])
 def test_small_linear_layers(M, K, N, gated):
     _linear(M, K, N, gated, "small")
@@ -20,6 +21,7 @@ def test_small_linear_layers(M, K, N, gated):
 
 @pytest.mark.parametrize("B,d,Hq,Hkv,A", [
     (1, 1024, 4, 1, 20), (2, 512, 4, 2, 37), (1, 384, 4, 2, 20), (1, 384, 3, 1, 74), (2, 512, 8, 2, 100), (1, 256, 4, 4, 60),
+    (1, 3072, 2, 1, 9), (1, 5120, 2, 1, 9), (1, 384, 4, 2, 16),  # tile kernel, head-split, neither
 ])
 def test_small_projections(B, d, Hq, Hkv, A):
     print("[case] small projection", B, d, Hq, Hkv, A, flush=True)
