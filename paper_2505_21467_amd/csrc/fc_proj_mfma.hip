@@ -592,16 +592,20 @@ bool fc_project_prefers_gemm(const fc_config &cfg, int M, bool scratch)
     return us > fc_project_gemm_us(slots, M, cfg.hidden);
 }
 
-// Small problems: the tile kernel, by estimate (us; 8 .. 300 rows, hidden 256 .. 1024, 6 .. 12 head slots).  Hidden 512, 12
-// slots, 40 / 74 / 300 rows: tiled GEMM 6.2 / 6.3 / 6.5, tile kernel 4.5 / 5.1 / 9.4; hidden 1024, 20 rows: head-split 8.0,
-// tile kernel 4.5; hidden 256, 8 rows: 3.8 and 3.9.
+// Small problems: the tile kernel, by estimate.  Measured with weights from HBM (us, tile kernel first), hidden 256 .. 8192, 6 .. 48
+// head slots, 1 .. 128 rows: against the tiled GEMM, hidden 512, 12 slots, 48 / 128 rows 5.0 and 5.7 / 6.0 and 5.8;
+// against the head-split kernels, two launches, hidden 1024, 24 slots, 16 / 32 rows 5.0 and 7.6 / 6.6 and 7.8, hidden 2048 6.9 and
+// 9.6 / 10.5 and 10.0; against k_proj_skinny (hidden no multiple of 512), hidden 768, 12 slots 4.9 and 4.3 at 16 rows, 4.9 and 5.3
+// at 24.  A wave's chain along the hidden dimension is what it loses by: 6 slots, 8 rows, hidden 3072 7.5 and 9.2, 5120 10.8
+// and 10.2, 8192 14.6 and 10.1; 48 slots, hidden 2560 13.2 and 11.2.
 bool fc_project_prefers_tile(const fc_config &cfg, int M)
 {
     if (cfg.dtype != FC_BF16 || cfg.head_dim != 128 || fc_knobs().proj_gemm_shape >= 0 || rows_covers(M, cfg.hidden)) return false;
-    const double mm = 128e-6 * M * (double)cfg.hidden * (cfg.n_q_heads + 2 * cfg.n_kv_heads);  // million products
+    const double weights = 128e-6 * (double)cfg.hidden * (cfg.n_q_heads + 2 * cfg.n_kv_heads);  // millions
     const bool skinny = M <= 32 && cfg.hidden % HS_K != 0;
+    if (cfg.hidden > 3072 || weights > 13.0 || (skinny && M <= 16)) return false;
     const double other = skinny ? 3.55 + 0.002 * cfg.hidden : 3.9 + 0.0043 * (cfg.hidden < 1024 ? cfg.hidden : 1024);
-    return fmax(4.0, 3.2 + 0.032 * mm) < 0.97 * other;
+    return fmax(4.0, 3.2 + 0.032 * M * weights) < 0.97 * other;
 }
 
 hipError_t fc_launch_project_mfma(const FcGeom &G, const void *x, const void *w, const void *bias,
