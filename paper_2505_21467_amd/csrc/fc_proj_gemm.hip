@@ -1000,6 +1000,28 @@ hipError_t launch_pieces(GemmArgs a, hipStream_t s)
     return hipSuccess;
 }
 
+// At most 32 rows of a gated layer or a vocabulary: the tiled GEMM streams the weights a little faster than the whole-row
+// kernel (6.3 TB/s instead of 6) where its tiles fill one round of workgroups (vocabulary: or two), and more slowly
+// otherwise; where the weight rows lie 8 KB apart it does so only in half slabs.  Both sides measured, weights from HBM (us at 16 /
+// 32 rows, tiled GEMM first):
+//   gated, hidden 3584: 6400 outputs (200 half slabs) 20.3 and 21.7 / 20.8 and 23.5, 8192 (256) 22.1 and 24.0 / 22.8 and 25.4,
+//   9472 32.1 and 29.2 / 33.1 and 30.7, 12288 (192 slabs) 34.6 and 33.2 / 35.5 and 34.6, 13312 (208) 35.5 and 36.5 / 36.5 and 38.1,
+//   16384 (256) 41.2 and 42.5 / 41.8 and 44.2, 18944 (237 tiles of 80 dealt pairs) 47.5 and 49.7 / 48.5 and 51.3, 22016 63.4 and
+//   59.8 / 66.0 and 62.0;
+//   gated, hidden 4096: 6400 24.3 and 23.8 / 24.8 and 25.9, 8192 30.2 and 33.6 / 30.3 and 33.8, 12288 44.2 and 37.2 / 44.9 and 39.4,
+//   16384 62.6 and 46.3 / 63.2 and 48.7, 18944 66.5 and 55.8 / 67.6 and 58.3;
+//   vocabulary, hidden 3584: 16000 35.0 and 30.1 / 35.3 and 31.6, 32000 (250 slabs) 44.7 and 48.2 / 45.0 and 50.3, 50304 70.5 and
+//   69.3 / 72.6 and 71.2, 65536 (512) 84.0 and 85.2 / 84.0 and 86.4, 152064 188.1 and 184.6 / 189.2 and 186.9; hidden 4096: 32000
+//   63.1 and 55.8 / 63.2 and 58.6, 65536 111.3 and 92.4 / 108.8 and 95.3.
+bool wide_beats_rows(int mode, int M, int K, int64_t slabs)
+{
+    auto in = [](int64_t n, int64_t lo) { return n >= lo && n <= 256; };
+    const bool far = K % 4096 == 0;
+    if (mode == FC_LIN_VOCAB) return !far && (in(slabs, 208) || in(slabs - 256, 208));
+    if (in(tiles_of(10, slabs, M), far ? 240 : 200)) return true;
+    return !far && (in(tiles_of(9, slabs, M), 208) || (slabs > 256 && in(tiles_of(6, slabs, M), 208)));
+}
+
 }  // namespace
 
 // Tiled-GEMM plan of a plain linear layer (host, pure function of the shape); kind 0: not for this kernel.
@@ -1013,27 +1035,18 @@ FcWidePlan fc_plan_wide(int dtype, int mode, int M, int K, int N)
     if (dtype != FC_BF16 || M < 1 || K < 4 * KS_MIN || K % KS_MIN != 0 || N < per_slab || N % per_slab != 0) return p;
     // 32-bit byte offsets inside X and each weight matrix
     if ((int64_t)N * K * 2 >= ((int64_t)1 << 32) || (int64_t)M * K * 2 >= ((int64_t)1 << 32)) return p;
-    // At most 32 rows: only where the estimate beats the whole-row kernel's (weights at 5.94 TB/s, 6 us of launch, X and
-    // last items and 1.2 more for the second 16 rows): a gated W_1 of 18944 outputs at hidden 3584, 32 rows 52.0 and
-    // 48.2 us, a vocabulary of 32000 51.1 and 45.3, of 152064 189.1 and 191.9.
+    // At most 32 rows: gated layers and vocabularies see above.  W_out and W_2 in parts against the slice-wise kernel, which has
+    // a second launch too and pulls a window slice per 128 weight rows: a large matrix, more than 16 rows (us at 24 rows,
+    // tiled GEMM first: 18944 x 3584 30.1 and 31.2, 16384 x 4096 37.0 and 43.1, 8192 x 8192 35.6 and 41.7, 24576 x 4096 41.0 and 42.0;
+    // 16 rows of the first 29.7 and 29.6).  Below the line it is mixed: 16384 x 3584 30.7 and 27.4, 12288 x 4096 25.0 and 25.0,
+    // 12288 x 3584 22.6 and 23.2, 10240 x 5120 24.2 and 26.3.
     if (M <= 32) {
         const FcSkinnyPlan rows = fc_plan_skinny(dtype, mode, M, K, N);
         const bool knob = fc_knobs().lin_wide_shape >= 6;
         if (!knob && (fc_knobs().lin_wgs > 0 || fc_knobs().lin_no_rows)) return p;  // tuning knobs of the streaming kernels
-        if (mode == FC_LIN_RESIDUAL) {
-            // In parts against the slice-wise kernel, which has a second launch too and pulls a window slice per 128 rows: a
-            // large matrix, more than 16 rows (32 x 18944 x 3584 32.5 and 30.2 us, 16 rows 29.9 and 29.7; half the
-            // matrix: equal).
-            if (!knob && !(rows.kind == 1 && M > 16 && (double)K * N >= 60e6)) return p;
-        } else {
-            if (!knob && (rows.kind != 2 || K < 2048)) return p;
-            GemmPiece pc[2];
-            const int n = plan_pieces(N / per_slab, M, K, mode != FC_LIN_VOCAB, mode == FC_LIN_GATE_UP, pc);
-            double us = n == 2 ? 7.0 : 4.0;
-            for (int i = 0; i < n; ++i) us += launch_cost(pc[i].shape, pc[i].slots, pc[i].m_end - pc[i].m_base) * (K / 64);
-            const double bytes = (mode == FC_LIN_GATE_UP ? 4.0 : 2.0) * K * (double)N;
-            if (!knob && us > bytes / 5.94e6 + (M > 16 ? 7.2 : 6.0)) return p;
-        }
+        if (!knob && !(mode == FC_LIN_RESIDUAL ? rows.kind == 1 && M > 16 && (double)K * N >= 60e6
+                                               : rows.kind == 2 && K >= 2048 && wide_beats_rows(mode, M, K, N / per_slab)))
+            return p;
     }
     p.kind = 1;
     const int64_t units = N / per_slab, t256 = (M + 255) / 256, t128 = (M + 127) / 128;

@@ -64,6 +64,20 @@ def test_few_row_tiles(shape, M, K, N, knob):
         _check_lm_head("bf16", x, w, "vocabulary, shape 9")
 
 
+@pytest.mark.parametrize("M,K,N", [(16, 4096, 7680), (16, 4096, 7616), (32, 3584, 6400), (9, 3584, 13312)])
+def test_few_rows_gated_on_both_sides_of_the_line(M, K, N):
+    """Tiled GEMM in half slabs (240 of them), whole-row kernel (238), half slabs (200), slabs (208)."""
+    _linear(M, K, N, True, "gated, few rows")
+
+
+@pytest.mark.parametrize("V", [26624, 26496])
+def test_few_rows_vocabulary_on_both_sides_of_the_line(V):
+    """208 slabs: tiled GEMM; 207: whole-row kernel."""
+    print("[case] vocabulary", V, flush=True)
+    x, w = inputs.normal(23, "x", (5, 3584), 1.0, "bf16"), inputs.normal(23, "w", (V, 3584), 0.03, "bf16")
+    _check_lm_head("bf16", x, w, "vocabulary of %d" % V)
+
+
 @pytest.mark.parametrize("shape", [6, 7, 8, 9, 10])
 @pytest.mark.parametrize("B,d,Hq,Hkv,A", [(3, 192, 8, 2, 23), (1, 64, 3, 1, 65), (2, 320, 4, 4, 160)])
 def test_few_row_tiles_projection(shape, B, d, Hq, Hkv, A, knob):
