@@ -62,12 +62,12 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # HBM bytes per launch of the attention call (main kernel + merge kernel) on the default workload,
 # from `rocprofv3 --pmc FETCH_SIZE` / `--pmc WRITE_SIZE` runs of this command, scaled by what the same
 # counters read for the plain 256 MiB copy at the end of this file (profiles/ holds the summary).
-# HBM bytes per launch of the gated W_1 at 32 rows and the 7B widths (k_linear_rows), same method
-# (profiles/c4_whole_layer_step.md): 273.8 MB fetched + 3.1 MB written.
-MEASURED_GATE_UP_TRAFFIC_BYTES = {(32, 3584, 18944): 274_990_000}
+# HBM bytes per launch of the gated W_1 at 32 rows and the 7B widths (k_proj_gemm, 64 rows x 80 dealt pairs), same
+# method (profiles/c4_whole_layer_step.md): 273.53 MB fetched + 1.21 MB written.
+MEASURED_GATE_UP_TRAFFIC_BYTES = {(32, 3584, 18944): 274_740_000}
 
-# The vocabulary projection of 32 rows (k_linear_rows, profiles/unmask_step.md): 1091.94 MB fetched, 0.1 MB written.
-MEASURED_LM_HEAD_TRAFFIC_BYTES = {(32, 3584, 152064): 1_092_040_000}
+# The vocabulary projection of 32 rows (k_linear_rows, profiles/unmask_step.md): 1092.05 MB fetched, 0.1 MB written.
+MEASURED_LM_HEAD_TRAFFIC_BYTES = {(32, 3584, 152064): 1_092_150_000}
 
 # HBM bytes per launch of the attention call (main kernel + merge kernel), from `rocprofv3 --pmc
 # FETCH_SIZE` / `--pmc WRITE_SIZE` runs of this command, scaled by what the same counters read for the
@@ -530,7 +530,8 @@ def main_layer(args, torch, fc, inputs, dev):
                 "frac": round(gate_flops / us_gate * 1e-6 / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": None,
                 "algorithmic_flops_per_launch": gate_flops, "us_per_launch": round(us_gate, 3)}
     else:
-        roof = {"kernel": "fc_ffn_gate_up (%s)" % ("k_linear_rows" if M <= 32 else
+        # (of the geometries here the whole-row kernel takes short windows of hidden 4096 only)
+        roof = {"kernel": "fc_ffn_gate_up (%s)" % ("k_linear_rows" if M <= 32 and d == 4096 else
                                                    "k_proj_gemm, SiLU-gate epilogue"), "bound": "hbm",
                 "achieved": gbs(w_bytes["gate_up"], us_gate), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(w_bytes["gate_up"] / us_gate * 1e-3 / HBM_PEAK_GBS, 4),

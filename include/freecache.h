@@ -81,7 +81,7 @@ const char *fc_last_error(void);
  * value NULL restores the default.  Names: FC_ATTN_TILES ("R,W": row tiles and waves per attention
  * workgroup), FC_ATTN_WGS, FC_LIN_WGS, FC_ACCEPT_WGS (target workgroup counts), FC_LIN_NO_ROWS,
  * FC_GEMM_NO_SPLIT, FC_PROJ_NO_HEADSPLIT (any value switches the named path off), FC_LIN_WIDE_SHAPE,
- * FC_PROJ_GEMM_SHAPE (one GEMM tile shape for everything), FC_LIN_KSPLIT (parts of the hidden
+ * FC_PROJ_GEMM_SHAPE (0..10: one GEMM tile shape for everything), FC_LIN_KSPLIT (parts of the hidden
  * dimension).  Host only; not thread-safe against concurrent calls into the library; workspace sizes
  * depend on the knobs, so query them after setting.
  * Errors: INVALID_ARG (NULL or unknown name). */
@@ -172,7 +172,8 @@ size_t fc_workspace_bytes(const fc_config *cfg, int32_t max_rows);
 /* The launch plan fc_active_attention would use for a window of A rows over kv_len cached rows with
  * fc_workspace_bytes(cfg, A) bytes of workspace (host, pure function of the shape and the tuning knobs; for reports and for tying a measured HBM
  * traffic figure to the plan it was measured with):
- *   plan[0] kind (0 fp32 / head_dim 64 kernel, 1 bf16 head_dim 128 kernel)   plan[1] key ranges (splits)
+ *   plan[0] kind (0 tile kernel: fp32, head_dim 64, and bf16 of head_dim 128 over short keys;
+ *           1 split-KV kernel: bf16 of head_dim 128)   plan[1] key ranges (splits)
  *   plan[2] keys per split   plan[3] 32-row (kind 0: 16-row) tiles per (sequence, kv head)
  *   plan[4] row tiles per workgroup   plan[5] waves per workgroup
  * Errors: INVALID_ARG, UNSUPPORTED (config), BOUNDS (kv_len). */

@@ -10,7 +10,7 @@
 
 // Launch plan of the split-KV attention (host, pure function of the shape).
 struct FcAttnPlan {
-    int kind;            // 0 = fp32 / head_dim 64 kernel, 1 = bf16 head_dim 128 split-KV
+    int kind;            // 0 = tile kernel (fp32, head_dim 64, bf16 head_dim 128 over short keys), 1 = bf16 head_dim 128 split-KV
     int splits;          // key ranges per (sequence, kv head); every one is non-empty
     int keys_per_split;  // multiple of 64 (kind 0: of 32)
     int row_tiles;       // 32-row (kind 0: 16-row) tiles of the flattened (head-in-group, a) rows per (b, kv head)
@@ -166,7 +166,7 @@ hipError_t fc_launch_unmask_select(const int32_t *tok, const float *conf, const 
 // Tiled-GEMM plan of the same linear layers on more than 32 rows.
 struct FcWidePlan {
     int kind;    // 0 = not covered, 1 = tiled GEMM
-    int shape;   // tile shape where ksplit > 1 or a tuning knob forces one (0: 256 rows x slab, 1: 128 rows x slab, 2: 128 rows x half slab, 3: 256 rows x two slabs)
+    int shape;   // tile shape where ksplit > 1 or a tuning knob forces one (numbered in fc_proj_gemm.hip)
     int ksplit;  // parts of the hidden dimension (1 = epilogue inside the GEMM, no workspace)
 };
 FcWidePlan fc_plan_wide(int dtype, int mode, int M, int K, int N);

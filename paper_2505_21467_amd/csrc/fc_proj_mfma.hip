@@ -348,7 +348,8 @@ __global__ __launch_bounds__(64) void k_proj_finish(ProjArgs p)
 }
 
 // -------------------------------------------------------------------------------------------------
-// Whole-row kernel for windows of at most 32 rows and hidden sizes of 512, 3584 and 4096 (the window rows fit in registers).
+// Whole-row kernel for windows of at most 32 rows at the hidden sizes it was measured at, 512, 3584 and 4096.  The window rows
+// would fit in registers at every multiple of 256 up to 4096; at other sizes the kernels above run.
 //
 // Every workgroup owns an equal run of rotary pairs (rows i and i + 64 of a head; 9 pairs at 36 head slots) and takes
 // them in items of 8 NF pairs over the whole hidden dimension, so no partial tiles leave the workgroup: its eight
