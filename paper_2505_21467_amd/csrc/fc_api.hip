@@ -344,10 +344,10 @@ FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len, size_t cap
             }
         }
     }
-    const int row_tiles = (g * A + 15) / 16;
+    const int64_t row_tiles = ((int64_t)g * A + 15) / 16;
     if (kv_len <= 1200 && pairs * row_tiles <= 256 && attn_tile_cost(pairs * row_tiles, ((int64_t)kv_len + 31) / 32, 16384) < best) {
         p.kind = 0;
-        p.row_tiles = row_tiles;
+        p.row_tiles = (int)row_tiles;
         p.tiles_per_wg = 1;
         p.waves = 8;
         p.splits = 1;

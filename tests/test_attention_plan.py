@@ -29,6 +29,12 @@ def test_plans_cover_the_keys_and_fit_the_workspace():
             assert need <= space, (a, kv, p, need, space)
 
 
+def test_window_rows_times_heads_beyond_32_bits():
+    c = fc.make_config(1, 1, 256, 256, 1, 128, 100, "bf16")
+    p = fc.fc_attention_plan(c, 1 << 24, 100)  # 2^32 query rows: the split-KV kernel, not a tile kernel of no tiles
+    assert p["kind"] == 1 and p["row_tiles"] == 1 << 27
+
+
 def _required(pairs, g, A, kv):
     """Partial results (bytes) of one round of workgroups, tiles by the row count: what a bf16 call must bring."""
     tiles, by_len = -(-g * A // 32), max(1, -(-kv // 64) // 2)
