@@ -28,6 +28,8 @@
 #include <math.h>
 #include <string.h>
 
+#include <type_traits>
+
 #include "fc_device.h"
 #include "fc_internal.h"
 
@@ -50,6 +52,7 @@ struct GemmArgs {
     int M, A, K, win_start;
     int n_mt;              // row tiles of 32 * NW window rows
     int n_units;           // head slots (NSUB = 4) or half-head slots (NSUB = 2)
+    uint32_t rot_step;     // ROTATE: stages / n_units in 1/65536
     int n_slots;           // 128-row slabs of W: head slots (EPI 0), N / 128 (EPI 1, 3), d_ff / 64 (EPI 2)
     // The part of the problem this launch covers (a problem may be cut into two launches with different
     // tile shapes, see launch_pieces): slabs [slot_base, slot_base + slots_here), rows [m_base, m_end).
@@ -347,7 +350,7 @@ __device__ __forceinline__ void gemm_epilogue_vocab(const GemmArgs &p, const f32
 // (the parts are tiles of their own), for matrices with too few slabs to fill the chip; 4 = vocabulary projection of the
 // unmasking step: of the 128 logits of a slab only the largest, its index and the sum of
 // exp(logit - largest) are kept per row (NSUB = 4 only).
-template <int KS, int NW, int NSUB, int MW, int NG, int SLOTS, int NL, int EPI>
+template <int KS, int NW, int NSUB, int MW, int NG, int SLOTS, int NL, int EPI, bool ROTATE>
 __global__ __launch_bounds__((NW + NL) * 64) void k_proj_gemm(GemmArgs p)
 {
     constexpr int ROWB = KS * 2;               // bytes of one row piece: 128 or 256
@@ -452,7 +455,17 @@ __global__ __launch_bounds__((NW + NL) * 64) void k_proj_gemm(GemmArgs p)
     const int all_stages = p.K / KS;
     const int st0 = EPI == 3 ? (int)((int64_t)kpart * all_stages / p.ksplit) : 0;
     const int n_stages = EPI == 3 ? (int)(((int64_t)kpart + 1) * all_stages / p.ksplit) - st0 : all_stages;
+    // Rows of W that lie a multiple of 4 KB apart: workgroup `unit` starts unit / n_units of the way along the hidden
+    // dimension and goes round.  In step, all workgroups ask for the same 128 bytes of all those rows, and these share a few
+    // memory channels.  One row tile of up to 128 rows, us without and with: gated 4096 x 12288, 64 / 128 rows 47.1 and
+    // 35.8 / 49.0 and 41.3; 4096 x 14336 53.2 and 41.7 / 55.9 and 47.9; 2048 x 16384, 48 rows 34.0 and 26.0; 6144 x 16384 90 and 70;
+    // 8192 x 8192 60 and 45; vocabulary 4096 x 32000, 64 rows 64.6 and 49.6; projection, 96 slots, hidden 4096, 64 rows 27.3
+    // and 24.9.  At other distances it gives nothing or costs (hidden 5120 34.6 and 35.6, 7168 44.1 and 45.7, 1024 15.0 and
+    // 15.3), and so it does with more row tiles, whose window rows then come from L2 at two places at a time (256 rows of
+    // gated 4096 x 12288 66.9 and 70.3).
+    const int rot = ROTATE ? (int)(((uint32_t)unit * p.rot_step) >> 16) : 0;
     auto issue_stage = [&](int st, int part) {
+        const int sr = st + rot, at = st0 + (ROTATE && sr >= n_stages ? sr - n_stages : sr);
         unsigned char *dst = smem + (st % SLOTS) * STAGE;
 #pragma unroll
         for (int i = 0; i < LBW; ++i) {
@@ -468,7 +481,7 @@ __global__ __launch_bounds__((NW + NL) * 64) void k_proj_gemm(GemmArgs p)
                 const bool up = EPI == 2 && RPB * (lw + NLW * i) >= (NSUB == 4 ? 64 : 32);
                 mat = up ? p.W2 : p.W;
             }
-            const unsigned char *src = (const unsigned char *)mat + (size_t)(st0 + st) * ROWB;
+            const unsigned char *src = (const unsigned char *)mat + (size_t)at * ROWB;
             load_lds16g(src + goff[i], dst + (lw + NLW * i) * 1024);
         }
     };
@@ -803,9 +816,6 @@ hipError_t launch_gemm(GemmArgs a, hipStream_t s)
     constexpr bool DEALT = NSUB == 5 || NSUB == 3;
     constexpr int LDS = SLOTS * ((DEALT ? 32 * NSUB : 32 * NSUB * NG) + XROWS) * KS * 2 + (EPI == 0 ? BIAS_LDS : 0);
     static_assert(LDS <= 160 * 1024, "LDS ring too large");
-    static hipError_t attr = hipFuncSetAttribute((const void *)k_proj_gemm<KS, NW, NSUB, MW, NG, SLOTS, NL, EPI>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-    if (attr != hipSuccess) return attr;
     const int slots = a.slots_here;
     a.n_units = DEALT ? (a.n_slots * 64 + 16 * NSUB - 1) / (16 * NSUB) : NSUB == 4 ? (slots + NG - 1) / NG : 2 * slots;
     if (DEALT && (a.slot_base != 0 || slots != a.n_slots)) return hipErrorInvalidValue;  // dealt pairs cover every slab
@@ -815,8 +825,19 @@ hipError_t launch_gemm(GemmArgs a, hipStream_t s)
     const int64_t n_tiles = (int64_t)a.n_units * a.n_mt * (EPI == 3 ? a.ksplit : 1);
     if (n_tiles > (1 << 30) || (EPI == 3 && a.ksplit < 1)) return hipErrorInvalidValue;
     const unsigned grid = (unsigned)((n_tiles + 7) / 8 * 8);
-    k_proj_gemm<KS, NW, NSUB, MW, NG, SLOTS, NL, EPI><<<dim3(grid), dim3((NW + NL) * 64), LDS, s>>>(a);
-    return hipGetLastError();
+    auto start = [&](auto rotate) {
+        constexpr auto kernel = k_proj_gemm<KS, NW, NSUB, MW, NG, SLOTS, NL, EPI, decltype(rotate)::value>;
+        static hipError_t attr = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        if (attr != hipSuccess) return attr;
+        kernel<<<dim3(grid), dim3((NW + NL) * 64), LDS, s>>>(a);
+        return hipGetLastError();
+    };
+    if constexpr (XROWS <= 128 && EPI != 3)
+        if (a.n_mt == 1 && a.K % 2048 == 0 && a.K / KS < 65536) {
+            a.rot_step = (uint32_t)(((int64_t)(a.K / KS) << 16) / a.n_units);  // (unit * rot_step stays below 2^32)
+            return start(std::true_type());
+        }
+    return start(std::false_type());
 }
 
 // Sum of the hidden-dimension parts of an EPI 3 launch + residual, four outputs per thread.
@@ -898,6 +919,10 @@ hipError_t launch_shape(int shape, const GemmArgs &a, hipStream_t s)
 // 67.5 / 81.6 us, now 50.4 / 58.3 (the weights alone 46 at 5.9 TB/s).
 constexpr int N_SHAPES = 11;
 constexpr double ROUND_US[N_SHAPES] = {1.03, 0.62, 0.39, 1.84, 1.30, 0.54, 0.75, 0.53, 0.95, 0.52, 0.34};
+// The same for up to one round of one row tile of the 64-row shapes (6, 7, 9, 10), where a workgroup's own pull counts and not how many there are:
+// line 0.85 + 0.15 x (gated hidden 3584, 32 rows, us per stage: shape 7 with 134 / 198 tiles 0.40 / 0.435, shape 9 with 100 / 148
+// 0.50 / 0.53, shape 6 with 80 / 119 0.54 / 0.57, shape 10 with 72 / 200 0.30 / 0.32).
+constexpr double SINGLE_US[N_SHAPES] = {0, 0, 0, 0, 0, 0, 0.60, 0.45, 0, 0.55, 0.33};
 constexpr bool shape_dealt(int shape) { return shape >= 4 && shape <= 8; }
 constexpr bool shape_half(int shape) { return shape == 2 || shape == 10; }
 
@@ -925,7 +950,8 @@ int64_t tiles_of(int shape, int64_t slots, int64_t rows)
 double launch_cost(int shape, int64_t slots, int64_t rows)
 {
     const int64_t n = tiles_of(shape, slots, rows), part = n % 256;
-    const double tiles = ROUND_US[shape] * ((double)(n / 256) + (part ? 0.6 + 0.4 * part / 256.0 : 0.0));
+    const double tiles = SINGLE_US[shape] > 0 && rows <= 64 && n <= 256 ? SINGLE_US[shape] * (0.85 + 0.15 * n / 256.0)
+                                                          : ROUND_US[shape] * ((double)(n / 256) + (part ? 0.6 + 0.4 * part / 256.0 : 0.0));
     const double weights = (double)slots * 128 * 128 / 5.8e6;
     return (tiles > weights ? tiles : weights) + 0.02 * tiles;  // (equally bound by the weights: the smaller tiles)
 }
@@ -1001,25 +1027,25 @@ hipError_t launch_pieces(GemmArgs a, hipStream_t s)
 }
 
 // At most 32 rows of a gated layer or a vocabulary: the tiled GEMM streams the weights a little faster than the whole-row
-// kernel (6.3 TB/s instead of 6) where its tiles fill one round of workgroups (vocabulary: or two), and more slowly
-// otherwise; where the weight rows lie 8 KB apart it does so only in half slabs.  Both sides measured, weights from HBM (us at 16 /
-// 32 rows, tiled GEMM first):
+// kernel (6.3 TB/s instead of 6) where its tiles fill one round of workgroups (vocabulary: or two), and more slowly otherwise.  Both sides measured, weights from HBM (us at 16 / 32 rows, tiled GEMM first):
 //   gated, hidden 3584: 6400 outputs (200 half slabs) 20.3 and 21.7 / 20.8 and 23.5, 8192 (256) 22.1 and 24.0 / 22.8 and 25.4,
-//   9472 32.1 and 29.2 / 33.1 and 30.7, 12288 (192 slabs) 34.6 and 33.2 / 35.5 and 34.6, 13312 (208) 35.5 and 36.5 / 36.5 and 38.1,
-//   16384 (256) 41.2 and 42.5 / 41.8 and 44.2, 18944 (237 tiles of 80 dealt pairs) 47.5 and 49.7 / 48.5 and 51.3, 22016 63.4 and
-//   59.8 / 66.0 and 62.0;
-//   gated, hidden 4096: 6400 24.3 and 23.8 / 24.8 and 25.9, 8192 30.2 and 33.6 / 30.3 and 33.8, 12288 44.2 and 37.2 / 44.9 and 39.4,
-//   16384 62.6 and 46.3 / 63.2 and 48.7, 18944 66.5 and 55.8 / 67.6 and 58.3;
+//   9472 (198 tiles of 48 dealt pairs) 26.3 and 29.1 / 27.4 and 31.0, 12288 (256) 32.3 and 33.2 / 32.7 and 34.7, 13312 (208 slabs)
+//   35.5 and 36.5 / 36.5 and 38.1, 16384 (256) 41.2 and 42.5 / 41.8 and 44.2, 18944 (237 tiles of 80 dealt pairs) 47.5 and 49.7 /
+//   48.5 and 51.3, 22016 63.4 and 59.8 / 66.0 and 62.0;
+//   gated, hidden 4096: 6400 23.2 and 24.1 / 23.8 and 26.2, 8192 24.2 and 33.6 / 24.3 and 33.8, 11008 (230 tiles of 48) 32.1 and 36.5 /
+//   32.4 and 38.5, 12288 35.5 and 37.9 / 35.8 and 40.2, 14336 41.0 and 42.7 / 41.7 and 45.4, 16384 47.3 and 46.1 / 47.6 and 49.1, 18944
+//   52.8 and 56.0 / 53.7 and 58.7, 22016 71.3 and 68.7 / 73.7 and 70.7;
 //   vocabulary, hidden 3584: 16000 35.0 and 30.1 / 35.3 and 31.6, 32000 (250 slabs) 44.7 and 48.2 / 45.0 and 50.3, 50304 70.5 and
-//   69.3 / 72.6 and 71.2, 65536 (512) 84.0 and 85.2 / 84.0 and 86.4, 152064 188.1 and 184.6 / 189.2 and 186.9; hidden 4096: 32000
-//   63.1 and 55.8 / 63.2 and 58.6, 65536 111.3 and 92.4 / 108.8 and 95.3.
+//   69.3 / 72.6 and 71.2, 65536 (512) 84.0 and 85.2 / 84.0 and 86.4, 152064 188.1 and 184.6 / 189.2 and 186.9; hidden 4096: 16000 38.5
+//   and 34.1 / 39.1 and 36.5, 32000 49.0 and 56.8 / 48.7 and 59.9, 65536 92.2 and 93.2 / 92.4 and 94.3, 152064 215 and 203 / 216 and 210
+//   (two rounds there gain 2 % and would ask for a larger workspace than the whole-row kernel: left to it).
 bool wide_beats_rows(int mode, int M, int K, int64_t slabs)
 {
     auto in = [](int64_t n, int64_t lo) { return n >= lo && n <= 256; };
-    const bool far = K % 4096 == 0;
-    if (mode == FC_LIN_VOCAB) return !far && (in(slabs, 208) || in(slabs - 256, 208));
-    if (in(tiles_of(10, slabs, M), far ? 240 : 200)) return true;
-    return !far && (in(tiles_of(9, slabs, M), 208) || (slabs > 256 && in(tiles_of(6, slabs, M), 208)));
+    if (mode == FC_LIN_VOCAB) return in(slabs, 208) || (K % 4096 != 0 && in(slabs - 256, 208));
+    const int64_t pairs48 = tiles_of(7, slabs, M);
+    return in(tiles_of(10, slabs, M), 200) || in(tiles_of(9, slabs, M), 208) || in(pairs48, 192) ||
+           (slabs > 256 && in(tiles_of(6, slabs, M), 208));
 }
 
 }  // namespace

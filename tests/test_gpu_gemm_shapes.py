@@ -66,8 +66,28 @@ def test_few_row_tiles(shape, M, K, N, knob):
 
 @pytest.mark.parametrize("M,K,N", [(16, 4096, 7680), (16, 4096, 7616), (32, 3584, 6400), (9, 3584, 13312)])
 def test_few_rows_gated_on_both_sides_of_the_line(M, K, N):
-    """Tiled GEMM in half slabs (240 of them), whole-row kernel (238), half slabs (200), slabs (208)."""
+    """Tiled GEMM in half slabs (240, 238 and 200 of them), slabs (208)."""
     _linear(M, K, N, True, "gated, few rows")
+
+
+@pytest.mark.parametrize("K,N", [(3584, 9216), (3584, 9152), (4096, 6400), (4096, 6336)])
+def test_few_rows_gated_by_dealt_pairs_and_at_hidden_4096(K, N):
+    """192 tiles of 48 dealt pairs: tiled GEMM, 191: whole-row kernel; 200 half slabs: tiled GEMM, 198: whole-row kernel."""
+    _linear(11, K, N, True, "gated, few rows")
+
+
+@pytest.mark.parametrize("shape", [1, 2, 5, 6, 7, 8, 9, 10])
+@pytest.mark.parametrize("M,K,N", [(33, 2048, 128), (64, 2048, 1152), (61, 4096, 384), (128, 2048, 640)])
+def test_start_along_the_hidden_dimension(shape, M, K, N, knob):
+    """Weight rows a multiple of 4 KB apart: each workgroup starts at a stage of its own (one row tile), one unit and several,
+    fewer and more units than stages."""
+    knob("FC_LIN_WIDE_SHAPE", str(shape))
+    _linear(M, K, N, True, "gated, shape %d" % shape)
+    if shape < 5 or shape >= 9:
+        _linear(M, K, N, False, "linear, shape %d" % shape)
+    if shape in (1, 9):
+        x, w = inputs.normal(24, "x", (M, K), 1.0, "bf16"), inputs.normal(24, "w", (N, K), 0.01, "bf16")
+        _check_lm_head("bf16", x, w, "vocabulary, shape %d" % shape)
 
 
 @pytest.mark.parametrize("V", [26624, 26496])
@@ -79,7 +99,7 @@ def test_few_rows_vocabulary_on_both_sides_of_the_line(V):
 
 
 @pytest.mark.parametrize("shape", [6, 7, 8, 9, 10])
-@pytest.mark.parametrize("B,d,Hq,Hkv,A", [(3, 192, 8, 2, 23), (1, 64, 3, 1, 65), (2, 320, 4, 4, 160)])
+@pytest.mark.parametrize("B,d,Hq,Hkv,A", [(3, 192, 8, 2, 23), (1, 64, 3, 1, 65), (2, 320, 4, 4, 160), (1, 2048, 4, 2, 63)])
 def test_few_row_tiles_projection(shape, B, d, Hq, Hkv, A, knob):
     print("[case] projection, shape", shape, B, d, Hq, Hkv, A, flush=True)
     knob("FC_PROJ_GEMM_SHAPE", str(shape))
