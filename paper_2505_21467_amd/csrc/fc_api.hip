@@ -187,16 +187,38 @@ double attn_cost(const AttnShape &sh, int64_t pairs, int row_tiles, int kv_len, 
 // The same for the tile kernel: `wgs` workgroups (at most 256: one round), one per sequence, kv head, 16 query rows and key
 // range, each over `groups` groups of 32 keys of `group_bytes` bytes.  What counts is what one compute unit can pull from
 // HBM, some 35 B/ns; with up to 64 / 128 workgroups the head dimension of V is cut in four / two (the launch does that).
-// Fitted to 130 bf16 shapes of head_dim 128, 60 .. 1160 keys, one range (rms error 3 .. 5 %), and used for them in that
-// range; fp32 and head_dim 64 follow it by their bytes.  Up to some 600 keys (64 workgroups) or 300 (256) it
-// beats every plan of the kernel above, whose stages, split partials and merge are made for long keys: 32 rows x
-// 28 query heads, 96 / 250 / 480 keys 8.8 / 9.5 / 10.3 us, tile kernel 4.6 / 5.8 / 8.0.
+// Fitted to 130 bf16 shapes of head_dim 128, 60 .. 1160 keys, one range (rms error 3 .. 5 %); fp32 and head_dim 64 follow it
+// by their bytes.
 double attn_tile_cost(int64_t wgs, int64_t groups, int64_t group_bytes)
 {
     const double g = (double)groups * (double)group_bytes / 16384.0;
     if (wgs <= 64) return 3.58 + 0.275 * g;
     if (wgs <= 128) return 3.92 + 0.341 * g;
     return 4.28 + (0.229 + 1.18e-3 * (double)wgs) * g;
+}
+
+// k_attn_groups: 16-row tiles of a workgroup, parts of the columns of V, waves, and its time (us) in up to one round of
+// workgroups: start + h (group + load x) for h groups of 32 keys per wave and x of the compute units in use, or the
+// stream from HBM, the longer of the two and a fifth of the shorter.  Fitted to 1380 measured (shape, workgroup) pairs (1 .. 8
+// sequences, 1 .. 32 kv heads, 4 .. 64 rows, 64 .. 4500 keys; rms error 6 .. 9 %).  Best of these against the best plan of the split-KV
+// kernel and the tile kernel, 880 drawn shapes: faster in 700 of them, by 1.34 x in the geometric mean: 28 / 4 heads, 32 rows,
+// 256 / 480 / 768 / 1056 keys 4.7 and 5.6 / 5.3 and 7.5 / 5.7 and 9.4 / 6.8 and 10.2; 64 rows, 1056 keys 7.5 and 11.1; 3 x 19 rows,
+// 1581 keys 9.6 and 12.1.  The estimates choose within 1 % of the best in the mean.
+struct GroupsShape {
+    int tiles, v_parts, waves;
+    double start, start_x, group, load;
+};
+const GroupsShape GROUPS_SHAPES[] = {{1, 4, 8, 3.25, 0.0, 0.69, 0.105},
+                                     {1, 2, 8, 3.05, 0.0, 0.85, 0.125},
+                                     {1, 1, 6, 3.04, 0.22, 0.92, 0.09},
+                                     {2, 2, 8, 3.80, 0.1, 1.04, 0.21}};
+double attn_groups_cost(const GroupsShape &sh, int64_t pairs, int64_t wgs, int kv_len)
+{
+    const int64_t stages = ((int64_t)kv_len + 63) / 64, n = (stages + sh.waves - 1) / sh.waves;
+    const bool half = (kv_len + 31) / 32 % 2 && stages % sh.waves == 1;  // only one wave has n stages, and half of the last
+    const double x = (double)wgs / 256.0, work = (double)(2 * n - half) * (sh.group + sh.load * x);
+    const double hbm = (double)pairs * kv_len * 512.0 / 5.73e6;
+    return sh.start + sh.start_x * x + fmax(work, hbm) + 0.19 * fmin(work, hbm);
 }
 
 // Most key ranges the planner considers for this many row tiles: one round of workgroups in some shape, or about 32 MB
@@ -344,15 +366,32 @@ FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len, size_t cap
             }
         }
     }
+    // one launch: 16 or 32 rows per workgroup, or (short keys only) the tile kernel
     const int64_t row_tiles = ((int64_t)g * A + 15) / 16;
-    if (kv_len <= 1200 && pairs * row_tiles <= 256 && attn_tile_cost(pairs * row_tiles, ((int64_t)kv_len + 31) / 32, 16384) < best) {
-        p.kind = 0;
-        p.row_tiles = (int)row_tiles;
-        p.tiles_per_wg = 1;
-        p.waves = 8;
+    auto one_launch = [&](int tiles, int v_parts, int waves) {
+        const bool tile = tiles == 1 && kv_len <= 1200;
+        p.kind = tile ? 0 : 2;
         p.splits = 1;
-        p.keys_per_split = (kv_len + 31) / 32 * 32;
+        p.keys_per_split = tile ? (kv_len + 31) / 32 * 32 : (int)(n_stages * 64);
+        p.row_tiles = (int)(tile ? row_tiles : (row_tiles + 1) / 2);
+        p.tiles_per_wg = tile ? 1 : 2 * tiles;
+        p.waves = waves;
+        p.group_tiles = v_parts ? tiles : 0;
+        p.v_parts = v_parts;
+    };
+    if (pairs * row_tiles > 512) return p;
+    for (const GroupsShape &sh : GROUPS_SHAPES) {
+        const int64_t wgs = pairs * ((row_tiles + sh.tiles - 1) / sh.tiles) * sh.v_parts;
+        if (wgs > 256 || (sh.waves == 6 && kv_len > 1200)) continue;
+        const double t = attn_groups_cost(sh, pairs, wgs, kv_len);
+        if (t < best) {
+            best = t;
+            one_launch(sh.tiles, sh.v_parts, sh.waves);
+        }
     }
+    // (32 rows x 28 heads, 32 / 64 keys 4.0 and 4.7 us; from 100 keys on the same or slower)
+    if (kv_len <= 96 && pairs * row_tiles <= 256 && attn_tile_cost(pairs * row_tiles, ((int64_t)kv_len + 31) / 32, 16384) < best)
+        one_launch(1, 0, 8);
     return p;
 }
 
@@ -645,7 +684,7 @@ static fc_status run_attention(fc_cache *cache, int32_t layer, const FcAttnPlan 
         return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", bytes, space);
     const FcGeom G = geom_of(cache);
     void *kl = layer_ptr(cache, cache->k, layer), *vl = layer_ptr(cache, cache->v, layer);
-    hipError_t e = plan.kind == 1
+    hipError_t e = plan.kind >= 1 || plan.group_tiles > 0
                        ? fc_launch_attention_mfma(G, plan, q, kl, vl, pos, A, kv_len, out, workspace,
                                                   (hipStream_t)stream)
                        : fc_launch_attention_tile(G, plan, cache->cfg.dtype, q, kl, vl, pos, A, kv_len, out, workspace,

@@ -10,12 +10,15 @@
 
 // Launch plan of the split-KV attention (host, pure function of the shape).
 struct FcAttnPlan {
-    int kind;            // 0 = tile kernel (fp32, head_dim 64, bf16 head_dim 128 over short keys), 1 = bf16 head_dim 128 split-KV
+    int kind;            // 0 = tile kernels (fp32, head_dim 64, bf16 head_dim 128 over short keys), 1 = bf16 head_dim 128 split-KV,
+                         // 2 = bf16 head_dim 128, longer keys without a split
     int splits;          // key ranges per (sequence, kv head); every one is non-empty
     int keys_per_split;  // multiple of 64 (kind 0: of 32)
     int row_tiles;       // 32-row (kind 0: 16-row) tiles of the flattened (head-in-group, a) rows per (b, kv head)
-    int tiles_per_wg;    // row tiles handled by one workgroup
-    int waves;           // waves per workgroup (tiles_per_wg or twice that)
+    int tiles_per_wg;    // row tiles handled by one workgroup (kind 2: in eights of query rows)
+    int waves;           // waves per workgroup
+    int group_tiles;     // k_attn_groups: 16-row tiles of a workgroup (0: another kernel)
+    int v_parts;         // and parts the columns of V are cut into
 };
 
 // A cache handle: written by fc_cache_alloc only.

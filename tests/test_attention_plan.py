@@ -127,6 +127,47 @@ def test_short_keys_take_the_tile_kernel(B, Hq, Hkv, A, S):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("B,Hq,Hkv,A,S,kind,per_wg,waves", [
+    # 16 rows, V in four parts: a last stage of one key, of exactly a half and a whole one; one stage more than waves
+    (1, 3, 1, 5, 97, 0, 1, 8), (1, 3, 1, 6, 128, 0, 1, 8), (1, 28, 4, 9, 1025, 0, 1, 8), (2, 28, 4, 4, 513, 0, 1, 8), (1, 5, 1, 7, 577, 0, 1, 8),
+    (2, 1, 1, 1, 160, 0, 1, 8), (1, 8, 8, 33, 1300, 2, 2, 8),
+    # in two parts; uncut, six waves
+    (2, 28, 4, 20, 129, 0, 1, 8), (3, 28, 4, 19, 1581, 2, 2, 8), (3, 32, 32, 8, 385, 0, 1, 8),
+    (4, 28, 4, 32, 321, 0, 1, 6), (5, 32, 32, 3, 385, 0, 1, 6), (2, 32, 32, 33, 769, 0, 1, 6),
+    # 32 rows, V in two parts
+    (4, 28, 4, 31, 1217, 2, 4, 8), (4, 28, 4, 29, 1281, 2, 4, 8),
+])
+def test_all_keys_in_one_launch(B, Hq, Hkv, A, S, kind, per_wg, waves):
+    print("[case] one launch", B, Hq, Hkv, A, S, flush=True)
+    from oracle import fc_oracle as orc
+    Dh, dt = 128, "bf16"
+    w = inputs.Workload("t", dt, B, 256, Hq, Hkv, Dh, S, A)
+    g = GpuLayerCache(dt, B, 256, Hq, Hkv, Dh, S + 70, max_rows=A, fill=float("nan"))  # keys past kv_len are not numbers
+    o = OracleLayerCache(dt, B, 256, Hq, Hkv, Dh, S + 70)
+    p = fc.fc_attention_plan(g.cfg, A, S)
+    assert (p["kind"], p["splits"], p["tiles_per_wg"], p["waves"]) == (kind, 1, per_wg, waves), p
+    K, V = inputs.kv_fill(w, 2, S)
+    g.write_rows(0, K, V, 0)
+    o.write_rows(K, V, 0)
+    Q = inputs.normal(2, "q", (B, Hq, A, Dh), 1.0, dt)
+    pos = inputs.window_positions(B, 0, A)
+    pos[B - 1, A // 2] = -1  # a padded row: zeros
+    ref = orc.attend(o.cfg, inputs.as_oracle(Q), o.Kc, o.Vc, S, inputs.as_oracle(pos))
+    O = g.attend(0, g.dev_t(Q), S, pos)
+    assert_close(inputs.as_oracle(O), ref, dt, "one launch")
+    assert not O[B - 1, A // 2].any()
+    # tensors that start at an odd element, and no workspace where none is required: the same bits
+    q, out = (torch.zeros(t.numel() + 1, dtype=t.dtype, device="cuda:0")[1:].view(t.shape) for t in (Q, O))
+    q.copy_(Q)
+    if _required(B * Hkv, Hq // Hkv, A, S) == 0:
+        fc.fc_active_attention(g.handle, 0, q, A, S, pos.to("cuda:0"), out, None, 0)
+    else:
+        fc.fc_active_attention(g.handle, 0, q, A, S, pos.to("cuda:0"), out, g.workspace, g.ws_bytes)
+    assert torch.equal(out.view(torch.int16), O.view(torch.int16))
+    g.close()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("tiles", ["8,8", "4,8", "2,8", "4,4", "2,4"])
 @pytest.mark.parametrize("Hq,Hkv,A,S", [(3, 1, 5, 70), (10, 2, 21, 777), (9, 1, 33, 300)])
 def test_every_tile_shape_matches_oracle(tiles, Hq, Hkv, A, S, knob):
