@@ -184,17 +184,36 @@ double attn_cost(const AttnShape &sh, int64_t pairs, int row_tiles, int kv_len, 
     return t > 7.4 ? t : 7.4;
 }
 
-// The same for the tile kernel: `wgs` workgroups (at most 256: one round), one per sequence, kv head, 16 query rows and key
-// range, each over `groups` groups of 32 keys of `group_bytes` bytes.  What counts is what one compute unit can pull from
-// HBM, some 35 B/ns; with up to 64 / 128 workgroups the head dimension of V is cut in four / two (the launch does that).
-// Fitted to 130 bf16 shapes of head_dim 128, 60 .. 1160 keys, one range (rms error 3 .. 5 %); fp32 and head_dim 64 follow it
-// by their bytes.
+// The same for the tile kernel where its operands come straight into registers (bf16 of head_dim 128, up to 96 keys): `wgs`
+// workgroups (at most 256: one round), one per sequence, kv head and 16 query rows, each over `groups` groups of 32 keys of
+// `group_bytes` bytes.  What counts is what one compute unit can pull that way, 38 B/ns; with up to 64 / 128 workgroups the
+// head dimension of V is cut in four / two (the launch does that).
 double attn_tile_cost(int64_t wgs, int64_t groups, int64_t group_bytes)
 {
     const double g = (double)groups * (double)group_bytes / 16384.0;
     if (wgs <= 64) return 3.58 + 0.275 * g;
     if (wgs <= 128) return 3.92 + 0.341 * g;
     return 4.28 + (0.229 + 1.18e-3 * (double)wgs) * g;
+}
+
+// The tile kernel of fp32 and of bf16 of head_dim 64, over `groups` groups of 32 keys per workgroup: start + each group + each
+// round of groups over the eight waves + what the other workgroups cost + each key range (uncut: operands by way of LDS; in
+// ranges: straight into registers, and a second kernel).  Fitted to 1200 shapes of 64 .. 2100 keys, 1 .. 250 workgroups (rms error 3 ..
+// 5 %, 13 % for fp32 rows of 128 in more than 128 workgroups and for two tiles per workgroup).  Rows: V in four parts, in two, uncut, two tiles per workgroup; in ranges.
+struct TileCost {
+    double start, group, round, load, range;
+};
+const TileCost TILE_F32_64[] = {{3.53, 0.187, 0.320, 0.203, 0}, {3.68, 0.210, 0.488, 0.075, 0}, {4.38, 0.210, 0.581, 0.101, 0},
+                                {5.75, 0.152, 0.296, 0.635, 0}, {5.75, 0.156, 0.565, 0.320, 0.296}};
+const TileCost TILE_F32_128[] = {{4.00, 0.487, 0.092, 0.562, 0}, {4.99, 0.340, 1.076, 0.189, 0}, {6.13, 0.251, -0.828, 0.954, 0},
+                                 {6.13, 0.251, -0.828, 0.954, 0}, {6.24, 0.543, 0.031, 0.751, 0.411}};
+const TileCost TILE_BF16_64[] = {{3.54, 0.083, -0.057, 0.058, 0}, {3.57, 0.108, -0.155, 0.023, 0}, {3.99, 0.137, -0.424, 0.039, 0},
+                                 {4.33, -0.144, 1.142, 0.277, 0}, {6.50, 0.100, 0, 0.050, 0.270}};
+double attn_tile_ranges_cost(bool f32, int head_dim, int tiles_per_wg, int64_t wgs, int64_t groups, int64_t splits)
+{
+    const int i = splits > 1 ? 4 : tiles_per_wg == 2 ? 3 : wgs <= 64 ? 0 : wgs <= 128 ? 1 : 2;
+    const TileCost &c = !f32 ? TILE_BF16_64[i] : head_dim == 64 ? TILE_F32_64[i] : TILE_F32_128[i];
+    return c.start + c.group * (double)groups + c.round * (double)((groups + 7) / 8) + c.load * (double)groups * (double)wgs / 256.0 + c.range * (double)splits;
 }
 
 // k_attn_groups: 16-row tiles of a workgroup, parts of the columns of V, waves, and its time (us) in up to one round of
@@ -319,12 +338,11 @@ FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len, size_t cap
         p.tiles_per_wg = cfg.head_dim == 64 && pairs * ((rows + 31) / 32) >= 128 ? 2 : 1;
         const int64_t base = pairs * ((p.row_tiles + p.tiles_per_wg - 1) / p.tiles_per_wg);
         const int64_t groups = ((int64_t)kv_len + 31) / 32;
-        const int64_t group_bytes = 64 * (int64_t)cfg.head_dim * (int64_t)esize_of(cfg.dtype);
         double best = 1e30;
         FcAttnPlan chosen = p;
-        for (int64_t n = 1; n == 1 || (n <= groups && n * base <= 256); ++n) {
+        for (int64_t n = 1; n == 1 || (n <= groups && n * base <= 256 && (p.tiles_per_wg == 1 || groups >= 32)); ++n) {
             const int64_t per = (groups + n - 1) / n, splits = (groups + per - 1) / per;
-            const double t = attn_tile_cost(base * splits, per, group_bytes) + (splits > 1 ? 2.6 + 0.45 * splits : 0.0);
+            const double t = attn_tile_ranges_cost(cfg.dtype == FC_F32, cfg.head_dim, p.tiles_per_wg, base * splits, per, splits);
             FcAttnPlan cut = p;
             cut.splits = (int)splits;
             cut.keys_per_split = (int)(32 * per);

@@ -82,6 +82,24 @@ __device__ __forceinline__ float partner32(float v)  // the value of lane ^ 32
     return (threadIdx.x & 32) ? __uint_as_float(r[0]) : __uint_as_float(r[1]);
 }
 
+// Over the four lanes l, l ^ 16, l ^ 32, l ^ 48 that share a column.
+__device__ __forceinline__ float max_rows(float v)
+{
+    unsigned u = __float_as_uint(v);
+    auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    u = __float_as_uint(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+    r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float sum_rows(float v)
+{
+    unsigned u = __float_as_uint(v);
+    auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    u = __float_as_uint(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+    r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 __device__ __forceinline__ void store4(float *p, const float (&y)[4]) { fc_store_any(p, make_float4(y[0], y[1], y[2], y[3])); }
 __device__ __forceinline__ void store4(bf16_t *p, const float (&y)[4])
 {
@@ -341,14 +359,20 @@ __global__ __launch_bounds__(TW * 64) void k_linear_tile(TileArgs p)
 // Attention of any supported shape: 16 QT query rows of a (sequence, kv head) per workgroup, its eight
 // waves take the 32-key groups of the workgroup's key range in turn and are merged through LDS.
 //
-// S^T = K Q^T and O^T += V^T P^T on the 16x16 matrix instructions, operands straight from global memory
-// (K rows and transposed V tiles are both in operand order, 16 bytes per lane).  The accumulator of S^T
+// S^T = K Q^T and O^T += V^T P^T on the 16x16 matrix instructions.  K rows and transposed V tiles are both in operand
+// order, 16 bytes per lane.  Uncut (LDS), they come by way of LDS, where every wave has areas of its own: loaded straight
+// into registers, with neighbouring lanes in different rows, a compute unit takes one lane a clock, 38 B/ns, and by direct-to-LDS
+// loads of 64 bytes or more per row up to 138.  700 drawn shapes of 64 .. 2100 keys, with the ranges planned anew: fp32 rows of 64 / 128
+// 1.075 / 1.14 x, bf16 rows of 64 1.13 x (288 keys, 8 heads x 16 rows: 6.4 -> 6.2, 11.1 -> 8.8, 4.6 -> 4.2 us); of it 1.03 x from dealing
+// the workgroups to the XCDs by what they read.  fp32 is bound by its matrix rate (a group of 32 keys, rows of 64: 1024 clocks of scores).
+// In ranges, a wave has one group or two and the longer way costs more than it brings (2 .. 9 %): straight into registers, and so for
+// the up to three groups of bf16 rows of 128.  The accumulator of S^T
 // puts keys 4 q + r of a 16-key group into register r of lane (query, q): for fp32 that is the operand
 // layout of P^T (four 16x16x4 instructions, keys 4 q + j); for bf16 the K rows of the two groups are read
 // permuted, so that the eight probabilities of a lane are the keys 8 q .. 8 q + 7.  No exchange for P.
 //
-// These caches are small: the kernel is bound by latency with few query rows and by L2 and the fp32 matrix
-// rate with many.  A short cache with a single workgroup per (head, tile) is cut into key ranges ("splits",
+// These caches are small: the kernel is bound by latency with few query rows and by the fp32 matrix
+// rate with many.  A cache with a single workgroup per (head, tile) is cut into key ranges ("splits",
 // planned on the host) whose partial states k_attn_tile_merge combines.  The plain-ALU kernel it replaces
 // (a thread per key, then a thread per output column) took 22 us for the tiny configuration.
 struct AttnTileArgs {
@@ -386,28 +410,102 @@ __device__ __forceinline__ void attn_store_row4(const AttnTileArgs &p, int bj, i
     store4((T *)p.out + ((size_t)b * p.A + a) * ((size_t)G.Hq * G.Dh) + (size_t)(j * G.g + hg) * G.Dh + d0, y);
 }
 
-template <typename T, int DH, int QT, int DS>
+// LDS of k_attn_tile: a wave's area holds KG keys and VG values of a group, or its results at the end.  20 KB at most, so that
+// eight waves fit; fp32 rows of 128 come in halves of 16 keys where that takes it.
+template <typename T, int DH, int QT, int DS, bool LDS>
+struct AttnTileLds {
+    static constexpr int KROW = DH * sizeof(T), VKEY = DH / DS * sizeof(T), MOST = 20 * 1024;
+    static constexpr int KG = 32 * (KROW + VKEY) <= MOST ? 32 : 16;
+    static constexpr int VG = KG * KROW + 32 * VKEY <= MOST ? 32 : 16;
+    static constexpr int VROW = VG * sizeof(T);
+    static constexpr int NK = KG * KROW / 1024, NVL = VG * VKEY / 1024;  // 1 KB loads
+    static constexpr int STAGE = KG * KROW + VG * VKEY, STATE = QT * 16 * (DH / DS + AT_STRIDE + 2) * (int)sizeof(float);
+    static constexpr int WAVE = ((LDS && STAGE > STATE ? STAGE : STATE) + 127) / 128 * 128;
+    static_assert(STAGE <= MOST && NVL >= 1, "areas");
+    template <int ROWB>
+    static __device__ __forceinline__ int swizzle(int row)
+    {
+        return ROWB >= 256 ? row & 15 : ROWB == 128 ? (row >> 1) & 7 : (row >> 2) & 3;
+    }
+};
+
+__device__ __forceinline__ void load_lds16t(const void *g, void *l)
+{
+    __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)g,
+                                     (void __attribute__((address_space(3))) *)l, 16, 0, 0);
+}
+
+// wait until at most N of this wave's vector-memory operations are outstanding
+template <int N>
+__device__ __forceinline__ void wait_vmt()
+{
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+
+template <typename T, int DH, int QT, int DS, bool LDS>
 __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
 {
     typedef Op<T> O;
     typedef typename O::frag frag;
+    typedef AttnTileLds<T, DH, QT, DS, LDS> L;
     constexpr int KB = O::KB, NKB = DH / (4 * KB), DV = DH / DS, ND = DV / 16, ROW = DV + AT_STRIDE;
     constexpr bool F32 = KB == 4;
     constexpr int NV = F32 ? 2 : 1;  // V fragments per 16 head-dim rows and 32 keys
     constexpr int NP = prob_terms<T, DH>();
-    extern __shared__ __align__(16) unsigned char attn_smem[];
-    float *xo = (float *)attn_smem;                  // [wave][16 QT][ROW]
-    float *xml = xo + TW * QT * 16 * ROW;            // [wave][16 QT][2]
+    extern __shared__ __align__(1024) unsigned char attn_smem[];
     const FcGeom &G = p.G;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rho = lane & 15, q = lane >> 4;
-    const int dv0 = (int)(blockIdx.x % DS) * DV;  // this workgroup's part of the head dimension of V
-    const int split = blockIdx.x / DS % p.splits, bt = blockIdx.x / DS / p.splits;
+    unsigned char *kbuf = attn_smem + wave * L::WAVE, *vbuf = kbuf + L::KG * L::KROW;
+    // at the end: [16 QT][ROW] partial outputs and [16 QT][2] row states of every wave, in its area
+    auto xo = [&](int w) { return (float *)(attn_smem + w * L::WAVE); };
+    auto xml = [&](int w) { return xo(w) + QT * 16 * ROW; };
+    // workgroup ids equal modulo 8 share an XCD: the workgroups, ordered by what they read, are dealt in equal contiguous runs
+    const uint32_t n_wgs = (uint32_t)G.B * G.Hkv * p.tiles * p.splits * DS, xcd = blockIdx.x & 7;
+    const uint32_t id = (uint32_t)((uint64_t)xcd * n_wgs >> 3) + (blockIdx.x >> 3);
+    if (id >= (uint32_t)((uint64_t)(xcd + 1) * n_wgs >> 3)) return;
+    const int dv0 = (int)(id % DS) * DV;  // this workgroup's part of the head dimension of V
+    const int split = id / DS % p.splits, bt = id / DS / p.splits;
     const int tile = bt % p.tiles, bj = bt / p.tiles;
     const int b = bj / G.Hkv, j = bj % G.Hkv;
     const T *kc = (const T *)p.Kc + (size_t)bj * G.spad * DH, *vc = (const T *)p.Vc + (size_t)bj * G.spad * DH;
 
+    const int n_groups = (p.kv_len + 31) / 32;
+    const int g0 = split * p.groups_per_split, g1 = min(n_groups, g0 + p.groups_per_split);
+    // key of row i of 16-key half h: fp32 in order; bf16 so that register pairs of the two halves are 8 keys in a row
+    auto key_of = [&](int h, int i) { return F32 ? 16 * h + i : 8 * (i >> 2) + 4 * h + (i & 3); };
+    // Part `part` of group g to LDS, in pieces of 1 KB; a row's 16-byte chunks are permuted so that 16 rows' chunks of one
+    // column fall into 16 different bank groups.
+    auto issue_k = [&](int g, int part) {
+#pragma unroll
+        for (int l = 0; l < L::NK; ++l) {
+            const int at = 1024 * l + 16 * lane, row = at / L::KROW, c = (at % L::KROW) >> 4, r = part * L::KG + row;
+            const unsigned char *src = (const unsigned char *)kc + (size_t)(32 * g + key_of(r >> 4, r & 15)) * L::KROW;
+            load_lds16t(src + 16 * (c ^ L::template swizzle<L::KROW>(row)), kbuf + 1024 * l);
+        }
+    };
+    auto issue_v = [&](int g, int part) {
+        const unsigned char *vt = (const unsigned char *)(vc + (size_t)(g >> 1) * (FC_VTILE * DH) + 32 * (g & 1) + L::VG * part);
+#pragma unroll
+        for (int l = 0; l < L::NVL; ++l) {
+            const int at = 1024 * l + 16 * lane, row = at / L::VROW, c = (at % L::VROW) >> 4;
+            load_lds16t(vt + (size_t)(dv0 + row) * (FC_VTILE * sizeof(T)) + 16 * (c ^ L::template swizzle<L::VROW>(row)), vbuf + 1024 * l);
+        }
+    };
+    frag kd[2][NKB], vd[ND][NV];  // without LDS
+    auto load_k = [&](int g) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int k = 0; k < NKB; ++k)
+                kd[h][k] = *(const frag *)(kc + (size_t)(32 * g + key_of(h, rho)) * DH + 4 * KB * k + KB * q);
+    };
+    if (LDS && g0 + wave < g1) {
+        issue_k(g0 + wave, 0);
+        issue_v(g0 + wave, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    }
     frag qf[QT][NKB];
 #pragma unroll
     for (int u = 0; u < QT; ++u) {
@@ -427,40 +525,57 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
         m[u] = -INFINITY;
         l[u] = 0.f;
     }
-
-    const int n_groups = (p.kv_len + 31) / 32;
-    const int g0 = split * p.groups_per_split, g1 = min(n_groups, g0 + p.groups_per_split);
-    // key of row i of 16-key group h: fp32 in order; bf16 so that register pairs of the two groups are 8 keys in a row
-    auto key_of = [&](int h, int i) { return F32 ? 16 * h + i : 8 * (i >> 2) + 4 * h + (i & 3); };
-    frag kf[2][NKB];
-    auto load_k = [&](int g) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int s = 0; s < NKB; ++s)
-                kf[h][s] = *(const frag *)(kc + (size_t)(32 * g + key_of(h, rho)) * DH + 4 * KB * s + KB * q);
-    };
-    if (g0 + wave < g1) load_k(g0 + wave);
+    if (!LDS && g0 + wave < g1) load_k(g0 + wave);
     for (int g = g0 + wave; g < g1; g += TW) {
-        frag vf[ND][NV];
-        const T *vt = vc + (size_t)(g >> 1) * (FC_VTILE * DH) + 32 * (g & 1);
+        const bool more = g + TW < g1;
+        if constexpr (!LDS) {
+            const T *vt = vc + (size_t)(g >> 1) * (FC_VTILE * DH) + 32 * (g & 1);
 #pragma unroll
-        for (int d = 0; d < ND; ++d)
+            for (int d = 0; d < ND; ++d)
 #pragma unroll
-            for (int h = 0; h < NV; ++h)
-                vf[d][h] = *(const frag *)(vt + (dv0 + 16 * d + rho) * FC_VTILE + (F32 ? 16 * h : 0) + KB * q);
+                for (int h = 0; h < NV; ++h)
+                    vd[d][h] = *(const frag *)(vt + (dv0 + 16 * d + rho) * FC_VTILE + (F32 ? 16 * h : 0) + KB * q);
+        }
         f32x4 s[QT][2];
 #pragma unroll
         for (int u = 0; u < QT; ++u)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                s[u][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int h = 0; h < 2; ++h) s[u][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (LDS) {
 #pragma unroll
-                for (int k = 0; k < NKB; ++k) s[u][h] = O::mfma(kf[h][k], qf[u][k], s[u][h]);
+            for (int part = 0; part < 32 / L::KG; ++part) {
+                if (part == 0) wait_vmt<L::NVL>();  // these keys are here; the values behind them may stay in flight
+                else wait_vmt<0>();
+                __builtin_amdgcn_sched_barrier(0);
+                frag kf[L::KG / 16][NKB];
+#pragma unroll
+                for (int h = 0; h < L::KG / 16; ++h)
+#pragma unroll
+                    for (int k = 0; k < NKB; ++k)
+                        kf[h][k] = *(const frag *)(kbuf + (16 * h + rho) * L::KROW + 16 * ((4 * k + q) ^ L::template swizzle<L::KROW>(16 * h + rho)));
+                __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the area may be overwritten
+                __builtin_amdgcn_sched_barrier(0);
+                if (part + 1 < 32 / L::KG) issue_k(g, part + 1);
+                else if (more) issue_k(g + TW, 0);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int k = 0; k < NKB; ++k)
+#pragma unroll
+                    for (int u = 0; u < QT; ++u)
+#pragma unroll
+                        for (int h = 0; h < L::KG / 16; ++h) s[u][part * (L::KG / 16) + h] = O::mfma(kf[h][k], qf[u][k], s[u][part * (L::KG / 16) + h]);
             }
-        if (g + TW < g1) load_k(g + TW);  // the next group's keys travel behind the softmax and the output products
-        if (32 * g + 32 > p.kv_len) {
-            // keys past the end may hold anything: no score, and zero values so that 0 * V stays 0
+        } else {
+#pragma unroll
+            for (int u = 0; u < QT; ++u)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int k = 0; k < NKB; ++k) s[u][h] = O::mfma(kd[h][k], qf[u][k], s[u][h]);
+            if (more) load_k(g + TW);  // the next group's keys travel behind the softmax and the output products
+        }
+        const bool past = 32 * g + 32 > p.kv_len;  // keys past the end may hold anything: no score, and zero values (0 * V stays 0)
+        if (past) {
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -469,22 +584,14 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
 #pragma unroll
                         for (int u = 0; u < QT; ++u) s[u][h][r] = -INFINITY;
                     }
-#pragma unroll
-            for (int d = 0; d < ND; ++d)
-#pragma unroll
-                for (int h = 0; h < NV; ++h)
-#pragma unroll
-                    for (int e = 0; e < KB; ++e)
-                        if (32 * g + (F32 ? 16 * h : 0) + KB * q + e >= p.kv_len) vf[d][h][e] = {};
         }
+        frag pf[QT][F32 ? NV : NP];
 #pragma unroll
         for (int u = 0; u < QT; ++u) {
             float mx = s[u][0][0];
 #pragma unroll
             for (int r = 1; r < 8; ++r) mx = fmaxf(mx, s[u][r >> 2][r & 3]);
-            mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-            const float m_new = fmaxf(m[u], mx);
+            const float m_new = fmaxf(m[u], max_rows(mx));
             const float alpha = __builtin_amdgcn_exp2f((m[u] - m_new) * p.c);
             m[u] = m_new;
             l[u] *= alpha;
@@ -498,37 +605,81 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
             for (int d = 0; d < ND; ++d)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) o[u][d][r] *= alpha;
-            frag pf[F32 ? NV : NP];
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
                 if constexpr (F32) {
-                    pf[r >> 2][r & 3] = pr[r];
+                    pf[u][r >> 2][r & 3] = pr[r];
                 } else {
 #pragma unroll
                     for (int h = 0; h < NP; ++h) {
-                        pf[h][r] = (__bf16)pr[r];
-                        pr[r] -= (float)pf[h][r];  // (exact)
+                        pf[u][h][r] = (__bf16)pr[r];
+                        pr[r] -= (float)pf[u][h][r];  // (exact)
                     }
                 }
             }
+        }
+        if constexpr (LDS) {
 #pragma unroll
-            for (int d = 0; d < ND; ++d)
+            for (int part = 0; part < 32 / L::VG; ++part) {
+                if (part == 0 && more) wait_vmt<L::NK>();  // these values are here; the next keys may stay in flight
+                else wait_vmt<0>();
+                __builtin_amdgcn_sched_barrier(0);
+                constexpr int NVP = NV * L::VG / 32;  // fragments per 16 rows
+                frag vf[ND][NVP];
 #pragma unroll
-                for (int h = 0; h < (F32 ? NV : NP); ++h) o[u][d] = O::mfma(vf[d][F32 ? h : 0], pf[h], o[u][d]);
+                for (int d = 0; d < ND; ++d)
+#pragma unroll
+                    for (int h = 0; h < NVP; ++h)
+                        vf[d][h] = *(const frag *)(vbuf + (16 * d + rho) * L::VROW + 16 * ((4 * h + q) ^ L::template swizzle<L::VROW>(16 * d + rho)));
+                __builtin_amdgcn_s_waitcnt(0xc07f);
+                __builtin_amdgcn_sched_barrier(0);
+                if (part + 1 < 32 / L::VG) issue_v(g, part + 1);
+                else if (more) issue_v(g + TW, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (past) {
+#pragma unroll
+                    for (int d = 0; d < ND; ++d)
+#pragma unroll
+                        for (int h = 0; h < NVP; ++h)
+#pragma unroll
+                            for (int e = 0; e < KB; ++e)
+                                if (32 * g + L::VG * part + (F32 ? 16 * h : 0) + KB * q + e >= p.kv_len) vf[d][h][e] = {};
+                }
+#pragma unroll
+                for (int u = 0; u < QT; ++u)
+#pragma unroll
+                    for (int d = 0; d < ND; ++d)
+#pragma unroll
+                        for (int h = 0; h < (F32 ? NVP : NP); ++h) o[u][d] = O::mfma(vf[d][F32 ? h : 0], pf[u][F32 ? NVP * part + h : h], o[u][d]);
+            }
+        } else {
+            if (past) {
+#pragma unroll
+                for (int d = 0; d < ND; ++d)
+#pragma unroll
+                    for (int h = 0; h < NV; ++h)
+#pragma unroll
+                        for (int e = 0; e < KB; ++e)
+                            if (32 * g + (F32 ? 16 * h : 0) + KB * q + e >= p.kv_len) vd[d][h][e] = {};
+            }
+#pragma unroll
+            for (int u = 0; u < QT; ++u)
+#pragma unroll
+                for (int d = 0; d < ND; ++d)
+#pragma unroll
+                    for (int h = 0; h < (F32 ? NV : NP); ++h) o[u][d] = O::mfma(vd[d][F32 ? h : 0], pf[u][h], o[u][d]);
         }
     }
 
     // ---- merge the eight waves through LDS
 #pragma unroll
     for (int u = 0; u < QT; ++u) {
-        float lu = l[u];
-        lu += __shfl_xor(lu, 16, 64);
-        lu += __shfl_xor(lu, 32, 64);
-        float *row = xo + ((size_t)wave * QT * 16 + 16 * u + rho) * ROW + 4 * q;
+        const float lu = sum_rows(l[u]);
+        float *row = xo(wave) + (16 * u + rho) * ROW + 4 * q;
 #pragma unroll
         for (int d = 0; d < ND; ++d) *(f32x4 *)(row + 16 * d) = o[u][d];
         if (q == 0) {
-            float *ml = xml + ((size_t)wave * QT * 16 + 16 * u + rho) * 2;
+            float *ml = xml(wave) + (16 * u + rho) * 2;
             ml[0] = m[u];
             ml[1] = lu;
         }
@@ -538,14 +689,14 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
         const int row = idx / (DV / 4), d0 = 4 * (idx % (DV / 4));
         float mm = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < TW; ++w) mm = fmaxf(mm, xml[(w * QT * 16 + row) * 2]);
+        for (int w = 0; w < TW; ++w) mm = fmaxf(mm, xml(w)[row * 2]);
         float den = 0.f;
         float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
         for (int w = 0; w < TW; ++w) {
-            const float *ml = xml + (w * QT * 16 + row) * 2;
+            const float *ml = xml(w) + row * 2;
             const float k = __builtin_amdgcn_exp2f((ml[0] - mm) * p.c);
-            const float4 v = *(const float4 *)(xo + ((size_t)w * QT * 16 + row) * ROW + d0);
+            const float4 v = *(const float4 *)(xo(w) + row * ROW + d0);
             den += k * ml[1];
             num.x += k * v.x;
             num.y += k * v.y;
@@ -839,34 +990,34 @@ hipError_t launch_tile(int dtype, const TileArgs &a, int n_tiles, hipStream_t s)
     return dtype == FC_F32 ? launch_tile_t<float, EPI>(a, n_tiles, s) : launch_tile_t<bf16_t, EPI>(a, n_tiles, s);
 }
 
-template <typename T, int DH, int QT, int DS>
+template <typename T, int DH, int QT, int DS, bool LDS>
 hipError_t launch_attn_tile(const AttnTileArgs &a, hipStream_t s)
 {
-    constexpr size_t LDS = (size_t)TW * QT * 16 * (DH / DS + AT_STRIDE + 2) * sizeof(float);
-    static hipError_t attr = hipFuncSetAttribute((const void *)k_attn_tile<T, DH, QT, DS>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
+    constexpr size_t BYTES = (size_t)TW * AttnTileLds<T, DH, QT, DS, LDS>::WAVE;
+    static hipError_t attr = hipFuncSetAttribute((const void *)k_attn_tile<T, DH, QT, DS, LDS>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)BYTES);
     if (attr != hipSuccess) return attr;
     const int64_t bt = (int64_t)a.G.B * a.G.Hkv * a.tiles;
     if (bt * a.splits > (1 << 30) || bt * (QT * DH / 64) > (1 << 30)) return hipErrorInvalidValue;
-    k_attn_tile<T, DH, QT, DS><<<dim3((unsigned)(bt * a.splits * DS)), dim3(TW * 64), LDS, s>>>(a);
+    k_attn_tile<T, DH, QT, DS, LDS><<<dim3((unsigned)((bt * a.splits * DS + 7) / 8 * 8)), dim3(TW * 64), BYTES, s>>>(a);
     if (a.splits > 1) k_attn_tile_merge<T, DH, QT><<<dim3((unsigned)(bt * (QT * DH / 64))), dim3(256), 0, s>>>(a);
     return hipGetLastError();
 }
 
 // With a quarter or half of the compute units at most, the head dimension of V is cut in four or two: every part
 // repeats the scores, but the values it loads, its output products and the merge of its waves shrink (fp32, head_dim 64,
-// 8 workgroups, 288 keys: 8.4 us uncut, now 6.5; 861 keys in two ranges, with the merge 11.4, now 9.5).  With more workgroups
+// 8 workgroups, 288 keys: 8.4 us uncut, 6.5 in four; 861 keys in two ranges, with the merge 11.4 and 9.5).  With more workgroups
 // it costs more than it brings (144 of head_dim 128, 305 keys: 12.3 us, 18.5 in halves).
-template <typename T, int DH>
+template <typename T, int DH, bool LDS>
 hipError_t launch_attn_tile_t(int qt, const AttnTileArgs &a, hipStream_t s)
 {
     if constexpr (DH == 64)
-        if (qt == 2) return launch_attn_tile<T, DH, 2, 1>(a, s);
+        if (qt == 2) return launch_attn_tile<T, DH, 2, 1, LDS>(a, s);
     if (qt != 1) return hipErrorInvalidValue;
     const int64_t wgs = (int64_t)a.G.B * a.G.Hkv * a.tiles * a.splits;
-    if (wgs <= 64) return launch_attn_tile<T, DH, 1, 4>(a, s);
-    if (wgs <= 128) return launch_attn_tile<T, DH, 1, 2>(a, s);
-    return launch_attn_tile<T, DH, 1, 1>(a, s);
+    if (wgs <= 64) return launch_attn_tile<T, DH, 1, 4, LDS>(a, s);
+    if (wgs <= 128) return launch_attn_tile<T, DH, 1, 2, LDS>(a, s);
+    return launch_attn_tile<T, DH, 1, 1, LDS>(a, s);
 }
 
 }  // namespace
@@ -953,6 +1104,11 @@ hipError_t fc_launch_attention_tile(const FcGeom &G, const FcAttnPlan &pl, int d
         a.part_ml = a.part_o + (size_t)G.B * G.Hkv * a.tiles * pl.splits * 16 * pl.tiles_per_wg * G.Dh;
     }
     const int qt = pl.tiles_per_wg;
-    if (dtype == FC_F32) return G.Dh == 64 ? launch_attn_tile_t<float, 64>(qt, a, s) : G.Dh == 128 ? launch_attn_tile_t<float, 128>(qt, a, s) : hipErrorInvalidValue;
-    return G.Dh == 64 ? launch_attn_tile_t<bf16_t, 64>(qt, a, s) : G.Dh == 128 ? launch_attn_tile_t<bf16_t, 128>(qt, a, s) : hipErrorInvalidValue;
+    if (pl.splits == 1) {
+        if (dtype == FC_F32) return G.Dh == 64 ? launch_attn_tile_t<float, 64, true>(qt, a, s) : G.Dh == 128 ? launch_attn_tile_t<float, 128, true>(qt, a, s) : hipErrorInvalidValue;
+        if (G.Dh == 64) return launch_attn_tile_t<bf16_t, 64, true>(qt, a, s);
+        return G.Dh == 128 ? launch_attn_tile_t<bf16_t, 128, false>(qt, a, s) : hipErrorInvalidValue;  // (up to three groups)
+    }
+    if (dtype == FC_F32) return G.Dh == 64 ? launch_attn_tile_t<float, 64, false>(qt, a, s) : G.Dh == 128 ? launch_attn_tile_t<float, 128, false>(qt, a, s) : hipErrorInvalidValue;
+    return G.Dh == 64 ? launch_attn_tile_t<bf16_t, 64, false>(qt, a, s) : hipErrorInvalidValue;
 }

@@ -58,6 +58,31 @@ def test_step_matches_oracle(dtype, B, d, Hq, Hkv, Dh, L, A):
     g.close()
 
 
+@pytest.mark.parametrize("dtype,Dh", [("f32", 64), ("f32", 128), ("bf16", 64)])
+@pytest.mark.parametrize("B,Hq,Hkv,A", [
+    (1, 4, 2, 9),     # 4 workgroups: V in four parts
+    (3, 8, 4, 45),    # 72: in two
+    (5, 8, 4, 55),    # 140: uncut
+    (3, 12, 12, 100), # rows of 64: 144 of two tiles each, the last one ragged
+])
+@pytest.mark.parametrize("S", [1, 31, 33, 257, 290])
+def test_attention_over_all_keys_by_way_of_lds(dtype, Dh, B, Hq, Hkv, A, S):
+    """A part of a group, one group and a bit, one more group than waves and a part of another; no space for ranges."""
+    print("[case] all keys", dtype, Dh, B, Hq, Hkv, A, S, flush=True)
+    w = inputs.Workload("t", dtype, B, 256, Hq, Hkv, Dh, S, A)
+    g = GpuLayerCache(dtype, B, 256, Hq, Hkv, Dh, S + 40, max_rows=A, fill=float("nan"))  # keys past kv_len are not numbers
+    o = OracleLayerCache(dtype, B, 256, Hq, Hkv, Dh, S + 40)
+    K, V = inputs.kv_fill(w, 5, S)
+    g.write_rows(0, K, V, 0)
+    o.write_rows(K, V, 0)
+    Q = inputs.normal(5, "q", (B, Hq, A, Dh), 1.0, dtype)
+    out = torch.full((B, A, Hq * Dh), float("nan"), dtype=g.tdt, device=DEV)
+    fc.fc_active_attention(g.handle, 0, g.dev_t(Q), A, S, None, out, None, 0)
+    torch.cuda.synchronize()
+    assert_close(inputs.as_oracle(out), orc.attend(o.cfg, inputs.as_oracle(Q), o.Kc, o.Vc, S, None), dtype, "all keys")
+    g.close()
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,A,S", [(1, 4, 4, 32, 288), (1, 8, 2, 5, 2000), (4, 8, 8, 33, 64)])
 def test_bf16_rows_of_64_keep_fp32_probabilities(B, Hq, Hkv, A, S):
     """With fp32 probabilities a result differs from the rounded exact one only where that lies within the error of the
