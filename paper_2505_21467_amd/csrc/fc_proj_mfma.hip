@@ -3,10 +3,10 @@
 //
 // The window is short (tens to a few hundred rows), so the product Y^T = W X^T is bound by streaming
 // the weight matrix once from HBM.  Both operands are contiguous along the hidden dimension, which is
-// exactly the per-lane operand layout of v_mfma_f32_16x16x32_bf16 (8 consecutive k per lane), so W
-// fragments are loaded straight from global memory into operand registers.  Three kernels: whole rows for at most 32
-// window rows at the hidden sizes it is built for (k_proj_rows), head slots cut along the hidden dimension for
-// at most 128 rows (k_proj_headsplit), and the one described here for what is left.
+// exactly the per-lane operand layout of v_mfma_f32_16x16x32_bf16 (8 consecutive k per lane).  Three kernels: runs of
+// rotary pairs over the whole hidden dimension for at most 96 window rows (k_proj_stream), head slots cut along the hidden
+// dimension for 33 .. 128 rows (k_proj_headsplit), both at multiples of 512, and k_proj_skinny, described here, for
+// what is left.
 //
 // A workgroup owns 16 rows of W -- 8 rows i0..i0+7 of one head and their rotary partners
 // i0+64..i0+71 -- and up to 32 rows of X.  Its waves split the hidden dimension, load both operands straight into
@@ -40,8 +40,9 @@ struct ProjArgs {
     double rot[6];         // rope_base^(-i/64), i = 1, 2, 4, .. 32
     float *partials;       // cache scratch: partial tiles of the hidden-dimension slices
     int mt;                // 16-row window tiles of a partial
+    int wave_bytes;        // k_proj_stream: LDS of a wave,
+    uint32_t div_grid, div_a;  // reciprocals of the grid and of A
 };
-
 
 __device__ __forceinline__ bf16x8 ld8(const uint16_t *p)
 {
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
 }
 
 // -------------------------------------------------------------------------------------------------
-// Head-split kernel for windows of at most 128 rows and hidden sizes that are multiples of 512.
+// Head-split kernel for windows of 33 .. 128 rows and hidden sizes that are multiples of 512.
 //
 // A workgroup owns one whole head slot (128 rows of W: 8 waves x 16 rows) and one 512-wide slice of
 // the hidden dimension, so the 512-wide slice of X is fetched once per workgroup (direct-to-LDS,
@@ -348,195 +349,226 @@ __global__ __launch_bounds__(64) void k_proj_finish(ProjArgs p)
 }
 
 // -------------------------------------------------------------------------------------------------
-// Whole-row kernel for windows of at most 32 rows at the hidden sizes it was measured at, 512, 3584 and 4096.  The window rows
-// would fit in registers at every multiple of 256 up to 4096; at other sizes the kernels above run.
+// Whole-row kernel: at most 96 window rows, hidden sizes that are multiples of 512.
 //
-// Every workgroup owns an equal run of rotary pairs (rows i and i + 64 of a head; 9 pairs at 36 head slots) and takes
-// them in items of 8 NF pairs over the whole hidden dimension, so no partial tiles leave the workgroup: its eight
-// waves cut the hidden dimension, keep their part of X in operand registers, and sum their tiles through LDS.
-//   NF = 1: one operand of 16 weight rows, lanes 0 .. 7 the first rows of 8 pairs, 8 .. 15 their partners
-//   NF = 2: two operands, the first rows of up to 16 pairs and their partners
-// X comes by way of LDS in whole cache lines (direct-to-LDS, 16 rows at a time, chunks permuted against bank conflicts):
-// loaded straight into operand registers, half a line per row and load, it was 7 us of the kernel at 32 rows.  One launch:
-// 36 head slots, hidden 3584, 16 / 32 rows 9.9 / 11.3 us (head-split and its finish 11.5 / 12.6); 96 slots, hidden 4096,
-// 32 rows 22.8 us (26.7 in the tiled GEMM); 12 slots, hidden 512, 4.2 (6.6).
+// Every workgroup owns an equal run of rotary pairs (rows i and i + 64 of a head; 9 pairs at 36 head slots) over the whole
+// hidden dimension, so no partial tiles leave it.  Its eight waves cut the hidden dimension; each streams its part of the
+// run's weight rows and of the window rows through LDS of its own, 64 hidden elements (one line of every row) per
+// stage, and waits for nobody until the waves' tiles are summed.
+//   * Bound by what a compute unit takes in, weights from HBM and all window rows from L2.  Loads whose lanes lie in eight
+//     whole lines run at 64 bytes per clock; loaded straight into operand registers, sixteen rows to an instruction,
+//     weights alone came at a quarter of that.
+//   * Where weight rows lie a multiple of 8 KB apart the workgroups of a die start at eight different stages: all at the
+//     same offset they meet in a part of the memory channels (96 slots, hidden 4096, 8 / 32 rows 20.2 / 22.1 -> 19.4 / 20.9).
+//   * The epilogue's tasks go by 16 pairs of four rows: more waves share it, a row is stored 32 bytes at a time, and its
+//     operands and first angle are at hand when the sums are (16 / 32 / 64 rows 9.1 / 10.5 / 14.3 -> 8.7 / 10.0 / 13.8 us).
+//   * NP = 2: runs of 17 .. 32 pairs.
+// Against the kernel it replaced (X kept in operand registers, at most 32 rows) and the head-split kernels, us: 36 head slots,
+// hidden 3584, 4 / 16 / 32 rows 9.4 / 9.6 / 11.1 -> 8.3 / 8.6 / 9.8, 48 / 64 rows 13.7 / 15.1 -> 11.7 / 13.4; 96 slots, hidden 4096, 32 rows
+// 23.3 -> 21.1; 24 slots, hidden 2048, 32 / 64 rows 9.5 / 11.9 -> 5.5 / 7.3.
 template <int N>
 __device__ __forceinline__ void wait_vm()
 {
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
+// x / d, d given as 2^32 / d rounded up (0: d is 1); exact for x d < 2^32
+__device__ __forceinline__ uint32_t quotient(uint32_t x, uint32_t reciprocal) { return reciprocal ? __umulhi(x, reciprocal) : x; }
+uint32_t reciprocal(int d) { return (uint32_t)((((int64_t)1 << 32) + d - 1) / d); }
 
-template <int MT, int NKW, int NF>
-__global__ __launch_bounds__(512) void k_proj_rows(ProjArgs p)
+constexpr int STREAM_K = 64;  // hidden elements per stage: one 128-byte line of every row
+template <int MT, int NP>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_proj_stream(ProjArgs p)
 {
     extern __shared__ __align__(1024) unsigned char lds[];
-    float(*red)[8][NF][MT * 4][64] = (float(*)[8][NF][MT * 4][64])lds;  // [2]
-    constexpr int XROW = NKW * 64;  // bytes of a wave's part of an X row
-    auto xswz = [](int r) { return NKW % 4 == 0 ? r & 15 : (r >> 1) & 7; };
     const FcGeom &G = p.G;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rho = lane & 15, q = lane >> 4;
-    const int n_pairs = p.n_tiles * 8;
-    int g0 = (int)((int64_t)blockIdx.x * n_pairs / gridDim.x);
-    const int g1 = (int)(((int64_t)blockIdx.x + 1) * n_pairs / gridDim.x);
-    const int kw0 = wave * (NKW * 32) + 8 * q;
+    const uint32_t n_pairs = (uint32_t)p.n_tiles * 8;
+    const int g0 = (int)quotient(blockIdx.x * n_pairs, p.div_grid);
+    const int R = (int)quotient((blockIdx.x + 1) * n_pairs, p.div_grid) - g0;  // pairs of this workgroup
+    const int n_stages = p.K / (8 * STREAM_K);
+    const int n_wl = (2 * R + 7) >> 3;  // weight loads of a stage
+    unsigned char *xbuf = lds + wave * p.wave_bytes, *wbuf = xbuf + MT * 2048;
 
-    // weight row of this lane in operand f of the item that starts at pair g (past the end: the run's last pair)
-    auto wrow_of = [&](int g, int f) -> const uint16_t * {
-        const int gp = min(g + (NF == 1 ? rho & 7 : rho), g1 - 1);
-        const bool partner = NF == 1 ? rho >= 8 : f == 1;
-        return p.W + ((size_t)(gp >> 6) * 128 + (gp & 63) + (partner ? 64 : 0)) * p.K + kw0;
-    };
-    bf16x8 xr[NKW][MT], wf[NKW][NF];
-    unsigned char *xw = lds + wave * (16 * XROW);
+    // row r of the workgroup's weight rows: the first rows of its pairs, then their partners
+    const int row0 = (g0 >> 6) * 128 + (g0 & 63);
+    const unsigned char *wbase = (const unsigned char *)(p.W + (size_t)row0 * p.K) + (size_t)wave * n_stages * 128;
+    const unsigned char *xbase = (const unsigned char *)p.X + (size_t)wave * n_stages * 128;
+    uint32_t woff[4 * NP], xoff[2 * MT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-        for (int i = 0; i < NKW; ++i) {
-            const int byte = 1024 * i + 16 * lane, r = byte / XROW, c = (byte - r * XROW) >> 4;
-            const int m = min(16 * mt + r, p.M - 1);  // padding rows read a valid row
-            load_lds16p(p.X + (size_t)m * p.K + wave * (NKW * 32) + 8 * (c ^ xswz(r)), xw + 1024 * i);
-        }
-        if (mt == MT - 1) {
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                const uint16_t *w = wrow_of(g0, f);
-#pragma unroll
-                for (int s = 0; s < NKW; ++s) wf[s][f] = ld8(w + 32 * s);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            wait_vm<NKW * NF>();  // everything before the weights
-        } else {
-            wait_vm<0>();
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int s = 0; s < NKW; ++s)
-            xr[s][mt] = *(const bf16x8 *)(xw + rho * XROW + (((4 * s + q) ^ xswz(rho)) << 4));
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the LDS rows may be overwritten
-        __builtin_amdgcn_sched_barrier(0);
+    for (int i = 0; i < 4 * NP; ++i) {
+        const int r = min(8 * i + (lane >> 3), 2 * R - 1), gp = g0 + (r < R ? r : r - R);
+        const int row = (gp >> 6) * 128 + (gp & 63) + (r < R ? 0 : 64) - row0;
+        woff[i] = (uint32_t)row * (uint32_t)(2 * p.K) + (((lane & 7) ^ ((8 * i + (lane >> 3)) >> 1 & 7)) << 4);
     }
-    __builtin_amdgcn_s_barrier();  // the partial tiles reuse the area
-
-    // In the epilogue wave e < 4 MT finishes register r = e & 3 of window tile e >> 2; its lanes hold pair 4 q + r of an
-    // item (NF = 1: pair 4 (q & 1) + r, lanes q >= 2 the partner).
-    const int mt_e = wave >> 2, r_e = wave & 3;
-    const int m = 16 * mt_e + rho, mm = min(m, p.M - 1);
-    const int b = mm / p.A, a = mm - b * p.A;
-    const int pp = p.pos ? p.pos[mm] : p.win_start + a;
-    const bool valid = pp >= 0 && pp < G.max_seq;
-    const int pair_e = NF == 1 ? 4 * (q & 1) + r_e : 4 * q + r_e;
-
-    f32x4 acc[NF][MT];
 #pragma unroll
-    for (int f = 0; f < NF; ++f)
+    for (int i = 0; i < 2 * MT; ++i) {
+        const int r = 8 * i + (lane >> 3);
+        xoff[i] = (uint32_t)min(r, p.M - 1) * (uint32_t)(2 * p.K) + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+    }
+    const int turn0 = p.K % 4096 == 0 ? (blockIdx.x >> 3) & 7 : 0;  // n_stages is a multiple of 8 there
+    auto issue = [&](int st) {
+        st += turn0;
+        if (st >= n_stages) st -= n_stages;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[f][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    int buf = 0;
-    auto item = [&](int g, auto more) {
-        constexpr bool MORE = decltype(more)::value;
-        // what the epilogue needs besides, while the weights are on their way
-        const int gp = min(g + pair_e, g1 - 1), hs = gp >> 6, i = gp & 63;
-        float bs[2] = {0.f, 0.f};
+        for (int i = 0; i < 4 * NP; ++i)
+            if (i < n_wl) load_lds16p(wbase + (size_t)st * 128 + woff[i], wbuf + 1024 * i);
+#pragma unroll
+        for (int i = 0; i < 2 * MT; ++i) load_lds16p(xbase + (size_t)st * 128 + xoff[i], xbuf + 1024 * i);
+    };
+    // The epilogue goes by tasks of 16 pairs in four window rows, lane = (row, pair), dealt to the waves.  Positions and
+    // bias are asked for first; the first task's angle comes while the last stage is on its way.
+    constexpr int TASKS = (NP * MT + 1) / 2;
+    int pp[TASKS];
+    uint16_t bs[TASKS][2];
+    auto task_row = [&](int j) { return 4 * ((wave + 8 * j) % (4 * MT)) + q; };
+    auto task_pair = [&](int j) { return 16 * ((wave + 8 * j) / (4 * MT)) + rho; };
+#pragma unroll
+    for (int j = 0; j < TASKS; ++j) {
+        const int mm = min(task_row(j), p.M - 1), gp = g0 + min(task_pair(j), R - 1);
+        pp[j] = p.pos ? p.pos[mm] : p.win_start + mm - (int)quotient(mm, p.div_a) * p.A;
+        bs[j][0] = bs[j][1] = 0;
         if (p.bias) {
-            bs[0] = fc_to_float(bf16_t{p.bias[hs * 128 + i]});
-            bs[1] = fc_to_float(bf16_t{p.bias[hs * 128 + i + 64]});
+            bs[j][0] = p.bias[(gp >> 6) * 128 + (gp & 63)];
+            bs[j][1] = p.bias[(gp >> 6) * 128 + (gp & 63) + 64];
         }
-        double f = 0.15915494309189533576888;  // base^(-i/64) / (2 pi): turns per position
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    issue(0);
+    __builtin_amdgcn_sched_barrier(0);
+    auto angle = [&](int j) {
+        const int i = (g0 + task_pair(j)) & 63;
+        double f = 0.15915494309189533576888;  // base^(-i/64) / (2 pi): turns per position of pair i
 #pragma unroll
         for (int bit = 0; bit < 6; ++bit)
             if (i & (1 << bit)) f *= p.rot[bit];
-        const double turns = (double)pp * f;
-        const float fr = (float)(turns - rint(turns));
-        const bool rotate = hs < G.Hq + G.Hkv;
-        const float cs = rotate ? __builtin_amdgcn_cosf(fr) : 1.f, sn = rotate ? __builtin_amdgcn_sinf(fr) : 0.f;
-        __builtin_amdgcn_sched_barrier(0);
+        const double turns = (double)pp[j] * f;
+        return (float)(turns - rint(turns));
+    };
+    float first_angle = 0.f;
 
-        const uint16_t *nxt[NF];
+    auto frag = [&](const unsigned char *buf, int row, int s) {
+        return *(const bf16x8 *)(buf + row * 128 + (((4 * s + q) ^ ((row >> 1) & 7)) << 4));
+    };
+    f32x4 acc[NP][2][MT];
 #pragma unroll
-        for (int f2 = 0; f2 < NF; ++f2)
-            if (MORE) nxt[f2] = wrow_of(g + 8 * NF, f2);
+    for (int t = 0; t < NP; ++t)
 #pragma unroll
-        for (int s = 0; s < NKW; ++s)
+        for (int f = 0; f < 2; ++f)
 #pragma unroll
-            for (int f2 = 0; f2 < NF; ++f2) {
+            for (int mt = 0; mt < MT; ++mt) acc[t][f][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int st = 0; st < n_stages; ++st) {
+        if (st == n_stages - 1) first_angle = angle(0);
+        wait_vm<0>();
+        __builtin_amdgcn_sched_barrier(0);
+        bf16x8 xf[2][MT], wf[2][NP][2];
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    acc[f2][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[s][f2], xr[s][mt], acc[f2][mt], 0, 0, 0);
-                if (MORE) wf[s][f2] = ld8(nxt[f2] + 32 * s);
-            }
+        for (int s = 0; s < 2; ++s) {
 #pragma unroll
-        for (int f2 = 0; f2 < NF; ++f2)
+            for (int mt = 0; mt < MT; ++mt) xf[s][mt] = frag(xbuf, 16 * mt + rho, s);
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    red[buf][wave][f2][mt * 4 + r][lane] = acc[f2][mt][r];
-                    acc[f2][mt][r] = 0.f;
-                }
-        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the tile is in LDS
-        __builtin_amdgcn_s_barrier();
-        if (wave < 4 * MT) {
-            float y0 = 0.f, y1 = 0.f;  // NF = 1: own value and partner's; NF = 2: first row and partner
-#pragma unroll
-            for (int w2 = 0; w2 < 8; ++w2) {
-                y0 += red[buf][w2][0][wave][lane];
-                y1 += NF == 1 ? red[buf][w2][0][wave][lane ^ 32] : red[buf][w2][NF - 1][wave][lane];
-            }
-            const bool second = NF == 1 && q >= 2;
-            y0 += second ? bs[1] : bs[0];
-            y1 += second ? bs[0] : bs[1];
-            const uint16_t o0 = fc_bf16_bits(second ? y0 * cs + y1 * sn : y0 * cs - y1 * sn);
-            const uint16_t o1 = fc_bf16_bits(y1 * cs + y0 * sn);
-            const int d0 = i + (second ? 64 : 0);
-            if (m < p.M && g + pair_e < g1) {
-                if (hs < G.Hq) {
-                    uint16_t *d = p.Q + (((size_t)b * G.Hq + hs) * p.A + a) * 128;
-                    d[d0] = valid ? o0 : 0;
-                    if (NF == 2) d[i + 64] = valid ? o1 : 0;
-                } else if (valid) {
-                    const bool is_k = hs < G.Hq + G.Hkv;
-                    const int j = hs - G.Hq - (is_k ? 0 : G.Hkv);
-                    uint16_t *base = is_k ? p.Kc : p.Vc;
-                    base[is_k ? fc_k_index(G, b, j, pp, d0) : fc_v_index(G, b, j, pp, d0)] = o0;
-                    if (NF == 2) base[is_k ? fc_k_index(G, b, j, pp, i + 64) : fc_v_index(G, b, j, pp, i + 64)] = o1;
-                }
+            for (int t = 0; t < NP; ++t) {
+                const int row = min(16 * t + rho, R - 1);
+                wf[s][t][0] = frag(wbuf, row, s);
+                wf[s][t][1] = frag(wbuf, R + row, s);
             }
         }
-        buf ^= 1;
-    };
-    if constexpr (NF == 1)
-        for (; g0 + 8 < g1; g0 += 8) item(g0, std::true_type());
-    item(g0, std::false_type());
+        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the areas may be overwritten
+        __builtin_amdgcn_sched_barrier(0);
+        if (st + 1 < n_stages) issue(st + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int t = 0; t < NP; ++t)
+#pragma unroll
+                for (int f = 0; f < 2; ++f)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+                        acc[t][f][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[s][t][f], xf[s][mt], acc[t][f][mt], 0, 0, 0);
+    }
+    // [pair tile][window tile][first / partner][lane] in the wave's own area, quarters 64 bytes apart for the reads below
+#pragma unroll
+    for (int t = 0; t < NP; ++t)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int f = 0; f < 2; ++f) *(f32x4 *)(xbuf + ((t * MT + mt) * 2 + f) * 1280 + q * 320 + rho * 16) = acc[t][f][mt];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < TASKS; ++j) {
+        const int m = task_row(j), pr = task_pair(j);
+        if (4 * ((wave + 8 * j) % (4 * MT)) >= p.M || (wave + 8 * j) / (4 * MT) >= NP) continue;
+        const unsigned char *part = lds + (((pr >> 4) * MT + (m >> 4)) * 2) * 1280 + ((pr & 15) >> 2) * 320 + (m & 15) * 16 + (pr & 3) * 4;
+        float y0 = 0.f, y1 = 0.f;
+#pragma unroll
+        for (int w2 = 0; w2 < 8; ++w2) {
+            y0 += *(const float *)(part + w2 * p.wave_bytes);
+            y1 += *(const float *)(part + w2 * p.wave_bytes + 1280);
+        }
+        if (m >= p.M || pr >= R) continue;
+        const int gp = g0 + pr, hs = gp >> 6, i = gp & 63;
+        y0 += fc_to_float(bf16_t{bs[j][0]});
+        y1 += fc_to_float(bf16_t{bs[j][1]});
+        if (hs < G.Hq + G.Hkv) {
+            const float turn = j ? angle(j) : first_angle;
+            const float cs = __builtin_amdgcn_cosf(turn), sn = __builtin_amdgcn_sinf(turn);
+            const float r0 = y0 * cs - y1 * sn, r1 = y1 * cs + y0 * sn;
+            y0 = r0;
+            y1 = r1;
+        }
+        const int b = (int)quotient(m, p.div_a), a = m - b * p.A;
+        const bool valid = pp[j] >= 0 && pp[j] < G.max_seq;
+        const uint16_t o0 = fc_bf16_bits(y0), o1 = fc_bf16_bits(y1);
+        if (hs < G.Hq) {
+            uint16_t *d = p.Q + (((size_t)b * G.Hq + hs) * p.A + a) * 128 + i;
+            d[0] = valid ? o0 : 0;
+            d[64] = valid ? o1 : 0;
+        } else if (valid) {
+            const bool is_k = hs < G.Hq + G.Hkv;
+            const int kv = hs - G.Hq - (is_k ? 0 : G.Hkv);
+            uint16_t *base = is_k ? p.Kc : p.Vc;
+            base[is_k ? fc_k_index(G, b, kv, pp[j], i) : fc_v_index(G, b, kv, pp[j], i)] = o0;
+            base[is_k ? fc_k_index(G, b, kv, pp[j], i + 64) : fc_v_index(G, b, kv, pp[j], i + 64)] = o1;
+        }
+    }
 }
 
-template <int MT, int NKW, int NF>
-hipError_t launch_rows(const ProjArgs &a, hipStream_t s)
+template <int MT, int NP>
+hipError_t launch_stream(ProjArgs a, int grid, hipStream_t s)
 {
-    constexpr int X = 8 * 16 * NKW * 64, RED = 2 * 8 * NF * MT * 4 * 64 * 4, LDS = X > RED ? X : RED;
-    static hipError_t attr = hipFuncSetAttribute((const void *)k_proj_rows<MT, NKW, NF>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+    const int run = (a.n_tiles * 8 + grid - 1) / grid;
+    const int ring = MT * 2048 + (2 * run + 7) / 8 * 1024;
+    const int state = NP * 2 * MT * 1280;
+    a.wave_bytes = ring > state ? ring : state;
+    if (run > 16 * NP || a.wave_bytes > 20 * 1024) return hipErrorInvalidValue;
+    a.div_grid = reciprocal(grid);
+    a.div_a = reciprocal(a.A);
+    static hipError_t attr = hipFuncSetAttribute((const void *)k_proj_stream<MT, NP>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return attr;
-    const int groups = a.n_tiles;  // of eight pairs
-    k_proj_rows<MT, NKW, NF><<<dim3((unsigned)(groups < 256 ? groups : 256)), dim3(512), LDS, s>>>(a);
+    k_proj_stream<MT, NP><<<dim3((unsigned)grid), dim3(512), 8 * a.wave_bytes, s>>>(a);
     return hipGetLastError();
 }
 
-// Two operands (one item of up to 16 pairs) where the runs are of 9 .. 16 pairs: with one they would be two items, the
-// second nearly empty (36 head slots, hidden 3584, 32 rows: 11.3 against 11.9 us).  At hidden 4096 they do not fit in
-// registers.
+// Runs of at least four pairs: with fewer the window rows are fetched for too little.
 template <int MT>
-hipError_t launch_rows_mt(const ProjArgs &a, hipStream_t s)
+hipError_t launch_stream_mt(const ProjArgs &a, hipStream_t s)
 {
-    const int run = (a.n_tiles * 8 + 255) / 256;
-    if (a.K == 512) return launch_rows<MT, 2, 1>(a, s);
-    if (a.K == 4096) return launch_rows<MT, 16, 1>(a, s);
-    return run > 8 && run <= 16 ? launch_rows<MT, 14, 2>(a, s) : launch_rows<MT, 14, 1>(a, s);
+    const int n_pairs = a.n_tiles * 8, grid = n_pairs < 1024 ? n_pairs / 4 : 256;
+    if ((n_pairs + grid - 1) / grid <= 16) return launch_stream<MT, 1>(a, grid, s);
+    if constexpr (MT <= 2) return launch_stream<MT, 2>(a, grid, s);
+    return hipErrorInvalidValue;
 }
 
-bool rows_covers(int M, int K) { return M <= 32 && (K == 512 || K == 3584 || K == 4096); }
+// Two operands (more than 64 head slots) lose to the tiled GEMM beyond 32 rows and, past 96 slots, at small hidden
+// sizes (us, GEMM second): 96 slots, hidden 3584, 32 / 48 / 64 rows 18.9 / 21.6 / 24.0 and 22.6 / 22.3 / 23.4; 128 slots, 16 rows,
+// hidden 2048 / 3584 16.3 / 22.0 and 13.9 / 24.  One operand loses beyond 64 rows where the hidden dimension is short (24 slots,
+// hidden 512, 96 rows 6.2 and 5.5).
+bool stream_covers(int slots, int M, int K)
+{
+    return K % 512 == 0 && (slots <= 64 ? M <= (K <= 1024 ? 64 : 96) : M <= 32 && (slots <= 96 || (slots <= 128 && K >= 3584)));
+}
 
 size_t headsplit_bytes(int slots, int M, int K)
 {
@@ -545,7 +577,7 @@ size_t headsplit_bytes(int slots, int M, int K)
 
 bool headsplit_covers(int slots, int M, int K)
 {
-    return !fc_knobs().proj_no_headsplit && M <= 128 && K % HS_K == 0 && headsplit_bytes(slots, M, K) <= FC_SCRATCH_BYTES;
+    return !fc_knobs().proj_no_headsplit && M > 32 && M <= 128 && K % HS_K == 0 && headsplit_bytes(slots, M, K) <= FC_SCRATCH_BYTES;
 }
 
 template <int MT>
@@ -575,38 +607,60 @@ bool fc_project_mfma_supported(const fc_config &cfg)
     return cfg.dtype == FC_BF16 && cfg.head_dim == 128 && cfg.hidden % 128 == 0;
 }
 
-// The head-split kernels against the tiled GEMM, by estimate (us): weights at 5 TB/s after 4 us of launch and first
-// latency, but no less than two short kernels; for every 16 rows the partial tiles, written and read back at 5.5 TB/s,
-// and the window rows.  Measured at 16 / 32 / 64 / 96 / 128 rows: 36 head slots, hidden 3584: 11.5 / 12.7 / 15.3 / 17.8 /
-// 19.6, the GEMM, whose 72 half-slab tiles leave most of the chip idle, 19.5 / 20.6 / 21.6 / 22.8 / 23.6.  96 slots,
-// hidden 4096 (three workgroups per compute unit): 27.4 / 29.9 / 38.4 at 16 / 32 / 64 rows against 25.8 / 26.5 / 27.9.
-// 12 slots, hidden 512: 9.1 / 9.5 / 10.8 against 6.2 / 6.6 / 6.8.
+// Estimates (us).
+// Head-split: weights at 5 TB/s after 4 us of launch and first latency, but no less than two short kernels; for every 16 rows
+// the partial tiles, written and read back at 5.5 TB/s, and the window rows.  Measured at 48 / 64 / 96 / 128 rows: 36 head
+// slots, hidden 3584: 13.7 / 15.1 / 17.5 / 19.2, the tiled GEMM, whose 72 half-slab tiles leave most of the chip idle,
+// 20.9 / 21.6 / 22.8 / 23.6.  96 slots, hidden 4096 (three workgroups per compute unit), 64 rows: 38.4 against 27.9.
+static double headsplit_us(int slots, int M, int K)
+{
+    const double weights = 256.0 * slots * K, part = (double)headsplit_bytes(slots, 16, K);
+    return fmax(8.5, 4.0 + weights / 5.0e6) + (M + 15) / 16 * (0.5 + 2.0 * part / 5.5e6);
+}
+
+// Tile kernel of small problems: a wave's chain along the hidden dimension rules it out where that is long.
+static double tile_us(int slots, int M, int K)
+{
+    const double weights = 128e-6 * (double)K * slots;  // millions
+    return K > 3072 || weights > 13.0 ? 1e30 : fmax(4.0, 3.2 + 0.032 * M * weights);
+}
+
+// Whole rows: launch and epilogue, the window rows' way into a compute unit, weights at 6.9 TB/s (6 % from the measured times in
+// the mean at hidden 512 .. 8192, 6 .. 64 head slots, 4 .. 96 rows).
+static double stream_us(int slots, int M, int K)
+{
+    return 2.34 + (M + 15) / 16 * (0.27 + 0.00039 * K) + 3.73e-5 * K * slots;
+}
+
+// Up to 32 rows nothing else is faster by more than 0.1 us.  Beyond, head-split gains where slots are few and the hidden
+// dimension long (24 slots, 64 rows, hidden 3584 / 5120 / 8192: whole rows 12.3 / 16.7 / 23.7, head-split 13.4 / 15.0 / 20.9) and
+// the tile kernel where all is small (6 slots, hidden 512, 96 rows 5.6 and 4.7).
+static bool stream_wins(int slots, int M, int K)
+{
+    return stream_covers(slots, M, K) && (M <= 32 || stream_us(slots, M, K) < fmin(0.94 * headsplit_us(slots, M, K), tile_us(slots, M, K)));
+}
+
 bool fc_project_prefers_gemm(const fc_config &cfg, int M, bool scratch)
 {
     if (!fc_project_gemm_supported(cfg, M)) return false;
     if (fc_knobs().proj_gemm_shape >= 0 && M > 32) return true;  // tuning knob
-    if (rows_covers(M, cfg.hidden)) return false;
-    const int slots = cfg.n_q_heads + 2 * cfg.n_kv_heads, mt = (M + 15) / 16;
-    if (!scratch || !headsplit_covers(slots, M, cfg.hidden)) return M > 32;
-    const double weights = 256.0 * slots * cfg.hidden, part = (double)headsplit_bytes(slots, 16, cfg.hidden);
-    const double us = fmax(8.5, 4.0 + weights / 5.0e6) + mt * (0.5 + 2.0 * part / 5.5e6);
-    return us > fc_project_gemm_us(slots, M, cfg.hidden);
+    const int slots = cfg.n_q_heads + 2 * cfg.n_kv_heads;
+    if (stream_wins(slots, M, cfg.hidden)) return false;
+    if (!scratch || !headsplit_covers(slots, M, cfg.hidden)) return M > 32 || cfg.hidden % HS_K == 0;
+    return headsplit_us(slots, M, cfg.hidden) > fc_project_gemm_us(slots, M, cfg.hidden);
 }
 
 // Small problems: the tile kernel, by estimate.  Measured with weights from HBM (us, tile kernel first), hidden 256 .. 8192, 6 .. 48
-// head slots, 1 .. 128 rows: against the tiled GEMM, hidden 512, 12 slots, 48 / 128 rows 5.0 and 5.7 / 6.0 and 5.8;
-// against the head-split kernels, two launches, hidden 1024, 24 slots, 16 / 32 rows 5.0 and 7.6 / 6.6 and 7.8, hidden 2048 6.9 and
-// 9.6 / 10.5 and 10.0; against k_proj_skinny (hidden no multiple of 512), hidden 768, 12 slots 4.9 and 4.3 at 16 rows, 4.9 and 5.3
-// at 24.  A wave's chain along the hidden dimension is what it loses by: 6 slots, 8 rows, hidden 3072 7.5 and 9.2, 5120 10.8
-// and 10.2, 8192 14.6 and 10.1; 48 slots, hidden 2560 13.2 and 11.2.
+// head slots, 1 .. 128 rows: against the tiled GEMM, hidden 512, 12 slots, 128 rows 5.7 and 5.8; against k_proj_skinny
+// (hidden no multiple of 512), hidden 768, 12 slots 4.9 and 4.3 at 16 rows, 4.9 and 5.3 at 24.
 bool fc_project_prefers_tile(const fc_config &cfg, int M)
 {
-    if (cfg.dtype != FC_BF16 || cfg.head_dim != 128 || fc_knobs().proj_gemm_shape >= 0 || rows_covers(M, cfg.hidden)) return false;
-    const double weights = 128e-6 * (double)cfg.hidden * (cfg.n_q_heads + 2 * cfg.n_kv_heads);  // millions
+    const int slots = cfg.n_q_heads + 2 * cfg.n_kv_heads;
+    if (cfg.dtype != FC_BF16 || cfg.head_dim != 128 || fc_knobs().proj_gemm_shape >= 0 || stream_wins(slots, M, cfg.hidden)) return false;
     const bool skinny = M <= 32 && cfg.hidden % HS_K != 0;
-    if (cfg.hidden > 3072 || weights > 13.0 || (skinny && M <= 16)) return false;
+    if (skinny && M <= 16) return false;
     const double other = skinny ? 3.55 + 0.002 * cfg.hidden : 3.9 + 0.0043 * (cfg.hidden < 1024 ? cfg.hidden : 1024);
-    return fmax(4.0, 3.2 + 0.032 * M * weights) < 0.97 * other;
+    return tile_us(slots, M, cfg.hidden) < 0.97 * other;
 }
 
 hipError_t fc_launch_project_mfma(const FcGeom &G, const void *x, const void *w, const void *bias,
@@ -631,12 +685,19 @@ hipError_t fc_launch_project_mfma(const FcGeom &G, const void *x, const void *w,
     a.partials = (float *)scratch;
     for (int i = 0; i < 6; ++i) a.rot[i] = exp(-G.log_base * (1 << i) / 64.0);
     const int slots = G.Hq + 2 * G.Hkv, mt = (a.M + 15) / 16;
-    if (rows_covers(a.M, a.K)) return mt == 1 ? launch_rows_mt<1>(a, s) : launch_rows_mt<2>(a, s);
+    if (stream_wins(slots, a.M, a.K)) {
+        switch (mt) {
+        case 1: return launch_stream_mt<1>(a, s);
+        case 2: return launch_stream_mt<2>(a, s);
+        case 3: return launch_stream_mt<3>(a, s);
+        case 4: return launch_stream_mt<4>(a, s);
+        case 5: return launch_stream_mt<5>(a, s);
+        default: return launch_stream_mt<6>(a, s);
+        }
+    }
     if (scratch && headsplit_covers(slots, a.M, a.K)) {
         a.mt = mt;
         switch (mt) {
-        case 1: return launch_headsplit<1>(a, slots, s);
-        case 2: return launch_headsplit<2>(a, slots, s);
         case 3: return launch_headsplit<3>(a, slots, s);
         case 4: return launch_headsplit<4>(a, slots, s);
         case 5: return launch_headsplit<5>(a, slots, s);

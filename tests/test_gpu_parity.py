@@ -306,6 +306,21 @@ def test_short_window_projection_bias_and_scattered_positions(B, d, Hq, Hkv, L, 
     g.close()
 
 
+@pytest.mark.parametrize("B,d,Hq,Hkv,L,A", [
+    (3, 512, 3, 1, 40, 11),      # 5 head slots: runs of four pairs, three tiles of window rows
+    (1, 1024, 15, 1, 40, 1),     # 17 head slots: runs of four and five pairs that end inside a head
+    (3, 1024, 8, 2, 33, 21),     # 63 rows
+    (3, 2048, 28, 4, 40, 32),    # 96 rows, runs of nine pairs
+    (5, 1536, 10, 2, 40, 16),    # 80 rows
+    (1, 4096, 48, 8, 40, 17),    # 64 head slots, runs of 16 pairs; workgroups start at different stages
+    (1, 512, 60, 3, 40, 31),     # 66 head slots, two operands
+    (2, 3584, 64, 32, 40, 16),   # 128 head slots, runs of 32 pairs
+])
+def test_short_window_projection_by_runs_of_pairs(B, d, Hq, Hkv, L, A):
+    """Ends of the runs, of the window tiles and of the covered range, with bias, contiguous and scattered positions."""
+    test_short_window_projection_bias_and_scattered_positions(B, d, Hq, Hkv, L, A)
+
+
 def test_scattered_positions_padding_and_bit_exact_scatter():
     """Arbitrary pos lists, padded rows, and the scatter as a pure bit copy (identity weights)."""
     dtype, B, Dh, Smax, A = "bf16", 2, 128, 210, 24
