@@ -969,8 +969,10 @@ hipError_t launch_tile_u(TileArgs a, int n_tiles, hipStream_t s)
 // registers: four workgroups per compute unit; 138 rows x 3072 x 512 took 28 us in tiles of 64 rows, 200 registers),
 // and 64 rows x two weight tiles, which halve the traffic, only for many rounds of workgroups.  A long hidden dimension
 // with few workgroups keeps four blocks in flight per wave instead of two (with two weight tiles as well that costs more
-// than it brings: 20 x 3584 x 9001 in bf16 27.1 us with two, 32.3 with four).  The vocabulary takes two weight tiles
-// always: its parts are workspace.
+// than it brings: 20 x 3584 x 9001 in bf16 27.1 us with two, 32.3 with four).  Not so bf16 in tiles of 32 rows: with four
+// blocks the compiler (clang 22, ROCm 7.2) hands registers of waiting X fragments to address arithmetic (v[10:17] in the
+// loop of the residual layer), and every result is wrong.  The vocabulary takes two weight tiles always: its parts are
+// workspace.
 template <typename T, int EPI>
 hipError_t launch_tile_t(const TileArgs &a, int n_tiles, hipStream_t s)
 {
@@ -979,8 +981,11 @@ hipError_t launch_tile_t(const TileArgs &a, int n_tiles, hipStream_t s)
     auto wgs = [&](int mt) { return blocks * ((a.M + 16 * mt - 1) / (16 * mt)); };
     const bool deep = NT == 1 && (a.K + 4 * Op<T>::KB - 1) / (4 * Op<T>::KB) >= 8 * TW;
     if (a.M > 32 && wgs(2) >= 4096) return launch_tile_u<T, 2, 4, 2, EPI>(a, n_tiles, s);
-    if (a.M > 16 && wgs(2) >= 256)
-        return deep && wgs(2) <= 512 ? launch_tile_u<T, NT, 2, 4, EPI>(a, n_tiles, s) : launch_tile_u<T, NT, 2, 2, EPI>(a, n_tiles, s);
+    if (a.M > 16 && wgs(2) >= 256) {
+        if constexpr (sizeof(T) == 4)
+            if (deep && wgs(2) <= 512) return launch_tile_u<T, NT, 2, 4, EPI>(a, n_tiles, s);
+        return launch_tile_u<T, NT, 2, 2, EPI>(a, n_tiles, s);
+    }
     return deep && wgs(1) <= 512 ? launch_tile_u<T, NT, 1, 4, EPI>(a, n_tiles, s) : launch_tile_u<T, NT, 1, 2, EPI>(a, n_tiles, s);
 }
 

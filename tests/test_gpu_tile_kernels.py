@@ -116,3 +116,28 @@ def test_linear_layers_match_oracle(dtype, M, K, N):
     assert_close(inputs.as_oracle(out), orc.linear_residual(xo, wo, inputs.as_oracle(r), dtype), dtype, "linear")
     fc.fc_ffn_gate_up(dtype, xd, wd, w2d, M, K, N, out, None, 0)
     assert_close(inputs.as_oracle(out), orc.ffn_gate_up(xo, wo, w2o, dtype), dtype, "gate_up")
+
+
+@pytest.mark.parametrize("dtype,M,K,N", [
+    ("bf16", 17, 2056, 4096), ("bf16", 64, 2056, 2048), ("bf16", 32, 2048, 4096), ("bf16", 9, 2056, 40), ("f32", 33, 1032, 2048),
+])
+def test_linear_layers_with_long_chains(dtype, M, K, N):
+    """At least eight blocks of the hidden dimension per wave, one and two tiles of window rows, whole rounds of workgroups."""
+    print("[case]", dtype, M, K, N, flush=True)
+    x, r = inputs.normal(2, "x", (M, K), 1.0, dtype), inputs.normal(2, "r", (M, N), 1.0, dtype)
+    w, w2 = inputs.normal(2, "w", (N, K), 0.02, dtype), inputs.normal(2, "w2", (N, K), 0.02, dtype)
+    xd, wd, w2d, rd = (t.to(DEV) for t in (x, w, w2, r))
+    xo, wo, w2o = (inputs.as_oracle(t) for t in (x, w, w2))
+    out = torch.full((M, N), float("nan"), dtype=xd.dtype, device=DEV)
+    ws = torch.empty(max(16, fc.fc_linear_workspace_bytes(dtype, M, K, 2 * N)), dtype=torch.uint8, device=DEV)
+    fc.fc_linear_residual(dtype, xd, wd, rd, M, K, N, out, ws)
+    assert_close(inputs.as_oracle(out), orc.linear_residual(xo, wo, inputs.as_oracle(r), dtype), dtype, "linear")
+    fc.fc_ffn_gate_up(dtype, xd, wd, w2d, M, K, N, out, ws)
+    assert_close(inputs.as_oracle(out), orc.ffn_gate_up(xo, wo, w2o, dtype), dtype, "gate_up")
+
+
+@pytest.mark.parametrize("dtype,B,d,Hq,Hkv,Dh,L,A", [
+    ("bf16", 1, 2056, 62, 1, 64, 10, 20), ("f32", 1, 1032, 62, 1, 64, 10, 20), ("bf16", 1, 2056, 4, 2, 64, 10, 16),
+])
+def test_projection_with_long_chains(dtype, B, d, Hq, Hkv, Dh, L, A):
+    test_step_matches_oracle(dtype, B, d, Hq, Hkv, Dh, L, A)
