@@ -879,6 +879,21 @@ size_t fc_linear_workspace_bytes(int32_t dtype, int32_t M, int32_t K, int32_t N)
 //   count; 2048 x 8192, 8 / 16 / 32 rows 11.0 and 13.5 / 12.9 and 13.6 / 17.2 and 14.8; 8192 x 1024 12.8 and 10.9 at 4 rows;
 //   18944 x 3584 28.1 and 29.4 at 4 rows, 36 and 30 at 12.  The estimate is wrong by more than 3 % (at most 8) in 4 of 386 measured
 //   cases (by products alone it was wrong in 94, by up to a factor of two).
+// Estimate of the tile kernel at up to 32 rows (us).
+static double linear_tile_us(bool gated, int M, int K, int N)
+{
+    const double weights = (gated ? 2e-6 : 1e-6) * K * (double)N;  // millions
+    const int tiles = gated ? (N + 7) / 8 : (N + 15) / 16, passes = M > 16 && tiles < 256 ? 2 : 1;  // over the weights
+    const int wgs = tiles * passes;
+    const double uneven = wgs > 256 ? (double)((wgs + 255) / 256 * 256) / wgs : 1.0, chain = K / 1024.0;
+    return fmax(4.7, 3.5 + fmax(1.1 * chain, 0.31 * weights * passes * uneven) + (M - 1) * fmax(0.052 * chain, 0.0125 * weights * uneven));
+}
+
+static double linear_slices_us(bool gated, int M, int K, int N)
+{
+    return 8.3 + (gated ? 0.62e-6 : 0.31e-6) * K * (double)N + (M > 16 ? 0.5 : 0.0);
+}
+
 static bool linear_prefers_tile(int dtype, int mode, int M, int K, int N, const FcWidePlan &wide, const FcSkinnyPlan &skinny)
 {
     if (dtype != FC_BF16 || fc_knobs().lin_wide_shape >= 0 || fc_knobs().lin_ksplit > 0 || fc_knobs().lin_wgs > 0 ||
@@ -889,11 +904,45 @@ static bool linear_prefers_tile(int dtype, int mode, int M, int K, int N, const 
     if (wide.kind == 1)
         return K <= 2048 && fmax(4.4, 3.2 + 0.027 * M * weights) < 0.97 * (3.5 + 0.0034 * (K < 1024 ? K : 1024));
     if (skinny.kind != 1) return false;
-    const int tiles = gated ? (N + 7) / 8 : (N + 15) / 16, passes = M > 16 && tiles < 256 ? 2 : 1;  // over the weights
-    const int wgs = tiles * passes;
-    const double uneven = wgs > 256 ? (double)((wgs + 255) / 256 * 256) / wgs : 1.0, chain = K / 1024.0;
-    const double tile = 3.5 + fmax(1.1 * chain, 0.31 * weights * passes * uneven) + (M - 1) * fmax(0.052 * chain, 0.0125 * weights * uneven);
-    return fmax(4.7, tile) < 0.97 * (8.3 + 0.31 * weights + (M > 16 ? 0.5 : 0.0));
+    return linear_tile_us(gated, M, K, N) < 0.97 * linear_slices_us(gated, M, K, N);
+}
+
+// The kernel for few outputs, one launch with every window row in every workgroup, against what the problem would take
+// otherwise.  Both sides measured, weights from HBM, hidden 512 .. 18944, 256 .. 8192 outputs, 4 .. 96 rows (us, this kernel
+// first):
+//   up to 32 rows it takes the whole-row kernel's place (3584 x 3584 7.0 / 7.1 / 8.1 and 7.8 / 8.5 / 9.9 at 4 / 16 / 32 rows; hidden
+//   512 with less than two million weights is a draw), and the tiled GEMM's except gated at hidden 4096 beyond 7168 outputs
+//   (8192: 27.7 and 24.0) and where the window rows outweigh the weights (18944 x 3584, 32 rows: 36.3 and 29.9); the tile and
+//   the slice-wise kernel by estimate (2048 x 4096, 32 rows 5.7 and 8.4; 8192 x 3584, 4 rows 14.9 and 13.9; 12288 x 2048
+//   18.6 and 15.4; 18944 x 8192, 16 rows 52.2 and 57.9), small problems at hidden 1024 stay in the tile kernel (1024 x 1024
+//   4.5 and 4.3);
+//   beyond 32 rows the tiled GEMM cuts the hidden dimension of W_out and W_2, so this kernel gains as long as rows x hidden is
+//   small (3584 x 3584, 48 / 64 / 96 rows 9.5 / 10.9 / 14.2 and 10.9 / 11.3 / 12.8; 2048 x 2048 5.4 / 6.3 / 8.2 and 7.9 / 8.3 / 9.6; 4096 x
+//   1024, 64 rows 8.6 and 9.3); gated layers of few outputs leave it few workgroups at any hidden size (2048 x 2048, 64 rows 7.2
+//   and 13.7; 8192 x 2048, 96 rows 32.4 and 36.1; 4096 x 6144, 48 rows 21.5 and 24.3; 3584 x 8192 24.4 and 23.7); and widths that
+//   are no whole slabs would go to the tile kernel (3584 x 6000, 40 rows 12.3 and 29.0).
+static bool linear_prefers_lines(int dtype, int mode, int M, int K, int N, const FcWidePlan &wide, const FcSkinnyPlan &skinny, bool tile)
+{
+    if (!fc_linear_lines_cover(dtype, mode, M, K, N) || fc_knobs().lin_wide_shape >= 0 || fc_knobs().lin_ksplit > 0 ||
+        fc_knobs().lin_wgs > 0 || fc_knobs().lin_no_rows)  // tuning knobs name the kernels
+        return false;
+    const bool gated = mode == FC_LIN_GATE_UP;
+    const double weights = (gated ? 2e-6 : 1e-6) * K * (double)N;  // millions
+    if (M > 32) {
+        if ((K <= 1024 && tile) || (K <= 512 && (M > 64 || weights > 2.7))) return false;
+        if (wide.kind == 0 && K > 1024) return true;  // else the tile kernel
+        if (gated) return N <= 4096 || (N <= 6144 && K >= 3072);
+        const int64_t rows_k = (int64_t)((M + 15) / 16) * K;
+        if (M > 64 && weights < 2.0) return false;
+        return rows_k <= (M <= 64 && N <= 2048 ? 16384 : N <= 4096 ? 14336 : 12288);
+    }
+    if (wide.kind == 1) return gated ? K % 4096 != 0 || N <= 7168 : K <= 8192;
+    if (skinny.kind == 2) return K > 512 || weights >= 2.0;
+    if (K > 8192) return (M <= 16 && N >= 5120) || skinny.kind == 0;
+    const double tile_us = linear_tile_us(gated, M, K, N);
+    if (K <= 1024 && tile_us <= 5.7) return false;
+    const double us = 2.28 + (M + 15) / 16 * (0.2 + 0.000265 * K) + 0.28 * weights + 0.00018 * K + 0.035 * fmax(0.0, weights - 33.0);
+    return us < (skinny.kind == 1 ? fmin(tile_us, linear_slices_us(gated, M, K, N)) : tile_us);
 }
 
 static fc_status linear_common(int32_t dtype, int mode, const void *x, const void *w, const void *w2,
@@ -916,7 +965,9 @@ static fc_status linear_common(int32_t dtype, int mode, const void *x, const voi
                     workspace ? workspace_bytes : (size_t)0);
     hipError_t e;
     const bool tile = linear_prefers_tile(dtype, mode, M, K, N, wide, plan);
-    if (wide.kind == 1 && !tile)
+    if (linear_prefers_lines(dtype, mode, M, K, N, wide, plan, tile))
+        e = fc_launch_linear_lines(mode, x, w, w2, res, M, K, N, out, (hipStream_t)stream);
+    else if (wide.kind == 1 && !tile)
         e = fc_launch_linear_wide(wide, mode, x, w, w2, res, M, K, N, out, workspace, (hipStream_t)stream);
     else if (plan.kind >= 1 && !tile)
         e = fc_launch_linear_skinny(plan, mode, x, w, w2, res, M, K, N, out, workspace, (hipStream_t)stream);

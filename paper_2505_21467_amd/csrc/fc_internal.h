@@ -150,6 +150,10 @@ struct FcSkinnyPlan {
     int maxseg;  // upper bound of the workgroups that meet one slab
     size_t reserve;  // kind 2: workspace asked of the caller and not used
 };
+// Layers of few outputs at up to 96 rows, one launch, no workspace: whether the kernel can, and the launch.
+bool fc_linear_lines_cover(int dtype, int mode, int M, int K, int N);
+hipError_t fc_launch_linear_lines(int mode, const void *x, const void *w, const void *w2, const void *res, int M, int K, int N,
+                                  void *out, hipStream_t s);
 FcSkinnyPlan fc_plan_skinny(int dtype, int mode, int M, int K, int N);
 size_t fc_skinny_workspace(const FcSkinnyPlan &p);
 hipError_t fc_launch_linear_skinny(const FcSkinnyPlan &pl, int mode, const void *x, const void *w,

@@ -3,9 +3,10 @@
 // (paper, Table 1, rows "Output projection", "FFN W_1", "FFN W_2" with the row count L replaced by
 // the window size A).
 //
-// With a few dozen rows the product Y^T = W X^T is bound by reading W once from HBM.  Two kernels:
-// the slice-wise one described here, for any hidden size that is a multiple of 512, and a whole-row
-// one (k_linear_rows, further down) for the hidden sizes whose X block fits in registers.  The weight
+// With a few dozen rows the product Y^T = W X^T is bound by reading W once from HBM.  Three kernels:
+// the slice-wise one described here, for any hidden size that is a multiple of 512, a whole-row
+// one (k_linear_rows, further down) for the hidden sizes whose X block fits in registers, and one for layers
+// of few outputs (k_linear_lines).  The weight
 // matrix is cut into work items of 128 rows x KSL hidden elements (every row piece is 1 KB, or 512 B,
 // of contiguous memory); the items, ordered row slab by row slab, are dealt out in equal contiguous
 // runs to one workgroup per compute unit, so the matrix streams once, evenly, whatever its shape.
@@ -42,6 +43,8 @@ struct LinArgs {
     float *partials;      // [m chunk][slab][maxseg][wave][mt][4][64]
     int M, K, N;          // N = output columns
     int S, T, G, maxseg, slabs;
+    int wave_bytes;       // k_linear_lines: LDS of a wave,
+    uint32_t div_grid;    // reciprocal of the grid
 };
 
 
@@ -520,6 +523,167 @@ hipError_t launch_rows_mode(const dim3 &g, const LinArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
+// -------------------------------------------------------------------------------------------------
+// Layers of at most 8192 outputs (two matrices: as many pairs) and 96 rows, hidden sizes that are multiples of 512.
+//
+// Every workgroup owns an equal run of outputs over the whole hidden dimension; its eight waves cut the hidden dimension, and
+// each streams its part of the run's weight rows and of the window rows through LDS of its own, 64 hidden elements (one
+// line of every row) a stage, waiting for nobody until the waves' tiles are summed.  One launch, no partial tiles in memory.
+//   * Bound by what a compute unit takes in: weights from HBM, all window rows from L2.  Direct-to-LDS loads whose lanes lie
+//     in eight whole lines run at 64 bytes per clock; straight into operand registers, sixteen rows to an instruction, a
+//     quarter of that.  So a long hidden dimension with few outputs, where the window rows outweigh the weights, is
+//     better off in parts (18944 x 3584, 32 rows: 36 us here, 30 in the tiled GEMM with its second launch).
+//   * Where weight rows lie a multiple of 8 KB apart the workgroups of a die start at eight different stages: all at the
+//     same offset they meet in a part of the memory channels.
+//   * The epilogue goes by tasks of 16 outputs of four rows, dealt to all waves; the residual is asked for at the start.
+// us at 4 / 16 / 32 / 64 rows: 3584 x 3584 7.0 / 7.1 / 8.1 / 10.9 (k_linear_rows 7.8 / 8.5 / 9.9, tiled GEMM in parts 11.3);
+// gated 3584 x 4096 11.7 / 11.9 / 13.2 / 17.3 (13.9 / 14.8 / 16.3, 21.5); gated 2048 x 2048 5.0 / 5.1 / 5.5 / 7.2 (tile kernel 5.8 /
+// 6.3, slice-wise 8.3, tiled GEMM 13.7); 8192 x 2048 11.3 / 11.6 / 12.9 (14.3 / 14.4 / 15.5).
+//
+// x / d, d given as 2^32 / d rounded up (0: d is 1); exact for x d < 2^32
+__device__ __forceinline__ uint32_t quotient(uint32_t x, uint32_t reciprocal) { return reciprocal ? __umulhi(x, reciprocal) : x; }
+
+constexpr int LINES_K = 64;  // hidden elements per stage: one 128-byte line of every row
+
+template <int MT, int NR, int MODE>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_linear_lines(LinArgs p)
+{
+    constexpr int NF = MODE == FC_LIN_GATE_UP ? 2 : 1, TASKS = (NR * MT + 1) / 2;
+    extern __shared__ __align__(1024) unsigned char lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rho = lane & 15, q = lane >> 4;
+    const int n0 = (int)quotient(blockIdx.x * (uint32_t)p.N, p.div_grid);
+    const int R = (int)quotient((blockIdx.x + 1) * (uint32_t)p.N, p.div_grid) - n0;  // outputs of this workgroup
+    const int n_stages = p.K / (8 * LINES_K);
+    const int n_wl = (R + 7) >> 3;  // loads of a stage and matrix
+    unsigned char *xbuf = lds + wave * p.wave_bytes, *wbuf = xbuf + MT * 2048;
+
+    const unsigned char *wbase[NF];
+    wbase[0] = (const unsigned char *)(p.W + (size_t)n0 * p.K) + (size_t)wave * n_stages * 128;
+    if (NF == 2) wbase[NF - 1] = (const unsigned char *)(p.W2 + (size_t)n0 * p.K) + (size_t)wave * n_stages * 128;
+    const unsigned char *xbase = (const unsigned char *)p.X + (size_t)wave * n_stages * 128;
+    uint32_t woff[2 * NR], xoff[2 * MT];
+#pragma unroll
+    for (int i = 0; i < 2 * NR; ++i) {
+        const int r = 8 * i + (lane >> 3);
+        woff[i] = (uint32_t)min(r, R - 1) * (uint32_t)(2 * p.K) + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+    }
+#pragma unroll
+    for (int i = 0; i < 2 * MT; ++i) {
+        const int r = 8 * i + (lane >> 3);
+        xoff[i] = (uint32_t)min(r, p.M - 1) * (uint32_t)(2 * p.K) + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+    }
+    const int turn0 = p.K % 4096 == 0 ? (blockIdx.x >> 3) & 7 : 0;  // n_stages is a multiple of 8 there
+    auto issue = [&](int st) {
+        st += turn0;
+        if (st >= n_stages) st -= n_stages;
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+            for (int i = 0; i < 2 * NR; ++i)
+                if (i < n_wl) load_lds16(wbase[f] + (size_t)st * 128 + woff[i], wbuf + f * (NR * 2048) + 1024 * i);
+#pragma unroll
+        for (int i = 0; i < 2 * MT; ++i) load_lds16(xbase + (size_t)st * 128 + xoff[i], xbuf + 1024 * i);
+    };
+    auto task_row = [&](int j) { return 4 * ((wave + 8 * j) % (4 * MT)) + q; };
+    auto task_col = [&](int j) { return 16 * ((wave + 8 * j) / (4 * MT)) + rho; };
+    uint16_t res[TASKS];
+#pragma unroll
+    for (int j = 0; j < TASKS; ++j)
+        res[j] = MODE == FC_LIN_RESIDUAL && p.res ? p.res[(size_t)min(task_row(j), p.M - 1) * p.N + n0 + min(task_col(j), R - 1)] : 0;
+    __builtin_amdgcn_sched_barrier(0);
+    issue(0);
+    __builtin_amdgcn_sched_barrier(0);
+
+    auto frag = [&](const unsigned char *buf, int row, int s) {
+        return *(const bf16x8 *)(buf + row * 128 + (((4 * s + q) ^ ((row >> 1) & 7)) << 4));
+    };
+    f32x4 acc[NR][NF][MT];
+#pragma unroll
+    for (int t = 0; t < NR; ++t)
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[t][f][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int st = 0; st < n_stages; ++st) {
+        wait_vm<0>();
+        __builtin_amdgcn_sched_barrier(0);
+        bf16x8 xf[2][MT], wf[2][NR][NF];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) xf[s][mt] = frag(xbuf, 16 * mt + rho, s);
+#pragma unroll
+            for (int t = 0; t < NR; ++t)
+#pragma unroll
+                for (int f = 0; f < NF; ++f) wf[s][t][f] = frag(wbuf + f * (NR * 2048), min(16 * t + rho, R - 1), s);
+        }
+        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the areas may be overwritten
+        __builtin_amdgcn_sched_barrier(0);
+        if (st + 1 < n_stages) issue(st + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int t = 0; t < NR; ++t)
+#pragma unroll
+                for (int f = 0; f < NF; ++f)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+                        acc[t][f][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[s][t][f], xf[s][mt], acc[t][f][mt], 0, 0, 0);
+    }
+#pragma unroll
+    for (int t = 0; t < NR; ++t)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int f = 0; f < NF; ++f) *(f32x4 *)(xbuf + ((t * MT + mt) * NF + f) * 1280 + q * 320 + rho * 16) = acc[t][f][mt];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < TASKS; ++j) {
+        const int m = task_row(j), c = task_col(j);
+        if (4 * ((wave + 8 * j) % (4 * MT)) >= p.M || (wave + 8 * j) / (4 * MT) >= NR) continue;
+        const unsigned char *part = lds + (((c >> 4) * MT + (m >> 4)) * NF) * 1280 + ((c & 15) >> 2) * 320 + (m & 15) * 16 + (c & 3) * 4;
+        float y[NF] = {};
+#pragma unroll
+        for (int w2 = 0; w2 < 8; ++w2)
+#pragma unroll
+            for (int f = 0; f < NF; ++f) y[f] += *(const float *)(part + w2 * p.wave_bytes + f * 1280);
+        if (m >= p.M || c >= R) continue;
+        p.out[(size_t)m * p.N + n0 + c] = fc_bf16_bits(MODE == FC_LIN_GATE_UP ? y[0] / (1.0f + expf(-y[0])) * y[NF - 1] : y[0] + fc_to_float(bf16_t{res[j]}));
+    }
+}
+
+uint32_t reciprocal(int d) { return (uint32_t)((((int64_t)1 << 32) + d - 1) / d); }
+
+template <int MT, int NR, int MODE>
+hipError_t launch_lines(LinArgs a, int grid, hipStream_t s)
+{
+    constexpr int NF = MODE == FC_LIN_GATE_UP ? 2 : 1;
+    const int ring = MT * 2048 + NF * NR * 2048, state = NR * NF * MT * 1280;
+    a.wave_bytes = ring > state ? ring : state;
+    if ((a.N + grid - 1) / grid > 16 * NR || a.wave_bytes > 20 * 1024) return hipErrorInvalidValue;
+    a.div_grid = reciprocal(grid);
+    static hipError_t attr = hipFuncSetAttribute((const void *)k_linear_lines<MT, NR, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (attr != hipSuccess) return attr;
+    k_linear_lines<MT, NR, MODE><<<dim3((unsigned)grid), dim3(512), 8 * a.wave_bytes, s>>>(a);
+    return hipGetLastError();
+}
+
+// Runs of at least four outputs: with fewer the window rows are fetched for too little.
+template <int MT>
+hipError_t launch_lines_mt(int mode, const LinArgs &a, hipStream_t s)
+{
+    const int grid = a.N < 1024 ? (a.N + 3) / 4 : 256, run = (a.N + grid - 1) / grid;
+    if (mode == FC_LIN_GATE_UP) {
+        if (run <= 16) return launch_lines<MT, 1, FC_LIN_GATE_UP>(a, grid, s);
+        if constexpr (MT <= 3) return launch_lines<MT, 2, FC_LIN_GATE_UP>(a, grid, s);
+        return hipErrorInvalidValue;
+    }
+    return run <= 16 ? launch_lines<MT, 1, FC_LIN_RESIDUAL>(a, grid, s) : launch_lines<MT, 2, FC_LIN_RESIDUAL>(a, grid, s);
+}
+
 #ifndef FC_LIN_KSL
 #define FC_LIN_KSL 512
 #endif
@@ -681,4 +845,34 @@ hipError_t fc_launch_linear_skinny(const FcSkinnyPlan &pl, int mode, const void 
         return hipGetLastError();
     }
     return mode == FC_LIN_GATE_UP ? launch_mode<FC_LIN_GATE_UP>(pl, a, s) : launch_mode<FC_LIN_RESIDUAL>(pl, a, s);
+}
+
+bool fc_linear_lines_cover(int dtype, int mode, int M, int K, int N)
+{
+    return dtype == FC_BF16 && mode != FC_LIN_VOCAB && M >= 1 && M <= 96 && K >= 512 && K % 512 == 0 && N >= 1 &&
+           N <= (mode == FC_LIN_GATE_UP && M > 48 ? 4096 : 8192);
+}
+
+hipError_t fc_launch_linear_lines(int mode, const void *x, const void *w, const void *w2, const void *res, int M, int K, int N,
+                                  void *out, hipStream_t s)
+{
+    if (!fc_linear_lines_cover(FC_BF16, mode, M, K, N)) return hipErrorInvalidValue;
+    LinArgs a;
+    memset(&a, 0, sizeof a);
+    a.X = (const uint16_t *)x;
+    a.W = (const uint16_t *)w;
+    a.W2 = (const uint16_t *)w2;
+    a.res = (const uint16_t *)res;
+    a.out = (uint16_t *)out;
+    a.M = M;
+    a.K = K;
+    a.N = N;
+    switch ((M + 15) / 16) {
+    case 1: return launch_lines_mt<1>(mode, a, s);
+    case 2: return launch_lines_mt<2>(mode, a, s);
+    case 3: return launch_lines_mt<3>(mode, a, s);
+    case 4: return launch_lines_mt<4>(mode, a, s);
+    case 5: return launch_lines_mt<5>(mode, a, s);
+    default: return launch_lines_mt<6>(mode, a, s);
+    }
 }

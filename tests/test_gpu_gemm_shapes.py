@@ -140,3 +140,24 @@ def test_problem_cut_into_two_launches(M, N, gated):
     else:
         fc.fc_linear_residual("bf16", x, w, None, M, K, N, out, ws)
     assert_close(inputs.as_oracle(out), inputs.as_oracle(ref), "bf16", "cut")
+
+
+@pytest.mark.parametrize("M,K,N,gated", [
+    (5, 3584, 1, False), (1, 1536, 1003, True),        # fewer outputs than workgroups: one workgroup, runs of three and four
+    (17, 2048, 1023, False), (33, 1536, 1027, False),  # runs of three and four, four and five; two and three tiles of rows
+    (96, 1536, 4097, False), (80, 2560, 4352, False),  # runs of 16 and 17: two weight tiles
+    (96, 2048, 4096, True), (48, 3072, 4160, True),    # pairs of 16 at six tiles of rows; two weight tiles at three
+    (64, 4096, 1024, False), (32, 4096, 8192, False),  # workgroups start at eight stages; runs of 32
+    (20, 512, 8192, True), (3, 8192, 264, False),
+    (7, 3584, 8200, False),                            # one output quad too many: whole-row kernel
+])
+def test_layers_of_few_outputs(M, K, N, gated):
+    """Ends of the runs, of the tiles of window rows and of the covered range."""
+    _linear(M, K, N, gated, "few outputs")
+    if not gated:  # without a residual
+        x, w = inputs.normal(2, "x", (M, K), 1.0, "bf16"), inputs.normal(2, "w", (N, K), 0.05, "bf16")
+        out = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=DEV)
+        ws = torch.empty(max(16, fc.fc_linear_workspace_bytes("bf16", M, K, N)), dtype=torch.uint8, device=DEV)
+        fc.fc_linear_residual("bf16", x.to(DEV), w.to(DEV), None, M, K, N, out, ws)
+        ref = orc.linear_residual(inputs.as_oracle(x), inputs.as_oracle(w), None, "bf16")
+        assert_close(inputs.as_oracle(out), ref, "bf16", "few outputs, no residual")
