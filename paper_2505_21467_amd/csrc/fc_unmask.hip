@@ -147,35 +147,132 @@ __global__ __launch_bounds__(NW * 64) void k_unmask_select(const int32_t *__rest
 // implementation details).  A row matches if the DLM's token t is among the topk best AR entries, that is, if ar[t] is a number and
 // fewer than topk AR entries come before (ar[t], t) in the order (larger value first, then smaller id).  No list of the
 // topk best is needed for that:
-//  - k_accept_scan cuts every still masked row's vocabulary into parts, 64 lanes each, and finds each part's best DLM and
-//    best AR entry: two running maxima per lane, so the scan is bound by reading the logits;
-//  - accept_rows (a wave per row) merges the parts, fetches ar[t], and counts.  Only parts whose best AR entry comes
-//    before (ar[t], t) hold any entry that does; with topk of them or more the row does not match, and else
-//    those few parts (usually none or one) are read again and counted exactly.
+//  - k_accept_scan cuts every still masked row's vocabulary into parts, a wave each, and keeps for every four parts the
+//    best DLM entry with the AR's value there and, of the other entries, the best AR entry and the second largest AR value.
+//    These are running maxima per lane, so the scan is bound by reading the logits.
+//  - accept_rows (half a wave per row) merges these records and counts.  Only a record whose best AR entry, or entry at its
+//    best DLM entry, comes before (ar[t], t) holds any that does, and just these if its second largest value is below ar[t];
+//    with topk of them or more the row does not match.  A record is read again only where fewer are certain and its second
+//    value counts or ties.
+//    With parts that held the two best entries alone, ar[t] and the parts' exact counts were two more memory round trips (us,
+//    32 rows x 2 x 152064: topk 2 18.0 -> 15.1, topk 8 22.3 -> 14.9; 64 rows 28.5 -> 22.8; 32 x 2 x 15999 13.2 -> 10.9).
 // Sorted lists per lane, merged by rounds of arg-max, took 14.8 us for the scan of 32 rows x 2 x 152064 floats (39 MB):
 // some lane of a wave updates its list at almost every step, and the whole wave pays for it.
 // Then the prefix: the longest run of matching masked rows is filled (or the first masked row), the rest listed.
 // Blocks of up to 64 rows do the last two in one kernel, one workgroup per sequence.
 constexpr int ACC_MAXK = 8;
-constexpr int ACC_PARTS = 128;      // at most, per row: two per lane of the merging wave
+constexpr int ACC_PARTS = 128;      // at most, per row
+constexpr int ACC_REC = 4;          // parts per record and workgroup of the scan: at most 32 records per row
 constexpr int ACC_FUSED_ROWS = 64;
 
 // (value, id) order: larger value first, then smaller id
 __device__ __forceinline__ bool acc_before(float v1, int i1, float v2, int i2) { return v1 > v2 || (v1 == v2 && i1 < i2); }
 
-struct AccPart {  // best entries of one part of a row; (-inf, int max) where there is none
-    float dv;
+struct AccRec {  // of four parts of a row; ids int max where there is no entry
+    float dv;        // best DLM entry,
     int di;
-    float av;
+    float dx;        // the AR's value there;
+    float av;        // of the other entries: best AR entry
     int ai;
+    float a2;        // and second largest AR value (its id is not known)
 };
+__device__ __forceinline__ AccRec acc_none()
+{
+    return AccRec{-INFINITY, 0x7fffffff, __builtin_nanf(""), -INFINITY, 0x7fffffff, -INFINITY};
+}
+__device__ __forceinline__ void acc_insert(AccRec &x, float v, int i)  // an AR entry (not a number: none)
+{
+    x.a2 = __builtin_amdgcn_fmed3f(x.av, x.a2, fmaxf(v, -INFINITY));
+    if (acc_before(v, i, x.av, x.ai)) {
+        x.av = v;
+        x.ai = i;
+    }
+}
+// The AR's entry at the lesser of the two DLM entries joins the others.
+__device__ __forceinline__ void acc_merge(AccRec &x, const AccRec &y)
+{
+    const bool second = acc_before(y.dv, y.di, x.dv, x.di);
+    const float v = second ? x.dx : y.dx;
+    const int i = second ? x.di : y.di;
+    if (second) {
+        x.dv = y.dv;
+        x.di = y.di;
+        x.dx = y.dx;
+    }
+    x.a2 = fmaxf(fmaxf(x.a2, y.a2), fminf(x.av, y.av));
+    if (acc_before(y.av, y.ai, x.av, x.ai)) {
+        x.av = y.av;
+        x.ai = y.ai;
+    }
+    acc_insert(x, v, i);
+}
+
+// Over the wave or each half: every lane ends with the merged record.  Neighbours within 16 lanes by DPP (once the lanes of a quad, or
+// of half a row, agree, the mirror image is as good a partner as lane ^ 4 or lane ^ 8), then the halves by permlane swaps;
+// through LDS (ds_bpermute) the six dependent steps cost 0.2 us more.
+template <int CTRL>
+__device__ __forceinline__ AccRec acc_dpp(const AccRec &x)
+{
+    auto mv = [](int v) { return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true); };
+    return AccRec{__int_as_float(mv(__float_as_int(x.dv))), mv(x.di), __int_as_float(mv(__float_as_int(x.dx))),
+                  __int_as_float(mv(__float_as_int(x.av))), mv(x.ai), __int_as_float(mv(__float_as_int(x.a2)))};
+}
+template <int HALF>
+__device__ __forceinline__ void acc_swap(const AccRec &x, AccRec &lo, AccRec &hi)
+{
+    auto sw = [](unsigned v, unsigned &a, unsigned &b) {
+        if constexpr (HALF == 16) {
+            const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+            a = r[0];
+            b = r[1];
+        } else {
+            const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+            a = r[0];
+            b = r[1];
+        }
+    };
+    unsigned a[6], b[6];
+    const unsigned v[6] = {__float_as_uint(x.dv), (unsigned)x.di, __float_as_uint(x.dx), __float_as_uint(x.av), (unsigned)x.ai, __float_as_uint(x.a2)};
+#pragma unroll
+    for (int i = 0; i < 6; ++i) sw(v[i], a[i], b[i]);
+    lo = AccRec{__uint_as_float(a[0]), (int)a[1], __uint_as_float(a[2]), __uint_as_float(a[3]), (int)a[4], __uint_as_float(a[5])};
+    hi = AccRec{__uint_as_float(b[0]), (int)b[1], __uint_as_float(b[2]), __uint_as_float(b[3]), (int)b[4], __uint_as_float(b[5])};
+}
+// ALL: whole records, over 64 lanes; else only the best DLM entry and the largest AR value (in av), over 32.
+template <bool ALL>
+__device__ __forceinline__ void acc_reduce(AccRec &x)
+{
+    auto merge = [](AccRec &p, const AccRec &q) {
+        if constexpr (ALL) {
+            acc_merge(p, q);
+        } else {
+            if (acc_before(q.dv, q.di, p.dv, p.di)) {
+                p.dv = q.dv;
+                p.di = q.di;
+                p.dx = q.dx;
+            }
+            p.av = fmaxf(p.av, q.av);
+        }
+    };
+    merge(x, acc_dpp<0xB1>(x));   // quad_perm [1, 0, 3, 2]
+    merge(x, acc_dpp<0x4E>(x));   // quad_perm [2, 3, 0, 1]
+    merge(x, acc_dpp<0x141>(x));  // row_half_mirror
+    merge(x, acc_dpp<0x140>(x));  // row_mirror
+    AccRec y;
+    acc_swap<16>(AccRec(x), x, y);
+    merge(x, y);
+    if constexpr (ALL) {
+        acc_swap<32>(AccRec(x), x, y);
+        merge(x, y);
+    }
+}
 
 struct AccArgs {
     const float *dlm, *ar;
     const int32_t *pos;
     int32_t *tokens;
-    AccPart *parts;                // [B][A][n_parts]
-    int win_start, A, V, chunk, n_parts, topk, mask_id, L;
+    AccRec *recs;                  // [B][A][n_recs]
+    int win_start, A, V, chunk, n_parts, n_recs, topk, mask_id, L;
     float tau;
 };
 
@@ -184,23 +281,24 @@ __device__ __forceinline__ int acc_position(const AccArgs &p, int b, int a)
     return p.pos ? p.pos[(size_t)b * p.A + a] : p.win_start + a;
 }
 
-// grid (parts / 4, A, B): 64 lanes scan entries [part * chunk, (part + 1) * chunk) of row (b, a), normally in one step
+// grid (records, A, B): each wave scans entries [part * chunk, (part + 1) * chunk) of row (b, a), normally in one step
 // with every load in flight at once.
 constexpr int ACC_LANES = 64, ACC_VEC_LOADS = 5;
+static_assert(ACC_REC * ACC_LANES == 256 && ACC_PARTS / ACC_REC <= 32, "a wave per part; a lane of half a wave per record");
 constexpr int ACC_STEP = ACC_LANES * 4 * ACC_VEC_LOADS;  // entries per step with 16-byte loads
 template <bool VEC>
 __global__ __launch_bounds__(256) void k_accept_scan(AccArgs p)
 {
     const int a = blockIdx.y, b = blockIdx.z, l = threadIdx.x % ACC_LANES;
-    const int part = blockIdx.x * (256 / ACC_LANES) + threadIdx.x / ACC_LANES;
+    const int wave = threadIdx.x / ACC_LANES, part = blockIdx.x * ACC_REC + wave;
+    __shared__ AccRec s_rec[ACC_REC];
     const size_t at = (size_t)b * p.A + a;
     const int ps = acc_position(p, b, a);
     if (!(ps >= 0 && ps < p.L && p.tokens[(size_t)b * p.L + ps] == p.mask_id)) return;  // not a candidate: nothing to scan
     const float *zd = p.dlm + at * p.V, *za = p.ar + at * p.V;
     const int v0 = min(part, p.n_parts) * p.chunk, v1 = min(p.V, v0 + p.chunk);
     constexpr int W = VEC ? 4 : 1, U = VEC ? ACC_VEC_LOADS : 10;  // entries per lane and load; loads of each array in flight
-    float dv = -INFINITY, av = -INFINITY;
-    int di = 0x7fffffff, ai = 0x7fffffff;
+    AccRec r = acc_none();
     for (int s0 = v0 + l * W; s0 < v1; s0 += ACC_LANES * W * U) {
         float d[U][W], x[U][W];
 #pragma unroll
@@ -219,129 +317,107 @@ __global__ __launch_bounds__(256) void k_accept_scan(AccArgs p)
 #pragma unroll
             for (int e = 0; e < W; ++e) {
                 const int v = s0 + u * ACC_LANES * W + e;
-                if (v < v1 && acc_before(d[u][e], v, dv, di)) {
-                    dv = d[u][e];
-                    di = v;
+                const bool in = v < v1, best = in && acc_before(d[u][e], v, r.dv, r.di);
+                const float ov = best ? r.dx : in ? x[u][e] : -INFINITY;
+                const int oi = best ? r.di : in ? v : 0x7fffffff;
+                if (best) {
+                    r.dv = d[u][e];
+                    r.di = v;
+                    r.dx = x[u][e];
                 }
-                if (v < v1 && acc_before(x[u][e], v, av, ai)) {
-                    av = x[u][e];
-                    ai = v;
-                }
+                acc_insert(r, ov, oi);
             }
     }
+    acc_reduce<true>(r);
+    if (l == 0) s_rec[wave] = r;
+    __syncthreads();
+    if (threadIdx.x) return;
 #pragma unroll
-    for (int off = ACC_LANES / 2; off > 0; off >>= 1) {
-        const float d2 = __shfl_xor(dv, off, 64), a2 = __shfl_xor(av, off, 64);
-        const int i2 = __shfl_xor(di, off, 64), j2 = __shfl_xor(ai, off, 64);
-        if (acc_before(d2, i2, dv, di)) {
-            dv = d2;
-            di = i2;
-        }
-        if (acc_before(a2, j2, av, ai)) {
-            av = a2;
-            ai = j2;
-        }
-    }
-    if (l == 0 && part < p.n_parts) p.parts[at * p.n_parts + part] = AccPart{dv, di, av, ai};
+    for (int w = 1; w < ACC_REC; ++w) acc_merge(r, s_rec[w]);
+    p.recs[at * p.n_recs + blockIdx.x] = r;
 }
 
-// One wave decides rows a0, a0 + step, .. (N of them at most) of sequence b: the DLM's token, and 1 / 0 for a match or
-// none, -1 for a row that is not a candidate.  The rows' memory round trips run together.
+// One wave decides 2 N rows, half a wave each: rows a0 + n step + (lane >> 5).  The DLM's token, and 1 / 0 for a match or none,
+// -1 for a row that is not a candidate.
 template <int N>
 __device__ __forceinline__ void accept_rows(const AccArgs &p, int b, int a0, int step, int lane, int (&tok)[N], int (&match)[N])
 {
-    AccPart pt[N][ACC_PARTS / 64];
-    float z[N], zmax[N];
+    AccRec rec[N];
     bool cand[N];
 #pragma unroll
     for (int n = 0; n < N; ++n) {
-        const int a = min(a0 + n * step, p.A - 1);
+        const int row = a0 + n * step + (lane >> 5), a = min(row, p.A - 1);
         const int ps = acc_position(p, b, a);
         const bool in = ps >= 0 && ps < p.L;
-        cand[n] = p.tokens[(size_t)b * p.L + (in ? ps : 0)] == p.mask_id && in && a0 + n * step < p.A;
-#pragma unroll
-        for (int g = 0; g < ACC_PARTS / 64; ++g)
-            pt[n][g] = 64 * g + lane < p.n_parts ? p.parts[((size_t)b * p.A + a) * p.n_parts + 64 * g + lane]
-                                                 : AccPart{-INFINITY, 0x7fffffff, -INFINITY, 0x7fffffff};
+        cand[n] = p.tokens[(size_t)b * p.L + (in ? ps : 0)] == p.mask_id && in && row < p.A;
+        rec[n] = (lane & 31) < p.n_recs ? p.recs[((size_t)b * p.A + a) * p.n_recs + (lane & 31)] : acc_none();
     }
 #pragma unroll
     for (int n = 0; n < N; ++n) {
-        float dv = pt[n][0].dv;
-        int di = pt[n][0].di;
-        float am = pt[n][0].av;
+        AccRec all = rec[n];
+        all.av = fmaxf(all.av, all.dx);
+        acc_reduce<false>(all);
+        const float z = all.dx;  // the AR's value of the DLM's token
+        tok[n] = all.di;
+        const bool want = cand[n] && (!(p.tau > 0.0f) || all.dv > p.tau * all.av);
+        const bool at_dlm = want && rec[n].di != tok[n] && acc_before(rec[n].dx, rec[n].di, z, tok[n]);
+        const bool ahead = want && acc_before(rec[n].av, rec[n].ai, z, tok[n]);
+        const uint64_t open = __ballot(ahead && rec[n].a2 >= z), closed = __ballot(ahead) & ~open, dlm = __ballot(at_dlm);
+        const int sh = lane & 32;
+        int count = __builtin_popcount((uint32_t)(open >> sh)) + __builtin_popcount((uint32_t)(closed >> sh)) +
+                    __builtin_popcount((uint32_t)(dlm >> sh)) + __builtin_popcount((uint32_t)(__ballot(ahead && rec[n].a2 > z) >> sh));  // certain
+        const uint64_t todo = __ballot(want && (uint32_t)(open >> sh) && count < p.topk);
+        if (todo) {
+#pragma unroll 1
+            for (int h = 0; h < 64; h += 32) {
+                if (!((todo >> h) & 1)) continue;
+                const float zh = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(z), h));
+                const int th = __builtin_amdgcn_readlane(tok[n], h);
+                const float *za = p.ar + ((size_t)b * p.A + a0 + n * step + (h >> 5)) * p.V;
+                int total = __builtin_popcount((uint32_t)(closed >> h)) + __builtin_popcount((uint32_t)((dlm & ~open) >> h));
+                for (uint32_t w = (uint32_t)(open >> h); w && total < p.topk; w &= w - 1) {
+                    const int rc = __builtin_ctz(w);
+                    const int v0 = rc * ACC_REC * p.chunk, v1 = min((int64_t)p.V, (int64_t)min((rc + 1) * ACC_REC, p.n_parts) * p.chunk);
+                    int c = 0;
+                    for (int s0 = v0; s0 < v1; s0 += 2 * ACC_STEP) {  // half a record's loads in flight at once
+                        constexpr int U = 2 * ACC_STEP / 64;
+                        float x[U];
 #pragma unroll
-        for (int g = 1; g < ACC_PARTS / 64; ++g) {
-            if (acc_before(pt[n][g].dv, pt[n][g].di, dv, di)) {
-                dv = pt[n][g].dv;
-                di = pt[n][g].di;
-            }
-            am = fmaxf(am, pt[n][g].av);
-        }
+                        for (int u = 0; u < U; ++u) x[u] = za[min(s0 + 64 * u + lane, p.V - 1)];
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const float v2 = __shfl_xor(dv, off, 64);
-            const int i2 = __shfl_xor(di, off, 64);
-            am = fmaxf(am, __shfl_xor(am, off, 64));
-            if (acc_before(v2, i2, dv, di)) {
-                dv = v2;
-                di = i2;
-            }
-        }
-        tok[n] = di;
-        zmax[n] = am;
-        match[n] = !cand[n] ? -1 : (!(p.tau > 0.0f) || dv > p.tau * am) ? 1 : 0;
-        // the AR's value of the DLM's token (rows that are no candidates hold anything: stay inside the row)
-        z[n] = p.ar[((size_t)b * p.A + min(a0 + n * step, p.A - 1)) * p.V + (di >= 0 && di < p.V ? di : 0)];
-    }
-#pragma unroll
-    for (int n = 0; n < N; ++n) {
-        if (match[n] != 1) continue;  // wave-uniform
-        uint64_t ahead[ACC_PARTS / 64];
-        int count = 0;
-#pragma unroll
-        for (int g = 0; g < ACC_PARTS / 64; ++g) {
-            ahead[g] = __ballot(acc_before(pt[n][g].av, pt[n][g].ai, z[n], tok[n]));
-            count += __builtin_popcountll(ahead[g]);
-        }
-        if (count > 0 && count < p.topk) {
-            // at least one entry in each of these parts: count them all
-            const float *za = p.ar + ((size_t)b * p.A + a0 + n * step) * p.V;
-            count = 0;
-#pragma unroll
-            for (int g = 0; g < ACC_PARTS / 64; ++g)
-                for (uint64_t w = ahead[g]; w && count < p.topk; w &= w - 1) {
-                    const int v0 = (64 * g + __builtin_ctzll(w)) * p.chunk, v1 = min(p.V, v0 + p.chunk);
-                    for (int v = v0; v < v1; v += ACC_STEP) {  // a part is one step: every load in flight at once
-                        float x[ACC_STEP / 64];
-#pragma unroll
-                        for (int u = 0; u < ACC_STEP / 64; ++u) x[u] = za[min(v + 64 * u + lane, p.V - 1)];
-#pragma unroll
-                        for (int u = 0; u < ACC_STEP / 64; ++u) {
-                            const int vv = v + 64 * u + lane;
-                            count += __builtin_popcountll(__ballot(vv < v1 && acc_before(x[u], vv, z[n], tok[n])));
+                        for (int u = 0; u < U; ++u) {
+                            const int v = s0 + 64 * u + lane;
+                            c += v < v1 && acc_before(x[u], v, zh, th);
                         }
                     }
+#pragma unroll
+                    for (int bit = 1; bit < 1024; bit <<= 1) total += bit * __builtin_popcountll(__ballot(c & bit));
                 }
+                if (sh == h) count = total;
+            }
         }
         // A NaN comes before nothing and nothing before it: counting alone would let it match.  (Token V and beyond: a DLM
-        // row of NaNs, no arg-max.)  Not an early `continue` at the top: hipcc 7.2 then dropped the assignment here.
-        if (count >= p.topk || !(z[n] == z[n]) || tok[n] >= p.V) match[n] = 0;
+        // row of NaNs, no arg-max.)
+        match[n] = !cand[n] ? -1 : want && count < p.topk && z == z && tok[n] < p.V ? 1 : 0;
     }
 }
 
-// Rows of a block that is too long for the fused kernel: one wave per row.
-__global__ __launch_bounds__(64) void k_accept_rowmerge(AccArgs p, int32_t *row_tok, int32_t *row_match)
+// Rows of a block that is too long for the fused kernel, two to a wave.  Token and match take the place of the row's first
+// record, which this wave alone has read.
+__global__ __launch_bounds__(64) void k_accept_rowmerge(AccArgs p)
 {
-    const int a = blockIdx.x, b = blockIdx.y;
-    int tok[1], match[1];
+    const int b = blockIdx.y;
+    int a = 2 * blockIdx.x, tok[1], match[1];
     accept_rows<1>(p, b, a, 1, threadIdx.x, tok, match);
-    if (threadIdx.x == 0) {
-        row_tok[(size_t)b * p.A + a] = tok[0];
-        row_match[(size_t)b * p.A + a] = match[0];
+    if (threadIdx.x % 32 == 0 && a + (int)threadIdx.x / 32 < p.A) {
+        a += threadIdx.x / 32;
+        int32_t *row = (int32_t *)(p.recs + ((size_t)b * p.A + a) * p.n_recs);
+        row[0] = tok[0];
+        row[1] = match[0];
     }
 }
 
-// Blocks of at most 64 rows: one workgroup per sequence, N rows per wave; its first wave, a lane per row, finds the prefix.
+// Blocks of at most 64 rows: one workgroup per sequence, 2 N rows per wave; its first wave, a lane per row, finds the prefix.
 template <int N>
 __global__ __launch_bounds__(1024) void k_accept_block(AccArgs p, int32_t *n_accept, int32_t *pos_next, int32_t *count_next)
 {
@@ -349,14 +425,16 @@ __global__ __launch_bounds__(1024) void k_accept_block(AccArgs p, int32_t *n_acc
     const int b = blockIdx.x, lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = blockDim.x >> 6;
     int tok[N], match[N];
-    accept_rows<N>(p, b, wave, n_waves, lane, tok, match);
-    if (lane == 0) {
+    accept_rows<N>(p, b, 2 * wave, 2 * n_waves, lane, tok, match);
+    if ((lane & 31) == 0) {
 #pragma unroll
-        for (int n = 0; n < N; ++n)
-            if (wave + n * n_waves < p.A) {
-                s_tok[wave + n * n_waves] = tok[n];
-                s_match[wave + n * n_waves] = match[n];
+        for (int n = 0; n < N; ++n) {
+            const int a = 2 * wave + n * 2 * n_waves + (lane >> 5);
+            if (a < p.A) {
+                s_tok[a] = tok[n];
+                s_match[a] = match[n];
             }
+        }
     }
     __syncthreads();
     if (wave) return;
@@ -380,7 +458,7 @@ __global__ __launch_bounds__(1024) void k_accept_block(AccArgs p, int32_t *n_acc
 }
 
 // Prefix of a longer block, one workgroup per sequence over the rows' results.
-__global__ __launch_bounds__(256) void k_accept_seq(const int32_t *__restrict__ row_tok, const int32_t *__restrict__ row_match,
+__global__ __launch_bounds__(256) void k_accept_seq(const int32_t *__restrict__ rows, int stride,
                                                     const int32_t *__restrict__ pos, int win_start, int A,
                                                     int32_t *tokens, int L, int32_t *n_accept, int32_t *pos_next,
                                                     int32_t *count_next)
@@ -398,7 +476,7 @@ __global__ __launch_bounds__(256) void k_accept_seq(const int32_t *__restrict__ 
     // pass 1: index j of every masked row among the masked rows; the first j that does not match
     for (int a0 = 0; a0 < A; a0 += 256) {
         const int a = a0 + tid;
-        const int mt = a < A ? row_match[(size_t)b * A + a] : -1;
+        const int mt = a < A ? rows[((size_t)b * A + a) * stride + 1] : -1;
         s_scan[tid] = mt >= 0 ? 1 : 0;
         __syncthreads();
         for (int off = 1; off < 256; off <<= 1) {
@@ -421,7 +499,7 @@ __global__ __launch_bounds__(256) void k_accept_seq(const int32_t *__restrict__ 
     // pass 2: fill the first n masked rows, list the others
     for (int a0 = 0; a0 < A; a0 += 256) {
         const int a = a0 + tid;
-        const int mt = a < A ? row_match[(size_t)b * A + a] : -1;
+        const int mt = a < A ? rows[((size_t)b * A + a) * stride + 1] : -1;
         s_scan[tid] = mt >= 0 ? 1 : 0;
         __syncthreads();
         for (int off = 1; off < 256; off <<= 1) {
@@ -433,7 +511,7 @@ __global__ __launch_bounds__(256) void k_accept_seq(const int32_t *__restrict__ 
         if (mt >= 0) {
             const int j = s_base + s_scan[tid] - 1;
             if (j < n)
-                seq[position(a)] = row_tok[(size_t)b * A + a];
+                seq[position(a)] = rows[((size_t)b * A + a) * stride];
             else
                 pos_next[(size_t)b * A + (j - n)] = position(a);
         }
@@ -475,7 +553,8 @@ int fc_accept_parts(int B, int A, int V)
 
 size_t fc_accept_workspace(int B, int A, int V)
 {
-    return (size_t)2 * B * A * sizeof(int32_t) + (size_t)B * A * fc_accept_parts(B, A, V) * sizeof(AccPart);
+    // (a record of 24 bytes per four parts is at most this much)
+    return (size_t)B * A * (8 + 16 * (size_t)fc_accept_parts(B, A, V));
 }
 
 hipError_t fc_launch_guided_accept(const float *dlm, const float *ar, const int32_t *pos, int win_start, int B, int A,
@@ -497,19 +576,18 @@ hipError_t fc_launch_guided_accept(const float *dlm, const float *ar, const int3
     p.mask_id = mask_id;
     p.L = L;
     p.tau = tau;
-    p.parts = (AccPart *)workspace;
-    int32_t *row_tok = (int32_t *)(p.parts + (size_t)B * A * p.n_parts), *row_match = row_tok + (size_t)B * A;
-    const dim3 grid((unsigned)((p.n_parts + 256 / ACC_LANES - 1) / (256 / ACC_LANES)), (unsigned)A, (unsigned)B);
+    p.recs = (AccRec *)workspace;
+    p.n_recs = (p.n_parts + ACC_REC - 1) / ACC_REC;
+    const dim3 grid((unsigned)p.n_recs, (unsigned)A, (unsigned)B);
     // rows of V floats are 16-byte aligned when V is a multiple of 4
     if ((V & 3) == 0) k_accept_scan<true><<<grid, dim3(256), 0, s>>>(p);
     else k_accept_scan<false><<<grid, dim3(256), 0, s>>>(p);
-    if (A <= 16) k_accept_block<1><<<dim3((unsigned)B), dim3((unsigned)A * 64), 0, s>>>(p, n_accept, pos_next, count_next);
-    else if (A <= 32) k_accept_block<2><<<dim3((unsigned)B), dim3(1024), 0, s>>>(p, n_accept, pos_next, count_next);
-    else if (A <= ACC_FUSED_ROWS) k_accept_block<4><<<dim3((unsigned)B), dim3(1024), 0, s>>>(p, n_accept, pos_next, count_next);
+    if (A <= 32) k_accept_block<1><<<dim3((unsigned)B), dim3((unsigned)(A + 1) / 2 * 64), 0, s>>>(p, n_accept, pos_next, count_next);
+    else if (A <= ACC_FUSED_ROWS) k_accept_block<2><<<dim3((unsigned)B), dim3(1024), 0, s>>>(p, n_accept, pos_next, count_next);
     else {
-        k_accept_rowmerge<<<dim3((unsigned)A, (unsigned)B), dim3(64), 0, s>>>(p, row_tok, row_match);
-        k_accept_seq<<<dim3((unsigned)B), dim3(256), 0, s>>>(row_tok, row_match, pos, win_start, A, tokens, L, n_accept,
-                                                             pos_next, count_next);
+        k_accept_rowmerge<<<dim3((unsigned)(A + 1) / 2, (unsigned)B), dim3(64), 0, s>>>(p);
+        k_accept_seq<<<dim3((unsigned)B), dim3(256), 0, s>>>((const int32_t *)p.recs, p.n_recs * (int)(sizeof(AccRec) / 4), pos, win_start,
+                                                             A, tokens, L, n_accept, pos_next, count_next);
     }
     return hipGetLastError();
 }

@@ -29,3 +29,45 @@ def test_long_prefixes_are_bit_exact(B, A, V):
         got_t, n, pn, cn = _gpu_accept(dlm, ar, pos, 0, topk, tau, MASK, tokens)
         assert np.array_equal(n, want[0]) and np.array_equal(got_t, want_t)
         assert np.array_equal(pn, want[1]) and np.array_equal(cn, want[2])
+
+
+@pytest.mark.parametrize("V", [777, 5124, 20487])
+@pytest.mark.parametrize("A", [5, 33, 66])
+def test_entries_ahead_of_the_token_wherever_they_lie(A, V):
+    """topk - 1 and topk entries of the guide ahead of the proposed token: around it, spread over the row, at the proposal's next
+    best entries, tied with it on either side, and a token whose guide value is the lowest there is."""
+    rng = np.random.default_rng(A * 7 + V)
+    MASK, L = 300000, A + 2
+    pos = np.arange(A, dtype=np.int32)[None]
+    for topk in (1, 2, 3, 8):
+        dlm = rng.normal(0, 1, (1, A, V)).astype(np.float32)
+        ar = rng.normal(0, 1, (1, A, V)).astype(np.float32)
+        for a in range(A):
+            t = int(rng.integers(20, V - 20))
+            n = topk - 1 if a + 1 < A else topk  # the last row does not match
+            order = np.argsort(-dlm[0, a])
+            where = (a + topk) % 5
+            if where == 0:
+                at = t + 1 + np.arange(n)
+            elif where == 1:
+                at = rng.choice(np.delete(np.arange(V), t), n, replace=False)
+            elif where == 2:
+                at = order[order != t][:n]
+            elif where == 3:
+                at = t - 1 - np.arange(n)
+            else:
+                at = t + 2 + 2 * np.arange(n)
+            dlm[0, a, t] = 50.0
+            ar[0, a, t] = 9.0
+            ar[0, a, at] = 9.0 if where == 3 else 10.0 + rng.random(n)  # smaller ids: ties count
+            if where == 4:
+                ar[0, a, t + 1] = 9.0  # a tie behind it does not
+                if a + 1 == A:
+                    ar[0, a] = -np.inf  # and here every entry ties
+        tokens = np.full((1, L), MASK, np.int32)
+        want_t = tokens.copy()
+        want = orc.guided_accept(dlm, ar, pos, topk, 0.0, MASK, want_t)
+        assert want[0][0] == A - 1
+        got_t, k, pn, cn = _gpu_accept(dlm, ar, pos, 0, topk, 0.0, MASK, tokens)
+        assert np.array_equal(k, want[0]) and np.array_equal(got_t, want_t)
+        assert np.array_equal(pn, want[1]) and np.array_equal(cn, want[2])
