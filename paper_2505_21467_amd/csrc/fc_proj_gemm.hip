@@ -462,7 +462,8 @@ __global__ __launch_bounds__((NW + NL) * 64) void k_proj_gemm(GemmArgs p)
     // 8192 x 8192 60 and 45; vocabulary 4096 x 32000, 64 rows 64.6 and 49.6; projection, 96 slots, hidden 4096, 64 rows 27.3
     // and 24.9.  At other distances it gives nothing or costs (hidden 5120 34.6 and 35.6, 7168 44.1 and 45.7, 1024 15.0 and
     // 15.3), and so it does with more row tiles, whose window rows then come from L2 at two places at a time (256 rows of
-    // gated 4096 x 12288 66.9 and 70.3).
+    // gated 4096 x 12288 66.9 and 70.3), and with the last rows of a problem, behind the launch that has just read the
+    // weights (300 rows of the same 102.8 and 107.0).
     const int rot = ROTATE ? (int)(((uint32_t)unit * p.rot_step) >> 16) : 0;
     auto issue_stage = [&](int st, int part) {
         const int sr = st + rot, at = st0 + (ROTATE && sr >= n_stages ? sr - n_stages : sr);
@@ -833,7 +834,7 @@ hipError_t launch_gemm(GemmArgs a, hipStream_t s)
         return hipGetLastError();
     };
     if constexpr (XROWS <= 128 && EPI != 3)
-        if (a.n_mt == 1 && a.K % 2048 == 0 && a.K / KS < 65536) {
+        if (a.n_mt == 1 && a.m_base == 0 && a.K % 2048 == 0 && a.K / KS < 65536) {
             a.rot_step = (uint32_t)(((int64_t)(a.K / KS) << 16) / a.n_units);  // (unit * rot_step stays below 2^32)
             return start(std::true_type());
         }
