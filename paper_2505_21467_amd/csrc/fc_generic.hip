@@ -75,6 +75,19 @@ struct Op<bf16_t> {
     }
 };
 
+__device__ __forceinline__ void load_lds16t(const void *g, void *l)
+{
+    __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)g,
+                                     (void __attribute__((address_space(3))) *)l, 16, 0, 0);
+}
+
+// wait until at most N of this wave's vector-memory operations are outstanding
+template <int N>
+__device__ __forceinline__ void wait_vmt()
+{
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+
 __device__ __forceinline__ float partner32(float v)  // the value of lane ^ 32
 {
     const unsigned u = __float_as_uint(v);
@@ -113,8 +126,13 @@ __device__ __forceinline__ void store4(bf16_t *p, const float (&y)[4])
 // Linear layers of any shape: Y^T = W X^T for a block of 16 NT weight rows and 16 MT window rows per
 // workgroup.  These problems are small (a few MB of weights at most), so what bounds them is latency:
 // the eight waves cut the hidden dimension, each streams its part of both operands from global memory
-// straight into operand registers (U blocks at a time, the next U in flight behind the multiplies of these),
-// and the partial tiles are summed through LDS, tile t by wave t mod 8, which applies the epilogue.
+// (U blocks at a time, the next U in flight behind the multiplies of these), and the partial tiles are summed
+// through LDS, tile t by wave t mod 8, which applies the epilogue.  The operands come by way of LDS (an area of its own per
+// wave, direct-to-LDS loads of 64 bytes per row): straight into registers, with neighbouring lanes in different rows, a
+// compute unit takes one lane a clock, 38 B/ns.  100 problems of 4 .. 160 rows, hidden 256 .. 2048 in fp32, 256 / 512 in bf16:
+// 0.83 of the time (fp32 32 x 1024 x 512 6.4 -> 4.5 us, gated 160 x 512 x 1024 11.7 -> 8.6, projection 32 x 512 x 1024 4.7 -> 4.1; the
+// same bits).  Pointers off 16 bytes and rows that are no whole blocks still go straight into registers (bf16 4 x 2056 x 2056
+// 4.9 that way, 5.1 with pieces that straddle lines).
 // Plain-ALU kernels with one dot product per wave took 36 us for the tiny configuration's projection (32
 // rows, hidden 256, 768 outputs; 0.3 TFLOP/s); this one takes about 5.
 //   EPI_QKV       bias, rotary embedding, scatter: a 16-row weight tile is the rotary indices i0 .. i0 + 7
@@ -138,17 +156,19 @@ struct TileArgs {
 };
 
 constexpr int TW = 8;  // waves per workgroup
-constexpr size_t tile_lds(int NT, int MT) { return (size_t)TW * NT * MT * 1024 + (size_t)MT * 16 * NT * 8 * sizeof(float2); }
+// LDS of a wave: its partial tiles, before that (LDS) a step's blocks of both operands
+constexpr size_t tile_wave(int NT, int MT, int U, bool lds) { return (size_t)1024 * (lds && U * (NT + MT) > NT * MT ? U * (NT + MT) : NT * MT); }
+constexpr size_t tile_lds(int NT, int MT, int U, bool lds) { return TW * tile_wave(NT, MT, U, lds) + (size_t)MT * 16 * NT * 8 * sizeof(float2); }
 
-template <typename T, int NT, int MT, int U, int EPI>
+template <typename T, int NT, int MT, int U, int EPI, bool LDS>
 __global__ __launch_bounds__(TW * 64) void k_linear_tile(TileArgs p)
 {
     typedef Op<T> O;
     typedef typename O::frag frag;
     constexpr int KB = O::KB;  // U blocks of 4 KB hidden elements per load step
     extern __shared__ __align__(16) unsigned char tile_smem[];
-    float *red = (float *)tile_smem;                               // [wave][tile][reg][lane]
-    float2 *cs = (float2 *)(tile_smem + (size_t)TW * NT * MT * 1024);  // EPI_QKV: [window row][8 NT rotary indices]
+    constexpr size_t WAVE = tile_wave(NT, MT, U, LDS);
+    float2 *cs = (float2 *)(tile_smem + TW * WAVE);                // EPI_QKV: [window row][8 NT rotary indices]
     const FcGeom &G = p.G;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -159,26 +179,41 @@ __global__ __launch_bounds__(TW * 64) void k_linear_tile(TileArgs p)
     auto head_of = [&](int tile) { return tile / (G.Dh / 16); };
     auto i0_of = [&](int tile) { return (tile % (G.Dh / 16)) * 8; };
 
+    // What the lane loads: row lr, elements KB lq of a block.  Into registers the operand's own; by way of LDS four
+    // neighbouring lanes take 64 bytes of a row, chunks permuted against bank conflicts.
+    const int lr = LDS ? lane >> 2 : rho, lq = LDS ? (lane & 3) ^ (lane >> 4) : q;
     const T *wrow[NT], *xrow[MT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         const int tile = n_blk * NT + t;
         if (EPI == EPI_QKV) {
             const int hs = min(head_of(tile), G.Hq + 2 * G.Hkv - 1), i0 = i0_of(tile);
-            wrow[t] = (const T *)p.W + (size_t)(hs * G.Dh + (rho < 8 ? i0 + rho : half + i0 + rho - 8)) * p.K;
+            wrow[t] = (const T *)p.W + (size_t)(hs * G.Dh + (lr < 8 ? i0 + lr : half + i0 + lr - 8)) * p.K;
         } else if (EPI == EPI_GATE_UP) {
-            wrow[t] = (const T *)(rho < 8 ? p.W : p.W2) + (size_t)min(tile * 8 + (rho & 7), p.N - 1) * p.K;
+            wrow[t] = (const T *)(lr < 8 ? p.W : p.W2) + (size_t)min(tile * 8 + (lr & 7), p.N - 1) * p.K;
         } else {
-            wrow[t] = (const T *)p.W + (size_t)min(tile * 16 + rho, p.N - 1) * p.K;
+            wrow[t] = (const T *)p.W + (size_t)min(tile * 16 + lr, p.N - 1) * p.K;
         }
-        wrow[t] += KB * q;
+        wrow[t] += KB * lq;
     }
 #pragma unroll
-    for (int t = 0; t < MT; ++t) xrow[t] = (const T *)p.X + (size_t)min(m0 + 16 * t + rho, p.M - 1) * p.K + KB * q;
+    for (int t = 0; t < MT; ++t) xrow[t] = (const T *)p.X + (size_t)min(m0 + 16 * t + lr, p.M - 1) * p.K + KB * lq;
 
     // this wave's blocks of the hidden dimension
     const int n_kb = (p.K + 4 * KB - 1) / (4 * KB);
     const int b0 = wave * n_kb / TW, b1 = (wave + 1) * n_kb / TW;
+    unsigned char *buf = tile_smem + wave * WAVE;
+    auto issue = [&](int b) {  // LDS: the next U blocks at most
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (b + u >= b1) break;
+            const int at = (b + u) * 4 * KB;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) load_lds16t(wrow[t] + at, buf + (u * (NT + MT) + t) * 1024);
+#pragma unroll
+            for (int t = 0; t < MT; ++t) load_lds16t(xrow[t] + at, buf + (u * (NT + MT) + NT + t) * 1024);
+        }
+    };
     auto load = [&](int b, frag(&wf)[U][NT], frag(&xf)[U][MT]) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -214,14 +249,15 @@ __global__ __launch_bounds__(TW * 64) void k_linear_tile(TileArgs p)
     };
 
     frag wa[U][NT], xa[U][MT], wb[U][NT], xb[U][MT];
-    load(b0, wa, xa);
+    if constexpr (LDS) issue(b0);
+    else load(b0, wa, xa);
     if (EPI == EPI_QKV) {
         // rotary factors of this workgroup's rows and indices, while the first loads are in flight
         const int hs0 = head_of(n_blk * NT);
         if (hs0 < G.Hq + G.Hkv) {
             for (int idx = tid; idx < 16 * MT * 8 * NT; idx += TW * 64) {
-                const int lr = idx / (8 * NT), e = idx % (8 * NT);
-                const int m = min(m0 + lr, p.M - 1);
+                const int row = idx / (8 * NT), e = idx % (8 * NT);
+                const int m = min(m0 + row, p.M - 1);
                 const int pp = p.pos ? p.pos[m] : p.win_start + m % p.A;
                 double turns = (double)pp * p.inv_freq[i0_of(n_blk * NT + e / 8) + e % 8] * 0.15915494309189533576888;
                 turns -= rint(turns);
@@ -231,19 +267,51 @@ __global__ __launch_bounds__(TW * 64) void k_linear_tile(TileArgs p)
             }
         }
     }
-    for (int b = b0;; b += 2 * U) {  // (a wave without blocks multiplies zeros once)
-        if (b + U >= b1) {
+    if constexpr (LDS) {
+        const int at = rho * 64 + ((q ^ (rho >> 2)) << 4);
+        for (int b = b0; b < b1; b += U) {
+            wait_vmt<0>();
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t) wa[u][t] = *(const frag *)(buf + (u * (NT + MT) + t) * 1024 + at);
+#pragma unroll
+                for (int t = 0; t < MT; ++t) xa[u][t] = *(const frag *)(buf + (u * (NT + MT) + NT + t) * 1024 + at);
+            }
+            __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the area may be overwritten
+            __builtin_amdgcn_sched_barrier(0);
+            if (b + U < b1) issue(b + U);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (b + u >= b1) break;
+                // fp32: with several waves per SIMD a pause behind each four matrix instructions lets another wave in
+                // (700 x 512 x 2048 26.3 -> 22.5 us, gated 160 x 512 x 2048 14.9 -> 13.4; without rivals it is not felt)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int m = 0; m < MT; ++m) {
+                        acc[t][m] = O::mfma(wa[u][t], xa[u][m], acc[t][m]);
+                        if constexpr (sizeof(T) == 4) asm volatile("s_nop 7");
+                    }
+            }
+        }
+    } else {
+        for (int b = b0;; b += 2 * U) {  // (a wave without blocks multiplies zeros once)
+            if (b + U >= b1) {
+                multiply(wa, xa);
+                break;
+            }
+            load(b + U, wb, xb);
             multiply(wa, xa);
-            break;
-        }
-        load(b + U, wb, xb);
-        multiply(wa, xa);
-        if (b + 2 * U >= b1) {
+            if (b + 2 * U >= b1) {
+                multiply(wb, xb);
+                break;
+            }
+            load(b + 2 * U, wa, xa);
             multiply(wb, xb);
-            break;
         }
-        load(b + 2 * U, wa, xa);
-        multiply(wb, xb);
     }
 
 #pragma unroll
@@ -251,7 +319,7 @@ __global__ __launch_bounds__(TW * 64) void k_linear_tile(TileArgs p)
 #pragma unroll
         for (int m = 0; m < MT; ++m)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) red[((wave * NT * MT + t * MT + m) * 4 + r) * 64 + lane] = acc[t][m][r];
+            for (int r = 0; r < 4; ++r) ((float *)buf)[((t * MT + m) * 4 + r) * 64 + lane] = acc[t][m][r];
     __syncthreads();
 
     float run_mx = -INFINITY, run_sm = 0.f;
@@ -265,7 +333,7 @@ __global__ __launch_bounds__(TW * 64) void k_linear_tile(TileArgs p)
 #pragma unroll
             for (int w2 = 0; w2 < TW; ++w2)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) y[r] += red[((w2 * NT * MT + t * MT + mt) * 4 + r) * 64 + lane];
+                for (int r = 0; r < 4; ++r) y[r] += ((const float *)(tile_smem + w2 * WAVE))[((t * MT + mt) * 4 + r) * 64 + lane];
             // lane (rho, q) holds weight rows 4 q .. 4 q + 3 of the tile for window row rho
             const int m = m0 + 16 * mt + rho, tile = n_blk * NT + t;
             const bool mvalid = m < p.M;
@@ -428,19 +496,6 @@ struct AttnTileLds {
         return ROWB >= 256 ? row & 15 : ROWB == 128 ? (row >> 1) & 7 : (row >> 2) & 3;
     }
 };
-
-__device__ __forceinline__ void load_lds16t(const void *g, void *l)
-{
-    __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)g,
-                                     (void __attribute__((address_space(3))) *)l, 16, 0, 0);
-}
-
-// wait until at most N of this wave's vector-memory operations are outstanding
-template <int N>
-__device__ __forceinline__ void wait_vmt()
-{
-    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
 
 template <typename T, int DH, int QT, int DS, bool LDS>
 __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
@@ -950,17 +1005,17 @@ hipError_t fc_launch_rmsnorm(int dtype, const void *x, const void *weight, float
 
 namespace {
 
-template <typename T, int NT, int MT, int U, int EPI>
+template <typename T, int NT, int MT, int U, int EPI, bool LDS>
 hipError_t launch_tile_u(TileArgs a, int n_tiles, hipStream_t s)
 {
-    constexpr size_t LDS = tile_lds(NT, MT);
-    static hipError_t attr = hipFuncSetAttribute((const void *)k_linear_tile<T, NT, MT, U, EPI>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
+    constexpr size_t BYTES = tile_lds(NT, MT, U, LDS);
+    static hipError_t attr = hipFuncSetAttribute((const void *)k_linear_tile<T, NT, MT, U, EPI, LDS>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)BYTES);
     if (attr != hipSuccess) return attr;
     a.n_blocks = (n_tiles + NT - 1) / NT;
     const int64_t grid = (int64_t)a.n_blocks * ((a.M + 16 * MT - 1) / (16 * MT));
     if (grid > INT32_MAX) return hipErrorInvalidValue;
-    k_linear_tile<T, NT, MT, U, EPI><<<dim3((unsigned)grid), dim3(TW * 64), LDS, s>>>(a);
+    k_linear_tile<T, NT, MT, U, EPI, LDS><<<dim3((unsigned)grid), dim3(TW * 64), BYTES, s>>>(a);
     return hipGetLastError();
 }
 
@@ -979,14 +1034,27 @@ hipError_t launch_tile_t(const TileArgs &a, int n_tiles, hipStream_t s)
     constexpr int NT = EPI == EPI_VOCAB ? 2 : 1;
     const int64_t blocks = (n_tiles + NT - 1) / NT;
     auto wgs = [&](int mt) { return blocks * ((a.M + 16 * mt - 1) / (16 * mt)); };
+    // By way of LDS: two blocks a step always (four leave one workgroup per compute unit where there were two: 6 % slower), and
+    // the tile with the fewest rounds of 256 workgroups by what a workgroup takes, 1 : 1.7 for 16 and 32 rows; bf16, which its
+    // matrix rate does not bind, also 64 rows x two weight tiles, 3 (fp32 would be 7; us at 16 / 32 / 64 rows: gated
+    // fp32 160 x 512 x 2048 13.9 / 12.8, 160 x 512 x 1024 8.6 / 9.0; 700 x 512 x 2048 25.8 / 23.0 / 25.5; bf16 64 x 1000 x 6000
+    // 12.8 / 10.2 / 8.2).
+    if (a.K % (4 * Op<T>::KB) == 0 && (((uintptr_t)a.X | (uintptr_t)a.W | (uintptr_t)a.W2) & 15) == 0) {
+        auto rounds = [&](int64_t n) { return (double)((n + 255) / 256); };
+        const double one = rounds(wgs(1)), two = 1.7 * rounds(wgs(2));
+        if constexpr (sizeof(T) == 2)
+            if (a.M > 32 && 3.0 * rounds((n_tiles + 1) / 2 * (int64_t)((a.M + 63) / 64)) < fmin(one, two))
+                return launch_tile_u<T, 2, 4, 2, EPI, true>(a, n_tiles, s);
+        return a.M > 16 && two < one ? launch_tile_u<T, NT, 2, 2, EPI, true>(a, n_tiles, s) : launch_tile_u<T, NT, 1, 2, EPI, true>(a, n_tiles, s);
+    }
     const bool deep = NT == 1 && (a.K + 4 * Op<T>::KB - 1) / (4 * Op<T>::KB) >= 8 * TW;
-    if (a.M > 32 && wgs(2) >= 4096) return launch_tile_u<T, 2, 4, 2, EPI>(a, n_tiles, s);
+    if (a.M > 32 && wgs(2) >= 4096) return launch_tile_u<T, 2, 4, 2, EPI, false>(a, n_tiles, s);
     if (a.M > 16 && wgs(2) >= 256) {
         if constexpr (sizeof(T) == 4)
-            if (deep && wgs(2) <= 512) return launch_tile_u<T, NT, 2, 4, EPI>(a, n_tiles, s);
-        return launch_tile_u<T, NT, 2, 2, EPI>(a, n_tiles, s);
+            if (deep && wgs(2) <= 512) return launch_tile_u<T, NT, 2, 4, EPI, false>(a, n_tiles, s);
+        return launch_tile_u<T, NT, 2, 2, EPI, false>(a, n_tiles, s);
     }
-    return deep && wgs(1) <= 512 ? launch_tile_u<T, NT, 1, 4, EPI>(a, n_tiles, s) : launch_tile_u<T, NT, 1, 2, EPI>(a, n_tiles, s);
+    return deep && wgs(1) <= 512 ? launch_tile_u<T, NT, 1, 4, EPI, false>(a, n_tiles, s) : launch_tile_u<T, NT, 1, 2, EPI, false>(a, n_tiles, s);
 }
 
 template <int EPI>
