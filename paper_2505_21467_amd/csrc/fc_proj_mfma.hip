@@ -4,8 +4,8 @@
 // The window is short (tens to a few hundred rows), so the product Y^T = W X^T is bound by streaming
 // the weight matrix once from HBM.  Both operands are contiguous along the hidden dimension, which is
 // exactly the per-lane operand layout of v_mfma_f32_16x16x32_bf16 (8 consecutive k per lane).  Three kernels: runs of
-// rotary pairs over the whole hidden dimension for at most 96 window rows (k_proj_stream), head slots cut along the hidden
-// dimension for 33 .. 128 rows (k_proj_headsplit), both at multiples of 512, and k_proj_skinny, described here, for
+// rotary pairs over the whole hidden dimension for at most 256 window rows (k_proj_stream), few head slots cut along a long
+// hidden dimension for 33 .. 128 rows (k_proj_headsplit), both at multiples of 512, and k_proj_skinny, described here, for
 // what is left.
 //
 // A workgroup owns 16 rows of W -- 8 rows i0..i0+7 of one head and their rotary partners
@@ -41,7 +41,7 @@ struct ProjArgs {
     float *partials;       // cache scratch: partial tiles of the hidden-dimension slices
     int mt;                // 16-row window tiles of a partial
     int wave_bytes;        // k_proj_stream: LDS of a wave,
-    uint32_t div_grid, div_a;  // reciprocals of the grid and of A
+    uint32_t div_runs, div_a;  // reciprocals of the number of runs and of A
 };
 
 __device__ __forceinline__ bf16x8 ld8(const uint16_t *p)
@@ -349,10 +349,10 @@ __global__ __launch_bounds__(64) void k_proj_finish(ProjArgs p)
 }
 
 // -------------------------------------------------------------------------------------------------
-// Whole-row kernel: at most 96 window rows, hidden sizes that are multiples of 512.
+// Whole-row kernel: at most 256 window rows, hidden sizes that are multiples of 512.
 //
-// Every workgroup owns an equal run of rotary pairs (rows i and i + 64 of a head; 9 pairs at 36 head slots) over the whole
-// hidden dimension, so no partial tiles leave it.  Its eight waves cut the hidden dimension; each streams its part of the
+// Every workgroup owns an equal run of rotary pairs (rows i and i + 64 of a head; 9 pairs at 36 head slots) and a tile of up
+// to 64 window rows over the whole hidden dimension, so no partial tiles leave it.  Its eight waves cut the hidden dimension; each streams its part of the
 // run's weight rows and of the window rows through LDS of its own, 64 hidden elements (one line of every row) per
 // stage, and waits for nobody until the waves' tiles are summed.
 //   * Bound by what a compute unit takes in, weights from HBM and all window rows from L2.  Loads whose lanes lie in eight
@@ -364,8 +364,8 @@ __global__ __launch_bounds__(64) void k_proj_finish(ProjArgs p)
 //     operands and first angle are at hand when the sums are (16 / 32 / 64 rows 9.1 / 10.5 / 14.3 -> 8.7 / 10.0 / 13.8 us).
 //   * NP = 2: runs of 17 .. 32 pairs.
 // Against the kernel it replaced (X kept in operand registers, at most 32 rows) and the head-split kernels, us: 36 head slots,
-// hidden 3584, 4 / 16 / 32 rows 9.4 / 9.6 / 11.1 -> 8.3 / 8.6 / 9.8, 48 / 64 rows 13.7 / 15.1 -> 11.7 / 13.4; 96 slots, hidden 4096, 32 rows
-// 23.3 -> 21.1; 24 slots, hidden 2048, 32 / 64 rows 9.5 / 11.9 -> 5.5 / 7.3.
+// hidden 3584, 4 / 16 / 32 rows 9.4 / 9.6 / 11.1 -> 8.3 / 8.6 / 9.8, 48 / 64 / 96 / 128 rows 13.6 / 15.0 / 17.4 / 19.2 -> 11.8 / 12.5 / 14.2 /
+// 16.1; 96 slots, hidden 4096, 32 rows 23.3 -> 21.1; 24 slots, hidden 2048, 32 / 64 / 128 rows 9.5 / 11.8 / 10.5 -> 5.5 / 6.2 / 7.6.
 template <int N>
 __device__ __forceinline__ void wait_vm()
 {
@@ -384,9 +384,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rho = lane & 15, q = lane >> 4;
+    // (run of pairs, tile of window rows): the runs are whole eights, so the tiles of one are on one die, which reads its
+    // weights from HBM once.  (Taken from one index by division this cost 0.25 us.)
+    const int run = blockIdx.x, m0 = 16 * MT * blockIdx.y;
     const uint32_t n_pairs = (uint32_t)p.n_tiles * 8;
-    const int g0 = (int)quotient(blockIdx.x * n_pairs, p.div_grid);
-    const int R = (int)quotient((blockIdx.x + 1) * n_pairs, p.div_grid) - g0;  // pairs of this workgroup
+    const int g0 = (int)quotient(run * n_pairs, p.div_runs);
+    const int R = (int)quotient((run + 1) * n_pairs, p.div_runs) - g0;  // pairs of this workgroup
     const int n_stages = p.K / (8 * STREAM_K);
     const int n_wl = (2 * R + 7) >> 3;  // weight loads of a stage
     unsigned char *xbuf = lds + wave * p.wave_bytes, *wbuf = xbuf + MT * 2048;
@@ -405,9 +408,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int i = 0; i < 2 * MT; ++i) {
         const int r = 8 * i + (lane >> 3);
-        xoff[i] = (uint32_t)min(r, p.M - 1) * (uint32_t)(2 * p.K) + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+        xoff[i] = (uint32_t)min(m0 + r, p.M - 1) * (uint32_t)(2 * p.K) + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
     }
-    const int turn0 = p.K % 4096 == 0 ? (blockIdx.x >> 3) & 7 : 0;  // n_stages is a multiple of 8 there
+    const int turn0 = p.K % 4096 == 0 ? (run >> 3) & 7 : 0;  // n_stages is a multiple of 8 there
     auto issue = [&](int st) {
         st += turn0;
         if (st >= n_stages) st -= n_stages;
@@ -426,7 +429,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     auto task_pair = [&](int j) { return 16 * ((wave + 8 * j) / (4 * MT)) + rho; };
 #pragma unroll
     for (int j = 0; j < TASKS; ++j) {
-        const int mm = min(task_row(j), p.M - 1), gp = g0 + min(task_pair(j), R - 1);
+        const int mm = min(m0 + task_row(j), p.M - 1), gp = g0 + min(task_pair(j), R - 1);
         pp[j] = p.pos ? p.pos[mm] : p.win_start + mm - (int)quotient(mm, p.div_a) * p.A;
         bs[j][0] = bs[j][1] = 0;
         if (p.bias) {
@@ -463,8 +466,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         wait_vm<0>();
         __builtin_amdgcn_sched_barrier(0);
         bf16x8 xf[2][MT], wf[2][NP][2];
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
+        auto read = [&](int s) {
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) xf[s][mt] = frag(xbuf, 16 * mt + rho, s);
 #pragma unroll
@@ -473,13 +475,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 wf[s][t][0] = frag(wbuf, row, s);
                 wf[s][t][1] = frag(wbuf, R + row, s);
             }
-        }
-        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the areas may be overwritten
-        __builtin_amdgcn_sched_barrier(0);
-        if (st + 1 < n_stages) issue(st + 1);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
+        };
+        auto multiply = [&](int s) {
 #pragma unroll
             for (int t = 0; t < NP; ++t)
 #pragma unroll
@@ -487,6 +484,15 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
                     for (int mt = 0; mt < MT; ++mt)
                         acc[t][f][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[s][t][f], xf[s][mt], acc[t][f][mt], 0, 0, 0);
+        };
+        read(0);
+        read(1);
+        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the areas may be overwritten
+        __builtin_amdgcn_sched_barrier(0);
+        if (st + 1 < n_stages) issue(st + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(0);
+        multiply(1);
     }
     // [pair tile][window tile][first / partner][lane] in the wave's own area, quarters 64 bytes apart for the reads below
 #pragma unroll
@@ -498,9 +504,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < TASKS; ++j) {
-        const int m = task_row(j), pr = task_pair(j);
-        if (4 * ((wave + 8 * j) % (4 * MT)) >= p.M || (wave + 8 * j) / (4 * MT) >= NP) continue;
-        const unsigned char *part = lds + (((pr >> 4) * MT + (m >> 4)) * 2) * 1280 + ((pr & 15) >> 2) * 320 + (m & 15) * 16 + (pr & 3) * 4;
+        const int ml = task_row(j), m = m0 + ml, pr = task_pair(j);
+        if (m0 + 4 * ((wave + 8 * j) % (4 * MT)) >= p.M || (wave + 8 * j) / (4 * MT) >= NP) continue;
+        const unsigned char *part = lds + (((pr >> 4) * MT + (ml >> 4)) * 2) * 1280 + ((pr & 15) >> 2) * 320 + (ml & 15) * 16 + (pr & 3) * 4;
         float y0 = 0.f, y1 = 0.f;
 #pragma unroll
         for (int w2 = 0; w2 < 8; ++w2) {
@@ -536,38 +542,42 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 }
 
 template <int MT, int NP>
-hipError_t launch_stream(ProjArgs a, int grid, hipStream_t s)
+hipError_t launch_stream(ProjArgs a, int runs, hipStream_t s)
 {
-    const int run = (a.n_tiles * 8 + grid - 1) / grid;
+    const int run = (a.n_tiles * 8 + runs - 1) / runs;
     const int ring = MT * 2048 + (2 * run + 7) / 8 * 1024;
     const int state = NP * 2 * MT * 1280;
     a.wave_bytes = ring > state ? ring : state;
-    if (run > 16 * NP || a.wave_bytes > 20 * 1024) return hipErrorInvalidValue;
-    a.div_grid = reciprocal(grid);
+    if (run > 16 * NP || runs % 8 || a.wave_bytes > 20 * 1024) return hipErrorInvalidValue;
+    a.div_runs = reciprocal(runs);
     a.div_a = reciprocal(a.A);
     static hipError_t attr = hipFuncSetAttribute((const void *)k_proj_stream<MT, NP>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return attr;
-    k_proj_stream<MT, NP><<<dim3((unsigned)grid), dim3(512), 8 * a.wave_bytes, s>>>(a);
+    k_proj_stream<MT, NP><<<dim3((unsigned)runs, (unsigned)((a.M + 16 * MT - 1) / (16 * MT))), dim3(512), 8 * a.wave_bytes, s>>>(a);
     return hipGetLastError();
 }
 
-// Runs of at least four pairs: with fewer the window rows are fetched for too little.
-template <int MT>
-hipError_t launch_stream_mt(const ProjArgs &a, hipStream_t s)
+// Tiles of 16 mt window rows and runs of pairs, one workgroup per compute unit; runs of at least four pairs: with fewer the
+// window rows are fetched for too little.
+struct StreamShape {
+    int mt, row_tiles, runs, run;
+};
+StreamShape stream_shape(int slots, int M, int mt)
 {
-    const int n_pairs = a.n_tiles * 8, grid = n_pairs < 1024 ? n_pairs / 4 : 256;
-    if ((n_pairs + grid - 1) / grid <= 16) return launch_stream<MT, 1>(a, grid, s);
-    if constexpr (MT <= 2) return launch_stream<MT, 2>(a, grid, s);
-    return hipErrorInvalidValue;
+    StreamShape s;
+    s.mt = mt;
+    s.row_tiles = (M + 16 * mt - 1) / (16 * mt);
+    const int n_pairs = slots * 64, most = s.row_tiles > 32 ? 8 : 256 / s.row_tiles / 8 * 8;
+    s.runs = n_pairs < 4 * most ? n_pairs / 32 * 8 : most;  // whole eights, one of each on every die
+    s.run = (n_pairs + s.runs - 1) / s.runs;
+    return s;
 }
 
-// Two operands (more than 64 head slots) lose to the tiled GEMM beyond 32 rows and, past 96 slots, at small hidden
-// sizes (us, GEMM second): 96 slots, hidden 3584, 32 / 48 / 64 rows 18.9 / 21.6 / 24.0 and 22.6 / 22.3 / 23.4; 128 slots, 16 rows,
-// hidden 2048 / 3584 16.3 / 22.0 and 13.9 / 24.  One operand loses beyond 64 rows where the hidden dimension is short (24 slots,
-// hidden 512, 96 rows 6.2 and 5.5).
-bool stream_covers(int slots, int M, int K)
+template <int MT>
+hipError_t launch_stream_mt(const ProjArgs &a, int slots, hipStream_t s)
 {
-    return K % 512 == 0 && (slots <= 64 ? M <= (K <= 1024 ? 64 : 96) : M <= 32 && (slots <= 96 || (slots <= 128 && K >= 3584)));
+    const StreamShape sh = stream_shape(slots, a.M, MT);
+    return sh.run <= 16 ? launch_stream<MT, 1>(a, sh.runs, s) : launch_stream<MT, 2>(a, sh.runs, s);
 }
 
 size_t headsplit_bytes(int slots, int M, int K)
@@ -625,19 +635,40 @@ static double tile_us(int slots, int M, int K)
     return K > 3072 || weights > 13.0 ? 1e30 : fmax(4.0, 3.2 + 0.032 * M * weights);
 }
 
-// Whole rows: launch and epilogue, the window rows' way into a compute unit, weights at 6.9 TB/s (6 % from the measured times in
-// the mean at hidden 512 .. 8192, 6 .. 64 head slots, 4 .. 96 rows).
-static double stream_us(int slots, int M, int K)
+// Runs of pairs: launch, the window rows' and the weights' way into a compute unit, the epilogue, the weights' from HBM (7 %
+// from the measured times in the mean at hidden 512 .. 5120, 24 .. 96 head slots, 33 .. 144 rows).  Rows in tiles of 32, 48 or
+// 64 by the same estimate, which picks within 0.1 % of the best of the three: 36 slots, hidden 3584, 64 / 96 / 128 rows 12.3 / 14.0 /
+// 16.9 us where one tile of all rows took 13.6 / 17.8 / 20.4.  (1e30: runs of more than 32 pairs.)
+static double stream_us(int slots, int M, int K, int *mt)
 {
-    return 2.34 + (M + 15) / 16 * (0.27 + 0.00039 * K) + 3.73e-5 * K * slots;
+    double best = 1e30;
+    for (int t = M <= 32 ? (M + 15) / 16 : 2; t <= (M <= 32 ? (M + 15) / 16 : 4); ++t) {
+        const StreamShape s = stream_shape(slots, M, t);
+        if (s.run > 32) continue;
+        const double rows = fmin(t, M / (16.0 * s.row_tiles));
+        const double us = 2.52 + 1e-3 * K * (0.311 * rows + 0.0362 * s.run + 0.0312 * slots) + 0.36 * t * ((s.run + 15) / 16);
+        if (us < best) {
+            best = us;
+            *mt = t;
+        }
+    }
+    return best;
 }
 
-// Up to 32 rows nothing else is faster by more than 0.1 us.  Beyond, head-split gains where slots are few and the hidden
-// dimension long (24 slots, 64 rows, hidden 3584 / 5120 / 8192: whole rows 12.3 / 16.7 / 23.7, head-split 13.4 / 15.0 / 20.9) and
-// the tile kernel where all is small (6 slots, hidden 512, 96 rows 5.6 and 4.7).
-static bool stream_wins(int slots, int M, int K)
+// Up to 32 rows nothing else is faster by more than 0.1 us, except past 96 head slots (two operands) the tiled GEMM at small
+// hidden sizes (128 slots, 16 rows, hidden 2048 / 3584 16.3 / 22.0 us and 13.9 / 24).  From 33 rows on by estimates.  Head-split keeps
+// few slots with a hidden dimension beyond 8192 (6 slots, hidden 12288, 64 rows 17.8 and 13.9); more than 80 slots, or 64
+// from 65 rows on, the tiled GEMM (96 slots, hidden 2048, 48 rows 15.3 and 14.2; 48 slots, hidden 4096, 160 rows 25.7 and 24.0), whose
+// estimate is a good third too long beyond 128 rows (36 slots, hidden 3584, 144 / 160 rows 16.4 / 18.2 and 17.5 / 17.9; 24
+// slots, hidden 5120, 192 rows 19.2 and 25.0; 12 slots, hidden 3584, 256 rows 10.3 and 15.5).
+static bool stream_wins(int slots, int M, int K, int *mt)
 {
-    return stream_covers(slots, M, K) && (M <= 32 || stream_us(slots, M, K) < fmin(0.94 * headsplit_us(slots, M, K), tile_us(slots, M, K)));
+    if (K % 512 != 0 || M > 256 || slots > (M > (K >= 3072 ? 64 : 48) ? 64 : M > 32 ? 80 : K >= 3584 ? 128 : 96) || (M > 128 && K <= 1024)) return false;
+    const double us = stream_us(slots, M, K, mt);
+    if (M <= 32) return us < 1e30;
+    if (M > 128) return 1.05 * us < 0.68 * fc_project_gemm_us(slots, M, K);
+    if (slots > 64) return us < 0.95 * fc_project_gemm_us(slots, M, K);
+    return us < fmin(0.94 * headsplit_us(slots, M, K), tile_us(slots, M, K));
 }
 
 bool fc_project_prefers_gemm(const fc_config &cfg, int M, bool scratch)
@@ -645,7 +676,8 @@ bool fc_project_prefers_gemm(const fc_config &cfg, int M, bool scratch)
     if (!fc_project_gemm_supported(cfg, M)) return false;
     if (fc_knobs().proj_gemm_shape >= 0 && M > 32) return true;  // tuning knob
     const int slots = cfg.n_q_heads + 2 * cfg.n_kv_heads;
-    if (stream_wins(slots, M, cfg.hidden)) return false;
+    int stream_mt;
+    if (stream_wins(slots, M, cfg.hidden, &stream_mt)) return false;
     if (!scratch || !headsplit_covers(slots, M, cfg.hidden)) return M > 32 || cfg.hidden % HS_K == 0;
     return headsplit_us(slots, M, cfg.hidden) > fc_project_gemm_us(slots, M, cfg.hidden);
 }
@@ -656,7 +688,9 @@ bool fc_project_prefers_gemm(const fc_config &cfg, int M, bool scratch)
 bool fc_project_prefers_tile(const fc_config &cfg, int M)
 {
     const int slots = cfg.n_q_heads + 2 * cfg.n_kv_heads;
-    if (cfg.dtype != FC_BF16 || cfg.head_dim != 128 || fc_knobs().proj_gemm_shape >= 0 || stream_wins(slots, M, cfg.hidden)) return false;
+    int stream_mt;
+    if (cfg.dtype != FC_BF16 || cfg.head_dim != 128 || fc_knobs().proj_gemm_shape >= 0 || stream_wins(slots, M, cfg.hidden, &stream_mt))
+        return false;
     const bool skinny = M <= 32 && cfg.hidden % HS_K != 0;
     if (skinny && M <= 16) return false;
     const double other = skinny ? 3.55 + 0.002 * cfg.hidden : 3.9 + 0.0043 * (cfg.hidden < 1024 ? cfg.hidden : 1024);
@@ -685,14 +719,13 @@ hipError_t fc_launch_project_mfma(const FcGeom &G, const void *x, const void *w,
     a.partials = (float *)scratch;
     for (int i = 0; i < 6; ++i) a.rot[i] = exp(-G.log_base * (1 << i) / 64.0);
     const int slots = G.Hq + 2 * G.Hkv, mt = (a.M + 15) / 16;
-    if (stream_wins(slots, a.M, a.K)) {
-        switch (mt) {
-        case 1: return launch_stream_mt<1>(a, s);
-        case 2: return launch_stream_mt<2>(a, s);
-        case 3: return launch_stream_mt<3>(a, s);
-        case 4: return launch_stream_mt<4>(a, s);
-        case 5: return launch_stream_mt<5>(a, s);
-        default: return launch_stream_mt<6>(a, s);
+    int stream_mt;
+    if (stream_wins(slots, a.M, a.K, &stream_mt)) {
+        switch (stream_mt) {
+        case 1: return launch_stream_mt<1>(a, slots, s);
+        case 2: return launch_stream_mt<2>(a, slots, s);
+        case 3: return launch_stream_mt<3>(a, slots, s);
+        default: return launch_stream_mt<4>(a, slots, s);
         }
     }
     if (scratch && headsplit_covers(slots, a.M, a.K)) {

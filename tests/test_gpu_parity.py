@@ -315,6 +315,11 @@ def test_short_window_projection_bias_and_scattered_positions(B, d, Hq, Hkv, L, 
     (1, 4096, 48, 8, 40, 17),    # 64 head slots, runs of 16 pairs; workgroups start at different stages
     (1, 512, 60, 3, 40, 31),     # 66 head slots, two operands
     (2, 3584, 64, 32, 40, 16),   # 128 head slots, runs of 32 pairs
+    (2, 512, 60, 3, 40, 20),     # 66 head slots, 40 rows: two operands, two or three tiles of rows
+    (5, 512, 28, 4, 40, 23),     # 115 rows, the last tile ragged
+    (7, 1536, 10, 2, 40, 32),    # 224 rows in four to seven tiles
+    (8, 2048, 4, 1, 40, 32),     # 256 rows, 6 head slots
+    (5, 3584, 28, 4, 40, 27),    # 135 rows, runs of 28 and 29 pairs
 ])
 def test_short_window_projection_by_runs_of_pairs(B, d, Hq, Hkv, L, A):
     """Ends of the runs, of the window tiles and of the covered range, with bias, contiguous and scattered positions."""
