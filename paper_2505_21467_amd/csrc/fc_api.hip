@@ -908,7 +908,7 @@ static bool linear_prefers_tile(int dtype, int mode, int M, int K, int N, const 
 }
 
 // The kernel for few outputs, one launch with every window row in every workgroup, against what the problem would take
-// otherwise.  Both sides measured, weights from HBM, hidden 512 .. 18944, 256 .. 8192 outputs, 4 .. 96 rows (us, this kernel
+// otherwise.  Both sides measured, weights from HBM, hidden 512 .. 18944, 256 .. 8192 outputs, 4 .. 256 rows (us, this kernel
 // first):
 //   up to 32 rows it takes the whole-row kernel's place (3584 x 3584 7.0 / 7.1 / 8.1 and 7.8 / 8.5 / 9.9 at 4 / 16 / 32 rows; hidden
 //   512 with less than two million weights is a draw), and the tiled GEMM's except gated at hidden 4096 beyond 7168 outputs
@@ -916,11 +916,12 @@ static bool linear_prefers_tile(int dtype, int mode, int M, int K, int N, const 
 //   the slice-wise kernel by estimate (2048 x 4096, 32 rows 5.7 and 8.4; 8192 x 3584, 4 rows 14.9 and 13.9; 12288 x 2048
 //   18.6 and 15.4; 18944 x 8192, 16 rows 52.2 and 57.9), small problems at hidden 1024 stay in the tile kernel (1024 x 1024
 //   4.5 and 4.3);
-//   beyond 32 rows the tiled GEMM cuts the hidden dimension of W_out and W_2, so this kernel gains as long as rows x hidden is
-//   small (3584 x 3584, 48 / 64 / 96 rows 9.5 / 10.9 / 14.2 and 10.9 / 11.3 / 12.8; 2048 x 2048 5.4 / 6.3 / 8.2 and 7.9 / 8.3 / 9.6; 4096 x
-//   1024, 64 rows 8.6 and 9.3); gated layers of few outputs leave it few workgroups at any hidden size (2048 x 2048, 64 rows 7.2
-//   and 13.7; 8192 x 2048, 96 rows 32.4 and 36.1; 4096 x 6144, 48 rows 21.5 and 24.3; 3584 x 8192 24.4 and 23.7); and widths that
-//   are no whole slabs would go to the tile kernel (3584 x 6000, 40 rows 12.3 and 29.0).
+//   beyond 32 rows the tiled GEMM cuts the hidden dimension of W_out and W_2, and gains where it is long or the outputs many
+//   (3584 x 3584, 64 / 128 / 256 rows 9.4 / 12.1 / 16.5 and 11.3 / 13.8 / 17.7; 2048 x 2048, 64 rows 6.1 and 8.3; 5120 x 5120 18.5 and 17.2;
+//   8192 x 2048, 256 rows 24.4 and 20.6; 3584 x 8192, 64 rows 17.5 and 16.8); gated layers of few outputs leave it few
+//   workgroups at any hidden size (2048 x 2048, 64 rows 7.2 and 13.7; 3584 x 4096, 128 rows 20.8 and 27.2; 4096 x 6144, 48 rows 21.5
+//   and 24.3; 3584 x 8192 24.4 and 23.7); and widths that are no whole slabs would go to the tile kernel (3584 x 6000,
+//   40 rows 12.3 and 29.0).
 static bool linear_prefers_lines(int dtype, int mode, int M, int K, int N, const FcWidePlan &wide, const FcSkinnyPlan &skinny, bool tile)
 {
     if (!fc_linear_lines_cover(dtype, mode, M, K, N) || fc_knobs().lin_wide_shape >= 0 || fc_knobs().lin_ksplit > 0 ||
@@ -931,10 +932,10 @@ static bool linear_prefers_lines(int dtype, int mode, int M, int K, int N, const
     if (M > 32) {
         if ((K <= 1024 && tile) || (K <= 512 && (M > 64 || weights > 2.7))) return false;
         if (wide.kind == 0 && K > 1024) return true;  // else the tile kernel
-        if (gated) return N <= 4096 || (N <= 6144 && K >= 3072);
-        const int64_t rows_k = (int64_t)((M + 15) / 16) * K;
+        if (gated) return N <= 4096 || (N <= 6144 && K >= 3072 && M <= 48);
         if (M > 64 && weights < 2.0) return false;
-        return rows_k <= (M <= 64 && N <= 2048 ? 16384 : N <= 4096 ? 14336 : 12288);
+        if (N > 5120) return M <= 96 && (int64_t)((M + 15) / 16) * K <= 12288;
+        return K <= 4096 || (K <= 5120 && N <= 3584 && M <= 192) || (K <= 8192 && N <= 1024);
     }
     if (wide.kind == 1) return gated ? K % 4096 != 0 || N <= 7168 : K <= 8192;
     if (skinny.kind == 2) return K > 512 || weights >= 2.0;

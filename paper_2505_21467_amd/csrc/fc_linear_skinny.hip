@@ -524,9 +524,9 @@ hipError_t launch_rows_mode(const dim3 &g, const LinArgs &a, hipStream_t s)
 }
 
 // -------------------------------------------------------------------------------------------------
-// Layers of at most 8192 outputs (two matrices: as many pairs) and 96 rows, hidden sizes that are multiples of 512.
+// Layers of at most 8192 outputs (two matrices: as many pairs) and 256 rows, hidden sizes that are multiples of 512.
 //
-// Every workgroup owns an equal run of outputs over the whole hidden dimension; its eight waves cut the hidden dimension, and
+// Every workgroup owns an equal run of outputs and a tile of up to 64 window rows over the whole hidden dimension; its eight waves cut the hidden dimension, and
 // each streams its part of the run's weight rows and of the window rows through LDS of its own, 64 hidden elements (one
 // line of every row) a stage, waiting for nobody until the waves' tiles are summed.  One launch, no partial tiles in memory.
 //   * Bound by what a compute unit takes in: weights from HBM, all window rows from L2.  Direct-to-LDS loads whose lanes lie
@@ -536,8 +536,8 @@ hipError_t launch_rows_mode(const dim3 &g, const LinArgs &a, hipStream_t s)
 //   * Where weight rows lie a multiple of 8 KB apart the workgroups of a die start at eight different stages: all at the
 //     same offset they meet in a part of the memory channels.
 //   * The epilogue goes by tasks of 16 outputs of four rows, dealt to all waves; the residual is asked for at the start.
-// us at 4 / 16 / 32 / 64 rows: 3584 x 3584 7.0 / 7.1 / 8.1 / 10.9 (k_linear_rows 7.8 / 8.5 / 9.9, tiled GEMM in parts 11.3);
-// gated 3584 x 4096 11.7 / 11.9 / 13.2 / 17.3 (13.9 / 14.8 / 16.3, 21.5); gated 2048 x 2048 5.0 / 5.1 / 5.5 / 7.2 (tile kernel 5.8 /
+// us at 4 / 16 / 32 / 64 rows: 3584 x 3584 7.0 / 7.1 / 8.1 / 9.4 (k_linear_rows 7.8 / 8.5 / 9.9, tiled GEMM in parts 11.3);
+// gated 3584 x 4096 11.7 / 11.9 / 13.2 / 16.8 (13.9 / 14.8 / 16.3, 21.5); gated 2048 x 2048 5.0 / 5.1 / 5.5 / 7.2 (tile kernel 5.8 /
 // 6.3, slice-wise 8.3, tiled GEMM 13.7); 8192 x 2048 11.3 / 11.6 / 12.9 (14.3 / 14.4 / 15.5).
 //
 // x / d, d given as 2^32 / d rounded up (0: d is 1); exact for x d < 2^32
@@ -553,6 +553,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rho = lane & 15, q = lane >> 4;
+    const int m0 = 16 * MT * blockIdx.y;  // (the runs are whole eights: the tiles of one are on one die)
     const int n0 = (int)quotient(blockIdx.x * (uint32_t)p.N, p.div_grid);
     const int R = (int)quotient((blockIdx.x + 1) * (uint32_t)p.N, p.div_grid) - n0;  // outputs of this workgroup
     const int n_stages = p.K / (8 * LINES_K);
@@ -572,7 +573,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int i = 0; i < 2 * MT; ++i) {
         const int r = 8 * i + (lane >> 3);
-        xoff[i] = (uint32_t)min(r, p.M - 1) * (uint32_t)(2 * p.K) + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+        xoff[i] = (uint32_t)min(m0 + r, p.M - 1) * (uint32_t)(2 * p.K) + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
     }
     const int turn0 = p.K % 4096 == 0 ? (blockIdx.x >> 3) & 7 : 0;  // n_stages is a multiple of 8 there
     auto issue = [&](int st) {
@@ -591,7 +592,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     uint16_t res[TASKS];
 #pragma unroll
     for (int j = 0; j < TASKS; ++j)
-        res[j] = MODE == FC_LIN_RESIDUAL && p.res ? p.res[(size_t)min(task_row(j), p.M - 1) * p.N + n0 + min(task_col(j), R - 1)] : 0;
+        res[j] = MODE == FC_LIN_RESIDUAL && p.res ? p.res[(size_t)min(m0 + task_row(j), p.M - 1) * p.N + n0 + min(task_col(j), R - 1)] : 0;
     __builtin_amdgcn_sched_barrier(0);
     issue(0);
     __builtin_amdgcn_sched_barrier(0);
@@ -642,9 +643,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < TASKS; ++j) {
-        const int m = task_row(j), c = task_col(j);
-        if (4 * ((wave + 8 * j) % (4 * MT)) >= p.M || (wave + 8 * j) / (4 * MT) >= NR) continue;
-        const unsigned char *part = lds + (((c >> 4) * MT + (m >> 4)) * NF) * 1280 + ((c & 15) >> 2) * 320 + (m & 15) * 16 + (c & 3) * 4;
+        const int ml = task_row(j), m = m0 + ml, c = task_col(j);
+        if (m0 + 4 * ((wave + 8 * j) % (4 * MT)) >= p.M || (wave + 8 * j) / (4 * MT) >= NR) continue;
+        const unsigned char *part = lds + (((c >> 4) * MT + (ml >> 4)) * NF) * 1280 + ((c & 15) >> 2) * 320 + (ml & 15) * 16 + (c & 3) * 4;
         float y[NF] = {};
 #pragma unroll
         for (int w2 = 0; w2 < 8; ++w2)
@@ -658,30 +659,42 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 uint32_t reciprocal(int d) { return (uint32_t)((((int64_t)1 << 32) + d - 1) / d); }
 
 template <int MT, int NR, int MODE>
-hipError_t launch_lines(LinArgs a, int grid, hipStream_t s)
+hipError_t launch_lines(LinArgs a, int runs, hipStream_t s)
 {
     constexpr int NF = MODE == FC_LIN_GATE_UP ? 2 : 1;
     const int ring = MT * 2048 + NF * NR * 2048, state = NR * NF * MT * 1280;
     a.wave_bytes = ring > state ? ring : state;
-    if ((a.N + grid - 1) / grid > 16 * NR || a.wave_bytes > 20 * 1024) return hipErrorInvalidValue;
-    a.div_grid = reciprocal(grid);
+    if ((a.N + runs - 1) / runs > 16 * NR || a.wave_bytes > 20 * 1024) return hipErrorInvalidValue;
+    a.div_grid = reciprocal(runs);
     static hipError_t attr = hipFuncSetAttribute((const void *)k_linear_lines<MT, NR, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return attr;
-    k_linear_lines<MT, NR, MODE><<<dim3((unsigned)grid), dim3(512), 8 * a.wave_bytes, s>>>(a);
+    k_linear_lines<MT, NR, MODE><<<dim3((unsigned)runs, (unsigned)((a.M + 16 * MT - 1) / (16 * MT))), dim3(512), 8 * a.wave_bytes, s>>>(a);
     return hipGetLastError();
 }
 
-// Runs of at least four outputs: with fewer the window rows are fetched for too little.
+// Tiles of 16 mt window rows and runs of outputs, one workgroup per compute unit; runs of at least four outputs: with fewer
+// the window rows are fetched for too little.
+struct LinesShape {
+    int row_tiles, runs, run;
+};
+LinesShape lines_shape(int N, int M, int mt)
+{
+    LinesShape s;
+    s.row_tiles = (M + 16 * mt - 1) / (16 * mt);
+    const int most = s.row_tiles > 32 ? 8 : 256 / s.row_tiles / 8 * 8;
+    s.runs = N >= 4 * most ? most : N >= 32 ? N / 32 * 8 : (N + 3) / 4;
+    s.run = (N + s.runs - 1) / s.runs;
+    return s;
+}
+
 template <int MT>
 hipError_t launch_lines_mt(int mode, const LinArgs &a, hipStream_t s)
 {
-    const int grid = a.N < 1024 ? (a.N + 3) / 4 : 256, run = (a.N + grid - 1) / grid;
-    if (mode == FC_LIN_GATE_UP) {
-        if (run <= 16) return launch_lines<MT, 1, FC_LIN_GATE_UP>(a, grid, s);
-        if constexpr (MT <= 3) return launch_lines<MT, 2, FC_LIN_GATE_UP>(a, grid, s);
-        return hipErrorInvalidValue;
-    }
-    return run <= 16 ? launch_lines<MT, 1, FC_LIN_RESIDUAL>(a, grid, s) : launch_lines<MT, 2, FC_LIN_RESIDUAL>(a, grid, s);
+    const LinesShape sh = lines_shape(a.N, a.M, MT);
+    if (mode == FC_LIN_GATE_UP) return sh.run <= 16 ? launch_lines<MT, 1, FC_LIN_GATE_UP>(a, sh.runs, s) : launch_lines<MT, 2, FC_LIN_GATE_UP>(a, sh.runs, s);
+    if (sh.run <= 16) return launch_lines<MT, 1, FC_LIN_RESIDUAL>(a, sh.runs, s);
+    if (sh.run <= 32) return launch_lines<MT, 2, FC_LIN_RESIDUAL>(a, sh.runs, s);
+    return launch_lines<MT, 4, FC_LIN_RESIDUAL>(a, sh.runs, s);
 }
 
 #ifndef FC_LIN_KSL
@@ -847,10 +860,34 @@ hipError_t fc_launch_linear_skinny(const FcSkinnyPlan &pl, int mode, const void 
     return mode == FC_LIN_GATE_UP ? launch_mode<FC_LIN_GATE_UP>(pl, a, s) : launch_mode<FC_LIN_RESIDUAL>(pl, a, s);
 }
 
+// Tiles of 16 window rows a workgroup takes; 0: not for this kernel.  Beyond 32 rows by an estimate (us: the window rows' and
+// the weights' way into a compute unit, the epilogue, the weights' from HBM; 11 % from 1200 measured times in the mean)
+// that picks within 1 % of the best of 32, 48 and 64 rows in the mean: 3584 x 3584, 64 / 96 / 128 / 176 rows 9.4 / 11.1 / 12.1 / 14.2, one tile of
+// all rows 10.9 / 14.2, tiled GEMM in parts 11.3 / 12.8 / 13.8 / 16.9.
+static int lines_tile(int mode, int M, int K, int N)
+{
+    const bool gated = mode == FC_LIN_GATE_UP;
+    if (M <= 32) return (M + 15) / 16;
+    double best = 1e30;
+    int mt = 0;
+    for (int t = 2; t <= 4; ++t) {
+        const LinesShape s = lines_shape(N, M, t);
+        if (s.run > (gated ? 32 : 64)) continue;
+        const double rows = M / (16.0 * s.row_tiles) < t ? M / (16.0 * s.row_tiles) : t, w = gated ? 2.0 : 1.0;
+        const double tail = 0.066 * w * t * (s.run <= 16 ? 1 : s.run <= 32 ? 2 : 4);
+        const double us = 1e-3 * K * (0.258 * rows + 0.0183 * w * s.run + 2.24e-4 * w * N) + tail;
+        if (us < best) {
+            best = us;
+            mt = t;
+        }
+    }
+    return mt;
+}
+
 bool fc_linear_lines_cover(int dtype, int mode, int M, int K, int N)
 {
-    return dtype == FC_BF16 && mode != FC_LIN_VOCAB && M >= 1 && M <= 96 && K >= 512 && K % 512 == 0 && N >= 1 &&
-           N <= (mode == FC_LIN_GATE_UP && M > 48 ? 4096 : 8192);
+    return dtype == FC_BF16 && mode != FC_LIN_VOCAB && M >= 1 && M <= 256 && K >= 512 && K % 512 == 0 && N >= 1 && N <= 8192 &&
+           lines_tile(mode, M, K, N) > 0;
 }
 
 hipError_t fc_launch_linear_lines(int mode, const void *x, const void *w, const void *w2, const void *res, int M, int K, int N,
@@ -867,12 +904,10 @@ hipError_t fc_launch_linear_lines(int mode, const void *x, const void *w, const 
     a.M = M;
     a.K = K;
     a.N = N;
-    switch ((M + 15) / 16) {
+    switch (lines_tile(mode, M, K, N)) {
     case 1: return launch_lines_mt<1>(mode, a, s);
     case 2: return launch_lines_mt<2>(mode, a, s);
     case 3: return launch_lines_mt<3>(mode, a, s);
-    case 4: return launch_lines_mt<4>(mode, a, s);
-    case 5: return launch_lines_mt<5>(mode, a, s);
-    default: return launch_lines_mt<6>(mode, a, s);
+    default: return launch_lines_mt<4>(mode, a, s);
     }
 }

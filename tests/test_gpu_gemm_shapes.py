@@ -149,6 +149,9 @@ def test_problem_cut_into_two_launches(M, N, gated):
     (96, 2048, 4096, True), (48, 3072, 4160, True),    # pairs of 16 at six tiles of rows; two weight tiles at three
     (64, 4096, 1024, False), (32, 4096, 8192, False),  # workgroups start at eight stages; runs of 32
     (20, 512, 8192, True), (3, 8192, 264, False),
+    (256, 2048, 2048, False), (200, 1536, 1000, False),  # four tiles of 64 rows; several tiles, the last ragged
+    (130, 2048, 4096, False), (65, 1536, 4100, False),   # three tiles, runs of 51 and 52; two tiles, runs of 32 and 33
+    (97, 1536, 2050, True), (128, 1536, 4096, True),     # pairs in runs of 25 and 26, and of 32
     (7, 3584, 8200, False),                            # one output quad too many: whole-row kernel
 ])
 def test_layers_of_few_outputs(M, K, N, gated):
