@@ -591,7 +591,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     auto task_col = [&](int j) { return 16 * ((wave + 8 * j) / (4 * MT)) + rho; };
     uint16_t res[TASKS];
 #pragma unroll
-    for (int j = 0; j < TASKS; ++j)
+    for (int j = 0; j < (MODE == FC_LIN_RESIDUAL ? TASKS : 0); ++j)
         res[j] = MODE == FC_LIN_RESIDUAL && p.res ? p.res[(size_t)min(m0 + task_row(j), p.M - 1) * p.N + n0 + min(task_col(j), R - 1)] : 0;
     __builtin_amdgcn_sched_barrier(0);
     issue(0);
@@ -641,6 +641,30 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
             for (int f = 0; f < NF; ++f) *(f32x4 *)(xbuf + ((t * MT + mt) * NF + f) * 1280 + q * 320 + rho * 16) = acc[t][f][mt];
     __syncthreads();
+    if constexpr (MODE == FC_LIN_VOCAB) {  // a wave per four rows, over all tiles of outputs
+        static_assert(MODE != FC_LIN_VOCAB || 4 * MT <= 8, "rows");
+        const int ml = 4 * wave + q;
+        if (wave >= 4 * MT || 4 * wave >= p.M) return;
+        float mx = -INFINITY, sm = 0.f;
+        int arg = 0x7fffffff;
+#pragma unroll
+        for (int t = 0; t < NR; ++t) {
+            if (16 * t >= R) break;
+            const unsigned char *part = lds + (t * MT + (ml >> 4)) * 1280 + (rho >> 2) * 320 + (ml & 15) * 16 + (rho & 3) * 4;
+            float y = 0.f;
+#pragma unroll
+            for (int w2 = 0; w2 < 8; ++w2) y += *(const float *)(part + w2 * p.wave_bytes);
+            if (16 * t + rho < R) fc_argmax_merge(mx, arg, sm, y, n0 + 16 * t + rho, 1.0f);
+        }
+#pragma unroll
+        for (int off = 1; off < 16; off <<= 1) {
+            const float mx2 = __shfl_xor(mx, off, 64), sm2 = __shfl_xor(sm, off, 64);
+            const int arg2 = __shfl_xor(arg, off, 64);
+            fc_argmax_merge(mx, arg, sm, mx2, arg2, sm2);
+        }
+        if (rho == 0 && ml < p.M) p.am.at(blockIdx.x, ml) = FcArgmax{mx, arg, sm};
+        return;
+    }
 #pragma unroll
     for (int j = 0; j < TASKS; ++j) {
         const int ml = task_row(j), m = m0 + ml, c = task_col(j);
@@ -882,6 +906,38 @@ static int lines_tile(int mode, int M, int K, int N)
         }
     }
     return mt;
+}
+
+template <int MT>
+static hipError_t launch_lines_vocab(const LinArgs &a, int runs, hipStream_t s)
+{
+    const int run = (a.N + runs - 1) / runs;
+    if (run <= 16) return launch_lines<MT, 1, FC_LIN_VOCAB>(a, runs, s);
+    if (run <= 32) return launch_lines<MT, 2, FC_LIN_VOCAB>(a, runs, s);
+    return launch_lines<MT, 4, FC_LIN_VOCAB>(a, runs, s);
+}
+
+// Vocabularies of up to 64 entries per workgroup: faster than what they took before at every size measured, 301 .. 16384 entries,
+// hidden 512 .. 5120, 1 .. 32 rows, the reduction included (us at 17 rows: hidden 3584, 2049 / 9001 / 15999 entries 15.7 / 22.4 / 31.8 in
+// the whole-row kernel, 10.7 / 18.6 / 26.9 here; hidden 1024, 5001 12.6 in the tile kernel, 9.2 here).
+int fc_lmhead_lines_parts(int dtype, int M, int K, int V, int parts)
+{
+    const int runs = parts < 256 ? parts : 256;
+    return dtype == FC_BF16 && M >= 1 && M <= 32 && K >= 512 && K % 512 == 0 && runs >= 1 && V >= runs && (V + runs - 1) / runs <= 64 ? runs : 0;
+}
+
+hipError_t fc_launch_lmhead_lines(const void *x, const void *w, int M, int K, int V, const FcArgmaxPart &am, hipStream_t s)
+{
+    if (fc_lmhead_lines_parts(FC_BF16, M, K, V, am.parts) != am.parts) return hipErrorInvalidValue;
+    LinArgs a;
+    memset(&a, 0, sizeof a);
+    a.X = (const uint16_t *)x;
+    a.W = (const uint16_t *)w;
+    a.am = am;
+    a.M = M;
+    a.K = K;
+    a.N = V;
+    return M <= 16 ? launch_lines_vocab<1>(a, am.parts, s) : launch_lines_vocab<2>(a, am.parts, s);
 }
 
 bool fc_linear_lines_cover(int dtype, int mode, int M, int K, int N)

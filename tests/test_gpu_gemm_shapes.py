@@ -164,3 +164,13 @@ def test_layers_of_few_outputs(M, K, N, gated):
         fc.fc_linear_residual("bf16", x.to(DEV), w.to(DEV), None, M, K, N, out, ws)
         ref = orc.linear_residual(inputs.as_oracle(x), inputs.as_oracle(w), None, "bf16")
         assert_close(inputs.as_oracle(out), ref, "bf16", "few outputs, no residual")
+
+
+@pytest.mark.parametrize("M,K,V", [
+    (1, 512, 2), (17, 3584, 33), (32, 512, 4097), (9, 1536, 8193), (32, 512, 16385), (31, 3584, 4095), (5, 4096, 300), (2, 512, 16384),
+])
+def test_small_vocabulary(M, K, V):
+    """Runs of one to 64 entries, one to four weight tiles, fewer entries than parts; 16385: one too many, whole-row kernel."""
+    print("[case] vocabulary", M, K, V, flush=True)
+    x, w = inputs.normal(25, "x", (M, K), 1.0, "bf16"), inputs.normal(25, "w", (V, K), 0.03, "bf16")
+    _check_lm_head("bf16", x, w, "small vocabulary of %d" % V)
