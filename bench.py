@@ -302,7 +302,8 @@ def hot_path_json(r, args_layers_note=""):
             "launch": "the timed steps are recorded into one HIP graph and replayed once",
         },
         "roofline": {
-            "kernel": "fc_active_attention (k_attn_mfma + k_attn_combine)",
+            "kernel": "fc_active_attention (%s)" % ("k_attn_mfma + k_attn_combine" if r["plan"]["splits"] > 1 else
+                                                    "k_attn_mfma" if r["plan"]["kind"] == 1 else "one launch over all keys"),
             "bound": "hbm",
             "achieved": round(attn_gbs, 1),
             "peak": HBM_PEAK_GBS,
