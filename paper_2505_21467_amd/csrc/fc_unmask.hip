@@ -390,8 +390,11 @@ __device__ __forceinline__ void accept_rows(const AccArgs &p, int b, int a0, int
                             c += v < v1 && acc_before(x[u], v, zh, th);
                         }
                     }
+                    // Up to ACC_MAXK of a lane count: topk is no more, so that the decision is the same.  (A lane of a large record
+                    // meets thousands.)
+                    c = min(c, ACC_MAXK);
 #pragma unroll
-                    for (int bit = 1; bit < 1024; bit <<= 1) total += bit * __builtin_popcountll(__ballot(c & bit));
+                    for (int bit = 1; bit <= ACC_MAXK; bit <<= 1) total += bit * __builtin_popcountll(__ballot(c & bit));
                 }
                 if (sh == h) count = total;
             }

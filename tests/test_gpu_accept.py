@@ -71,3 +71,47 @@ def test_entries_ahead_of_the_token_wherever_they_lie(A, V):
         got_t, k, pn, cn = _gpu_accept(dlm, ar, pos, 0, topk, 0.0, MASK, tokens)
         assert np.array_equal(k, want[0]) and np.array_equal(got_t, want_t)
         assert np.array_equal(pn, want[1]) and np.array_equal(cn, want[2])
+
+
+@pytest.mark.parametrize("V,parts", [(2097152, 0), (131072, 8), (140003, 8)])
+def test_many_entries_of_one_record_ahead_of_the_token(V, parts, knob):
+    """Records of 65536 entries and more (parts: asked for by the tuning knob), read again for topk 3 and 8: so many entries ahead of
+    the proposed token, or tied with it, that a lane of the wave meets 1024 of them, and just topk - 1, topk and topk + 1 in
+    one lane.  Behind the row under test one that matches: two accepted, or one."""
+    print("[case]", V, parts, flush=True)
+    from paper_2505_21467_amd import binding as fc
+    B, A, MASK, L, REC = 9, 2, 3000000, 2, 65536
+    if parts:
+        knob("FC_ACCEPT_WGS", str(parts * B * A))
+    assert fc.fc_guided_accept_workspace_bytes(B, A, V) == B * A * (8 + 16 * (parts or 128))
+    pos = np.arange(A, dtype=np.int32)[None].repeat(B, 0)
+    for topk in (2, 3, 8):
+        dlm = np.zeros((B, A, V), np.float32)
+        ar = np.full((B, A, V), -1.0, np.float32)
+        expect = []
+        for b in range(B):
+            t = V - 5 if b != 1 else 3  # in the last record, or in the first
+            dlm[b, 0, t], ar[b, 0, t] = 50.0, 9.0
+            dlm[b, 1, 7], ar[b, 1, 7] = 50.0, 9.0
+            lane = 11  # entries 11, 75, ... are one lane's
+            if b == 0:
+                ar[b, 0, :REC] = 10.0
+            elif b == 1:
+                ar[b, 0, -REC:] = 10.0
+            elif b == 2:
+                ar[b, 0, :REC] = 9.0  # smaller ids: ties count
+            elif b == 3:
+                ar[b, 0, lane:REC:64] = 10.0
+            elif b == 4:
+                ar[b, 0, :REC // 2] = 10.0
+            else:
+                n = topk - 1 + (0, 1, 2, 0)[b - 5]
+                ar[b, 0, lane:lane + 64 * n:64] = 10.0 if b < 8 else 9.0
+            expect.append(2 if b in (5, 8) else 1)
+        tokens = np.full((B, L), MASK, np.int32)
+        want_t = tokens.copy()
+        want = orc.guided_accept(dlm, ar, pos, topk, 0.0, MASK, want_t)
+        assert list(want[0]) == expect
+        got_t, n, pn, cn = _gpu_accept(dlm, ar, pos, 0, topk, 0.0, MASK, tokens)
+        assert np.array_equal(n, want[0]) and np.array_equal(got_t, want_t), (topk, n, want[0])
+        assert np.array_equal(pn, want[1]) and np.array_equal(cn, want[2])
