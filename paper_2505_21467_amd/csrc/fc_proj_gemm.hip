@@ -52,7 +52,7 @@ struct GemmArgs {
     int M, A, K, win_start;
     int n_mt;              // row tiles of 32 * NW window rows
     int n_units;           // head slots (NSUB = 4) or half-head slots (NSUB = 2)
-    uint32_t rot_step;     // ROTATE: stages / n_units in 1/65536
+    uint32_t rot_step;     // ROTATE: stages / (units of a round of workgroups) in 1/65536
     int n_slots;           // 128-row slabs of W: head slots (EPI 0), N / 128 (EPI 1, 3), d_ff / 64 (EPI 2)
     // The part of the problem this launch covers (a problem may be cut into two launches with different
     // tile shapes, see launch_pieces): slabs [slot_base, slot_base + slots_here), rows [m_base, m_end).
@@ -464,7 +464,15 @@ __global__ __launch_bounds__((NW + NL) * 64) void k_proj_gemm(GemmArgs p)
     // 15.3), and so it does with more row tiles, whose window rows then come from L2 at two places at a time (256 rows of
     // gated 4096 x 12288 66.9 and 70.3), and with the last rows of a problem, behind the launch that has just read the
     // weights (300 rows of the same 102.8 and 107.0).
-    const int rot = ROTATE ? (int)(((uint32_t)unit * p.rot_step) >> 16) : 0;
+    // More than one round of workgroups: by the place among the 256 that run together, 32 on each XCD.  (By unit / n_units
+    // those together cover a fifth of the hidden dimension at 1188 units.)  Vocabularies at hidden 4096, us without, by the
+    // unit, by the place: 64 rows, 33024 entries (258 units) 86.2, 72.8, 72.6; 50304 86.6, 82.1, 81.9; 65536 110.5, 92.5, 92.4; 98304 144.1,
+    // 140.8, 138.7; 152064 219.5, 217.2, 216.2; 196608 278.0, 270.0, 269.5; 96 rows, 65536 125.6, 100.7, 95.9; 106496 194.6, 177.9, 177.8.
+    // From four rounds on the workgroups drift apart by themselves and it is a few per cent either way: 96 rows,
+    // 128256 189.6, 196.3, 193.5 (the largest loss; 131072 192.3, 196.1, 197.4), 152064 234.0, 232.8, 231.4, 163840 255.4, 254.2, 249.9;
+    // 64 rows at hidden 2048, 131072 114.9, 96.1, 95.2; 96 rows at hidden 8192, 131072 377.0, 376.2, 380.2, 147456 445.4, 450.8, 456.0.
+    const int per_round = min(p.n_units, 256);
+    const int rot = ROTATE ? (int)(((uint32_t)(xcd * per_round / 8 + (qd & 31)) * p.rot_step) >> 16) : 0;
     auto issue_stage = [&](int st, int part) {
         const int sr = st + rot, at = st0 + (ROTATE && sr >= n_stages ? sr - n_stages : sr);
         unsigned char *dst = smem + (st % SLOTS) * STAGE;
@@ -835,7 +843,7 @@ hipError_t launch_gemm(GemmArgs a, hipStream_t s)
     };
     if constexpr (XROWS <= 128 && EPI != 3)
         if (a.n_mt == 1 && a.m_base == 0 && a.K % 2048 == 0 && a.K / KS < 65536) {
-            a.rot_step = (uint32_t)(((int64_t)(a.K / KS) << 16) / a.n_units);  // (unit * rot_step stays below 2^32)
+            a.rot_step = (uint32_t)(((int64_t)(a.K / KS) << 16) / (a.n_units < 256 ? a.n_units : 256));  // (place * rot_step stays below 2^32)
             return start(std::true_type());
         }
     return start(std::false_type());

@@ -90,6 +90,18 @@ def test_start_along_the_hidden_dimension(shape, M, K, N, knob):
         _check_lm_head("bf16", x, w, "vocabulary, shape %d" % shape)
 
 
+@pytest.mark.parametrize("shape,M,K,units", [(9, 33, 2048, 257), (9, 64, 2048, 520), (1, 128, 4096, 264), (10, 40, 2048, 258), (7, 61, 2048, 300)])
+def test_start_along_the_hidden_dimension_beyond_one_round(shape, M, K, units, knob):
+    """The same by the place of a workgroup among 256: one and two units more than a round, two rounds and eight."""
+    knob("FC_LIN_WIDE_SHAPE", str(shape))
+    if shape in (1, 9):
+        print("[case] vocabulary", shape, M, K, units, flush=True)
+        x, w = inputs.normal(25, "x", (M, K), 1.0, "bf16"), inputs.normal(25, "w", (128 * units, K), 0.01, "bf16")
+        _check_lm_head("bf16", x, w, "vocabulary, shape %d" % shape)
+    else:
+        _linear(M, K, {7: 48 * 64 * (units // 64 + 1), 10: 32 * units}[shape], True, "gated, shape %d" % shape)
+
+
 @pytest.mark.parametrize("V", [26624, 26496])
 def test_few_rows_vocabulary_on_both_sides_of_the_line(V):
     """208 slabs: tiled GEMM; 207: whole-row kernel."""
