@@ -274,6 +274,11 @@ def _traffic(r):
     return rec["bytes"], {"profile": rec["profile"], "plan": rec["plan"], "kernels": rec["kernels"]}
 
 
+def _attention_kernels(plan):
+    kernel, merge = (("k_attn_tile", "k_attn_tile_merge"), ("k_attn_mfma", "k_attn_combine"), ("k_attn_groups", ""))[plan["kind"]]
+    return kernel + " + " + merge if plan["splits"] > 1 else kernel
+
+
 def hot_path_json(r, args_layers_note=""):
     w, refresh = r["w"], r["refresh"]
     us_step, us_attn, us_proj = r["us_step"], r["us_attn"], r["us_proj"]
@@ -302,8 +307,7 @@ def hot_path_json(r, args_layers_note=""):
             "launch": "the timed steps are recorded into one HIP graph and replayed once",
         },
         "roofline": {
-            "kernel": "fc_active_attention (%s)" % ("k_attn_mfma + k_attn_combine" if r["plan"]["splits"] > 1 else
-                                                    "k_attn_mfma" if r["plan"]["kind"] == 1 else "one launch over all keys"),
+            "kernel": "fc_active_attention (%s)" % _attention_kernels(r["plan"]),
             "bound": "hbm",
             "achieved": round(attn_gbs, 1),
             "peak": HBM_PEAK_GBS,

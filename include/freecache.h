@@ -172,10 +172,11 @@ size_t fc_workspace_bytes(const fc_config *cfg, int32_t max_rows);
 /* The launch plan fc_active_attention would use for a window of A rows over kv_len cached rows with
  * fc_workspace_bytes(cfg, A) bytes of workspace (host, pure function of the shape and the tuning knobs; for reports and for tying a measured HBM
  * traffic figure to the plan it was measured with):
- *   plan[0] kind (0 tile kernels: fp32, head_dim 64, and bf16 of head_dim 128 over up to 1200 keys;
- *           1 split-KV kernel, 2 all keys in one launch: bf16 of head_dim 128)   plan[1] key ranges (splits)
- *   plan[2] keys per split   plan[3] 32-row (kind 0: 16-row) tiles per (sequence, kv head)
- *   plan[4] row tiles per workgroup (kind 2: eights of query rows)   plan[5] waves per workgroup
+ *   plan[0] kind (0 tile kernel: fp32, head_dim 64, and bf16 of head_dim 128 over up to 96 keys;
+ *           bf16 of head_dim 128: 1 split-KV kernel, 2 all keys in one launch, key groups summed in LDS)
+ *   plan[1] key ranges (splits)   plan[2] keys per split
+ *   plan[3] 16-row (kind 1: 32-row) tiles per (sequence, kv head)
+ *   plan[4] row tiles per workgroup   plan[5] waves per workgroup
  * Errors: INVALID_ARG, UNSUPPORTED (config), BOUNDS (kv_len). */
 fc_status fc_attention_plan(const fc_config *cfg, int32_t A, int32_t kv_len, int32_t plan[6]);
 

@@ -386,30 +386,32 @@ FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len, size_t cap
     }
     // one launch: 16 or 32 rows per workgroup, or (short keys only) the tile kernel
     const int64_t row_tiles = ((int64_t)g * A + 15) / 16;
-    auto one_launch = [&](int tiles, int v_parts, int waves) {
-        const bool tile = tiles == 1 && kv_len <= 1200;
-        p.kind = tile ? 0 : 2;
+    auto one_launch = [&](int kind, int tiles, int v_parts, int waves) {
+        p.kind = kind;
         p.splits = 1;
-        p.keys_per_split = tile ? (kv_len + 31) / 32 * 32 : (int)(n_stages * 64);
-        p.row_tiles = (int)(tile ? row_tiles : (row_tiles + 1) / 2);
-        p.tiles_per_wg = tile ? 1 : 2 * tiles;
+        p.keys_per_split = kind == 0 ? (kv_len + 31) / 32 * 32 : (int)(n_stages * 64);
+        p.row_tiles = (int)row_tiles;
+        p.tiles_per_wg = tiles;
         p.waves = waves;
-        p.group_tiles = v_parts ? tiles : 0;
         p.v_parts = v_parts;
     };
     if (pairs * row_tiles > 512) return p;
+    // Six waves beyond 1200 keys: the estimate takes them where the other shapes are as fast or faster.  60 drawn shapes of
+    // 1201 .. 3500 keys that would change, in the geometric mean 0.955 x (us without and with: 8 x 10 rows, 28 / 4 heads, 1425 keys 13.3 and
+    // 14.8; 3 x 45 rows, 1220 keys 11.8 and 12.5; 2 x 42 rows, 32 / 32 heads, 2716 keys 23.6 and 28.5); the others, most of them against
+    // the split-KV kernel, gain (6 x 13 rows, 32 / 32 heads, 1250 keys 27.2 and 23.2).
     for (const GroupsShape &sh : GROUPS_SHAPES) {
         const int64_t wgs = pairs * ((row_tiles + sh.tiles - 1) / sh.tiles) * sh.v_parts;
         if (wgs > 256 || (sh.waves == 6 && kv_len > 1200)) continue;
         const double t = attn_groups_cost(sh, pairs, wgs, kv_len);
         if (t < best) {
             best = t;
-            one_launch(sh.tiles, sh.v_parts, sh.waves);
+            one_launch(2, sh.tiles, sh.v_parts, sh.waves);
         }
     }
     // (32 rows x 28 heads, 32 / 64 keys 4.0 and 4.7 us; from 100 keys on the same or slower)
     if (kv_len <= 96 && pairs * row_tiles <= 256 && attn_tile_cost(pairs * row_tiles, ((int64_t)kv_len + 31) / 32, 16384) < best)
-        one_launch(1, 0, 8);
+        one_launch(0, 1, 0, 8);
     return p;
 }
 
@@ -702,7 +704,7 @@ static fc_status run_attention(fc_cache *cache, int32_t layer, const FcAttnPlan 
         return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", bytes, space);
     const FcGeom G = geom_of(cache);
     void *kl = layer_ptr(cache, cache->k, layer), *vl = layer_ptr(cache, cache->v, layer);
-    hipError_t e = plan.kind >= 1 || plan.group_tiles > 0
+    hipError_t e = plan.kind != 0
                        ? fc_launch_attention_mfma(G, plan, q, kl, vl, pos, A, kv_len, out, workspace,
                                                   (hipStream_t)stream)
                        : fc_launch_attention_tile(G, plan, cache->cfg.dtype, q, kl, vl, pos, A, kv_len, out, workspace,

@@ -863,9 +863,9 @@ hipError_t fc_launch_attention_mfma(const FcGeom &G, const FcAttnPlan &pl, const
     a.c = G.scale * 1.4426950408889634f;
     hipError_t e;
     const int R = pl.tiles_per_wg;
-    if (pl.group_tiles > 0) {  // all keys in one launch
+    if (pl.kind == 2) {  // all keys in one launch
         if (pl.splits != 1) return hipErrorInvalidValue;
-        if (pl.group_tiles == 2) return launch_groups<2, 2, 8>(a, s);
+        if (R == 2) return launch_groups<2, 2, 8>(a, s);
         if (pl.v_parts == 4) return launch_groups<1, 4, 8>(a, s);
         if (pl.v_parts == 2) return launch_groups<1, 2, 8>(a, s);
         if (pl.v_parts == 1) return launch_groups<1, 1, 6>(a, s);

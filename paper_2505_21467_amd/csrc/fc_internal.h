@@ -10,15 +10,14 @@
 
 // Launch plan of the split-KV attention (host, pure function of the shape).
 struct FcAttnPlan {
-    int kind;            // 0 = tile kernels (fp32, head_dim 64, bf16 head_dim 128 over short keys), 1 = bf16 head_dim 128 split-KV,
-                         // 2 = bf16 head_dim 128, longer keys without a split
+    int kind;            // 0 = k_attn_tile (fp32, head_dim 64, bf16 head_dim 128 over up to 96 keys); bf16 head_dim 128: 1 = k_attn_mfma,
+                         // split-KV, 2 = k_attn_groups, all keys in one launch
     int splits;          // key ranges per (sequence, kv head); every one is non-empty
     int keys_per_split;  // multiple of 64 (kind 0: of 32)
-    int row_tiles;       // 32-row (kind 0: 16-row) tiles of the flattened (head-in-group, a) rows per (b, kv head)
-    int tiles_per_wg;    // row tiles handled by one workgroup (kind 2: in eights of query rows)
+    int row_tiles;       // 16-row (kind 1: 32-row) tiles of the flattened (head-in-group, a) rows per (b, kv head)
+    int tiles_per_wg;    // row tiles handled by one workgroup
     int waves;           // waves per workgroup
-    int group_tiles;     // k_attn_groups: 16-row tiles of a workgroup (0: another kernel)
-    int v_parts;         // and parts the columns of V are cut into
+    int v_parts;         // kind 2: parts the columns of V are cut into
 };
 
 // A cache handle: written by fc_cache_alloc only.

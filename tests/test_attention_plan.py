@@ -21,10 +21,17 @@ def test_plans_cover_the_keys_and_fit_the_workspace():
             a, kv = rng.randint(1, rows), rng.randint(1, smax)
             p = fc.fc_attention_plan(c, a, kv)
             assert p["splits"] * p["keys_per_split"] >= kv > (p["splits"] - 1) * p["keys_per_split"], (a, kv, p)
-            if p["kind"] == 0:  # tile kernel: one round of workgroups, all keys in each
-                assert p["splits"] == p["tiles_per_wg"] == 1 and p["row_tiles"] * batch * hkv <= 256 and kv <= 1200, (a, kv, p)
+            if p["kind"] != 1:  # one round of workgroups, all keys in each: the tile kernel, or the one that sums groups of keys
+                assert p["splits"] == 1 and p["row_tiles"] == -(-g * a // 16), (a, kv, p)
+                assert -(-p["row_tiles"] // p["tiles_per_wg"]) * batch * hkv <= 256, (a, kv, p)
+            if p["kind"] == 0:
+                assert p["tiles_per_wg"] == 1 and p["waves"] == 8 and kv <= 96, (a, kv, p)
                 continue
-            assert p["keys_per_split"] % 64 == 0 and p["tiles_per_wg"] in (2, 4, 8) and p["waves"] in (4, 8)
+            assert p["keys_per_split"] % 64 == 0
+            if p["kind"] == 2:
+                assert (p["tiles_per_wg"], p["waves"]) in ((1, 8), (1, 6), (2, 8)) and (p["waves"] == 8 or kv <= 1200), (a, kv, p)
+                continue
+            assert p["kind"] == 1 and p["tiles_per_wg"] in (2, 4, 8) and p["waves"] in (4, 8)
             need = batch * hkv * p["row_tiles"] * p["splits"] * 32 * (256 + 16) if p["splits"] > 1 else 0
             assert need <= space, (a, kv, p, need, space)
 
@@ -106,8 +113,9 @@ def test_less_workspace_means_fewer_key_ranges(dt, B, Hq, Hkv, Dh, A, S):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("B,Hq,Hkv,A,S", [
-    (1, 2, 1, 3, 5), (1, 28, 4, 32, 96), (2, 3, 1, 100, 333),  # head dimension of V in four parts
-    (2, 28, 4, 20, 300), (8, 14, 2, 16, 64), (4, 32, 32, 9, 64),  # in two; uncut (two of them full)
+    (1, 2, 1, 3, 5), (1, 28, 4, 32, 96), (2, 3, 1, 100, 95),  # head dimension of V in four parts
+    (2, 28, 4, 20, 63), (8, 14, 2, 16, 64), (4, 32, 32, 9, 64),  # in two
+    (5, 32, 32, 9, 64), (7, 28, 4, 11, 33),  # uncut
 ])
 def test_short_keys_take_the_tile_kernel(B, Hq, Hkv, A, S):
     print("[case] short keys", B, Hq, Hkv, A, S, flush=True)
@@ -127,17 +135,17 @@ def test_short_keys_take_the_tile_kernel(B, Hq, Hkv, A, S):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("B,Hq,Hkv,A,S,kind,per_wg,waves", [
+@pytest.mark.parametrize("B,Hq,Hkv,A,S,per_wg,waves", [
     # 16 rows, V in four parts: a last stage of one key, of exactly a half and a whole one; one stage more than waves
-    (1, 3, 1, 5, 97, 0, 1, 8), (1, 3, 1, 6, 128, 0, 1, 8), (1, 28, 4, 9, 1025, 0, 1, 8), (2, 28, 4, 4, 513, 0, 1, 8), (1, 5, 1, 7, 577, 0, 1, 8),
-    (2, 1, 1, 1, 160, 0, 1, 8), (1, 8, 8, 33, 1300, 2, 2, 8),
+    (1, 3, 1, 5, 97, 1, 8), (1, 3, 1, 6, 128, 1, 8), (1, 28, 4, 9, 1025, 1, 8), (2, 28, 4, 4, 513, 1, 8), (1, 5, 1, 7, 577, 1, 8),
+    (2, 1, 1, 1, 160, 1, 8), (1, 8, 8, 33, 1300, 1, 8), (2, 3, 1, 100, 333, 1, 8),
     # in two parts; uncut, six waves
-    (2, 28, 4, 20, 129, 0, 1, 8), (3, 28, 4, 19, 1581, 2, 2, 8), (3, 32, 32, 8, 385, 0, 1, 8),
-    (4, 28, 4, 32, 321, 0, 1, 6), (5, 32, 32, 3, 385, 0, 1, 6), (2, 32, 32, 33, 769, 0, 1, 6),
+    (2, 28, 4, 20, 129, 1, 8), (2, 28, 4, 20, 300, 1, 8), (3, 28, 4, 19, 1581, 1, 8), (3, 32, 32, 8, 385, 1, 8),
+    (4, 28, 4, 32, 321, 1, 6), (5, 32, 32, 3, 385, 1, 6), (2, 32, 32, 33, 769, 1, 6),
     # 32 rows, V in two parts
-    (4, 28, 4, 31, 1217, 2, 4, 8), (4, 28, 4, 29, 1281, 2, 4, 8),
+    (4, 28, 4, 31, 1217, 2, 8), (4, 28, 4, 29, 1281, 2, 8),
 ])
-def test_all_keys_in_one_launch(B, Hq, Hkv, A, S, kind, per_wg, waves):
+def test_all_keys_in_one_launch(B, Hq, Hkv, A, S, per_wg, waves):
     print("[case] one launch", B, Hq, Hkv, A, S, flush=True)
     from oracle import fc_oracle as orc
     Dh, dt = 128, "bf16"
@@ -145,7 +153,7 @@ def test_all_keys_in_one_launch(B, Hq, Hkv, A, S, kind, per_wg, waves):
     g = GpuLayerCache(dt, B, 256, Hq, Hkv, Dh, S + 70, max_rows=A, fill=float("nan"))  # keys past kv_len are not numbers
     o = OracleLayerCache(dt, B, 256, Hq, Hkv, Dh, S + 70)
     p = fc.fc_attention_plan(g.cfg, A, S)
-    assert (p["kind"], p["splits"], p["tiles_per_wg"], p["waves"]) == (kind, 1, per_wg, waves), p
+    assert (p["kind"], p["splits"], p["tiles_per_wg"], p["waves"]) == (2, 1, per_wg, waves), p
     K, V = inputs.kv_fill(w, 2, S)
     g.write_rows(0, K, V, 0)
     o.write_rows(K, V, 0)
