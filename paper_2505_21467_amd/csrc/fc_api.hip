@@ -196,22 +196,22 @@ double attn_tile_cost(int64_t wgs, int64_t groups, int64_t group_bytes)
     return 4.28 + (0.229 + 1.18e-3 * (double)wgs) * g;
 }
 
-// The tile kernel of fp32 and of bf16 of head_dim 64, over `groups` groups of 32 keys per workgroup: start + each group + each
-// round of groups over the eight waves + what the other workgroups cost + each key range (uncut: operands by way of LDS; in
-// ranges: straight into registers, and a second kernel).  Fitted to 1200 shapes of 64 .. 2100 keys, 1 .. 250 workgroups (rms error 3 ..
-// 5 %, 13 % for fp32 rows of 128 in more than 128 workgroups and for two tiles per workgroup).  Rows: V in four parts, in two, uncut, two tiles per workgroup; in ranges.
+// The tile kernel of fp32 and of bf16 of head_dim 64, one tile per workgroup and at most 128 of them, over `groups` groups of 32 keys
+// per workgroup: start + each group + each round of groups over the eight waves + what the other workgroups cost + each key
+// range (uncut: operands by way of LDS; in ranges: straight into registers, and a second kernel).  Rows: V in four parts (up to 64
+// workgroups), in two; in ranges.  fp32 is fitted to 64 .. 2100 keys (rms error 3 .. 5 %), bf16 to 100 .. 16800.  What they choose
+// against the best number of ranges, 111 shapes of each of 4 .. 128 workgroups x 100 .. 16800 keys: 0.6 % slower in the mean and 8 % at
+// most for fp32 of head_dim 64 (beyond 2100 keys 1.0 and 7 %), 1.7 and 18 % for 128 (2.3 and 9 %), 0.4 and 11 % for bf16 (fitted to
+// the short ones only, it was 2.1 and 25 %: it cut 96 workgroups over 4200 keys in two, 20.6 us instead of 16.5).
 struct TileCost {
     double start, group, round, load, range;
 };
-const TileCost TILE_F32_64[] = {{3.53, 0.187, 0.320, 0.203, 0}, {3.68, 0.210, 0.488, 0.075, 0}, {4.38, 0.210, 0.581, 0.101, 0},
-                                {5.75, 0.152, 0.296, 0.635, 0}, {5.75, 0.156, 0.565, 0.320, 0.296}};
-const TileCost TILE_F32_128[] = {{4.00, 0.487, 0.092, 0.562, 0}, {4.99, 0.340, 1.076, 0.189, 0}, {6.13, 0.251, -0.828, 0.954, 0},
-                                 {6.13, 0.251, -0.828, 0.954, 0}, {6.24, 0.543, 0.031, 0.751, 0.411}};
-const TileCost TILE_BF16_64[] = {{3.54, 0.083, -0.057, 0.058, 0}, {3.57, 0.108, -0.155, 0.023, 0}, {3.99, 0.137, -0.424, 0.039, 0},
-                                 {4.33, -0.144, 1.142, 0.277, 0}, {6.50, 0.100, 0, 0.050, 0.270}};
-double attn_tile_ranges_cost(bool f32, int head_dim, int tiles_per_wg, int64_t wgs, int64_t groups, int64_t splits)
+const TileCost TILE_F32_64[] = {{3.53, 0.187, 0.320, 0.203, 0}, {3.68, 0.210, 0.488, 0.075, 0}, {5.75, 0.156, 0.565, 0.320, 0.296}};
+const TileCost TILE_F32_128[] = {{4.00, 0.487, 0.092, 0.562, 0}, {4.99, 0.340, 1.076, 0.189, 0}, {6.24, 0.543, 0.031, 0.751, 0.411}};
+const TileCost TILE_BF16_64[] = {{3.76, 0.084, 0, 0.039, 0}, {3.93, 0.091, 0, 0.018, 0}, {6.15, 0.111, 0, 0.129, 0.285}};
+double attn_tile_ranges_cost(bool f32, int head_dim, int64_t wgs, int64_t groups, int64_t splits)
 {
-    const int i = splits > 1 ? 4 : tiles_per_wg == 2 ? 3 : wgs <= 64 ? 0 : wgs <= 128 ? 1 : 2;
+    const int i = splits > 1 ? 2 : wgs <= 64 ? 0 : 1;
     const TileCost &c = !f32 ? TILE_BF16_64[i] : head_dim == 64 ? TILE_F32_64[i] : TILE_F32_128[i];
     return c.start + c.group * (double)groups + c.round * (double)((groups + 7) / 8) + c.load * (double)groups * (double)wgs / 256.0 + c.range * (double)splits;
 }
@@ -330,25 +330,38 @@ FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len, size_t cap
     if (cfg.dtype != FC_BF16 || cfg.head_dim != 128) {
         // kind 0: one workgroup per (sequence, kv head, one or two 16-row tiles); two tiles share the key
         // and value loads and are taken once they still fill half the chip (head_dim 64 only: with fp32 rows
-        // of 128 the operands of two tiles do not fit in registers).  The keys are cut into ranges where the
-        // estimate says that their shorter chains pay for the second launch that merges them (3 to 5 us).
+        // of 128 the operands of two tiles do not fit in registers).  The keys are cut into ranges, one round of workgroups
+        // at most, where their shorter chains pay for the second launch that merges them (3 to 5 us).
+        const bool f32 = cfg.dtype == FC_F32;
         const int64_t rows = (int64_t)g * A, pairs = (int64_t)cfg.batch * cfg.n_kv_heads;
         p.row_tiles = (int)((rows + 15) / 16);
         p.waves = 8;
         p.tiles_per_wg = cfg.head_dim == 64 && pairs * ((rows + 31) / 32) >= 128 ? 2 : 1;
         const int64_t base = pairs * ((p.row_tiles + p.tiles_per_wg - 1) / p.tiles_per_wg);
         const int64_t groups = ((int64_t)kv_len + 31) / 32;
+        auto cut = [&](int64_t n) {
+            FcAttnPlan c = p;
+            const int64_t per = (groups + n - 1) / n;
+            c.splits = (int)((groups + per - 1) / per);
+            c.keys_per_split = (int)(32 * per);
+            return c;
+        };
+        FcAttnPlan chosen = cut(1);
+        if (p.tiles_per_wg == 2) {
+            // Two tiles fill half a round at least: just half of one leaves a choice, and two ranges pay from 13 / 53 groups on
+            // (us uncut and in two, fp32: 200 keys 9.7 and 11.0, 384 13.0 and 13.4, 448 15.6 and 13.7, 700 20.7 and 16.9, 2100 46.5 and 33.1;
+            // bf16: 1000 keys 10.2 and 11.5, 1664 13.4 and 13.5, 1800 14.9 and 14.3, 4000 27.4 and 21.8).
+            const FcAttnPlan two = cut(2);
+            if (base == 128 && groups >= (f32 ? 13 : 53) && fc_plan_workspace(cfg, two) <= cap) chosen = two;
+            return chosen;
+        }
         double best = 1e30;
-        FcAttnPlan chosen = p;
-        for (int64_t n = 1; n == 1 || (n <= groups && n * base <= 256 && (p.tiles_per_wg == 1 || groups >= 32)); ++n) {
-            const int64_t per = (groups + n - 1) / n, splits = (groups + per - 1) / per;
-            const double t = attn_tile_ranges_cost(cfg.dtype == FC_F32, cfg.head_dim, p.tiles_per_wg, base * splits, per, splits);
-            FcAttnPlan cut = p;
-            cut.splits = (int)splits;
-            cut.keys_per_split = (int)(32 * per);
-            if (t < best && fc_plan_workspace(cfg, cut) <= cap) {
+        for (int64_t n = 1; n <= groups && n * base <= 256; ++n) {
+            const FcAttnPlan c = cut(n);
+            const double t = attn_tile_ranges_cost(f32, cfg.head_dim, base * c.splits, c.keys_per_split / 32, c.splits);
+            if (t < best && fc_plan_workspace(cfg, c) <= cap) {
                 best = t;
-                chosen = cut;
+                chosen = c;
             }
         }
         return chosen;

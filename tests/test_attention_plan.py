@@ -36,6 +36,36 @@ def test_plans_cover_the_keys_and_fit_the_workspace():
             assert need <= space, (a, kv, p, need, space)
 
 
+@pytest.mark.parametrize("dt,line", [("f32", 13 * 32), ("bf16", 53 * 32)])
+def test_two_tiles_per_workgroup_are_cut_where_they_fill_half_a_round(dt, line):
+    """128 workgroups of two tiles: in two ranges from the line on, space permitting; more workgroups: never cut."""
+    for hkv, A, keys, splits in ((4, 128, line - 32, 1), (4, 128, line, 2), (4, 113, line - 31, 2), (4, 160, 16000, 1), (1, 1000, 16000, 2)):
+        c = fc.make_config(1, 8 if hkv == 4 else 4, 256, hkv, hkv, 64, keys, dt)
+        p = fc.fc_attention_plan(c, A, keys)
+        assert (p["kind"], p["tiles_per_wg"], p["splits"]) == (0, 2, splits), (A, keys, p)
+        per = -(-keys // 32 // splits) if keys % 32 == 0 else -(-(keys // 32 + 1) // splits)
+        assert p["keys_per_split"] == 32 * per
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt,A,S", [("f32", 128, 416), ("f32", 113, 449), ("bf16", 120, 1696), ("bf16", 113, 1697)])
+def test_two_tiles_per_workgroup_in_two_ranges(dt, A, S):
+    print("[case] two tiles", dt, A, S, flush=True)
+    from oracle import fc_oracle as orc
+    B, H, Dh = 8, 4, 64
+    w = inputs.Workload("t", dt, B, 256, H, H, Dh, S, A)
+    g = GpuLayerCache(dt, B, 256, H, H, Dh, S + 3, max_rows=A, fill=float("nan"))  # keys past kv_len are not numbers
+    o = OracleLayerCache(dt, B, 256, H, H, Dh, S + 3)
+    assert fc.fc_attention_plan(g.cfg, A, S)["splits"] == 2
+    K, V = inputs.kv_fill(w, 2, S)
+    g.write_rows(0, K, V, 0)
+    o.write_rows(K, V, 0)
+    Q = inputs.normal(2, "q", (B, H, A, Dh), 1.0, dt)
+    O = g.attend(0, g.dev_t(Q), S)
+    assert_close(inputs.as_oracle(O), orc.attend(o.cfg, inputs.as_oracle(Q), o.Kc, o.Vc, S, None), dt, "two tiles")
+    g.close()
+
+
 def test_window_rows_times_heads_beyond_32_bits():
     c = fc.make_config(1, 1, 256, 256, 1, 128, 100, "bf16")
     p = fc.fc_attention_plan(c, 1 << 24, 100)  # 2^32 query rows: the split-KV kernel, not a tile kernel of no tiles
