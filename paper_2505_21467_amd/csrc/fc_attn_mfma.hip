@@ -101,28 +101,11 @@ __device__ __forceinline__ float row_sum16(float v)
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// x / d, d given as 2^32 / d rounded up (0: d is 1); exact for x d < 2^32
-__device__ __forceinline__ uint32_t quotient(uint32_t x, uint32_t reciprocal) { return reciprocal ? __umulhi(x, reciprocal) : x; }
-
 __device__ __forceinline__ bool row_is_padded(const int32_t *pos, int idx, int max_seq)
 {
     if (!pos) return false;
     const int p = pos[idx];
     return p < 0 || p >= max_seq;
-}
-
-__device__ __forceinline__ void load_lds16(const void *g, void *l)
-{
-    __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)g,
-                                     (void __attribute__((address_space(3))) *)l, 16, 0, 0);
-}
-
-// wait until at most N of this wave's vector-memory operations are outstanding
-template <int N>
-__device__ __forceinline__ void wait_vm()
-{
-    // gfx9 s_waitcnt immediate: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] at [15:14]
-    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
 // State of one 32-row tile inside a wave.
@@ -268,7 +251,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         const unsigned char *src = gsrc + (size_t)st * (STAGE_BYTES / 2);  // 64 keys * 256 B for K and for V
         unsigned char *dst = smem + (st % SLOTS) * STAGE_BYTES + lds_dst;
 #pragma unroll
-        for (int i = 0; i < LB; ++i) load_lds16(src + goff[i], dst + i * 1024);
+        for (int i = 0; i < LB; ++i) fc_load_lds16(src + goff[i], dst + i * 1024);
     };
 
     // ---- operand read offsets inside a stage (bytes)
@@ -292,17 +275,17 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             // stage it-1: the load can go out ahead of this stage's barrier.
             if (it + AHEAD < n_stages) {
                 issue_stage(it + AHEAD);
-                wait_vm<2 * LB>();
+                fc_wait_vm<2 * LB>();
             } else if (it + 1 < n_stages) {
-                wait_vm<LB>();
+                fc_wait_vm<LB>();
             } else {
-                wait_vm<0>();
+                fc_wait_vm<0>();
             }
             __builtin_amdgcn_s_barrier();
         } else {
             // Two slots: the next stage overwrites stage it-1, which other waves may still be reading
             // until they arrive at this barrier, so its load goes out behind the barrier.
-            wait_vm<0>();
+            fc_wait_vm<0>();
             __builtin_amdgcn_s_barrier();
             if (it + 1 < n_stages) issue_stage(it + 1);
         }
@@ -466,7 +449,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             rowid[col] = row_valid[u] ? dst : ~(size_t)0;
         }
         __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the staged tile is visible to the whole wave
+        fc_wait_lds();  // lgkmcnt(0): the staged tile is visible to the whole wave
 #pragma unroll 2
         for (int i = 0; i < 16; ++i) {
             const int idx = i * 64 + lane;
@@ -482,7 +465,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             *(uint2 *)o = w;
         }
         __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_s_waitcnt(0xc07f);  // reads of the staging area are done before the next tile reuses it
+        fc_wait_lds();  // reads of the staging area are done before the next tile reuses it
     }
 }
 
@@ -507,7 +490,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((NW + 3
     const uint32_t per_pair = (uint32_t)p.row_tiles * VP, n_tiles = (uint32_t)p.n_units * per_pair;
     const uint32_t tile = xcd * n_tiles / 8 + qd;
     if (tile >= (xcd + 1) * n_tiles / 8) return;
-    const int bj = (int)quotient(tile, p.div_pair), mine = (int)(tile - bj * per_pair);
+    const int bj = (int)fc_quotient(tile, p.div_pair), mine = (int)(tile - bj * per_pair);
     const int rt = mine / VP, vp = mine - rt * VP;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -534,12 +517,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((NW + 3
     auto issue_k = [&](int i) {  // half i & 1 of the wave's stage i >> 1
         const unsigned char *src = kbase + (size_t)(wave + NW * (i >> 1)) * (64 * 256) + (i & 1) * (32 * 256);
 #pragma unroll
-        for (int l = 0; l < NK; ++l) load_lds16(src + koff[l], kbuf + l * 1024);
+        for (int l = 0; l < NK; ++l) fc_load_lds16(src + koff[l], kbuf + l * 1024);
     };
     auto issue_v = [&](int t) {
         const unsigned char *src = vbase + (size_t)(wave + NW * t) * (FC_VTILE * 256);
 #pragma unroll
-        for (int l = 0; l < NV; ++l) load_lds16(src + voff[l], vbuf + l * 1024);
+        for (int l = 0; l < NV; ++l) fc_load_lds16(src + voff[l], vbuf + l * 1024);
     };
     if (n > 0) {
         issue_k(0);
@@ -548,14 +531,14 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((NW + 3
     __builtin_amdgcn_sched_barrier(0);
 
     // query rows (past the end: the last row, never stored)
-    const int b = (int)quotient(bj, p.div_hkv), j = bj - b * p.Hkv;
+    const int b = (int)fc_quotient(bj, p.div_hkv), j = bj - b * p.Hkv;
     bf16x8 qf[QT][4];
     size_t orow[QT];  // output row (element offset)
     int pp[QT];
 #pragma unroll
     for (int u = 0; u < QT; ++u) {
         const int row = min(rt * (16 * QT) + 16 * u + rho, p.g * p.A - 1);
-        const int hg = (int)quotient(row, p.div_a), a = row - hg * p.A, hq = j * p.g + hg;
+        const int hg = (int)fc_quotient(row, p.div_a), a = row - hg * p.A, hq = j * p.g + hg;
         const uint16_t *qrow = p.Q + (((size_t)b * p.Hq + hq) * p.A + a) * DH + 8 * q;
 #pragma unroll
         for (int s = 0; s < 4; ++s) qf[u][s] = fc_load_any<bf16x8>(qrow + 32 * s);
@@ -584,8 +567,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((NW + 3
         for (int half = 0; half < 2; ++half) {
             const int i = 2 * t + half, kb = ks0 + 32 * half;
             // this group has arrived, with the first one the stage's values too; the next stage's values may stay in flight
-            if (half == 1 && t + 1 < n) wait_vm<NV>();
-            else wait_vm<0>();
+            if (half == 1 && t + 1 < n) fc_wait_vm<NV>();
+            else fc_wait_vm<0>();
             __builtin_amdgcn_sched_barrier(0);
             bf16x8 kf[2][4];
 #pragma unroll
@@ -598,7 +581,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((NW + 3
 #pragma unroll
                     for (int d = 0; d < ND; ++d) vf[h][d] = *(const bf16x8 *)(vbuf + d * 2048 + vfo[h]);
             }
-            __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the areas may be overwritten
+            fc_wait_lds();  // lgkmcnt(0): the areas may be overwritten
             __builtin_amdgcn_sched_barrier(0);
             if (half == 0 || t + 1 < n) issue_k(i + 1);
             if (half == 0 && t + 1 < n) issue_v(t + 1);
@@ -821,12 +804,11 @@ hipError_t launch_groups(AttnArgs a, hipStream_t s)
     const int64_t rows = (int64_t)a.g * a.A, row_tiles = (rows + 16 * QT - 1) / (16 * QT), pairs = (int64_t)a.B * a.Hkv;
     const int64_t n = pairs * row_tiles * VP;
     if (n > 4096 || rows > 32768) return hipErrorInvalidValue;
-    auto reciprocal = [](int64_t d) { return (uint32_t)((((int64_t)1 << 32) + d - 1) / d); };  // (d = 1: 0)
     a.row_tiles = (int)row_tiles;
     a.n_units = (int)pairs;
-    a.div_pair = reciprocal(row_tiles * VP);
-    a.div_hkv = reciprocal(a.Hkv);
-    a.div_a = reciprocal(a.A);
+    a.div_pair = fc_reciprocal(row_tiles * VP);
+    a.div_hkv = fc_reciprocal(a.Hkv);
+    a.div_a = fc_reciprocal(a.A);
     k_attn_groups<QT, VP, NW><<<dim3((unsigned)((n + 7) / 8 * 8)), dim3(NW * 64), LDS_BYTES, s>>>(a);
     return hipGetLastError();
 }

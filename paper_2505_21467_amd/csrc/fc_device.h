@@ -1,4 +1,5 @@
-// Device-side helpers shared by the kernel files: storage-type conversion, pieces of tensors at any element.
+// Device-side helpers shared by the kernel files: storage-type conversion, pieces of tensors at any element, loads into LDS
+// and the waits for them, quotients by a launch's constants.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -39,6 +40,27 @@ __device__ __forceinline__ void fc_store_any(void *p, V v)
     if constexpr (sizeof(V) == 16) *(fc_any16 *)p = __builtin_bit_cast(fc_any16, v);
     else *(fc_any8 *)p = __builtin_bit_cast(fc_any8, v);
 }
+
+// Direct-to-LDS load: 16 bytes per lane, from a global address of each lane's own to the wave's `l` + 16 lane.
+__device__ __forceinline__ void fc_load_lds16(const void *g, void *l)
+{
+    __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)g,
+                                     (void __attribute__((address_space(3))) *)l, 16, 0, 0);
+}
+
+// Wait until at most N of this wave's vector-memory operations are outstanding; LGKM0: and no LDS one.
+template <int N, bool LGKM0 = false>
+__device__ __forceinline__ void fc_wait_vm()
+{
+    // gfx9 s_waitcnt immediate: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] at [15:14]
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | ((LGKM0 ? 0 : 15) << 8) | ((N >> 4) << 14));
+}
+// Until no LDS operation is outstanding (lgkmcnt(0)).
+__device__ __forceinline__ void fc_wait_lds() { fc_wait_vm<63, true>(); }
+
+// x / d, d given as 2^32 / d rounded up (0: d is 1); exact for x d < 2^32.
+inline uint32_t fc_reciprocal(int64_t d) { return (uint32_t)((((int64_t)1 << 32) + d - 1) / d); }
+__device__ __forceinline__ uint32_t fc_quotient(uint32_t x, uint32_t reciprocal) { return reciprocal ? __umulhi(x, reciprocal) : x; }
 
 template <typename T>
 __device__ __forceinline__ T fc_from_float(float f);

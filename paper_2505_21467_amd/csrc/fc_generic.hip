@@ -75,19 +75,6 @@ struct Op<bf16_t> {
     }
 };
 
-__device__ __forceinline__ void load_lds16t(const void *g, void *l)
-{
-    __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)g,
-                                     (void __attribute__((address_space(3))) *)l, 16, 0, 0);
-}
-
-// wait until at most N of this wave's vector-memory operations are outstanding
-template <int N>
-__device__ __forceinline__ void wait_vmt()
-{
-    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
-
 __device__ __forceinline__ float partner32(float v)  // the value of lane ^ 32
 {
     const unsigned u = __float_as_uint(v);
@@ -209,9 +196,9 @@ __global__ __launch_bounds__(TW * 64) void k_linear_tile(TileArgs p)
             if (b + u >= b1) break;
             const int at = (b + u) * 4 * KB;
 #pragma unroll
-            for (int t = 0; t < NT; ++t) load_lds16t(wrow[t] + at, buf + (u * (NT + MT) + t) * 1024);
+            for (int t = 0; t < NT; ++t) fc_load_lds16(wrow[t] + at, buf + (u * (NT + MT) + t) * 1024);
 #pragma unroll
-            for (int t = 0; t < MT; ++t) load_lds16t(xrow[t] + at, buf + (u * (NT + MT) + NT + t) * 1024);
+            for (int t = 0; t < MT; ++t) fc_load_lds16(xrow[t] + at, buf + (u * (NT + MT) + NT + t) * 1024);
         }
     };
     auto load = [&](int b, frag(&wf)[U][NT], frag(&xf)[U][MT]) {
@@ -270,7 +257,7 @@ __global__ __launch_bounds__(TW * 64) void k_linear_tile(TileArgs p)
     if constexpr (LDS) {
         const int at = rho * 64 + ((q ^ (rho >> 2)) << 4);
         for (int b = b0; b < b1; b += U) {
-            wait_vmt<0>();
+            fc_wait_vm<0>();
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -279,7 +266,7 @@ __global__ __launch_bounds__(TW * 64) void k_linear_tile(TileArgs p)
 #pragma unroll
                 for (int t = 0; t < MT; ++t) xa[u][t] = *(const frag *)(buf + (u * (NT + MT) + NT + t) * 1024 + at);
             }
-            __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the area may be overwritten
+            fc_wait_lds();  // lgkmcnt(0): the area may be overwritten
             __builtin_amdgcn_sched_barrier(0);
             if (b + U < b1) issue(b + U);
             __builtin_amdgcn_sched_barrier(0);
@@ -537,7 +524,7 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
         for (int l = 0; l < L::NK; ++l) {
             const int at = 1024 * l + 16 * lane, row = at / L::KROW, c = (at % L::KROW) >> 4, r = part * L::KG + row;
             const unsigned char *src = (const unsigned char *)kc + (size_t)(32 * g + key_of(r >> 4, r & 15)) * L::KROW;
-            load_lds16t(src + 16 * (c ^ L::template swizzle<L::KROW>(row)), kbuf + 1024 * l);
+            fc_load_lds16(src + 16 * (c ^ L::template swizzle<L::KROW>(row)), kbuf + 1024 * l);
         }
     };
     auto issue_v = [&](int g, int part) {
@@ -545,7 +532,7 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
 #pragma unroll
         for (int l = 0; l < L::NVL; ++l) {
             const int at = 1024 * l + 16 * lane, row = at / L::VROW, c = (at % L::VROW) >> 4;
-            load_lds16t(vt + (size_t)(dv0 + row) * (FC_VTILE * sizeof(T)) + 16 * (c ^ L::template swizzle<L::VROW>(row)), vbuf + 1024 * l);
+            fc_load_lds16(vt + (size_t)(dv0 + row) * (FC_VTILE * sizeof(T)) + 16 * (c ^ L::template swizzle<L::VROW>(row)), vbuf + 1024 * l);
         }
     };
     frag kd[2][NKB], vd[ND][NV];  // without LDS
@@ -599,8 +586,8 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
         if constexpr (LDS) {
 #pragma unroll
             for (int part = 0; part < 32 / L::KG; ++part) {
-                if (part == 0) wait_vmt<L::NVL>();  // these keys are here; the values behind them may stay in flight
-                else wait_vmt<0>();
+                if (part == 0) fc_wait_vm<L::NVL>();  // these keys are here; the values behind them may stay in flight
+                else fc_wait_vm<0>();
                 __builtin_amdgcn_sched_barrier(0);
                 frag kf[L::KG / 16][NKB];
 #pragma unroll
@@ -608,7 +595,7 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
 #pragma unroll
                     for (int k = 0; k < NKB; ++k)
                         kf[h][k] = *(const frag *)(kbuf + (16 * h + rho) * L::KROW + 16 * ((4 * k + q) ^ L::template swizzle<L::KROW>(16 * h + rho)));
-                __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the area may be overwritten
+                fc_wait_lds();  // lgkmcnt(0): the area may be overwritten
                 __builtin_amdgcn_sched_barrier(0);
                 if (part + 1 < 32 / L::KG) issue_k(g, part + 1);
                 else if (more) issue_k(g + TW, 0);
@@ -676,8 +663,8 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
         if constexpr (LDS) {
 #pragma unroll
             for (int part = 0; part < 32 / L::VG; ++part) {
-                if (part == 0 && more) wait_vmt<L::NK>();  // these values are here; the next keys may stay in flight
-                else wait_vmt<0>();
+                if (part == 0 && more) fc_wait_vm<L::NK>();  // these values are here; the next keys may stay in flight
+                else fc_wait_vm<0>();
                 __builtin_amdgcn_sched_barrier(0);
                 constexpr int NVP = NV * L::VG / 32;  // fragments per 16 rows
                 frag vf[ND][NVP];
@@ -686,7 +673,7 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
 #pragma unroll
                     for (int h = 0; h < NVP; ++h)
                         vf[d][h] = *(const frag *)(vbuf + (16 * d + rho) * L::VROW + 16 * ((4 * h + q) ^ L::template swizzle<L::VROW>(16 * d + rho)));
-                __builtin_amdgcn_s_waitcnt(0xc07f);
+                fc_wait_lds();
                 __builtin_amdgcn_sched_barrier(0);
                 if (part + 1 < 32 / L::VG) issue_v(g, part + 1);
                 else if (more) issue_v(g + TW, 0);

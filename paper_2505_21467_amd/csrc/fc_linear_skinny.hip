@@ -55,19 +55,6 @@ __device__ __forceinline__ bf16x8 ld8(const uint16_t *p)
     return x.v;
 }
 
-__device__ __forceinline__ void load_lds16(const void *g, void *l)
-{
-    __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)g,
-                                     (void __attribute__((address_space(3))) *)l, 16, 0, 0);
-}
-
-// wait until at most N of this wave's vector-memory operations are outstanding
-template <int N>
-__device__ __forceinline__ void wait_vm()
-{
-    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
-
 __device__ __forceinline__ float swap32(float v)
 {
     const unsigned u = __float_as_uint(v);
@@ -111,7 +98,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(KSL >= 512 
             const int mrow = ld * RPL + lane / (64 / RPL);
             const int c = (lane % (64 / RPL)) ^ (mrow & 15);  // chunk c of row m is stored at c ^ (m & 15)
             const int mg = min(m0 + mrow, p.M - 1);            // padding rows read a valid row
-            load_lds16(p.X + (size_t)mg * p.K + (size_t)sl * KSL + c * 8, xb + ld * 1024);
+            fc_load_lds16(p.X + (size_t)mg * p.K + (size_t)sl * KSL + c * 8, xb + ld * 1024);
         }
         const uint16_t *wrow;
         if (MODE == FC_LIN_GATE_UP)
@@ -362,7 +349,7 @@ __global__ __launch_bounds__(512) void k_linear_rows(LinArgs p)
         for (int i = 0; i < NKW; ++i) {
             const int byte = 1024 * i + 16 * lane, r = byte / XROW, c = (byte - r * XROW) >> 4;
             const int m = min(16 * mt + r, p.M - 1);  // padding rows read a valid row
-            load_lds16(p.X + (size_t)m * p.K + wave * (NKW * 32) + 8 * (c ^ xswz(r)), xw + 1024 * i);
+            fc_load_lds16(p.X + (size_t)m * p.K + wave * (NKW * 32) + 8 * (c ^ xswz(r)), xw + 1024 * i);
         }
         if (mt == MT - 1) {
             __builtin_amdgcn_sched_barrier(0);
@@ -370,16 +357,16 @@ __global__ __launch_bounds__(512) void k_linear_rows(LinArgs p)
 #pragma unroll
             for (int s = 0; s < NKW; ++s) wf[s] = ld8(cur + 32 * s);
             __builtin_amdgcn_sched_barrier(0);
-            wait_vm<NKW>();  // everything before the weights
+            fc_wait_vm<NKW>();  // everything before the weights
         } else {
-            wait_vm<0>();
+            fc_wait_vm<0>();
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int s = 0; s < NKW; ++s)
             xr[s][mt] = *(const bf16x8 *)(xw + rho * XROW + (((4 * s + q) ^ xswz(rho)) << 4));
         __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the LDS rows may be overwritten
+        fc_wait_lds();  // lgkmcnt(0): the LDS rows may be overwritten
         __builtin_amdgcn_sched_barrier(0);
     }
     __builtin_amdgcn_s_barrier();  // the partial tiles reuse the area
@@ -476,7 +463,7 @@ __global__ __launch_bounds__(512) void k_linear_rows(LinArgs p)
         constexpr bool MORE = decltype(more)::value;
         // The previous item is finished here, one iteration late: what it loads or stores is then issued
         // behind the wait for this item's fragments and never part of it.
-        __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8) | (0 << 14));  // vmcnt(0): this item's fragments have landed
+        fc_wait_vm<0>();  // vmcnt(0): this item's fragments have landed
         __builtin_amdgcn_sched_barrier(0);
         if (it > it0 && wave < MT) finish_item(it - 1, buf ^ 1);
         __builtin_amdgcn_sched_barrier(0);
@@ -498,7 +485,7 @@ __global__ __launch_bounds__(512) void k_linear_rows(LinArgs p)
                 mine[(mt * 4 + r) * 64] = acc[mt][r];
                 acc[mt][r] = 0.f;
             }
-        __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));  // lgkmcnt(0): the tile is in LDS
+        fc_wait_lds();  // lgkmcnt(0): the tile is in LDS
         __builtin_amdgcn_s_barrier();
         buf ^= 1;
     };
@@ -540,9 +527,6 @@ hipError_t launch_rows_mode(const dim3 &g, const LinArgs &a, hipStream_t s)
 // gated 3584 x 4096 11.7 / 11.9 / 13.2 / 16.8 (13.9 / 14.8 / 16.3, 21.5); gated 2048 x 2048 5.0 / 5.1 / 5.5 / 7.2 (tile kernel 5.8 /
 // 6.3, slice-wise 8.3, tiled GEMM 13.7); 8192 x 2048 11.3 / 11.6 / 12.9 (14.3 / 14.4 / 15.5).
 //
-// x / d, d given as 2^32 / d rounded up (0: d is 1); exact for x d < 2^32
-__device__ __forceinline__ uint32_t quotient(uint32_t x, uint32_t reciprocal) { return reciprocal ? __umulhi(x, reciprocal) : x; }
-
 constexpr int LINES_K = 64;  // hidden elements per stage: one 128-byte line of every row
 
 template <int MT, int NR, int MODE>
@@ -554,8 +538,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rho = lane & 15, q = lane >> 4;
     const int m0 = 16 * MT * blockIdx.y;  // (the runs are whole eights: the tiles of one are on one die)
-    const int n0 = (int)quotient(blockIdx.x * (uint32_t)p.N, p.div_grid);
-    const int R = (int)quotient((blockIdx.x + 1) * (uint32_t)p.N, p.div_grid) - n0;  // outputs of this workgroup
+    const int n0 = (int)fc_quotient(blockIdx.x * (uint32_t)p.N, p.div_grid);
+    const int R = (int)fc_quotient((blockIdx.x + 1) * (uint32_t)p.N, p.div_grid) - n0;  // outputs of this workgroup
     const int n_stages = p.K / (8 * LINES_K);
     const int n_wl = (R + 7) >> 3;  // loads of a stage and matrix
     unsigned char *xbuf = lds + wave * p.wave_bytes, *wbuf = xbuf + MT * 2048;
@@ -583,9 +567,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int f = 0; f < NF; ++f)
 #pragma unroll
             for (int i = 0; i < 2 * NR; ++i)
-                if (i < n_wl) load_lds16(wbase[f] + (size_t)st * 128 + woff[i], wbuf + f * (NR * 2048) + 1024 * i);
+                if (i < n_wl) fc_load_lds16(wbase[f] + (size_t)st * 128 + woff[i], wbuf + f * (NR * 2048) + 1024 * i);
 #pragma unroll
-        for (int i = 0; i < 2 * MT; ++i) load_lds16(xbase + (size_t)st * 128 + xoff[i], xbuf + 1024 * i);
+        for (int i = 0; i < 2 * MT; ++i) fc_load_lds16(xbase + (size_t)st * 128 + xoff[i], xbuf + 1024 * i);
     };
     auto task_row = [&](int j) { return 4 * ((wave + 8 * j) % (4 * MT)) + q; };
     auto task_col = [&](int j) { return 16 * ((wave + 8 * j) / (4 * MT)) + rho; };
@@ -608,7 +592,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) acc[t][f][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int st = 0; st < n_stages; ++st) {
-        wait_vm<0>();
+        fc_wait_vm<0>();
         __builtin_amdgcn_sched_barrier(0);
         bf16x8 xf[2][MT], wf[2][NR][NF];
 #pragma unroll
@@ -620,7 +604,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
                 for (int f = 0; f < NF; ++f) wf[s][t][f] = frag(wbuf + f * (NR * 2048), min(16 * t + rho, R - 1), s);
         }
-        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the areas may be overwritten
+        fc_wait_lds();  // lgkmcnt(0): the areas may be overwritten
         __builtin_amdgcn_sched_barrier(0);
         if (st + 1 < n_stages) issue(st + 1);
         __builtin_amdgcn_sched_barrier(0);
@@ -680,8 +664,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
 }
 
-uint32_t reciprocal(int d) { return (uint32_t)((((int64_t)1 << 32) + d - 1) / d); }
-
 template <int MT, int NR, int MODE>
 hipError_t launch_lines(LinArgs a, int runs, hipStream_t s)
 {
@@ -689,7 +671,7 @@ hipError_t launch_lines(LinArgs a, int runs, hipStream_t s)
     const int ring = MT * 2048 + NF * NR * 2048, state = NR * NF * MT * 1280;
     a.wave_bytes = ring > state ? ring : state;
     if ((a.N + runs - 1) / runs > 16 * NR || a.wave_bytes > 20 * 1024) return hipErrorInvalidValue;
-    a.div_grid = reciprocal(runs);
+    a.div_grid = fc_reciprocal(runs);
     static hipError_t attr = hipFuncSetAttribute((const void *)k_linear_lines<MT, NR, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return attr;
     k_linear_lines<MT, NR, MODE><<<dim3((unsigned)runs, (unsigned)((a.M + 16 * MT - 1) / (16 * MT))), dim3(512), 8 * a.wave_bytes, s>>>(a);

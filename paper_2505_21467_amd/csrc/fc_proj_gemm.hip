@@ -69,27 +69,14 @@ struct GemmArgs {
 };
 
 
-__device__ __forceinline__ void load_lds16g(const void *g, void *l)
-{
-    __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)g,
-                                     (void __attribute__((address_space(3))) *)l, 16, 0, 0);
-}
-
-// wait until at most N vector-memory operations of this wave are outstanding; LGKM0: and no LDS one
-template <int N, bool LGKM0 = false>
-__device__ __forceinline__ void wait_vmg()
-{
-    // gfx9 s_waitcnt immediate: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] at [15:14]
-    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | ((LGKM0 ? 0 : 15) << 8) | ((N >> 4) << 14));
-}
-// the same with N = k * PER for a run-time k in 0..3
+// fc_wait_vm with N = k * PER for a run-time k in 0..3
 template <int PER, bool LGKM0>
 __device__ __forceinline__ void wait_stages(int k)
 {
-    if (k >= 3) wait_vmg<3 * PER, LGKM0>();
-    else if (k == 2) wait_vmg<2 * PER, LGKM0>();
-    else if (k == 1) wait_vmg<PER, LGKM0>();
-    else wait_vmg<0, LGKM0>();
+    if (k >= 3) fc_wait_vm<3 * PER, LGKM0>();
+    else if (k == 2) fc_wait_vm<2 * PER, LGKM0>();
+    else if (k == 1) fc_wait_vm<PER, LGKM0>();
+    else fc_wait_vm<0, LGKM0>();
 }
 
 // silu(g) * u in fp32, in front of the rounding to bf16, with the hardware's exponential and reciprocal (gates below
@@ -134,7 +121,7 @@ __device__ __forceinline__ void load_bias(const GemmArgs &p, unsigned char *dst,
         else
             *(uint32_t *)(dst + d * 4) = (uint32_t)src[0] | ((uint32_t)src[1] << 16);
     }
-    wait_vmg<63, true>();  // LDS writes done, if any
+    fc_wait_lds();  // LDS writes done, if any
 }
 
 // Epilogue of a wave.  Lane (col, hi) of sub-tile i holds window row m_first + 32 i + col; register r of
@@ -203,7 +190,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x16 (&acc)[M
                         make_float4(acc[i][t][4 * rq], acc[i][t][4 * rq + 1], acc[i][t][4 * rq + 2], acc[i][t][4 * rq + 3]);
             }
         __builtin_amdgcn_wave_barrier();
-        wait_vmg<63, true>();
+        fc_wait_lds();
         // ---- and back as rows, eight low and eight high values per lane and step
         const int per_row = DEALT ? 2 * nt : NT * 2;  // pieces of eight pairs per row
 #pragma unroll 1
@@ -298,7 +285,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x16 (&acc)[M
             }
         }
         __builtin_amdgcn_wave_barrier();
-        wait_vmg<63, true>();
+        fc_wait_lds();
     }
 }
 
@@ -491,7 +478,7 @@ __global__ __launch_bounds__((NW + NL) * 64) void k_proj_gemm(GemmArgs p)
                 mat = up ? p.W2 : p.W;
             }
             const unsigned char *src = (const unsigned char *)mat + (size_t)at * ROWB;
-            load_lds16g(src + goff[i], dst + (lw + NLW * i) * 1024);
+            fc_load_lds16(src + goff[i], dst + (lw + NLW * i) * 1024);
         }
     };
 
@@ -568,7 +555,7 @@ __global__ __launch_bounds__((NW + NL) * 64) void k_proj_gemm(GemmArgs p)
             }
             const int nslot = slot == SLOTS - 1 ? 0 : slot + 1;
             if (it + 1 < n_stages) {
-                wait_vmg<63, true>();  // lgkmcnt(0): the reads of stage `it` have returned
+                fc_wait_lds();  // lgkmcnt(0): the reads of stage `it` have returned
                 __builtin_amdgcn_s_barrier();
                 read_frags(nslot, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
@@ -657,14 +644,14 @@ __device__ __forceinline__ void gemm_pp_loop(int n_stages, Issue issue, Read rea
 {
     constexpr int AHEAD = 2 * (GRP == 0 ? 5 : 6);
     auto end_m = [&]() {  // end of a memory interval
-        wait_vmg<GRP == 1 ? AHEAD : 63, true>();
+        fc_wait_vm<GRP == 1 ? AHEAD : 63, true>();
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
     };
     auto compute = [&](int i, int tp) {
         mul(i, tp);
         __builtin_amdgcn_sched_barrier(0);
-        if (GRP == 0) wait_vmg<AHEAD>();
+        if (GRP == 0) fc_wait_vm<AHEAD>();
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -673,12 +660,12 @@ __device__ __forceinline__ void gemm_pp_loop(int n_stages, Issue issue, Read rea
     for (int part = 0; part < 4; ++part) issue(0, part);
 #pragma unroll
     for (int part = 0; part < (GRP == 0 ? 3 : 4); ++part) issue(1, part);
-    wait_vmg<AHEAD>();  // X0 and W01 of stage 0
+    fc_wait_vm<AHEAD>();  // X0 and W01 of stage 0
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     read(0, 0);
     if (GRP == 1) {
-        wait_vmg<63, true>();
+        fc_wait_lds();
         __builtin_amdgcn_s_barrier();  // one interval behind
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -705,7 +692,7 @@ __device__ __forceinline__ void gemm_pp_loop(int n_stages, Issue issue, Read rea
         compute(1, 1);
     }
     if (GRP == 0) __builtin_amdgcn_s_barrier();
-    wait_vmg<0>();  // no load may still arrive in LDS when the epilogue uses it
+    fc_wait_vm<0>();  // no load may still arrive in LDS when the epilogue uses it
     __builtin_amdgcn_s_barrier();
 }
 
@@ -753,7 +740,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const unsigned char *src = (const unsigned char *)mat + (size_t)min(st, n_stages - 1) * 128;
         unsigned char *dst = smem + (st & 1) * STAGE + part * PART + wave * 2048;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) load_lds16g(src + goff[part][i], dst + i * 1024);
+        for (int i = 0; i < 2; ++i) fc_load_lds16(src + goff[part][i], dst + i * 1024);
     };
 
     // bias, behind everything else

@@ -194,12 +194,6 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
 // (252 workgroups, one per compute unit) 9.2 us for 33 MB.
 constexpr int HS_K = 512;  // hidden elements per workgroup
 
-__device__ __forceinline__ void load_lds16p(const void *g, void *l)
-{
-    __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)g,
-                                     (void __attribute__((address_space(3))) *)l, 16, 0, 0);
-}
-
 template <int MT>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_proj_headsplit(ProjArgs p)
 {
@@ -218,7 +212,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
         const int m = wave * 2 * MT + i;
         const int mg = min(m, p.M - 1);
         const int c = lane ^ (m & 15);
-        load_lds16p(p.X + (size_t)mg * p.K + (size_t)ks * HS_K + c * 8, xs + m * 1024);
+        fc_load_lds16(p.X + (size_t)mg * p.K + (size_t)ks * HS_K + c * 8, xs + m * 1024);
     }
     // W fragments of this wave's 16 rows: all 16 k-steps in flight
     const uint16_t *wrow = p.W + (size_t)n * p.K + (size_t)ks * HS_K + 8 * q;
@@ -366,14 +360,6 @@ __global__ __launch_bounds__(64) void k_proj_finish(ProjArgs p)
 // Against the kernel it replaced (X kept in operand registers, at most 32 rows) and the head-split kernels, us: 36 head slots,
 // hidden 3584, 4 / 16 / 32 rows 9.4 / 9.6 / 11.1 -> 8.3 / 8.6 / 9.8, 48 / 64 / 96 / 128 rows 13.6 / 15.0 / 17.4 / 19.2 -> 11.8 / 12.5 / 14.2 /
 // 16.1; 96 slots, hidden 4096, 32 rows 23.3 -> 21.1; 24 slots, hidden 2048, 32 / 64 / 128 rows 9.5 / 11.8 / 10.5 -> 5.5 / 6.2 / 7.6.
-template <int N>
-__device__ __forceinline__ void wait_vm()
-{
-    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
-// x / d, d given as 2^32 / d rounded up (0: d is 1); exact for x d < 2^32
-__device__ __forceinline__ uint32_t quotient(uint32_t x, uint32_t reciprocal) { return reciprocal ? __umulhi(x, reciprocal) : x; }
-uint32_t reciprocal(int d) { return (uint32_t)((((int64_t)1 << 32) + d - 1) / d); }
 
 constexpr int STREAM_K = 64;  // hidden elements per stage: one 128-byte line of every row
 template <int MT, int NP>
@@ -388,8 +374,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // weights from HBM once.  (Taken from one index by division this cost 0.25 us.)
     const int run = blockIdx.x, m0 = 16 * MT * blockIdx.y;
     const uint32_t n_pairs = (uint32_t)p.n_tiles * 8;
-    const int g0 = (int)quotient(run * n_pairs, p.div_runs);
-    const int R = (int)quotient((run + 1) * n_pairs, p.div_runs) - g0;  // pairs of this workgroup
+    const int g0 = (int)fc_quotient(run * n_pairs, p.div_runs);
+    const int R = (int)fc_quotient((run + 1) * n_pairs, p.div_runs) - g0;  // pairs of this workgroup
     const int n_stages = p.K / (8 * STREAM_K);
     const int n_wl = (2 * R + 7) >> 3;  // weight loads of a stage
     unsigned char *xbuf = lds + wave * p.wave_bytes, *wbuf = xbuf + MT * 2048;
@@ -416,9 +402,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         if (st >= n_stages) st -= n_stages;
 #pragma unroll
         for (int i = 0; i < 4 * NP; ++i)
-            if (i < n_wl) load_lds16p(wbase + (size_t)st * 128 + woff[i], wbuf + 1024 * i);
+            if (i < n_wl) fc_load_lds16(wbase + (size_t)st * 128 + woff[i], wbuf + 1024 * i);
 #pragma unroll
-        for (int i = 0; i < 2 * MT; ++i) load_lds16p(xbase + (size_t)st * 128 + xoff[i], xbuf + 1024 * i);
+        for (int i = 0; i < 2 * MT; ++i) fc_load_lds16(xbase + (size_t)st * 128 + xoff[i], xbuf + 1024 * i);
     };
     // The epilogue goes by tasks of 16 pairs in four window rows, lane = (row, pair), dealt to the waves.  Positions and
     // bias are asked for first; the first task's angle comes while the last stage is on its way.
@@ -430,7 +416,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int j = 0; j < TASKS; ++j) {
         const int mm = min(m0 + task_row(j), p.M - 1), gp = g0 + min(task_pair(j), R - 1);
-        pp[j] = p.pos ? p.pos[mm] : p.win_start + mm - (int)quotient(mm, p.div_a) * p.A;
+        pp[j] = p.pos ? p.pos[mm] : p.win_start + mm - (int)fc_quotient(mm, p.div_a) * p.A;
         bs[j][0] = bs[j][1] = 0;
         if (p.bias) {
             bs[j][0] = p.bias[(gp >> 6) * 128 + (gp & 63)];
@@ -463,7 +449,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             for (int mt = 0; mt < MT; ++mt) acc[t][f][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int st = 0; st < n_stages; ++st) {
         if (st == n_stages - 1) first_angle = angle(0);
-        wait_vm<0>();
+        fc_wait_vm<0>();
         __builtin_amdgcn_sched_barrier(0);
         bf16x8 xf[2][MT], wf[2][NP][2];
         auto read = [&](int s) {
@@ -487,7 +473,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         };
         read(0);
         read(1);
-        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the areas may be overwritten
+        fc_wait_lds();  // lgkmcnt(0): the areas may be overwritten
         __builtin_amdgcn_sched_barrier(0);
         if (st + 1 < n_stages) issue(st + 1);
         __builtin_amdgcn_sched_barrier(0);
@@ -524,7 +510,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             y0 = r0;
             y1 = r1;
         }
-        const int b = (int)quotient(m, p.div_a), a = m - b * p.A;
+        const int b = (int)fc_quotient(m, p.div_a), a = m - b * p.A;
         const bool valid = pp[j] >= 0 && pp[j] < G.max_seq;
         const uint16_t o0 = fc_bf16_bits(y0), o1 = fc_bf16_bits(y1);
         if (hs < G.Hq) {
@@ -549,8 +535,8 @@ hipError_t launch_stream(ProjArgs a, int runs, hipStream_t s)
     const int state = NP * 2 * MT * 1280;
     a.wave_bytes = ring > state ? ring : state;
     if (run > 16 * NP || runs % 8 || a.wave_bytes > 20 * 1024) return hipErrorInvalidValue;
-    a.div_runs = reciprocal(runs);
-    a.div_a = reciprocal(a.A);
+    a.div_runs = fc_reciprocal(runs);
+    a.div_a = fc_reciprocal(a.A);
     static hipError_t attr = hipFuncSetAttribute((const void *)k_proj_stream<MT, NP>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return attr;
     k_proj_stream<MT, NP><<<dim3((unsigned)runs, (unsigned)((a.M + 16 * MT - 1) / (16 * MT))), dim3(512), 8 * a.wave_bytes, s>>>(a);
