@@ -1034,14 +1034,16 @@ hipError_t launch_tile_t(const TileArgs &a, int n_tiles, hipStream_t s)
                 return launch_tile_u<T, 2, 4, 2, EPI, true>(a, n_tiles, s);
         return a.M > 16 && two < one ? launch_tile_u<T, NT, 2, 2, EPI, true>(a, n_tiles, s) : launch_tile_u<T, NT, 1, 2, EPI, true>(a, n_tiles, s);
     }
-    const bool deep = NT == 1 && (a.K + 4 * Op<T>::KB - 1) / (4 * Op<T>::KB) >= 8 * TW;
+    const bool deep = (a.K + 4 * Op<T>::KB - 1) / (4 * Op<T>::KB) >= 8 * TW;
     if (a.M > 32 && wgs(2) >= 4096) return launch_tile_u<T, 2, 4, 2, EPI, false>(a, n_tiles, s);
     if (a.M > 16 && wgs(2) >= 256) {
-        if constexpr (sizeof(T) == 4)
+        if constexpr (sizeof(T) == 4 && NT == 1)
             if (deep && wgs(2) <= 512) return launch_tile_u<T, NT, 2, 4, EPI, false>(a, n_tiles, s);
         return launch_tile_u<T, NT, 2, 2, EPI, false>(a, n_tiles, s);
     }
-    return deep && wgs(1) <= 512 ? launch_tile_u<T, NT, 1, 4, EPI, false>(a, n_tiles, s) : launch_tile_u<T, NT, 1, 2, EPI, false>(a, n_tiles, s);
+    if constexpr (NT == 1)
+        if (deep && wgs(1) <= 512) return launch_tile_u<T, NT, 1, 4, EPI, false>(a, n_tiles, s);
+    return launch_tile_u<T, NT, 1, 2, EPI, false>(a, n_tiles, s);
 }
 
 template <int EPI>
@@ -1060,7 +1062,8 @@ hipError_t launch_attn_tile(const AttnTileArgs &a, hipStream_t s)
     const int64_t bt = (int64_t)a.G.B * a.G.Hkv * a.tiles;
     if (bt * a.splits > (1 << 30) || bt * (QT * DH / 64) > (1 << 30)) return hipErrorInvalidValue;
     k_attn_tile<T, DH, QT, DS, LDS><<<dim3((unsigned)((bt * a.splits * DS + 7) / 8 * 8)), dim3(TW * 64), BYTES, s>>>(a);
-    if (a.splits > 1) k_attn_tile_merge<T, DH, QT><<<dim3((unsigned)(bt * (QT * DH / 64))), dim3(256), 0, s>>>(a);
+    if constexpr (!LDS && (Op<T>::KB != 8 || DH != 128))  // (the others are never cut)
+        if (a.splits > 1) k_attn_tile_merge<T, DH, QT><<<dim3((unsigned)(bt * (QT * DH / 64))), dim3(256), 0, s>>>(a);
     return hipGetLastError();
 }
 

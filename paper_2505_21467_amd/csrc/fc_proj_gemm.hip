@@ -873,9 +873,10 @@ hipError_t launch_shape(int shape, const GemmArgs &a, hipStream_t s)
     case 0: return launch_gemm<64, 8, 4, 1, 1, 3, 0, EPI>(a, s);
     case 1: return launch_gemm<64, 4, 4, 1, 1, 4, 4, EPI>(a, s);
     case 2:
-        if constexpr (EPI == 4) return hipErrorInvalidValue;
-        else if (EPI == 0 && a.K % 128 == 0) return launch_gemm<128, 4, 2, 1, 1, 3, 4, EPI>(a, s);
-        else return launch_gemm<64, 4, 2, 1, 1, 4, 4, EPI>(a, s);
+        if constexpr (EPI == 0)
+            if (a.K % 128 == 0) return launch_gemm<128, 4, 2, 1, 1, 3, 4, EPI>(a, s);
+        if constexpr (EPI != 4) return launch_gemm<64, 4, 2, 1, 1, 4, 4, EPI>(a, s);
+        return hipErrorInvalidValue;
     case 3:
         if constexpr (EPI == 3) return hipErrorInvalidValue;
         else return launch_gemm_pp<EPI>(a, s);
