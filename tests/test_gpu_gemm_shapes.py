@@ -48,7 +48,7 @@ def test_two_slab_tile_vocabulary(knob):
     _check_lm_head("bf16", x, w, "vocabulary, shape 3")
 
 
-@pytest.mark.parametrize("shape", [6, 7, 8, 9, 10])
+@pytest.mark.parametrize("shape", [5, 6, 7, 8, 9, 10])
 @pytest.mark.parametrize("M,K,N", [(5, 256, 256), (64, 320, 384), (65, 256, 1152), (130, 448, 640)])
 def test_few_row_tiles(shape, M, K, N, knob):
     """64 or 128 rows per tile: ragged rows, one tile and several, dealt pairs that end inside a tile."""
@@ -85,6 +85,8 @@ def test_start_along_the_hidden_dimension(shape, M, K, N, knob):
     _linear(M, K, N, True, "gated, shape %d" % shape)
     if shape < 5 or shape >= 9:
         _linear(M, K, N, False, "linear, shape %d" % shape)
+        knob("FC_LIN_KSPLIT", "1")  # (so few outputs are cut along the hidden dimension otherwise)
+        _linear(M, K, N, False, "linear in one part, shape %d" % shape)
     if shape in (1, 9):
         x, w = inputs.normal(24, "x", (M, K), 1.0, "bf16"), inputs.normal(24, "w", (N, K), 0.01, "bf16")
         _check_lm_head("bf16", x, w, "vocabulary, shape %d" % shape)
@@ -110,7 +112,7 @@ def test_few_rows_vocabulary_on_both_sides_of_the_line(V):
     _check_lm_head("bf16", x, w, "vocabulary of %d" % V)
 
 
-@pytest.mark.parametrize("shape", [6, 7, 8, 9, 10])
+@pytest.mark.parametrize("shape", [1, 2, 5, 6, 7, 8, 9, 10])
 @pytest.mark.parametrize("B,d,Hq,Hkv,A", [(3, 192, 8, 2, 23), (1, 64, 3, 1, 65), (2, 320, 4, 4, 160), (1, 2048, 4, 2, 63)])
 def test_few_row_tiles_projection(shape, B, d, Hq, Hkv, A, knob):
     print("[case] projection, shape", shape, B, d, Hq, Hkv, A, flush=True)
@@ -165,6 +167,8 @@ def test_problem_cut_into_two_launches(M, N, gated):
     (130, 2048, 4096, False), (65, 1536, 4100, False),   # three tiles, runs of 51 and 52; two tiles, runs of 32 and 33
     (97, 1536, 2050, True), (128, 1536, 4096, True),     # pairs in runs of 25 and 26, and of 32
     (7, 3584, 8200, False),                            # one output quad too many: whole-row kernel
+    (33, 512, 2753, False), (34, 512, 4225, False),    # tiles of 48 rows, one and two weight tiles
+    (36, 512, 2243, True), (148, 1024, 1153, True),    # gated: tiles of 48 and of 64 rows, runs of up to 16
 ])
 def test_layers_of_few_outputs(M, K, N, gated):
     """Ends of the runs, of the tiles of window rows and of the covered range."""
@@ -179,7 +183,7 @@ def test_layers_of_few_outputs(M, K, N, gated):
 
 
 @pytest.mark.parametrize("M,K,V", [
-    (1, 512, 2), (17, 3584, 33), (32, 512, 4097), (9, 1536, 8193), (32, 512, 16385), (31, 3584, 4095), (5, 4096, 300), (2, 512, 16384),
+    (1, 512, 2), (15, 2560, 1721), (17, 3584, 33), (32, 512, 4097), (9, 1536, 8193), (32, 512, 16385), (31, 3584, 4095), (5, 4096, 300), (2, 512, 16384),
 ])
 def test_small_vocabulary(M, K, V):
     """Runs of one to 64 entries, one to four weight tiles, fewer entries than parts; 16385: one too many, whole-row kernel."""

@@ -24,7 +24,7 @@ def _ws(nbytes):
 
 @pytest.mark.parametrize("dtype,rows,hidden", [
     ("f32", 5, 200), ("bf16", 5, 200), ("bf16", 32, 3584), ("bf16", 3, 8), ("bf16", 4, 2048), ("bf16", 3, 4096),
-    ("bf16", 2, 8192), ("bf16", 2, 8200), ("bf16", 3, 100),
+    ("bf16", 2, 8192), ("bf16", 2, 8200), ("bf16", 3, 100), ("f32", 3, 1028), ("f32", 2, 4096), ("f32", 2, 4100), ("f32", 3, 1999),
 ])
 def test_rmsnorm_matches_oracle(dtype, rows, hidden):
     x = inputs.normal(1, "x", (rows, hidden), 1.5, dtype)
@@ -50,8 +50,9 @@ LINEAR_SHAPES = [
     ("bf16", 32, 4608, 1536, True),    # long rows: many slices per slab, runs that straddle slabs
     ("bf16", 40, 1024, 384, True),     # two passes of up to 32 rows, ragged second pass
     ("bf16", 17, 512, 408, True),      # whole-row kernel: 51 half items of 8 rows (the last item is half), ragged rows
-    ("bf16", 32, 4096, 4096 + 24, False),  # whole-row kernel at hidden 4096, more items than workgroups, odd half item
-    ("bf16", 3, 3584, 16 * 300, True),  # whole-row kernel, one 16-row tile of X, uneven runs (300 items over 256 workgroups)
+    ("bf16", 32, 4096, 4096 + 24, False),  # streamed through LDS at hidden 4096, ragged runs
+    ("bf16", 3, 3584, 16 * 300, True),  # the same with one 16-row tile of X
+    ("bf16", 15, 9216, 512, True),     # slice-wise kernel: one 16-row tile, 18 slices
 ]
 
 
@@ -95,7 +96,8 @@ def test_linear_residual_any_number_of_workgroups(wgs, knob):
     ("f32", 6, 40, 70), ("bf16", 5, 136, 72), ("bf16", 32, 1024, 320), ("bf16", 16, 512, 64),
     ("bf16", 32, 3584, 2368), ("bf16", 50, 1024, 192),
     ("bf16", 9, 512, 100),        # whole-row kernel: 25 half items of 4 features
-    ("bf16", 32, 4096, 2052),     # whole-row kernel at hidden 4096, 513 half items over 256 workgroups
+    ("bf16", 32, 4096, 2052),     # streamed through LDS at hidden 4096
+    ("bf16", 15, 1024, 10304), ("bf16", 19, 1024, 8640),  # slice-wise kernel, one and two 16-row tiles
     ("bf16", 64, 1024, 12800),    # tiled GEMM, 200 slabs and at most 128 rows: 128-row tiles of half slabs
 ])
 def test_ffn_gate_up_matches_oracle(dtype, M, K, F):

@@ -1,6 +1,6 @@
 """GPU parity of the projection kernels at the edges of their ranges, with bias and with padded and out-of-range
-positions: whole rows up to 32 window rows (runs of less than an item, of one and of several), head-split at 33 .. 128
-(each number of 16-row tiles, ragged last tiles), and the sizes where the tiled GEMM takes over."""
+positions: runs of pairs streamed through LDS (one and two pair tiles, each number of 16-row tiles, ragged last tiles), head-split
+beyond hidden 8192 at 33 .. 128 rows, and the sizes where the tiled GEMM and the tile kernel take over."""
 import numpy as np
 import pytest
 import torch
@@ -14,11 +14,15 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("B,d,Hq,Hkv,A", [
     (1, 3584, 4, 1, 33), (1, 3584, 2, 1, 48), (3, 3584, 4, 2, 19), (1, 4096, 3, 1, 65), (4, 3584, 2, 2, 24),
-    (2, 4096, 2, 1, 50), (1, 3584, 2, 1, 127), (1, 3584, 2, 1, 128),  # head-split, three to eight tiles
-    (1, 3584, 2, 1, 129), (1, 768, 4, 2, 33), (1, 1024, 2, 1, 20),    # tiled GEMM: more rows; few rows of a small matrix
-    (1, 512, 4, 2, 5), (2, 512, 30, 5, 16), (1, 512, 60, 4, 17),       # whole rows, hidden 512: one item or two per run
-    (1, 3584, 28, 4, 32), (2, 3584, 30, 5, 8), (1, 3584, 3, 1, 9),     # hidden 3584: 9 or 10 pairs in one item; 8 pairs
-    (1, 4096, 33, 3, 18), (3, 4096, 1, 1, 5),                          # hidden 4096: 9 or 10 pairs in two items; few
+    (2, 4096, 2, 1, 50), (1, 3584, 2, 1, 127), (1, 3584, 2, 1, 128),  # streamed, two to eight tiles of rows
+    (1, 3584, 2, 1, 129), (1, 768, 4, 2, 33), (1, 1024, 2, 1, 20),    # more rows; few rows of a small matrix (tile kernel)
+    (1, 512, 4, 2, 5), (2, 512, 30, 5, 16), (1, 512, 60, 4, 17),       # hidden 512: runs of few pairs
+    (1, 3584, 28, 4, 32), (2, 3584, 30, 5, 8), (1, 3584, 3, 1, 9),     # hidden 3584: runs of 9 or 10 pairs; of few
+    (1, 4096, 33, 3, 18), (3, 4096, 1, 1, 5),                          # hidden 4096: runs of 9 or 10 pairs; of few
+    (1, 512, 56, 8, 9), (1, 512, 28, 4, 34), (3, 512, 16, 8, 34), (4, 512, 16, 16, 29),  # 16 rows x two pair tiles; 48 rows; 64 rows x one, two
+    (1, 10240, 1, 1, 45), (3, 10240, 1, 1, 17), (1, 11264, 1, 1, 74), (1, 10240, 1, 1, 94), (1, 10240, 7, 1, 112),
+    (1, 12288, 8, 1, 123),                                             # head-split, three to eight tiles
+    (3, 2048, 56, 8, 22), (2, 2048, 112, 16, 35), (1, 1024, 128, 16, 3), (4, 64, 64, 16, 82),  # tiled GEMM: half heads, 48 pairs, 64 rows; 80 pairs
 ])
 def test_projection_rows(B, d, Hq, Hkv, A):
     print("[case] projection rows", B, d, Hq, Hkv, A, flush=True)

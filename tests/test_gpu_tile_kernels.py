@@ -8,6 +8,7 @@ from oracle import fc_oracle as orc
 from paper_2505_21467_amd import binding as fc
 from paper_2505_21467_amd import inputs
 from tests.harness import GpuLayerCache, OracleLayerCache, assert_close
+from tests.test_gpu_unmask import _check_lm_head
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -83,6 +84,28 @@ def test_attention_over_all_keys_by_way_of_lds(dtype, Dh, B, Hq, Hkv, A, S):
     g.close()
 
 
+@pytest.mark.parametrize("dtype,Dh,B,Hq,Hkv,A,S,wgs", [
+    ("f32", 64, 4, 8, 8, 5, 1130, (129, 256)), ("f32", 64, 3, 8, 8, 3, 805, (65, 128)),
+    ("f32", 128, 4, 8, 8, 3, 405, (129, 256)), ("f32", 128, 8, 2, 2, 7, 437, (65, 128)),
+    ("bf16", 64, 8, 3, 3, 2, 2747, (129, 256)), ("bf16", 64, 3, 4, 4, 9, 2779, (65, 128)),
+])
+def test_key_ranges_in_many_workgroups(dtype, Dh, B, Hq, Hkv, A, S, wgs):
+    """Ranges in so many workgroups that the head dimension of V is uncut, or cut in two; the last group of keys ragged."""
+    print("[case] ranges", dtype, Dh, B, Hq, Hkv, A, S, flush=True)
+    w = inputs.Workload("t", dtype, B, 256, Hq, Hkv, Dh, S, A)
+    g = GpuLayerCache(dtype, B, 256, Hq, Hkv, Dh, S + 5, max_rows=A, fill=float("nan"))  # keys past kv_len are not numbers
+    o = OracleLayerCache(dtype, B, 256, Hq, Hkv, Dh, S + 5)
+    p = fc.fc_attention_plan(g.cfg, A, S)
+    assert p["splits"] > 1 and wgs[0] <= B * Hkv * p["row_tiles"] * p["splits"] <= wgs[1], p
+    K, V = inputs.kv_fill(w, 6, S)
+    g.write_rows(0, K, V, 0)
+    o.write_rows(K, V, 0)
+    Q = inputs.normal(6, "q", (B, Hq, A, Dh), 1.0, dtype)
+    O = g.attend(0, g.dev_t(Q), S)
+    assert_close(inputs.as_oracle(O), orc.attend(o.cfg, inputs.as_oracle(Q), o.Kc, o.Vc, S, None), dtype, "ranges")
+    g.close()
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,A,S", [(1, 4, 4, 32, 288), (1, 8, 2, 5, 2000), (4, 8, 8, 33, 64)])
 def test_bf16_rows_of_64_keep_fp32_probabilities(B, Hq, Hkv, A, S):
     """With fp32 probabilities a result differs from the rounded exact one only where that lies within the error of the
@@ -104,6 +127,8 @@ def test_bf16_rows_of_64_keep_fp32_probabilities(B, Hq, Hkv, A, S):
 
 @pytest.mark.parametrize("dtype,M,K,N", [
     ("f32", 1, 8, 1), ("f32", 33, 24, 15), ("f32", 300, 40, 1702), ("bf16", 17, 8, 33), ("bf16", 65, 40, 4100),
+    ("f32", 2, 1160, 5), ("f32", 289, 16, 229), ("f32", 268, 16, 128),      # a long chain of few workgroups; tiles of 32 rows
+    ("bf16", 156, 32, 1667), ("bf16", 40, 8, 33211), ("f32", 42, 8, 34297),  # 64 rows x two weight tiles
 ])
 def test_linear_layers_match_oracle(dtype, M, K, N):
     print("[case]", dtype, M, K, N, flush=True)
@@ -136,8 +161,21 @@ def test_linear_layers_with_long_chains(dtype, M, K, N):
     assert_close(inputs.as_oracle(out), orc.ffn_gate_up(xo, wo, w2o, dtype), dtype, "gate_up")
 
 
+@pytest.mark.parametrize("dtype,M,K,V", [
+    ("bf16", 2, 32, 2), ("bf16", 3, 2304, 2307), ("bf16", 319, 32, 405), ("bf16", 98, 32, 3585),  # by way of LDS: 16, 32 and 64 rows
+    ("bf16", 34, 8, 4263), ("bf16", 289, 8, 13697),                                               # straight into registers
+    ("f32", 4, 16, 33), ("f32", 311, 16, 391), ("f32", 174, 8, 1409), ("f32", 39, 8, 70145),
+])
+def test_vocabularies(dtype, M, K, V):
+    """Two weight tiles per workgroup and part, the last one ragged, over the tiles of window rows."""
+    print("[case] vocabulary", dtype, M, K, V, flush=True)
+    x, w = inputs.normal(27, "x", (M, K), 1.0, dtype), inputs.normal(27, "w", (V, K), 0.05, dtype)
+    _check_lm_head(dtype, x, w, "vocabulary")
+
+
 @pytest.mark.parametrize("dtype,B,d,Hq,Hkv,Dh,L,A", [
     ("bf16", 1, 2056, 62, 1, 64, 10, 20), ("f32", 1, 1032, 62, 1, 64, 10, 20), ("bf16", 1, 2056, 4, 2, 64, 10, 16),
+    ("f32", 1, 1032, 3, 1, 64, 10, 5), ("bf16", 3, 8, 64, 16, 64, 10, 109), ("f32", 1, 8, 16, 16, 128, 10, 323),  # 64 rows x two weight tiles
 ])
 def test_projection_with_long_chains(dtype, B, d, Hq, Hkv, Dh, L, A):
     test_step_matches_oracle(dtype, B, d, Hq, Hkv, Dh, L, A)

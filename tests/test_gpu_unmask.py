@@ -55,12 +55,13 @@ def _check_lm_head(dtype, x, w, what):
 @pytest.mark.parametrize("dtype,M,K,V", [
     ("f32", 5, 40, 300),          # plain kernel
     ("bf16", 6, 136, 1000),       # bf16 shape the streaming kernels do not cover (vocabulary not a multiple of 128)
-    ("bf16", 7, 512, 128),        # one slab, one item
+    ("bf16", 7, 512, 128),        # one slab
+    ("bf16", 7, 1024, 256),       # slice-wise kernel: two slabs, two items each
     ("bf16", 32, 1024, 2048),
     ("bf16", 40, 1024, 640),      # two passes of rows
     ("bf16", 32, 3584, 8192),     # the 7B hidden width, a slice of the vocabulary
-    ("bf16", 11, 512, 1000),      # whole-row kernel: 125 half items, running triple per workgroup
-    ("bf16", 32, 4096, 4344),     # whole-row kernel at hidden 4096: 543 half items over 256 workgroups
+    ("bf16", 11, 512, 1000),      # streamed through LDS: runs of four, a triple per workgroup
+    ("bf16", 32, 4096, 4344),     # the same at hidden 4096, ragged runs
 ])
 def test_lm_head_argmax_matches_oracle(dtype, M, K, V):
     x = inputs.normal(21, "x", (M, K), 1.0, dtype)
@@ -68,8 +69,12 @@ def test_lm_head_argmax_matches_oracle(dtype, M, K, V):
     _check_lm_head(dtype, x, w, "lm_head %s %dx%dx%d" % (dtype, M, K, V))
 
 
-def test_lm_head_whole_row_kernel_seeded_shape_sweep():
-    # hidden 512 (the whole-row kernel), 12 seeded shapes: 1..32 rows, vocabulary of 1..600 half items of 8
+@pytest.mark.parametrize("wgs", [None, "256"])
+def test_lm_head_whole_row_kernel_seeded_shape_sweep(wgs, knob):
+    # hidden 512 (streamed through LDS; the whole-row kernel where a number of workgroups is named), 12 seeded
+    # shapes: 1..32 rows, vocabulary of 1..600 half items of 8
+    if wgs:
+        knob("FC_LIN_WGS", wgs)
     rng = np.random.default_rng(20250528)
     for case in range(12):
         M, V = int(rng.integers(1, 33)), int(rng.integers(1, 601)) * 8
