@@ -116,8 +116,8 @@ __device__ __forceinline__ void store4(bf16_t *p, const float (&y)[4])
 // (U blocks at a time, the next U in flight behind the multiplies of these), and the partial tiles are summed
 // through LDS, tile t by wave t mod 8, which applies the epilogue.  The operands come by way of LDS (an area of its own per
 // wave, direct-to-LDS loads of 64 bytes per row): straight into registers, with neighbouring lanes in different rows, a
-// compute unit takes one lane a clock, 38 B/ns.  100 problems of 4 .. 160 rows, hidden 256 .. 2048 in fp32, 256 / 512 in bf16:
-// 0.83 of the time (fp32 32 x 1024 x 512 6.4 -> 4.5 us, gated 160 x 512 x 1024 11.7 -> 8.6, projection 32 x 512 x 1024 4.7 -> 4.1; the
+// compute unit takes one lane a clock, 38 B/ns.  108 problems of 4 .. 160 rows, hidden 256 .. 2048 in fp32, 256 / 512 in bf16:
+// 0.78 of the time (fp32 32 x 1024 x 512 6.4 -> 4.4 us, gated 160 x 512 x 1024 11.7 -> 8.6, projection 32 x 512 x 1024 4.7 -> 4.1; the
 // same bits).  Pointers off 16 bytes and rows that are no whole blocks still go straight into registers (bf16 4 x 2056 x 2056
 // 4.9 that way, 5.1 with pieces that straddle lines).
 // Plain-ALU kernels with one dot product per wave took 36 us for the tiny configuration's projection (32

@@ -149,7 +149,7 @@ struct FcSkinnyPlan {
     int maxseg;  // upper bound of the workgroups that meet one slab
     size_t reserve;  // kind 2: workspace asked of the caller and not used
 };
-// Layers of few outputs at up to 96 rows, one launch, no workspace: whether the kernel can, and the launch.
+// Layers of up to 8192 outputs and 256 rows, one launch, no workspace: whether the kernel can, and the launch.
 bool fc_linear_lines_cover(int dtype, int mode, int M, int K, int N);
 // The same for a small vocabulary: parts of the arg-max it writes, `parts` at most (0: not for it), and the launch.
 int fc_lmhead_lines_parts(int dtype, int M, int K, int V, int parts);
