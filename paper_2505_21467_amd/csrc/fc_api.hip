@@ -52,7 +52,16 @@ fc_status check_config(const fc_config *c)
 
 int spad_of(const fc_config &c) { return (c.max_seq + FC_VTILE - 1) / FC_VTILE * FC_VTILE; }
 
-FcGeom geom_of(const fc_cache *cache)
+// Bytes of a pass over all layers: projection weights, keys and values, and the layers' other weights (d_ff; 0: none of them).
+double pass_bytes(const fc_cache *cache, int32_t d_ff)
+{
+    const fc_config &c = cache->cfg;
+    const double d = c.hidden, e = (double)c.n_q_heads * c.head_dim, kv = (double)c.n_kv_heads * c.head_dim;
+    const double rest = d_ff > 0 ? d * e + 3.0 * d * d_ff : 0.0;
+    return c.n_layers * ((e + 2.0 * kv) * d + 2.0 * (double)cache->layer_elems + rest) * (double)cache->esize;
+}
+
+FcGeom geom_of(const fc_cache *cache, int32_t d_ff = 0)
 {
     const fc_config &c = cache->cfg;
     FcGeom G;
@@ -64,6 +73,7 @@ FcGeom geom_of(const fc_cache *cache)
     G.max_seq = c.max_seq;
     G.spad = cache->spad;
     G.g = c.n_q_heads / c.n_kv_heads;
+    G.once = fc_read_once(pass_bytes(cache, d_ff));
     G.scale = c.softmax_scale > 0.f ? c.softmax_scale : (float)(1.0 / sqrt((double)c.head_dim));
     G.log_base = log((double)c.rope_base);
     return G;
@@ -672,9 +682,9 @@ fc_status fc_window(int32_t step, int32_t P, int32_t G, int32_t Bk, int32_t step
     return FC_OK;
 }
 
-fc_status fc_qkv_project_scatter(fc_cache *cache, int32_t layer, const void *x, const void *w_qkv,
-                                 const void *b_qkv, int32_t win_start, int32_t A, const int32_t *pos,
-                                 void *q_out, void *stream)
+// d_ff: of the layer the call is a part of (0: projections and attention alone)
+static fc_status project_scatter(fc_cache *cache, int32_t layer, int32_t d_ff, const void *x, const void *w_qkv, const void *b_qkv,
+                                 int32_t win_start, int32_t A, const int32_t *pos, void *q_out, void *stream)
 {
     fc_status st = check_cache_layer(cache, layer);
     if (st != FC_OK) return st;
@@ -685,7 +695,7 @@ fc_status fc_qkv_project_scatter(fc_cache *cache, int32_t layer, const void *x, 
     if (!pos && (win_start < 0 || win_start > cache->cfg.max_seq - A))
         return fail(FC_ERR_BOUNDS, "window [%d, %d+%d) outside the cache of %d rows", win_start, win_start,
                     A, cache->cfg.max_seq);
-    const FcGeom G = geom_of(cache);
+    const FcGeom G = geom_of(cache, d_ff);
     void *kl = layer_ptr(cache, cache->k, layer), *vl = layer_ptr(cache, cache->v, layer);
     // wide windows: tiled GEMM; short windows: weight-streaming kernels; small problems, other shapes and fp32: tile kernel
     hipError_t e;
@@ -703,19 +713,26 @@ fc_status fc_qkv_project_scatter(fc_cache *cache, int32_t layer, const void *x, 
     return e == hipSuccess ? FC_OK : hip_fail(e, "projection launch");
 }
 
+fc_status fc_qkv_project_scatter(fc_cache *cache, int32_t layer, const void *x, const void *w_qkv,
+                                 const void *b_qkv, int32_t win_start, int32_t A, const int32_t *pos,
+                                 void *q_out, void *stream)
+{
+    return project_scatter(cache, layer, 0, x, w_qkv, b_qkv, win_start, A, pos, q_out, stream);
+}
+
 size_t fc_workspace_bytes(const fc_config *cfg, int32_t max_rows)
 {
     if (check_config(cfg) != FC_OK || max_rows < 1) return 0;
     return attn_workspace(*cfg, max_rows, true);
 }
 
-static fc_status run_attention(fc_cache *cache, int32_t layer, const FcAttnPlan &plan, const void *q, int32_t A,
+static fc_status run_attention(fc_cache *cache, int32_t layer, int32_t d_ff, const FcAttnPlan &plan, const void *q, int32_t A,
                                int32_t kv_len, const int32_t *pos, void *out, void *workspace, size_t space, void *stream)
 {
     const size_t bytes = fc_plan_workspace(cache->cfg, plan);
     if (bytes > space)  // (not reached: the planner keeps within the space, and the plan of a tuning knob is required space)
         return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", bytes, space);
-    const FcGeom G = geom_of(cache);
+    const FcGeom G = geom_of(cache, d_ff);
     void *kl = layer_ptr(cache, cache->k, layer), *vl = layer_ptr(cache, cache->v, layer);
     hipError_t e = plan.kind != 0
                        ? fc_launch_attention_mfma(G, plan, q, kl, vl, pos, A, kv_len, out, workspace,
@@ -725,9 +742,8 @@ static fc_status run_attention(fc_cache *cache, int32_t layer, const FcAttnPlan 
     return e == hipSuccess ? FC_OK : hip_fail(e, "attention launch");
 }
 
-fc_status fc_active_attention(fc_cache *cache, int32_t layer, const void *q, int32_t A, int32_t kv_len,
-                              const int32_t *pos, void *out, void *workspace, size_t workspace_bytes,
-                              void *stream)
+static fc_status active_attention(fc_cache *cache, int32_t layer, int32_t d_ff, const void *q, int32_t A, int32_t kv_len,
+                                  const int32_t *pos, void *out, void *workspace, size_t workspace_bytes, void *stream)
 {
     fc_status st = check_cache_layer(cache, layer);
     if (st != FC_OK) return st;
@@ -740,7 +756,14 @@ fc_status fc_active_attention(fc_cache *cache, int32_t layer, const void *q, int
     const size_t need = attn_required(cache->cfg, A, kv_len), given = workspace ? workspace_bytes : 0;
     if (given < need) return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, given);
     const FcAttnPlan plan = plan_with_workspace(cache->cfg, A, kv_len, given);
-    return run_attention(cache, layer, plan, q, A, kv_len, pos, out, workspace, given, stream);
+    return run_attention(cache, layer, d_ff, plan, q, A, kv_len, pos, out, workspace, given, stream);
+}
+
+fc_status fc_active_attention(fc_cache *cache, int32_t layer, const void *q, int32_t A, int32_t kv_len,
+                              const int32_t *pos, void *out, void *workspace, size_t workspace_bytes,
+                              void *stream)
+{
+    return active_attention(cache, layer, 0, q, A, kv_len, pos, out, workspace, workspace_bytes, stream);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -806,7 +829,7 @@ fc_status fc_active_attention_static(fc_cache *cache, int32_t layer, const void 
     }
     // Nothing in the scratch has to start at zero: every (row tile, split) slot the merge kernel
     // reads is written by the first kernel of the same call.
-    return run_attention(cache, layer, plan, q, A, kv_len, pos, out, scratch, FC_STATIC_SCRATCH_BYTES, stream);
+    return run_attention(cache, layer, 0, plan, q, A, kv_len, pos, out, scratch, FC_STATIC_SCRATCH_BYTES, stream);
 }
 
 fc_status fc_refresh(fc_cache *cache, int32_t layer, const void *x, const void *w_qkv, const void *b_qkv,
@@ -963,7 +986,7 @@ static bool linear_prefers_lines(int dtype, int mode, int M, int K, int N, const
 
 static fc_status linear_common(int32_t dtype, int mode, const void *x, const void *w, const void *w2,
                                const void *res, int32_t M, int32_t K, int32_t N, void *out, void *workspace,
-                               size_t workspace_bytes, void *stream)
+                               size_t workspace_bytes, bool once, void *stream)
 {
     fc_status st = check_dtype(dtype);
     if (st != FC_OK) return st;
@@ -982,9 +1005,9 @@ static fc_status linear_common(int32_t dtype, int mode, const void *x, const voi
     hipError_t e;
     const bool tile = linear_prefers_tile(dtype, mode, M, K, N, wide, plan);
     if (linear_prefers_lines(dtype, mode, M, K, N, wide, plan, tile))
-        e = fc_launch_linear_lines(mode, x, w, w2, res, M, K, N, out, (hipStream_t)stream);
+        e = fc_launch_linear_lines(mode, x, w, w2, res, M, K, N, out, once, (hipStream_t)stream);
     else if (wide.kind == 1 && !tile)
-        e = fc_launch_linear_wide(wide, mode, x, w, w2, res, M, K, N, out, workspace, (hipStream_t)stream);
+        e = fc_launch_linear_wide(wide, mode, x, w, w2, res, M, K, N, out, workspace, once, (hipStream_t)stream);
     else if (plan.kind >= 1 && !tile)
         e = fc_launch_linear_skinny(plan, mode, x, w, w2, res, M, K, N, out, workspace, (hipStream_t)stream);
     else
@@ -993,19 +1016,22 @@ static fc_status linear_common(int32_t dtype, int mode, const void *x, const voi
     return e == hipSuccess ? FC_OK : hip_fail(e, "linear launch");
 }
 
+// A layer called by itself: its matrix comes round again behind those of the other layers, of which there are at least a few.
+static bool layer_read_once(double K, double N) { return fc_read_once(4.0 * 2.0 * K * N); }
+
 fc_status fc_linear_residual(int32_t dtype, const void *x, const void *w, const void *residual, int32_t M,
                              int32_t K, int32_t N, void *out, void *workspace, size_t workspace_bytes,
                              void *stream)
 {
     return linear_common(dtype, FC_LIN_RESIDUAL, x, w, nullptr, residual, M, K, N, out, workspace,
-                         workspace_bytes, stream);
+                         workspace_bytes, layer_read_once(K, N), stream);
 }
 
 fc_status fc_ffn_gate_up(int32_t dtype, const void *x, const void *w_gate, const void *w_up, int32_t M,
                          int32_t K, int32_t F, void *out, void *workspace, size_t workspace_bytes, void *stream)
 {
     return linear_common(dtype, FC_LIN_GATE_UP, x, w_gate, w_up, nullptr, M, K, F, out, workspace,
-                         workspace_bytes, stream);
+                         workspace_bytes, layer_read_once(K, 2.0 * F), stream);
 }
 
 namespace {
@@ -1092,13 +1118,17 @@ fc_status fc_full_layer_step(fc_cache *cache, int32_t layer, const fc_layer_weig
     const size_t attn_bytes = workspace_bytes - w.attn;
     void *lin = w.lin_bytes ? ws + w.lin : nullptr, *attn = attn_bytes ? ws + w.attn : nullptr;
 
+    const bool once = fc_read_once(pass_bytes(cache, wt->d_ff));
     st = fc_rmsnorm(c.dtype, x, wt->norm1, wt->eps, M, d, h, stream);
-    if (st == FC_OK) st = fc_qkv_project_scatter(cache, layer, h, wt->w_qkv, wt->b_qkv, win_start, A, pos, q, stream);
-    if (st == FC_OK) st = fc_active_attention(cache, layer, q, A, kv_len, pos, o, attn, attn_bytes, stream);
-    if (st == FC_OK) st = fc_linear_residual(c.dtype, o, wt->w_out, x, M, E, d, x2, lin, w.lin_bytes, stream);
+    if (st == FC_OK) st = project_scatter(cache, layer, wt->d_ff, h, wt->w_qkv, wt->b_qkv, win_start, A, pos, q, stream);
+    if (st == FC_OK) st = active_attention(cache, layer, wt->d_ff, q, A, kv_len, pos, o, attn, attn_bytes, stream);
+    if (st == FC_OK)
+        st = linear_common(c.dtype, FC_LIN_RESIDUAL, o, wt->w_out, nullptr, x, M, E, d, x2, lin, w.lin_bytes, once, stream);
     if (st == FC_OK) st = fc_rmsnorm(c.dtype, x2, wt->norm2, wt->eps, M, d, h, stream);
-    if (st == FC_OK) st = fc_ffn_gate_up(c.dtype, h, wt->w_gate, wt->w_up, M, d, wt->d_ff, act, lin, w.lin_bytes, stream);
-    if (st == FC_OK) st = fc_linear_residual(c.dtype, act, wt->w_down, x2, M, wt->d_ff, d, y, lin, w.lin_bytes, stream);
+    if (st == FC_OK)
+        st = linear_common(c.dtype, FC_LIN_GATE_UP, h, wt->w_gate, wt->w_up, nullptr, M, d, wt->d_ff, act, lin, w.lin_bytes, once, stream);
+    if (st == FC_OK)
+        st = linear_common(c.dtype, FC_LIN_RESIDUAL, act, wt->w_down, nullptr, x2, M, wt->d_ff, d, y, lin, w.lin_bytes, once, stream);
     return st;
 }
 
@@ -1172,7 +1202,7 @@ fc_status fc_lm_head_argmax(int32_t dtype, const void *x, const void *w_vocab, i
         e = fc_launch_lmhead_lines(x, w_vocab, M, K, V, am, (hipStream_t)stream);
     } else if (w.wide.kind == 1)
         e = fc_launch_linear_wide(w.wide, FC_LIN_VOCAB, x, w_vocab, nullptr, nullptr, M, K, V, nullptr, nullptr,
-                                  (hipStream_t)stream, &am);
+                                  fc_read_once(2.0 * K * V), (hipStream_t)stream, &am);
     else if (w.plan.kind >= 1)
         e = fc_launch_linear_skinny(w.plan, FC_LIN_VOCAB, x, w_vocab, nullptr, nullptr, M, K, V, nullptr, ws + w.tiles,
                                     (hipStream_t)stream, &am);

@@ -66,6 +66,7 @@ struct AttnArgs {
     int row_tiles, n_rg, splits, keys_per_split, n_units;
     float c;              // softmax scale * log2(e)
     uint32_t div_pair, div_hkv, div_a;  // k_attn_groups: see launch_groups
+    bool once;            // k_attn_mfma: keys and values with the non-temporal hint
 };
 
 
@@ -250,8 +251,10 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     auto issue_stage = [&](int st) {
         const unsigned char *src = gsrc + (size_t)st * (STAGE_BYTES / 2);  // 64 keys * 256 B for K and for V
         unsigned char *dst = smem + (st % SLOTS) * STAGE_BYTES + lds_dst;
+        fc_with_hint(p.once, [&](auto once) {
 #pragma unroll
-        for (int i = 0; i < LB; ++i) fc_load_lds16(src + goff[i], dst + i * 1024);
+            for (int i = 0; i < LB; ++i) fc_load_lds16<decltype(once)::value>(src + goff[i], dst + i * 1024);
+        });
     };
 
     // ---- operand read offsets inside a stage (bytes)
@@ -842,6 +845,7 @@ hipError_t fc_launch_attention_mfma(const FcGeom &G, const FcAttnPlan &pl, const
     a.splits = pl.splits;
     a.keys_per_split = pl.keys_per_split;
     a.n_units = G.B * G.Hkv * pl.splits;
+    a.once = G.once && a.n_rg == 1;
     a.c = G.scale * 1.4426950408889634f;
     hipError_t e;
     const int R = pl.tiles_per_wg;

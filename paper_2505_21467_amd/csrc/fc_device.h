@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 struct bf16_t {
     uint16_t bits;
 };
@@ -42,10 +44,20 @@ __device__ __forceinline__ void fc_store_any(void *p, V v)
 }
 
 // Direct-to-LDS load: 16 bytes per lane, from a global address of each lane's own to the wave's `l` + 16 lane.
+// ONCE: with the non-temporal hint, for bytes that one workgroup reads once and that no cache holds (fc_read_once): they pass
+// the memory-side cache by and are the first to leave L2.
+template <bool ONCE = false>
 __device__ __forceinline__ void fc_load_lds16(const void *g, void *l)
 {
     __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)g,
-                                     (void __attribute__((address_space(3))) *)l, 16, 0, 0);
+                                     (void __attribute__((address_space(3))) *)l, 16, 0, ONCE ? 2 : 0);
+}
+// f(true_type) or f(false_type): a wave-uniform choice of the hint around a group of loads.
+template <typename F>
+__device__ __forceinline__ void fc_with_hint(bool once, F f)
+{
+    if (once) f(std::true_type());
+    else f(std::false_type());
 }
 
 // Wait until at most N of this wave's vector-memory operations are outstanding; LGKM0: and no LDS one.

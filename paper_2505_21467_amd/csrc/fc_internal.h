@@ -58,9 +58,19 @@ const FcKnobs &fc_knobs();
 // Geometry handed to kernels by value.
 struct FcGeom {
     int32_t B, d, Hq, Hkv, Dh, max_seq, spad, g;
+    bool once;        // weights and rows of a pass exceed the memory-side cache (fc_read_once)
     float scale;      // softmax scale
     double log_base;  // ln(rope_base)
 };
+
+// Whether a pass over so many bytes finds nothing of them in the memory-side cache (256 MB) when it comes round again.  Streams
+// that a single workgroup reads are then loaded with the non-temporal hint: they do not go through that cache on their way.
+// Per launch, without and with, us: 36 head slots, hidden 3584, 8 / 32 rows 9.9 / 11.6 and 9.1 / 11.0; gated 3584 x 18944, 32 rows 48.5 and
+// 44.1 (5.6 and 6.2 TB/s); 18944 x 3584 27.2 and 24.7; 136 MB of keys and values 52.5 and 47.1.  Where the bytes would have been
+// in that cache the hint loses: the same projection over one or two layers 8.6 and 11.0; and it loses where several
+// workgroups share a stream by way of L2 (attention with two groups of row tiles, 16800 keys 17.3 and 19.3; tiles of 48 rows,
+// three to a run, 17.9 and 19.1).
+inline bool fc_read_once(double bytes_per_pass) { return bytes_per_pass > 256.0 * 1024 * 1024; }
 
 // Element offset of K[b][j][row][i] inside one layer.
 __host__ __device__ inline size_t fc_k_index(const FcGeom &G, int b, int j, int row, int i)
@@ -155,7 +165,7 @@ bool fc_linear_lines_cover(int dtype, int mode, int M, int K, int N);
 int fc_lmhead_lines_parts(int dtype, int M, int K, int V, int parts);
 hipError_t fc_launch_lmhead_lines(const void *x, const void *w, int M, int K, int V, const FcArgmaxPart &am, hipStream_t s);
 hipError_t fc_launch_linear_lines(int mode, const void *x, const void *w, const void *w2, const void *res, int M, int K, int N,
-                                  void *out, hipStream_t s);
+                                  void *out, bool once, hipStream_t s);
 FcSkinnyPlan fc_plan_skinny(int dtype, int mode, int M, int K, int N);
 size_t fc_skinny_workspace(const FcSkinnyPlan &p);
 hipError_t fc_launch_linear_skinny(const FcSkinnyPlan &pl, int mode, const void *x, const void *w,
@@ -181,7 +191,7 @@ struct FcWidePlan {
 FcWidePlan fc_plan_wide(int dtype, int mode, int M, int K, int N);
 size_t fc_wide_workspace(const FcWidePlan &p, int M, int N);
 hipError_t fc_launch_linear_wide(const FcWidePlan &pl, int mode, const void *x, const void *w, const void *w2,
-                                 const void *res, int M, int K, int N, void *out, void *workspace, hipStream_t s,
+                                 const void *res, int M, int K, int N, void *out, void *workspace, bool once, hipStream_t s,
                                  const FcArgmaxPart *am = nullptr);
 hipError_t fc_launch_gather_rows(const void *table, int64_t R, int row_bytes, const int32_t *idx, int64_t n, void *out,
                                  hipStream_t s);

@@ -44,7 +44,8 @@ struct LinArgs {
     int M, K, N;          // N = output columns
     int S, T, G, maxseg, slabs;
     int wave_bytes;       // k_linear_lines: LDS of a wave,
-    uint32_t div_grid;    // reciprocal of the grid
+    uint32_t div_grid;    // reciprocal of the grid,
+    bool once;            // weights with the non-temporal hint
 };
 
 
@@ -563,11 +564,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     auto issue = [&](int st) {
         st += turn0;
         if (st >= n_stages) st -= n_stages;
+        fc_with_hint(p.once, [&](auto once) {
 #pragma unroll
-        for (int f = 0; f < NF; ++f)
+            for (int f = 0; f < NF; ++f)
 #pragma unroll
-            for (int i = 0; i < 2 * NR; ++i)
-                if (i < n_wl) fc_load_lds16(wbase[f] + (size_t)st * 128 + woff[i], wbuf + f * (NR * 2048) + 1024 * i);
+                for (int i = 0; i < 2 * NR; ++i)
+                    if (i < n_wl) fc_load_lds16<decltype(once)::value>(wbase[f] + (size_t)st * 128 + woff[i], wbuf + f * (NR * 2048) + 1024 * i);
+        });
 #pragma unroll
         for (int i = 0; i < 2 * MT; ++i) fc_load_lds16(xbase + (size_t)st * 128 + xoff[i], xbuf + 1024 * i);
     };
@@ -672,6 +675,7 @@ hipError_t launch_lines(LinArgs a, int runs, hipStream_t s)
     a.wave_bytes = ring > state ? ring : state;
     if ((a.N + runs - 1) / runs > 16 * NR || a.wave_bytes > 20 * 1024) return hipErrorInvalidValue;
     a.div_grid = fc_reciprocal(runs);
+    a.once = a.once && a.M <= 16 * MT;
     static hipError_t attr = hipFuncSetAttribute((const void *)k_linear_lines<MT, NR, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return attr;
     k_linear_lines<MT, NR, MODE><<<dim3((unsigned)runs, (unsigned)((a.M + 16 * MT - 1) / (16 * MT))), dim3(512), 8 * a.wave_bytes, s>>>(a);
@@ -929,7 +933,7 @@ bool fc_linear_lines_cover(int dtype, int mode, int M, int K, int N)
 }
 
 hipError_t fc_launch_linear_lines(int mode, const void *x, const void *w, const void *w2, const void *res, int M, int K, int N,
-                                  void *out, hipStream_t s)
+                                  void *out, bool once, hipStream_t s)
 {
     if (!fc_linear_lines_cover(FC_BF16, mode, M, K, N)) return hipErrorInvalidValue;
     LinArgs a;
@@ -942,6 +946,7 @@ hipError_t fc_launch_linear_lines(int mode, const void *x, const void *w, const 
     a.M = M;
     a.K = K;
     a.N = N;
+    a.once = once;
     switch (lines_tile(mode, M, K, N)) {
     case 1: return launch_lines_mt<1>(mode, a, s);
     case 2: return launch_lines_mt<2>(mode, a, s);

@@ -64,6 +64,7 @@ struct GemmArgs {
     uint16_t *out;         // EPI 1, 2: [M][N]
     float *part;           // EPI 3: partial sums [ksplit][M][N]
     int N;                 // output columns
+    bool once;             // weights with the non-temporal hint, where there is one tile of rows
     int ksplit;            // EPI 3: parts the hidden dimension is cut into
     FcArgmaxPart am;       // EPI 4: per (slab, row) largest logit, its index, sum of exponentials
 };
@@ -337,7 +338,7 @@ __device__ __forceinline__ void gemm_epilogue_vocab(const GemmArgs &p, const f32
 // (the parts are tiles of their own), for matrices with too few slabs to fill the chip; 4 = vocabulary projection of the
 // unmasking step: of the 128 logits of a slab only the largest, its index and the sum of
 // exp(logit - largest) are kept per row (NSUB = 4 only).
-template <int KS, int NW, int NSUB, int MW, int NG, int SLOTS, int NL, int EPI, bool ROTATE>
+template <int KS, int NW, int NSUB, int MW, int NG, int SLOTS, int NL, int EPI, bool ROTATE, bool ONCE>
 __global__ __launch_bounds__((NW + NL) * 64) void k_proj_gemm(GemmArgs p)
 {
     constexpr int ROWB = KS * 2;               // bytes of one row piece: 128 or 256
@@ -467,6 +468,7 @@ __global__ __launch_bounds__((NW + NL) * 64) void k_proj_gemm(GemmArgs p)
         for (int i = 0; i < LBW; ++i) {
             if (part >= 0 && (i & 3) != part) continue;
             if (DEALT && i >= my_blocks) continue;
+            static_assert(!ONCE || NL > 0, "weight blocks known at compile time");
             const uint16_t *mat = p.X;
             if (DEALT) {
                 // rows 16..31 of a sub-tile are the high rows: EPI 2 takes them from the up matrix
@@ -478,7 +480,8 @@ __global__ __launch_bounds__((NW + NL) * 64) void k_proj_gemm(GemmArgs p)
                 mat = up ? p.W2 : p.W;
             }
             const unsigned char *src = (const unsigned char *)mat + (size_t)at * ROWB;
-            fc_load_lds16(src + goff[i], dst + (lw + NLW * i) * 1024);
+            if (ONCE && i < WBW) fc_load_lds16<true>(src + goff[i], dst + (lw + NLW * i) * 1024);
+            else fc_load_lds16(src + goff[i], dst + (lw + NLW * i) * 1024);
         }
     };
 
@@ -821,19 +824,25 @@ hipError_t launch_gemm(GemmArgs a, hipStream_t s)
     const int64_t n_tiles = (int64_t)a.n_units * a.n_mt * (EPI == 3 ? a.ksplit : 1);
     if (n_tiles > (1 << 30) || (EPI == 3 && a.ksplit < 1)) return hipErrorInvalidValue;
     const unsigned grid = (unsigned)((n_tiles + 7) / 8 * 8);
-    auto start = [&](auto rotate) {
-        constexpr auto kernel = k_proj_gemm<KS, NW, NSUB, MW, NG, SLOTS, NL, EPI, decltype(rotate)::value>;
+    auto start = [&](auto rotate, auto once) {
+        constexpr auto kernel = k_proj_gemm<KS, NW, NSUB, MW, NG, SLOTS, NL, EPI, decltype(rotate)::value, decltype(once)::value>;
         static hipError_t attr = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
         if (attr != hipSuccess) return attr;
         kernel<<<dim3(grid), dim3((NW + NL) * 64), LDS, s>>>(a);
         return hipGetLastError();
     };
+    // One tile of rows: its workgroups are the only ones to read their weights.
+    auto with_hint = [&](auto rotate) {
+        if constexpr (XROWS <= 128)
+            if (a.once && a.M <= XROWS) return start(rotate, std::true_type());
+        return start(rotate, std::false_type());
+    };
     if constexpr (XROWS <= 128 && EPI != 3)
         if (a.n_mt == 1 && a.m_base == 0 && a.K % 2048 == 0 && a.K / KS < 65536) {
             a.rot_step = (uint32_t)(((int64_t)(a.K / KS) << 16) / (a.n_units < 256 ? a.n_units : 256));  // (place * rot_step stays below 2^32)
-            return start(std::true_type());
+            return with_hint(std::true_type());
         }
-    return start(std::false_type());
+    return with_hint(std::false_type());
 }
 
 // Sum of the hidden-dimension parts of an EPI 3 launch + residual, four outputs per thread.
@@ -1122,7 +1131,7 @@ size_t fc_wide_workspace(const FcWidePlan &p, int M, int N)
 }
 
 hipError_t fc_launch_linear_wide(const FcWidePlan &pl, int mode, const void *x, const void *w, const void *w2,
-                                 const void *res, int M, int K, int N, void *out, void *workspace, hipStream_t s,
+                                 const void *res, int M, int K, int N, void *out, void *workspace, bool once, hipStream_t s,
                                  const FcArgmaxPart *am)
 {
     if (pl.kind != 1 || (pl.ksplit > 1 && !workspace)) return hipErrorInvalidValue;
@@ -1140,6 +1149,7 @@ hipError_t fc_launch_linear_wide(const FcWidePlan &pl, int mode, const void *x, 
     a.N = N;
     a.n_slots = mode == FC_LIN_GATE_UP ? N / 64 : N / 128;
     a.ksplit = pl.ksplit;
+    a.once = once;
     a.slot_base = 0;
     a.slots_here = a.n_slots;
     a.m_base = 0;
@@ -1202,6 +1212,7 @@ hipError_t fc_launch_project_gemm(const FcGeom &G, const void *x, const void *w,
     a.out = nullptr;
     a.part = nullptr;
     a.N = 0;
+    a.once = G.once;
     a.ksplit = 1;
     a.rot1 = exp(-G.log_base / 64.0);
     a.rot8 = exp(-G.log_base / 8.0);

@@ -42,6 +42,7 @@ struct ProjArgs {
     int mt;                // 16-row window tiles of a partial
     int wave_bytes;        // k_proj_stream: LDS of a wave,
     uint32_t div_runs, div_a;  // reciprocals of the number of runs and of A
+    bool once;             // k_proj_stream: weights with the non-temporal hint
 };
 
 __device__ __forceinline__ bf16x8 ld8(const uint16_t *p)
@@ -400,9 +401,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     auto issue = [&](int st) {
         st += turn0;
         if (st >= n_stages) st -= n_stages;
+        fc_with_hint(p.once, [&](auto once) {
 #pragma unroll
-        for (int i = 0; i < 4 * NP; ++i)
-            if (i < n_wl) fc_load_lds16(wbase + (size_t)st * 128 + woff[i], wbuf + 1024 * i);
+            for (int i = 0; i < 4 * NP; ++i)
+                if (i < n_wl) fc_load_lds16<decltype(once)::value>(wbase + (size_t)st * 128 + woff[i], wbuf + 1024 * i);
+        });
 #pragma unroll
         for (int i = 0; i < 2 * MT; ++i) fc_load_lds16(xbase + (size_t)st * 128 + xoff[i], xbuf + 1024 * i);
     };
@@ -537,6 +540,7 @@ hipError_t launch_stream(ProjArgs a, int runs, hipStream_t s)
     if (run > 16 * NP || runs % 8 || a.wave_bytes > 20 * 1024) return hipErrorInvalidValue;
     a.div_runs = fc_reciprocal(runs);
     a.div_a = fc_reciprocal(a.A);
+    a.once = a.G.once && a.M <= 16 * MT;
     static hipError_t attr = hipFuncSetAttribute((const void *)k_proj_stream<MT, NP>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return attr;
     k_proj_stream<MT, NP><<<dim3((unsigned)runs, (unsigned)((a.M + 16 * MT - 1) / (16 * MT))), dim3(512), 8 * a.wave_bytes, s>>>(a);
