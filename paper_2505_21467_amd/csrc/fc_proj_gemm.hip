@@ -2,17 +2,10 @@
 // tiled matrix-core GEMM (bf16, head_dim 128), fused with bias, rotary embedding and the scatter into
 // the cache.  Table 1's "W_Q, W_K, W_V projections" row with L replaced by the window length.
 //
-// Y^T = W X^T: the weight rows are the A operand of v_mfma_f32_32x32x16_bf16 and the window rows the B
-// operand, so a lane of the accumulator holds 16 output features of ONE window row.  A wave owns 32
-// window rows and all NSUB 32-feature sub-tiles of its workgroup; with NSUB = 4 the workgroup covers a
-// whole head (features i and i + 64 of a rotary pair sit in sub-tiles t and t + 2, same lane, same
-// register), with NSUB = 2 it covers the rotary-paired half head {32 h .. 32 h + 31} u {64 + 32 h ..}
-// (more, smaller workgroups when the window is too short to fill the chip).  The rotation, the bias and
-// the stores to q_out / the K rows / the transposed V tiles therefore need no exchange between lanes.
-// A second kernel, k_gemm_pp, covers 256 window rows x two heads.  Two more shapes (NSUB = 5, 3) deal the rotary pairs of all head slots, laid end to end, 80 or 48 to a
-// workgroup (16 per sub-tile, low rows then high rows: the partner of register r is register r + 8): a
-// quarter more work per workgroup than a head for grids that would otherwise be a little more than one
-// round, a quarter less for grids well short of one.
+// Y^T = W X^T: the weight rows are the A operand of v_mfma_f32_16x16x32_bf16 and the window rows the B
+// operand, so a lane of the accumulator holds four output features of ONE window row.  The weight rows go by pairs -- the two
+// members of a rotary pair, or gate and up row -- and the pairs of all slabs, laid end to end, are dealt to the workgroups in
+// equal runs: 128, 80, 64, 48 or 32 pairs, so that a grid a little over one round of workgroups in one width fits a round in another.
 //
 // Both operands are contiguous along the hidden dimension.  64 (or 128) hidden elements of every row
 // of the tile (128- or 256-byte row pieces) stream HBM/L2 -> LDS with direct-to-LDS 16-byte loads into
@@ -20,11 +13,9 @@
 // 0..3) of the row (applied to the global address of the loading lane), which spreads the 16 lanes the
 // LDS serves per clock over 16 different bank groups.
 //
-// A wave that issues a direct-to-LDS load waits until the memory pipeline has taken it (about 46
-// cycles per load measured), and that wait is not hidden when the wave is alone on its SIMD.  The
-// 128-row shapes (four multiplying waves) therefore carry four more waves that do nothing but issue
-// the loads; in the 256-row shapes (two multiplying waves per SIMD) every wave issues its share, a
-// quarter at a time between its multiplies.
+// k_gemm_wide (256 window rows) issues its loads between its multiplies.  A wave that issues a direct-to-LDS load waits until the
+// memory pipeline has taken it (about 46 cycles per load measured back to back); k_proj_gemm (64 or 128 window rows, where the
+// weights' way in counts and not the multiplies) carries more waves that do nothing but issue the loads.
 #include <math.h>
 #include <string.h>
 
@@ -36,7 +27,7 @@
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int KS_MIN = 64;      // hidden elements per stage: 64 or 128 (template parameter KS)
 
@@ -50,8 +41,8 @@ struct GemmArgs {
     uint16_t *Vc;          // one layer
     FcGeom G;
     int M, A, K, win_start;
-    int n_mt;              // row tiles of 32 * NW window rows
-    int n_units;           // head slots (NSUB = 4) or half-head slots (NSUB = 2)
+    int n_mt;              // tiles of window rows
+    int n_units;           // tiles of pairs of weight rows
     uint32_t rot_step;     // ROTATE: stages / (units of a round of workgroups) in 1/65536
     int n_slots;           // 128-row slabs of W: head slots (EPI 0), N / 128 (EPI 1, 3), d_ff / 64 (EPI 2)
     // The part of the problem this launch covers (a problem may be cut into two launches with different
@@ -99,22 +90,22 @@ __device__ __forceinline__ uint4 pack8(const float (&y)[8])
     return w;
 }
 
-// bytes of LDS a wave needs for its epilogue: 32 rows of NT sub-tiles in fp32, 16 bytes of padding each
-__host__ __device__ constexpr int epi_bytes(int NT) { return 32 * (NT * 128 + 16); }
+// LDS a wave needs for its epilogue: 32 window rows of NT tiles of 16 weight rows in fp32, 16 bytes of padding each
+__host__ __device__ constexpr int epi_bytes(int NT) { return 32 * (NT * 64 + 16); }
 
 // The workgroup's bias goes to LDS at the very start: nothing else asks for it before the end, and a layer's bias
-// comes from HBM (2.5 us with the matrix core idle when the epilogue fetched it).  NPW pairs: the low values, then
-// the high ones; pairs (2 d, 2 d + 1) of all slabs laid end to end, from pair `first` on.  One wave calls this.
+// comes from HBM (2.5 us with the matrix core idle when the epilogue fetched it).  npw pairs from `first` on: the first
+// members, then their partners.  One wave calls this.
 // A direct load takes two values from a 4-byte address; a bias that starts at an odd element goes through registers.
 constexpr int BIAS_LDS = 512;
-__device__ __forceinline__ void load_bias(const GemmArgs &p, unsigned char *dst, int first, int npw, int n_pairs, int lane)
+__device__ __forceinline__ void load_bias(const GemmArgs &p, unsigned char *dst, int first, int npw, int pair_end, int lane)
 {
     if (!p.bias) return;
     for (int d0 = 0; d0 < npw; d0 += 64) {
         const int d = d0 + lane;
         if (d >= npw) break;
         const bool high = d >= npw / 2;
-        const int pr = min(first + 2 * (high ? d - npw / 2 : d), n_pairs - 2);
+        const int pr = min(first + 2 * (high ? d - npw / 2 : d), pair_end - 2);
         const uint16_t *src = p.bias + (pr >> 6) * 128 + (pr & 63) + (high ? 64 : 0);
         if (((uintptr_t)p.bias & 3) == 0)
             __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)src,
@@ -125,78 +116,71 @@ __device__ __forceinline__ void load_bias(const GemmArgs &p, unsigned char *dst,
     fc_wait_lds();  // LDS writes done, if any
 }
 
-// Epilogue of a wave.  Lane (col, hi) of sub-tile i holds window row m_first + 32 i + col; register r of
-// sub-tile t is row 8 (r >> 2) + 4 hi + (r & 3) of the sub-tile.  Sub-tiles are, in units of 32 features of slab hs:
-// t for a whole slab (NT = 4), {half, half + 2} for a half slab (NT = 2); or (DEALT) 16 pairs each, the low rows in
-// registers 0..7 and the high rows in 8..15, starting with pair pair0 of all slabs laid end to end, nt of them.
-// Either way the tile is a row of "low" and a row of "high" values per window row; the two members of a pair
-// (rotary pair, gate and up product) have the same place in the two.
+// A workgroup's weight rows are pairs: (i, i + 64) of a slab of 128 rows -- the two members of a rotary pair -- or (gate row,
+// up row) of a gated layer.  The pairs of all slabs, laid end to end, are dealt to the workgroups in runs of whole eights, and a wave's
+// tile holds the first members of its 8 NT pairs in its first 8 NT rows and their partners in the others.
 //
-// The values go through LDS, 32 window rows at a time in the wave's own area: in the accumulator layout a
-// store instruction covers 16 bytes of 32 different rows (128 KB of a 256 x 256 tile took 7.6 us to leave),
-// read back as rows it covers 128 or 256 contiguous bytes.  The loop over eight-value pieces is not
-// unrolled: this code runs once per tile, and unrolled it costs more in instruction fetches than in work.
-template <int NT, int MW, int EPI, bool DEALT>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x16 (&acc)[MW][NT], unsigned char *area,
-                                              const uint16_t *bias_low, const uint16_t *bias_high, int hs, int half, int pair0,
-                                              int nt, int m_first, int lane, int kpart)
+// Epilogue of a wave.  Lane (l, q) = (lane & 15, lane >> 4) of tile (i, t) holds rows 16 t + 4 q + r of the wave's weight rows for
+// window row m_first + 16 i + l.  The values go through LDS, 32 window rows at a time in the wave's own area: in the
+// accumulator layout a store instruction covers 8 bytes of 16 different rows, read back as rows it covers 128
+// or 256 contiguous bytes.  The loop over eight-value pieces is not unrolled: this code runs once per tile, and unrolled it
+// costs more in instruction fetches than in work.
+template <int MT, int NT, int EPI>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x4 (&acc)[MT][NT], unsigned char *area, const uint16_t *bias_low,
+                                              const uint16_t *bias_high, int pair0, int pair_end, int m_first, int lane, int kpart)
 {
-    constexpr int PITCH = NT * 128 + 16;         // bytes per window row: low values, high values, padding
-    constexpr int HIGH = NT * 64;                // offset of the high values
+    constexpr int P = 8 * NT;               // pairs of the wave
+    constexpr int PITCH = NT * 64 + 16;     // bytes per window row: first members, partners, padding
     const FcGeom &G = p.G;
-    const int col = lane & 31, hi = lane >> 5;
-    const int first_v = G.Hq + G.Hkv;            // EPI 0: first value slab
+    const int l = lane & 15, q = lane >> 4;
+    const int first_v = G.Hq + G.Hkv;       // EPI 0: first value slab
+    const bool has_v = EPI == 0 && pair0 + P > first_v * 64;
+    static_assert(MT % 2 == 0, "32 window rows at a time");
 #pragma unroll
-    for (int i = 0; i < MW; ++i) {
-        const int m_i = m_first + 32 * i;
-        // EPI 0: sequence, window row and position of row m_i + col (pp < 0: padded or past the end)
+    for (int i = 0; i < MT; i += 2) {
+        const int m_i = m_first + 16 * i;
+        // EPI 0: sequence, window row and position of row m_i + (lane & 31) (pp < 0: padded or past the end)
         int b_l = 0, a_l = 0, pp_l = -1;
-        if (EPI == 0 && m_i + col < p.m_end) {
-            b_l = (m_i + col) / p.A;
-            a_l = m_i + col - b_l * p.A;
-            pp_l = p.pos ? p.pos[m_i + col] : p.win_start + a_l;
-            if (pp_l >= G.max_seq) pp_l = -1;
+        if (EPI == 0) {
+            const int m = m_i + (lane & 31);
+            if (m < p.m_end) {
+                b_l = m / p.A;
+                a_l = m - b_l * p.A;
+                pp_l = p.pos ? p.pos[m] : p.win_start + a_l;
+                if (pp_l >= G.max_seq) pp_l = -1;
+            }
         }
-        if (EPI == 0 && (DEALT || hs >= first_v)) {
+        if (has_v) {
             // value rows go to the transposed tiles straight from the accumulators: lanes run along the keys
 #pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const int pr = pair0 + 16 * t, hs_t = DEALT ? pr >> 6 : hs;
-                if (DEALT && (t >= nt || hs_t < first_v || hs_t >= p.n_slots)) continue;
-                if (pp_l < 0) continue;
+            for (int h = 0; h < 2; ++h) {
+                const int b = __shfl(b_l, 16 * h + l, 64), pp = __shfl(pp_l, 16 * h + l, 64);
 #pragma unroll
-                for (int rq = 0; rq < 4; ++rq) {
-                    const int d0 = DEALT ? (pr & 63) + 8 * (rq & 1) + 4 * hi + 64 * (rq >> 1)
-                                         : 32 * (NT == 4 ? t : half + 2 * t) + 8 * rq + 4 * hi;
-                    uint16_t *v = p.Vc + fc_v_index(G, b_l, hs_t - first_v, pp_l, d0);
-                    // (the same place in the wave's low or high values as below)
-                    const uint16_t *bs = DEALT ? (rq >= 2 ? bias_high : bias_low) + 16 * t + 8 * (rq & 1) + 4 * hi
-                                               : (t >= NT / 2 ? bias_high : bias_low) + 32 * (t % (NT / 2 > 0 ? NT / 2 : 1)) + 8 * rq + 4 * hi;
+                for (int t = 0; t < NT; ++t) {
+                    const int j = 16 * t + 4 * q;
+                    const bool high = j >= P;
+                    const int pr = pair0 + (high ? j - P : j), hs = pr >> 6;
+                    if (hs < first_v || pr >= pair_end || pp < 0) continue;
+                    uint16_t *v = p.Vc + fc_v_index(G, b, hs - first_v, pp, (pr & 63) + (high ? 64 : 0));
+                    const uint16_t *bs = high ? bias_high + j - P : bias_low + j;
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        v[e * FC_VTILE] = fc_bf16_bits(acc[i][t][4 * rq + e] + (p.bias ? fc_to_float(bf16_t{bs[e]}) : 0.f));
+                        v[e * FC_VTILE] = fc_bf16_bits(acc[i + h][t][e] + (p.bias ? fc_to_float(bf16_t{bs[e]}) : 0.f));
                 }
             }
-            if (!DEALT) continue;
+            if (pair0 >= first_v * 64) continue;
         }
         // ---- to LDS
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
-                const bool high = DEALT ? rq >= 2 : t >= NT / 2;
-                const int at = (DEALT ? 64 * t + 32 * (rq & 1) : 128 * (t % (NT / 2 > 0 ? NT / 2 : 1)) + 32 * rq) + 16 * hi;
-                if (!DEALT || t < nt)
-                    *(float4 *)(area + col * PITCH + (high ? HIGH : 0) + at) =
-                        make_float4(acc[i][t][4 * rq], acc[i][t][4 * rq + 1], acc[i][t][4 * rq + 2], acc[i][t][4 * rq + 3]);
-            }
+            for (int t = 0; t < NT; ++t) *(f32x4 *)(area + (16 * h + l) * PITCH + 64 * t + 16 * q) = acc[i + h][t];
         __builtin_amdgcn_wave_barrier();
         fc_wait_lds();
-        // ---- and back as rows, eight low and eight high values per lane and step
-        const int per_row = DEALT ? 2 * nt : NT * 2;  // pieces of eight pairs per row
+        // ---- and back as rows, eight first members and their partners per lane and step
 #pragma unroll 1
-        for (int u = lane; u < 32 * per_row; u += 64) {
-            const int row = u / per_row, s = u - row * per_row;
+        for (int u = lane; u < 32 * NT; u += 64) {
+            const int row = u / NT, s = u - row * NT;
             const int m = m_i + row;
             int b = 0, a = 0, pp = 0;
             if (EPI == 0) {
@@ -209,15 +193,13 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x16 (&acc)[M
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 *(float4 *)(lo + 4 * h) = *(const float4 *)(src + 4 * h);
-                *(float4 *)(hv + 4 * h) = *(const float4 *)(src + HIGH / 4 + 4 * h);
+                *(float4 *)(hv + 4 * h) = *(const float4 *)(src + P + 4 * h);
             }
-            if (m >= p.m_end) continue;
-            const int pr = pair0 + 8 * s;                     // DEALT: pair
-            const int lf = DEALT ? pr & 63 : NT == 4 ? 8 * s : 32 * half + 8 * s;  // first low feature of the slab
-            const int hs_t = DEALT ? pr >> 6 : hs;
-            if (DEALT && hs_t >= p.n_slots) continue;
+            const int pr = pair0 + 8 * s;                 // first of the eight pairs
+            if (m >= p.m_end || pr >= pair_end) continue;
+            const int hs = pr >> 6, lf = pr & 63;         // slab, and place among its first members
             if constexpr (EPI == 0) {
-                if (DEALT && hs_t >= first_v) continue;
+                if (hs >= first_v) continue;
                 const bool valid = pp >= 0;
                 if (p.bias) {
                     union { uint4 u4; uint16_t h[8]; } bl, bh;
@@ -240,18 +222,18 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x16 (&acc)[M
                     const double turns = (double)pp * f;
                     const float ph = (float)(turns - rint(turns));
                     const float c = __builtin_amdgcn_cosf(ph), sn = __builtin_amdgcn_sinf(ph);
-                    const float l = lo[e], h = hv[e];
-                    lo[e] = l * c - h * sn;
-                    hv[e] = h * c + l * sn;
+                    const float x = lo[e], y = hv[e];
+                    lo[e] = x * c - y * sn;
+                    hv[e] = y * c + x * sn;
                     f *= p.rot1;
                 }
-                if (hs_t < G.Hq) {
-                    uint16_t *q = p.Q + (((size_t)b * G.Hq + hs_t) * p.A + a) * 128 + lf;
+                if (hs < G.Hq) {
+                    uint16_t *d = p.Q + (((size_t)b * G.Hq + hs) * p.A + a) * 128 + lf;
                     const uint4 ql = valid ? pack8(lo) : make_uint4(0, 0, 0, 0), qh = valid ? pack8(hv) : make_uint4(0, 0, 0, 0);
-                    fc_store_any(q, ql);
-                    fc_store_any(q + 64, qh);
+                    fc_store_any(d, ql);
+                    fc_store_any(d + 64, qh);
                 } else if (valid) {
-                    uint16_t *k = p.Kc + fc_k_index(G, b, hs_t - G.Hq, pp, lf);
+                    uint16_t *k = p.Kc + fc_k_index(G, b, hs - G.Hq, pp, lf);
                     *(uint4 *)k = pack8(lo);
                     *(uint4 *)(k + 64) = pack8(hv);
                 }
@@ -259,9 +241,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x16 (&acc)[M
                 float y[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) y[e] = silu_mul(lo[e], hv[e]);
-                *(uint4 *)(p.out + (size_t)m * p.N + hs_t * 64 + lf) = pack8(y);
+                *(uint4 *)(p.out + (size_t)m * p.N + pr) = pack8(y);
             } else {
-                const size_t at = (size_t)m * p.N + (size_t)hs * 128 + lf;  // low features at `at`, high ones 64 on
+                const size_t at = (size_t)m * p.N + (size_t)hs * 128 + lf;  // partners 64 on
                 if constexpr (EPI == 3) {
                     float *o = p.part + (size_t)kpart * p.M * p.N + at;
 #pragma unroll
@@ -290,542 +272,521 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x16 (&acc)[M
     }
 }
 
-// Vocabulary mode (EPI 4): lane (col, hi) holds, for window row col, the logits 32 t + 8 (r >> 2) + 4 hi + (r & 3)
-// of slab hs, ascending in (t, r), so that ties keep the smaller index; the other half is in lane ^ 32.  First the
+// Vocabulary mode (EPI 4): a wave's 128 weight rows are slab hs, a lane holds its logits 16 t + 4 q + r for window row 16 i + l,
+// ascending in (t, r), so that ties keep the smaller index; the others are in lanes 16, 32 and 48 on.  First the
 // maximum and its place, then the sum of exponentials against it, by the hardware's exponential of a rounded product.
 // On logits that are exact in fp32 the error of the confidences against 64 bits is 5 .. 10e-8, 0.87 times that of a running
 // maximum with expf and 0.89 times that of expf in this form, which also takes longer (256 rows x 152064: 309.0 us, this
 // 303.9); on others the logits' own error covers it.
-template <int MW>
-__device__ __forceinline__ void gemm_epilogue_vocab(const GemmArgs &p, const f32x16 (&acc)[MW][4], int hs, int m_first, int lane)
+template <int MT>
+__device__ __forceinline__ void gemm_epilogue_vocab(const GemmArgs &p, const f32x4 (&acc)[MT][8], int hs, int m_first, int lane)
 {
-    const int col = lane & 31, hi = lane >> 5;
+    const int l = lane & 15, q = lane >> 4;
 #pragma unroll
-    for (int i = 0; i < MW; ++i) {
-        const int m = m_first + 32 * i + col;
+    for (int i = 0; i < MT; ++i) {
+        const int m = m_first + 16 * i + l;
         float mx = -INFINITY, sm = 0.f;
         int arg = 0;
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < 8; ++t)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
+            for (int r = 0; r < 4; ++r) {
                 const bool more = acc[i][t][r] > mx;
                 mx = more ? acc[i][t][r] : mx;
-                arg = more ? 32 * t + 8 * (r >> 2) + (r & 3) : arg;
+                arg = more ? 16 * t + r : arg;
             }
-        arg += hs * 128 + 4 * hi;
+        arg += hs * 128 + 4 * q;
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < 8; t += 2) {
+            float e[8];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) sm += __builtin_amdgcn_exp2f((acc[i][t][r] - mx) * 1.4426950408889634f);
-        const float mx2 = __shfl_xor(mx, 32, 64), sm2 = __shfl_xor(sm, 32, 64);
-        const int arg2 = __shfl_xor(arg, 32, 64);
-        fc_argmax_merge(mx, arg, sm, mx2, arg2, sm2);
-        if (hi == 0 && m < p.m_end) p.am.at(hs, m) = FcArgmax{mx, arg, sm};
+            for (int r = 0; r < 8; ++r) e[r] = __builtin_amdgcn_exp2f((acc[i][t + r / 4][r % 4] - mx) * 1.4426950408889634f);
+            sm += ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
+        }
+#pragma unroll
+        for (int off = 16; off < 64; off <<= 1) {
+            const float mx2 = __shfl_xor(mx, off, 64), sm2 = __shfl_xor(sm, off, 64);
+            const int arg2 = __shfl_xor(arg, off, 64);
+            fc_argmax_merge(mx, arg, sm, mx2, arg2, sm2);
+        }
+        if (q == 0 && m < p.m_end) p.am.at(hs, m) = FcArgmax{mx, arg, sm};
     }
 }
 
-// Workgroup tile: NG head groups x WM row groups of waves (NW = NG * WM waves).  A wave owns MW
-// 32-row sub-tiles of window rows and the NSUB 32-feature sub-tiles of one head (NSUB = 4) or of one
-// rotary-paired half head (NSUB = 2).  SLOTS = stages in the LDS ring.
-// NL = 0: every wave also issues its share of the loads; NL > 0: NL extra waves do nothing but issue
-// the loads, so that the multiplying waves never wait for the memory pipeline to take a load.
+// Weight row of place `j` of a wave tile of 8 NT pairs from pair0 on, and the matrix it is of (EPI 2: first members gate, partners up).
+// Pairs past the end re-read the last one; they are never stored.
+template <int NT, int EPI>
+__device__ __forceinline__ uint32_t weight_row(int pair0, int pair_end, int j)
+{
+    const bool high = j >= 8 * NT;
+    const int pr = min(pair0 + (high ? j - 8 * NT : j), pair_end - 1);
+    return EPI == 2 ? pr : (uint32_t)((pr >> 6) * 128 + (pr & 63) + (high ? 64 : 0));
+}
+
+// Workgroup -> (tile of pairs and rows, part of the hidden dimension).  Workgroup ids that are equal modulo 8 land on the same XCD; the
+// tiles, ordered unit by unit, are dealt to the eight XCDs in equal contiguous runs, so the workgroups that stream the same weight
+// rows share an L2 and every XCD gets the same number of tiles (dealing whole units instead left 35 tiles on four XCDs and 28
+// on the others for 36 head slots x 7 row tiles: two rounds of 32 compute units instead of one, 100 us instead of 62).
+// The parts of the hidden dimension (EPI 3) count as tiles too.
+struct TilePlace {
+    int unit, mt, kpart;
+};
+template <int EPI>
+__device__ __forceinline__ bool tile_place(const GemmArgs &p, TilePlace &w)
+{
+    const int xcd = blockIdx.x & 7, qd = blockIdx.x >> 3;
+    const int n_kp = EPI == 3 ? p.ksplit : 1;
+    const int64_t n_tiles = (int64_t)p.n_units * p.n_mt * n_kp;
+    const int tile_k = (int)(xcd * n_tiles / 8) + qd;
+    if (tile_k >= (int)((xcd + 1) * n_tiles / 8)) return false;
+    const int tile = tile_k / n_kp;
+    w.kpart = tile_k - tile * n_kp;
+    w.unit = tile / p.n_mt;
+    w.mt = tile - w.unit * p.n_mt;
+    return true;
+}
+
+// -------------------------------------------------------------------------------------------------
+// At most 128 window rows per workgroup: NW waves that multiply, 32 window rows each and all 32 NSUB weight rows, and NL that
+// only load.
 // EPI selects the epilogue: 0 = QKV (bias, rotary embedding, scatter into the cache); the others are
 // the plain linear layers of the rest of the layer, whose 128-row slabs of W take the place of the
 // head slots: 1 = out = residual + x w^T; 2 = out = silu(x w_gate^T) * (x w_up^T), a slab being 64
-// gate rows (sub-tiles 0, 1) and the same 64 up rows (sub-tiles 2, 3), so that both products of an
-// output sit in one lane like a rotary pair; 3 = fp32 partial sums of one part of the hidden dimension
+// gate rows and the same 64 up rows; 3 = fp32 partial sums of one part of the hidden dimension
 // (the parts are tiles of their own), for matrices with too few slabs to fill the chip; 4 = vocabulary projection of the
 // unmasking step: of the 128 logits of a slab only the largest, its index and the sum of
 // exp(logit - largest) are kept per row (NSUB = 4 only).
-template <int KS, int NW, int NSUB, int MW, int NG, int SLOTS, int NL, int EPI, bool ROTATE, bool ONCE>
-__global__ __launch_bounds__((NW + NL) * 64) void k_proj_gemm(GemmArgs p)
+// SLOTS: stages in the LDS ring.  ONCE: the weights with the non-temporal hint.
+template <int KS, int NW, int NSUB, int SLOTS, int NL, int EPI, bool ROTATE, bool ONCE>
+__global__ __launch_bounds__((NW + NL) * 64) __attribute__((amdgpu_waves_per_eu((EPI == 4 && NW == 2) || NW + NL > 4 ? 2 : 1))) void k_proj_gemm(GemmArgs p)
 {
     constexpr int ROWB = KS * 2;               // bytes of one row piece: 128 or 256
     constexpr int CPR = ROWB / 16;             // 16-byte chunks per row piece
     constexpr int RPB = 1024 / ROWB;           // row pieces per 1 KB block (= one wave-wide load)
-    constexpr int NKK = KS / 16;               // k-steps per stage
-    constexpr int WM = NW / NG;
-    constexpr int NLW = NL > 0 ? NL : NW;      // waves that issue loads
-    constexpr bool DEALT = NSUB == 5 || NSUB == 3;
-    constexpr int PPU = 16 * NSUB;             // DEALT: pairs per workgroup
-    constexpr int WROWS = DEALT ? 32 * NSUB : 32 * NSUB * NG, XROWS = 32 * MW * WM;
+    constexpr int NKK = KS / 32;               // k-steps per stage
+    constexpr int MT = 2, NT = 2 * NSUB;       // tiles of 16 window rows and weight rows of a wave
+    constexpr int WROWS = 16 * NT, XROWS = 32 * NW, PAIRS = WROWS / 2;
     constexpr int WBYTES = WROWS * ROWB, STAGE = (WROWS + XROWS) * ROWB;
-    constexpr int NBLK = (WROWS + XROWS) / RPB;  // 1 KB blocks per stage
-    // NSUB = 5 or 3 ("dealt pairs", EPI 0 and 2 only): the workgroup takes 16 NSUB consecutive PAIRS of weight rows
-    // -- rotary pairs (i, i + 64) of the head slots laid end to end, or (gate row, up row) pairs -- 16
-    // pairs per sub-tile: the low rows in rows 0..15 of the sub-tile, the high rows in rows 16..31, so
-    // that the two members of a pair sit in one lane, registers r and r + 8.  The 52 blocks of a stage
-    // of the 80-pair shape do not divide by its eight waves: waves 0..3 issue seven loads per stage, waves
-    // 4..7 six (the 48-pair shape has four loading waves of seven blocks each).
-    // With NG = 2 the five sub-tiles are split between the two waves of a SIMD (sub-tiles 0..2 and 3..4),
-    // each wave taking MW = 2 row sub-tiles: the pair of waves reads 5 + 4 fragments for its 6 + 4
-    // multiplies of a k-step instead of 2 x 6 for 2 x 5 with 32-row waves (same time measured, less LDS
-    // traffic).
-    constexpr int NT = DEALT && NG == 2 ? (NSUB + 1) / 2 : NSUB;  // sub-tiles a wave owns (at most)
-    constexpr int WBLK = WROWS / RPB;          // weight blocks of a stage (the first ones)
-    constexpr int LBW = (NBLK + NLW - 1) / NLW;  // blocks per loading wave and stage (DEALT: at most)
-    constexpr int WBW = WBLK / NLW;            // of which weight blocks (not DEALT)
+    constexpr int NBLK = (WROWS + XROWS) / RPB, WBLK = WROWS / RPB;  // 1 KB blocks per stage, weight blocks first
+    constexpr int LBW = NBLK / NL, WBW = WBLK / NL;                  // per loading wave
     static_assert(KS == 64 || KS == 128, "stage depth");
-    static_assert(NW % NG == 0 && (DEALT || (NBLK % NLW == 0 && WBLK % NLW == 0)) && (NSUB >= 4 || NG == 1), "tile shape");
-    static_assert(!DEALT || ((EPI == 0 || EPI == 2) && (NG == 1 || NG == 2) &&
-                             (NL == 0 ? NBLK - (LBW - 1) * NLW == NLW / 2 : (NBLK % NLW == 0 && WBLK % NLW == 0))),
-                  "dealt pairs: QKV or gated epilogue");
+    static_assert(NBLK % NL == 0 && WBLK % NL == 0 && PAIRS % RPB == 0 && (EPI != 4 || NSUB == 4), "tile shape");
     static_assert((SLOTS - 1) * LBW < 64 && SLOTS >= 2 && SLOTS <= 4, "vmcnt range");
-    static_assert(EPI == 0 || NG == 1 || DEALT, "the plain linear layers use one slab per workgroup");
     extern __shared__ __align__(1024) unsigned char smem[];
 
-    // Workgroup -> (unit, row tile).  Workgroup ids that are equal modulo 8 land on the same XCD; the
-    // tiles, ordered unit by unit, are dealt to the eight XCDs in equal contiguous runs, so the
-    // workgroups that stream the same weight rows share an L2 and every XCD gets the same number of
-    // tiles (dealing whole units instead left 35 tiles on four XCDs and 28 on the others for 36 head
-    // slots x 7 row tiles: two rounds of 32 compute units instead of one, 100 us instead of 62).
-    const int id = blockIdx.x;
-    const int xcd = id & 7, qd = id >> 3;
-    // (EPI 3: the parts of the hidden dimension count as tiles too, so that they are dealt evenly as well)
-    const int n_kp = EPI == 3 ? p.ksplit : 1;
-    const int64_t n_tiles = (int64_t)p.n_units * p.n_mt * n_kp;
-    const int tile_k = (int)(xcd * n_tiles / 8) + qd;
-    if (tile_k >= (int)((xcd + 1) * n_tiles / 8)) return;
-    const int tile = tile_k / n_kp, kpart = tile_k - tile * n_kp;
-    const int unit = tile / p.n_mt, mt = tile - unit * p.n_mt;
-    const int m0 = p.m_base + mt * XROWS;
-    const int n_slots = p.n_slots;             // EPI 0: Hq query heads, Hkv key heads, Hkv value heads
+    TilePlace at;
+    if (!tile_place<EPI>(p, at)) return;
+    const int m0 = p.m_base + at.mt * XROWS;
+    const int pair0 = p.slot_base * 64 + at.unit * PAIRS, pair_end = (p.slot_base + p.slots_here) * 64;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int col = lane & 31, hi = lane >> 5;
-    const bool is_loader = NL > 0 && wave >= NW;  // wave-uniform
-    const int lw = NL > 0 ? wave - NW : wave;     // index among the loading waves
-    const int wn = (wave % NW) / WM, wm = wave % WM;  // this wave's head group and row group
-    const int hs = p.slot_base + (NSUB >= 4 ? unit * NG + wn : unit >> 1);  // (DEALT: not used)
-    const int half = NSUB >= 4 ? 0 : unit & 1;  // which rotary-paired half of the head
-    const bool head_valid = DEALT || hs < n_slots;  // an odd number of heads leaves the last pair half empty
-    const int n_pairs = n_slots * 64;           // DEALT: pairs of the whole problem
-    const int my_blocks = DEALT && NL == 0 && lw >= NLW / 2 ? LBW - 1 : LBW;  // wave-uniform
-    const int t0 = DEALT && NG == 2 && wn ? NT : 0;              // DEALT: first sub-tile of this wave
-    const int nt_mine = DEALT && NG == 2 && wn ? NSUB - NT : NT;  // and how many it owns (wave-uniform)
+    const int l = lane & 15, q = lane >> 4;
+    const int lw = wave - NW;                  // index among the loading waves
 
-    // ---- loader: per-lane source offsets (bytes from W / X, hidden offset 0) of this wave's blocks
-    uint32_t goff[LBW];
-#pragma unroll
-    for (int i = 0; i < LBW; ++i) {
-        const int bid = lw + NLW * i;               // block of the stage: weight blocks first (junk for lw < 0)
-        const bool is_w = DEALT ? bid < WBLK : i < WBW;
-        const int rl = RPB * (is_w ? bid : bid - WBLK) + lane / CPR;  // row of the W / X tile
-        // logical 16-byte chunk that lands at position lane % CPR of the row piece: 128-byte pieces are
-        // swizzled with bits 1..3 of the row, 256-byte pieces with bits 0..3
-        const int c = (lane % CPR) ^ (KS == 64 ? (rl >> 1) & 7 : rl & 15);
-        if (is_w) {
-            int n;
-            if (DEALT) {
-                const int pr = min(PPU * unit + 16 * (rl >> 5) + (rl & 15), n_pairs - 1);  // pairs past the end are never stored
-                if (EPI == 2) n = pr;  // row pr of the gate matrix (low) or of the up matrix (high)
-                else n = (pr >> 6) * 128 + (pr & 63) + ((rl & 16) ? 64 : 0);
-            } else if (EPI == 2) {  // row of the gate or of the up matrix (which of the two: see issue_stage)
-                const int u = min(hs, n_slots - 1);  // NG = 1 here: hs is the slab of the whole workgroup
-                n = u * 64 + (NSUB == 4 ? rl & 63 : 32 * half + (rl & 31));
-            } else if (NSUB == 4) {
-                n = min(p.slot_base + unit * NG + rl / 128, n_slots - 1) * 128 + (rl & 127);
-            } else {
-                n = min(hs, n_slots - 1) * 128 + (rl >> 5) * 64 + 32 * half + (rl & 31);
-            }
-            goff[i] = (uint32_t)n * (uint32_t)(p.K * 2) + c * 16;
-        } else {
-            const int m = min(m0 + rl, p.m_end - 1);  // rows past the end re-read the last row; never stored
-            goff[i] = (uint32_t)m * (uint32_t)(p.K * 2) + c * 16;
-        }
-    }
-    // The loads of a stage are issued in four parts spread over the multiplies of the stage before,
-    // because a wave that issues many of them back to back waits for the memory pipeline to take
-    // them before it can issue anything else.  part < 0: all of them.
     // part of the hidden dimension this workgroup covers (EPI 3 only: part kpart of p.ksplit)
     const int all_stages = p.K / KS;
-    const int st0 = EPI == 3 ? (int)((int64_t)kpart * all_stages / p.ksplit) : 0;
-    const int n_stages = EPI == 3 ? (int)(((int64_t)kpart + 1) * all_stages / p.ksplit) - st0 : all_stages;
-    // Rows of W that lie a multiple of 4 KB apart: workgroup `unit` starts unit / n_units of the way along the hidden
-    // dimension and goes round.  In step, all workgroups ask for the same 128 bytes of all those rows, and these share a few
-    // memory channels.  One row tile of up to 128 rows, us without and with: gated 4096 x 12288, 64 / 128 rows 47.1 and
-    // 35.8 / 49.0 and 41.3; 4096 x 14336 53.2 and 41.7 / 55.9 and 47.9; 2048 x 16384, 48 rows 34.0 and 26.0; 6144 x 16384 90 and 70;
-    // 8192 x 8192 60 and 45; vocabulary 4096 x 32000, 64 rows 64.6 and 49.6; projection, 96 slots, hidden 4096, 64 rows 27.3
-    // and 24.9.  At other distances it gives nothing or costs (hidden 5120 34.6 and 35.6, 7168 44.1 and 45.7, 1024 15.0 and
-    // 15.3), and so it does with more row tiles, whose window rows then come from L2 at two places at a time (256 rows of
-    // gated 4096 x 12288 66.9 and 70.3), and with the last rows of a problem, behind the launch that has just read the
-    // weights (300 rows of the same 102.8 and 107.0).
-    // More than one round of workgroups: by the place among the 256 that run together, 32 on each XCD.  (By unit / n_units
-    // those together cover a fifth of the hidden dimension at 1188 units.)  Vocabularies at hidden 4096, us without, by the
-    // unit, by the place: 64 rows, 33024 entries (258 units) 86.2, 72.8, 72.6; 50304 86.6, 82.1, 81.9; 65536 110.5, 92.5, 92.4; 98304 144.1,
-    // 140.8, 138.7; 152064 219.5, 217.2, 216.2; 196608 278.0, 270.0, 269.5; 96 rows, 65536 125.6, 100.7, 95.9; 106496 194.6, 177.9, 177.8.
-    // From four rounds on the workgroups drift apart by themselves and it is a few per cent either way: 96 rows,
-    // 128256 189.6, 196.3, 193.5 (the largest loss; 131072 192.3, 196.1, 197.4), 152064 234.0, 232.8, 231.4, 163840 255.4, 254.2, 249.9;
-    // 64 rows at hidden 2048, 131072 114.9, 96.1, 95.2; 96 rows at hidden 8192, 131072 377.0, 376.2, 380.2, 147456 445.4, 450.8, 456.0.
-    const int per_round = min(p.n_units, 256);
-    const int rot = ROTATE ? (int)(((uint32_t)(xcd * per_round / 8 + (qd & 31)) * p.rot_step) >> 16) : 0;
-    auto issue_stage = [&](int st, int part) {
-        const int sr = st + rot, at = st0 + (ROTATE && sr >= n_stages ? sr - n_stages : sr);
-        unsigned char *dst = smem + (st % SLOTS) * STAGE;
+    const int st0 = EPI == 3 ? (int)((int64_t)at.kpart * all_stages / p.ksplit) : 0;
+    const int n_stages = EPI == 3 ? (int)(((int64_t)at.kpart + 1) * all_stages / p.ksplit) - st0 : all_stages;
+    unsigned char *bias_area = smem + SLOTS * STAGE;  // behind the ring
+
+    if (wave >= NW) {
+        // ---- loading waves: per-lane source offsets (bytes from W / X, hidden offset 0) of this wave's blocks
+        uint32_t goff[LBW];
 #pragma unroll
         for (int i = 0; i < LBW; ++i) {
-            if (part >= 0 && (i & 3) != part) continue;
-            if (DEALT && i >= my_blocks) continue;
-            static_assert(!ONCE || NL > 0, "weight blocks known at compile time");
-            const uint16_t *mat = p.X;
-            if (DEALT) {
-                // rows 16..31 of a sub-tile are the high rows: EPI 2 takes them from the up matrix
-                const int bid = lw + NLW * i;
-                if (bid < WBLK) mat = (EPI == 2 && ((RPB * bid) & 16)) ? p.W2 : p.W;
-            } else if (i < WBW) {
-                // EPI 2: the second half of the tile rows (a whole number of 1 KB blocks) is the up matrix
-                const bool up = EPI == 2 && RPB * (lw + NLW * i) >= (NSUB == 4 ? 64 : 32);
-                mat = up ? p.W2 : p.W;
-            }
-            const unsigned char *src = (const unsigned char *)mat + (size_t)at * ROWB;
-            if (ONCE && i < WBW) fc_load_lds16<true>(src + goff[i], dst + (lw + NLW * i) * 1024);
-            else fc_load_lds16(src + goff[i], dst + (lw + NLW * i) * 1024);
+            const int bid = lw + NL * i;
+            const int rl = RPB * (i < WBW ? bid : bid - WBLK) + lane / CPR;  // row of the W / X tile
+            // logical 16-byte chunk that lands at position lane % CPR of the row piece: 128-byte pieces are
+            // swizzled with bits 1..3 of the row, 256-byte pieces with bits 0..3
+            const int c = (lane % CPR) ^ (KS == 64 ? (rl >> 1) & 7 : rl & 15);
+            const uint32_t row = i < WBW ? weight_row<NT, EPI>(pair0, pair_end, rl)
+                                         : (uint32_t)min(m0 + rl, p.m_end - 1);  // rows past the end: never stored
+            goff[i] = row * (uint32_t)(p.K * 2) + c * 16;
         }
-    };
+        // Rows of W that lie a multiple of 4 KB apart: workgroup `unit` starts unit / n_units of the way along the hidden
+        // dimension and goes round.  In step, all workgroups ask for the same 128 bytes of all those rows, and these share a few
+        // memory channels.  One row tile of up to 128 rows, us without and with: gated 4096 x 12288, 64 / 128 rows 47.1 and
+        // 35.8 / 49.0 and 41.3; 4096 x 14336 53.2 and 41.7 / 55.9 and 47.9; 2048 x 16384, 48 rows 34.0 and 26.0; 6144 x 16384 90 and 70;
+        // 8192 x 8192 60 and 45; vocabulary 4096 x 32000, 64 rows 64.6 and 49.6; projection, 96 slots, hidden 4096, 64 rows 27.3
+        // and 24.9.  At other distances it gives nothing or costs (hidden 5120 34.6 and 35.6, 7168 44.1 and 45.7, 1024 15.0 and
+        // 15.3), and so it does with more row tiles, whose window rows then come from L2 at two places at a time (256 rows of
+        // gated 4096 x 12288 66.9 and 70.3), and with the last rows of a problem, behind the launch that has just read the
+        // weights (300 rows of the same 102.8 and 107.0).
+        // More than one round of workgroups: by the place among the 256 that run together, 32 on each XCD.  (By unit / n_units
+        // those together cover a fifth of the hidden dimension at 1188 units.)  Vocabularies at hidden 4096, us without, by the
+        // unit, by the place: 64 rows, 33024 entries (258 units) 86.2, 72.8, 72.6; 50304 86.6, 82.1, 81.9; 65536 110.5, 92.5, 92.4; 98304 144.1,
+        // 140.8, 138.7; 152064 219.5, 217.2, 216.2; 196608 278.0, 270.0, 269.5; 96 rows, 65536 125.6, 100.7, 95.9; 106496 194.6, 177.9, 177.8.
+        // From four rounds on the workgroups drift apart by themselves and it is a few per cent either way: 96 rows,
+        // 128256 189.6, 196.3, 193.5 (the largest loss; 131072 192.3, 196.1, 197.4), 152064 234.0, 232.8, 231.4, 163840 255.4, 254.2, 249.9;
+        // 64 rows at hidden 2048, 131072 114.9, 96.1, 95.2; 96 rows at hidden 8192, 131072 377.0, 376.2, 380.2, 147456 445.4, 450.8, 456.0.
+        const int per_round = min(p.n_units, 256);
+        const int place = (int)(blockIdx.x & 7) * per_round / 8 + (int)(blockIdx.x >> 3 & 31);
+        const int rot = ROTATE ? (int)(((uint32_t)place * p.rot_step) >> 16) : 0;
+        auto issue_stage = [&](int st) {
+            const int sr = st + rot, hidden = st0 + (ROTATE && sr >= n_stages ? sr - n_stages : sr);
+            unsigned char *dst = smem + (st % SLOTS) * STAGE;
+#pragma unroll
+            for (int i = 0; i < LBW; ++i) {
+                // EPI 2: the partners (whole blocks) are rows of the up matrix
+                const uint16_t *mat = i >= WBW ? p.X : EPI == 2 && RPB * (lw + NL * i) >= PAIRS ? p.W2 : p.W;
+                const unsigned char *src = (const unsigned char *)mat + (size_t)hidden * ROWB;
+                if (ONCE && i < WBW) fc_load_lds16<true>(src + goff[i], dst + (lw + NL * i) * 1024);
+                else fc_load_lds16(src + goff[i], dst + (lw + NL * i) * 1024);
+            }
+        };
+        if (EPI == 0 && lw == 0) load_bias(p, bias_area, pair0, PAIRS, pair_end, lane);
+        // One barrier per stage, shared with the multiplying waves.  Barrier `it` (it = 0 .. n_stages - 2) means: stage it+1 is
+        // complete and every multiplying wave has left stage it, whose slot takes stage it + SLOTS.
+        const int n_pro = min(SLOTS, n_stages);
+        for (int st = 0; st < n_pro; ++st) issue_stage(st);
+        wait_stages<LBW, false>(n_pro - 1);
+        __builtin_amdgcn_s_barrier();  // stage 0 is complete
+        for (int it = 0; it + 1 < n_stages; ++it) {
+            // stages requested so far: min(n_stages, it + SLOTS); those after it+1 may stay in flight
+            wait_stages<LBW, false>(min(n_stages, it + SLOTS) - (it + 2));
+            __builtin_amdgcn_s_barrier();
+            if (it + SLOTS < n_stages) issue_stage(it + SLOTS);
+        }
+        return;
+    }
 
-    // bias, behind the ring
-    constexpr int NPW = DEALT ? PPU : NSUB == 4 ? 64 * NG : 32;  // pairs per workgroup
-    unsigned char *bias_area = smem + SLOTS * STAGE;
-    if (EPI == 0 && lw == 0)
-        load_bias(p, bias_area, DEALT ? PPU * unit : NSUB == 4 ? (p.slot_base + unit * NG) * 64 : hs * 64 + 32 * half, NPW, n_pairs, lane);
-
-    // ---- operand read offsets inside a stage (bytes): row `col` of a 32-row sub-tile, k-step kk
+    // ---- operand read offsets inside a stage (bytes): row l of a 16-row tile, k-step kk
     uint32_t foff[NKK];
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk)
-        foff[kk] = (uint32_t)(col * ROWB + (((2 * kk + hi) ^ (KS == 64 ? (col >> 1) & 7 : col & 15)) << 4));
-    const uint32_t w_base = (uint32_t)((DEALT ? t0 : wn * NSUB) * 32 * ROWB);
-    const uint32_t x_base = (uint32_t)(WBYTES + wm * MW * 32 * ROWB);
+        foff[kk] = (uint32_t)(l * ROWB + (((4 * kk + q) ^ (KS == 64 ? (l >> 1) & 7 : l)) << 4));
+    const uint32_t x_base = (uint32_t)(WBYTES + wave * 32 * ROWB);
 
-    f32x16 acc[MW][NT];
+    f32x4 acc[MT][NT];
 #pragma unroll
-    for (int i = 0; i < MW; ++i)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
+        for (int t = 0; t < NT; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // Logits of up to 64 rows are summed in two levels, chains over 512 elements and those.  Relative error of the confidences against
+    // 64 bits, 32 rows x 152064, hidden 3584 / 4096: 7.8e-7 / 6.2e-7 in one chain over all elements, 2.1e-7 / 1.7e-7 in two levels, 2.4e-7 / 2.3e-7
+    // in the whole-row kernel, whose waves cut the hidden dimension in eight.
+    constexpr bool LEVELS = EPI == 4 && XROWS == 64;
+    constexpr int RUN = 512 / KS;
+    f32x4 total[LEVELS ? MT : 1][LEVELS ? NT : 1];
+    auto fold = [&]() {
+        if constexpr (LEVELS) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][t][r] = 0.f;
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        total[i][t][r] += acc[i][t][r];
+                        acc[i][t][r] = 0.f;
+                    }
+        }
+    };
+    if constexpr (LEVELS) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) total[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
 
     // Fragments are double-buffered in registers: the LDS reads of k-step kk+1 are issued before the
     // multiplies of k-step kk, and the first reads of the next stage go out (behind that stage's
     // barrier) before the last multiplies of this one, so the matrix core never waits for LDS.
-    bf16x8 xf[2][MW], wf[2][NT];
+    bf16x8 xf[2][MT], wf[2][NT];
     auto read_frags = [&](int slot, int kk, int buf) {
         const unsigned char *st = smem + slot * STAGE;
 #pragma unroll
-        for (int i = 0; i < MW; ++i) xf[buf][i] = *(const bf16x8 *)(st + x_base + i * (32 * ROWB) + foff[kk]);
+        for (int i = 0; i < MT; ++i) xf[buf][i] = *(const bf16x8 *)(st + x_base + i * (16 * ROWB) + foff[kk]);
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
-            if (t < nt_mine) wf[buf][t] = *(const bf16x8 *)(st + w_base + t * (32 * ROWB) + foff[kk]);
+        for (int t = 0; t < NT; ++t) wf[buf][t] = *(const bf16x8 *)(st + t * (16 * ROWB) + foff[kk]);
     };
     auto multiply = [&](int buf) {
 #pragma unroll
-        for (int i = 0; i < MW; ++i)
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
             for (int t = 0; t < NT; ++t)
-                if (t < nt_mine)
-                    acc[i][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[buf][t], xf[buf][i], acc[i][t], 0, 0, 0);
+                acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[buf][t], xf[buf][i], acc[i][t], 0, 0, 0);
     };
-
-    const int n_pro = min(SLOTS, n_stages);
-    if (NL > 0) {
-        // ---- loading waves: one barrier per stage, shared with the multiplying waves.  Barrier `it`
-        // (it = 0 .. n_stages - 2) means: stage it+1 is complete and every multiplying wave has left
-        // stage it, whose slot takes stage it + SLOTS.
-        if (is_loader) {
-            for (int st = 0; st < n_pro; ++st) issue_stage(st, -1);
-            wait_stages<LBW, false>(n_pro - 1);
-            __builtin_amdgcn_s_barrier();  // stage 0 is complete
-            for (int it = 0; it + 1 < n_stages; ++it) {
-                // stages requested so far: min(n_stages, it + SLOTS); those after it+1 may stay in flight
-                wait_stages<LBW, false>(min(n_stages, it + SLOTS) - (it + 2));
-                __builtin_amdgcn_s_barrier();
-                if (it + SLOTS < n_stages) issue_stage(it + SLOTS, -1);
-            }
-            return;
-        }
-        __builtin_amdgcn_s_barrier();  // stage 0 is complete
-        read_frags(0, 0, 0);
-        int slot = 0;
-        for (int it = 0; it < n_stages; ++it) {
-#pragma unroll
-            for (int kk = 0; kk < NKK - 1; ++kk) {
-                read_frags(slot, kk + 1, (kk + 1) & 1);
-                __builtin_amdgcn_sched_barrier(0);
-                multiply(kk & 1);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            const int nslot = slot == SLOTS - 1 ? 0 : slot + 1;
-            if (it + 1 < n_stages) {
-                fc_wait_lds();  // lgkmcnt(0): the reads of stage `it` have returned
-                __builtin_amdgcn_s_barrier();
-                read_frags(nslot, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            multiply(1);
-            __builtin_amdgcn_sched_barrier(0);
-            slot = nslot;
-        }
-    } else {
-    for (int st = 0; st < n_pro; ++st) issue_stage(st, -1);
-    if (my_blocks == LBW) wait_stages<LBW, false>(n_pro - 1);
-    else wait_stages<LBW - 1, false>(n_pro - 1);
-    __builtin_amdgcn_s_barrier();  // stage 0 is complete for every wave
+    __builtin_amdgcn_s_barrier();  // stage 0 is complete
     read_frags(0, 0, 0);
     int slot = 0;
     for (int it = 0; it < n_stages; ++it) {
-        // The slot of stage it-1 was released by the barrier in the middle of the previous iteration;
-        // stage it-1+SLOTS goes there: its first quarter was issued behind that barrier, the rest now.
-        const int refill = it - 1 + SLOTS;
-        const bool do_refill = it > 0 && refill < n_stages;
 #pragma unroll
         for (int kk = 0; kk < NKK - 1; ++kk) {
             read_frags(slot, kk + 1, (kk + 1) & 1);
-            if (do_refill && kk < 3) issue_stage(refill, kk + 1);
             __builtin_amdgcn_sched_barrier(0);
             multiply(kk & 1);
             __builtin_amdgcn_sched_barrier(0);
         }
         const int nslot = slot == SLOTS - 1 ? 0 : slot + 1;
         if (it + 1 < n_stages) {
-            // This wave's reads of stage `it` have all returned (lgkmcnt 0); behind the barrier that
-            // holds for every wave, and stage it+1 is complete (later stages may still be in flight).
-            if (my_blocks == LBW) wait_stages<LBW, true>(min(n_stages, it + SLOTS) - (it + 2));
-            else wait_stages<LBW - 1, true>(min(n_stages, it + SLOTS) - (it + 2));
+            fc_wait_lds();  // lgkmcnt(0): the reads of stage `it` have returned
             __builtin_amdgcn_s_barrier();
-            if (it + SLOTS < n_stages) issue_stage(it + SLOTS, 0);
             read_frags(nslot, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
-        multiply(1);
+        multiply((NKK - 1) & 1);
         __builtin_amdgcn_sched_barrier(0);
+        if (LEVELS && it % RUN == RUN - 1) fold();
         slot = nslot;
-    }
     }
 
     // ---- epilogue; the LDS ring is its staging area, once every wave has left it
     if constexpr (EPI == 4) {
-        if (head_valid) gemm_epilogue_vocab<MW>(p, acc, hs, m0 + 32 * wm * MW, lane);
+        if constexpr (LEVELS) {
+            fold();
+            gemm_epilogue_vocab<MT>(p, total, pair0 >> 6, m0 + 32 * wave, lane);
+        } else {
+            gemm_epilogue_vocab<MT>(p, acc, pair0 >> 6, m0 + 32 * wave, lane);
+        }
     } else {
         static_assert(NW * epi_bytes(NT) <= SLOTS * STAGE, "epilogue staging");
         __builtin_amdgcn_s_barrier();
-        if (!head_valid) return;
-        const uint16_t *bias_low = (const uint16_t *)bias_area + (DEALT ? 16 * t0 : NSUB == 4 ? 64 * wn : 0);
-        gemm_epilogue<NT, MW, EPI, DEALT>(p, acc, smem + wave * epi_bytes(NT), bias_low, bias_low + NPW, hs, half, PPU * unit + 16 * t0, nt_mine,
-                                          m0 + 32 * wm * MW, lane, kpart);
+        const uint16_t *bias_low = (const uint16_t *)bias_area;
+        gemm_epilogue<MT, NT, EPI>(p, acc, smem + wave * epi_bytes(NT), bias_low, bias_low + PAIRS, pair0, pair_end, m0 + 32 * wave, lane, at.kpart);
     }
 }
 
 // -------------------------------------------------------------------------------------------------
-// 256 window rows x two slabs (256 weight rows), for problems with enough such tiles to fill the chip.
+// 256 window rows: four waves, one per SIMD, WN of them along the weight rows, each with MT x NT tiles of 16 x 16 (128 x 128, 128 x 80
+// or 64 x 128).
 //
-// A workgroup has eight waves in two groups of four, one wave of each group per SIMD; group wn owns slab wn
-// and its wave wm the window rows 64 wm .. 64 wm + 63 (MW = 2, NT = 4 sub-tiles of 32 x 32).  The loop over
-// 64 hidden elements (a stage) alternates between reading operand fragments from LDS (and issuing loads)
-// and multiplying, with a workgroup barrier behind each such interval, and group 1 runs one interval behind
-// group 0: on every SIMD one wave multiplies while the other reads, so that LDS results never have to
-// wait for the register ports of a running multiply and the matrix core always has a wave to run.  The loads
-// of an interval are issued behind its reads: in front of them they held the reads back (1.74 us per stage at half
-// the compute units, 1.32 behind).  2304 rows x 296 gated slabs, hidden 3584: 635 us in tiles of one slab, 560 in
-// this one, 551 with the last round cut off (1135 TFLOP/s); with all compute units multiplying and no loads at
-// all the same loop runs at 1380 TFLOP/s, which is what the clock allows under that load.
+// One wave per SIMD keeps up to 256 accumulators and reads the fewest operand bytes from LDS: 131 KB per 64 hidden
+// elements of a 256 x 256 tile against 196 KB with eight waves of 64 x 128, which together with the 64 KB of loads is
+// as much as LDS moves in the time of the multiplies.  v_mfma 16x16x32 instead of 32x32x16: under the power limit, multiplies
+// alone, 2024 against 1780 TFLOP/s (the accumulators are read and written half as often).  A stage of 64 hidden elements is two
+// phases of MT * NT multiplies; between them go the fragment reads of the next phase and the loads of later stages, one every
+// few multiplies, so nothing is waited for but the stage's barrier in the middle:
 //
-//   interval   M0            C0          M1         C1          M2            C2          M3               C3
-//   reads      W sub 0,1                 X sub 1                W sub 2,3                 X sub 0 (next)
-//   multiplies               X0 W01                 X1 W01                    X0 W23                       X1 W23
+//   barrier(s)   stage s+1 has arrived, every wave has read all of stage s: its slots are free
+//   phase B(s)   multiplies the second half of stage s; reads the first half of stage s+1, issues the first loads of batch s
+//   phase A(s+1) multiplies the first half of stage s+1; reads the second half, issues the other loads of batch s
 //
-// LDS holds two stages of 64 KB in four parts (X0, W01, X1, W23: 128 rows x 128 B, swizzled like the other
-// shapes).  A part is refilled, for the stage after the next, one or two intervals after its last reader:
-// group 0 issues its half of W23, X0, W01, X1 in M0 .. M3, group 1 its half of X0, W01, X1, W23, so a
-// load has eleven intervals (about 1.4 us) to arrive, and some 88 KB are always in flight.  Each wave
-// waits for its own loads of the part that group 0 reads next at the end of every second interval; the count of
-// younger loads is the same every time (five parts in group 0, six in group 1, two loads each).  Past the last
-// stage the loads go on, from the last stage's addresses, into parts nobody reads: the counts stay exact.
-template <int GRP, typename Issue, typename Read, typename Mul>
-__device__ __forceinline__ void gemm_pp_loop(int n_stages, Issue issue, Read read, Mul mul)
+// Batch s is window rows of stage s + XS and weight rows of stage s + WS, into the slots just freed.
+// Against eight waves and 32x32x16 multiplies, us: gated 3584 x 18944, 2304 rows (256 x 256) 492 -> 431 + 37, 256 rows (256 x 160, weights
+// from HBM) 83 -> 71; 18944 x 3584, 2304 rows (256 x 128) 470 -> 405; vocabulary 3584 x 152064, 256 rows 325 -> 283.  In the loop a
+// 256 x 256 x 64 stage takes 2460 clocks of which 2048 are multiplies; the clock is what the power limit leaves, 1.8 GHz.
+// Weights from HBM: a compute unit has some 64 KB of loads under way, taken in order, so window rows that are in L2 wait behind
+// weights that are not (256 x 160: loads alone 0.97 us a stage, weights alone 0.75, with the non-temporal hint both 0.86).
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_for(F f)
 {
-    constexpr int AHEAD = 2 * (GRP == 0 ? 5 : 6);
-    auto end_m = [&]() {  // end of a memory interval
-        fc_wait_vm<GRP == 1 ? AHEAD : 63, true>();
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    auto compute = [&](int i, int tp) {
-        mul(i, tp);
-        __builtin_amdgcn_sched_barrier(0);
-        if (GRP == 0) fc_wait_vm<AHEAD>();
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    // parts: 0 X0, 1 W01, 2 X1, 3 W23
-#pragma unroll
-    for (int part = 0; part < 4; ++part) issue(0, part);
-#pragma unroll
-    for (int part = 0; part < (GRP == 0 ? 3 : 4); ++part) issue(1, part);
-    fc_wait_vm<AHEAD>();  // X0 and W01 of stage 0
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    read(0, 0);
-    if (GRP == 1) {
-        fc_wait_lds();
-        __builtin_amdgcn_s_barrier();  // one interval behind
-        __builtin_amdgcn_sched_barrier(0);
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>());
+        static_for<I + 1, N>(f);
     }
-    for (int st = 0; st < n_stages; ++st) {
-        // M0
-        read(st, 1);
-        issue(GRP == 0 ? st + 1 : st + 2, GRP == 0 ? 3 : 0);
-        end_m();
-        compute(0, 0);
-        // M1
-        read(st, 2);
-        issue(st + 2, GRP == 0 ? 0 : 1);
-        end_m();
-        compute(1, 0);
-        // M2
-        read(st, 3);
-        issue(st + 2, GRP == 0 ? 1 : 2);
-        end_m();
-        compute(0, 1);
-        // M3
-        read(st + 1, 0);  // (behind the last stage: not used)
-        issue(st + 2, GRP == 0 ? 2 : 3);
-        end_m();
-        compute(1, 1);
-    }
-    if (GRP == 0) __builtin_amdgcn_s_barrier();
-    fc_wait_vm<0>();  // no load may still arrive in LDS when the epilogue uses it
-    __builtin_amdgcn_s_barrier();
 }
 
-constexpr int PP_LDS = 8 * epi_bytes(4) > 128 * 1024 ? 8 * epi_bytes(4) : 128 * 1024;  // the loop's two stages; the epilogue
-template <int EPI>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_pp(GemmArgs p)
+template <int MT, int NT, int WN, int WS, int XS, int EPI, bool ONCE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_gemm_wide(GemmArgs p)
 {
-    constexpr int PART = 128 * 128, STAGE = 4 * PART;
+    constexpr int WROWS = 16 * NT * WN, XROWS = 16 * MT * 4 / WN, PAIRS = WROWS / 2;
+    constexpr int WBYTES = WROWS * 128, XBYTES = XROWS * 128;       // a stage of 64 hidden elements
+    constexpr int WL = WROWS / 32, XL = XROWS / 32, BATCH = WL + XL;  // 1 KB loads per wave
+    constexpr int NM = MT * NT, NR = MT + NT;                       // multiplies and reads of a phase
+    // loads that may still be on their way when stage s + 1 has to be there: those behind X(s + 1) and behind W(s + 1)
+    constexpr int BEHIND_X = (XS - 2) * BATCH + WL, BEHIND_W = (WS - 2) * BATCH;
+    constexpr int AHEAD = BEHIND_X < BEHIND_W ? BEHIND_X : BEHIND_W;
+    static_assert(XROWS == 256 && XS >= 2 && WS >= XS && WS <= 4 && AHEAD + BATCH < 64, "ring");
+    static_assert(WS * WBYTES + XS * XBYTES >= 4 * epi_bytes(NT) + 1024, "epilogue staging, bias");
+    static_assert(EPI != 4 || NT == 8, "a slab per wave");
     extern __shared__ __align__(1024) unsigned char smem[];
-    // workgroup -> (slab pair, row tile), dealt to the XCDs as in k_proj_gemm
-    const int id = blockIdx.x;
-    const int xcd = id & 7, qd = id >> 3;
-    const int64_t n_tiles = (int64_t)p.n_units * p.n_mt;
-    const int tile = (int)(xcd * n_tiles / 8) + qd;
-    if (tile >= (int)((xcd + 1) * n_tiles / 8)) return;
-    const int unit = tile / p.n_mt, mt = tile - unit * p.n_mt;
-    const int m0 = p.m_base + mt * 256;
+    unsigned char *const wring = smem, *const xring = smem + WS * WBYTES;
+
+    TilePlace at;
+    if (!tile_place<EPI>(p, at)) return;
+    const int m0 = p.m_base + at.mt * XROWS;
+    const int pair0 = p.slot_base * 64 + at.unit * PAIRS, pair_end = (p.slot_base + p.slots_here) * 64;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int col = lane & 31, hi = lane >> 5;
-    const int wn = wave >> 2, wm = wave & 3;
+    const int wn = WN == 1 ? 0 : wave >> 1, wm = WN == 1 ? wave : wave & 1;
+    const int l = lane & 15, q = lane >> 4;
 
-    // ---- loads: two 1 KB blocks (8 rows x 128 B) of each part per wave
-    uint32_t goff[4][2];
+    // The workgroup's bias, one weight row per thread, is asked for here and waits in a register (the ring takes all of LDS):
+    // fetched by the epilogue it cost 2.5 us with the matrix cores idle.
+    uint16_t bias = 0;
+    if (EPI == 0 && p.bias && tid < WROWS) bias = p.bias[weight_row<NT, EPI>(pair0 + (tid / (16 * NT)) * 8 * NT, pair_end, tid % (16 * NT))];
+
+    // ---- loads: 8 rows x 128 B each, the 16-byte chunks of a row permuted by bits 1..3 of the row
+    uint32_t woff[WL], xoff[XL];
 #pragma unroll
-    for (int part = 0; part < 4; ++part)
+    for (int i = 0; i < WL; ++i) {
+        const int r = 8 * (wave + 4 * i) + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+        woff[i] = weight_row<NT, EPI>(pair0 + (r / (16 * NT)) * 8 * NT, pair_end, r % (16 * NT)) * (uint32_t)(p.K * 2) + c * 16;
+    }
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int r = 8 * (2 * wave + i) + (lane >> 3);  // row of the part
-            const int c = (lane & 7) ^ ((r >> 1) & 7);
-            int row;
-            if ((part & 1) == 0) {
-                row = min(m0 + 64 * (r >> 5) + 16 * part + (r & 31), p.m_end - 1);  // rows past the end: never stored
-            } else {
-                const int slab = min(p.slot_base + 2 * unit + (r >> 6), p.n_slots - 1);
-                row = EPI == 2 ? slab * 64 + (r & 63) : slab * 128 + (part == 3 ? 64 : 0) + (r & 63);
-            }
-            goff[part][i] = (uint32_t)row * (uint32_t)(p.K * 2) + c * 16;
-        }
-    const int n_stages = p.K / 64;
-    auto issue = [&](int st, int part) {
-        __builtin_amdgcn_sched_barrier(0);
-        const uint16_t *mat = (part & 1) == 0 ? p.X : (EPI == 2 && part == 3) ? p.W2 : p.W;
-        const unsigned char *src = (const unsigned char *)mat + (size_t)min(st, n_stages - 1) * 128;
-        unsigned char *dst = smem + (st & 1) * STAGE + part * PART + wave * 2048;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) fc_load_lds16(src + goff[part][i], dst + i * 1024);
+    for (int i = 0; i < XL; ++i) {
+        const int r = 8 * (wave + 4 * i) + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+        xoff[i] = (uint32_t)min(m0 + r, p.m_end - 1) * (uint32_t)(p.K * 2) + c * 16;  // rows past the end: never stored
+    }
+    // part of the hidden dimension this workgroup covers (EPI 3 only: part kpart of p.ksplit)
+    const int all_stages = p.K / 64;
+    const int st0 = EPI == 3 ? (int)((int64_t)at.kpart * all_stages / p.ksplit) : 0;
+    const int n_stages = EPI == 3 ? (int)(((int64_t)at.kpart + 1) * all_stages / p.ksplit) - st0 : all_stages;
+    auto load_w = [&](int st, int slot, int i) {
+        const bool up = EPI == 2 && 8 * (wave + 4 * i) % (16 * NT) >= 8 * NT;  // (whole blocks)
+        const unsigned char *src = (const unsigned char *)(up ? p.W2 : p.W) + (size_t)(st0 + st) * 128;
+        fc_load_lds16<ONCE>(src + woff[i], wring + slot * WBYTES + (wave + 4 * i) * 1024);
     };
-
-    // bias, behind everything else
-    unsigned char *bias_area = smem + PP_LDS;
-    if (EPI == 0 && wave == 0) load_bias(p, bias_area, (p.slot_base + 2 * unit) * 64, 128, p.n_slots * 64, lane);
+    auto load_x = [&](int st, int slot, int i) {
+        const unsigned char *src = (const unsigned char *)p.X + (size_t)(st0 + st) * 128;
+        fc_load_lds16(src + xoff[i], xring + slot * XBYTES + (wave + 4 * i) * 1024);
+    };
 
     // ---- operand fragments
-    uint32_t foff[4];
+    uint32_t foff[2];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) foff[kk] = (uint32_t)(col * 128 + (((2 * kk + hi) ^ ((col >> 1) & 7)) << 4));
-    bf16x8 xf[2][4], wf[2][4];
-    auto read = [&](int st, int part) {
-        const unsigned char *base = smem + (st & 1) * STAGE + part * PART;
-        if ((part & 1) == 0) {
+    for (int h = 0; h < 2; ++h) foff[h] = (uint32_t)(l * 128 + (((4 * h + q) ^ ((l >> 1) & 7)) << 4));
+    bf16x8 xf[2][MT], wf[2][NT];
+    auto read = [&](int h, int wslot, int xslot, int j) {
+        if (j < MT) xf[h][j] = *(const bf16x8 *)(xring + xslot * XBYTES + wm * (MT * 2048) + j * 2048 + foff[h]);
+        else wf[h][j - MT] = *(const bf16x8 *)(wring + wslot * WBYTES + wn * (NT * 2048) + (j - MT) * 2048 + foff[h]);
+    };
+    f32x4 acc[MT][NT];
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) xf[part >> 1][kk] = *(const bf16x8 *)(base + wm * 4096 + foff[kk]);
-        } else {
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk)
+        for (int t = 0; t < NT; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // The multiplies of half h; read_at(j) and load_at(j) go between them, load_at for loads first .. last - 1.
+    auto phase = [&](auto hc, auto first, auto last, auto read_at, auto load_at) {
+        constexpr int H = decltype(hc)::value, L0 = decltype(first)::value, L1 = decltype(last)::value, SPAN = NM * 7 / 8;
+        static_for<0, NM>([&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            static_for<0, NR>([&](auto j) {
+                if constexpr (decltype(j)::value * SPAN / NR == m) {
+                    read_at(decltype(j)::value);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            });
+            static_for<L0, L1>([&](auto j) {
+                if constexpr ((decltype(j)::value - L0) * SPAN / (L1 - L0) + 1 == m) {
+                    load_at(decltype(j)::value);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            });
+            acc[m / NT][m % NT] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[H][m % NT], xf[H][m / NT], acc[m / NT][m % NT], 0, 0, 0);
+            if ((m & 1) == 1) __builtin_amdgcn_sched_barrier(0);
+        });
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    using std::integral_constant;
+    const integral_constant<int, 0> none;
+    const integral_constant<int, 1> half1;
+    const integral_constant<int, XS == 2 ? XL : (BATCH + 1) / 2> mid;
+    const integral_constant<int, BATCH> all;
+    auto no_load = [](int) {};
+
+    // ---- fill the ring in the order of the batches, then the first half of stage 0
 #pragma unroll
-                for (int t = 0; t < 2; ++t) wf[t][kk] = *(const bf16x8 *)(base + wn * 8192 + t * 4096 + foff[kk]);
+    for (int b = -WS; b < 0; ++b) {
+        if (b + XS >= 0 && b + XS < n_stages)
+#pragma unroll
+            for (int i = 0; i < XL; ++i) load_x(b + XS, b + XS, i);
+        if (b + WS < n_stages)
+#pragma unroll
+            for (int i = 0; i < WL; ++i) load_w(b + WS, b + WS, i);
+    }
+    if (n_stages >= WS) fc_wait_vm<AHEAD + BATCH>();
+    else fc_wait_vm<0>();
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    int ws = 0, xs = 0;  // slots of stage s
+#pragma unroll
+    for (int j = 0; j < NR; ++j) read(0, 0, 0, j);
+    fc_wait_lds();
+    __builtin_amdgcn_sched_barrier(0);
+    phase(none, none, none, [&](int j) { read(1, 0, 0, j); }, no_load);
+
+    auto stage = [&](int s, auto tail) {
+        constexpr bool TAIL = decltype(tail)::value;  // the ring drains: loads that there are, by comparison
+        if (!TAIL || s - 1 + WS < n_stages) fc_wait_vm<AHEAD, true>();
+        else fc_wait_vm<0, true>();
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        const int ws1 = ws == WS - 1 ? 0 : ws + 1, xs1 = xs == XS - 1 ? 0 : xs + 1;
+        auto load = [&](int j) {
+            if (j < XL) {
+                if (!TAIL || s + XS < n_stages) load_x(s + XS, xs, j);
+            } else if (!TAIL) {
+                load_w(s + WS, ws, j - XL);
+            }
+        };
+        phase(half1, none, mid, [&](int j) { read(0, ws1, xs1, j); }, load);
+        fc_wait_lds();
+        __builtin_amdgcn_sched_barrier(0);
+        phase(none, mid, all, [&](int j) { read(1, ws1, xs1, j); }, load);
+        ws = ws1;
+        xs = xs1;
+    };
+    int s = 0;
+    for (; s + WS < n_stages; ++s) stage(s, std::false_type());
+    for (; s + 1 < n_stages; ++s) stage(s, std::true_type());
+    fc_wait_vm<0, true>();
+    phase(half1, none, none, [](int) {}, no_load);
+
+    // ---- epilogue; the LDS ring is its staging area, once every wave has left it
+    if constexpr (EPI == 4) {
+        const int hs = (pair0 >> 6) + wn;
+        if (hs < p.slot_base + p.slots_here)  // an odd number of slabs leaves the last pair half empty
+            gemm_epilogue_vocab<MT>(p, acc, hs, m0 + 16 * MT * wm, lane);
+    } else {
+        uint16_t *bias_area = (uint16_t *)(smem + 4 * epi_bytes(NT));
+        __builtin_amdgcn_s_barrier();
+        if (EPI == 0) {
+            if (tid < WROWS) bias_area[tid] = bias;
+            fc_wait_lds();
+            __builtin_amdgcn_s_barrier();
         }
-    };
-    f32x16 acc[2][4];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][t][r] = 0.f;
-    auto mul = [&](int i, int tp) {
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-                acc[i][2 * tp + t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[t][kk], xf[i][kk], acc[i][2 * tp + t], 0, 0, 0);
-    };
-    if (wn == 0) gemm_pp_loop<0>(n_stages, issue, read, mul);
-    else gemm_pp_loop<1>(n_stages, issue, read, mul);
-
-    const int hs = p.slot_base + 2 * unit + wn;
-    if (hs >= p.slot_base + p.slots_here) return;  // an odd number of slabs leaves the last pair half empty
-    if constexpr (EPI == 4) gemm_epilogue_vocab<2>(p, acc, hs, m0 + 64 * wm, lane);
-    else gemm_epilogue<4, 2, EPI, false>(p, acc, smem + wave * epi_bytes(4), (const uint16_t *)bias_area + 64 * wn,
-                                         (const uint16_t *)bias_area + 128 + 64 * wn, hs, 0, 0, 4, m0 + 64 * wm, lane, 0);
+        bias_area += wn * 16 * NT;
+        gemm_epilogue<MT, NT, EPI>(p, acc, smem + wave * epi_bytes(NT), bias_area, bias_area + 8 * NT, pair0 + wn * 8 * NT, pair_end,
+                                   m0 + 16 * MT * wm, lane, at.kpart);
+    }
 }
 
+// Tiles of `pairs` pairs x `rows` window rows; the grid, a multiple of eight, or 0: not a launch.
 template <int EPI>
-hipError_t launch_gemm_pp(GemmArgs a, hipStream_t s)
+unsigned set_tiles(GemmArgs &a, int pairs, int rows)
 {
-    constexpr int LDS = PP_LDS + (EPI == 0 ? BIAS_LDS : 0);
-    static hipError_t attr = hipFuncSetAttribute((const void *)k_gemm_pp<EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-    if (attr != hipSuccess) return attr;
-    a.n_units = (a.slots_here + 1) / 2;
-    a.n_mt = (a.m_end - a.m_base + 255) / 256;
-    if (a.slots_here < 1 || a.n_mt < 1 || a.slot_base < 0 || a.slot_base + a.slots_here > a.n_slots || a.m_base < 0 ||
-        a.m_end > a.M || a.K % 64 != 0)
-        return hipErrorInvalidValue;
-    const int64_t n_tiles = (int64_t)a.n_units * a.n_mt;
-    if (n_tiles > (1 << 30)) return hipErrorInvalidValue;
-    k_gemm_pp<EPI><<<dim3((unsigned)((n_tiles + 7) / 8 * 8)), dim3(512), LDS, s>>>(a);
-    return hipGetLastError();
+    if (a.slots_here < 1 || a.slot_base < 0 || a.slot_base + a.slots_here > a.n_slots || a.m_base < 0 || a.m_end > a.M || a.m_end <= a.m_base ||
+        (EPI == 3 && a.ksplit < 1))
+        return 0;
+    a.n_units = (int)(((int64_t)a.slots_here * 64 + pairs - 1) / pairs);
+    a.n_mt = (a.m_end - a.m_base + rows - 1) / rows;
+    const int64_t n_tiles = (int64_t)a.n_units * a.n_mt * (EPI == 3 ? a.ksplit : 1);
+    return n_tiles > (1 << 30) ? 0 : (unsigned)((n_tiles + 7) / 8 * 8);
 }
 
-template <int KS, int NW, int NSUB, int MW, int NG, int SLOTS, int NL, int EPI = 0>
+template <int MT, int NT, int WN, int WS, int XS, int EPI>
+hipError_t launch_wide(GemmArgs a, hipStream_t s)
+{
+    constexpr int LDS = (WS * 16 * NT * WN + XS * 256) * 128;
+    static_assert(LDS <= 160 * 1024, "LDS ring too large");
+    const unsigned grid = set_tiles<EPI>(a, 8 * NT * WN, 256);
+    if (grid == 0 || a.K % 64 != 0) return hipErrorInvalidValue;
+    auto start = [&](auto once) {
+        constexpr auto kernel = k_gemm_wide<MT, NT, WN, WS, XS, EPI, decltype(once)::value>;
+        static hipError_t attr = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        if (attr != hipSuccess) return attr;
+        kernel<<<dim3(grid), dim3(256), LDS, s>>>(a);
+        return hipGetLastError();
+    };
+    // One tile of rows: its workgroups are the only ones to read their weights.
+    return a.once && a.M <= 256 ? start(std::true_type()) : start(std::false_type());
+}
+
+template <int KS, int NW, int NSUB, int SLOTS, int NL, int EPI>
 hipError_t launch_gemm(GemmArgs a, hipStream_t s)
 {
-    constexpr int XROWS = 32 * MW * (NW / NG);
-    constexpr bool DEALT = NSUB == 5 || NSUB == 3;
-    constexpr int LDS = SLOTS * ((DEALT ? 32 * NSUB : 32 * NSUB * NG) + XROWS) * KS * 2 + (EPI == 0 ? BIAS_LDS : 0);
+    constexpr int XROWS = 32 * NW;
+    constexpr int LDS = SLOTS * (32 * NSUB + XROWS) * KS * 2 + (EPI == 0 ? BIAS_LDS : 0);
     static_assert(LDS <= 160 * 1024, "LDS ring too large");
-    const int slots = a.slots_here;
-    a.n_units = DEALT ? (a.n_slots * 64 + 16 * NSUB - 1) / (16 * NSUB) : NSUB == 4 ? (slots + NG - 1) / NG : 2 * slots;
-    if (DEALT && (a.slot_base != 0 || slots != a.n_slots)) return hipErrorInvalidValue;  // dealt pairs cover every slab
-    a.n_mt = (a.m_end - a.m_base + XROWS - 1) / XROWS;
-    if (slots < 1 || a.n_mt < 1 || a.slot_base < 0 || a.slot_base + slots > a.n_slots || a.m_base < 0 || a.m_end > a.M)
-        return hipErrorInvalidValue;
-    const int64_t n_tiles = (int64_t)a.n_units * a.n_mt * (EPI == 3 ? a.ksplit : 1);
-    if (n_tiles > (1 << 30) || (EPI == 3 && a.ksplit < 1)) return hipErrorInvalidValue;
-    const unsigned grid = (unsigned)((n_tiles + 7) / 8 * 8);
+    const unsigned grid = set_tiles<EPI>(a, 16 * NSUB, XROWS);
+    if (grid == 0 || a.K % KS != 0) return hipErrorInvalidValue;
     auto start = [&](auto rotate, auto once) {
-        constexpr auto kernel = k_proj_gemm<KS, NW, NSUB, MW, NG, SLOTS, NL, EPI, decltype(rotate)::value, decltype(once)::value>;
+        constexpr auto kernel = k_proj_gemm<KS, NW, NSUB, SLOTS, NL, EPI, decltype(rotate)::value, decltype(once)::value>;
         static hipError_t attr = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
         if (attr != hipSuccess) return attr;
         kernel<<<dim3(grid), dim3((NW + NL) * 64), LDS, s>>>(a);
@@ -833,11 +794,9 @@ hipError_t launch_gemm(GemmArgs a, hipStream_t s)
     };
     // One tile of rows: its workgroups are the only ones to read their weights.
     auto with_hint = [&](auto rotate) {
-        if constexpr (XROWS <= 128)
-            if (a.once && a.M <= XROWS) return start(rotate, std::true_type());
-        return start(rotate, std::false_type());
+        return a.once && a.M <= XROWS ? start(rotate, std::true_type()) : start(rotate, std::false_type());
     };
-    if constexpr (XROWS <= 128 && EPI != 3)
+    if constexpr (EPI != 3)
         if (a.n_mt == 1 && a.m_base == 0 && a.K % 2048 == 0 && a.K / KS < 65536) {
             a.rot_step = (uint32_t)(((int64_t)(a.K / KS) << 16) / (a.n_units < 256 ? a.n_units : 256));  // (place * rot_step stays below 2^32)
             return with_hint(std::true_type());
@@ -879,35 +838,35 @@ template <int EPI>
 hipError_t launch_shape(int shape, const GemmArgs &a, hipStream_t s)
 {
     switch (shape) {
-    case 0: return launch_gemm<64, 8, 4, 1, 1, 3, 0, EPI>(a, s);
-    case 1: return launch_gemm<64, 4, 4, 1, 1, 4, 4, EPI>(a, s);
+    case 0: return launch_wide<4, 8, 1, 4, 3, EPI>(a, s);
+    case 1: return launch_gemm<64, 4, 4, 4, 4, EPI>(a, s);
     case 2:
         if constexpr (EPI == 0)
-            if (a.K % 128 == 0) return launch_gemm<128, 4, 2, 1, 1, 3, 4, EPI>(a, s);
-        if constexpr (EPI != 4) return launch_gemm<64, 4, 2, 1, 1, 4, 4, EPI>(a, s);
+            if (a.K % 128 == 0) return launch_gemm<128, 4, 2, 3, 4, EPI>(a, s);
+        if constexpr (EPI != 4) return launch_gemm<64, 4, 2, 4, 4, EPI>(a, s);
         return hipErrorInvalidValue;
     case 3:
         if constexpr (EPI == 3) return hipErrorInvalidValue;
-        else return launch_gemm_pp<EPI>(a, s);
+        else return launch_wide<8, 8, 2, 3, 2, EPI>(a, s);
     case 4:
-        if constexpr (EPI == 0 || EPI == 2) return launch_gemm<64, 8, 5, 2, 2, 3, 0, EPI>(a, s);
+        if constexpr (EPI == 0 || EPI == 2) return launch_wide<8, 5, 2, 3, 3, EPI>(a, s);
         return hipErrorInvalidValue;
     case 5:
-        if constexpr (EPI == 0 || EPI == 2) return launch_gemm<64, 4, 3, 1, 1, 4, 4, EPI>(a, s);
+        if constexpr (EPI == 0 || EPI == 2) return launch_gemm<64, 4, 3, 4, 4, EPI>(a, s);
         return hipErrorInvalidValue;
     case 6:
-        if constexpr (EPI == 0 || EPI == 2) return launch_gemm<64, 2, 5, 1, 1, 4, 4, EPI>(a, s);
+        if constexpr (EPI == 0 || EPI == 2) return launch_gemm<64, 2, 5, 4, 4, EPI>(a, s);
         return hipErrorInvalidValue;
     case 7:
-        if constexpr (EPI == 0 || EPI == 2) return launch_gemm<64, 2, 3, 1, 1, 4, 4, EPI>(a, s);
+        if constexpr (EPI == 0 || EPI == 2) return launch_gemm<64, 2, 3, 4, 4, EPI>(a, s);
         return hipErrorInvalidValue;
     case 8:
-        if constexpr (EPI == 0 || EPI == 2) return launch_gemm<64, 4, 5, 1, 1, 4, 4, EPI>(a, s);
+        if constexpr (EPI == 0 || EPI == 2) return launch_gemm<64, 4, 5, 4, 4, EPI>(a, s);
         return hipErrorInvalidValue;
-    case 9: return launch_gemm<64, 2, 4, 1, 1, 3, 2, EPI>(a, s);
+    case 9: return launch_gemm<64, 2, 4, 3, 2, EPI>(a, s);
     case 10:
         if constexpr (EPI == 4) return hipErrorInvalidValue;
-        else return launch_gemm<64, 2, 2, 1, 1, 4, 4, EPI>(a, s);
+        else return launch_gemm<64, 2, 2, 4, 4, EPI>(a, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -924,7 +883,7 @@ hipError_t launch_shape(int shape, const GemmArgs &a, hipStream_t s)
 // of those padding); 64 rows x 160 weight rows pull 1.4.  Gated W_1 of 18944 outputs at hidden 3584, 64 / 128 rows:
 // 67.5 / 81.6 us, now 50.4 / 58.3 (the weights alone 46 at 5.9 TB/s).
 constexpr int N_SHAPES = 11;
-constexpr double ROUND_US[N_SHAPES] = {1.03, 0.62, 0.39, 1.84, 1.30, 0.54, 0.75, 0.53, 0.95, 0.52, 0.34};
+constexpr double ROUND_US[N_SHAPES] = {0.92, 0.62, 0.39, 1.52, 1.08, 0.54, 0.75, 0.53, 0.95, 0.52, 0.34};
 // The same for up to one round of one row tile of the 64-row shapes (6, 7, 9, 10), where a workgroup's own pull counts and not how many there are:
 // line 0.85 + 0.15 x (gated hidden 3584, 32 rows, us per stage: shape 7 with 134 / 198 tiles 0.40 / 0.435, shape 9 with 100 / 148
 // 0.50 / 0.53, shape 6 with 80 / 119 0.54 / 0.57, shape 10 with 72 / 200 0.30 / 0.32).
