@@ -1197,9 +1197,13 @@ fc_status fc_lm_head_argmax(int32_t dtype, const void *x, const void *w_vocab, i
     hipError_t e;
     const bool knobs = fc_knobs().lin_wide_shape >= 0 || fc_knobs().lin_wgs > 0 || fc_knobs().lin_no_rows;  // they name the kernels
     const int runs = knobs || w.wide.kind == 1 || w.plan.kind == 1 ? 0 : fc_lmhead_lines_parts(dtype, M, K, V, w.parts);
+    const int long_runs = knobs || w.wide.kind == 1 || w.plan.kind != 2 ? 0 : fc_lmhead_runs_parts(dtype, M, K, V, w.parts);
     if (runs > 0) {
         am.parts = runs;
         e = fc_launch_lmhead_lines(x, w_vocab, M, K, V, am, (hipStream_t)stream);
+    } else if (long_runs > 0) {
+        am.parts = long_runs;
+        e = fc_launch_lmhead_runs(x, w_vocab, M, K, V, am, (hipStream_t)stream);
     } else if (w.wide.kind == 1)
         e = fc_launch_linear_wide(w.wide, FC_LIN_VOCAB, x, w_vocab, nullptr, nullptr, M, K, V, nullptr, nullptr,
                                   fc_read_once(2.0 * K * V), (hipStream_t)stream, &am);

@@ -164,6 +164,9 @@ bool fc_linear_lines_cover(int dtype, int mode, int M, int K, int N);
 // The same for a small vocabulary: parts of the arg-max it writes, `parts` at most (0: not for it), and the launch.
 int fc_lmhead_lines_parts(int dtype, int M, int K, int V, int parts);
 hipError_t fc_launch_lmhead_lines(const void *x, const void *w, int M, int K, int V, const FcArgmaxPart &am, hipStream_t s);
+// And for a large one.
+int fc_lmhead_runs_parts(int dtype, int M, int K, int V, int parts);
+hipError_t fc_launch_lmhead_runs(const void *x, const void *w, int M, int K, int V, const FcArgmaxPart &am, hipStream_t s);
 hipError_t fc_launch_linear_lines(int mode, const void *x, const void *w, const void *w2, const void *res, int M, int K, int N,
                                   void *out, bool once, hipStream_t s);
 FcSkinnyPlan fc_plan_skinny(int dtype, int mode, int M, int K, int N);

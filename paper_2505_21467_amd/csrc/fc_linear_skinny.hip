@@ -682,6 +682,188 @@ hipError_t launch_lines(LinArgs a, int runs, hipStream_t s)
     return hipGetLastError();
 }
 
+// -------------------------------------------------------------------------------------------------
+// Large vocabularies, at most 32 rows: a workgroup per compute unit owns an equal run of entries, takes it in passes of up to
+// 256 and keeps (largest, index, sum of exponentials) per row to itself until the end.
+//   * Bound by the weights from HBM.  Four waves only load: each takes every fourth stage of 64 hidden elements, whole lines of
+//     all the pass's rows, into the slot of its own in the ring, so it has to wait for nothing but its own last loads and the loads of
+//     three stages (90 KB) are always on their way, over the end of a pass as well.  The lines carry the non-temporal hint.
+//   * Four waves multiply, 64 entries each; what they have to do takes a quarter of the time the loads take.
+//   * Logits are summed in chains over 512 elements and those: relative error of the confidences against 64 bits @@.
+//   * Where weight rows lie a multiple of 4 KB apart every workgroup starts at a stage of its own.
+// us, whole-row kernel / this one, at 4 / 32 rows: @@
+constexpr int RUN_ENTRIES = 256, RUN_WAVES = 4, RUN_SLOTS = 4;  // entries of a pass, multiplying waves, slots = loading waves
+__host__ __device__ constexpr int run_slot(int MT) { return (RUN_ENTRIES + 16 * MT) * 128; }
+
+template <int MT, bool ONCE>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_vocab_runs(LinArgs p)
+{
+    extern __shared__ __align__(1024) unsigned char lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int first = (int)((int64_t)blockIdx.x * p.N / p.G), R = (int)(((int64_t)blockIdx.x + 1) * p.N / p.G) - first;
+    const int n_pass = (R + RUN_ENTRIES - 1) / RUN_ENTRIES;
+    const int per_pass = ((R + n_pass - 1) / n_pass + 7) & ~7;  // whole blocks of eight rows
+    const int n_st = p.K / 64, total = (R + per_pass - 1) / per_pass * n_st;
+
+    if (wave >= RUN_WAVES) {
+        const int lw = wave - RUN_WAVES, lr = lane >> 3;
+        const int rot = p.K % 2048 == 0 ? (int)((int64_t)blockIdx.x * n_st / p.G) : 0;
+        unsigned char *slot = lds + lw * run_slot(MT);
+        int pass = 0, st = lw;  // of this wave's next stage
+        auto issue = [&]() {
+            for (; st >= n_st; st -= n_st) ++pass;
+            const int at = st + rot < n_st ? st + rot : st + rot - n_st;
+            const int rows = min(per_pass, R - pass * per_pass);
+            const unsigned char *w = (const unsigned char *)(p.W + (size_t)(first + pass * per_pass) * p.K) + (size_t)at * 128;
+            const unsigned char *x = (const unsigned char *)p.X + (size_t)at * 128;
+#pragma unroll
+            for (int i = 0; i < 2 * MT; ++i) {
+                const int r = 8 * i + lr;
+                fc_load_lds16(x + (uint32_t)min(r, p.M - 1) * (uint32_t)(2 * p.K) + (((lane & 7) ^ (r >> 1 & 7)) << 4), slot + RUN_ENTRIES * 128 + i * 1024);
+            }
+#pragma unroll 4
+            for (int i = 0; 8 * i < rows; ++i) {
+                const int r = 8 * i + lr;
+                fc_load_lds16<ONCE>(w + (uint32_t)min(r, rows - 1) * (uint32_t)(2 * p.K) + (((lane & 7) ^ (r >> 1 & 7)) << 4), slot + i * 1024);
+            }
+            st += RUN_SLOTS;
+        };
+        // Barrier `it` (it = 0 .. total - 2): stage it + 1 is complete and every multiplying wave has left stage it.
+        if (lw < total) issue();
+        if (lw == 0) fc_wait_vm<0>();
+        __builtin_amdgcn_s_barrier();  // stage 0 is complete
+        for (int it = 0; it + 1 < total; ++it) {
+            if ((it + 1) % RUN_SLOTS == lw) fc_wait_vm<0>();
+            __builtin_amdgcn_s_barrier();
+            if (it % RUN_SLOTS == lw && it + RUN_SLOTS < total) issue();
+        }
+        return;
+    }
+
+    const int l = lane & 15, q = lane >> 4;
+    float run_mx[MT], run_sm[MT];
+    int run_arg[MT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+        run_mx[i] = -INFINITY;
+        run_sm[i] = 0.f;
+        run_arg[i] = 0x7fffffff;
+    }
+    f32x4 acc[MT][4], sum[MT][4];
+    auto fold = [&]() {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    sum[i][t][r] += acc[i][t][r];
+                    acc[i][t][r] = 0.f;
+                }
+    };
+    __builtin_amdgcn_s_barrier();  // stage 0 is complete
+    int it = 0;
+    for (int done = 0; done < R; done += per_pass) {
+        const int rows = min(per_pass, R - done) - 64 * wave;  // of this wave, if positive
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[i][t] = sum[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int st = 0; st < n_st; ++st, ++it) {
+            const unsigned char *slot = lds + (it % RUN_SLOTS) * run_slot(MT);
+            bf16x8 xf[2][MT], wf[2][4];
+            if (rows > 0) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int off = l * 128 + (((4 * h + q) ^ (l >> 1 & 7)) << 4);
+#pragma unroll
+                    for (int i = 0; i < MT; ++i) xf[h][i] = *(const bf16x8 *)(slot + RUN_ENTRIES * 128 + i * 2048 + off);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) wf[h][t] = *(const bf16x8 *)(slot + wave * 8192 + t * 2048 + off);
+                }
+            }
+            fc_wait_lds();  // lgkmcnt(0): the slot may be overwritten
+            __builtin_amdgcn_sched_barrier(0);
+            if (it + 1 < total) __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            if (rows <= 0) continue;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[h][t], xf[h][i], acc[i][t], 0, 0, 0);
+            if (st % 8 == 7) fold();
+        }
+        if (rows <= 0) continue;
+        fold();
+        // lane (l, q): window row 16 i + l, entries 16 t + 4 q + r of the wave, ascending; the largest first, then the sum against it
+        const int base = first + done + 64 * wave + 4 * q;
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            float mx = -INFINITY, sm = 0.f;
+            int arg = base;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const bool more = 16 * t + 4 * q + r < rows && sum[i][t][r] > mx;
+                    mx = more ? sum[i][t][r] : mx;
+                    arg = more ? base + 16 * t + r : arg;
+                }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                float e[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    e[r] = 16 * t + 4 * q + r < rows ? __builtin_amdgcn_exp2f((sum[i][t][r] - mx) * 1.4426950408889634f) : 0.f;
+                sm += (e[0] + e[1]) + (e[2] + e[3]);
+            }
+            if (4 * q < rows) fc_argmax_merge(run_mx[i], run_arg[i], run_sm[i], mx, arg, sm);
+        }
+    }
+    // over the lanes of a row, then over the waves
+    FcArgmax *state = (FcArgmax *)lds;  // [multiplying wave][16 MT]; every slot has been left and no load is on its way
+    __builtin_amdgcn_s_barrier();
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+#pragma unroll
+        for (int off = 16; off < 64; off <<= 1) {
+            const float mx2 = __shfl_xor(run_mx[i], off, 64), sm2 = __shfl_xor(run_sm[i], off, 64);
+            const int arg2 = __shfl_xor(run_arg[i], off, 64);
+            fc_argmax_merge(run_mx[i], run_arg[i], run_sm[i], mx2, arg2, sm2);
+        }
+        if (q == 0) state[wave * 16 * MT + 16 * i + l] = FcArgmax{run_mx[i], run_arg[i], run_sm[i]};
+    }
+    fc_wait_lds();
+    __builtin_amdgcn_s_barrier();
+    if (tid < 16 * MT && tid < p.M) {
+        FcArgmax a = state[tid];
+#pragma unroll
+        for (int w = 1; w < RUN_WAVES; ++w) {
+            const FcArgmax b = state[w * 16 * MT + tid];
+            fc_argmax_merge(a.mx, a.arg, a.sm, b.mx, b.arg, b.sm);
+        }
+        p.am.at(blockIdx.x, tid) = a;
+    }
+}
+
+template <int MT>
+hipError_t launch_vocab_runs(const LinArgs &a, hipStream_t s)
+{
+    constexpr int LDS = RUN_SLOTS * run_slot(MT);
+    static_assert(LDS <= 160 * 1024 && RUN_SLOTS == 4 && RUN_WAVES == 4, "512 threads");
+    auto start = [&](auto once) {
+        constexpr auto kernel = k_vocab_runs<MT, decltype(once)::value>;
+        static hipError_t attr = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        if (attr != hipSuccess) return attr;
+        kernel<<<dim3((unsigned)a.G), dim3(512), LDS, s>>>(a);
+        return hipGetLastError();
+    };
+    return a.once ? start(std::true_type()) : start(std::false_type());
+}
+
 // Tiles of 16 mt window rows and runs of outputs, one workgroup per compute unit; runs of at least four outputs: with fewer
 // the window rows are fetched for too little.
 struct LinesShape {
@@ -924,6 +1106,29 @@ hipError_t fc_launch_lmhead_lines(const void *x, const void *w, int M, int K, in
     a.K = K;
     a.N = V;
     return M <= 16 ? launch_lines_vocab<1>(a, am.parts, s) : launch_lines_vocab<2>(a, am.parts, s);
+}
+
+// Parts of the arg-max the kernel for large vocabularies writes, `parts` at most (0: not for it), and the launch.
+int fc_lmhead_runs_parts(int dtype, int M, int K, int V, int parts)
+{
+    const int runs = parts < 256 ? parts : 256;
+    return dtype == FC_BF16 && M >= 1 && M <= 32 && K >= 512 && K % 64 == 0 && runs == 256 && V >= 64 * 256 ? runs : 0;
+}
+
+hipError_t fc_launch_lmhead_runs(const void *x, const void *w, int M, int K, int V, const FcArgmaxPart &am, hipStream_t s)
+{
+    if (fc_lmhead_runs_parts(FC_BF16, M, K, V, am.parts) != am.parts) return hipErrorInvalidValue;
+    LinArgs a;
+    memset(&a, 0, sizeof a);
+    a.X = (const uint16_t *)x;
+    a.W = (const uint16_t *)w;
+    a.am = am;
+    a.M = M;
+    a.K = K;
+    a.N = V;
+    a.G = am.parts;
+    a.once = fc_read_once(2.0 * K * V);
+    return M <= 16 ? launch_vocab_runs<1>(a, s) : launch_vocab_runs<2>(a, s);
 }
 
 bool fc_linear_lines_cover(int dtype, int mode, int M, int K, int N)
