@@ -569,15 +569,6 @@ __global__ __launch_bounds__((NW + NL) * 64) __attribute__((amdgpu_waves_per_eu(
 // 256 x 256 x 64 stage takes 2460 clocks of which 2048 are multiplies; the clock is what the power limit leaves, 1.8 GHz.
 // Weights from HBM: a compute unit has some 64 KB of loads under way, taken in order, so window rows that are in L2 wait behind
 // weights that are not (256 x 160: loads alone 0.97 us a stage, weights alone 0.75, with the non-temporal hint both 0.86).
-template <int I, int N, typename F>
-__device__ __forceinline__ void static_for(F f)
-{
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>());
-        static_for<I + 1, N>(f);
-    }
-}
-
 template <int MT, int NT, int WN, int WS, int XS, int EPI, bool ONCE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_gemm_wide(GemmArgs p)
 {
@@ -650,26 +641,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // The multiplies of half h; read_at(j) and load_at(j) go between them, load_at for loads first .. last - 1.
+    // The multiplies of half h; read_at(j) and load_at(j) go between them, load_at for loads first .. last - 1.  (Loops with conditions
+    // that unrolling decides: as a recursion of templates over the same places the file took 16 minutes to compile.)
     auto phase = [&](auto hc, auto first, auto last, auto read_at, auto load_at) {
         constexpr int H = decltype(hc)::value, L0 = decltype(first)::value, L1 = decltype(last)::value, SPAN = NM * 7 / 8;
-        static_for<0, NM>([&](auto mc) {
-            constexpr int m = decltype(mc)::value;
-            static_for<0, NR>([&](auto j) {
-                if constexpr (decltype(j)::value * SPAN / NR == m) {
-                    read_at(decltype(j)::value);
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+#pragma unroll
+            for (int j = 0; j < NR; ++j)
+                if (j * SPAN / NR == m) {
+                    read_at(j);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-            });
-            static_for<L0, L1>([&](auto j) {
-                if constexpr ((decltype(j)::value - L0) * SPAN / (L1 - L0) + 1 == m) {
-                    load_at(decltype(j)::value);
+#pragma unroll
+            for (int j = L0; j < L1; ++j)
+                if ((j - L0) * SPAN / (L1 - L0) + 1 == m) {
+                    load_at(j);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-            });
             acc[m / NT][m % NT] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[H][m % NT], xf[H][m / NT], acc[m / NT][m % NT], 0, 0, 0);
             if ((m & 1) == 1) __builtin_amdgcn_sched_barrier(0);
-        });
+        }
         __builtin_amdgcn_sched_barrier(0);
     };
     using std::integral_constant;
