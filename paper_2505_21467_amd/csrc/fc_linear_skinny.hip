@@ -816,8 +816,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             for (int t = 0; t < 4; ++t) {
                 float e[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    e[r] = 16 * t + 4 * q + r < rows ? __builtin_amdgcn_exp2f((sum[i][t][r] - mx) * 1.4426950408889634f) : 0.f;
+                for (int r = 0; r < 4; ++r) {
+                    const float part = __builtin_amdgcn_exp2f((sum[i][t][r] - mx) * 1.4426950408889634f);
+                    // the largest adds 1 whatever it is (an infinite logit: inf - inf)
+                    e[r] = 16 * t + 4 * q + r >= rows ? 0.f : base + 16 * t + r == arg ? 1.f : part;
+                }
                 sm += (e[0] + e[1]) + (e[2] + e[3]);
             }
             if (4 * q < rows) fc_argmax_merge(run_mx[i], run_arg[i], run_sm[i], mx, arg, sm);

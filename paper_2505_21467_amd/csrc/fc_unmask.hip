@@ -54,7 +54,7 @@ __global__ __launch_bounds__(RED_ROWS * RED_GROUPS) void k_lmhead_reduce(FcArgma
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (v[u].sm != 0.f) sum += (double)v[u].sm * expf(v[u].mx - top);
+            if (v[u].sm != 0.f) sum += v[u].arg == at ? (double)v[u].sm : (double)v[u].sm * expf(v[u].mx - top);  // (an infinite logit: inf - inf)
         fc_argmax_merge(mx, arg, sm, top, at, (float)sum);
     }
     merge_lanes();

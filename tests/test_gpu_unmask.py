@@ -113,6 +113,23 @@ def test_lm_head_exact_ties_go_to_the_smaller_index():
     assert np.all(tok2 == 77) and np.allclose(conf2, np.tile(rc, 5), rtol=2e-3)
 
 
+@pytest.mark.parametrize("dtype,M,K,V", [
+    ("f32", 5, 64, 300), ("bf16", 16, 512, 1000), ("bf16", 9, 1024, 20480), ("bf16", 17, 3584, 16391), ("bf16", 3, 512, 66001),
+])
+def test_infinite_logit_has_confidence_one_and_is_filled(dtype, M, K, V):
+    x, w = inputs.normal(24, "x", (M, K), 1.0, dtype), inputs.normal(24, "w", (V, K), 0.03, dtype)
+    x[:, 0] = w[:, 0] = 0.0
+    x[0, 0] = 1e38
+    for place in (0, V // 2 + 1, V - 1):
+        w[:, 0] = 0.0
+        w[place, 0] = 1e38
+        tok, conf = _lm_head(dtype, x, w)
+        assert tok[0] == place and conf[0] == 1.0 and np.all((conf[1:] > 0.0) & (conf[1:] < 1.0))
+        start, L = 3, M + 5
+        filled, pos_next, count = _gpu_select(tok[None], conf[None], None, start, 1, V, np.full((1, L), V, np.int32))
+        assert filled[0, start] == place and count[0] == M - 1 and np.array_equal(pos_next[0, :M - 1], start + np.arange(1, M))
+
+
 def _random_case(rng, B, A, L, mask, frac_masked=0.6, pad=0.15):
     pos = np.stack([np.sort(rng.choice(L, A, replace=False)) for _ in range(B)]).astype(np.int32)
     pos[rng.random((B, A)) < pad] = -1
