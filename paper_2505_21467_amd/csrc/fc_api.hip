@@ -52,16 +52,8 @@ fc_status check_config(const fc_config *c)
 
 int spad_of(const fc_config &c) { return (c.max_seq + FC_VTILE - 1) / FC_VTILE * FC_VTILE; }
 
-// Bytes of a pass over all layers: projection weights, keys and values, and the layers' other weights (d_ff; 0: none of them).
-double pass_bytes(const fc_cache *cache, int32_t d_ff)
-{
-    const fc_config &c = cache->cfg;
-    const double d = c.hidden, e = (double)c.n_q_heads * c.head_dim, kv = (double)c.n_kv_heads * c.head_dim;
-    const double rest = d_ff > 0 ? d * e + 3.0 * d * d_ff : 0.0;
-    return c.n_layers * ((e + 2.0 * kv) * d + 2.0 * (double)cache->layer_elems + rest) * (double)cache->esize;
-}
-
-FcGeom geom_of(const fc_cache *cache, int32_t d_ff = 0)
+// keys: of each layer that the pass around the call reads, as far as the call can know (`once` is a hint)
+FcGeom geom_of(const fc_cache *cache, int32_t d_ff = 0, int32_t keys = 0)
 {
     const fc_config &c = cache->cfg;
     FcGeom G;
@@ -73,7 +65,7 @@ FcGeom geom_of(const fc_cache *cache, int32_t d_ff = 0)
     G.max_seq = c.max_seq;
     G.spad = cache->spad;
     G.g = c.n_q_heads / c.n_kv_heads;
-    G.once = fc_read_once(pass_bytes(cache, d_ff));
+    G.once = fc_read_once(fc_pass_bytes(c, d_ff, keys));
     G.scale = c.softmax_scale > 0.f ? c.softmax_scale : (float)(1.0 / sqrt((double)c.head_dim));
     G.log_base = log((double)c.rope_base);
     return G;
@@ -682,8 +674,8 @@ fc_status fc_window(int32_t step, int32_t P, int32_t G, int32_t Bk, int32_t step
     return FC_OK;
 }
 
-// d_ff: of the layer the call is a part of (0: projections and attention alone)
-static fc_status project_scatter(fc_cache *cache, int32_t layer, int32_t d_ff, const void *x, const void *w_qkv, const void *b_qkv,
+// d_ff: of the layer the call is a part of (0: projections and attention alone); keys: that its attention reads (0: not known)
+static fc_status project_scatter(fc_cache *cache, int32_t layer, int32_t d_ff, int32_t keys, const void *x, const void *w_qkv, const void *b_qkv,
                                  int32_t win_start, int32_t A, const int32_t *pos, void *q_out, void *stream)
 {
     fc_status st = check_cache_layer(cache, layer);
@@ -695,7 +687,8 @@ static fc_status project_scatter(fc_cache *cache, int32_t layer, int32_t d_ff, c
     if (!pos && (win_start < 0 || win_start > cache->cfg.max_seq - A))
         return fail(FC_ERR_BOUNDS, "window [%d, %d+%d) outside the cache of %d rows", win_start, win_start,
                     A, cache->cfg.max_seq);
-    const FcGeom G = geom_of(cache, d_ff);
+    // Not told, the keys up to the window's end count; where rows are listed on the device, all there is room for.
+    const FcGeom G = geom_of(cache, d_ff, keys > 0 ? keys : pos ? cache->cfg.max_seq : win_start + A);
     void *kl = layer_ptr(cache, cache->k, layer), *vl = layer_ptr(cache, cache->v, layer);
     // wide windows: tiled GEMM; short windows: weight-streaming kernels; small problems, other shapes and fp32: tile kernel
     hipError_t e;
@@ -717,7 +710,7 @@ fc_status fc_qkv_project_scatter(fc_cache *cache, int32_t layer, const void *x, 
                                  const void *b_qkv, int32_t win_start, int32_t A, const int32_t *pos,
                                  void *q_out, void *stream)
 {
-    return project_scatter(cache, layer, 0, x, w_qkv, b_qkv, win_start, A, pos, q_out, stream);
+    return project_scatter(cache, layer, 0, 0, x, w_qkv, b_qkv, win_start, A, pos, q_out, stream);
 }
 
 size_t fc_workspace_bytes(const fc_config *cfg, int32_t max_rows)
@@ -732,7 +725,7 @@ static fc_status run_attention(fc_cache *cache, int32_t layer, int32_t d_ff, con
     const size_t bytes = fc_plan_workspace(cache->cfg, plan);
     if (bytes > space)  // (not reached: the planner keeps within the space, and the plan of a tuning knob is required space)
         return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", bytes, space);
-    const FcGeom G = geom_of(cache, d_ff);
+    const FcGeom G = geom_of(cache, d_ff, kv_len);
     void *kl = layer_ptr(cache, cache->k, layer), *vl = layer_ptr(cache, cache->v, layer);
     hipError_t e = plan.kind != 0
                        ? fc_launch_attention_mfma(G, plan, q, kl, vl, pos, A, kv_len, out, workspace,
@@ -852,7 +845,7 @@ fc_status fc_refresh(fc_cache *cache, int32_t layer, const void *x, const void *
         const size_t need = attn_required(cache->cfg, R, kv_len), given = workspace ? workspace_bytes : 0;
         if (given < need) return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, given);
     }
-    st = fc_qkv_project_scatter(cache, layer, x, w_qkv, b_qkv, start, R, nullptr, q_scratch, stream);
+    st = project_scatter(cache, layer, 0, out ? kv_len : 0, x, w_qkv, b_qkv, start, R, nullptr, q_scratch, stream);
     if (st != FC_OK || !out) return st;
     return fc_active_attention(cache, layer, q_scratch, R, kv_len, nullptr, out, workspace, workspace_bytes,
                                stream);
@@ -1016,7 +1009,11 @@ static fc_status linear_common(int32_t dtype, int mode, const void *x, const voi
     return e == hipSuccess ? FC_OK : hip_fail(e, "linear launch");
 }
 
-// A layer called by itself: its matrix comes round again behind those of the other layers, of which there are at least a few.
+// A layer called by itself: its matrix comes round again behind those of the other layers, and the call takes it that there are four
+// such matrices at least.  us without and with the hint, one matrix again and again / two in turn / four in turn: gated 3584 x 8192
+// (117 MB), 32 rows 18.7 and 19.4 / 18.6 and 20.2 / 22.7 and 20.8, 128 rows 21.6 and 28.5 / 25.8 and 29.1 / 30.8 and 29.5; gated
+// 3584 x 9472, 256 rows 43.4 and 49.9 / 47.1 and 49.0 / 51.4 and 49.2; 18944 x 3584 (136 MB), 32 rows 27.6 and 28.3 / 28.2 and 28.2 /
+// 31.0 and 28.4.  (A program that goes over one such matrix only is the one that loses.)
 static bool layer_read_once(double K, double N) { return fc_read_once(4.0 * 2.0 * K * N); }
 
 fc_status fc_linear_residual(int32_t dtype, const void *x, const void *w, const void *residual, int32_t M,
@@ -1118,9 +1115,9 @@ fc_status fc_full_layer_step(fc_cache *cache, int32_t layer, const fc_layer_weig
     const size_t attn_bytes = workspace_bytes - w.attn;
     void *lin = w.lin_bytes ? ws + w.lin : nullptr, *attn = attn_bytes ? ws + w.attn : nullptr;
 
-    const bool once = fc_read_once(pass_bytes(cache, wt->d_ff));
+    const bool once = fc_read_once(fc_pass_bytes(c, wt->d_ff, kv_len));
     st = fc_rmsnorm(c.dtype, x, wt->norm1, wt->eps, M, d, h, stream);
-    if (st == FC_OK) st = project_scatter(cache, layer, wt->d_ff, h, wt->w_qkv, wt->b_qkv, win_start, A, pos, q, stream);
+    if (st == FC_OK) st = project_scatter(cache, layer, wt->d_ff, kv_len, h, wt->w_qkv, wt->b_qkv, win_start, A, pos, q, stream);
     if (st == FC_OK) st = active_attention(cache, layer, wt->d_ff, q, A, kv_len, pos, o, attn, attn_bytes, stream);
     if (st == FC_OK)
         st = linear_common(c.dtype, FC_LIN_RESIDUAL, o, wt->w_out, nullptr, x, M, E, d, x2, lin, w.lin_bytes, once, stream);

@@ -32,7 +32,7 @@ def test_hint_keeps_the_bits(B, d, Hq, Hkv, F, A, L):
          "w_down": rnd((d, F), 0.02)}
     wt = fc.make_layer_weights(d_ff=F, eps=1e-6, **t)
     x, k, v = rnd((B, A, d)), rnd((B, Hkv, L, Dh)), rnd((B, Hkv, L, Dh))
-    layer_bytes = 2 * sum(t[n].numel() for n in ("w_qkv", "w_out", "w_gate", "w_up", "w_down")) + 4 * B * Hkv * ((S + 63) // 64 * 64) * Dh
+    layer_bytes = 2 * sum(t[n].numel() for n in ("w_qkv", "w_out", "w_gate", "w_up", "w_down")) + 4 * B * Hkv * S * Dh
     many = (256 << 20) // layer_bytes + 1
     assert many > 1  # (alone: within the memory-side cache)
     got = []
