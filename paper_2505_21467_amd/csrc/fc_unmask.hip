@@ -16,10 +16,8 @@ namespace {
 
 // Merge of the vocabulary parts: a workgroup takes a group of eight rows, whose (part, row) triples lie in one piece, 128
 // parts at a time.  (One row per workgroup and triples in three [part][row] arrays touched a line per value: 256 parts
-// x 32 rows 4.6 us, 1188 x 256 11.1; now 4.3 and 6.6.)  U: parts per thread, all in flight at once, the largest of them first
-// and then the sum against it, whose exponentials do not wait for one another.
+// x 32 rows 4.6 us, 1188 x 256 11.1; now 4.3 and 6.6.)
 constexpr int RED_ROWS = 8, RED_GROUPS = 128, RED_WAVES = RED_ROWS * RED_GROUPS / 64;
-template <int U>
 __global__ __launch_bounds__(RED_ROWS * RED_GROUPS) void k_lmhead_reduce(FcArgmaxPart am, int M, int32_t *tok, float *conf)
 {
     __shared__ float s_mx[RED_WAVES][RED_ROWS], s_sm[RED_WAVES][RED_ROWS];
@@ -36,26 +34,14 @@ __global__ __launch_bounds__(RED_ROWS * RED_GROUPS) void k_lmhead_reduce(FcArgma
             fc_argmax_merge(mx, arg, sm, mx2, arg2, sm2);
         }
     };
+    constexpr int U = 4;  // parts per thread in flight at a time
     for (int base = 0; base < parts; base += RED_GROUPS * U) {
         FcArgmax v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) v[u] = am.at(min(base + RED_GROUPS * u + group, parts - 1), mm);
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (base + RED_GROUPS * u + group >= parts) v[u] = FcArgmax{-INFINITY, 0x7fffffff, 0.f};
-        float top = v[0].mx;
-        double sum = 0.0;
-        int at = v[0].arg;
-#pragma unroll
-        for (int u = 1; u < U; ++u) {
-            const bool before = v[u].mx > top || (v[u].mx == top && v[u].arg < at);
-            top = before ? v[u].mx : top;
-            at = before ? v[u].arg : at;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (v[u].sm != 0.f) sum += v[u].arg == at ? (double)v[u].sm : (double)v[u].sm * expf(v[u].mx - top);  // (an infinite logit: inf - inf)
-        fc_argmax_merge(mx, arg, sm, top, at, (float)sum);
+            if (base + RED_GROUPS * u + group < parts) fc_argmax_merge(mx, arg, sm, v[u].mx, v[u].arg, v[u].sm);
     }
     merge_lanes();
     if (lane < RED_ROWS) {
@@ -619,9 +605,7 @@ hipError_t fc_launch_gather_rows(const void *table, int64_t R, int row_bytes, co
 hipError_t fc_launch_lmhead_reduce(const FcArgmaxPart &am, int M, int32_t *tok, float *conf,
                                    hipStream_t s)
 {
-    const dim3 grid((unsigned)((M + RED_ROWS - 1) / RED_ROWS)), block(RED_ROWS * RED_GROUPS);
-    if (am.parts <= 2 * RED_GROUPS) k_lmhead_reduce<2><<<grid, block, 0, s>>>(am, M, tok, conf);
-    else k_lmhead_reduce<10><<<grid, block, 0, s>>>(am, M, tok, conf);
+    k_lmhead_reduce<<<dim3((unsigned)((M + RED_ROWS - 1) / RED_ROWS)), dim3(RED_ROWS * RED_GROUPS), 0, s>>>(am, M, tok, conf);
     return hipGetLastError();
 }
 
