@@ -113,6 +113,25 @@ def test_lm_head_exact_ties_go_to_the_smaller_index():
     assert np.all(tok2 == 77) and np.allclose(conf2, np.tile(rc, 5), rtol=2e-3)
 
 
+def test_confidences_of_a_large_vocabulary_keep_their_precision():
+    # Rms relative error of 6 x 32 confidences against 64 bits, hidden 512: 1.1e-7 where the hidden dimension is summed in eight
+    # chains and those (here and in the whole-row kernel), 2.4e-7 in one chain.  (The largest logits are about 3, where fp32 lies 2.4e-7
+    # apart: 0.7e-7 rms for the last addition alone.)
+    M, K, V = 32, 512, 30001
+    sq = 0.0
+    for seed in range(6):
+        gen = torch.Generator(device=DEV).manual_seed(seed)
+        w = torch.empty((V, K), dtype=torch.bfloat16, device=DEV).normal_(0, 0.02, generator=gen)
+        lean = torch.randint(0, V, (M,), generator=gen, device=DEV)
+        force = torch.empty((M, 1), device=DEV).uniform_(3, 12, generator=gen)
+        x = (torch.empty((M, K), device=DEV).normal_(generator=gen) + force * w[lean].float()).to(torch.bfloat16)
+        tok, conf = _lm_head("bf16", x, w)
+        z = x.double() @ w.double().T
+        ref = (1.0 / torch.exp(z - z.amax(1, keepdim=True)).sum(1)).cpu().numpy()
+        sq += np.mean(((conf - ref) / ref) ** 2)
+    assert np.sqrt(sq / 6) < 1.8e-7
+
+
 @pytest.mark.parametrize("dtype,M,K,V", [
     ("f32", 5, 64, 300), ("bf16", 16, 512, 1000), ("bf16", 9, 1024, 20480), ("bf16", 17, 3584, 16391), ("bf16", 3, 512, 66001),
 ])
