@@ -687,13 +687,19 @@ hipError_t launch_lines(LinArgs a, int runs, hipStream_t s)
 // 256 and keeps (largest, index, sum of exponentials) per row to itself until the end.
 //   * Bound by the weights from HBM.  Four waves only load: each takes every fourth stage of 64 hidden elements, whole lines of
 //     all the pass's rows, into the slot of its own in the ring, so it has to wait for nothing but its own last loads and the loads of
-//     three stages (90 KB) are always on their way, over the end of a pass as well.  The lines carry the non-temporal hint.
+//     three stages (90 KB in a full pass, less where the run is short) are always on their way, over the end of a pass as well.  The
+//     lines carry the non-temporal hint where the matrix exceeds the memory-side cache.
 //   * Four waves multiply, 64 entries each; what they have to do takes a quarter of the time the loads take.
-//   * Logits are summed in eight chains along the hidden dimension and those.  Relative error (rms) of the confidences against 64 bits, whole-row
-//     kernel / this one, 32 rows: hidden 512, 152064 entries 1.18e-7 / 1.20e-7 (chains over 512 elements: 2.58e-7), hidden 3584 4.26e-7 / 4.28e-7, 40001
-//     entries 3.32e-7 / 3.34e-7, hidden 4096 4.45e-7 / 4.00e-7; with expf in place of the hardware's exponential of a rounded product the same.
-//   * Where weight rows lie a multiple of 4 KB apart every workgroup starts at a stage of its own.
-// us, whole-row kernel / this one, at 4 / 32 rows: @@
+//   * Logits are summed in eight chains along the hidden dimension, and those by twos.  Relative error (rms) of the confidences against 64
+//     bits, whole-row kernel / this one, 32 rows: 512 x 152064 1.18e-7 / 1.11e-7 (chains over 512 elements 2.58e-7), 3584 x 152064 4.26e-7 / 3.35e-7,
+//     3584 x 40001 3.32e-7 / 2.90e-7, 4096 x 152064 4.45e-7 / 3.68e-7; with expf in place of the hardware's exponential of a rounded product the same.
+//   * Where weight rows lie a multiple of 4 KB apart, workgroups in step would all ask for the same 128 bytes of all those rows, which share
+//     a few memory channels.  They take the chains there in four orders, c ^ mix: the pairs, and the pairs of pairs, are the same ones, so a
+//     weight row gives the same bits in every workgroup and equal logits go to the smaller index.  Hidden 4096, 32 rows, us in one order / four
+//     (/ every workgroup from a stage of its own on, where equal logits went either way): 32001 entries 65.3 / 53.4 (/ 50.1), 50304 81.0 / 68.6
+//     (/ 68.8), 100001 139.2 / 124.2 (/ 129.9), 152064 192.5 / 190.8 (/ 189.9).
+// us with the merge, whole-row kernel / this one: 3584 x 152064, 4 rows 185.4 / 162.8 (6.7 TB/s), 32 rows 187.9 / 164.9; 3584 x 40001, 32 rows
+// 59.0 / 51.4; 4096 x 152064, 32 rows 210.5 / 190.8; 512 x 152064, 32 rows 70.0 / 36.8.
 constexpr int RUN_ENTRIES = 256, RUN_WAVES = 4, RUN_SLOTS = 4;  // entries of a pass, multiplying waves, slots = loading waves
 __host__ __device__ constexpr int run_slot(int MT) { return (RUN_ENTRIES + 16 * MT) * 128; }
 
@@ -706,16 +712,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int first = (int)((int64_t)blockIdx.x * p.N / p.G), R = (int)(((int64_t)blockIdx.x + 1) * p.N / p.G) - first;
     const int n_pass = (R + RUN_ENTRIES - 1) / RUN_ENTRIES;
     const int per_pass = ((R + n_pass - 1) / n_pass + 7) & ~7;  // whole blocks of eight rows
-    const int n_st = p.K / 64, chain = (n_st + 7) / 8, total = (R + per_pass - 1) / per_pass * n_st;
+    const int n_st = p.K / 64, chain = n_st / 8, total = (R + per_pass - 1) / per_pass * n_st;
 
     if (wave >= RUN_WAVES) {
         const int lw = wave - RUN_WAVES, lr = lane >> 3;
-        const int rot = p.K % 2048 == 0 ? (int)((int64_t)blockIdx.x * n_st / p.G) : 0;
+        const int mix = p.K % 2048 == 0 ? (blockIdx.x >> 3 & 3) * 2 : 0;
         unsigned char *slot = lds + lw * run_slot(MT);
         int pass = 0, st = lw;  // of this wave's next stage
         auto issue = [&]() {
             for (; st >= n_st; st -= n_st) ++pass;
-            const int at = st + rot < n_st ? st + rot : st + rot - n_st;
+            const int at = mix ? ((st / chain) ^ mix) * chain + st % chain : st;
             const int rows = min(per_pass, R - pass * per_pass);
             const unsigned char *w = (const unsigned char *)(p.W + (size_t)(first + pass * per_pass) * p.K) + (size_t)at * 128;
             const unsigned char *x = (const unsigned char *)p.X + (size_t)at * 128;
@@ -752,57 +758,80 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         run_sm[i] = 0.f;
         run_arg[i] = 0x7fffffff;
     }
-    f32x4 acc[MT][4], sum[MT][4];
-    auto fold = [&]() {
+    f32x4 acc[MT][4];
+    auto add = [&](f32x4 (&kept)[MT][4]) {
 #pragma unroll
         for (int i = 0; i < MT; ++i)
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    sum[i][t][r] += acc[i][t][r];
-                    acc[i][t][r] = 0.f;
-                }
+                for (int r = 0; r < 4; ++r) acc[i][t][r] += kept[i][t][r];
     };
-    __builtin_amdgcn_s_barrier();  // stage 0 is complete
-    int it = 0;
-    for (int done = 0; done < R; done += per_pass) {
-        const int rows = min(per_pass, R - done) - 64 * wave;  // of this wave, if positive
+    auto keep = [&](f32x4 (&kept)[MT][4]) {
 #pragma unroll
         for (int i = 0; i < MT; ++i)
 #pragma unroll
-            for (int t = 0; t < 4; ++t) acc[i][t] = sum[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int st = 0, left = chain; st < n_st; ++st, ++it) {
+            for (int t = 0; t < 4; ++t) {
+                kept[i][t] = acc[i][t];
+                asm volatile("" : "+v"(kept[i][t]));  // summed here and not where it is used, or all eight chains wait in registers
+            }
+    };
+    __builtin_amdgcn_s_barrier();  // stage 0 is complete
+    int it = 0;
+    auto one_chain = [&]() {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int end = it + chain;
+        do {
             const unsigned char *slot = lds + (it % RUN_SLOTS) * run_slot(MT);
             bf16x8 xf[2][MT], wf[2][4];
-            if (rows > 0) {
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int off = l * 128 + (((4 * h + q) ^ (l >> 1 & 7)) << 4);
+            for (int h = 0; h < 2; ++h) {
+                const int off = l * 128 + (((4 * h + q) ^ (l >> 1 & 7)) << 4);
 #pragma unroll
-                    for (int i = 0; i < MT; ++i) xf[h][i] = *(const bf16x8 *)(slot + RUN_ENTRIES * 128 + i * 2048 + off);
+                for (int i = 0; i < MT; ++i) xf[h][i] = *(const bf16x8 *)(slot + RUN_ENTRIES * 128 + i * 2048 + off);
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) wf[h][t] = *(const bf16x8 *)(slot + wave * 8192 + t * 2048 + off);
-                }
+                for (int t = 0; t < 4; ++t) wf[h][t] = *(const bf16x8 *)(slot + wave * 8192 + t * 2048 + off);
             }
             fc_wait_lds();  // lgkmcnt(0): the slot may be overwritten
             __builtin_amdgcn_sched_barrier(0);
             if (it + 1 < total) __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
-            if (rows <= 0) continue;
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
                 for (int i = 0; i < MT; ++i)
 #pragma unroll
                     for (int t = 0; t < 4; ++t) acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[h][t], xf[h][i], acc[i][t], 0, 0, 0);
-            if (--left == 0) {
-                fold();
-                left = chain;
-            }
+        } while (++it < end);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    for (int done = 0; done < R; done += per_pass) {
+        const int rows = min(per_pass, R - done) - 64 * wave;  // of this wave, if positive
+        if (rows <= 0) {
+            for (int end = it + n_st; it < end; ++it)
+                if (it + 1 < total) __builtin_amdgcn_s_barrier();
+            continue;
         }
-        if (rows <= 0) continue;
-        fold();
+        f32x4 one[MT][4], two[MT][4], four[MT][4];  // sums of so many chains
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            one_chain();
+            if ((c & 1) == 0) {
+                keep(one);
+                continue;
+            }
+            add(one);
+            if ((c & 2) == 0) {
+                keep(two);
+                continue;
+            }
+            add(two);
+            if ((c & 4) == 0) keep(four);
+            else add(four);
+        }
         // lane (l, q): window row 16 i + l, entries 16 t + 4 q + r of the wave, ascending; the largest first, then the sum against it
         const int base = first + done + 64 * wave + 4 * q;
 #pragma unroll
@@ -813,8 +842,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             for (int t = 0; t < 4; ++t)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const bool more = 16 * t + 4 * q + r < rows && sum[i][t][r] > mx;
-                    mx = more ? sum[i][t][r] : mx;
+                    const bool more = 16 * t + 4 * q + r < rows && acc[i][t][r] > mx;
+                    mx = more ? acc[i][t][r] : mx;
                     arg = more ? base + 16 * t + r : arg;
                 }
 #pragma unroll
@@ -822,7 +851,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 float e[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float part = __builtin_amdgcn_exp2f((sum[i][t][r] - mx) * 1.4426950408889634f);
+                    const float part = __builtin_amdgcn_exp2f((acc[i][t][r] - mx) * 1.4426950408889634f);
                     // the largest adds 1 whatever it is (an infinite logit: inf - inf)
                     e[r] = 16 * t + 4 * q + r >= rows ? 0.f : base + 16 * t + r == arg ? 1.f : part;
                 }
@@ -1120,7 +1149,7 @@ hipError_t fc_launch_lmhead_lines(const void *x, const void *w, int M, int K, in
 int fc_lmhead_runs_parts(int dtype, int M, int K, int V, int parts)
 {
     const int runs = parts < 256 ? parts : 256;
-    return dtype == FC_BF16 && M >= 1 && M <= 32 && K >= 512 && K % 64 == 0 && runs == 256 && V >= 64 * 256 ? runs : 0;
+    return dtype == FC_BF16 && M >= 1 && M <= 32 && K >= 512 && K % 512 == 0 && runs == 256 && V >= 64 * 256 ? runs : 0;
 }
 
 hipError_t fc_launch_lmhead_runs(const void *x, const void *w, int M, int K, int V, const FcArgmaxPart &am, hipStream_t s)
