@@ -1145,11 +1145,18 @@ hipError_t fc_launch_lmhead_lines(const void *x, const void *w, int M, int K, in
     return M <= 16 ? launch_lines_vocab<1>(a, am.parts, s) : launch_lines_vocab<2>(a, am.parts, s);
 }
 
-// Parts of the arg-max the kernel for large vocabularies writes, `parts` at most (0: not for it), and the launch.
+// Parts of the arg-max the kernel for large vocabularies writes, `parts` at most (0: not for it), and the launch.  From runs of 90
+// entries on (hidden 512: 64, where it takes over from k_linear_lines; hidden 4096, whose rows share memory channels: 120); a shorter run has
+// too few bytes on their way.  us, whole-row kernel / this one, weights from HBM, 4 / 32 rows: hidden 3584, 16385 entries 28.0 and 29.5 / 32.9 and
+// 35.3, 20001 34.4 and 36.3 / 36.0 and 38.6, 22017 35.7 and 37.7 / 38.4 and 41.2, 23040 38.3 and 40.0 / 36.9 and 39.0, 26497 41.3 and 43.3 / 39.9
+// and 41.4, 32771 47.4 and 48.7 / 47.9 and 48.4, 50304 68.7 and 70.7 / 59.9 and 61.0; hidden 4096, 23041 42.1 and 44.2 / 43.8 and 44.5, 26497 44.2
+// and 46.2 / 46.3 and 47.0, 29001 49.8 and 52.1 / 51.2 and 52.4, 32001 55.1 and 57.9 / 51.9 and 53.4, 32771 52.9 and 53.3 / 52.8 and 53.3, 40001 66.1
+// and 69.5 / 57.6 and 58.3, 65537 (257 entries, two passes) 92.3 and 96.2 / 95.9 and 98.9, 131072 183.3 and 187.7 / 160.5 and 161.1; hidden 512,
+// 16391 13.3 and 14.6 / 12.2 and 13.7, 32771 19.9 and 21.5 / 14.7 and 16.3.
 int fc_lmhead_runs_parts(int dtype, int M, int K, int V, int parts)
 {
     const int runs = parts < 256 ? parts : 256;
-    return dtype == FC_BF16 && M >= 1 && M <= 32 && K >= 512 && K % 512 == 0 && runs == 256 && V >= 64 * 256 ? runs : 0;
+    return dtype == FC_BF16 && M >= 1 && M <= 32 && K >= 512 && K % 512 == 0 && runs == 256 && V >= (K <= 512 ? 64 : K % 2048 == 0 ? 120 : 90) * 256 ? runs : 0;
 }
 
 hipError_t fc_launch_lmhead_runs(const void *x, const void *w, int M, int K, int V, const FcArgmaxPart &am, hipStream_t s)

@@ -644,7 +644,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     // The multiplies of half h; read_at(j) and load_at(j) go between them, load_at for loads first .. last - 1.  (Loops with conditions
     // that unrolling decides: as a recursion of templates over the same places the file took 16 minutes to compile.)
     auto phase = [&](auto hc, auto first, auto last, auto read_at, auto load_at) {
-        constexpr int H = decltype(hc)::value, L0 = decltype(first)::value, L1 = decltype(last)::value, SPAN = NM * 7 / 8;
+        constexpr int H = decltype(hc)::value, L0 = decltype(first)::value, L1 = decltype(last)::value, SPAN = NM * 7 / 8, LOADS = L1 > L0 ? L1 - L0 : 1;
 #pragma unroll
         for (int m = 0; m < NM; ++m) {
 #pragma unroll
@@ -655,7 +655,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                 }
 #pragma unroll
             for (int j = L0; j < L1; ++j)
-                if ((j - L0) * SPAN / (L1 - L0) + 1 == m) {
+                if ((j - L0) * SPAN / LOADS + 1 == m) {
                     load_at(j);
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -984,7 +984,7 @@ hipError_t launch_pieces(GemmArgs a, hipStream_t s)
 }
 
 // At most 32 rows of a gated layer or a vocabulary: the tiled GEMM streams the weights a little faster than the whole-row
-// kernel (6.3 TB/s instead of 6) where its tiles fill one round of workgroups (vocabulary: or two), and more slowly otherwise.  Both sides measured, weights from HBM (us at 16 / 32 rows, tiled GEMM first):
+// kernel (6.3 TB/s instead of 6) where its tiles fill one round of workgroups, and more slowly otherwise.  Both sides measured, weights from HBM (us at 16 / 32 rows, tiled GEMM first):
 //   gated, hidden 3584: 6400 outputs (200 half slabs) 20.3 and 21.7 / 20.8 and 23.5, 8192 (256) 22.1 and 24.0 / 22.8 and 25.4,
 //   9472 (198 tiles of 48 dealt pairs) 26.3 and 29.1 / 27.4 and 31.0, 12288 (256) 32.3 and 33.2 / 32.7 and 34.7, 13312 (208 slabs)
 //   35.5 and 36.5 / 36.5 and 38.1, 16384 (256) 41.2 and 42.5 / 41.8 and 44.2, 18944 (237 tiles of 80 dealt pairs) 47.5 and 49.7 /
@@ -992,14 +992,16 @@ hipError_t launch_pieces(GemmArgs a, hipStream_t s)
 //   gated, hidden 4096: 6400 23.2 and 24.1 / 23.8 and 26.2, 8192 24.2 and 33.6 / 24.3 and 33.8, 11008 (230 tiles of 48) 32.1 and 36.5 /
 //   32.4 and 38.5, 12288 35.5 and 37.9 / 35.8 and 40.2, 14336 41.0 and 42.7 / 41.7 and 45.4, 16384 47.3 and 46.1 / 47.6 and 49.1, 18944
 //   52.8 and 56.0 / 53.7 and 58.7, 22016 71.3 and 68.7 / 73.7 and 70.7;
-//   vocabulary, hidden 3584: 16000 35.0 and 30.1 / 35.3 and 31.6, 32000 (250 slabs) 44.7 and 48.2 / 45.0 and 50.3, 50304 70.5 and
-//   69.3 / 72.6 and 71.2, 65536 (512) 84.0 and 85.2 / 84.0 and 86.4, 152064 188.1 and 184.6 / 189.2 and 186.9; hidden 4096: 16000 38.5
-//   and 34.1 / 39.1 and 36.5, 32000 49.0 and 56.8 / 48.7 and 59.9, 65536 92.2 and 93.2 / 92.4 and 94.3, 152064 215 and 203 / 216 and 210
-//   (two rounds there gain 2 % and would ask for a larger workspace than the whole-row kernel: left to it).
-bool wide_beats_rows(int mode, int M, int K, int64_t slabs)
+//   vocabulary, against the runs of entries (k_vocab_runs; hidden 4096 up to 30719 entries: whole rows), with the merge, us at 4 / 32 rows: hidden
+//   3584, 26624 (208 slabs) 40.4 and 39.0 / 41.4 and 41.0, 29056 42.3 and 43.6 / 43.0 and 45.7, 32000 (250) 45.2 and 46.2 / 45.6 and 47.0, 32768 45.9 and
+//   46.6 / 46.4 and 47.7; hidden 4096, 26624 42.0 and 44.2 / 42.7 and 46.2, 29056 44.7 and 49.8 / 45.1 and 52.1, 32000 49.3 and 51.9 / 49.7 and 53.4, 32768 49.7
+//   and 52.8 / 49.7 and 53.3.
+//   Two rounds of tiles (hidden 3584, 59392 .. 65536 entries) are within 2 % of them either way, the runs ahead at most sizes (59392 69.1
+//   and 68.4 / 71.4 and 69.6, 62080 71.4 and 71.7 / 73.1 and 73.1, 65536 75.1 and 74.5 / 75.8 and 75.9), and so left to them.
+bool wide_beats_rows(int mode, int M, int64_t slabs)
 {
     auto in = [](int64_t n, int64_t lo) { return n >= lo && n <= 256; };
-    if (mode == FC_LIN_VOCAB) return in(slabs, 208) || (K % 4096 != 0 && in(slabs - 256, 208));
+    if (mode == FC_LIN_VOCAB) return in(slabs, 208);
     const int64_t pairs48 = tiles_of(7, slabs, M);
     return in(tiles_of(10, slabs, M), 200) || in(tiles_of(9, slabs, M), 208) || in(pairs48, 192) ||
            (slabs > 256 && in(tiles_of(6, slabs, M), 208));
@@ -1028,7 +1030,7 @@ FcWidePlan fc_plan_wide(int dtype, int mode, int M, int K, int N)
         const bool knob = fc_knobs().lin_wide_shape >= 6;
         if (!knob && (fc_knobs().lin_wgs > 0 || fc_knobs().lin_no_rows)) return p;  // tuning knobs of the streaming kernels
         if (!knob && !(mode == FC_LIN_RESIDUAL ? rows.kind == 1 && M > 16 && (double)K * N >= 60e6
-                                               : rows.kind == 2 && K >= 2048 && wide_beats_rows(mode, M, K, N / per_slab)))
+                                               : rows.kind == 2 && K >= 2048 && wide_beats_rows(mode, M, N / per_slab)))
             return p;
     }
     p.kind = 1;

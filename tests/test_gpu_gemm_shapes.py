@@ -106,7 +106,7 @@ def test_start_along_the_hidden_dimension_beyond_one_round(shape, M, K, units, k
 
 @pytest.mark.parametrize("V", [26624, 26496])
 def test_few_rows_vocabulary_on_both_sides_of_the_line(V):
-    """208 slabs: tiled GEMM; 207: whole-row kernel."""
+    """208 slabs: tiled GEMM; 207: runs of entries."""
     print("[case] vocabulary", V, flush=True)
     x, w = inputs.normal(23, "x", (5, 3584), 1.0, "bf16"), inputs.normal(23, "w", (V, 3584), 0.03, "bf16")
     _check_lm_head("bf16", x, w, "vocabulary of %d" % V)
@@ -186,7 +186,7 @@ def test_layers_of_few_outputs(M, K, N, gated):
     (1, 512, 2), (15, 2560, 1721), (17, 3584, 33), (32, 512, 4097), (9, 1536, 8193), (32, 512, 16385), (31, 3584, 4095), (5, 4096, 300), (2, 512, 16384),
 ])
 def test_small_vocabulary(M, K, V):
-    """Runs of one to 64 entries, one to four weight tiles, fewer entries than parts; 16385: one too many, whole-row kernel."""
+    """Runs of one to 64 entries, one to four weight tiles, fewer entries than parts; 16385: one too many, runs in passes."""
     print("[case] vocabulary", M, K, V, flush=True)
     x, w = inputs.normal(25, "x", (M, K), 1.0, "bf16"), inputs.normal(25, "w", (V, K), 0.03, "bf16")
     _check_lm_head("bf16", x, w, "small vocabulary of %d" % V)

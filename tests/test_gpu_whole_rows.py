@@ -30,7 +30,7 @@ def test_many_items(M, K, N, gated):
 
 @pytest.mark.parametrize("M,K,V", [
     (20, 3584, 1001), (32, 512, 15999), (1, 4096, 9), (16, 512, 8193),            # up to 16384 entries: streamed through LDS
-    (3, 512, 17239), (2, 4096, 16418), (17, 4096, 16461), (9, 3584, 16386), (32, 3584, 16391),  # more: whole rows
+    (3, 512, 17239), (2, 4096, 16418), (17, 4096, 16461), (9, 3584, 16386), (32, 3584, 16391),  # more: whole rows at hidden 3584 and 4096
 ])
 def test_odd_vocabulary(M, K, V):
     print("[case] odd vocabulary", M, K, V, flush=True)
