@@ -18,6 +18,9 @@ DEV = "cuda:0"
     (1, 3584, 4, 4, 8192, 17, 2500),    # attention in ranges of keys, one workgroup each; hidden dimension of W_2 in parts
     (4, 1024, 24, 24, 10240, 32, 3000),  # 128-row tiles
     (3, 4096, 40, 8, 4096, 33, 1000),  # 99 rows, rotated starts
+    (8, 2048, 16, 4, 18944, 32, 90),   # 256 rows: tiles of 256, gated by dealt pairs
+    (5, 3584, 28, 4, 8192, 33, 60),    # 165 rows
+    (1, 4096, 32, 8, 6144, 200, 70),   # 200 rows of one sequence
 ])
 def test_hint_keeps_the_bits(B, d, Hq, Hkv, F, A, L):
     print("[case] read once", B, d, Hq, Hkv, F, A, L, flush=True)
