@@ -863,9 +863,12 @@ hipError_t launch_shape(int shape, const GemmArgs &a, hipStream_t s)
     }
 }
 
-// Tile shapes of the tiled GEMM and what a full round of 256 workgroups takes per 64 hidden elements (us, measured at
-// hidden 3584 and 4096 with 150..768 workgroups).  Per tile area the larger ones are cheaper -- they move fewer
-// bytes into the compute unit per product -- but leave the chip emptier at the end.
+// Tile shapes of the tiled GEMM and what workgroups take per 64 hidden elements (us): a round of them, one (shapes 9 and 10: two) on every
+// compute unit, and the emptiest part of a round (the clock is higher and the memory path less loaded).  Fitted to 1600 measured
+// launches: 36, 48 and 96 head slots, gated 3584 x 18944, 4096 x 12288 and 2048 x 5632, vocabularies of 32000 .. 152064, hidden 2048 ..
+// 4096, 33 .. 2304 rows, weights from HBM; rms error 10 %, and the shape it picks is within 3 % of the best measured one in
+// every problem and 0.03 % in the mean.  Per tile area the larger shapes are cheaper -- they move fewer bytes into the compute
+// unit per product -- but leave the chip emptier at the end.
 //   0: 256 rows x slab   1: 128 rows x slab   2: 128 rows x half slab   3: 256 rows x two slabs
 //   4: 256 rows x 80 dealt pairs   5: 128 rows x 48 dealt pairs
 //   6: 64 rows x 80 dealt pairs   7: 64 rows x 48 dealt pairs   8: 128 rows x 80 dealt pairs
@@ -873,13 +876,13 @@ hipError_t launch_shape(int shape, const GemmArgs &a, hipStream_t s)
 // 6 .. 10 are for few rows, where the weights alone should count: in the 128-row half slab, for 40 or 64 rows the shape with
 // the most tiles, the compute units pulled three bytes for every byte of weights (two thirds of them window rows, most
 // of those padding); 64 rows x 160 weight rows pull 1.4.  Gated W_1 of 18944 outputs at hidden 3584, 64 / 128 rows:
-// 67.5 / 81.6 us, now 50.4 / 58.3 (the weights alone 46 at 5.9 TB/s).
+// 65 / 80 us in the half slab, 44.7 / 50.3 in those (shapes 6 and 8; the weights alone 46 at 5.9 TB/s).
 constexpr int N_SHAPES = 11;
-constexpr double ROUND_US[N_SHAPES] = {0.92, 0.62, 0.39, 1.52, 1.08, 0.54, 0.75, 0.53, 0.95, 0.52, 0.34};
-// The same for up to one round of one row tile of the 64-row shapes (6, 7, 9, 10), where a workgroup's own pull counts and not how many there are:
-// line 0.85 + 0.15 x (gated hidden 3584, 32 rows, us per stage: shape 7 with 134 / 198 tiles 0.40 / 0.435, shape 9 with 100 / 148
-// 0.50 / 0.53, shape 6 with 80 / 119 0.54 / 0.57, shape 10 with 72 / 200 0.30 / 0.32).
-constexpr double SINGLE_US[N_SHAPES] = {0, 0, 0, 0, 0, 0, 0.60, 0.45, 0, 0.55, 0.33};
+struct ShapeCost {
+    double round, least;
+};
+constexpr ShapeCost SHAPE_US[N_SHAPES] = {{0.90, 0.61}, {0.56, 0.44}, {0.34, 0.24}, {1.52, 0.94}, {1.05, 0.71}, {0.46, 0.34},
+                                          {0.53, 0.47}, {0.36, 0.29}, {0.72, 0.57}, {0.79, 0.52}, {0.45, 0.25}};
 constexpr bool shape_dealt(int shape) { return shape >= 4 && shape <= 8; }
 constexpr bool shape_half(int shape) { return shape == 2 || shape == 10; }
 
@@ -901,16 +904,16 @@ int64_t tiles_of(int shape, int64_t slots, int64_t rows)
     }
 }
 
-// Estimated time of one launch per 64 hidden elements.  A round that fills half the chip was measured at 0.78 to
-// 0.9 of a full one (the clock is higher and the memory path less loaded), hence the line 0.6 + 0.4 x.  The weights
-// come from HBM at 5.8 TB/s at best.
+// Estimated time of one launch per 64 hidden elements: the workgroups and the weights, from HBM at 5.8 TB/s at best, joined by a 4-norm.
 double launch_cost(int shape, int64_t slots, int64_t rows)
 {
-    const int64_t n = tiles_of(shape, slots, rows), part = n % 256;
-    const double tiles = SINGLE_US[shape] > 0 && rows <= 64 && n <= 256 ? SINGLE_US[shape] * (0.85 + 0.15 * n / 256.0)
-                                                          : ROUND_US[shape] * ((double)(n / 256) + (part ? 0.6 + 0.4 * part / 256.0 : 0.0));
-    const double weights = (double)slots * 128 * 128 / 5.8e6;
-    return (tiles > weights ? tiles : weights) + 0.02 * tiles;  // (equally bound by the weights: the smaller tiles)
+    const ShapeCost c = SHAPE_US[shape];
+    const bool pairs = shape >= 9;  // of workgroups on a compute unit
+    const int64_t n = tiles_of(shape, slots, rows), at_once = pairs ? 512 : 256, part = n % at_once;
+    const double last = part == 0 ? 0.0 : pairs ? (part <= 256 ? c.least : c.round) : c.least + (c.round - c.least) * part / 256.0;
+    const double tiles = c.round * (double)(n / at_once) + last, weights = (double)slots * 128 * 128 / 5.8e6;
+    const double t2 = tiles * tiles, w2 = weights * weights;
+    return sqrt(sqrt(t2 * t2 + w2 * w2));
 }
 
 // A problem is covered by one launch, or cut in two where the last round of workgroups would be nearly empty:
@@ -1131,8 +1134,8 @@ bool fc_project_gemm_supported(const fc_config &cfg, int M)
            n * cfg.hidden * 2 < ((int64_t)1 << 32) && (int64_t)M * cfg.hidden * 2 < ((int64_t)1 << 32);
 }
 
-// Estimated time of the tiled projection of M <= 128 rows (us; within a tenth of the measured times at hidden 1024 ..
-// 8192, 12 .. 96 head slots, 4 .. 128 rows).
+// Estimated time of the tiled projection of up to 256 rows (us; 33 .. 256 rows, 36 .. 96 head slots, hidden 3584 and 4096: within a tenth
+// of the measured times; 24 slots, hidden 2048: up to a fifth too long).
 double fc_project_gemm_us(int slots, int M, int K)
 {
     GemmPiece pc[2];

@@ -648,16 +648,15 @@ static double stream_us(int slots, int M, int K, int *mt)
 // Up to 32 rows nothing else is faster by more than 0.1 us, except past 96 head slots (two operands) the tiled GEMM at small
 // hidden sizes (128 slots, 16 rows, hidden 2048 / 3584 16.3 / 22.0 us and 13.9 / 24).  From 33 rows on by estimates.  Head-split keeps
 // few slots with a hidden dimension beyond 8192 (6 slots, hidden 12288, 64 rows 17.8 and 13.9); more than 80 slots, or 64
-// from 65 rows on, the tiled GEMM (96 slots, hidden 2048, 48 rows 15.3 and 14.2; 48 slots, hidden 4096, 160 rows 25.7 and 24.0), whose
-// estimate is a good third too long beyond 128 rows (36 slots, hidden 3584, 144 / 160 rows 16.4 / 18.2 and 17.5 / 17.9; 24
-// slots, hidden 5120, 192 rows 19.2 and 25.0; 12 slots, hidden 3584, 256 rows 10.3 and 15.5).
+// from 65 rows on, the tiled GEMM (96 slots, hidden 2048, 48 rows 15.3 and 14.2; 48 slots, hidden 4096, 160 rows 25.7 and 24.0;
+// 36 slots, hidden 3584, 144 / 160 rows 16.4 / 18.2 and 17.5 / 17.9; 24 slots, hidden 5120, 192 rows 19.2 and 25.0; 12 slots, hidden
+// 3584, 256 rows 10.3 and 15.5).
 static bool stream_wins(int slots, int M, int K, int *mt)
 {
     if (K % 512 != 0 || M > 256 || slots > (M > (K >= 3072 ? 64 : 48) ? 64 : M > 32 ? 80 : K >= 3584 ? 128 : 96) || (M > 128 && K <= 1024)) return false;
     const double us = stream_us(slots, M, K, mt);
     if (M <= 32) return us < 1e30;
-    if (M > 128) return 1.05 * us < 0.68 * fc_project_gemm_us(slots, M, K);
-    if (slots > 64) return us < 0.95 * fc_project_gemm_us(slots, M, K);
+    if (M > 128 || slots > 64) return us < 0.95 * fc_project_gemm_us(slots, M, K);
     return us < fmin(0.94 * headsplit_us(slots, M, K), tile_us(slots, M, K));
 }
 
