@@ -921,7 +921,8 @@ hipError_t launch_lines_mt(int mode, const LinArgs &a, hipStream_t s)
 {
     const LinesShape sh = lines_shape(a.N, a.M, MT);
     if (mode == FC_LIN_GATE_UP) return sh.run <= 16 ? launch_lines<MT, 1, FC_LIN_GATE_UP>(a, sh.runs, s) : launch_lines<MT, 2, FC_LIN_GATE_UP>(a, sh.runs, s);
-    if (sh.run <= 16) return launch_lines<MT, 1, FC_LIN_RESIDUAL>(a, sh.runs, s);
+    if constexpr (MT < 4)  // (lines_tile takes four row tiles for longer runs only)
+        if (sh.run <= 16) return launch_lines<MT, 1, FC_LIN_RESIDUAL>(a, sh.runs, s);
     if constexpr (MT == 1) return launch_lines<MT, 2, FC_LIN_RESIDUAL>(a, sh.runs, s);  // (256 runs for one row tile: 32 outputs at most)
     else return sh.run <= 32 ? launch_lines<MT, 2, FC_LIN_RESIDUAL>(a, sh.runs, s) : launch_lines<MT, 4, FC_LIN_RESIDUAL>(a, sh.runs, s);
 }

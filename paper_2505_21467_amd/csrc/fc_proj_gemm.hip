@@ -788,7 +788,8 @@ hipError_t launch_gemm(GemmArgs a, hipStream_t s)
     auto with_hint = [&](auto rotate) {
         return a.once && a.M <= XROWS ? start(rotate, std::true_type()) : start(rotate, std::false_type());
     };
-    if constexpr (EPI != 3)
+    // (the 128-row half slab of the projection is here for a hidden size that is no multiple of 128)
+    if constexpr (EPI != 3 && !(EPI == 0 && NW == 4 && NSUB == 2 && KS == 64))
         if (a.n_mt == 1 && a.m_base == 0 && a.K % 2048 == 0 && a.K / KS < 65536) {
             a.rot_step = (uint32_t)(((int64_t)(a.K / KS) << 16) / (a.n_units < 256 ? a.n_units : 256));  // (place * rot_step stays below 2^32)
             return with_hint(std::true_type());
