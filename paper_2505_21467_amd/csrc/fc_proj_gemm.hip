@@ -406,20 +406,18 @@ __global__ __launch_bounds__((NW + NL) * 64) __attribute__((amdgpu_waves_per_eu(
         }
         // Rows of W that lie a multiple of 4 KB apart: workgroup `unit` starts unit / n_units of the way along the hidden
         // dimension and goes round.  In step, all workgroups ask for the same 128 bytes of all those rows, and these share a few
-        // memory channels.  One row tile of up to 128 rows, us without and with: gated 4096 x 12288, 64 / 128 rows 47.1 and
-        // 35.8 / 49.0 and 41.3; 4096 x 14336 53.2 and 41.7 / 55.9 and 47.9; 2048 x 16384, 48 rows 34.0 and 26.0; 6144 x 16384 90 and 70;
-        // 8192 x 8192 60 and 45; vocabulary 4096 x 32000, 64 rows 64.6 and 49.6; projection, 96 slots, hidden 4096, 64 rows 27.3
-        // and 24.9.  At other distances it gives nothing or costs (hidden 5120 34.6 and 35.6, 7168 44.1 and 45.7, 1024 15.0 and
-        // 15.3), and so it does with more row tiles, whose window rows then come from L2 at two places at a time (256 rows of
-        // gated 4096 x 12288 66.9 and 70.3), and with the last rows of a problem, behind the launch that has just read the
-        // weights (300 rows of the same 102.8 and 107.0).
+        // memory channels.  One row tile of up to 128 rows, us without and with: gated 4096 x 12288, 64 / 128 rows 40.3 and 32.7 /
+        // 44.4 and 39.7; 4096 x 14336 50.0 and 41.9 / 52.4 and 46.7; 2048 x 16384, 48 rows 28.0 and 23.2; 6144 x 16384 78 and 69; 8192 x 8192,
+        // 64 rows 51.8 and 45.1; vocabulary 4096 x 32000, 64 rows 60.4 and 51.0; projection, 96 slots, hidden 4096, 64 rows 27.3 and 24.9.
+        // At other distances it gives nothing or costs (hidden 5120 34.6 and 35.6, 7168 44.1 and 45.7, 1024 15.0 and 15.3), and so it
+        // does with more row tiles, whose window rows then come from L2 at two places at a time (256 rows of gated 4096 x
+        // 12288 66.9 and 70.3), and with the last rows of a problem, behind the launch that has just read the weights (300 rows of
+        // the same 102.8 and 107.0).
         // More than one round of workgroups: by the place among the 256 that run together, 32 on each XCD.  (By unit / n_units
-        // those together cover a fifth of the hidden dimension at 1188 units.)  Vocabularies at hidden 4096, us without, by the
-        // unit, by the place: 64 rows, 33024 entries (258 units) 86.2, 72.8, 72.6; 50304 86.6, 82.1, 81.9; 65536 110.5, 92.5, 92.4; 98304 144.1,
-        // 140.8, 138.7; 152064 219.5, 217.2, 216.2; 196608 278.0, 270.0, 269.5; 96 rows, 65536 125.6, 100.7, 95.9; 106496 194.6, 177.9, 177.8.
-        // From four rounds on the workgroups drift apart by themselves and it is a few per cent either way: 96 rows,
-        // 128256 189.6, 196.3, 193.5 (the largest loss; 131072 192.3, 196.1, 197.4), 152064 234.0, 232.8, 231.4, 163840 255.4, 254.2, 249.9;
-        // 64 rows at hidden 2048, 131072 114.9, 96.1, 95.2; 96 rows at hidden 8192, 131072 377.0, 376.2, 380.2, 147456 445.4, 450.8, 456.0.
+        // those together cover a fifth of the hidden dimension at 1188 units; 96 rows, vocabulary of 65536 4.7 us slower.)  Vocabularies, us
+        // without and with: hidden 4096, 64 rows, 50304 entries 81.2 and 76.2; 65536 101.9 and 83.6; 152064 198.3 and 195.5; 96 rows, 50304 96.0
+        // and 87.0; 65536 120.9 and 95.4; 128 rows, 152064 247.9 and 243.4; hidden 2048, 64 rows, 131072 104.2 and 86.7; hidden 8192, 32000 108.5
+        // and 83.3.  From four rounds on the workgroups drift apart by themselves and it is a few per cent either way.
         const int per_round = min(p.n_units, 256);
         const int place = (int)(blockIdx.x & 7) * per_round / 8 + (int)(blockIdx.x >> 3 & 31);
         const int rot = ROTATE ? (int)(((uint32_t)place * p.rot_step) >> 16) : 0;
@@ -864,12 +862,13 @@ hipError_t launch_shape(int shape, const GemmArgs &a, hipStream_t s)
     }
 }
 
-// Tile shapes of the tiled GEMM and what workgroups take per 64 hidden elements (us): a round of them, one (shapes 9 and 10: two) on every
-// compute unit, and the emptiest part of a round (the clock is higher and the memory path less loaded).  Fitted to 1600 measured
-// launches: 36, 48 and 96 head slots, gated 3584 x 18944, 4096 x 12288 and 2048 x 5632, vocabularies of 32000 .. 152064, hidden 2048 ..
-// 4096, 33 .. 2304 rows, weights from HBM; rms error 10 %, and the shape it picks is within 3 % of the best measured one in
-// every problem and 0.03 % in the mean.  Per tile area the larger shapes are cheaper -- they move fewer bytes into the compute
-// unit per product -- but leave the chip emptier at the end.
+// Tile shapes of the tiled GEMM and what workgroups take per 64 hidden elements (us): the first round of them, one on every compute
+// unit, nearly empty and full, a further round, and the share of one that its emptiest part takes.  One row tile, whose weights come from
+// HBM, and several, which share them by way of L2, have figures of their own.  Fitted to 6000 measured launches, 917 problems: 24 .. 96
+// head slots, gated layers of 2048 .. 22016 outputs, vocabularies of 32000 .. 152064, plain layers of 8192 .. 18944 outputs, hidden 1024 ..
+// 8192, 8 .. 2304 rows, weights from HBM; rms error 8 %, and the shape it picks is 0.1 % slower than the best measured one in the
+// mean, more than 4 % in three problems; the same on problems left out of the fit.  Per tile area the larger shapes are cheaper -- they
+// move fewer bytes into the compute unit per product -- but leave the chip emptier at the end.
 //   0: 256 rows x slab   1: 128 rows x slab   2: 128 rows x half slab   3: 256 rows x two slabs
 //   4: 256 rows x 80 dealt pairs   5: 128 rows x 48 dealt pairs
 //   6: 64 rows x 80 dealt pairs   7: 64 rows x 48 dealt pairs   8: 128 rows x 80 dealt pairs
@@ -880,10 +879,15 @@ hipError_t launch_shape(int shape, const GemmArgs &a, hipStream_t s)
 // 65 / 80 us in the half slab, 44.7 / 50.3 in those (shapes 6 and 8; the weights alone 46 at 5.9 TB/s).
 constexpr int N_SHAPES = 11;
 struct ShapeCost {
-    double round, least;
+    double least, first, further, start;
 };
-constexpr ShapeCost SHAPE_US[N_SHAPES] = {{0.90, 0.61}, {0.56, 0.44}, {0.34, 0.24}, {1.52, 0.94}, {1.05, 0.71}, {0.46, 0.34},
-                                          {0.53, 0.47}, {0.36, 0.29}, {0.72, 0.57}, {0.79, 0.52}, {0.45, 0.25}};
+constexpr ShapeCost SHAPE_US[2][N_SHAPES] = {  // one row tile, several
+    {{0.60, 0.87, 0.80, 0.75}, {0.41, 0.52, 0.66, 0.95}, {0.24, 0.36, 0.38, 0.87}, {0.85, 1.34, 1.36, 0.79},
+     {0.63, 1.01, 1.04, 0.80}, {0.36, 0.45, 0.48, 0.95}, {0.47, 0.49, 0.67, 0.96}, {0.31, 0.31, 0.39, 1.00},
+     {0.58, 0.58, 0.79, 0.87}, {0.47, 0.47, 0.45, 0.93}, {0.21, 0.24, 0.25, 0.99}},
+    {{0.58, 0.82, 0.90, 0.59}, {0.50, 0.53, 0.58, 0.76}, {0.25, 0.34, 0.37, 0.79}, {1.07, 1.35, 1.52, 0.79},
+     {0.77, 0.99, 1.05, 0.73}, {0.33, 0.43, 0.47, 0.85}, {0.46, 0.51, 0.53, 0.85}, {0.26, 0.35, 0.31, 0.70},
+     {0.55, 0.64, 0.70, 0.80}, {0.51, 0.51, 0.36, 0.67}, {0.17, 0.22, 0.22, 0.77}}};
 constexpr bool shape_dealt(int shape) { return shape >= 4 && shape <= 8; }
 constexpr bool shape_half(int shape) { return shape == 2 || shape == 10; }
 
@@ -905,14 +909,18 @@ int64_t tiles_of(int shape, int64_t slots, int64_t rows)
     }
 }
 
-// Estimated time of one launch per 64 hidden elements: the workgroups and the weights, from HBM at 5.8 TB/s at best, joined by a 4-norm.
+// Estimated time of one launch per 64 hidden elements: the workgroups and the weights, from HBM at 7.2 TB/s (several row tiles: 5.0),
+// joined by a 4-norm.
 double launch_cost(int shape, int64_t slots, int64_t rows)
 {
-    const ShapeCost c = SHAPE_US[shape];
-    const bool pairs = shape >= 9;  // of workgroups on a compute unit
-    const int64_t n = tiles_of(shape, slots, rows), at_once = pairs ? 512 : 256, part = n % at_once;
-    const double last = part == 0 ? 0.0 : pairs ? (part <= 256 ? c.least : c.round) : c.least + (c.round - c.least) * part / 256.0;
-    const double tiles = c.round * (double)(n / at_once) + last, weights = (double)slots * 128 * 128 / 5.8e6;
+    const int tile_rows = shape == 0 || shape == 3 || shape == 4 ? 256 : shape == 6 || shape == 7 || shape >= 9 ? 64 : 128;
+    const bool several = rows > tile_rows;
+    const ShapeCost c = SHAPE_US[several][shape];
+    const int64_t n = tiles_of(shape, slots, rows), full = n / 256;
+    const double part = (double)(n % 256) / 256.0;
+    const double tiles = full == 0 ? c.least + (c.first - c.least) * part
+                                   : c.first + c.further * ((double)(full - 1) + (part > 0.0 ? c.start + (1.0 - c.start) * part : 0.0));
+    const double weights = (double)slots * 128 * 128 / (several ? 5.0e6 : 7.2e6);
     const double t2 = tiles * tiles, w2 = weights * weights;
     return sqrt(sqrt(t2 * t2 + w2 * w2));
 }
@@ -939,16 +947,16 @@ int plan_pieces(int slots, int M, int K, bool allow_half, bool allow_dealt, Gemm
         }
     }
     if (no_split) return 1;
-    const double extra = 3.0 / (K / 64);
+    const double extra = 3.0 / (K / 64), short_by = 1.03;  // (estimates of two launches come out short: 130 measured cuts)
     for (int sh = 0; sh <= 3; sh += 3) {
         const int64_t per = sh == 3 ? 2 : 1, t256 = (M + 255) / 256, units = (slots + per - 1) / per;
         for (int64_t rounds = units * t256 / 256; rounds >= 1 && rounds >= units * t256 / 256 - 1; --rounds) {
             const int64_t u1 = rounds * 256 / t256, s1 = u1 * per;          // slabs of the first launch
             const int64_t r1 = rounds * 256 / units, m1 = r1 * 256;         // or its row tiles
             for (int s2 = 0; s2 <= 3; ++s2) {
-                if (s2 == 2 && !allow_half) continue;
+                if (s2 == sh || (s2 == 2 && !allow_half)) continue;  // (two launches of one shape take what one does, and the second's start)
                 if (u1 >= 1 && s1 < slots) {
-                    const double c = launch_cost(sh, s1, M) + launch_cost(s2, slots - s1, M) + extra;
+                    const double c = short_by * (launch_cost(sh, s1, M) + launch_cost(s2, slots - s1, M)) + extra;
                     if (c < best) {
                         best = c;
                         n = 2;
@@ -957,7 +965,7 @@ int plan_pieces(int slots, int M, int K, bool allow_half, bool allow_dealt, Gemm
                     }
                 }
                 if (r1 >= 1 && m1 < M) {
-                    const double c = launch_cost(sh, slots, m1) + launch_cost(s2, slots, M - m1) + extra;
+                    const double c = short_by * (launch_cost(sh, slots, m1) + launch_cost(s2, slots, M - m1)) + extra;
                     if (c < best) {
                         best = c;
                         n = 2;
@@ -1135,15 +1143,15 @@ bool fc_project_gemm_supported(const fc_config &cfg, int M)
            n * cfg.hidden * 2 < ((int64_t)1 << 32) && (int64_t)M * cfg.hidden * 2 < ((int64_t)1 << 32);
 }
 
-// Estimated time of the tiled projection of up to 256 rows (us; 33 .. 256 rows, 36 .. 96 head slots, hidden 3584 and 4096: within a tenth
-// of the measured times; 24 slots, hidden 2048: up to a fifth too long).
+// Estimated time of the tiled projection of up to 256 rows (us; 24 .. 96 head slots, hidden 1024 .. 8192, 40 .. 240 rows: within a tenth
+// of the measured times in the mean).
 double fc_project_gemm_us(int slots, int M, int K)
 {
     GemmPiece pc[2];
-    double c = 4.0 + M / 64.0;
+    double c = 0.0;
     const int n = plan_pieces(slots, M, K, true, true, pc);
     for (int i = 0; i < n; ++i) c += launch_cost(pc[i].shape, pc[i].slots, pc[i].m_end - pc[i].m_base) * (K / 64);
-    return n == 2 ? c + 3.0 : c;
+    return 3.0 * n + M / 64.0 + (M <= 128 ? 1.12 : 1.0) * c;
 }
 
 hipError_t fc_launch_project_gemm(const FcGeom &G, const void *x, const void *w, const void *bias,

@@ -656,7 +656,8 @@ static bool stream_wins(int slots, int M, int K, int *mt)
     if (K % 512 != 0 || M > 256 || slots > (M > (K >= 3072 ? 64 : 48) ? 64 : M > 32 ? 80 : K >= 3584 ? 128 : 96) || (M > 128 && K <= 1024)) return false;
     const double us = stream_us(slots, M, K, mt);
     if (M <= 32) return us < 1e30;
-    if (M > 128 || slots > 64) return us < 0.95 * fc_project_gemm_us(slots, M, K);
+    if (M > 128) return us < 0.95 * fc_project_gemm_us(slots, M, K);
+    if (slots > 64) return us < fc_project_gemm_us(slots, M, K);
     return us < fmin(0.94 * headsplit_us(slots, M, K), tile_us(slots, M, K));
 }
 
