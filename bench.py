@@ -63,11 +63,11 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # from `rocprofv3 --pmc FETCH_SIZE` / `--pmc WRITE_SIZE` runs of this command, scaled by what the same
 # counters read for the plain 256 MiB copy at the end of this file (profiles/ holds the summary).
 # HBM bytes per launch of the gated W_1 at 32 rows and the 7B widths (k_proj_gemm, 64 rows x 80 dealt pairs), same
-# method (profiles/c4_whole_layer_step.md): 273.53 MB fetched + 1.21 MB written.
-MEASURED_GATE_UP_TRAFFIC_BYTES = {(32, 3584, 18944): 274_740_000}
+# method (profiles/c4_whole_layer_step.md): 273.50 MB fetched + 1.21 MB written.
+MEASURED_GATE_UP_TRAFFIC_BYTES = {(32, 3584, 18944): 274_710_000}
 
-# The vocabulary projection of 32 rows (k_linear_rows, profiles/unmask_step.md): 1092.05 MB fetched, 0.1 MB written.
-MEASURED_LM_HEAD_TRAFFIC_BYTES = {(32, 3584, 152064): 1_092_150_000}
+# The vocabulary projection of 32 rows (k_vocab_runs, profiles/unmask_step.md): 1092.07 MB fetched, 0.1 MB written.
+MEASURED_LM_HEAD_TRAFFIC_BYTES = {(32, 3584, 152064): 1_092_170_000}
 
 # HBM bytes per launch of the attention call (main kernel + merge kernel), from `rocprofv3 --pmc
 # FETCH_SIZE` / `--pmc WRITE_SIZE` runs of this command, scaled by what the same counters read for the
@@ -342,7 +342,7 @@ def hot_path_json(r, args_layers_note=""):
         # the refresh is a dense pass: both calls are bound by the matrix cores, the projection GEMM
         # being the longer one
         out["roofline"] = {
-            "kernel": "fc_qkv_project_scatter (k_proj_gemm)",
+            "kernel": "fc_qkv_project_scatter (k_gemm_wide)",
             "bound": "mfma",
             "achieved": round(r["proj_flops"] / us_proj * 1e-6, 1),
             "peak": MFMA_BF16_PEAK_TFLOPS,
@@ -530,14 +530,12 @@ def main_layer(args, torch, fc, inputs, dev):
     # the gated W_1 is the longest call: bound by the weight stream for a block of rows, by the matrix
     # cores for a refresh of thousands of rows
     if M >= 1024:
-        roof = {"kernel": "fc_ffn_gate_up (k_proj_gemm, SiLU-gate epilogue)", "bound": "mfma",
+        roof = {"kernel": "fc_ffn_gate_up (k_gemm_wide, SiLU-gate epilogue)", "bound": "mfma",
                 "achieved": round(gate_flops / us_gate * 1e-6, 1), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(gate_flops / us_gate * 1e-6 / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": None,
                 "algorithmic_flops_per_launch": gate_flops, "us_per_launch": round(us_gate, 3)}
     else:
-        # (of the geometries here the whole-row kernel takes short windows of hidden 4096 only)
-        roof = {"kernel": "fc_ffn_gate_up (%s)" % ("k_linear_rows" if M <= 32 and d == 4096 else
-                                                   "k_proj_gemm, SiLU-gate epilogue"), "bound": "hbm",
+        roof = {"kernel": "fc_ffn_gate_up (%s, SiLU-gate epilogue)" % ("k_proj_gemm" if M <= 128 else "k_gemm_wide"), "bound": "hbm",
                 "achieved": gbs(w_bytes["gate_up"], us_gate), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(w_bytes["gate_up"] / us_gate * 1e-3 / HBM_PEAK_GBS, 4),
                 "traffic": MEASURED_GATE_UP_TRAFFIC_BYTES.get((M, d, F)),
@@ -750,7 +748,7 @@ def main_decode(args, torch, fc, inputs, dev):
             res.append(a0.elapsed_time(a1) * 1000.0 / (2 * NL))
         us_gate = sorted(res)[len(res) // 2]
         gate_bytes = 2 * F * d * esz + M * (d + F) * esz
-        roof = {"kernel": "fc_ffn_gate_up of the cached step (k_proj_gemm, SiLU-gate epilogue, 256 rows)", "bound": "hbm",
+        roof = {"kernel": "fc_ffn_gate_up of the cached step (k_gemm_wide, SiLU-gate epilogue, 256 rows)", "bound": "hbm",
                 "achieved": round(gate_bytes / us_gate * 1e-3, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(gate_bytes / us_gate * 1e-3 / HBM_PEAK_GBS, 4), "traffic": None,
                 "algorithmic_bytes_per_launch": gate_bytes, "us_per_launch": round(us_gate, 3),
@@ -849,7 +847,7 @@ def main_unmask(args, torch, fc, inputs, dev):
         "config": {"workload": w.name + "/unmask", "batch": B, "block_rows": A, "hidden": d, "vocab": V,
                    "unmasked_per_step": k, "matrices_rotated": n_mats},
         "roofline": {"kernel": "fc_lm_head_argmax (%s + k_lmhead_reduce)" % (
-                         "k_linear_rows" if M <= 32 else "k_proj_gemm with the arg-max epilogue"),
+                         "k_vocab_runs" if M <= 32 else "k_gemm_wide with the arg-max epilogue"),
                      "bound": "hbm",
                      "achieved": round(w_bytes / us_head * 1e-3, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(w_bytes / us_head * 1e-3 / HBM_PEAK_GBS, 4),
