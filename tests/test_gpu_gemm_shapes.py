@@ -1,4 +1,4 @@
-"""GPU parity of the tiled GEMM's 256 x 256 tile (two slabs, two wave groups an interval apart) and of problems
+"""GPU parity of the tiled GEMM's 256 x 256 tile (two slabs, one wave per SIMD) and of problems
 cut into two launches, at the edges: an odd number of slabs, ragged rows, one and few stages, parts of the
 hidden dimension."""
 import numpy as np
@@ -138,7 +138,8 @@ def test_few_row_tiles_projection(shape, B, d, Hq, Hkv, A, knob):
     (20, 296 * 64, True),      # few rows of a wide layer, where the tiled GEMM takes over from the whole-row kernel
     (1200, 53 * 128, False),   # the last two slabs in a second launch
     (1800, 36 * 128, False),   # the last eight rows in a second launch
-    (512, 296 * 64, True),     # 256 gated slabs in the 256 x 256 tile, 40 in a smaller one
+    (512, 296 * 64, True),     # 474 tiles of 80 dealt pairs, in one launch
+    (1024, 296 * 64, True),    # 256 gated slabs in the 256 x 256 tile, 40 in a smaller one
 ])
 def test_problem_cut_into_two_launches(M, N, gated):
     """At the 7B hidden width, where the planner cuts; against plain fp32 products on the GPU."""
