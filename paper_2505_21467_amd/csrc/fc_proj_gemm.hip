@@ -936,10 +936,15 @@ struct GemmPiece {
 int plan_pieces(int slots, int M, int K, bool allow_half, bool allow_dealt, GemmPiece out[2])
 {
     const bool no_split = fc_knobs().gemm_no_split != 0;  // tuning knob
+    // Two 64-row half slabs on a compute unit against one 128-row slab: more than 512 rows, 257 .. 512 such tiles.  The half slabs start and end
+    // sooner, and the slabs move fewer bytes, so that the hidden dimension decides (us, half slabs first): 2048 x 2176, 930 rows
+    // 16.9 and 19.4, 2560 x 2816, 704 rows 24.3 and 27.2, 3584 x 3584, 525 rows 29.2 and 29.9, but 8192 x 2176, 930 rows 59.8 and 58.3, 10240 x 1280,
+    // 1537 rows 82.4 and 70.7, 18944 x 3584, 525 rows 135 and 127.
+    const bool no64 = M > 512 && K > 4096 && tiles_of(10, slots, M) > 256;
     double best = 1e30;
     int n = 1;
     for (int sh = 0; sh < N_SHAPES; ++sh) {
-        if ((shape_half(sh) && !allow_half) || (shape_dealt(sh) && !allow_dealt)) continue;
+        if ((shape_half(sh) && !allow_half) || (shape_dealt(sh) && !allow_dealt) || (no64 && sh >= 9)) continue;
         const double c = launch_cost(sh, slots, M);
         if (c < best) {
             best = c;
