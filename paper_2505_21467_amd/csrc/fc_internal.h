@@ -69,7 +69,8 @@ struct FcGeom {
 // 44.1 (5.6 and 6.2 TB/s); 18944 x 3584 27.2 and 24.7; 136 MB of keys and values 52.5 and 47.1.  Where the bytes would have been
 // in that cache the hint loses: the same projection over one or two layers 8.6 and 11.0; and it loses where several
 // workgroups share a stream by way of L2 (attention with two groups of row tiles, 16800 keys 17.3 and 19.3; tiles of 48 rows,
-// three to a run, 17.9 and 19.1).
+// three to a run, 17.9 and 19.1).  Just above the line that cache would still hold a part: steps of 4 .. 8 layers, hidden 3584, as fast
+// as without the hint x 0.96 .. 1.14 (mean 1.017, 50 of them) at 268 .. 320 MB, 0.97 .. 1.18 (1.025) to 420 MB, 0.99 .. 1.18 (1.047) above.
 inline bool fc_read_once(double bytes_per_pass) { return bytes_per_pass > 256.0 * 1024 * 1024; }
 
 // Bytes of a pass over all layers: projection weights, `keys` keys and values per sequence, and the layers' other weights (d_ff; 0: none of
