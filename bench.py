@@ -275,7 +275,7 @@ def _traffic(r):
 
 
 def _attention_kernels(plan):
-    kernel, merge = (("k_attn_tile", "k_attn_tile_merge"), ("k_attn_mfma", "k_attn_combine"), ("k_attn_groups", ""))[plan["kind"]]
+    kernel, merge = (("k_attn_tile", "k_attn_tile_merge"), ("k_attn_ranges", "k_attn_combine"), ("k_attn_groups", ""))[plan["kind"]]
     return kernel + " + " + merge if plan["splits"] > 1 else kernel
 
 
@@ -725,7 +725,7 @@ def main_decode(args, torch, fc, inputs, dev):
         res.append(a0.elapsed_time(a1) * 1000.0 / (2 * NL))
     us_attn = sorted(res)[len(res) // 2]
     attn_bytes = 2 * B * S * Hkv * Dh * esz + 2 * B * A * Hq * Dh * esz
-    roof = {"kernel": "fc_active_attention of the cached step (k_attn_mfma + k_attn_combine)", "bound": "hbm",
+    roof = {"kernel": "fc_active_attention of the cached step (k_attn_ranges + k_attn_combine)", "bound": "hbm",
             "achieved": round(attn_bytes / us_attn * 1e-3, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(attn_bytes / us_attn * 1e-3 / HBM_PEAK_GBS, 4), "traffic": None,
             "algorithmic_bytes_per_launch": attn_bytes, "us_per_launch": round(us_attn, 3)}

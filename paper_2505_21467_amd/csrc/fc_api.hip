@@ -151,39 +151,31 @@ const FcKnobs &fc_knobs() { return knobs_mut(); }
 
 namespace {
 
-// Row tiles and waves per attention workgroup, with the measured time of one 64-key stage (us).  Eight-wave
-// workgroups fill a compute unit; two of four waves share one, a stage of each then taking 1.476 times as long.
+// Row tiles and waves of a workgroup of k_attn_ranges (one on a compute unit) and what it takes (us): its start and end, and each
+// stage of 64 keys, on an otherwise idle chip and what a full one adds.
 struct AttnShape {
     int R, W;
-    double stage;
+    double start, stage, full;
 };
-const AttnShape ATTN_SHAPES[] = {{8, 8, 1.174}, {4, 8, 0.826}, {2, 8, 0.706}, {4, 4, 1.179}, {2, 4, 0.939}};
+const AttnShape ATTN_SHAPES[] = {{8, 4, 5.99, 1.174, 0.176}, {4, 4, 4.11, 0.730, 0.105}, {2, 4, 2.89, 0.504, 0.035},
+                                 {8, 8, 4.44, 1.620, 0.185}, {4, 8, 3.81, 0.644, 0.243}};
 
-// Estimated time of the attention call (us), fitted to 2600 measured (shape, plan) pairs (1..8 sequences, 2..1000
-// window rows, 100..17000 keys from HBM; rms error 9 %): a fixed part and a workgroup's start and stages per round,
-// the bandwidth of the stream (5.9 TB/s) and of its copies into the compute units (16 TB/s), joined by a
-// 5-norm, and the merge kernel.  The plans it picks are within 3 % of the best measured ones in the mean; choosing
-// tiles by the row count and splits by "nearest to 256 workgroups" was 14 % off, mostly through grids a little over
-// one round.  (Returns some value >= limit where the largest of the joined terms alone reaches it.)
+// Estimated time of the attention call (us): the rounds of workgroups and the stream from HBM (6.86 TB/s), joined by a 2-norm, a fixed
+// part, and the merge kernel, which reads what the first one wrote (2.44 TB/s both ways).  Fitted to 18000 measured (shape, plan) pairs, 748 shapes
+// (1 .. 8 sequences, 1 .. 32 kv heads, 1 .. 8 query heads each, 2 .. 2304 window rows, 100 .. 17000 keys from HBM): rms error 5.6 %; the
+// plan it picks is 0.8 % slower than the best measured one in the mean, 2.7 % in nine of ten shapes, 22 % at most (4 x 10 rows, 64 / 8
+// heads, 9727 keys: 256 workgroups of four tiles 42.9, 192 35.0).  The five shapes against the three of four waves: 0.3 %, up to 11 %.
+// (Returns some value >= limit where the terms without the norm reach it.)
 double attn_cost(const AttnShape &sh, int64_t pairs, int row_tiles, int kv_len, int64_t splits, int64_t stages, double limit)
 {
-    const int64_t n = pairs * ((row_tiles + sh.R - 1) / sh.R) * splits, at_once = sh.W == 8 ? 256 : 512;
-    const int64_t rounds = n / at_once, rest = n % at_once;
-    const double start = sh.W == 8 ? 4.013 : 2.418;
-    const double one = start + stages * sh.stage;                               // a workgroup alone on its compute unit
-    const double full = sh.W == 8 ? one : start + stages * sh.stage * 1.476;
-    double wg = rounds * full;
-    if (rest) {
-        const double last = sh.W == 8 || rest <= 256 ? one : one + (full - one) * (double)(rest - 256) / 256.0;
-        wg += last * (rounds ? 0.966 : 1.0);
-    }
-    const double hbm = (double)pairs * kv_len * 512.0 / 5.916e6, fill = (double)n * stages * 32768.0 / 16.2e6;
-    auto p5 = [](double v) { return v * v * v * v * v; };
-    const double rest_us = 3.6 + (splits > 1 ? 0.044 * splits + (double)pairs * row_tiles * splits * 8704.0 / 1.52e6 : 0.0);
-    const double least = rest_us + fmax(wg, fmax(hbm, fill));
+    const int64_t n = pairs * ((row_tiles + sh.R - 1) / sh.R) * splits, rounds = n / 256, rest = n % 256;
+    const double wg = (double)rounds * (sh.start + stages * (sh.stage + sh.full)) +
+                      (rest ? sh.start + stages * (sh.stage + sh.full * (double)rest / 256.0) : 0.0);
+    const double hbm = (double)pairs * kv_len * 512.0 / 6.86e6;
+    const double rest_us = 2.35 + (splits > 1 ? 2.39 + 0.059 * splits + (double)pairs * row_tiles * splits * 8704.0 / 2.44e6 : 0.0);
+    const double least = rest_us + fmax(wg, hbm);
     if (least >= limit) return least;
-    const double t = rest_us + pow(p5(wg) + p5(hbm) + p5(fill), 0.2);
-    return t > 7.4 ? t : 7.4;
+    return rest_us + sqrt(wg * wg + hbm * hbm);
 }
 
 // The same for the tile kernel where its operands come straight into registers (bf16 of head_dim 128, up to 96 keys): `wgs`
@@ -248,7 +240,7 @@ int64_t attn_splits_bound(int64_t pairs, int row_tiles, int64_t by_len)
 {
     int64_t bound = 1;
     for (const AttnShape &sh : ATTN_SHAPES) {
-        const int64_t b = (sh.W == 8 ? 256 : 512) / (pairs * ((row_tiles + sh.R - 1) / sh.R));
+        const int64_t b = 256 / (pairs * ((row_tiles + sh.R - 1) / sh.R));
         if (b > bound) bound = b;
     }
     if (pairs * row_tiles >= 200 && 3800 / (pairs * row_tiles) > bound) bound = 3800 / (pairs * row_tiles);
@@ -256,11 +248,18 @@ int64_t attn_splits_bound(int64_t pairs, int row_tiles, int64_t by_len)
     return bound < by_len ? bound : by_len;
 }
 
+// Stages of a range when the keys are cut into `splits`: eight waves take them by twos (fewer ranges, as fast).
+int64_t stages_per_range(int W, int64_t splits, int64_t n_stages)
+{
+    const int64_t stages = (n_stages + splits - 1) / splits;
+    return W == 8 && splits > 1 ? (stages + 1) / 2 * 2 : stages;
+}
+
 void set_attn_plan(FcAttnPlan &p, int R, int W, int64_t splits, int64_t n_stages)
 {
     p.tiles_per_wg = R;
     p.waves = W;
-    const int64_t stages = (n_stages + splits - 1) / splits;
+    const int64_t stages = stages_per_range(W, splits, n_stages);
     p.keys_per_split = (int)(stages * 64);
     p.splits = (int)((n_stages + stages - 1) / stages);
 }
@@ -290,10 +289,10 @@ ForcedTiles forced_tiles(int64_t pairs, int row_tiles, int64_t by_len)
 {
     int R = fc_knobs().attn_r, W = fc_knobs().attn_w;
     int64_t target = fc_knobs().attn_wgs;
-    if (W != 4) W = 8;
+    if (W != 8) W = 4;
     if (R != 2 && R != 4 && R != 8) R = row_tiles <= 2 ? 2 : (row_tiles <= 7 ? 4 : 8);
-    if (W == 4 && R == 8) R = 4;
-    if (target <= 0) target = W == 4 ? 512 : 256;
+    if (R == 2) W = 4;
+    if (target <= 0) target = 256;
     return ForcedTiles{R, W, nearest_splits(target, pairs * ((row_tiles + R - 1) / R), by_len)};
 }
 
@@ -382,14 +381,14 @@ FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len, size_t cap
     const int64_t within = (int64_t)(cap / ((size_t)pairs * p.row_tiles * ATTN_PART_BYTES));
     double best = 1e30;
     for (const AttnShape &sh : ATTN_SHAPES) {
-        const int64_t base = pairs * ((p.row_tiles + sh.R - 1) / sh.R), at_once = sh.W == 8 ? 256 : 512;
+        const int64_t base = pairs * ((p.row_tiles + sh.R - 1) / sh.R);
         // the first few splits, whole rounds of workgroups, and steps of a third between
         static const int STEPS[] = {1, 2, 3, 4, 5, 6, 7, 8, 12, 16, 24, 32, 48, 64, 96};
         constexpr int NS = sizeof STEPS / sizeof STEPS[0];
         for (int c = 0; c < NS + 3; ++c) {
-            const int64_t splits = c < NS ? STEPS[c] : at_once * (c - NS + 1) / base;
+            const int64_t splits = c < NS ? STEPS[c] : 256 * (c - NS + 1) / base;
             if (splits < 1 || splits > bound) continue;
-            const int64_t stages = (n_stages + splits - 1) / splits, ranges = (n_stages + stages - 1) / stages;
+            const int64_t stages = stages_per_range(sh.W, splits, n_stages), ranges = (n_stages + stages - 1) / stages;
             if (ranges > 1 && ranges > within) continue;
             const double limit = best * (1 - 1e-9);
             const double t = attn_cost(sh, pairs, p.row_tiles, kv_len, ranges, stages, limit);
@@ -418,7 +417,7 @@ FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len, size_t cap
     for (const GroupsShape &sh : GROUPS_SHAPES) {
         const int64_t wgs = pairs * ((row_tiles + sh.tiles - 1) / sh.tiles) * sh.v_parts;
         if (wgs > 256 || (sh.waves == 6 && kv_len > 1200)) continue;
-        const double t = attn_groups_cost(sh, pairs, wgs, kv_len);
+        const double t = 1.06 * attn_groups_cost(sh, pairs, wgs, kv_len);  // (286 shapes measured beside k_attn_ranges: 6 % short)
         if (t < best) {
             best = t;
             one_launch(2, sh.tiles, sh.v_parts, sh.waves);

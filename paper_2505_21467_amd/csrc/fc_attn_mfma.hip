@@ -1,28 +1,20 @@
-// Active-query attention on the matrix cores (bf16, head_dim 128), split over the key axis.
+// Active-query attention on the matrix cores (bf16, head_dim 128).
 //
-// Work decomposition.  For one (sequence, kv head) the g*A query rows (head-in-group major, then
-// window row) are cut into 32-row tiles.  A workgroup of W waves owns R row tiles and one contiguous
-// key range ("split").  A wave owns T row tiles; KW waves share the same tiles and divide the keys
-// among themselves (KW = 2: one 32-key half of every 64-key stage each; KW = 4: additionally
-// alternate stages), so R = T * W / KW.
+// For one (sequence, kv head) the g*A query rows (head-in-group major, then window row) are cut into 16-row tiles.  Two kernels:
 //
-// Data movement.  K rows and transposed V tiles stream HBM -> LDS with 16-byte direct-to-LDS loads
-// (no registers in between) into a ring of four 32 KB stages, two stages ahead of the compute.  The
-// LDS image is XOR-swizzled at 16-byte granularity (the swizzle is applied to the global address of
-// each lane, since direct loads land in lane order) so that the 16 lanes the LDS serves per clock
-// hit 16 different 16-byte bank groups: K rows (256 B) by the low four bits of the row, V^T rows
-// (128 B, two per 256 B of banks) by bits 1..3 of the row.
+// k_attn_ranges  a workgroup owns a number of row tiles and one contiguous range of keys; with several ranges each writes
+//                unnormalised partial outputs with their reference maximum and sum, which k_attn_combine merges.
+// k_attn_groups  a workgroup owns one or two row tiles and all keys; its waves take the keys in turn.
 //
-// Per 32 keys a wave computes S^T = K Q^T with v_mfma_f32_32x32x16_bf16 (K rows are the A operand,
-// so each lane ends up holding 16 scores of ONE query row), does the online-softmax update with a
-// single cross-lane exchange (lanes l and l^32 hold the two halves of a row), and feeds the
-// probabilities, converted to bf16 in place, straight back as the B operand of O^T += V^T P^T.  The
-// key order inside a 32-key group is permuted on the K side (bits 2 and 3 of the row index
-// swapped) so that the accumulator layout of S^T is exactly the operand layout P^T needs for
-// natural-order V^T rows: no shuffles and no LDS round trip for P.
+// Both compute S^T = K Q^T with v_mfma_f32_16x16x32_bf16 (K rows are the A operand: a lane (rho, q) = (lane & 15, lane >> 4) holds
+// scores of ONE query row rho) and feed the probabilities, converted to bf16 in place, back as the B operand of
+// O^T += V^T P^T.  Within a block of 32 keys the K rows are read in the order in which a lane ends up with keys 8 q .. 8 q + 7,
+// the operand layout of P^T for natural-order V^T rows: no shuffles and no LDS round trip for P.
 //
-// Each split writes unnormalised partial outputs with their running max and sum; a small second
-// kernel merges the splits.  With one split the first kernel writes the final output itself.
+// K rows and transposed V tiles stream HBM -> LDS with 16-byte direct-to-LDS loads (no registers in between).  The LDS image is
+// XOR-swizzled at 16-byte granularity (the swizzle is applied to the global address of each lane, since direct loads land
+// in lane order) so that the 16 lanes the LDS serves per clock hit 16 different 16-byte bank groups: K rows (256 B) by the low
+// four bits of the row, V^T rows (128 B, two per 256 B of banks) by bits 1..3 of the row.
 #include <stdlib.h>
 
 #include "fc_device.h"
@@ -32,20 +24,11 @@ namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 constexpr int DH = 128;
 constexpr int KT = 64;                 // keys per stage (= one transposed V tile)
 constexpr int K_BYTES = KT * DH * 2;   // 16384
-constexpr int STAGE_BYTES = 2 * K_BYTES;
-// Eight-wave workgroups (one per compute unit) keep a ring of four stages, two in flight ahead of the
-// one being consumed; four-wave workgroups (two per compute unit, drifting independently so that one
-// computes while the other waits) keep two stages, one in flight.  The ring is reused as exchange /
-// output staging area (17152 B per wave group).
-__host__ __device__ constexpr int ring_slots(int W) { return W == 8 ? 4 : 2; }
-__host__ __device__ constexpr int lds_bytes(int W) { return W == 8 ? 136 * 1024 : 68 * 1024; }
-constexpr int XCHG_FLOATS = 66 * 64;   // one tile state handed between waves: 64 O regs + m + l per lane
-constexpr int OROW = 132;              // floats per row of the output staging tile (128 + 4 padding)
+constexpr int OROW = 132;              // floats per row of the output staging area (128 + 4 padding)
 
 // k_attn_groups: LDS of a wave, a group of keys and a stage of values, or its state of 16 QT rows at the end
 __host__ __device__ constexpr int groups_wave_bytes(int QT, int VP)
@@ -60,17 +43,14 @@ struct AttnArgs {
     const uint16_t *Vc;   // one layer, [B][Hkv][spad/64][128][64]
     const int32_t *pos;   // [B][A] or nullptr
     uint16_t *out;        // [B][A][Hq*128]
-    float *part_o;        // [B*Hkv*row_tiles][splits][8 slot pairs][64 lanes][8 halves]: accumulators as the lanes hold them
+    float *part_o;        // [B*Hkv*row_tiles][splits][8 slots][64 lanes][8 halves]: accumulators as the lanes hold them
     float *part_ml;       // [B*Hkv*row_tiles][splits][32 rows][4]  (max in the log2 domain, sum, scaling exponent, -)
     int B, Hq, Hkv, g, A, kv_len, spad, max_seq;
     int row_tiles, n_rg, splits, keys_per_split, n_units;
     float c;              // softmax scale * log2(e)
-    uint32_t div_pair, div_hkv, div_a;  // k_attn_groups: see launch_groups
-    bool once;            // k_attn_mfma: keys and values with the non-temporal hint
+    uint32_t div_pair, div_hkv, div_a;  // reciprocals: see launch_groups, launch_ranges
+    bool once;            // k_attn_ranges: keys and values with the non-temporal hint
 };
-
-
-__device__ __forceinline__ int kappa(int x) { return (x & 0x13) | ((x & 4) << 1) | ((x & 8) >> 1); }
 
 // Lanes l and l^32 hold the two halves of a query row.  v_permlane32_swap exchanges the upper 32
 // lanes of its first operand with the lower 32 lanes of its second; fed the same value twice it
@@ -109,366 +89,382 @@ __device__ __forceinline__ bool row_is_padded(const int32_t *pos, int idx, int m
     return p < 0 || p >= max_seq;
 }
 
-// State of one 32-row tile inside a wave.
-struct Tile {
-    bf16x8 q[8];
-    f32x16 o[4];
-    float m, l;
-};
-
-// One 32-key group against one row tile: online softmax on the scores s, bf16 probabilities out.
-__device__ __forceinline__ void softmax_tile(Tile &t, f32x16 &s, bf16x8 (&pf)[2], float c, int kbase, int k1,
-                                             int hi)
+// -------------------------------------------------------------------------------------------------
+// 16 QT NW query rows per workgroup over one range of keys: NW waves, each with QT tiles of 16 rows and all keys of the range.
+//
+// One wave per SIMD (NW = 4) has to hide its own latencies, so the arithmetic is one stream in which every multiply has other work beside
+// it: while the weights (exponentials) of a tile and block of 32 keys are computed, the matrix core forms the scores of the
+// next block and the output products of the tile before, and the fragments of the keys and values are replaced one by one
+// behind the last multiply that reads them.  Nothing in the loop depends on a maximum: weights are exp2(c (s - m)) with m the row's
+// maximum over the first block of the range.  bf16 and fp32 hold such a weight to the same relative precision whatever m is, until
+// it overflows; a row whose sum passes 2^100 or whose output is not finite -- the scores rose by some 70 nats behind the first
+// 32 keys -- is computed again with the exact running maximum, by its wave alone.
+// What bounds it: a multiply keeps the VALU of its SIMD for 8 of its 16 clocks, an exponential takes 8, other VALU instructions 4.4, an LDS
+// read 6: 2550 clocks for 64 rows x 64 keys per wave against 2048 of multiplies; measured 2900 at the 2.2 GHz that the power limit leaves.
+// Against eight waves of 32x32x16 multiplies with a maximum per block (in phase, each stage the sum of both), us per call: 8 x 256
+// rows of 28 / 4 heads, 2304 keys 70.0 -> 59.4; 2304 rows 74.6 -> 62.4; 2 x 300 rows, 1001 keys 22.7 -> 18.3; 2 x 256 rows of 32 / 32, 2000 keys
+// 30.0 -> 26.5; 32 rows, 16800 keys 21.6 -> 18.7; 8 x 32 rows, 2304 keys 23.1 -> 19.9; 4 x 64 rows of 32 / 32, 4160 keys 49.2 -> 46.2.
+// Two waves per SIMD with half the rows each (NW = 8) read twice the fragments: 8 x 256 rows 61.6, and a little faster or slower
+// elsewhere; the planner weighs them.
+// The scores' multiplies are inline assembly to have them in the VALU's half of the registers: the compiler puts every accumulator
+// into the other half and moves 64 scores per stage and lane across (62.0 -> 63.4 us).  Its hazard rules do not see them, so: a score is read no
+// sooner than three multiplies (48 clocks) behind its last one, or behind s_nops.
+template <int QT, int NW, bool ONCE>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void k_attn_ranges(AttnArgs p)
 {
-    if (kbase + 32 > k1) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int key = kbase + kappa(8 * (r >> 2) + 4 * hi + (r & 3));
-            s[r] = key < k1 ? s[r] : -INFINITY;
-        }
-    }
-    float mx = s[0];
-#pragma unroll
-    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
-    mx = row_max2(mx);
-    // t.m is a reference maximum, not the exact running one: it only moves (and the accumulators are
-    // only rescaled) when some row's scores exceed it by more than 8 in the log2 domain, so the
-    // probabilities stay below 2^8 and the common case costs no rescaling work at all.
-    if (__any((mx - t.m) * c > 8.0f)) {
-        const float m_new = fmaxf(t.m, mx);
-        const float alpha = __builtin_amdgcn_exp2f((t.m - m_new) * c);
-        t.l *= alpha;
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) t.o[dt][r] *= alpha;
-        t.m = m_new;
-    }
-    const float mc = t.m * c;
-    float lsum = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const float pr = __builtin_amdgcn_exp2f(s[r] * c - mc);
-        lsum += pr;
-        pf[r >> 3][r & 7] = (__bf16)pr;
-    }
-    t.l += lsum;
-}
-
-template <int T, int W, int KW>
-__global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_mfma(AttnArgs p)
-{
-    constexpr int NT = W * 64;
-    constexpr int SLOTS = ring_slots(W);
-    constexpr int AHEAD = SLOTS / 2;  // stages in flight ahead of the one being consumed
-    constexpr int G = W / KW;      // wave groups: each owns T row tiles, its KW waves split the keys
-    constexpr int R = G * T;       // row tiles per workgroup
-    constexpr int LB = 32 / W;     // 1 KB load blocks per wave and stage
-    static_assert(W % KW == 0 && (KW == 1 || KW == 2 || KW == 4) && (W == 4 || W == 8), "shape");
+    constexpr int LB = 16 / NW;  // 1 KB loads of a stage's keys, and of its values, per wave
     extern __shared__ __align__(1024) unsigned char smem[];
+    unsigned char *const kring = smem, *const vring = smem + 4 * K_BYTES;  // four stages each
 
-    // Workgroup -> (unit, row group).  Workgroup ids that are equal modulo 8 land on the same XCD; the
-    // (unit, row group) pairs, ordered unit by unit, are dealt to the eight XCDs in equal contiguous
-    // runs, so the workgroups that stream the same keys share an L2 and every XCD gets the same number
-    // of workgroups whatever the number of units.
     const int id = blockIdx.x;
     const int xcd = id & 7, qd = id >> 3;
     const int64_t n_tiles = (int64_t)p.n_units * p.n_rg;
     const int tile = (int)(xcd * n_tiles / 8) + qd;
     if (tile >= (int)((xcd + 1) * n_tiles / 8)) return;
     const int unit = tile / p.n_rg, rg = tile - unit * p.n_rg;
-    const int split = unit % p.splits, bj = unit / p.splits;
-    const int b = bj / p.Hkv, j = bj % p.Hkv;
+    const int bj = unit / p.splits, split = unit - bj * p.splits;
+    const int b = bj / p.Hkv, j = bj - b * p.Hkv;
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: keeps per-wave branches uniform
-    const int col = lane & 31, hi = lane >> 5;
-    const int gi = wave % G, kw = wave / G;
-    const int rt0 = rg * R + gi * T;  // first row tile of this wave
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rho = lane & 15, q = lane >> 4;
     const int nrows = p.g * p.A;
+    const int row0 = (rg * NW + wave) * (16 * QT);  // first query row of this wave
+    auto head_of = [&](int row) { return p.div_a == 1 ? row / p.A : (int)fc_quotient(row, p.div_a); };
 
-    bool tile_valid[T], row_valid[T];
-    int hq[T], a[T];
-    size_t grow[T];
-    Tile t[T];
+    // ---- query rows (past the end: the last row, never stored)
+    bf16x8 qf[QT][4];
 #pragma unroll
-    for (int u = 0; u < T; ++u) {
-        tile_valid[u] = rt0 + u < p.row_tiles;
-        const int rho = (rt0 + u) * 32 + col;
-        row_valid[u] = tile_valid[u] && rho < nrows;
-        const int hg = row_valid[u] ? rho / p.A : 0;
-        a[u] = row_valid[u] ? rho - hg * p.A : 0;
-        hq[u] = j * p.g + hg;
-        grow[u] = ((size_t)b * p.Hq + hq[u]) * p.A + a[u];
-        const uint4 *qrow = (const uint4 *)(p.Q + grow[u] * DH);
+    for (int u = 0; u < QT; ++u) {
+        const int row = min(row0 + 16 * u + rho, nrows - 1);
+        const int hg = head_of(row), a = row - hg * p.A;
+        const uint16_t *qrow = p.Q + (((size_t)b * p.Hq + j * p.g + hg) * p.A + a) * DH + 8 * q;
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            union { uint4 u4; bf16x8 v; } x;
-            x.u4 = row_valid[u] ? qrow[2 * s + hi] : make_uint4(0, 0, 0, 0);
-            t[u].q[s] = x.v;
-        }
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) t[u].o[dt][r] = 0.f;
-        t[u].m = -INFINITY;
-        t[u].l = 0.f;
+        for (int k = 0; k < 4; ++k) qf[u][k] = fc_load_any<bf16x8>(qrow + 32 * k);
     }
+    __builtin_amdgcn_sched_barrier(0);
 
     const int k0 = split * p.keys_per_split;
     const int k1 = min(p.kv_len, k0 + p.keys_per_split);
     const int n_stages = (k1 - k0 + KT - 1) / KT;
 
-    // ---- loader: the first half of the waves brings the 16 K blocks of a stage, the second half the
-    // 16 V^T blocks; a block is one wave-wide direct-to-LDS load of 1 KB.  Per-lane source offsets (in
-    // bytes, relative to the stage's first K row / V tile) are fixed for the whole kernel.
-    const unsigned char *gsrc;  // this wave's source for stage k0
-    uint32_t goff[LB];
-    uint32_t lds_dst;           // byte offset inside a stage of this wave's first block
-    if (wave < W / 2) {
-        gsrc = (const unsigned char *)(p.Kc + ((size_t)bj * p.spad + k0) * DH);
+    // ---- loads of a stage: 16 KB of key rows and 16 KB of transposed values
+    const unsigned char *ksrc = (const unsigned char *)(p.Kc + ((size_t)bj * p.spad + k0) * DH);
+    const unsigned char *vsrc = (const unsigned char *)(p.Vc + ((size_t)bj * p.spad + k0) * DH);
+    uint32_t kgo[LB], vgo[LB];
 #pragma unroll
-        for (int i = 0; i < LB; ++i) {
-            const int bi = wave * LB + i;
-            const int rf = 4 * bi + (lane >> 4);  // LDS row 0..63: half * 32 + rho
-            const int rho = rf & 31;
-            const int key = (rf & 32) + kappa(rho);
-            const int c = (lane & 15) ^ (rho & 15);
-            goff[i] = (uint32_t)(key * 256 + c * 16);
-        }
-        lds_dst = (uint32_t)(wave * LB * 1024);
-    } else {
-        gsrc = (const unsigned char *)(p.Vc + ((size_t)bj * p.spad + k0) * DH);
-#pragma unroll
-        for (int i = 0; i < LB; ++i) {
-            const int bi = (wave - W / 2) * LB + i;
-            const int dh = 8 * bi + (lane >> 3);
-            const int c = (lane & 7) ^ ((dh >> 1) & 7);
-            goff[i] = (uint32_t)(dh * 128 + c * 16);
-        }
-        lds_dst = (uint32_t)(K_BYTES + (wave - W / 2) * LB * 1024);
+    for (int i = 0; i < LB; ++i) {
+        const int rr = 4 * (LB * wave + i) + (lane >> 4), r = rr & 15;  // LDS row, 256 bytes: row r of 16-key half (rr >> 4) & 1 of a block
+        kgo[i] = (uint32_t)(((rr & 32) + 8 * (r >> 2) + 4 * ((rr >> 4) & 1) + (r & 3)) * 256 + (((lane & 15) ^ r) << 4));
+        const int dh = 8 * (LB * wave + i) + (lane >> 3);  // LDS row, 128 bytes
+        vgo[i] = (uint32_t)(dh * 128 + (((lane & 7) ^ ((dh >> 1) & 7)) << 4));
     }
-    auto issue_stage = [&](int st) {
-        const unsigned char *src = gsrc + (size_t)st * (STAGE_BYTES / 2);  // 64 keys * 256 B for K and for V
-        unsigned char *dst = smem + (st % SLOTS) * STAGE_BYTES + lds_dst;
-        fc_with_hint(p.once, [&](auto once) {
-#pragma unroll
-            for (int i = 0; i < LB; ++i) fc_load_lds16<decltype(once)::value>(src + goff[i], dst + i * 1024);
-        });
+    auto load_k = [&](int st, int slot, int i) {
+        const unsigned char *src = ksrc + (size_t)st * K_BYTES;
+        uint32_t at = kgo[i];
+        asm("" : "+s"(src), "+v"(at));  // (a scalar base and the lane's 32-bit offset, not a 64-bit sum per load and lane)
+        fc_load_lds16<ONCE>(src + at, kring + slot * K_BYTES + (LB * wave + i) * 1024);
     };
-
-    // ---- operand read offsets inside a stage (bytes)
-    uint32_t koff[8];  // K fragment ss of LDS row `col` (add half * 8192)
+    auto load_v = [&](int st, int slot, int i) {
+        const unsigned char *src = vsrc + (size_t)st * K_BYTES;
+        uint32_t at = vgo[i];
+        asm("" : "+s"(src), "+v"(at));
+        fc_load_lds16<ONCE>(src + at, vring + slot * K_BYTES + (LB * wave + i) * 1024);
+    };
+    // keys of stages 0 .. 3, values of 0 .. 2 (past the end the last one again, never read)
 #pragma unroll
-    for (int ss = 0; ss < 8; ++ss) koff[ss] = (uint32_t)(col * 256 + (((2 * ss + hi) ^ (col & 15)) << 4));
-    uint32_t voff[2][2];  // V^T fragment (half, jj) of row `col` (add dt * 4096)
+    for (int st = 0; st < 4; ++st) {
+        const int have = min(st, n_stages - 1);
 #pragma unroll
-    for (int sub = 0; sub < 2; ++sub)
+        for (int i = 0; i < LB; ++i) load_k(have, st, i);
+        if (st < 3)
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
-            voff[sub][jj] = (uint32_t)(K_BYTES + col * 128 + (((4 * sub + 2 * jj + hi) ^ ((col >> 1) & 7)) << 4));
-
-    if (n_stages > 0) issue_stage(0);
-    if (AHEAD > 1 && n_stages > 1) issue_stage(1);
-
-    for (int it = 0; it < n_stages; ++it) {
-        const int ks = k0 + it * KT;
-        if (SLOTS == 4) {
-            // The slot of stage it+2 last held stage it-2, which every wave left before the barrier of
-            // stage it-1: the load can go out ahead of this stage's barrier.
-            if (it + AHEAD < n_stages) {
-                issue_stage(it + AHEAD);
-                fc_wait_vm<2 * LB>();
-            } else if (it + 1 < n_stages) {
-                fc_wait_vm<LB>();
-            } else {
-                fc_wait_vm<0>();
-            }
-            __builtin_amdgcn_s_barrier();
-        } else {
-            // Two slots: the next stage overwrites stage it-1, which other waves may still be reading
-            // until they arrive at this barrier, so its load goes out behind the barrier.
-            fc_wait_vm<0>();
-            __builtin_amdgcn_s_barrier();
-            if (it + 1 < n_stages) issue_stage(it + 1);
-        }
-        unsigned char *st = smem + (it % SLOTS) * STAGE_BYTES;
-
-        if (ks + KT > p.kv_len) {
-            // Rows past kv_len may hold anything (also NaN): zero their V so that 0 * V stays 0.
-            for (int e = tid; e < DH * KT; e += NT) {
-                const int dh = e >> 6, kl = e & 63;
-                if (ks + kl >= p.kv_len)
-                    *(uint16_t *)(st + K_BYTES + dh * 128 + (((kl >> 3) ^ ((dh >> 1) & 7)) << 4) + (kl & 7) * 2) = 0;
-            }
-            __syncthreads();
-        }
-        if (KW == 4 && (it & 1) != (kw >> 1)) continue;
-#pragma unroll
-        for (int hh = 0; hh < (KW == 1 ? 2 : 1); ++hh) {
-            const int sub = (KW == 1) ? hh : (kw & 1);
-            const int kbase = ks + 32 * sub;
-            if (kbase >= k1 || !tile_valid[0]) continue;  // wave-uniform
-            const unsigned char *kb = st + sub * 8192;
-            bf16x8 kf[8];
-#pragma unroll
-            for (int ss = 0; ss < 8; ++ss) kf[ss] = *(const bf16x8 *)(kb + koff[ss]);
-            f32x16 s[T];
-#pragma unroll
-            for (int u = 0; u < T; ++u) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) s[u][r] = 0.f;
-                if (u == 0 || tile_valid[u]) {
-#pragma unroll
-                    for (int ss = 0; ss < 8; ++ss)
-                        s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ss], t[u].q[ss], s[u], 0, 0, 0);
-                }
-            }
-            bf16x8 vf[8];
-#pragma unroll
-            for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-                for (int jj = 0; jj < 2; ++jj)
-                    vf[dt * 2 + jj] = *(const bf16x8 *)(st + voff[sub][jj] + dt * 4096);
-#pragma unroll
-            for (int u = 0; u < T; ++u) {
-                if (u == 0 || tile_valid[u]) {
-                    bf16x8 pf[2];
-                    softmax_tile(t[u], s[u], pf, p.c, kbase, k1, hi);
-#pragma unroll
-                    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-                        for (int jj = 0; jj < 2; ++jj)
-                            t[u].o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt * 2 + jj], pf[jj], t[u].o[dt], 0, 0, 0);
-                }
-            }
-        }
+            for (int i = 0; i < LB; ++i) load_v(have, st, i);
     }
-    __syncthreads();  // every wave is done with the ring; LDS is reused below
+    __builtin_amdgcn_sched_barrier(0);
 
-    float *xch = (float *)smem;
+    // ---- operand fragments: row rho of a tile, step k of the head dimension / half of a stage
+    uint32_t kfo[4], vfo[2];
 #pragma unroll
-    for (int u = 0; u < T; ++u) t[u].l = row_sum2(t[u].l);
+    for (int k = 0; k < 4; ++k) kfo[k] = (uint32_t)(rho * 256 + (((4 * k + q) ^ rho) << 4));
+#pragma unroll
+    for (int h = 0; h < 2; ++h) vfo[h] = (uint32_t)(rho * 128 + (((4 * h + q) ^ ((rho >> 1) & 7)) << 4));
+    const float c = p.c;
+    bf16x8 kf[2][4], vf[8], pf[QT];
+    f32x4 s[2][QT][2], o[QT][8];
+    float l[QT], nm[QT];  // sum of weights, -c times the reference maximum
+    auto read_k = [&](const unsigned char *slot, int half, int i) {  // in the order in which `score` takes them
+        kf[i & 1][i >> 1] = *(const bf16x8 *)(slot + half * 8192 + (i & 1) * 4096 + kfo[i >> 1]);
+    };
+    auto read_v = [&](const unsigned char *slot, int half, int d) { vf[d] = *(const bf16x8 *)(slot + d * 2048 + vfo[half]); };
+    // Multiply i of eight: scores of tile u.
+    auto score = [&](int buf, int u, int i) {
+        f32x4 &d = s[buf][u][i & 1];
+        if (i < 2) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=v"(d) : "v"(kf[i & 1][i >> 1]), "a"(qf[u][i >> 1]));
+        else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(kf[i & 1][i >> 1]), "a"(qf[u][i >> 1]));
+    };
+    auto output = [&](int u, int d) { o[u][d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[d], pf[u], o[u][d], 0, 0, 0); };
 
-    if (KW > 1) {
-        // merge the KW partial states of each tile into the kw == 0 wave
-        if (kw > 0) {
+    // ---- first block: its scores and their maxima
+    fc_wait_vm<6 * LB>();
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int u = 0; u < T; ++u) {
-                float *x = xch + (size_t)(((kw - 1) * G + gi) * T + u) * XCHG_FLOATS;
+    for (int u = 0; u < QT; ++u)
 #pragma unroll
-                for (int dt = 0; dt < 4; ++dt)
+        for (int k = 0; k < 4; ++k) asm("" : "+a"(qf[u][k]));
 #pragma unroll
-                    for (int rq = 0; rq < 4; ++rq)  // 16-byte LDS accesses, lane-contiguous
-                        *(float4 *)(x + ((dt * 4 + rq) * 64 + lane) * 4) =
-                            make_float4(t[u].o[dt][4 * rq], t[u].o[dt][4 * rq + 1], t[u].o[dt][4 * rq + 2],
-                                        t[u].o[dt][4 * rq + 3]);
-                x[64 * 64 + lane] = t[u].m;
-                x[65 * 64 + lane] = t[u].l;
-            }
-        }
-        __syncthreads();
-        if (kw == 0) {
+    for (int i = 0; i < 8; ++i) read_k(kring, 0, i);
 #pragma unroll
-            for (int u = 0; u < T; ++u) {
-                for (int w2 = 1; w2 < KW; ++w2) {
-                    const float *x = xch + (size_t)(((w2 - 1) * G + gi) * T + u) * XCHG_FLOATS;
-                    const float m1 = x[64 * 64 + lane], l1 = x[65 * 64 + lane];
-                    const float mf = fmaxf(t[u].m, m1);
-                    const float a0 = (t[u].m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((t[u].m - mf) * p.c);
-                    const float a1 = (m1 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((m1 - mf) * p.c);
+    for (int i = 0; i < 8; ++i) {
 #pragma unroll
-                    for (int dt = 0; dt < 4; ++dt)
+        for (int u = 0; u < QT; ++u) score(0, u, i);
+        read_k(kring, 1, i);
+    }
+    asm volatile("s_nop 15\n\ts_nop 15");  // the last products have left the matrix core
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                        for (int rq = 0; rq < 4; ++rq) {
-                            const float4 v = *(const float4 *)(x + ((dt * 4 + rq) * 64 + lane) * 4);
-                            t[u].o[dt][4 * rq] = a0 * t[u].o[dt][4 * rq] + a1 * v.x;
-                            t[u].o[dt][4 * rq + 1] = a0 * t[u].o[dt][4 * rq + 1] + a1 * v.y;
-                            t[u].o[dt][4 * rq + 2] = a0 * t[u].o[dt][4 * rq + 2] + a1 * v.z;
-                            t[u].o[dt][4 * rq + 3] = a0 * t[u].o[dt][4 * rq + 3] + a1 * v.w;
+    for (int u = 0; u < QT; ++u) {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) mx = fmaxf(mx, k0 + 8 * q + r < k1 ? s[0][u][r >> 2][r & 3] : -INFINITY);
+        nm[u] = -row_max2(row_max16(mx)) * c;
+        l[u] = 0.f;
+#pragma unroll
+        for (int d = 0; d < 8; ++d) o[u][d] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        pf[QT - 1][r] = (__bf16)0.f;
+#pragma unroll
+        for (int d = 0; d < 8; ++d) vf[d][r] = (__bf16)0.f;
+    }
+
+    float t[8], e[8], sum = 0.f;
+    bf16x8 pw;  // weights of the tile at hand (one tile: those of the block before are still being multiplied)
+    auto weight_end = [&](int u) {
+        pw[7] = (__bf16)e[7];
+        pf[u] = pw;
+        l[u] += sum + e[7];
+    };
+    auto mask_values = [&](int d, int base) {  // values of keys past the end may hold anything (also NaN): their weights are 0
+        union { uint32_t w[4]; bf16x8 v; } x;
+        x.v = vf[d];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x.w[r] &= (base + 2 * r < k1 ? 0xffffu : 0u) | (base + 2 * r + 1 < k1 ? 0xffff0000u : 0u);
+        vf[d] = x.v;
+    };
+    // A stage.  LOADS: with all its loads, keys of stage st + 4 and values of stage st + 3; LAST: the last one, with keys past the end.
+    auto stage = [&](int st, auto loads, auto last) {
+        constexpr bool LOADS = decltype(loads)::value, LAST = decltype(last)::value;
+        // the values of stage st and the keys of stage st + 1 have arrived; every wave has read the keys of stage st and the values
+        // of stage st - 1
+        if (LAST) fc_wait_vm<0, true>();
+        else if (LOADS || st + 3 < n_stages) fc_wait_vm<4 * LB, true>();
+        else if (st + 2 < n_stages) fc_wait_vm<3 * LB, true>();
+        else fc_wait_vm<LB, true>();
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        const unsigned char *const keys = kring + ((st + 1) & 3) * K_BYTES, *const values = vring + (st & 3) * K_BYTES;
+        // A block of 32 keys, tile by tile: weights of block i, tile u; beside them the scores of block i + 1, tile u, and the output
+        // products of the tile before; fragments of the keys of block i + 2 and of the values of block i, each right behind the last
+        // multiply by the one before.
+        auto block = [&](auto bc) {
+            constexpr int B = decltype(bc)::value, N = B ^ 1;
+            constexpr bool SCORES = !LAST || B == 0;
+            const int base = k0 + st * KT + 32 * B + 8 * q;
+            auto weight = [&](int u, int i) {  // step i of 16 of the weights of tile u
+                const int k = i >> 1;
+                if ((i & 1) == 0) {
+                    t[k] = __builtin_fmaf(s[B][u][k >> 2][k & 3], c, nm[u]);
+                    if (LAST) t[k] = base + k < k1 ? t[k] : -INFINITY;
+                    if (k >= 1) sum = k == 1 ? e[0] : sum + e[k - 1];
+                } else {
+                    e[k] = __builtin_amdgcn_exp2f(t[k]);
+                    if (k >= 1) pw[k - 1] = (__bf16)e[k - 1];
+                }
+            };
+#pragma unroll
+            for (int u = 0; u < QT; ++u)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    if ((i & 1) == 0) {
+                        if (SCORES) score(N, u, i >> 1);
+                        if (!LAST && u == QT - 1) read_k(keys, B, i >> 1);
+                    } else {
+                        if (LAST && QT > 1 && u == 1) mask_values(i >> 1, base);
+                        if (LAST && QT == 1 && B == 1) mask_values(i >> 1, base - 32);
+                        output(u == 0 ? QT - 1 : u - 1, i >> 1);
+                        if (u == 0) read_v(values, B, i >> 1);
+                    }
+                    if (i == 0 && (u > 0 || B > 0)) weight_end(u == 0 ? QT - 1 : u - 1);
+                    weight(u, i);
+                    const int g = 16 * u + i, step = 16 * QT / LB;  // a load every `step` multiplies: keys in the first block, values in the other
+                    if (g % step == step / 2) {
+                        if (B == 0) {
+                            if (LOADS || (!LAST && st + 3 < n_stages)) load_v(st + 3, (st + 3) & 3, g / step);
+                        } else if (LOADS) {
+                            load_k(st + 4, st & 3, g / step);
                         }
-                    t[u].l = a0 * t[u].l + a1 * l1;
-                    t[u].m = mf;
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+        };
+        block(std::integral_constant<int, 0>());
+        block(std::integral_constant<int, 1>());
+        weight_end(QT - 1);
+    };
+    // what goes round the loops keeps its half of the registers
+    auto pin = [&]() {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) asm("" : "+v"(kf[i & 1][i >> 1]), "+v"(vf[i]));
+#pragma unroll
+        for (int u = 0; u < QT; ++u) {
+            asm("" : "+v"(s[0][u][0]), "+v"(s[0][u][1]));
+#pragma unroll
+            for (int d = 0; d < 8; ++d) asm("" : "+a"(o[u][d]));
+        }
+    };
+    pin();
+    int st = 0;
+    for (; st + 4 < n_stages; ++st) stage(st, std::true_type(), std::false_type()), pin();
+    for (; st + 1 < n_stages; ++st) stage(st, std::false_type(), std::false_type()), pin();
+    stage(st, std::false_type(), std::true_type());
+#pragma unroll
+    for (int d = 0; d < 8; ++d) {
+        if (QT == 1) mask_values(d, k0 + st * KT + 32 + 8 * q);
+        output(QT - 1, d);
+    }
+    __syncthreads();  // every wave is done with the rings; LDS is reused below
+
+    // Largest magnitude of a row of partial outputs (NaN if one is), and whether the reference maximum was too far off.
+    float amax[QT];
+    bool off = false;
+#pragma unroll
+    for (int u = 0; u < QT; ++u) {
+        l[u] = row_sum2(row_sum16(l[u]));
+        amax[u] = 0.f;
+#pragma unroll
+        for (int d = 0; d < 8; ++d)
+#pragma unroll
+            for (int r = 0; r < 4; r += 2)
+                amax[u] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(amax[u], fabsf(o[u][d][r])), fabsf(o[u][d][r + 1]));
+        off |= !(l[u] < 0x1p100f) || !(amax[u] < INFINITY);
+    }
+    if (__any(off)) {
+        // Again with the exact running maximum, operands straight from memory.
+#pragma unroll
+        for (int u = 0; u < QT; ++u) {
+            nm[u] = INFINITY;
+            l[u] = 0.f;
+#pragma unroll
+            for (int d = 0; d < 8; ++d) o[u][d] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll 1
+        for (int ks = k0; ks < k1; ks += 32) {
+            const uint16_t *kb = (const uint16_t *)ksrc + (size_t)(ks - k0) * DH + 8 * q;
+            const uint16_t *vb = (const uint16_t *)vsrc + (size_t)((ks - k0) & ~63) * DH + rho * 64 + (ks & 32) + 8 * q;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                kf[i & 1][i >> 1] = *(const bf16x8 *)(kb + (8 * (rho >> 2) + 4 * (i & 1) + (rho & 3)) * DH + 32 * (i >> 1));
+                vf[i] = *(const bf16x8 *)(vb + i * (16 * 64));
+            }
+#pragma unroll
+            for (int d = 0; d < 8; ++d) mask_values(d, ks + 8 * q);
+#pragma unroll
+            for (int u = 0; u < QT; ++u) {
+                f32x4 x[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+                for (int i = 0; i < 8; ++i) x[i & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[i & 1][i >> 1], qf[u][i >> 1], x[i & 1], 0, 0, 0);
+                float mx = -INFINITY;
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    if (ks + 8 * q + r >= k1) x[r >> 2][r & 3] = -INFINITY;
+                    mx = fmaxf(mx, x[r >> 2][r & 3]);
+                }
+                const float to = fminf(nm[u], -row_max2(row_max16(mx)) * c), alpha = __builtin_amdgcn_exp2f(to - nm[u]);
+                nm[u] = to;
+                l[u] *= alpha;
+                float part = 0.f;
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    const float w = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r >> 2][r & 3], c, to));
+                    part += w;
+                    pf[u][r] = (__bf16)w;
+                }
+                l[u] += part;
+#pragma unroll
+                for (int d = 0; d < 8; ++d) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) o[u][d][r] *= alpha;
+                    o[u][d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[d], pf[u], o[u][d], 0, 0, 0);
                 }
             }
         }
-        __syncthreads();  // the exchange area is reused as output staging
+#pragma unroll
+        for (int u = 0; u < QT; ++u) {
+            l[u] = row_sum2(row_sum16(l[u]));
+            amax[u] = 0.f;
+#pragma unroll
+            for (int d = 0; d < 8; ++d)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) amax[u] = fmaxf(amax[u], fabsf(o[u][d][r]));
+        }
     }
-    if (kw != 0) return;
 
     if (p.splits > 1) {
-        // ---- partial output, in accumulator order, as scaled half floats: the partial of a row is
-        // normalised by its own sum (a convex combination of V rows, so it is no larger than the
-        // largest |V|) and by a power of two that brings the row's largest magnitude into
-        // [2^14, 2^15); eleven significant bits per value, with the row's max, sum and exponent in
-        // fp32.  That halves the one traffic this kernel adds on top of the key/value stream.
-        // Lane (col, hi) holds for query row `col` the head-dim elements 32 dt + 8 rq + 4 hi .. + 3 in
-        // registers o[dt][4 rq .. 4 rq + 3]; a 16-byte store takes the two rq of a pair.
+        // ---- partial output, in accumulator order, as scaled half floats: the partial of a row is normalised by its own sum (a convex
+        // combination of V rows, so it is no larger than the largest |V|) and by a power of two that brings the row's largest
+        // magnitude into [2^14, 2^15); eleven significant bits per value, with the row's maximum, sum and exponent in fp32.  That halves
+        // the one traffic this kernel adds on top of the key/value stream.  Slot 4 h + d2 of a tile of 32 rows: lane (rho, q) holds of
+        // row 16 h + rho the head-dim elements 32 d2 + 4 q .. + 3 and those 16 on.
 #pragma unroll
-        for (int u = 0; u < T; ++u) {
-            if (!tile_valid[u]) continue;
-            const size_t ts = ((size_t)bj * p.row_tiles + rt0 + u) * p.splits + split;
-            uint4 *po = (uint4 *)p.part_o + ts * (8 * 64) + lane;
-            float amax = 0.f;
+        for (int u = 0; u < QT; ++u) {
+            const int t16 = (rg * NW + wave) * QT + u, tt = t16 >> 1, h = t16 & 1;
+            if (tt >= p.row_tiles) continue;
+            const size_t ts = ((size_t)bj * p.row_tiles + tt) * p.splits + split;
+            uint4 *po = (uint4 *)p.part_o + ts * (8 * 64) + h * 256 + lane;
+            const float inv_l = 1.0f / l[u];
+            const int k = 15 - __builtin_amdgcn_frexp_expf(row_max2(row_max16(amax[u])) * inv_l);  // 15 for an all-zero row
 #pragma unroll
-            for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) amax = fmaxf(amax, fabsf(t[u].o[dt][r]));
-            amax = row_max2(amax);
-            const float inv_l = 1.0f / t[u].l;
-            const int k = 15 - __builtin_amdgcn_frexp_expf(amax * inv_l);  // 15 for an all-zero row
-#pragma unroll
-            for (int q2 = 0; q2 < 8; ++q2) {
+            for (int d2 = 0; d2 < 4; ++d2) {
                 union { _Float16 h[8]; uint4 u4; } x;
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    x.h[e] = (_Float16)__builtin_amdgcn_ldexpf(t[u].o[q2 >> 1][8 * (q2 & 1) + e] * inv_l, k);
-                po[q2 * 64] = x.u4;
+                for (int e2 = 0; e2 < 8; ++e2) x.h[e2] = (_Float16)__builtin_amdgcn_ldexpf(o[u][2 * d2 + (e2 >> 2)][e2 & 3] * inv_l, k);
+                po[d2 * 64] = x.u4;
             }
-            if (hi == 0) ((float4 *)p.part_ml)[ts * 32 + col] = make_float4(t[u].m * p.c, t[u].l, (float)k, 0.f);
+            // a sum beyond 2^24 (the maximum has moved far from the reference) hands its exponent to the maximum
+            const int by = l[u] > 0x1p24f ? __builtin_amdgcn_frexp_expf(l[u]) : 0;
+            if (q == 0) ((float4 *)p.part_ml)[ts * 32 + 16 * h + rho] = make_float4(-nm[u] + (float)by, __builtin_amdgcn_ldexpf(l[u], -by), (float)k, 0.f);
         }
         return;
     }
 
-    // ---- final output (single split).  Each owner wave stages its tile as [row][128] floats in its
-    // own LDS area, then writes whole rows of 256 bytes.
-    float *stg = xch + (size_t)gi * (32 * OROW + 64);
-    size_t *rowid = (size_t *)(stg + 32 * OROW);  // 32 entries
+    // ---- final output, through the wave's own area: written as whole rows of 256 bytes
+    float *stg = (float *)(smem + wave * (QT * 16 * OROW * 4));
 #pragma unroll
-    for (int u = 0; u < T; ++u) {
-        if (!tile_valid[u]) continue;
-        const float inv = 1.0f / t[u].l;
+    for (int u = 0; u < QT; ++u) {
+        const float inv = 1.0f / l[u];
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-            for (int rq = 0; rq < 4; ++rq)
-                *(float4 *)(stg + col * OROW + 32 * dt + 8 * rq + 4 * hi) =
-                    make_float4(t[u].o[dt][4 * rq] * inv, t[u].o[dt][4 * rq + 1] * inv,
-                                t[u].o[dt][4 * rq + 2] * inv, t[u].o[dt][4 * rq + 3] * inv);
-        if (hi == 0) {
-            // destination row (or an all-ones marker for rows that do not exist)
-            size_t dst = ((size_t)b * p.A + a[u]) * ((size_t)p.Hq * DH) + (size_t)hq[u] * DH;
-            if (row_is_padded(p.pos, b * p.A + a[u], p.max_seq)) dst |= (size_t)1 << 62;
-            rowid[col] = row_valid[u] ? dst : ~(size_t)0;
-        }
-        __builtin_amdgcn_wave_barrier();
-        fc_wait_lds();  // lgkmcnt(0): the staged tile is visible to the whole wave
-#pragma unroll 2
-        for (int i = 0; i < 16; ++i) {
-            const int idx = i * 64 + lane;
-            const int row = idx >> 5, c4 = idx & 31;
-            const size_t dst = rowid[row];
-            if (dst == ~(size_t)0) continue;
-            const float4 v = *(const float4 *)(stg + row * OROW + c4 * 4);
-            const bool padded = (dst >> 62) & 1;
-            uint16_t *o = p.out + (dst & (((size_t)1 << 62) - 1)) + c4 * 4;
-            uint2 w;
-            w.x = padded ? 0u : ((uint32_t)fc_bf16_bits(v.x) | ((uint32_t)fc_bf16_bits(v.y) << 16));
-            w.y = padded ? 0u : ((uint32_t)fc_bf16_bits(v.z) | ((uint32_t)fc_bf16_bits(v.w) << 16));
-            *(uint2 *)o = w;
-        }
-        __builtin_amdgcn_wave_barrier();
-        fc_wait_lds();  // reads of the staging area are done before the next tile reuses it
+        for (int d = 0; d < 8; ++d)
+            *(float4 *)(stg + (16 * u + rho) * OROW + 16 * d + 4 * q) = make_float4(o[u][d][0] * inv, o[u][d][1] * inv, o[u][d][2] * inv, o[u][d][3] * inv);
+    }
+    __builtin_amdgcn_wave_barrier();
+    fc_wait_lds();
+    const int c8 = (lane & 15) * 8;
+#pragma unroll 4
+    for (int i = 0; i < 4 * QT; ++i) {
+        const int r = 4 * i + q, row = row0 + r;
+        const float4 x = *(const float4 *)(stg + r * OROW + c8), y = *(const float4 *)(stg + r * OROW + c8 + 4);
+        if (row >= nrows) continue;
+        const int hg = head_of(row), a = row - hg * p.A;
+        const bool padded = row_is_padded(p.pos, b * p.A + a, p.max_seq);
+        uint4 w;
+        w.x = padded ? 0u : ((uint32_t)fc_bf16_bits(x.x) | ((uint32_t)fc_bf16_bits(x.y) << 16));
+        w.y = padded ? 0u : ((uint32_t)fc_bf16_bits(x.z) | ((uint32_t)fc_bf16_bits(x.w) << 16));
+        w.z = padded ? 0u : ((uint32_t)fc_bf16_bits(y.x) | ((uint32_t)fc_bf16_bits(y.y) << 16));
+        w.w = padded ? 0u : ((uint32_t)fc_bf16_bits(y.z) | ((uint32_t)fc_bf16_bits(y.w) << 16));
+        fc_store_any(p.out + ((size_t)b * p.A + a) * ((size_t)p.Hq * DH) + (size_t)(j * p.g + hg) * DH + c8, w);
     }
 }
 
@@ -688,21 +684,21 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((NW + 3
         }
 }
 
-// Merge the per-split partials: one workgroup of NWV waves per (row tile, pair of 16-byte accumulator
-// slots).  Lane (col, hi) owns row `col` of the tile and two groups of four consecutive head-dim
-// elements, exactly as in the first kernel's accumulators, so every load is a wave-wide contiguous
-// 1 KB.  Each wave merges an equal share of the splits, CB of them per batch with all their loads in
-// flight together (the launch picks NWV and CB so that one batch per wave covers every split up to
-// 128: the merge is one memory round trip); the waves' states are then merged through LDS.
+// Merge the per-range partials: one workgroup of NWV waves per (tile of 32 rows, slot).  Lane (rho, q) owns one row of the tile
+// and two groups of four consecutive head-dim elements, exactly as in the first kernel's accumulators, so every load is a
+// wave-wide contiguous 1 KB.  Each wave merges an equal share of the ranges, CB of them per batch with all their loads in
+// flight together (the launch picks NWV and CB so that one batch per wave covers every range up to 128: the merge is one
+// memory round trip); the waves' states are then merged through LDS.
 template <int CB, int NWV>
 __global__ __launch_bounds__(64 * NWV) void k_attn_combine(AttnArgs p)
 {
     __shared__ float xw[NWV > 1 ? NWV : 1][10][64];
-    const int lane = threadIdx.x & 63, col = lane & 31, hi = lane >> 5;
+    const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int per = (p.splits + NWV - 1) / NWV;
     const int s_lo = min(wv * per, p.splits), s_hi = min(s_lo + per, p.splits);
-    const int q2 = blockIdx.x & 7;           // accumulator slots 2 q2 and 2 q2 + 1: dt = q2 >> 1, rq = 2 (q2 & 1) + {0, 1}
+    const int q2 = blockIdx.x & 7;           // slot
+    const int col = 16 * (q2 >> 2) + (lane & 15);
     const size_t tg = blockIdx.x >> 3;       // (b * Hkv + j) * row_tiles + rt
     const int rt = (int)(tg % p.row_tiles);
     const int bj = (int)(tg / p.row_tiles);
@@ -779,21 +775,27 @@ __global__ __launch_bounds__(64 * NWV) void k_attn_combine(AttnArgs p)
         uint2 w;
         w.x = padded ? 0u : ((uint32_t)fc_bf16_bits(num[4 * g2] / den) | ((uint32_t)fc_bf16_bits(num[4 * g2 + 1] / den) << 16));
         w.y = padded ? 0u : ((uint32_t)fc_bf16_bits(num[4 * g2 + 2] / den) | ((uint32_t)fc_bf16_bits(num[4 * g2 + 3] / den) << 16));
-        const int dh = 32 * (q2 >> 1) + 8 * (2 * (q2 & 1) + g2) + 4 * hi;
+        const int dh = 32 * (q2 & 3) + 16 * g2 + 4 * (lane >> 4);
         *(uint2 *)(orow + dh) = w;
     }
 }
 
-template <int T, int W, int KW>
-hipError_t launch(const AttnArgs &args, hipStream_t s)
+// 16 QT NW rows per workgroup
+template <int QT, int NW>
+hipError_t launch_ranges(AttnArgs a, hipStream_t s)
 {
-    constexpr int LDS_BYTES = lds_bytes(W);
-    static hipError_t attr = hipFuncSetAttribute((const void *)k_attn_mfma<T, W, KW>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
-    if (attr != hipSuccess) return attr;
-    const unsigned grid = (unsigned)(((int64_t)args.n_units * args.n_rg + 7) / 8 * 8);
-    k_attn_mfma<T, W, KW><<<dim3(grid), dim3(W * 64), LDS_BYTES, s>>>(args);
-    return hipGetLastError();
+    constexpr int STAGING = NW * QT * 16 * OROW * 4, LDS_BYTES = STAGING > 8 * K_BYTES ? STAGING : 8 * K_BYTES;
+    static_assert(LDS_BYTES <= 160 * 1024, "LDS");
+    a.div_a = (int64_t)a.g * a.A * a.A < ((int64_t)1 << 32) ? fc_reciprocal(a.A) : 1;  // 1: too many rows for a reciprocal
+    auto start = [&](auto once) {
+        constexpr auto kernel = k_attn_ranges<QT, NW, decltype(once)::value>;
+        static hipError_t attr = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+        if (attr != hipSuccess) return attr;
+        const unsigned grid = (unsigned)(((int64_t)a.n_units * a.n_rg + 7) / 8 * 8);
+        kernel<<<dim3(grid), dim3(NW * 64), LDS_BYTES, s>>>(a);
+        return hipGetLastError();
+    };
+    return a.once ? start(std::true_type()) : start(std::false_type());
 }
 
 template <int QT, int VP, int NW>
@@ -857,14 +859,14 @@ hipError_t fc_launch_attention_mfma(const FcGeom &G, const FcAttnPlan &pl, const
         if (pl.v_parts == 1) return launch_groups<1, 1, 6>(a, s);
         return hipErrorInvalidValue;
     }
-    if (pl.waves == 8) {  // one tile per wave
-        if (R == 8) e = launch<1, 8, 1>(a, s);
-        else if (R == 4) e = launch<1, 8, 2>(a, s);
-        else if (R == 2) e = launch<1, 8, 4>(a, s);
+    if (pl.waves == 4) {  // a wave per SIMD
+        if (R == 8) e = launch_ranges<4, 4>(a, s);
+        else if (R == 4) e = launch_ranges<2, 4>(a, s);
+        else if (R == 2) e = launch_ranges<1, 4>(a, s);
         else return hipErrorInvalidValue;
-    } else {              // four-wave workgroups, two per compute unit
-        if (R == 4) e = launch<1, 4, 1>(a, s);
-        else if (R == 2) e = launch<1, 4, 2>(a, s);
+    } else {              // two
+        if (R == 8) e = launch_ranges<2, 8>(a, s);
+        else if (R == 4) e = launch_ranges<1, 8>(a, s);
         else return hipErrorInvalidValue;
     }
     if (e != hipSuccess || pl.splits == 1) return e;

@@ -10,7 +10,7 @@
 
 // Launch plan of the split-KV attention (host, pure function of the shape).
 struct FcAttnPlan {
-    int kind;            // 0 = k_attn_tile (fp32, head_dim 64, bf16 head_dim 128 over up to 96 keys); bf16 head_dim 128: 1 = k_attn_mfma,
+    int kind;            // 0 = k_attn_tile (fp32, head_dim 64, bf16 head_dim 128 over up to 96 keys); bf16 head_dim 128: 1 = k_attn_ranges,
                          // split-KV, 2 = k_attn_groups, all keys in one launch
     int splits;          // key ranges per (sequence, kv head); every one is non-empty
     int keys_per_split;  // multiple of 64 (kind 0: of 32)
