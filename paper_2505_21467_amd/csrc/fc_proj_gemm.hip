@@ -90,8 +90,9 @@ __device__ __forceinline__ uint4 pack8(const float (&y)[8])
     return w;
 }
 
-// LDS a wave needs for its epilogue: 32 window rows of NT tiles of 16 weight rows in fp32, 16 bytes of padding each
-__host__ __device__ constexpr int epi_bytes(int NT) { return 32 * (NT * 64 + 16); }
+// Window rows a wave's epilogue takes at a time, and the LDS it needs for them: fp32, 16 bytes of padding each
+__host__ __device__ constexpr int epi_rows(int MT) { return MT >= 4 ? 64 : 32; }
+__host__ __device__ constexpr int epi_bytes(int MT, int NT) { return epi_rows(MT) * (NT * 64 + 16); }
 
 // The workgroup's bias goes to LDS at the very start: nothing else asks for it before the end, and a layer's bias
 // comes from HBM (2.5 us with the matrix core idle when the epilogue fetched it).  npw pairs from `first` on: the first
@@ -121,28 +122,34 @@ __device__ __forceinline__ void load_bias(const GemmArgs &p, unsigned char *dst,
 // tile holds the first members of its 8 NT pairs in its first 8 NT rows and their partners in the others.
 //
 // Epilogue of a wave.  Lane (l, q) = (lane & 15, lane >> 4) of tile (i, t) holds rows 16 t + 4 q + r of the wave's weight rows for
-// window row m_first + 16 i + l.  The values go through LDS, 32 window rows at a time in the wave's own area: in the
+// window row m_first + 16 i + l.  The values go through LDS, 64 (or 32) window rows at a time in the wave's own area: in the
 // accumulator layout a store instruction covers 8 bytes of 16 different rows, read back as rows it covers 128
-// or 256 contiguous bytes.  The loop over eight-value pieces is not unrolled: this code runs once per tile, and unrolled it
-// costs more in instruction fetches than in work.
+// or 256 contiguous bytes.  The loop over eight-value pieces is not unrolled where it holds the rotation or the gate: this code
+// runs once per tile, and unrolled it costs more in instruction fetches than in work.
+// With one wave per SIMD nothing hides a wait, so a piece's operands are fetched before the arithmetic of the one before it, and
+// residuals before the values go to LDS.  What a workgroup takes beside its stages (one stage instead of 56; us, 32 rows a step, fetched
+// when due -> this): projection 2048 rows of 36 slots 21.0 -> 13.4, a start off a multiple of eight 20.6 -> 16.4, with bias 24.4 -> 16.9;
+// gated 256 rows 9.3 -> 8.6, residual 2304 rows 9.6 -> 8.3; 4.9 of each is the launch and the first stage.  It was the wave with the last
+// query or key rows and the first value rows that all others waited for: value rows by single keys (6 us) and the rotation for all its pieces.
 template <int MT, int NT, int EPI>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x4 (&acc)[MT][NT], unsigned char *area, const uint16_t *bias_low,
                                               const uint16_t *bias_high, int pair0, int pair_end, int m_first, int lane, int kpart)
 {
     constexpr int P = 8 * NT;               // pairs of the wave
     constexpr int PITCH = NT * 64 + 16;     // bytes per window row: first members, partners, padding
+    constexpr int ROWS = epi_rows(MT), TI = ROWS / 16, TASKS = ROWS * NT / 64;  // pieces per lane
     const FcGeom &G = p.G;
     const int l = lane & 15, q = lane >> 4;
     const int first_v = G.Hq + G.Hkv;       // EPI 0: first value slab
     const bool has_v = EPI == 0 && pair0 + P > first_v * 64;
-    static_assert(MT % 2 == 0, "32 window rows at a time");
+    static_assert(MT % TI == 0 && ROWS * NT % 64 == 0, "whole steps");
 #pragma unroll
-    for (int i = 0; i < MT; i += 2) {
+    for (int i = 0; i < MT; i += TI) {
         const int m_i = m_first + 16 * i;
-        // EPI 0: sequence, window row and position of row m_i + (lane & 31) (pp < 0: padded or past the end)
+        // EPI 0: sequence, window row and position of row m_i + lane % ROWS (pp < 0: padded or past the end)
         int b_l = 0, a_l = 0, pp_l = -1;
         if (EPI == 0) {
-            const int m = m_i + (lane & 31);
+            const int m = m_i + lane % ROWS;
             if (m < p.m_end) {
                 b_l = m / p.A;
                 a_l = m - b_l * p.A;
@@ -151,55 +158,137 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x4 (&acc)[MT
             }
         }
         if (has_v) {
-            // value rows go to the transposed tiles straight from the accumulators: lanes run along the keys
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int b = __shfl(b_l, 16 * h + l, 64), pp = __shfl(pp_l, 16 * h + l, 64);
+            // Value rows go to the transposed tiles.  Where these 64 rows are consecutive positions of one sequence by way of LDS, [weight
+            // row][window row], rounded, as far from a multiple of eight there as in the tile: they leave in pieces of eight keys, 16 bytes, and
+            // single keys at both ends.  Otherwise straight from the accumulators, lanes along the keys (32 rows of 128 x 80-pair tiles
+            // by way of LDS: 6 x 100 rows 28.7 -> 29.5 us).
+            constexpr int VPITCH = ROWS * 2 + 16, GROUPS = ROWS / 8;
+            const int64_t per_head = (int64_t)G.spad * 128;
+            const int n_in = min(ROWS, p.m_end - m_i), r_l = lane % ROWS;
+            const int pp0 = __builtin_amdgcn_readfirstlane(pp_l), b0 = __builtin_amdgcn_readfirstlane(b_l);
+            if (ROWS == 64 && n_in >= 16 && pp0 >= 0 && __all(r_l >= n_in || (pp_l == pp0 + r_l && b_l == b0))) {
+                const int shift = pp0 & 7;
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
                     const int j = 16 * t + 4 * q;
-                    const bool high = j >= P;
-                    const int pr = pair0 + (high ? j - P : j), hs = pr >> 6;
-                    if (hs < first_v || pr >= pair_end || pp < 0) continue;
-                    uint16_t *v = p.Vc + fc_v_index(G, b, hs - first_v, pp, (pr & 63) + (high ? 64 : 0));
-                    const uint16_t *bs = high ? bias_high + j - P : bias_low + j;
+                    float bs[4];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        v[e * FC_VTILE] = fc_bf16_bits(acc[i + h][t][e] + (p.bias ? fc_to_float(bf16_t{bs[e]}) : 0.f));
+                    for (int e = 0; e < 4; ++e) bs[e] = p.bias ? fc_to_float(bf16_t{(j >= P ? bias_high + j - P : bias_low + j)[e]}) : 0.f;
+#pragma unroll
+                    for (int h = 0; h < TI; ++h)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            *(uint16_t *)(area + (j + e) * VPITCH + (16 * h + l + shift) * 2) = fc_bf16_bits(acc[i + h][t][e] + bs[e]);
+                }
+                __builtin_amdgcn_wave_barrier();
+                fc_wait_lds();
+                // elements from value 0 of the sequence's first head to value row j's; -1: none of this wave's
+                auto offset_of = [&](int j) -> int64_t {
+                    const int pr = pair0 + (j >= P ? j - P : j);
+                    if (pr < first_v * 64 || pr >= pair_end) return -1;
+                    return ((pr >> 6) - first_v) * per_head + ((pr & 63) + (j >= P ? 64 : 0)) * FC_VTILE;
+                };
+                auto key_at = [&](int pp) -> int64_t { return (int64_t)(pp / FC_VTILE) * (FC_VTILE * 128) + pp % FC_VTILE; };
+                uint16_t *const vb = p.Vc + (size_t)b0 * G.Hkv * per_head;
+                const int c_lo = (shift + 7) & ~7, c_hi = (shift + n_in) & ~7, base = pp0 - shift;  // whole pieces: columns c_lo .. c_hi - 1
+                {
+                    const int c = c_lo + 8 * (lane % GROUPS);
+                    const int64_t at = key_at(base + c);
+#pragma unroll 2
+                    for (int j = lane / GROUPS; j < 16 * NT; j += 64 / GROUPS) {
+                        const uint4 v8 = *(const uint4 *)(area + j * VPITCH + 2 * c);
+                        const int64_t o = offset_of(j);
+                        if (o >= 0 && c < c_hi) *(uint4 *)(vb + o + at) = v8;
+                    }
+                }
+                const int before = c_lo - shift, single = before + shift + n_in - c_hi;  // at most 7 + 7
+                if (single) {
+                    const int e = lane & 15, c = e < before ? shift + e : c_hi + e - before;
+                    const int64_t at = key_at(base + c);
+#pragma unroll 2
+                    for (int j = lane >> 4; j < 16 * NT; j += 4) {
+                        const uint16_t v1 = *(const uint16_t *)(area + j * VPITCH + 2 * min(c, ROWS + 7));
+                        const int64_t o = offset_of(j);
+                        if (o >= 0 && e < single) vb[o + at] = v1;
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int h = 0; h < TI; ++h) {
+                    const int b = __shfl(b_l, 16 * h + l, 64), pp = __shfl(pp_l, 16 * h + l, 64);
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        const int j = 16 * t + 4 * q;
+                        const bool high = j >= P;
+                        const int pr = pair0 + (high ? j - P : j), hs = pr >> 6;
+                        if (hs < first_v || pr >= pair_end || pp < 0) continue;
+                        uint16_t *v = p.Vc + fc_v_index(G, b, hs - first_v, pp, (pr & 63) + (high ? 64 : 0));
+                        const uint16_t *bs = high ? bias_high + j - P : bias_low + j;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            v[e * FC_VTILE] = fc_bf16_bits(acc[i + h][t][e] + (p.bias ? fc_to_float(bf16_t{bs[e]}) : 0.f));
+                    }
                 }
             }
+            __builtin_amdgcn_wave_barrier();
+            fc_wait_lds();
             if (pair0 >= first_v * 64) continue;
+        }
+        // Piece k of a lane: eight first members and their partners of one row.  (EPI 0, a wave with value slabs behind others: the others)
+        const int eights = EPI == 0 && has_v ? min(NT, (first_v * 64 - pair0) / 8) : NT;
+        const int n_pieces = EPI == 0 && has_v ? (ROWS * eights + 63) / 64 : TASKS;
+        auto piece_row = [&](int k) { return EPI == 0 && has_v ? (lane + 64 * k) / eights : (lane + 64 * k) / NT; };
+        auto piece_eight = [&](int k) { return lane + 64 * k - piece_row(k) * (EPI == 0 && has_v ? eights : NT); };
+        // EPI 1: the residual is asked for before the values go to LDS
+        uint4 rl[EPI == 1 ? TASKS : 1], rh[EPI == 1 ? TASKS : 1];
+        if constexpr (EPI == 1) {
+            if (p.res) {
+#pragma unroll
+                for (int k = 0; k < TASKS; ++k) {
+                    const int m = min(m_i + piece_row(k), p.m_end - 1), pr = min(pair0 + 8 * piece_eight(k), pair_end - 8);
+                    const uint16_t *r = p.res + (size_t)m * p.N + (size_t)(pr >> 6) * 128 + (pr & 63);
+                    rl[k] = *(const uint4 *)r;
+                    rh[k] = *(const uint4 *)(r + 64);
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < TASKS; ++k) rl[k] = rh[k] = make_uint4(0, 0, 0, 0);
+            }
         }
         // ---- to LDS
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < TI; ++h)
 #pragma unroll
             for (int t = 0; t < NT; ++t) *(f32x4 *)(area + (16 * h + l) * PITCH + 64 * t + 16 * q) = acc[i + h][t];
         __builtin_amdgcn_wave_barrier();
         fc_wait_lds();
-        // ---- and back as rows, eight first members and their partners per lane and step
-#pragma unroll 1
-        for (int u = lane; u < 32 * NT; u += 64) {
-            const int row = u / NT, s = u - row * NT;
-            const int m = m_i + row;
-            int b = 0, a = 0, pp = 0;
-            if (EPI == 0) {
-                b = __shfl(b_l, row, 64);
-                a = __shfl(a_l, row, 64);
-                pp = __shfl(pp_l, row, 64);
-            }
+        // ---- and back as rows
+        struct Eight {
             float lo[8], hv[8];
-            const float *src = (const float *)(area + row * PITCH) + 8 * s;
+            int row, s, b, a, pp;
+        };
+        auto fetch = [&](int k, Eight &x) {
+            x.row = piece_row(k);
+            x.s = piece_eight(k);
+            if (EPI == 0) {
+                x.b = __shfl(b_l, x.row, 64);
+                x.a = __shfl(a_l, x.row, 64);
+                x.pp = __shfl(pp_l, x.row, 64);
+            }
+            const float *src = (const float *)(area + (EPI == 0 ? min(x.row, ROWS - 1) : x.row) * PITCH) + 8 * x.s;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                *(float4 *)(lo + 4 * h) = *(const float4 *)(src + 4 * h);
-                *(float4 *)(hv + 4 * h) = *(const float4 *)(src + P + 4 * h);
+                *(float4 *)(x.lo + 4 * h) = *(const float4 *)(src + 4 * h);
+                *(float4 *)(x.hv + 4 * h) = *(const float4 *)(src + P + 4 * h);
             }
+        };
+        auto finish = [&](int k, Eight &x) {
+            float (&lo)[8] = x.lo, (&hv)[8] = x.hv;
+            const int s = x.s, m = m_i + x.row, b = x.b, a = x.a, pp = x.pp;
             const int pr = pair0 + 8 * s;                 // first of the eight pairs
-            if (m >= p.m_end || pr >= pair_end) continue;
+            if (m >= p.m_end || pr >= pair_end || (EPI == 0 && x.row >= ROWS)) return;
             const int hs = pr >> 6, lf = pr & 63;         // slab, and place among its first members
             if constexpr (EPI == 0) {
-                if (hs >= first_v) continue;
                 const bool valid = pp >= 0;
                 if (p.bias) {
                     union { uint4 u4; uint16_t h[8]; } bl, bh;
@@ -222,9 +311,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x4 (&acc)[MT
                     const double turns = (double)pp * f;
                     const float ph = (float)(turns - rint(turns));
                     const float c = __builtin_amdgcn_cosf(ph), sn = __builtin_amdgcn_sinf(ph);
-                    const float x = lo[e], y = hv[e];
-                    lo[e] = x * c - y * sn;
-                    hv[e] = y * c + x * sn;
+                    const float xv = lo[e], y = hv[e];
+                    lo[e] = xv * c - y * sn;
+                    hv[e] = y * c + xv * sn;
                     f *= p.rot1;
                 }
                 if (hs < G.Hq) {
@@ -233,9 +322,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x4 (&acc)[MT
                     fc_store_any(d, ql);
                     fc_store_any(d + 64, qh);
                 } else if (valid) {
-                    uint16_t *k = p.Kc + fc_k_index(G, b, hs - G.Hq, pp, lf);
-                    *(uint4 *)k = pack8(lo);
-                    *(uint4 *)(k + 64) = pack8(hv);
+                    uint16_t *kr = p.Kc + fc_k_index(G, b, hs - G.Hq, pp, lf);
+                    *(uint4 *)kr = pack8(lo);
+                    *(uint4 *)(kr + 64) = pack8(hv);
                 }
             } else if constexpr (EPI == 2) {
                 float y[8];
@@ -252,19 +341,36 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x4 (&acc)[MT
                         *(float4 *)(o + 64 + 4 * h) = *(float4 *)(hv + 4 * h);
                     }
                 } else {
-                    if (p.res) {
-                        union { uint4 u4; uint16_t h[8]; } rl, rh;
-                        rl.u4 = *(const uint4 *)(p.res + at);
-                        rh.u4 = *(const uint4 *)(p.res + at + 64);
+                    union { uint4 u4; uint16_t h[8]; } xl, xh;
+                    xl.u4 = rl[k];
+                    xh.u4 = rh[k];
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            lo[e] += fc_to_float(bf16_t{rl.h[e]});
-                            hv[e] += fc_to_float(bf16_t{rh.h[e]});
-                        }
+                    for (int e = 0; e < 8; ++e) {
+                        lo[e] += fc_to_float(bf16_t{xl.h[e]});
+                        hv[e] += fc_to_float(bf16_t{xh.h[e]});
                     }
                     *(uint4 *)(p.out + at) = pack8(lo);
                     *(uint4 *)(p.out + at + 64) = pack8(hv);
                 }
+            }
+        };
+        if constexpr (EPI == 0 || EPI == 2) {
+            Eight x[2];
+            fetch(0, x[0]);
+#pragma unroll 1
+            for (int k = 0; k + 1 < n_pieces; ++k) {
+                fetch(k + 1, x[1]);
+                __builtin_amdgcn_sched_barrier(0);
+                finish(k, x[0]);
+                x[0] = x[1];
+            }
+            finish(n_pieces - 1, x[0]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < TASKS; ++k) {
+                Eight x;
+                fetch(k, x);
+                finish(k, x);
             }
         }
         __builtin_amdgcn_wave_barrier();
@@ -539,10 +645,10 @@ __global__ __launch_bounds__((NW + NL) * 64) __attribute__((amdgpu_waves_per_eu(
             gemm_epilogue_vocab<MT>(p, acc, pair0 >> 6, m0 + 32 * wave, lane);
         }
     } else {
-        static_assert(NW * epi_bytes(NT) <= SLOTS * STAGE, "epilogue staging");
+        static_assert(NW * epi_bytes(MT, NT) <= SLOTS * STAGE, "epilogue staging");
         __builtin_amdgcn_s_barrier();
         const uint16_t *bias_low = (const uint16_t *)bias_area;
-        gemm_epilogue<MT, NT, EPI>(p, acc, smem + wave * epi_bytes(NT), bias_low, bias_low + PAIRS, pair0, pair_end, m0 + 32 * wave, lane, at.kpart);
+        gemm_epilogue<MT, NT, EPI>(p, acc, smem + wave * epi_bytes(MT, NT), bias_low, bias_low + PAIRS, pair0, pair_end, m0 + 32 * wave, lane, at.kpart);
     }
 }
 
@@ -578,7 +684,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     constexpr int BEHIND_X = (XS - 2) * BATCH + WL, BEHIND_W = (WS - 2) * BATCH;
     constexpr int AHEAD = BEHIND_X < BEHIND_W ? BEHIND_X : BEHIND_W;
     static_assert(XROWS == 256 && XS >= 2 && WS >= XS && WS <= 4 && AHEAD + BATCH < 64, "ring");
-    static_assert(WS * WBYTES + XS * XBYTES >= 4 * epi_bytes(NT) + 1024, "epilogue staging, bias");
+    static_assert(WS * WBYTES + XS * XBYTES >= 4 * epi_bytes(MT, NT) + 1024, "epilogue staging, bias");
     static_assert(EPI != 4 || NT == 8, "a slab per wave");
     extern __shared__ __align__(1024) unsigned char smem[];
     unsigned char *const wring = smem, *const xring = smem + WS * WBYTES;
@@ -723,7 +829,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         if (hs < p.slot_base + p.slots_here)  // an odd number of slabs leaves the last pair half empty
             gemm_epilogue_vocab<MT>(p, acc, hs, m0 + 16 * MT * wm, lane);
     } else {
-        uint16_t *bias_area = (uint16_t *)(smem + 4 * epi_bytes(NT));
+        uint16_t *bias_area = (uint16_t *)(smem + 4 * epi_bytes(MT, NT));
         __builtin_amdgcn_s_barrier();
         if (EPI == 0) {
             if (tid < WROWS) bias_area[tid] = bias;
@@ -731,7 +837,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             __builtin_amdgcn_s_barrier();
         }
         bias_area += wn * 16 * NT;
-        gemm_epilogue<MT, NT, EPI>(p, acc, smem + wave * epi_bytes(NT), bias_area, bias_area + 8 * NT, pair0 + wn * 8 * NT, pair_end,
+        gemm_epilogue<MT, NT, EPI>(p, acc, smem + wave * epi_bytes(MT, NT), bias_area, bias_area + 8 * NT, pair0 + wn * 8 * NT, pair_end,
                                    m0 + 16 * MT * wm, lane, at.kpart);
     }
 }

@@ -134,6 +134,41 @@ def test_few_row_tiles_projection(shape, B, d, Hq, Hkv, A, knob):
     g.close()
 
 
+# Value rows of the 256-row tiles: 64 consecutive positions leave in pieces of eight keys and single keys at both ends, others one by one.
+@pytest.mark.parametrize("shape", [0, 3, 4])
+@pytest.mark.parametrize("B,L,A,listed", [
+    (1, 40, 64, False),   # whole pieces only
+    (2, 43, 131, False),  # off a multiple of eight, across a tile of 64 keys; the second sequence begins inside a step
+    (1, 0, 80, False),    # a last step of 16 rows, the fewest that are taken in pieces
+    (1, 5, 79, False),    # and of 15
+    (3, 61, 192, False),  # every step one sequence's, two row tiles
+    (2, 33, 128, True),   # lists: a step of consecutive positions, one with gaps, padded rows
+])
+def test_value_rows_of_the_wide_tiles(shape, B, L, A, listed, knob):
+    print("[case] value rows, shape", shape, B, L, A, listed, flush=True)
+    knob("FC_PROJ_GEMM_SHAPE", str(shape))
+    dtype, d, Hq, Hkv = "bf16", 128, 4, 2  # the first value slab lies inside a wave's 40 dealt pairs
+    S = L + (2 * A if listed else A)
+    w = inputs.Workload("t", dtype, B, d, Hq, Hkv, 128, L, A)
+    g, o = _pair(dtype, B, d, Hq, Hkv, 128, S + 5, max_rows=A, fill=-0.75)
+    W, b, X = inputs.weights(w, 12), inputs.bias(w, 12), inputs.hidden_states(w, 12, A)
+    pos = None
+    written = np.zeros((B, S + 5), bool)
+    if listed:
+        pos = torch.full((B, A), -1, dtype=torch.int32)
+        pos[:, :64] = torch.arange(L, L + 64)
+        pos[:, 64:A - 3] = torch.arange(L + 65, L + 65 + 2 * (A - 67), 2)
+        for i in range(B):
+            written[i, pos[i][pos[i] >= 0].numpy()] = True
+    else:
+        written[:, L:S] = True
+    Qg = g.project(0, X, W, b, L, pos=pos)
+    Qo = o.project_only(X, W, b, L, pos=pos)
+    assert_close(inputs.as_oracle(Qg), Qo, dtype, "Q")
+    _compare_cache(g, o, dtype, written=written, what="value rows")
+    g.close()
+
+
 @pytest.mark.parametrize("M,N,gated", [
     (20, 296 * 64, True),      # few rows of a wide layer, where the tiled GEMM takes over from the whole-row kernel
     (1200, 53 * 128, False),   # the last two slabs in a second launch
