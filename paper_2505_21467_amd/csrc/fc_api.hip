@@ -468,6 +468,12 @@ struct AttnPlanKey {
 };
 static_assert(sizeof(AttnPlanKey) == sizeof(size_t) + 8 * sizeof(int32_t), "no padding");
 
+struct WidePlanKey {
+    size_t bytes;
+    int32_t dtype, mode, M, K, N, knobs;
+};
+static_assert(sizeof(WidePlanKey) == sizeof(size_t) + 6 * sizeof(int32_t), "no padding");
+
 // The plan of one call that brings `bytes` of workspace.
 FcAttnPlan plan_with_workspace(const fc_config &c, int A, int kv_len, size_t bytes)
 {
@@ -880,22 +886,30 @@ static fc_status check_linear_shape(int32_t M, int32_t K, int32_t N)
     return FC_OK;
 }
 
-// Workspace of one linear call: tiled GEMM where it is planned, streaming kernels otherwise.
-static size_t linear_need(int dtype, int mode, int M, int K, int N)
+// Workspace of one linear call, what it must bring and (`useful`) what its best plan takes where that is more: tiled GEMM where it is
+// planned, streaming kernels otherwise.
+static size_t linear_need(int dtype, int mode, int M, int K, int N, bool useful)
 {
     const FcWidePlan wide = fc_plan_wide(dtype, mode, M, K, N);
-    if (wide.kind == 1) return fc_wide_workspace(wide, M, N);
-    return fc_skinny_workspace(fc_plan_skinny(dtype, mode, M, K, N));
+    if (wide.kind != 1) return fc_skinny_workspace(fc_plan_skinny(dtype, mode, M, K, N));
+    const size_t best = useful ? fc_wide_workspace(wide, M, N) : 0;
+    return best > wide.required ? best : wide.required;
+}
+
+// ... of the layer whose output is N wide and of the gated one of N / 2 outputs.
+static size_t linear_workspace(int32_t dtype, int32_t M, int32_t K, int32_t N, bool useful)
+{
+    // the gated W_1 is planned on its F = N / 2 outputs; its slabs hold half as many outputs, so the
+    // two plans need the same space and one query serves both calls
+    const size_t a = linear_need(dtype, FC_LIN_RESIDUAL, M, K, N, useful);
+    const size_t b = N % 2 == 0 ? linear_need(dtype, FC_LIN_GATE_UP, M, K, N / 2, useful) : 0;
+    return a > b ? a : b;
 }
 
 size_t fc_linear_workspace_bytes(int32_t dtype, int32_t M, int32_t K, int32_t N)
 {
     if ((dtype != FC_F32 && dtype != FC_BF16) || M < 1 || K < 1 || N < 1) return 0;
-    // the gated W_1 is planned on its F = N / 2 outputs; its slabs hold half as many outputs, so the
-    // two plans need the same space and one query serves both calls
-    const size_t a = linear_need(dtype, FC_LIN_RESIDUAL, M, K, N);
-    const size_t b = N % 2 == 0 ? linear_need(dtype, FC_LIN_GATE_UP, M, K, N / 2) : 0;
-    return a > b ? a : b;
+    return linear_workspace(dtype, M, K, N, true);
 }
 
 // Small bf16 problems run in the tile kernel: it is one launch, and short as long as the products are few, where the
@@ -988,9 +1002,11 @@ static fc_status linear_common(int32_t dtype, int mode, const void *x, const voi
     if (st != FC_OK) return st;
     if (((uintptr_t)x | (uintptr_t)w | (uintptr_t)w2 | (uintptr_t)res | (uintptr_t)out | (uintptr_t)workspace) & 15)
         return fail(FC_ERR_INVALID_ARG, "pointers must be 16-byte aligned");
-    const FcWidePlan wide = fc_plan_wide(dtype, mode, M, K, N);
+    static thread_local Memo<WidePlanKey, FcWidePlan> memo;  // (planning weighs a hundred tiles and parts)
+    const WidePlanKey key = {workspace ? workspace_bytes : 0, dtype, mode, M, K, N, fc_knobs().version};
+    const FcWidePlan wide = memo.get(key, [&] { return fc_plan_wide(dtype, mode, M, K, N, key.bytes); });
     const FcSkinnyPlan plan = fc_plan_skinny(dtype, mode, M, K, N);
-    const size_t need = wide.kind == 1 ? fc_wide_workspace(wide, M, N) : fc_skinny_workspace(plan);
+    const size_t need = wide.kind == 1 ? wide.required : fc_skinny_workspace(plan);
     if (need > 0 && (!workspace || workspace_bytes < need))
         return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need,
                     workspace ? workspace_bytes : (size_t)0);
@@ -1036,7 +1052,7 @@ namespace {
 struct LayerWs {
     size_t h, q, o, x2, act, lin, attn;  // attn: last, the attention takes what is left
     size_t least;                        // bytes a call must bring
-    size_t lin_bytes;
+    size_t useful;                       // bytes that all parts' best plans take
 };
 
 struct LayerWsKey {
@@ -1061,15 +1077,17 @@ LayerWs layer_ws(const fc_config &c, int32_t d_ff, int32_t A)
     w.o = take(M * E * es);
     w.x2 = take(M * d * es);
     w.act = take(M * (size_t)d_ff * es);
-    size_t lin = fc_linear_workspace_bytes(c.dtype, (int)M, (int)E, c.hidden);
-    const size_t l2 = fc_linear_workspace_bytes(c.dtype, (int)M, c.hidden, 2 * d_ff);
-    const size_t l3 = fc_linear_workspace_bytes(c.dtype, (int)M, d_ff, c.hidden);
-    if (l2 > lin) lin = l2;
-    if (l3 > lin) lin = l3;
-    w.lin_bytes = lin;
-    w.lin = take(lin);
+    // The linear layers' partial sums may run on over the attention's space, which is free again by then.
+    auto lin = [&](bool useful) {
+        const size_t l1 = linear_workspace(c.dtype, (int)M, (int)E, c.hidden, useful);
+        const size_t l2 = linear_workspace(c.dtype, (int)M, c.hidden, 2 * d_ff, useful);
+        const size_t l3 = linear_workspace(c.dtype, (int)M, d_ff, c.hidden, useful);
+        return l1 > l2 ? (l1 > l3 ? l1 : l3) : (l2 > l3 ? l2 : l3);
+    };
+    w.lin = take(lin(false));
     w.attn = off;
     w.least = off + align256(attn_workspace(c, A, false));
+    w.useful = w.lin + align256(lin(true));
     return w;
 }
 
@@ -1079,7 +1097,9 @@ size_t fc_full_layer_workspace_bytes(const fc_config *cfg, int32_t d_ff, int32_t
 {
     if (check_config(cfg) != FC_OK || d_ff < 1 || max_rows < 1 || (int64_t)max_rows * cfg->batch > (1 << 24))
         return 0;
-    return layer_ws(*cfg, d_ff, max_rows).attn + align256(attn_workspace(*cfg, max_rows, true));
+    const LayerWs w = layer_ws(*cfg, d_ff, max_rows);
+    const size_t attn = w.attn + align256(attn_workspace(*cfg, max_rows, true));
+    return attn > w.useful ? attn : w.useful;
 }
 
 fc_status fc_full_layer_step(fc_cache *cache, int32_t layer, const fc_layer_weights *wt, const void *x,
@@ -1111,20 +1131,20 @@ fc_status fc_full_layer_step(fc_cache *cache, int32_t layer, const fc_layer_weig
     char *ws = (char *)workspace;
     const int M = c.batch * A, d = c.hidden, E = c.n_q_heads * c.head_dim;
     void *h = ws + w.h, *q = ws + w.q, *o = ws + w.o, *x2 = ws + w.x2, *act = ws + w.act;
-    const size_t attn_bytes = workspace_bytes - w.attn;
-    void *lin = w.lin_bytes ? ws + w.lin : nullptr, *attn = attn_bytes ? ws + w.attn : nullptr;
+    const size_t attn_bytes = workspace_bytes - w.attn, lin_bytes = workspace_bytes - w.lin;
+    void *lin = lin_bytes ? ws + w.lin : nullptr, *attn = attn_bytes ? ws + w.attn : nullptr;
 
     const bool once = fc_read_once(fc_pass_bytes(c, wt->d_ff, kv_len));
     st = fc_rmsnorm(c.dtype, x, wt->norm1, wt->eps, M, d, h, stream);
     if (st == FC_OK) st = project_scatter(cache, layer, wt->d_ff, kv_len, h, wt->w_qkv, wt->b_qkv, win_start, A, pos, q, stream);
     if (st == FC_OK) st = active_attention(cache, layer, wt->d_ff, q, A, kv_len, pos, o, attn, attn_bytes, stream);
     if (st == FC_OK)
-        st = linear_common(c.dtype, FC_LIN_RESIDUAL, o, wt->w_out, nullptr, x, M, E, d, x2, lin, w.lin_bytes, once, stream);
+        st = linear_common(c.dtype, FC_LIN_RESIDUAL, o, wt->w_out, nullptr, x, M, E, d, x2, lin, lin_bytes, once, stream);
     if (st == FC_OK) st = fc_rmsnorm(c.dtype, x2, wt->norm2, wt->eps, M, d, h, stream);
     if (st == FC_OK)
-        st = linear_common(c.dtype, FC_LIN_GATE_UP, h, wt->w_gate, wt->w_up, nullptr, M, d, wt->d_ff, act, lin, w.lin_bytes, once, stream);
+        st = linear_common(c.dtype, FC_LIN_GATE_UP, h, wt->w_gate, wt->w_up, nullptr, M, d, wt->d_ff, act, lin, lin_bytes, once, stream);
     if (st == FC_OK)
-        st = linear_common(c.dtype, FC_LIN_RESIDUAL, act, wt->w_down, nullptr, x2, M, wt->d_ff, d, y, lin, w.lin_bytes, once, stream);
+        st = linear_common(c.dtype, FC_LIN_RESIDUAL, act, wt->w_down, nullptr, x2, M, wt->d_ff, d, y, lin, lin_bytes, once, stream);
     return st;
 }
 

@@ -201,8 +201,9 @@ struct FcWidePlan {
     int kind;    // 0 = not covered, 1 = tiled GEMM
     int shape;   // tile shape where ksplit > 1 or a tuning knob forces one (numbered in fc_proj_gemm.hip)
     int ksplit;  // parts of the hidden dimension (1 = epilogue inside the GEMM, no workspace)
+    size_t required;  // bytes of workspace a call must bring (the plan keeps within `cap` bytes from there on)
 };
-FcWidePlan fc_plan_wide(int dtype, int mode, int M, int K, int N);
+FcWidePlan fc_plan_wide(int dtype, int mode, int M, int K, int N, size_t cap = SIZE_MAX);
 size_t fc_wide_workspace(const FcWidePlan &p, int M, int N);
 hipError_t fc_launch_linear_wide(const FcWidePlan &pl, int mode, const void *x, const void *w, const void *w2,
                                  const void *res, int M, int K, int N, void *out, void *workspace, bool once, hipStream_t s,

@@ -901,22 +901,28 @@ hipError_t launch_gemm(GemmArgs a, hipStream_t s)
     return with_hint(std::false_type());
 }
 
-// Sum of the hidden-dimension parts of an EPI 3 launch + residual, four outputs per thread.
+// Sum of the KS hidden-dimension parts of an EPI 3 launch + residual, four outputs per thread, all its loads under way at once: the
+// kernel is a launch and one memory round trip.
+template <int KS>
 __global__ __launch_bounds__(256) void k_splitk_finish(const float *__restrict__ part, const uint16_t *res,
-                                                       uint16_t *out, size_t quads, size_t plane, int ksplit)
+                                                       uint16_t *out, size_t quads, size_t plane)
 {
     const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= quads) return;
-    float4 a = *(const float4 *)(part + 4 * i);
-    for (int k = 1; k < ksplit; ++k) {
-        const float4 b = *(const float4 *)(part + (size_t)k * plane + 4 * i);
-        a.x += b.x;
-        a.y += b.y;
-        a.z += b.z;
-        a.w += b.w;
+    float4 v[KS];
+#pragma unroll
+    for (int k = 0; k < KS; ++k) v[k] = *(const float4 *)(part + (size_t)k * plane + 4 * i);
+    const uint2 rv = res ? *(const uint2 *)(res + 4 * i) : make_uint2(0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    float4 a = v[0];
+#pragma unroll
+    for (int k = 1; k < KS; ++k) {
+        a.x += v[k].x;
+        a.y += v[k].y;
+        a.z += v[k].z;
+        a.w += v[k].w;
     }
     if (res) {
-        const uint2 rv = *(const uint2 *)(res + 4 * i);
         a.x += __uint_as_float(rv.x << 16);
         a.y += __uint_as_float(rv.x & 0xffff0000u);
         a.z += __uint_as_float(rv.y << 16);
@@ -926,6 +932,19 @@ __global__ __launch_bounds__(256) void k_splitk_finish(const float *__restrict__
     w.x = (uint32_t)fc_bf16_bits(a.x) | ((uint32_t)fc_bf16_bits(a.y) << 16);
     w.y = (uint32_t)fc_bf16_bits(a.z) | ((uint32_t)fc_bf16_bits(a.w) << 16);
     *(uint2 *)(out + 4 * i) = w;
+}
+
+constexpr int MAX_PARTS = 16;
+template <int KS = 2>
+hipError_t launch_finish(const GemmArgs &a, hipStream_t s)
+{
+    if constexpr (KS > MAX_PARTS) return hipErrorInvalidValue;
+    else {
+        if (a.ksplit != KS) return launch_finish<KS + 1>(a, s);
+        const size_t quads = (size_t)a.M * a.N / 4;
+        k_splitk_finish<KS><<<dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s>>>(a.part, a.res, a.out, quads, (size_t)a.M * a.N);
+        return hipGetLastError();
+    }
 }
 
 // A launch in one tile shape (numbered below).  Loads of the 128-row shapes are issued by four extra waves: their four
@@ -943,8 +962,7 @@ hipError_t launch_shape(int shape, const GemmArgs &a, hipStream_t s)
         if constexpr (EPI != 4) return launch_gemm<64, 4, 2, 4, 4, EPI>(a, s);
         return hipErrorInvalidValue;
     case 3:
-        if constexpr (EPI == 3) return hipErrorInvalidValue;
-        else return launch_wide<8, 8, 2, 3, 2, EPI>(a, s);
+        return launch_wide<8, 8, 2, 3, 2, EPI>(a, s);
     case 4:
         if constexpr (EPI == 0 || EPI == 2) return launch_wide<8, 5, 2, 3, 3, EPI>(a, s);
         return hipErrorInvalidValue;
@@ -1130,15 +1148,104 @@ bool wide_beats_rows(int mode, int M, int64_t slabs)
            (slabs > 256 && in(tiles_of(6, slabs, M), 208));
 }
 
+// Layers without pairs (EPI 1, 3): a launch of at most one round of workgroups, the hidden dimension in `parts` parts (1: uncut, without the
+// sum).  A workgroup takes `start` and each 64 hidden elements, a + b x with x of the compute units in use, for one row tile (weights
+// from HBM at 6.8 TB/s) and several (by way of L2, 5.3); the partial sums are written and read at 2 TB/s together, and their sum is a launch
+// of its own.  Fitted to 8000 measured launches of this kind: 14 matrices of 2048 x 2048 .. 18944 x 3584, 24 .. 2304 rows, weights from
+// HBM; rms error 7 % for those near the best.  The tile and number of parts it picks are 1.2 % slower than the best in the mean.
+struct PartCost {
+    int shape;
+    double start, one_a, one_b, more_a, more_b;
+};
+constexpr PartCost PART_US[] = {{0, 2.18, 0.490, 0.363, 0.544, 0.235}, {1, 2.21, 0.405, 0.209, 0.413, 0.116},
+                                {2, 1.56, 0.291, 0.090, 0.269, 0.071}, {3, 0.00, 0.929, 0.451, 0.944, 0.338},
+                                {9, 2.01, 0.523, 0.001, 0.512, 0.001}, {10, 1.13, 0.290, 0.003, 0.208, 0.063}};
+double part_cost(const PartCost &c, int64_t tiles, int64_t M, int64_t K, int64_t N, int parts)
+{
+    const bool several = M > (c.shape == 0 || c.shape == 3 ? 256 : c.shape < 9 ? 128 : 64);
+    const double x = (double)(tiles * parts) / 256.0, weights = (double)K * N * 2.0 / (several ? 5.30e6 : 6.81e6);
+    const double loop = c.start + (double)K / KS_MIN / parts * (several ? c.more_a + c.more_b * x : c.one_a + c.one_b * x);
+    const double l2 = loop * loop, w2 = weights * weights;
+    return sqrt(sqrt(l2 * l2 + w2 * w2)) + (parts > 1 ? 3.71 + (double)parts * M * N * 4.0 / 1.96e6 : 1.83);
+}
+
+// The tile and the parts that a layer takes with so many bytes for partial sums.  A few row tiles of a long hidden dimension fill a round
+// well in parts only: 18944 x 3584, 480 / 580 / 760 rows, uncut 128-row half slabs 111 / 142 / 166 us, 256-row slabs in 4 / 3 / 3 parts 77 / 98 /
+// 101; 12288 x 4096, 360 / 760 rows 75 / 113 and 57 / 86; 1200 rows, more than one round of any tile, 256 x 256 in three parts 144 -> 113.  The
+// estimate of the uncut launches is that of plan_pieces, or that of one round here where it is the larger; it has to be beaten by 7 %,
+// and where a round would be less than three quarters full may be missed by 5 %.  Against parts for fewer than 192 workgroups
+// of 128 rows x half a slab, by fill rates (the rule that says what space a call must bring), over 390 problems not of the fit: 1.06 x in
+// the mean, up to 1.64 x, a few sizes slower by up to 8 % (13824 x 5120, 120 rows 37.8 -> 40.7); 2 % from the best measured in the mean.
+void choose_parts(FcWidePlan &p, int M, int K, int N, size_t cap)
+{
+    const int64_t units = N / 128;
+    const int stages = K / KS_MIN;
+    GemmPiece pc[2];
+    const int pieces = plan_pieces((int)units, M, K, true, false, pc);
+    double uncut = 0.0, round = 1e30;
+    for (int i = 0; i < pieces; ++i) uncut += launch_cost(pc[i].shape, pc[i].slots, pc[i].m_end - pc[i].m_base) * stages;
+    uncut = uncut * 0.99 + 3.45 * pieces;
+    for (const PartCost &c : PART_US) {
+        const int64_t tiles = tiles_of(c.shape, units, M);
+        if (tiles <= 256) round = fmin(round, part_cost(c, tiles, M, K, N, 1));
+    }
+    if (round < 1e30) uncut = fmax(uncut, round);
+    double best = uncut * (2 * units * ((M + 127) / 128) >= 192 ? 0.93 : 1.05);
+    for (const PartCost &c : PART_US) {
+        const int64_t tiles = tiles_of(c.shape, units, M);
+        for (int parts = 2; parts <= MAX_PARTS && parts <= stages / 8 && tiles * parts <= 256; ++parts) {
+            if ((size_t)parts * M * N * sizeof(float) > cap) break;
+            const double t = part_cost(c, tiles, M, K, N, parts);
+            if (t < best) {
+                best = t;
+                p.shape = c.shape;
+                p.ksplit = parts;
+            }
+        }
+    }
+}
+
+// The parts for which a call has to bring space: of layers that fill less than three quarters of a round uncut, by a workgroup's fill
+// rate and the rate of the partial sums.  (With that much a call may find a better plan, with more a better one still.)
+void required_parts(FcWidePlan &p, int mode, int M, int K, int N)
+{
+    const int64_t units = N / (mode == FC_LIN_GATE_UP ? 64 : 128), t256 = (M + 255) / 256, t128 = (M + 127) / 128;
+    if (M <= 128 && units >= 192) p.shape = mode == FC_LIN_VOCAB ? 1 : 2;
+    else if (units * t256 >= 192) p.shape = 0;
+    else if (units * t128 >= 144 || mode == FC_LIN_VOCAB) p.shape = 1;
+    else p.shape = 2;
+    if (mode != FC_LIN_RESIDUAL || p.shape != 2 || 2 * units * t128 >= 192) return;
+    const int64_t stages = K / KS_MIN;
+    double best = 1e30;
+    for (const int sh : {0, 1, 2, 9, 10}) {
+        const int64_t rows = sh == 0 ? 256 : sh < 3 ? 128 : 64, wrows = shape_half(sh) ? 64 : 128;
+        if (rows == 64 && M > 64) continue;
+        const int64_t tiles = tiles_of(sh, units, M);
+        for (int64_t ks = 1; ks <= MAX_PARTS; ++ks) {
+            if (ks > 1 && ks > stages / 8) break;
+            const int64_t wg = tiles * ks;
+            if (wg > 288) break;
+            const double fill_us = (double)((wg + 255) / 256) * (double)(rows + wrows) * (double)(K / ks) * 2.0 / 50e3;
+            const double part_us = ks > 1 ? (double)ks * M * N * 8.0 / 3e6 : 0.0;
+            if (fill_us + part_us < best) {
+                best = fill_us + part_us;
+                p.shape = sh;
+                p.ksplit = (int)ks;
+            }
+        }
+    }
+}
+
 }  // namespace
 
-// Tiled-GEMM plan of a plain linear layer (host, pure function of the shape); kind 0: not for this kernel.
-FcWidePlan fc_plan_wide(int dtype, int mode, int M, int K, int N)
+// Tiled-GEMM plan of a plain linear layer (host, pure function of the shape and the space for partial sums); kind 0: not for this kernel.
+FcWidePlan fc_plan_wide(int dtype, int mode, int M, int K, int N, size_t cap)
 {
     FcWidePlan p;
     p.kind = 0;
     p.shape = 0;
     p.ksplit = 1;
+    p.required = 0;
     const int per_slab = mode == FC_LIN_GATE_UP ? 64 : 128;  // FC_LIN_VOCAB: slabs of 128 vocabulary rows
     if (dtype != FC_BF16 || M < 1 || K < 4 * KS_MIN || K % KS_MIN != 0 || N < per_slab || N % per_slab != 0) return p;
     // 32-bit byte offsets inside X and each weight matrix
@@ -1148,55 +1255,30 @@ FcWidePlan fc_plan_wide(int dtype, int mode, int M, int K, int N)
     // tiled GEMM first: 18944 x 3584 30.1 and 31.2, 16384 x 4096 37.0 and 43.1, 8192 x 8192 35.6 and 41.7, 24576 x 4096 41.0 and 42.0;
     // 16 rows of the first 29.7 and 29.6).  Below the line it is mixed: 16384 x 3584 30.7 and 27.4, 12288 x 4096 25.0 and 25.0,
     // 12288 x 3584 22.6 and 23.2, 10240 x 5120 24.2 and 26.3.
+    const FcKnobs &knobs = fc_knobs();
     if (M <= 32) {
         const FcSkinnyPlan rows = fc_plan_skinny(dtype, mode, M, K, N);
-        const bool knob = fc_knobs().lin_wide_shape >= 6;
-        if (!knob && (fc_knobs().lin_wgs > 0 || fc_knobs().lin_no_rows)) return p;  // tuning knobs of the streaming kernels
+        const bool knob = knobs.lin_wide_shape >= 6;
+        if (!knob && (knobs.lin_wgs > 0 || knobs.lin_no_rows)) return p;  // tuning knobs of the streaming kernels
         if (!knob && !(mode == FC_LIN_RESIDUAL ? rows.kind == 1 && M > 16 && (double)K * N >= 60e6
                                                : rows.kind == 2 && K >= 2048 && wide_beats_rows(mode, M, N / per_slab)))
             return p;
     }
     p.kind = 1;
-    const int64_t units = N / per_slab, t256 = (M + 255) / 256, t128 = (M + 127) / 128;
     // (The shape counts only where the hidden dimension is cut into parts or a tuning knob asks for one shape;
     // everything else goes through plan_pieces at launch.)
-    if (M <= 128 && units >= 192) p.shape = mode == FC_LIN_VOCAB ? 1 : 2;
-    else if (units * t256 >= 192) p.shape = 0;
-    else if (units * t128 >= 144 || mode == FC_LIN_VOCAB) p.shape = 1;
-    else p.shape = 2;
-    // Too few slabs even for the smallest tile: also cut the hidden dimension (partial sums in fp32).
-    // Tile and number of parts are chosen together by a two-term estimate that reproduces the measured
-    // order (256 rows, 28 slabs, hidden 18944: 53 us for the 256-row tile in 8 parts, 58 for the 128-row
-    // tile in 4, 68 for the half slab in 2; hidden 3584: 24, 20, 18): a workgroup pulls the rows of
-    // both its operands at about 50 GB/s, and the partial sums are written and read at about 3 TB/s.
-    const int64_t wgs = 2 * units * t128;
-    if (mode == FC_LIN_RESIDUAL && p.shape == 2 && wgs < 192) {
-        const int64_t stages = K / KS_MIN;
-        double best = 1e30;
-        for (const int sh : {0, 1, 2, 9, 10}) {
-            const int64_t rows = sh == 0 ? 256 : sh < 3 ? 128 : 64, wrows = shape_half(sh) ? 64 : 128;
-            if (rows == 64 && M > 64) continue;  // (256 rows in four such tiles, uncut: 25.0 us for W_out, 19.8 as chosen here)
-            const int64_t tiles = tiles_of(sh, units, M);
-            for (int64_t ks = 1; ks <= 16; ++ks) {
-                if (ks > 1 && ks > stages / 8) break;
-                const int64_t wg = tiles * ks;
-                if (wg > 288) break;
-                const double fill_us = (double)((wg + 255) / 256) * (double)(rows + wrows) * (double)(K / ks) * 2.0 / 50e3;
-                const double part_us = ks > 1 ? (double)ks * M * N * 8.0 / 3e6 : 0.0;
-                if (fill_us + part_us < best) {
-                    best = fill_us + part_us;
-                    p.shape = sh;
-                    p.ksplit = (int)ks;
-                }
-            }
-        }
-    }
-    {  // tuning knobs
-        const int v = fc_knobs().lin_wide_shape;
+    required_parts(p, mode, M, K, N);
+    if (knobs.lin_wide_shape >= 0 || knobs.lin_ksplit > 0) {  // tuning knobs
+        const int v = knobs.lin_wide_shape, ks = knobs.lin_ksplit;
         if (v >= 0 && v < N_SHAPES && (!shape_half(v) || mode != FC_LIN_VOCAB) && (!shape_dealt(v) || mode == FC_LIN_GATE_UP)) p.shape = v;
-        const int ks = fc_knobs().lin_ksplit;
-        if (ks >= 1 && ks <= 16 && ks <= K / KS_MIN / 4 && mode == FC_LIN_RESIDUAL) p.ksplit = ks;
-        if (p.shape == 3) p.ksplit = 1;  // (forced: 256 rows x two slabs come in one piece only)
+        if (ks >= 1 && ks <= MAX_PARTS && ks <= K / KS_MIN / 4 && mode == FC_LIN_RESIDUAL) p.ksplit = ks;
+        p.required = fc_wide_workspace(p, M, N);
+        return p;
+    }
+    p.required = fc_wide_workspace(p, M, N);
+    if (mode == FC_LIN_RESIDUAL && cap >= p.required) {
+        p.ksplit = 1;
+        choose_parts(p, M, K, N, cap);
     }
     return p;
 }
@@ -1240,10 +1322,7 @@ hipError_t fc_launch_linear_wide(const FcWidePlan &pl, int mode, const void *x, 
     if (pl.ksplit <= 1) return forced ? launch_shape<1>(pl.shape, a, s) : launch_pieces<1>(a, s);
     hipError_t e = launch_shape<3>(pl.shape, a, s);
     if (e != hipSuccess) return e;
-    const size_t quads = (size_t)M * N / 4;
-    k_splitk_finish<<<dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s>>>((const float *)workspace, a.res, a.out,
-                                                                                  quads, (size_t)M * N, pl.ksplit);
-    return hipGetLastError();
+    return launch_finish(a, s);
 }
 
 bool fc_project_gemm_supported(const fc_config &cfg, int M)

@@ -226,3 +226,29 @@ def test_small_vocabulary(M, K, V):
     print("[case] vocabulary", M, K, V, flush=True)
     x, w = inputs.normal(25, "x", (M, K), 1.0, "bf16"), inputs.normal(25, "w", (V, K), 0.03, "bf16")
     _check_lm_head("bf16", x, w, "small vocabulary of %d" % V)
+
+
+# The hidden dimension in parts, every tile shape that has them: an odd number of slabs, ragged rows, parts of unequal numbers of stages.
+@pytest.mark.parametrize("shape,parts", [(0, 3), (1, 2), (2, 5), (3, 2), (3, 7), (9, 16), (10, 4)])
+@pytest.mark.parametrize("M,K,N", [(300, 4160, 384), (33, 4096, 128)])
+def test_parts_of_every_shape(shape, parts, M, K, N, knob):
+    knob("FC_LIN_WIDE_SHAPE", str(shape))
+    knob("FC_LIN_KSPLIT", str(parts))
+    _linear(M, K, N, False, "shape %d in %d parts" % (shape, parts))
+
+
+# Layers that are cut where there is space for the partial sums, and run uncut where a call brings only what it must.
+@pytest.mark.parametrize("M,K,N", [(480, 8192, 3072), (600, 6144, 3584), (700, 8192, 2048)])
+def test_parts_as_the_space_allows(M, K, N):
+    print("[case] parts by space", M, K, N, flush=True)
+    x, w, r = inputs.normal(4, "x", (M, K), 1.0, "bf16"), inputs.normal(4, "w", (N, K), 0.05, "bf16"), inputs.normal(4, "r", (M, N), 1.0, "bf16")
+    xd, wd, rd = x.to(DEV), w.to(DEV), r.to(DEV)
+    ref = orc.linear_residual(inputs.as_oracle(x), inputs.as_oracle(w), inputs.as_oracle(r), "bf16")
+    useful = fc.fc_linear_workspace_bytes("bf16", M, K, N)
+    assert useful > 0 and useful % (4 * M * N) == 0
+    ws = torch.empty(useful, dtype=torch.uint8, device=DEV)
+    for space, n in ((ws, useful), (ws, useful - 1), (None, 0)):
+        out = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=DEV)
+        fc.fc_linear_residual("bf16", xd, wd, rd, M, K, N, out, space, n)
+        torch.cuda.synchronize()
+        assert_close(inputs.as_oracle(out), ref, "bf16", "%d bytes of workspace" % n)
