@@ -74,6 +74,25 @@ __device__ __forceinline__ void fc_wait_lds() { fc_wait_vm<63, true>(); }
 inline uint32_t fc_reciprocal(int64_t d) { return (uint32_t)((((int64_t)1 << 32) + d - 1) / d); }
 __device__ __forceinline__ uint32_t fc_quotient(uint32_t x, uint32_t reciprocal) { return reciprocal ? __umulhi(x, reciprocal) : x; }
 
+// x / d for any x and any d >= 1, without a branch: T. Granlund, P. Montgomery, Division by invariant integers using multiplication
+// (1994), figure 4.1.  (As a plain division by an argument it is a chain of 35 instructions.)
+struct FcDivisor {
+    uint32_t mul, shift1, shift2;
+    void set(uint32_t d)
+    {
+        uint32_t l = 0;
+        while (((uint64_t)1 << l) < d) ++l;
+        mul = (uint32_t)((((((uint64_t)1 << l) - d) << 32) / d) + 1);
+        shift1 = l < 1 ? l : 1;
+        shift2 = l - shift1;
+    }
+    __device__ __forceinline__ uint32_t over(uint32_t x) const
+    {
+        const uint32_t t = __umulhi(mul, x);
+        return (t + ((x - t) >> shift1)) >> shift2;
+    }
+};
+
 template <typename T>
 __device__ __forceinline__ T fc_from_float(float f);
 template <>

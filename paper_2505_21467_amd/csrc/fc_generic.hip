@@ -133,6 +133,7 @@ struct TileArgs {
     const void *X, *W, *W2, *aux;  // aux: bias [N] (EPI_QKV) or residual [M][N]
     void *out;                     // [M][N], or q
     int M, K, N, n_blocks;         // n_blocks: workgroups along the weight rows
+    FcDivisor by_blocks, by_a;
     // EPI_QKV
     FcGeom G;
     const int32_t *pos;
@@ -160,11 +161,11 @@ __global__ __launch_bounds__(TW * 64) void k_linear_tile(TileArgs p)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rho = lane & 15, q = lane >> 4;
-    const int n_blk = blockIdx.x % p.n_blocks, m0 = blockIdx.x / p.n_blocks * (16 * MT);
-    const int half = G.Dh / 2;
-    // EPI_QKV: tiles per head = Dh / 16
-    auto head_of = [&](int tile) { return tile / (G.Dh / 16); };
-    auto i0_of = [&](int tile) { return (tile % (G.Dh / 16)) * 8; };
+    const int m_blk = (int)p.by_blocks.over(blockIdx.x), n_blk = (int)blockIdx.x - m_blk * p.n_blocks, m0 = m_blk * (16 * MT);
+    const int half = G.Dh / 2, head_shift = G.Dh == 128 ? 3 : 2;
+    // EPI_QKV: tiles per head = Dh / 16, four or eight
+    auto head_of = [&](int tile) { return tile >> head_shift; };
+    auto i0_of = [&](int tile) { return (tile & ((1 << head_shift) - 1)) * 8; };
 
     // What the lane loads: row lr, elements KB lq of a block.  Into registers the operand's own; by way of LDS four
     // neighbouring lanes take 64 bytes of a row, chunks permuted against bank conflicts.
@@ -245,7 +246,7 @@ __global__ __launch_bounds__(TW * 64) void k_linear_tile(TileArgs p)
             for (int idx = tid; idx < 16 * MT * 8 * NT; idx += TW * 64) {
                 const int row = idx / (8 * NT), e = idx % (8 * NT);
                 const int m = min(m0 + row, p.M - 1);
-                const int pp = p.pos ? p.pos[m] : p.win_start + m % p.A;
+                const int pp = p.pos ? p.pos[m] : p.win_start + m - (int)p.by_a.over(m) * p.A;
                 double turns = (double)pp * p.inv_freq[i0_of(n_blk * NT + e / 8) + e % 8] * 0.15915494309189533576888;
                 turns -= rint(turns);
                 float c, s;
@@ -329,7 +330,7 @@ __global__ __launch_bounds__(TW * 64) void k_linear_tile(TileArgs p)
                 if (hs >= G.Hq + 2 * G.Hkv) continue;
                 const int d0 = (q >= 2 ? half : 0) + i0 + 4 * (q & 1);
                 const int mm = mvalid ? m : 0;
-                const int b = mm / p.A, a = mm - b * p.A;
+                const int b = (int)p.by_a.over(mm), a = mm - b * p.A;
                 const int pp = p.pos ? p.pos[mm] : p.win_start + a;
                 const bool valid = mvalid && pp >= 0 && pp < G.max_seq;
                 if (p.aux) {
@@ -421,7 +422,11 @@ __global__ __launch_bounds__(TW * 64) void k_linear_tile(TileArgs p)
 // 1.075 / 1.14 x, bf16 rows of 64 1.13 x (288 keys, 8 heads x 16 rows: 6.4 -> 6.2, 11.1 -> 8.8, 4.6 -> 4.2 us); of it 1.03 x from dealing
 // the workgroups to the XCDs by what they read.  fp32 is bound by its matrix rate (a group of 32 keys, rows of 64: 1024 clocks of scores).
 // In ranges, a wave has one group or two and the longer way costs more than it brings (2 .. 9 %): straight into registers, and so for
-// the up to three groups of bf16 rows of 128.  The accumulator of S^T
+// the up to three groups of bf16 rows of 128.  The queries come to LDS once per workgroup: operand-shaped, by each of its waves, they
+// took as long as the keys (4 to 8 KB x 8 at a lane a clock, behind the keys and in two trips).  With that, without integer divisions
+// ahead of the first load and with the last groups of fp32 dealt by halves, us: fp32 32 rows x 4 heads of 64, 256 / 288 / 544 keys
+// 5.04 / 6.00 / 7.75 -> 4.79 / 5.48 / 7.42, in ranges 1056 keys 8.00 -> 7.36; 4 x 30 rows, 8 / 4 heads of 128, 400 keys 13.5 -> 11.8; bf16 rows of 128,
+// 64 keys 3.78 -> 3.09.  (A second pair of areas, a group ahead: no gain.)  The accumulator of S^T
 // puts keys 4 q + r of a 16-key group into register r of lane (query, q): for fp32 that is the operand
 // layout of P^T (four 16x16x4 instructions, keys 4 q + j); for bf16 the K rows of the two groups are read
 // permuted, so that the eight probabilities of a lane are the keys 8 q .. 8 q + 7.  No exchange for P.
@@ -438,6 +443,7 @@ struct AttnTileArgs {
     FcGeom G;
     int A, kv_len, tiles, splits, groups_per_split;
     float c;                  // softmax scale * log2(e)
+    FcDivisor by_splits, by_tiles, by_hkv, by_a;
 };
 
 constexpr int AT_STRIDE = 4;  // padding floats per row of the exchange area
@@ -456,7 +462,7 @@ __device__ __forceinline__ void attn_store_row4(const AttnTileArgs &p, int bj, i
 {
     const FcGeom &G = p.G;
     if (row >= G.g * p.A) return;
-    const int b = bj / G.Hkv, j = bj % G.Hkv, hg = row / p.A, a = row - hg * p.A;
+    const int b = (int)p.by_hkv.over(bj), j = bj - b * G.Hkv, hg = (int)p.by_a.over(row), a = row - hg * p.A;
     if (p.pos) {  // padded row: same rule as the projection (negative or beyond the cache)
         const int pp = p.pos[b * p.A + a];
         if (pp < 0 || pp >= G.max_seq) v = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -476,6 +482,12 @@ struct AttnTileLds {
     static constexpr int NK = KG * KROW / 1024, NVL = VG * VKEY / 1024;  // 1 KB loads
     static constexpr int STAGE = KG * KROW + VG * VKEY, STATE = QT * 16 * (DH / DS + AT_STRIDE + 2) * (int)sizeof(float);
     static constexpr int WAVE = ((LDS && STAGE > STATE ? STAGE : STATE) + 127) / 128 * 128;
+    // The queries: 1 KB pieces, one per wave, behind the areas (BEHIND) or, where they do not fit there (fp32 rows of 128 with V in
+    // four parts), at the start in the waves' areas for the values.  (Behind them it is 0.1 us less, 8 x 64 rows, 800 keys 0.3.)
+    static constexpr int NQ = QT * 16 * KROW / 1024;
+    static constexpr bool BEHIND = LDS && TW * WAVE + NQ * 1024 <= 160 * 1024;
+    static constexpr int QAT = BEHIND ? TW * WAVE : LDS ? KG * KROW : 0, QSTEP = BEHIND ? 1024 : WAVE, BYTES = TW * WAVE + (BEHIND ? NQ * 1024 : 0);
+    static_assert(NQ <= TW && (BEHIND || QAT + 1024 <= WAVE), "a piece of the queries per wave");
     static_assert(STAGE <= MOST && NVL >= 1, "areas");
     template <int ROWB>
     static __device__ __forceinline__ int swizzle(int row)
@@ -508,18 +520,26 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
     const uint32_t id = (uint32_t)((uint64_t)xcd * n_wgs >> 3) + (blockIdx.x >> 3);
     if (id >= (uint32_t)((uint64_t)(xcd + 1) * n_wgs >> 3)) return;
     const int dv0 = (int)(id % DS) * DV;  // this workgroup's part of the head dimension of V
-    const int split = id / DS % p.splits, bt = id / DS / p.splits;
-    const int tile = bt % p.tiles, bj = bt / p.tiles;
-    const int b = bj / G.Hkv, j = bj % G.Hkv;
+    const int bt = (int)p.by_splits.over(id / DS), split = id / DS - bt * p.splits;
+    const int bj = (int)p.by_tiles.over(bt), tile = bt - bj * p.tiles;
+    const int b = (int)p.by_hkv.over(bj), j = bj - b * G.Hkv;
     const T *kc = (const T *)p.Kc + (size_t)bj * G.spad * DH, *vc = (const T *)p.Vc + (size_t)bj * G.spad * DH;
 
     const int n_groups = (p.kv_len + 31) / 32;
     const int g0 = split * p.groups_per_split, g1 = min(n_groups, g0 + p.groups_per_split);
+    // The wave's groups: every eighth.  fp32, which the matrix rate binds: up to four groups left for the last round are dealt by halves,
+    // so that a SIMD has half a group more than another and not a whole one.
+    const int rest = (g1 - g0) % TW;
+    const bool halves = LDS && F32 && rest >= 1 && rest <= TW / 2;
+    const int rounds = (g1 - g0) / TW, last0 = g0 + rounds * TW;
+    const int n = rounds + (halves ? 32 * last0 + 16 * wave < p.kv_len : wave < rest);
+    auto group_of = [&](int i) { return halves && i == rounds ? last0 + (wave >> 1) : g0 + wave + i * TW; };
     // key of row i of 16-key half h: fp32 in order; bf16 so that register pairs of the two halves are 8 keys in a row
     auto key_of = [&](int h, int i) { return F32 ? 16 * h + i : 8 * (i >> 2) + 4 * h + (i & 3); };
     // Part `part` of group g to LDS, in pieces of 1 KB; a row's 16-byte chunks are permuted so that 16 rows' chunks of one
     // column fall into 16 different bank groups.
-    auto issue_k = [&](int g, int part) {
+    auto issue_k = [&](int i, int part) {
+        const int g = group_of(i);
 #pragma unroll
         for (int l = 0; l < L::NK; ++l) {
             const int at = 1024 * l + 16 * lane, row = at / L::KROW, c = (at % L::KROW) >> 4, r = part * L::KG + row;
@@ -527,7 +547,8 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
             fc_load_lds16(src + 16 * (c ^ L::template swizzle<L::KROW>(row)), kbuf + 1024 * l);
         }
     };
-    auto issue_v = [&](int g, int part) {
+    auto issue_v = [&](int i, int part) {
+        const int g = group_of(i);
         const unsigned char *vt = (const unsigned char *)(vc + (size_t)(g >> 1) * (FC_VTILE * DH) + 32 * (g & 1) + L::VG * part);
 #pragma unroll
         for (int l = 0; l < L::NVL; ++l) {
@@ -543,20 +564,45 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
             for (int k = 0; k < NKB; ++k)
                 kd[h][k] = *(const frag *)(kc + (size_t)(32 * g + key_of(h, rho)) * DH + 4 * KB * k + KB * q);
     };
-    if (LDS && g0 + wave < g1) {
-        issue_k(g0 + wave, 0);
-        issue_v(g0 + wave, 0);
-        __builtin_amdgcn_sched_barrier(0);
+    // Queries (rows past the end take row 0's, their results are never stored): a wave brings 1 KB of them to LDS, ahead of its keys, and all
+    // read them there.  Loaded by every wave straight into registers they took a compute unit 0.86 us, a lane a clock.
+    auto query_row = [&](int at) {
+        const int row = at < G.g * p.A ? at : 0, hg = (int)p.by_a.over(row), a = row - hg * p.A;
+        return (const unsigned char *)p.Q + (((size_t)b * G.Hq + j * G.g + hg) * p.A + a) * L::KROW;
+    };
+    if (wave < L::NQ) {
+        const int at = 1024 * wave + 16 * lane, row = at / L::KROW, c = (at % L::KROW) >> 4;
+        const unsigned char *src = query_row(tile * (16 * QT) + row) + 16 * (c ^ L::template swizzle<L::KROW>(row));
+        unsigned char *dst = attn_smem + L::QAT + wave * L::QSTEP;
+        if (((uintptr_t)p.Q & 15) == 0) fc_load_lds16(src, dst);
+        else *(uint4 *)(dst + 16 * lane) = fc_load_any<uint4>(src);
     }
+    __builtin_amdgcn_sched_barrier(0);
+    if (n > 0) {
+        if (LDS) issue_k(0, 0);
+        else load_k(g0 + wave);
+        if (L::BEHIND) issue_v(0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        fc_wait_vm<!LDS ? 2 * NKB : L::BEHIND ? L::NK + L::NVL : L::NK, true>();
+    } else {
+        fc_wait_vm<0, true>();
+    }
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
     frag qf[QT][NKB];
 #pragma unroll
-    for (int u = 0; u < QT; ++u) {
-        const int row = tile * (16 * QT) + 16 * u + rho;
-        const bool ok = row < G.g * p.A;
-        const int hg = ok ? row / p.A : 0, a = ok ? row - hg * p.A : 0;
-        const T *qr = (const T *)p.Q + (((size_t)b * G.Hq + j * G.g + hg) * p.A + a) * DH + KB * q;
+    for (int u = 0; u < QT; ++u)
 #pragma unroll
-        for (int s = 0; s < NKB; ++s) qf[u][s] = ok ? fc_load_any<frag>(qr + 4 * KB * s) : frag{};
+        for (int k = 0; k < NKB; ++k) {
+            const int row = 16 * u + rho, at = row * L::KROW + 16 * ((4 * k + q) ^ L::template swizzle<L::KROW>(row));
+            qf[u][k] = *(const frag *)(attn_smem + L::QAT + (at >> 10) * L::QSTEP + (at & 1023));
+        }
+    fc_wait_lds();
+    if constexpr (!L::BEHIND) {  // (without LDS: the areas are written at the end only, by then every wave may be past its reads)
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        if (LDS && n > 0) issue_v(0, 0);
+        __builtin_amdgcn_sched_barrier(0);
     }
     f32x4 o[QT][ND];
     float m[QT], l[QT];
@@ -567,9 +613,9 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
         m[u] = -INFINITY;
         l[u] = 0.f;
     }
-    if (!LDS && g0 + wave < g1) load_k(g0 + wave);
-    for (int g = g0 + wave; g < g1; g += TW) {
-        const bool more = g + TW < g1;
+    for (int i = 0; i < n; ++i) {
+        const int g = group_of(i), half = halves && i == rounds ? wave & 1 : -1;  // -1: both
+        const bool more = i + 1 < n;
         if constexpr (!LDS) {
             const T *vt = vc + (size_t)(g >> 1) * (FC_VTILE * DH) + 32 * (g & 1);
 #pragma unroll
@@ -597,15 +643,26 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
                         kf[h][k] = *(const frag *)(kbuf + (16 * h + rho) * L::KROW + 16 * ((4 * k + q) ^ L::template swizzle<L::KROW>(16 * h + rho)));
                 fc_wait_lds();  // lgkmcnt(0): the area may be overwritten
                 __builtin_amdgcn_sched_barrier(0);
-                if (part + 1 < 32 / L::KG) issue_k(g, part + 1);
-                else if (more) issue_k(g + TW, 0);
+                if (part + 1 < 32 / L::KG) issue_k(i, part + 1);
+                else if (more) issue_k(i + 1, 0);
                 __builtin_amdgcn_sched_barrier(0);
+                auto scores = [&](auto first, auto last) {  // 16-key halves first .. last - 1 of the part
 #pragma unroll
-                for (int k = 0; k < NKB; ++k)
+                    for (int k = 0; k < NKB; ++k)
 #pragma unroll
-                    for (int u = 0; u < QT; ++u)
+                        for (int u = 0; u < QT; ++u)
 #pragma unroll
-                        for (int h = 0; h < L::KG / 16; ++h) s[u][part * (L::KG / 16) + h] = O::mfma(kf[h][k], qf[u][k], s[u][part * (L::KG / 16) + h]);
+                            for (int h = decltype(first)::value; h < decltype(last)::value; ++h)
+                                s[u][part * (L::KG / 16) + h] = O::mfma(kf[h][k], qf[u][k], s[u][part * (L::KG / 16) + h]);
+                };
+                const std::integral_constant<int, 0> c0;
+                const std::integral_constant<int, 1> c1;
+                const std::integral_constant<int, L::KG / 16> c2;
+                if (!F32 || half < 0) scores(c0, c2);
+                else if (L::KG == 16) {
+                    if (half == part) scores(c0, c1);
+                } else if (half == 0) scores(c0, c1);
+                else scores(c1, c2);
             }
         } else {
 #pragma unroll
@@ -615,6 +672,15 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
 #pragma unroll
                     for (int k = 0; k < NKB; ++k) s[u][h] = O::mfma(kd[h][k], qf[u][k], s[u][h]);
             if (more) load_k(g + TW);  // the next group's keys travel behind the softmax and the output products
+        }
+        if (F32 && LDS && half >= 0) {
+#pragma unroll
+            for (int u = 0; u < QT; ++u)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    if (half == 1) s[u][0][r] = -INFINITY;
+                    else s[u][1][r] = -INFINITY;
+                }
         }
         const bool past = 32 * g + 32 > p.kv_len;  // keys past the end may hold anything: no score, and zero values (0 * V stays 0)
         if (past) {
@@ -675,8 +741,8 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
                         vf[d][h] = *(const frag *)(vbuf + (16 * d + rho) * L::VROW + 16 * ((4 * h + q) ^ L::template swizzle<L::VROW>(16 * d + rho)));
                 fc_wait_lds();
                 __builtin_amdgcn_sched_barrier(0);
-                if (part + 1 < 32 / L::VG) issue_v(g, part + 1);
-                else if (more) issue_v(g + TW, 0);
+                if (part + 1 < 32 / L::VG) issue_v(i, part + 1);
+                else if (more) issue_v(i + 1, 0);
                 __builtin_amdgcn_sched_barrier(0);
                 if (past) {
 #pragma unroll
@@ -688,11 +754,13 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
                                 if (32 * g + L::VG * part + (F32 ? 16 * h : 0) + KB * q + e >= p.kv_len) vf[d][h][e] = {};
                 }
 #pragma unroll
-                for (int u = 0; u < QT; ++u)
+                for (int h = 0; h < (F32 ? NVP : NP); ++h) {
+                    if (F32 && half >= 0 && half != NVP * part + h) continue;
 #pragma unroll
-                    for (int d = 0; d < ND; ++d)
+                    for (int u = 0; u < QT; ++u)
 #pragma unroll
-                        for (int h = 0; h < (F32 ? NVP : NP); ++h) o[u][d] = O::mfma(vf[d][F32 ? h : 0], pf[u][F32 ? NVP * part + h : h], o[u][d]);
+                        for (int d = 0; d < ND; ++d) o[u][d] = O::mfma(vf[d][F32 ? h : 0], pf[u][F32 ? NVP * part + h : h], o[u][d]);
+                }
             }
         } else {
             if (past) {
@@ -1000,6 +1068,7 @@ hipError_t launch_tile_u(TileArgs a, int n_tiles, hipStream_t s)
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)BYTES);
     if (attr != hipSuccess) return attr;
     a.n_blocks = (n_tiles + NT - 1) / NT;
+    a.by_blocks.set(a.n_blocks);
     const int64_t grid = (int64_t)a.n_blocks * ((a.M + 16 * MT - 1) / (16 * MT));
     if (grid > INT32_MAX) return hipErrorInvalidValue;
     k_linear_tile<T, NT, MT, U, EPI, LDS><<<dim3((unsigned)grid), dim3(TW * 64), BYTES, s>>>(a);
@@ -1055,7 +1124,7 @@ hipError_t launch_tile(int dtype, const TileArgs &a, int n_tiles, hipStream_t s)
 template <typename T, int DH, int QT, int DS, bool LDS>
 hipError_t launch_attn_tile(const AttnTileArgs &a, hipStream_t s)
 {
-    constexpr size_t BYTES = (size_t)TW * AttnTileLds<T, DH, QT, DS, LDS>::WAVE;
+    constexpr size_t BYTES = AttnTileLds<T, DH, QT, DS, LDS>::BYTES;
     static hipError_t attr = hipFuncSetAttribute((const void *)k_attn_tile<T, DH, QT, DS, LDS>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)BYTES);
     if (attr != hipSuccess) return attr;
@@ -1102,6 +1171,7 @@ hipError_t fc_launch_project_tile(const FcGeom &G, const double *inv_freq, int d
     a.pos = pos;
     a.win_start = win_start;
     a.A = A;
+    a.by_a.set(A);
     a.Kc = k_layer;
     a.Vc = v_layer;
     memcpy(a.inv_freq, inv_freq, sizeof a.inv_freq);
@@ -1161,6 +1231,10 @@ hipError_t fc_launch_attention_tile(const FcGeom &G, const FcAttnPlan &pl, int d
     a.splits = pl.splits;
     a.groups_per_split = pl.keys_per_split / 32;
     a.c = G.scale * 1.4426950408889634f;
+    a.by_splits.set(a.splits);
+    a.by_tiles.set(a.tiles);
+    a.by_hkv.set(G.Hkv);
+    a.by_a.set(A);
     if (pl.splits > 1) {
         if (!workspace) return hipErrorInvalidValue;
         a.part_o = (float *)workspace;
