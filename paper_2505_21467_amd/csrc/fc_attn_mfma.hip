@@ -48,8 +48,11 @@ struct AttnArgs {
     int B, Hq, Hkv, g, A, kv_len, spad, max_seq;
     int row_tiles, n_rg, splits, keys_per_split, n_units;
     float c;              // softmax scale * log2(e)
-    uint32_t div_pair, div_hkv, div_a;  // reciprocals: see launch_groups, launch_ranges
+    uint32_t div_pair, div_hkv, div_a;  // k_attn_groups: reciprocals (its launch bounds what they divide)
     bool once;            // k_attn_ranges: keys and values with the non-temporal hint
+    // k_attn_ranges and k_attn_combine, any size; five divisions ahead of the first load took 0.3 us of a call.  (In k_attn_groups, which
+    // has its quotients for a multiply each, these cost 0.2 us more: three arguments and four instructions more apiece.)
+    FcDivisor by_rg, by_splits, by_tiles, by_hkv, by_a;
 };
 
 // Lanes l and l^32 hold the two halves of a query row.  v_permlane32_swap exchanges the upper 32
@@ -121,16 +124,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
     const int64_t n_tiles = (int64_t)p.n_units * p.n_rg;
     const int tile = (int)(xcd * n_tiles / 8) + qd;
     if (tile >= (int)((xcd + 1) * n_tiles / 8)) return;
-    const int unit = tile / p.n_rg, rg = tile - unit * p.n_rg;
-    const int bj = unit / p.splits, split = unit - bj * p.splits;
-    const int b = bj / p.Hkv, j = bj - b * p.Hkv;
+    const int unit = (int)p.by_rg.over(tile), rg = tile - unit * p.n_rg;
+    const int bj = (int)p.by_splits.over(unit), split = unit - bj * p.splits;
+    const int b = (int)p.by_hkv.over(bj), j = bj - b * p.Hkv;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rho = lane & 15, q = lane >> 4;
     const int nrows = p.g * p.A;
     const int row0 = (rg * NW + wave) * (16 * QT);  // first query row of this wave
-    auto head_of = [&](int row) { return p.div_a == 1 ? row / p.A : (int)fc_quotient(row, p.div_a); };
+    auto head_of = [&](int row) { return (int)p.by_a.over(row); };
 
     // ---- query rows (past the end: the last row, never stored)
     bf16x8 qf[QT][4];
@@ -700,9 +703,8 @@ __global__ __launch_bounds__(64 * NWV) void k_attn_combine(AttnArgs p)
     const int q2 = blockIdx.x & 7;           // slot
     const int col = 16 * (q2 >> 2) + (lane & 15);
     const size_t tg = blockIdx.x >> 3;       // (b * Hkv + j) * row_tiles + rt
-    const int rt = (int)(tg % p.row_tiles);
-    const int bj = (int)(tg / p.row_tiles);
-    const int b = bj / p.Hkv, j = bj % p.Hkv;
+    const int bj = (int)p.by_tiles.over(blockIdx.x >> 3), rt = (int)(blockIdx.x >> 3) - bj * p.row_tiles;
+    const int b = (int)p.by_hkv.over(bj), j = bj - b * p.Hkv;
     const uint4 *po = (const uint4 *)p.part_o + tg * p.splits * (8 * 64) + q2 * 64 + lane;
     const float4 *ml = (const float4 *)p.part_ml + tg * p.splits * 32 + col;
 
@@ -766,7 +768,7 @@ __global__ __launch_bounds__(64 * NWV) void k_attn_combine(AttnArgs p)
 
     const int rho = rt * 32 + col;
     if (rho >= p.g * p.A) return;  // row past the end of the last tile
-    const int hg = rho / p.A, a = rho - hg * p.A;
+    const int hg = (int)p.by_a.over(rho), a = rho - hg * p.A;
     const int hq = j * p.g + hg;
     const bool padded = row_is_padded(p.pos, b * p.A + a, p.max_seq);
     uint16_t *orow = p.out + ((size_t)b * p.A + a) * ((size_t)p.Hq * DH) + (size_t)hq * DH;
@@ -786,7 +788,6 @@ hipError_t launch_ranges(AttnArgs a, hipStream_t s)
 {
     constexpr int STAGING = NW * QT * 16 * OROW * 4, LDS_BYTES = STAGING > 8 * K_BYTES ? STAGING : 8 * K_BYTES;
     static_assert(LDS_BYTES <= 160 * 1024, "LDS");
-    a.div_a = (int64_t)a.g * a.A * a.A < ((int64_t)1 << 32) ? fc_reciprocal(a.A) : 1;  // 1: too many rows for a reciprocal
     auto start = [&](auto once) {
         constexpr auto kernel = k_attn_ranges<QT, NW, decltype(once)::value>;
         static hipError_t attr = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
@@ -849,6 +850,11 @@ hipError_t fc_launch_attention_mfma(const FcGeom &G, const FcAttnPlan &pl, const
     a.n_units = G.B * G.Hkv * pl.splits;
     a.once = G.once && a.n_rg == 1;
     a.c = G.scale * 1.4426950408889634f;
+    a.by_rg.set(a.n_rg);
+    a.by_splits.set(pl.splits);
+    a.by_tiles.set(pl.row_tiles);
+    a.by_hkv.set(G.Hkv);
+    a.by_a.set(A);
     hipError_t e;
     const int R = pl.tiles_per_wg;
     if (pl.kind == 2) {  // all keys in one launch

@@ -57,6 +57,7 @@ struct GemmArgs {
     int N;                 // output columns
     bool once;             // weights with the non-temporal hint, where there is one tile of rows
     int ksplit;            // EPI 3: parts the hidden dimension is cut into
+    FcDivisor by_mt, by_parts, by_a;  // n_mt, ksplit, A
     FcArgmaxPart am;       // EPI 4: per (slab, row) largest logit, its index, sum of exponentials
 };
 
@@ -151,7 +152,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x4 (&acc)[MT
         if (EPI == 0) {
             const int m = m_i + lane % ROWS;
             if (m < p.m_end) {
-                b_l = m / p.A;
+                b_l = (int)p.by_a.over(m);
                 a_l = m - b_l * p.A;
                 pp_l = p.pos ? p.pos[m] : p.win_start + a_l;
                 if (pp_l >= G.max_seq) pp_l = -1;
@@ -445,9 +446,9 @@ __device__ __forceinline__ bool tile_place(const GemmArgs &p, TilePlace &w)
     const int64_t n_tiles = (int64_t)p.n_units * p.n_mt * n_kp;
     const int tile_k = (int)(xcd * n_tiles / 8) + qd;
     if (tile_k >= (int)((xcd + 1) * n_tiles / 8)) return false;
-    const int tile = tile_k / n_kp;
+    const int tile = EPI == 3 ? (int)p.by_parts.over(tile_k) : tile_k;
     w.kpart = tile_k - tile * n_kp;
-    w.unit = tile / p.n_mt;
+    w.unit = (int)p.by_mt.over(tile);
     w.mt = tile - w.unit * p.n_mt;
     return true;
 }
@@ -492,8 +493,8 @@ __global__ __launch_bounds__((NW + NL) * 64) __attribute__((amdgpu_waves_per_eu(
 
     // part of the hidden dimension this workgroup covers (EPI 3 only: part kpart of p.ksplit)
     const int all_stages = p.K / KS;
-    const int st0 = EPI == 3 ? (int)((int64_t)at.kpart * all_stages / p.ksplit) : 0;
-    const int n_stages = EPI == 3 ? (int)(((int64_t)at.kpart + 1) * all_stages / p.ksplit) - st0 : all_stages;
+    const int st0 = EPI == 3 ? (int)p.by_parts.over((uint32_t)(at.kpart * all_stages)) : 0;
+    const int n_stages = EPI == 3 ? (int)p.by_parts.over((uint32_t)((at.kpart + 1) * all_stages)) - st0 : all_stages;
     unsigned char *bias_area = smem + SLOTS * STAGE;  // behind the ring
 
     if (wave >= NW) {
@@ -718,8 +719,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
     // part of the hidden dimension this workgroup covers (EPI 3 only: part kpart of p.ksplit)
     const int all_stages = p.K / 64;
-    const int st0 = EPI == 3 ? (int)((int64_t)at.kpart * all_stages / p.ksplit) : 0;
-    const int n_stages = EPI == 3 ? (int)(((int64_t)at.kpart + 1) * all_stages / p.ksplit) - st0 : all_stages;
+    const int st0 = EPI == 3 ? (int)p.by_parts.over((uint32_t)(at.kpart * all_stages)) : 0;
+    const int n_stages = EPI == 3 ? (int)p.by_parts.over((uint32_t)((at.kpart + 1) * all_stages)) - st0 : all_stages;
     auto load_w = [&](int st, int slot, int i) {
         const bool up = EPI == 2 && 8 * (wave + 4 * i) % (16 * NT) >= 8 * NT;  // (whole blocks)
         const unsigned char *src = (const unsigned char *)(up ? p.W2 : p.W) + (size_t)(st0 + st) * 128;
@@ -851,6 +852,9 @@ unsigned set_tiles(GemmArgs &a, int pairs, int rows)
         return 0;
     a.n_units = (int)(((int64_t)a.slots_here * 64 + pairs - 1) / pairs);
     a.n_mt = (a.m_end - a.m_base + rows - 1) / rows;
+    a.by_mt.set(a.n_mt);
+    a.by_parts.set(a.ksplit);
+    a.by_a.set(a.A);
     const int64_t n_tiles = (int64_t)a.n_units * a.n_mt * (EPI == 3 ? a.ksplit : 1);
     return n_tiles > (1 << 30) ? 0 : (unsigned)((n_tiles + 7) / 8 * 8);
 }
