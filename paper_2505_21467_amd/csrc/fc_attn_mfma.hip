@@ -22,6 +22,7 @@
 
 namespace {
 
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
@@ -705,22 +706,32 @@ __global__ __launch_bounds__(64 * NWV) void k_attn_combine(AttnArgs p)
     const size_t tg = blockIdx.x >> 3;       // (b * Hkv + j) * row_tiles + rt
     const int bj = (int)p.by_tiles.over(blockIdx.x >> 3), rt = (int)(blockIdx.x >> 3) - bj * p.row_tiles;
     const int b = (int)p.by_hkv.over(bj), j = bj - b * p.Hkv;
-    const uint4 *po = (const uint4 *)p.part_o + tg * p.splits * (8 * 64) + q2 * 64 + lane;
+    const u32x4 *po = (const u32x4 *)p.part_o + tg * p.splits * (8 * 64) + q2 * 64 + lane;
     const float4 *ml = (const float4 *)p.part_ml + tg * p.splits * 32 + col;
+
+    const int rho = rt * 32 + col, row = min(rho, p.g * p.A - 1);
+    const int hg = (int)p.by_a.over(row), a = row - hg * p.A;
+    const int pos = p.pos ? p.pos[b * p.A + a] : 0;
 
     float m_run = -INFINITY, den = 0.f;
     float num[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) num[e] = 0.f;
     for (int sb = s_lo; sb < s_hi; sb += CB) {
-        uint4 v[CB];
+        u32x4 v[CB];
         float4 mlv[CB];  // (max in the log2 domain, sum, exponent of the half-float scaling, -)
 #pragma unroll
         for (int u = 0; u < CB; ++u) {
             const int s = min(sb + u, s_hi - 1);
             v[u] = po[(size_t)s * (8 * 64)];
-            mlv[u] = ml[(size_t)s * 32];
         }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < CB; ++u) mlv[u] = ml[(size_t)min(sb + u, s_hi - 1) * 32];
+        __builtin_amdgcn_sched_barrier(0);
+        // (left to itself the compiler asks for half of these, waits for them, and asks for the other half then)
+#pragma unroll
+        for (int u = 0; u < CB; ++u) asm volatile("" : "+v"(v[u]));
         float mb = mlv[0].x;
 #pragma unroll
         for (int u = 1; u < CB; ++u) mb = fmaxf(mb, mlv[u].x);
@@ -734,7 +745,7 @@ __global__ __launch_bounds__(64 * NWV) void k_attn_combine(AttnArgs p)
             // weight of the split's sum; its stored values are (partial / sum) * 2^k
             const float w = (sb + u < s_hi) ? __builtin_amdgcn_exp2f(mlv[u].x - m_new) * mlv[u].y : 0.f;
             const float wn = __builtin_amdgcn_ldexpf(w, -(int)mlv[u].z);
-            union { uint4 u4; _Float16 h[8]; } x;
+            union { u32x4 u4; _Float16 h[8]; } x;
             x.u4 = v[u];
 #pragma unroll
             for (int e = 0; e < 8; ++e) num[e] += wn * (float)x.h[e];
@@ -766,11 +777,9 @@ __global__ __launch_bounds__(64 * NWV) void k_attn_combine(AttnArgs p)
         }
     }
 
-    const int rho = rt * 32 + col;
     if (rho >= p.g * p.A) return;  // row past the end of the last tile
-    const int hg = (int)p.by_a.over(rho), a = rho - hg * p.A;
     const int hq = j * p.g + hg;
-    const bool padded = row_is_padded(p.pos, b * p.A + a, p.max_seq);
+    const bool padded = p.pos && (pos < 0 || pos >= p.max_seq);
     uint16_t *orow = p.out + ((size_t)b * p.A + a) * ((size_t)p.Hq * DH) + (size_t)hq * DH;
 #pragma unroll
     for (int g2 = 0; g2 < 2; ++g2) {

@@ -832,17 +832,19 @@ __global__ __launch_bounds__(256) void k_attn_tile_merge(AttnTileArgs p)
     const size_t at = (size_t)bt * p.splits * (QT * 16) + row;
     float mm = -INFINITY, den = 0.f;
     float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int s0 = 0; s0 < p.splits; s0 += 4) {  // four ranges' loads in flight together
-        float2 ml[4];
-        float4 v[4];
+    constexpr int U = 8;  // ranges whose loads are in flight together
+    for (int s0 = 0; s0 < p.splits; s0 += U) {
+        float2 ml[U];
+        float4 v[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < U; ++u) {
             const size_t as = at + (size_t)min(s0 + u, p.splits - 1) * (QT * 16);
             ml[u] = *(const float2 *)(p.part_ml + as * 2);
             v[u] = *(const float4 *)(p.part_o + as * DH + d0);
         }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < U; ++u) {
             if (s0 + u >= p.splits) break;
             const float m_new = fmaxf(mm, ml[u].x);
             const float k0 = __builtin_amdgcn_exp2f((mm - m_new) * p.c), k1 = __builtin_amdgcn_exp2f((ml[u].x - m_new) * p.c);
@@ -854,7 +856,8 @@ __global__ __launch_bounds__(256) void k_attn_tile_merge(AttnTileArgs p)
             num.w = num.w * k0 + v[u].w * k1;
         }
     }
-    attn_store_row4<T>(p, bt / p.tiles, (bt % p.tiles) * (16 * QT) + row, d0,
+    const int bj = (int)p.by_tiles.over(bt);
+    attn_store_row4<T>(p, bj, (bt - bj * p.tiles) * (16 * QT) + row, d0,
                        make_float4(num.x / den, num.y / den, num.z / den, num.w / den));
 }
 

@@ -576,10 +576,15 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     };
     auto task_row = [&](int j) { return 4 * ((wave + 8 * j) % (4 * MT)) + q; };
     auto task_col = [&](int j) { return 16 * ((wave + 8 * j) / (4 * MT)) + rho; };
-    uint16_t res[TASKS];
+    // Residuals, all under way at once and waited for with the first stage (as 16-bit values, each behind its own test of the
+    // pointer, the compiler waited for them one by one: eight trips to memory ahead of the weights in the tile of 64 rows).
+    uint32_t res[TASKS];
 #pragma unroll
-    for (int j = 0; j < (MODE == FC_LIN_RESIDUAL ? TASKS : 0); ++j)
-        res[j] = MODE == FC_LIN_RESIDUAL && p.res ? p.res[(size_t)min(m0 + task_row(j), p.M - 1) * p.N + n0 + min(task_col(j), R - 1)] : 0;
+    for (int j = 0; j < TASKS; ++j) res[j] = 0;
+    if (MODE == FC_LIN_RESIDUAL && p.res) {
+#pragma unroll
+        for (int j = 0; j < TASKS; ++j) res[j] = p.res[(size_t)min(m0 + task_row(j), p.M - 1) * p.N + n0 + min(task_col(j), R - 1)];
+    }
     __builtin_amdgcn_sched_barrier(0);
     issue(0);
     __builtin_amdgcn_sched_barrier(0);
@@ -663,7 +668,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
             for (int f = 0; f < NF; ++f) y[f] += *(const float *)(part + w2 * p.wave_bytes + f * 1280);
         if (m >= p.M || c >= R) continue;
-        p.out[(size_t)m * p.N + n0 + c] = fc_bf16_bits(MODE == FC_LIN_GATE_UP ? y[0] / (1.0f + expf(-y[0])) * y[NF - 1] : y[0] + fc_to_float(bf16_t{res[j]}));
+        asm volatile("" : "+v"(res[j]));  // (its conversion stays here: ahead of the loop it would wait there)
+        p.out[(size_t)m * p.N + n0 + c] = fc_bf16_bits(MODE == FC_LIN_GATE_UP ? y[0] / (1.0f + expf(-y[0])) * y[NF - 1] : y[0] + __uint_as_float(res[j] << 16));
     }
 }
 

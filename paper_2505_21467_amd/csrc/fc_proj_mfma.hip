@@ -385,18 +385,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int row0 = (g0 >> 6) * 128 + (g0 & 63);
     const unsigned char *wbase = (const unsigned char *)(p.W + (size_t)row0 * p.K) + (size_t)wave * n_stages * 128;
     const unsigned char *xbase = (const unsigned char *)p.X + (size_t)wave * n_stages * 128;
+    // A run has fewer than 64 pairs and meets the end of a head once at most, at pair `turn`: 64 rows on from there, as for the partners.
+    const int turn = 64 - (g0 & 63);
+    const uint32_t chunk = (uint32_t)((lane & 7) ^ (lane >> 4)) << 4;  // swizzled by bits 1..3 of the row
     uint32_t woff[4 * NP], xoff[2 * MT];
 #pragma unroll
     for (int i = 0; i < 4 * NP; ++i) {
-        const int r = min(8 * i + (lane >> 3), 2 * R - 1), gp = g0 + (r < R ? r : r - R);
-        const int row = (gp >> 6) * 128 + (gp & 63) + (r < R ? 0 : 64) - row0;
-        woff[i] = (uint32_t)row * (uint32_t)(2 * p.K) + (((lane & 7) ^ ((8 * i + (lane >> 3)) >> 1 & 7)) << 4);
+        const int r = min(8 * i + (lane >> 3), 2 * R - 1), e = r < R ? r : r - R;
+        const int row = e + (e < turn ? 0 : 64) + (r < R ? 0 : 64);
+        woff[i] = __umul24(row, 2 * p.K) + (chunk ^ (i & 1) << 6);
     }
 #pragma unroll
-    for (int i = 0; i < 2 * MT; ++i) {
-        const int r = 8 * i + (lane >> 3);
-        xoff[i] = (uint32_t)min(m0 + r, p.M - 1) * (uint32_t)(2 * p.K) + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
-    }
+    for (int i = 0; i < 2 * MT; ++i) xoff[i] = (uint32_t)min(m0 + 8 * i + (lane >> 3), p.M - 1) * (uint32_t)(2 * p.K) + (chunk ^ (i & 1) << 6);
     const int turn0 = p.K % 4096 == 0 ? (run >> 3) & 7 : 0;  // n_stages is a multiple of 8 there
     auto issue = [&](int st) {
         st += turn0;
@@ -413,15 +413,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // bias are asked for first; the first task's angle comes while the last stage is on its way.
     constexpr int TASKS = (NP * MT + 1) / 2;
     int pp[TASKS];
-    uint16_t bs[TASKS][2];
+    uint32_t bs[TASKS][2];  // (as 16 bits the compiler packs a pair, and waits for both here: a trip to HBM ahead of the weights)
     auto task_row = [&](int j) { return 4 * ((wave + 8 * j) % (4 * MT)) + q; };
     auto task_pair = [&](int j) { return 16 * ((wave + 8 * j) / (4 * MT)) + rho; };
 #pragma unroll
     for (int j = 0; j < TASKS; ++j) {
-        const int mm = min(m0 + task_row(j), p.M - 1), gp = g0 + min(task_pair(j), R - 1);
+        const int mm = min(m0 + task_row(j), p.M - 1);
         pp[j] = p.pos ? p.pos[mm] : p.win_start + mm - (int)fc_quotient(mm, p.div_a) * p.A;
         bs[j][0] = bs[j][1] = 0;
-        if (p.bias) {
+    }
+    if (p.bias) {
+#pragma unroll
+        for (int j = 0; j < TASKS; ++j) {
+            const int gp = g0 + min(task_pair(j), R - 1);
             bs[j][0] = p.bias[(gp >> 6) * 128 + (gp & 63)];
             bs[j][1] = p.bias[(gp >> 6) * 128 + (gp & 63) + 64];
         }
@@ -504,8 +508,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         }
         if (m >= p.M || pr >= R) continue;
         const int gp = g0 + pr, hs = gp >> 6, i = gp & 63;
-        y0 += fc_to_float(bf16_t{bs[j][0]});
-        y1 += fc_to_float(bf16_t{bs[j][1]});
+        asm volatile("" : "+v"(bs[j][0]), "+v"(bs[j][1]));  // (their conversion stays here: ahead of the loop it would wait there)
+        y0 += __uint_as_float(bs[j][0] << 16);
+        y1 += __uint_as_float(bs[j][1] << 16);
         if (hs < G.Hq + G.Hkv) {
             const float turn = j ? angle(j) : first_angle;
             const float cs = __builtin_amdgcn_cosf(turn), sn = __builtin_amdgcn_sinf(turn);

@@ -91,7 +91,10 @@ __global__ __launch_bounds__(NW * 64) void k_unmask_select(const int32_t *__rest
         if (a < A) {
             const int p = position(a), t = tok[at + a];
             const float cv = conf[at + a];
-            if (p >= 0 && p < L && seq[p] == mask_id) c = cv;
+            const bool inside = p >= 0 && p < L;
+            const int now = seq[inside ? p : 0];  // (asked for with the others, not behind a test)
+            __builtin_amdgcn_sched_barrier(0);
+            if (inside && now == mask_id) c = cv;
             if (a == tid) {
                 p0 = p;
                 t0 = t;
