@@ -81,7 +81,7 @@ const char *fc_last_error(void);
  * value NULL restores the default.  Names: FC_ATTN_TILES ("R,W": row tiles and waves per attention
  * workgroup), FC_ATTN_WGS, FC_LIN_WGS, FC_ACCEPT_WGS (target workgroup counts), FC_LIN_NO_ROWS,
  * FC_GEMM_NO_SPLIT, FC_PROJ_NO_HEADSPLIT (any value switches the named path off), FC_LIN_WIDE_SHAPE,
- * FC_PROJ_GEMM_SHAPE (0..10: one GEMM tile shape for everything), FC_LIN_KSPLIT (parts of the hidden
+ * FC_PROJ_GEMM_SHAPE (0..11: one GEMM tile shape for everything), FC_LIN_KSPLIT (parts of the hidden
  * dimension).  Host only; not thread-safe against concurrent calls into the library; workspace sizes
  * depend on the knobs, so query them after setting.
  * Errors: INVALID_ARG (NULL or unknown name). */

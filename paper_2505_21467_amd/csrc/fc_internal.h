@@ -45,10 +45,10 @@ struct FcKnobs {
     int attn_wgs;           // FC_ATTN_WGS=n          workgroups the split heuristic aims for
     int lin_wgs;            // FC_LIN_WGS=n           workgroups of the weight-streaming linear kernels
     int lin_no_rows;        // FC_LIN_NO_ROWS         slice-wise instead of whole-row weight streaming
-    int lin_wide_shape;     // FC_LIN_WIDE_SHAPE=0..10 (4..8: gated layer only) one tile shape for the tiled linear GEMM (-1 = planned)
+    int lin_wide_shape;     // FC_LIN_WIDE_SHAPE=0..11 (4..8, 11: gated layer only) one tile shape for the tiled linear GEMM (-1 = planned)
     int lin_ksplit;         // FC_LIN_KSPLIT=n        parts of the hidden dimension
     int gemm_no_split;      // FC_GEMM_NO_SPLIT       never cut a GEMM into two launches
-    int proj_gemm_shape;    // FC_PROJ_GEMM_SHAPE=0..10 one tile shape for the projection GEMM (-1 = planned)
+    int proj_gemm_shape;    // FC_PROJ_GEMM_SHAPE=0..11 one tile shape for the projection GEMM (-1 = planned)
     int proj_no_headsplit;  // FC_PROJ_NO_HEADSPLIT   short-window projection without the head-split kernels
     int version;            // changes with every fc_tuning_set
     int accept_wgs;         // FC_ACCEPT_WGS=n        workgroups of the acceptance scan

@@ -5,7 +5,7 @@
 // Y^T = W X^T: the weight rows are the A operand of v_mfma_f32_16x16x32_bf16 and the window rows the B
 // operand, so a lane of the accumulator holds four output features of ONE window row.  The weight rows go by pairs -- the two
 // members of a rotary pair, or gate and up row -- and the pairs of all slabs, laid end to end, are dealt to the workgroups in
-// equal runs: 128, 80, 64, 48 or 32 pairs, so that a grid a little over one round of workgroups in one width fits a round in another.
+// equal runs: 128, 96, 80, 64, 48 or 32 pairs, so that a grid a little over one round of workgroups in one width fits a round in another.
 //
 // Both operands are contiguous along the hidden dimension.  64 (or 128) hidden elements of every row
 // of the tile (128- or 256-byte row pieces) stream HBM/L2 -> LDS with direct-to-LDS 16-byte loads into
@@ -654,8 +654,8 @@ __global__ __launch_bounds__((NW + NL) * 64) __attribute__((amdgpu_waves_per_eu(
 }
 
 // -------------------------------------------------------------------------------------------------
-// 256 window rows: four waves, one per SIMD, WN of them along the weight rows, each with MT x NT tiles of 16 x 16 (128 x 128, 128 x 80
-// or 64 x 128).
+// 256 window rows: four waves, one per SIMD, WN of them along the weight rows, each with MT x NT tiles of 16 x 16 (128 x 128, 128 x 96,
+// 128 x 80 or 64 x 128).
 //
 // One wave per SIMD keeps up to 256 accumulators and reads the fewest operand bytes from LDS: 131 KB per 64 hidden
 // elements of a 256 x 256 tile against 196 KB with eight waves of 64 x 128, which together with the 64 KB of loads is
@@ -986,6 +986,9 @@ hipError_t launch_shape(int shape, const GemmArgs &a, hipStream_t s)
     case 10:
         if constexpr (EPI == 4) return hipErrorInvalidValue;
         else return launch_gemm<64, 2, 2, 4, 4, EPI>(a, s);
+    case 11:
+        if constexpr (EPI == 0 || EPI == 2) return launch_wide<8, 6, 2, 3, 2, EPI>(a, s);
+        return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
     }
 }
@@ -1000,23 +1003,28 @@ hipError_t launch_shape(int shape, const GemmArgs &a, hipStream_t s)
 //   0: 256 rows x slab   1: 128 rows x slab   2: 128 rows x half slab   3: 256 rows x two slabs
 //   4: 256 rows x 80 dealt pairs   5: 128 rows x 48 dealt pairs
 //   6: 64 rows x 80 dealt pairs   7: 64 rows x 48 dealt pairs   8: 128 rows x 80 dealt pairs
-//   9: 64 rows x slab   10: 64 rows x half slab
+//   9: 64 rows x slab   10: 64 rows x half slab   11: 256 rows x 96 dealt pairs
+// 11 is for what fills one round in it and in no other, between the 160 and the 256 weight rows of 4 and 3 (us without and with): 36 head
+// slots, hidden 3584, 2100 / 2200 / 2304 rows 73.0 / 75.5 / 74.7 and 67.1 / 67.6 / 67.3; 96 slots, hidden 4096, 780 / 1000 rows 89.4 / 89.3 and 80.3 /
+// 80.6; gated 4096 x 12288, 260 / 400 rows 90.5 / 89.9 and 84.8 / 84.7, 3584 x 11008, 350 rows 76.4 and 68.9; 36 such problems 1.056 x in the mean. In
+// several rounds 3 is as good (fitted to those too, it was taken for 3584 x 18944, 2304 rows: 470 -> 484), so its further rounds are
+// set to cost what keeps it out of them.
 // 6 .. 10 are for few rows, where the weights alone should count: in the 128-row half slab, for 40 or 64 rows the shape with
 // the most tiles, the compute units pulled three bytes for every byte of weights (two thirds of them window rows, most
 // of those padding); 64 rows x 160 weight rows pull 1.4.  Gated W_1 of 18944 outputs at hidden 3584, 64 / 128 rows:
 // 65 / 80 us in the half slab, 44.7 / 50.3 in those (shapes 6 and 8; the weights alone 46 at 5.9 TB/s).
-constexpr int N_SHAPES = 11;
+constexpr int N_SHAPES = 12;
 struct ShapeCost {
     double least, first, further, start;
 };
 constexpr ShapeCost SHAPE_US[2][N_SHAPES] = {  // one row tile, several
     {{0.60, 0.87, 0.80, 0.75}, {0.41, 0.52, 0.66, 0.95}, {0.24, 0.36, 0.38, 0.87}, {0.85, 1.34, 1.36, 0.79},
      {0.63, 1.01, 1.04, 0.80}, {0.36, 0.45, 0.48, 0.95}, {0.47, 0.49, 0.67, 0.96}, {0.31, 0.31, 0.39, 1.00},
-     {0.58, 0.58, 0.79, 0.87}, {0.47, 0.47, 0.45, 0.93}, {0.21, 0.24, 0.25, 0.99}},
+     {0.58, 0.58, 0.79, 0.87}, {0.47, 0.47, 0.45, 0.93}, {0.21, 0.24, 0.25, 0.99}, {0.75, 1.17, 1.17, 0.80}},
     {{0.58, 0.82, 0.90, 0.59}, {0.50, 0.53, 0.58, 0.76}, {0.25, 0.34, 0.37, 0.79}, {1.07, 1.35, 1.52, 0.79},
      {0.77, 0.99, 1.05, 0.73}, {0.33, 0.43, 0.47, 0.85}, {0.46, 0.51, 0.53, 0.85}, {0.26, 0.35, 0.31, 0.70},
-     {0.55, 0.64, 0.70, 0.80}, {0.51, 0.51, 0.36, 0.67}, {0.17, 0.22, 0.22, 0.77}}};
-constexpr bool shape_dealt(int shape) { return shape >= 4 && shape <= 8; }
+     {0.55, 0.64, 0.70, 0.80}, {0.51, 0.51, 0.36, 0.67}, {0.17, 0.22, 0.22, 0.77}, {0.90, 1.16, 1.60, 0.90}}};
+constexpr bool shape_dealt(int shape) { return (shape >= 4 && shape <= 8) || shape == 11; }
 constexpr bool shape_half(int shape) { return shape == 2 || shape == 10; }
 
 int64_t tiles_of(int shape, int64_t slots, int64_t rows)
@@ -1033,6 +1041,7 @@ int64_t tiles_of(int shape, int64_t slots, int64_t rows)
     case 7: return (slots * 64 + 47) / 48 * t64;
     case 8: return (slots * 64 + 79) / 80 * t128;
     case 9: return slots * t64;
+    case 11: return (slots * 64 + 95) / 96 * t256;
     default: return 2 * slots * t64;
     }
 }
@@ -1041,7 +1050,7 @@ int64_t tiles_of(int shape, int64_t slots, int64_t rows)
 // joined by a 4-norm.
 double launch_cost(int shape, int64_t slots, int64_t rows)
 {
-    const int tile_rows = shape == 0 || shape == 3 || shape == 4 ? 256 : shape == 6 || shape == 7 || shape >= 9 ? 64 : 128;
+    const int tile_rows = shape == 0 || shape == 3 || shape == 4 || shape == 11 ? 256 : shape == 6 || shape == 7 || shape >= 9 ? 64 : 128;
     const bool several = rows > tile_rows;
     const ShapeCost c = SHAPE_US[several][shape];
     const int64_t n = tiles_of(shape, slots, rows), full = n / 256;

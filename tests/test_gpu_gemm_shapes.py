@@ -8,6 +8,7 @@ import torch
 from oracle import fc_oracle as orc
 from paper_2505_21467_amd import binding as fc
 from paper_2505_21467_amd import inputs
+from tests import test_gpu_read_once
 from tests.harness import assert_close
 from tests.test_gpu_parity import _compare_cache, _pair
 from tests.test_gpu_unmask import _check_lm_head
@@ -167,6 +168,24 @@ def test_value_rows_of_the_wide_tiles(shape, B, L, A, listed, knob):
     assert_close(inputs.as_oracle(Qg), Qo, dtype, "Q")
     _compare_cache(g, o, dtype, written=written, what="value rows")
     g.close()
+
+
+# The tile of 256 rows x 96 dealt pairs (shape 11): value rows as above, gated layers whose last run is short, and the non-temporal hint.
+@pytest.mark.parametrize("B,L,A,listed", [(1, 40, 64, False), (2, 43, 131, False), (1, 5, 79, False), (3, 61, 192, False), (2, 33, 128, True)])
+def test_runs_of_96_pairs_projection(B, L, A, listed, knob):
+    test_value_rows_of_the_wide_tiles(11, B, L, A, listed, knob)
+
+
+@pytest.mark.parametrize("M,K,N", [(1, 256, 64), (255, 320, 192), (257, 1088, 320), (600, 512, 576)])
+def test_runs_of_96_pairs_gated(M, K, N, knob):
+    knob("FC_LIN_WIDE_SHAPE", "11")
+    _linear(M, K, N, True, "gated, shape 11")
+
+
+@pytest.mark.parametrize("K", [1088, 1024])
+def test_runs_of_96_pairs_read_once(K, knob, monkeypatch):
+    monkeypatch.setitem(test_gpu_read_once.ROWS, 11, 200)
+    test_gpu_read_once.test_projection_in_every_tile_shape(11, K, knob)
 
 
 @pytest.mark.parametrize("M,N,gated", [
