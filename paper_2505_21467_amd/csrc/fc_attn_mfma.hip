@@ -23,6 +23,7 @@
 namespace {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
@@ -246,10 +247,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
 
     float t[8], e[8], sum = 0.f;
     bf16x8 pw;  // weights of the tile at hand (one tile: those of the block before are still being multiplied)
+    // The sum is of the weights as they are multiplied, so that what rounding does to a large one cancels.  (Against 64 bits, before rounding /
+    // this: scores of deviation 4, 32 rows, 9000 keys 2.33e-3 / 1.94e-3, 2 x 200 rows, 1500 keys 2.33e-3 / 1.89e-3, with an exact running
+    // maximum 1.74e-3 and 2.00e-3; of deviation 1 all three within 1 %.  It costs 0.5 to 1 % of a call.)
+    auto add_pair = [&](int j, float to) {
+        return __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pw[2 * j], pw[2 * j + 1]}, bf16x2{(__bf16)1.0f, (__bf16)1.0f}, to, false);
+    };
     auto weight_end = [&](int u) {
         pw[7] = (__bf16)e[7];
         pf[u] = pw;
-        l[u] += sum + e[7];
+        l[u] = add_pair(3, l[u] + sum);
     };
     auto mask_values = [&](int d, int base) {  // values of keys past the end may hold anything (also NaN): their weights are 0
         union { uint32_t w[4]; bf16x8 v; } x;
@@ -282,7 +289,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
                 if ((i & 1) == 0) {
                     t[k] = __builtin_fmaf(s[B][u][k >> 2][k & 3], c, nm[u]);
                     if (LAST) t[k] = base + k < k1 ? t[k] : -INFINITY;
-                    if (k >= 1) sum = k == 1 ? e[0] : sum + e[k - 1];
+                    if (k >= 3 && (k & 1)) sum = add_pair((k - 3) / 2, k == 3 ? 0.f : sum);
                 } else {
                     e[k] = __builtin_amdgcn_exp2f(t[k]);
                     if (k >= 1) pw[k - 1] = (__bf16)e[k - 1];
@@ -393,8 +400,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
 #pragma unroll
                 for (int r = 0; r < 8; ++r) {
                     const float w = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r >> 2][r & 3], c, to));
-                    part += w;
                     pf[u][r] = (__bf16)w;
+                    part += (float)pf[u][r];
                 }
                 l[u] += part;
 #pragma unroll
