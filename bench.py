@@ -76,15 +76,15 @@ MEASURED_LM_HEAD_TRAFFIC_BYTES = {(32, 3584, 152064): 1_092_170_000}
 # whose planner picks another plan reports null instead.
 MEASURED_ATTENTION_TRAFFIC = {
     "c4_dream7b_long_L16384_A32": {
-        "bytes": 53_010_000,   # 35.08 MB read + 7.31 MB written (main kernel), 10.39 + 0.23 MB (merge)
-        "plan": {"kind": 1, "splits": 30, "keys_per_split": 576, "tiles_per_wg": 4, "waves": 8},
-        "kernels": "k_attn_mfma<1,8,2> + k_attn_combine<8,4>",
-        "profile": "profiles/c4_long_context_layer_step.md"},
+        "bytes": 43_890_000,   # 35.12 MB read + 3.90 MB written (main kernel), 4.64 + 0.23 MB (merge)
+        "plan": {"kind": 1, "splits": 16, "keys_per_split": 1088, "tiles_per_wg": 2, "waves": 4},
+        "kernels": "k_attn_ranges<1,4> + k_attn_combine<8,2>",
+        "profile": "profiles/measured_cases.md"},
     "c3_llada8b_B4_L4096_A64": {
-        "bytes": 287_800_000,  # 274.9 + 4.46 MB, 6.34 + 2.10 MB
-        "plan": {"kind": 1, "splits": 2, "keys_per_split": 2112, "tiles_per_wg": 2, "waves": 8},
-        "kernels": "k_attn_mfma<1,8,4> + k_attn_combine<2,1>",
-        "profile": "profiles/other_workloads_layer_step.md"},
+        "bytes": 286_770_000,  # 274.92 + 4.46 MB, 5.29 + 2.10 MB
+        "plan": {"kind": 1, "splits": 2, "keys_per_split": 2112, "tiles_per_wg": 2, "waves": 4},
+        "kernels": "k_attn_ranges<1,4> + k_attn_combine<2,1>",
+        "profile": "profiles/measured_cases.md"},
 }
 
 
