@@ -80,9 +80,9 @@ struct FcDivisor {
     uint32_t mul, shift1, shift2;
     void set(uint32_t d)
     {
-        uint32_t l = 0;
-        while (((uint64_t)1 << l) < d) ++l;
-        mul = (uint32_t)((((((uint64_t)1 << l) - d) << 32) / d) + 1);
+        const uint32_t l = d > 1 ? 32 - (uint32_t)__builtin_clz(d - 1) : 0;  // 2^l is the first power of two from d on
+        const uint64_t more = ((uint64_t)1 << l) - d;
+        mul = more ? (uint32_t)((more << 32) / d + 1) : 1;
         shift1 = l < 1 ? l : 1;
         shift2 = l - shift1;
     }
