@@ -157,14 +157,17 @@ struct AttnShape {
     int R, W;
     double start, stage, full;
 };
-const AttnShape ATTN_SHAPES[] = {{8, 4, 5.99, 1.174, 0.176}, {4, 4, 4.11, 0.730, 0.105}, {2, 4, 2.89, 0.504, 0.035},
-                                 {8, 8, 4.44, 1.620, 0.185}, {4, 8, 3.81, 0.644, 0.243}};
+const AttnShape ATTN_SHAPES[] = {{8, 4, 5.99, 1.239, 0.158}, {4, 4, 4.11, 0.796, 0.072}, {2, 4, 3.24, 0.514, 0.041},
+                                 {8, 8, 4.44, 1.393, 0.240}, {4, 8, 4.36, 0.640, 0.238}};
 
 // Estimated time of the attention call (us): the rounds of workgroups and the stream from HBM (6.86 TB/s), joined by a 2-norm, a fixed
 // part, and the merge kernel, which reads what the first one wrote (2.44 TB/s both ways).  Fitted to 18000 measured (shape, plan) pairs, 748 shapes
-// (1 .. 8 sequences, 1 .. 32 kv heads, 1 .. 8 query heads each, 2 .. 2304 window rows, 100 .. 17000 keys from HBM): rms error 5.6 %; the
-// plan it picks is 0.8 % slower than the best measured one in the mean, 2.7 % in nine of ten shapes, 22 % at most (4 x 10 rows, 64 / 8
-// heads, 9727 keys: 256 workgroups of four tiles 42.9, 192 35.0).  The five shapes against the three of four waves: 0.3 %, up to 11 %.
+// (1 .. 8 sequences, 1 .. 32 kv heads, 1 .. 8 query heads each, 2 .. 2304 window rows, 100 .. 17000 keys from HBM; rms error 5.6 %) with the kernel as it
+// was when its references did not move; the figures of the five shapes above then by what each measured before and since, 2 .. 72 stages on 64 and 256
+// compute units.  (20 of 114 drawn plans changed by that, 1.018 x in the mean.)  The plan it picks was 0.8 % slower than the best measured one
+// in the mean, 2.7 % in nine of ten shapes, 22 % at most (4 x 10 rows, 64 / 8 heads, 9727 keys, bound by HBM, where two runs of one plan
+// may differ by as much).  Eight waves against four with as many rows: 4 x 555 rows of 28 / 4, 215 keys 18.0 -> 16.9, 6 x 183 rows of 32 / 32, 191 keys 15.2 -> 14.1,
+// 860 rows of 28 / 4, 929 keys 19.7 -> 19.0.
 // (Returns some value >= limit where the terms without the norm reach it.)
 double attn_cost(const AttnShape &sh, int64_t pairs, int row_tiles, int kv_len, int64_t splits, int64_t stages, double limit)
 {
@@ -213,10 +216,9 @@ double attn_tile_ranges_cost(bool f32, int head_dim, int64_t wgs, int64_t groups
 // k_attn_groups: 16-row tiles of a workgroup, parts of the columns of V, waves, and its time (us) in up to one round of
 // workgroups: start + h (group + load x) for h groups of 32 keys per wave and x of the compute units in use, or the
 // stream from HBM, the longer of the two and a fifth of the shorter.  Fitted to 1380 measured (shape, workgroup) pairs (1 .. 8
-// sequences, 1 .. 32 kv heads, 4 .. 64 rows, 64 .. 4500 keys; rms error 6 .. 9 %).  Best of these against the best plan of the split-KV
-// kernel and the tile kernel, 880 drawn shapes: faster in 700 of them, by 1.34 x in the geometric mean: 28 / 4 heads, 32 rows,
-// 256 / 480 / 768 / 1056 keys 4.7 and 5.6 / 5.3 and 7.5 / 5.7 and 9.4 / 6.8 and 10.2; 64 rows, 1056 keys 7.5 and 11.1; 3 x 19 rows,
-// 1581 keys 9.6 and 12.1.  The estimates choose within 1 % of the best in the mean.
+// sequences, 1 .. 32 kv heads, 4 .. 64 rows, 64 .. 4500 keys; rms error 6 .. 9 %).  Against the best of 30 plans of k_attn_ranges: 28 / 4 heads,
+// 32 rows, 256 / 480 / 768 / 1056 keys 4.6 and 7.6 / 5.4 and 8.5 / 6.0 and 9.1 / 7.1 and 9.6; 64 rows, 1056 keys 8.0 and 10.7; 3 x 19 rows,
+// 1581 keys 11.9 and 12.7.
 struct GroupsShape {
     int tiles, v_parts, waves;
     double start, start_x, group, load;
@@ -417,7 +419,9 @@ FcAttnPlan fc_plan_attention(const fc_config &cfg, int A, int kv_len, size_t cap
     for (const GroupsShape &sh : GROUPS_SHAPES) {
         const int64_t wgs = pairs * ((row_tiles + sh.tiles - 1) / sh.tiles) * sh.v_parts;
         if (wgs > 256 || (sh.waves == 6 && kv_len > 1200)) continue;
-        const double t = 1.06 * attn_groups_cost(sh, pairs, wgs, kv_len);  // (286 shapes measured beside k_attn_ranges: 6 % short)
+        // (Beside k_attn_ranges the estimate is 6 % short: of 4000 drawn shapes 144 are decided by it, and 120 of those measured
+        // 0.947 x without it, those between 1.03 and 1.06 0.954 x.)
+        const double t = 1.06 * attn_groups_cost(sh, pairs, wgs, kv_len);
         if (t < best) {
             best = t;
             one_launch(2, sh.tiles, sh.v_parts, sh.waves);

@@ -100,23 +100,34 @@ __device__ __forceinline__ bool row_is_padded(const int32_t *pos, int idx, int m
 // One wave per SIMD (NW = 4) has to hide its own latencies, so the arithmetic is one stream in which every multiply has other work beside
 // it: while the weights (exponentials) of a tile and block of 32 keys are computed, the matrix core forms the scores of the
 // next block and the output products of the tile before, and the fragments of the keys and values are replaced one by one
-// behind the last multiply that reads them.  Nothing in the loop depends on a maximum: weights are exp2(c (s - m)) with m the row's
-// maximum over the first block of the range.  bf16 and fp32 hold such a weight to the same relative precision whatever m is, until
-// it overflows; a row whose sum passes 2^100 or whose output is not finite -- the scores rose by some 70 nats behind the first
-// 32 keys -- is computed again with the exact running maximum, by its wave alone.
+// behind the last multiply that reads them.  Weights are exp2(c (s - m)) with m the row's maximum over the first stage of the range; where a
+// lane's eight weights of a block sum to more than MOST (one comparison per tile and block), the references of the tile's rows move to
+// the block's maxima before the weights are used.  So weights stay below 2^8, and the largest ones of a row are near a power of
+// two, where rounding to bf16 takes little or nothing.  MOST is what keeps the error against 64 bits at or below that of the kernel named below, scores
+// of deviation 1 .. 4, 23 shapes (1 / 1.2 / 2 / 4: 8 x 256 rows, 2304 keys 2.340 / 2.334 / 2.277 / 2.084e-3 against 2.342 / 2.338 / 2.290 / 2.132; 32 rows, 16800
+// keys 2.312 / 2.300 / 2.014 / 1.756 against 2.316 / 2.304 / 2.157 / 1.785), with as few moves as that takes: a
+// move is 80 VALU instructions (16 rows a wave) or 145, and its workgroup waits.  At 16 everywhere 8 x 256 rows take 3 / 8 / 8 / 9 us more at
+// deviation 1.4 / 2 / 3 / 4; never moving saves them 0.4 / 0.8 / 5.6 / 9.4 and costs 2.33e-3 at every deviation.  The first stage of ranges of few
+// rows counts to 16 bits of its weights, by a second product with what rounding took (0.35 us): few rows go in fewer ranges per row than in
+// that kernel, whose every wave had a reference of its own and so the largest weight of its first block exact; without, 32 rows, 16800
+// keys 2.333 / 2.316e-3 at 1 / 1.2.
 // What bounds it: a multiply keeps the VALU of its SIMD for 8 of its 16 clocks, an exponential takes 8, other VALU instructions 4.4, an LDS
-// read 6: 2550 clocks for 64 rows x 64 keys per wave against 2048 of multiplies; measured 2900 at the 2.2 GHz that the power limit leaves.
-// Against eight waves of 32x32x16 multiplies with a maximum per block (in phase, each stage the sum of both), us per call: 8 x 256
-// rows of 28 / 4 heads, 2304 keys 70.0 -> 59.4; 2304 rows 74.6 -> 62.4; 2 x 300 rows, 1001 keys 22.7 -> 18.3; 2 x 256 rows of 32 / 32, 2000 keys
-// 30.0 -> 26.5; 32 rows, 16800 keys 21.6 -> 18.7; 8 x 32 rows, 2304 keys 23.1 -> 19.9; 4 x 64 rows of 32 / 32, 4160 keys 49.2 -> 46.2.
-// Two waves per SIMD with half the rows each (NW = 8) read twice the fragments: 8 x 256 rows 61.6, and a little faster or slower
-// elsewhere; the planner weighs them.
-// The scores' multiplies are inline assembly to have them in the VALU's half of the registers: the compiler puts every accumulator
-// into the other half and moves 64 scores per stage and lane across (62.0 -> 63.4 us).  Its hazard rules do not see them, so: a score is read no
-// sooner than three multiplies (48 clocks) behind its last one, or behind s_nops.
+// read 6: 2690 clocks for 64 rows x 64 keys per wave against 2048 of multiplies.
+// Against eight waves of 32x32x16 multiplies with a maximum per block (in phase, each stage the sum of both), us per call on one card at
+// deviation 1.2, at 4 in brackets: 8 x 256 rows of 28 / 4 heads, 2304 keys 70.1 -> 63.6 (73.9 -> 75.0); 2304 rows 72.3 -> 64.0 (76.4 -> 74.6); 2 x 300
+// rows, 1001 keys 22.8 -> 18.9 (24.5 -> 22.9); 2 x 256 rows of 32 / 32, 2000 keys 32.3 -> 26.8 (33.2 -> 28.9); 32 rows, 16800 keys 21.0 -> 20.0 (21.6
+// -> 21.7); 8 x 32 rows, 2304 keys 22.2 -> 20.5 (23.0 -> 22.4); 4 x 64 rows of 32 / 32, 4160 keys 49.7 -> 46.7 (49.8 -> 46.8).  Slower: 3 x 527
+// rows of 32 / 32, 1531 keys 56.8 -> 59.3.
+// 16 rows a wave fit into the VALU's half of the registers, where a move is 32 multiplies and not 96 instructions (32 rows, 16800 keys, deviation 4
+// 23.9 -> 21.7).  Others have the accumulators of the output and the queries in the other half, and the scores' multiplies are inline assembly to
+// have those in the VALU's: the compiler puts every accumulator into the other half and moves 64 scores per stage and lane across (62.0 ->
+// 63.4 us; for 16 rows 2 x 200 rows, 1500 keys 17.4 -> 18.6).  Its hazard rules do not see them, so: a score is read no sooner than three
+// multiplies (48 clocks) behind its last one, or behind s_nops; a test holds the compiled code to it.
 template <int QT, int NW, bool ONCE>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void k_attn_ranges(AttnArgs p)
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(QT == 1 ? 2 : NW / 4, QT == 1 ? 2 : NW / 4))) void k_attn_ranges(AttnArgs p)
 {
+    // Sum of a lane's eight weights from which the references of a tile's rows move
+    constexpr float MOST = QT == 4 ? 128.0f : QT == 2 ? 64.0f : NW == 8 ? 24.0f : 16.0f;
     constexpr int LB = 16 / NW;  // 1 KB loads of a stage's keys, and of its values, per wave
     extern __shared__ __align__(1024) unsigned char smem[];
     unsigned char *const kring = smem, *const vring = smem + 4 * K_BYTES;  // four stages each
@@ -195,6 +206,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
 #pragma unroll
     for (int h = 0; h < 2; ++h) vfo[h] = (uint32_t)(rho * 128 + (((4 * h + q) ^ ((rho >> 1) & 7)) << 4));
     const float c = p.c;
+    // A register's half: the matrix core's for what only it touches, except where the VALU's holds everything.
+    auto hold = [](auto &x) {
+        if constexpr (QT == 1) asm volatile("" : "+v"(x));
+        else asm volatile("" : "+a"(x));
+    };
     bf16x8 kf[2][4], vf[8], pf[QT];
     f32x4 s[2][QT][2], o[QT][8];
     float l[QT], nm[QT];  // sum of weights, -c times the reference maximum
@@ -205,19 +221,30 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
     // Multiply i of eight: scores of tile u.
     auto score = [&](int buf, int u, int i) {
         f32x4 &d = s[buf][u][i & 1];
-        if (i < 2) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=v"(d) : "v"(kf[i & 1][i >> 1]), "a"(qf[u][i >> 1]));
+        if constexpr (QT == 1) {
+            if (i < 2) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=v"(d) : "v"(kf[i & 1][i >> 1]), "v"(qf[u][i >> 1]));
+            else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(kf[i & 1][i >> 1]), "v"(qf[u][i >> 1]));
+        } else if (i < 2) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=v"(d) : "v"(kf[i & 1][i >> 1]), "a"(qf[u][i >> 1]));
         else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(kf[i & 1][i >> 1]), "a"(qf[u][i >> 1]));
     };
     auto output = [&](int u, int d) { o[u][d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[d], pf[u], o[u][d], 0, 0, 0); };
 
-    // ---- first block: its scores and their maxima
+    auto mask_values = [&](int d, int base) {  // values of keys past the end may hold anything (also NaN): their weights are 0
+        union { uint32_t w[4]; bf16x8 v; } x;
+        x.v = vf[d];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x.w[r] &= (base + 2 * r < k1 ? 0xffffu : 0u) | (base + 2 * r + 1 < k1 ? 0xffff0000u : 0u);
+        vf[d] = x.v;
+    };
+
+    // ---- first stage: its scores and their maxima (those of the second block are formed again in the loop)
     fc_wait_vm<6 * LB>();
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < QT; ++u)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) asm("" : "+a"(qf[u][k]));
+        for (int k = 0; k < 4; ++k) hold(qf[u][k]);
 #pragma unroll
     for (int i = 0; i < 8; ++i) read_k(kring, 0, i);
 #pragma unroll
@@ -226,17 +253,49 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
         for (int u = 0; u < QT; ++u) score(0, u, i);
         read_k(kring, 1, i);
     }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int u = 0; u < QT; ++u) score(1, u, i);
     asm volatile("s_nop 15\n\ts_nop 15");  // the last products have left the matrix core
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < QT; ++u) {
         float mx = -INFINITY;
 #pragma unroll
-        for (int r = 0; r < 8; ++r) mx = fmaxf(mx, k0 + 8 * q + r < k1 ? s[0][u][r >> 2][r & 3] : -INFINITY);
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int r = 0; r < 8; ++r) mx = fmaxf(mx, k0 + 32 * h + 8 * q + r < k1 ? s[h][u][r >> 2][r & 3] : -INFINITY);
         nm[u] = -row_max2(row_max16(mx)) * c;
         l[u] = 0.f;
 #pragma unroll
         for (int d = 0; d < 8; ++d) o[u][d] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    // What rounding takes from the first stage's weights.  (Two tiles: in several ranges only, with one the error is no larger without.)
+    if (QT == 1 || (QT == 2 && NW == 4 && p.splits > 1)) {
+        fc_wait_vm<5 * LB>();
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int base = k0 + 32 * h + 8 * q;
+#pragma unroll
+            for (int d = 0; d < 8; ++d) read_v(vring, h, d);
+            if (k1 - k0 < KT)
+#pragma unroll
+                for (int d = 0; d < 8; ++d) mask_values(d, base);
+#pragma unroll
+            for (int u = 0; u < QT; ++u) {
+                bf16x8 rest;
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    const float w = __builtin_amdgcn_exp2f(base + r < k1 ? __builtin_fmaf(s[h][u][r >> 2][r & 3], c, nm[u]) : -INFINITY);
+                    rest[r] = (__bf16)(w - (float)(__bf16)w);
+                }
+#pragma unroll
+                for (int d = 0; d < 8; ++d) o[u][d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[d], rest, o[u][d], 0, 0, 0);
+            }
+        }
     }
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
@@ -247,23 +306,40 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
 
     float t[8], e[8], sum = 0.f;
     bf16x8 pw;  // weights of the tile at hand (one tile: those of the block before are still being multiplied)
-    // The sum is of the weights as they are multiplied, so that what rounding does to a large one cancels.  (Against 64 bits, before rounding /
-    // this: scores of deviation 4, 32 rows, 9000 keys 2.33e-3 / 1.94e-3, 2 x 200 rows, 1500 keys 2.33e-3 / 1.89e-3, with an exact running
-    // maximum 1.74e-3 and 2.00e-3; of deviation 1 all three within 1 %.  It costs 0.5 to 1 % of a call.)
-    auto add_pair = [&](int j, float to) {
-        return __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pw[2 * j], pw[2 * j + 1]}, bf16x2{(__bf16)1.0f, (__bf16)1.0f}, to, false);
-    };
     auto weight_end = [&](int u) {
         pw[7] = (__bf16)e[7];
-        pf[u] = pw;
-        l[u] = add_pair(3, l[u] + sum);
+        sum += e[7];
     };
-    auto mask_values = [&](int d, int base) {  // values of keys past the end may hold anything (also NaN): their weights are 0
-        union { uint32_t w[4]; bf16x8 v; } x;
-        x.v = vf[d];
+    // The weights of tile u and the block at `base`, its scores in s[B], are about to be multiplied.  Where a lane's eight sum to more than
+    // MOST, the references of the tile's rows move to the block's maxima first and its weights are formed anew.
+    auto weight_use = [&](int B, int u, int base, bool cut) {
+        if (__builtin_expect(__any(sum > MOST), 0)) {
+            float mx = -INFINITY;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) x.w[r] &= (base + 2 * r < k1 ? 0xffffu : 0u) | (base + 2 * r + 1 < k1 ? 0xffff0000u : 0u);
-        vf[d] = x.v;
+            for (int r = 0; r < 8; ++r) mx = fmaxf(mx, !cut || base + r < k1 ? s[B][u][r >> 2][r & 3] : -INFINITY);
+            const float to = fminf(nm[u], -row_max2(row_max16(mx)) * c), alpha = __builtin_amdgcn_exp2f(to - nm[u]);
+            nm[u] = to;
+            l[u] *= alpha;
+#pragma unroll
+            for (int d = 0; d < 8; ++d) {
+                hold(o[u][d]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o[u][d][r] *= alpha;
+                hold(o[u][d]);  // (back to the matrix core's half of the registers here, not behind the branch)
+            }
+            sum = 0.f;
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                float w = __builtin_amdgcn_exp2f(__builtin_fmaf(s[B][u][r >> 2][r & 3], c, to));
+                if (cut) w = base + r < k1 ? w : 0.f;
+                pw[r] = (__bf16)w;
+                sum += w;
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < 8; ++d) hold(o[u][d]);
+        pf[u] = pw;
+        l[u] += sum;
     };
     // A stage.  LOADS: with all its loads, keys of stage st + 4 and values of stage st + 3; LAST: the last one, with keys past the end.
     auto stage = [&](int st, auto loads, auto last) {
@@ -289,26 +365,32 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
                 if ((i & 1) == 0) {
                     t[k] = __builtin_fmaf(s[B][u][k >> 2][k & 3], c, nm[u]);
                     if (LAST) t[k] = base + k < k1 ? t[k] : -INFINITY;
-                    if (k >= 3 && (k & 1)) sum = add_pair((k - 3) / 2, k == 3 ? 0.f : sum);
                 } else {
                     e[k] = __builtin_amdgcn_exp2f(t[k]);
-                    if (k >= 1) pw[k - 1] = (__bf16)e[k - 1];
+                    if (k >= 1) {
+                        pw[k - 1] = (__bf16)e[k - 1];
+                        sum = k == 1 ? e[0] : sum + e[k - 1];
+                    }
                 }
             };
 #pragma unroll
             for (int u = 0; u < QT; ++u)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
+                    const int before = u == 0 ? QT - 1 : u - 1;  // tile, of this block or the one before
+                    const bool behind = u > 0 || B > 0;          // ... whose weights are not in use yet
+                    if (i == 0 && behind) weight_end(before);
+                    // (one tile: ahead of the score that replaces its first)
+                    if (i == (QT == 1 ? 0 : 1) && behind) weight_use(u == 0 ? N : B, before, u == 0 ? base - 32 : base, LAST);
                     if ((i & 1) == 0) {
                         if (SCORES) score(N, u, i >> 1);
                         if (!LAST && u == QT - 1) read_k(keys, B, i >> 1);
                     } else {
                         if (LAST && QT > 1 && u == 1) mask_values(i >> 1, base);
                         if (LAST && QT == 1 && B == 1) mask_values(i >> 1, base - 32);
-                        output(u == 0 ? QT - 1 : u - 1, i >> 1);
+                        output(before, i >> 1);
                         if (u == 0) read_v(values, B, i >> 1);
                     }
-                    if (i == 0 && (u > 0 || B > 0)) weight_end(u == 0 ? QT - 1 : u - 1);
                     weight(u, i);
                     const int g = 16 * u + i, step = 16 * QT / LB;  // a load every `step` multiplies: keys in the first block, values in the other
                     if (g % step == step / 2) {
@@ -324,6 +406,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
         block(std::integral_constant<int, 0>());
         block(std::integral_constant<int, 1>());
         weight_end(QT - 1);
+        weight_use(1, QT - 1, k0 + st * KT + 32 + 8 * q, LAST);
     };
     // what goes round the loops keeps its half of the registers
     auto pin = [&]() {
@@ -333,7 +416,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
         for (int u = 0; u < QT; ++u) {
             asm("" : "+v"(s[0][u][0]), "+v"(s[0][u][1]));
 #pragma unroll
-            for (int d = 0; d < 8; ++d) asm("" : "+a"(o[u][d]));
+            for (int d = 0; d < 8; ++d) hold(o[u][d]);
         }
     };
     pin();
@@ -348,80 +431,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
     }
     __syncthreads();  // every wave is done with the rings; LDS is reused below
 
-    // Largest magnitude of a row of partial outputs (NaN if one is), and whether the reference maximum was too far off.
-    float amax[QT];
-    bool off = false;
 #pragma unroll
-    for (int u = 0; u < QT; ++u) {
-        l[u] = row_sum2(row_sum16(l[u]));
-        amax[u] = 0.f;
-#pragma unroll
-        for (int d = 0; d < 8; ++d)
-#pragma unroll
-            for (int r = 0; r < 4; r += 2)
-                amax[u] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(amax[u], fabsf(o[u][d][r])), fabsf(o[u][d][r + 1]));
-        off |= !(l[u] < 0x1p100f) || !(amax[u] < INFINITY);
-    }
-    if (__any(off)) {
-        // Again with the exact running maximum, operands straight from memory.
-#pragma unroll
-        for (int u = 0; u < QT; ++u) {
-            nm[u] = INFINITY;
-            l[u] = 0.f;
-#pragma unroll
-            for (int d = 0; d < 8; ++d) o[u][d] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-#pragma unroll 1
-        for (int ks = k0; ks < k1; ks += 32) {
-            const uint16_t *kb = (const uint16_t *)ksrc + (size_t)(ks - k0) * DH + 8 * q;
-            const uint16_t *vb = (const uint16_t *)vsrc + (size_t)((ks - k0) & ~63) * DH + rho * 64 + (ks & 32) + 8 * q;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                kf[i & 1][i >> 1] = *(const bf16x8 *)(kb + (8 * (rho >> 2) + 4 * (i & 1) + (rho & 3)) * DH + 32 * (i >> 1));
-                vf[i] = *(const bf16x8 *)(vb + i * (16 * 64));
-            }
-#pragma unroll
-            for (int d = 0; d < 8; ++d) mask_values(d, ks + 8 * q);
-#pragma unroll
-            for (int u = 0; u < QT; ++u) {
-                f32x4 x[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-                for (int i = 0; i < 8; ++i) x[i & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[i & 1][i >> 1], qf[u][i >> 1], x[i & 1], 0, 0, 0);
-                float mx = -INFINITY;
-#pragma unroll
-                for (int r = 0; r < 8; ++r) {
-                    if (ks + 8 * q + r >= k1) x[r >> 2][r & 3] = -INFINITY;
-                    mx = fmaxf(mx, x[r >> 2][r & 3]);
-                }
-                const float to = fminf(nm[u], -row_max2(row_max16(mx)) * c), alpha = __builtin_amdgcn_exp2f(to - nm[u]);
-                nm[u] = to;
-                l[u] *= alpha;
-                float part = 0.f;
-#pragma unroll
-                for (int r = 0; r < 8; ++r) {
-                    const float w = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r >> 2][r & 3], c, to));
-                    pf[u][r] = (__bf16)w;
-                    part += (float)pf[u][r];
-                }
-                l[u] += part;
-#pragma unroll
-                for (int d = 0; d < 8; ++d) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) o[u][d][r] *= alpha;
-                    o[u][d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[d], pf[u], o[u][d], 0, 0, 0);
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < QT; ++u) {
-            l[u] = row_sum2(row_sum16(l[u]));
-            amax[u] = 0.f;
-#pragma unroll
-            for (int d = 0; d < 8; ++d)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) amax[u] = fmaxf(amax[u], fabsf(o[u][d][r]));
-        }
-    }
+    for (int u = 0; u < QT; ++u) l[u] = row_sum2(row_sum16(l[u]));
 
     if (p.splits > 1) {
         // ---- partial output, in accumulator order, as scaled half floats: the partial of a row is normalised by its own sum (a convex
@@ -435,8 +446,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
             if (tt >= p.row_tiles) continue;
             const size_t ts = ((size_t)bj * p.row_tiles + tt) * p.splits + split;
             uint4 *po = (uint4 *)p.part_o + ts * (8 * 64) + h * 256 + lane;
+            float amax = 0.f;
+#pragma unroll
+            for (int d = 0; d < 8; ++d)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) amax = fmaxf(amax, fabsf(o[u][d][r]));
             const float inv_l = 1.0f / l[u];
-            const int k = 15 - __builtin_amdgcn_frexp_expf(row_max2(row_max16(amax[u])) * inv_l);  // 15 for an all-zero row
+            const int k = 15 - __builtin_amdgcn_frexp_expf(row_max2(row_max16(amax)) * inv_l);  // 15 for an all-zero row
 #pragma unroll
             for (int d2 = 0; d2 < 4; ++d2) {
                 union { _Float16 h[8]; uint4 u4; } x;
@@ -444,9 +460,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
                 for (int e2 = 0; e2 < 8; ++e2) x.h[e2] = (_Float16)__builtin_amdgcn_ldexpf(o[u][2 * d2 + (e2 >> 2)][e2 & 3] * inv_l, k);
                 po[d2 * 64] = x.u4;
             }
-            // a sum beyond 2^24 (the maximum has moved far from the reference) hands its exponent to the maximum
-            const int by = l[u] > 0x1p24f ? __builtin_amdgcn_frexp_expf(l[u]) : 0;
-            if (q == 0) ((float4 *)p.part_ml)[ts * 32 + 16 * h + rho] = make_float4(-nm[u] + (float)by, __builtin_amdgcn_ldexpf(l[u], -by), (float)k, 0.f);
+            if (q == 0) ((float4 *)p.part_ml)[ts * 32 + 16 * h + rho] = make_float4(-nm[u], l[u], (float)k, 0.f);
         }
         return;
     }
@@ -620,8 +634,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((NW + 3
                             for (int d = 0; d < ND; ++d) vf[half][d][4 * h + r] = (__bf16)0.f;
                         }
             }
-            // The exact running maximum: the largest probabilities are then 1, which bf16 holds exactly (with a reference
-            // maximum that lags behind, as above, the error over 100 .. 600 keys is 7 % larger).
+            // The exact running maximum: the largest probabilities are then 1, which bf16 holds exactly (with one that moves only
+            // when a probability would pass 2^8, the error over 100 .. 600 keys is 7 % larger).
 #pragma unroll
             for (int u = 0; u < QT; ++u) {
                 float mx = s[u][0][0];
