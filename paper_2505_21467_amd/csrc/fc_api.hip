@@ -890,30 +890,43 @@ static fc_status check_linear_shape(int32_t M, int32_t K, int32_t N)
     return FC_OK;
 }
 
-// Workspace of one linear call, what it must bring and (`useful`) what its best plan takes where that is more: tiled GEMM where it is
-// planned, streaming kernels otherwise.
-static size_t linear_need(int dtype, int mode, int M, int K, int N, bool useful)
+// Workspace of a linear call: what it must bring, and what its best plan takes where that is more.
+struct LinearSpace {
+    size_t least, useful;
+    uint64_t plan;  // what of the plan the two sizes depend on besides the rows (a word per mode)
+};
+
+// Tiled GEMM where it is planned, streaming kernels otherwise.
+static LinearSpace linear_need(int dtype, int mode, int M, int K, int N)
 {
     const FcWidePlan wide = fc_plan_wide(dtype, mode, M, K, N);
-    if (wide.kind != 1) return fc_skinny_workspace(fc_plan_skinny(dtype, mode, M, K, N));
-    const size_t best = useful ? fc_wide_workspace(wide, M, N) : 0;
-    return best > wide.required ? best : wide.required;
+    if (wide.kind != 1) {
+        const size_t n = fc_skinny_workspace(fc_plan_skinny(dtype, mode, M, K, N));
+        return LinearSpace{n, n, 0};
+    }
+    const size_t best = fc_wide_workspace(wide, M, N), part = (size_t)M * N * sizeof(float);
+    return LinearSpace{wide.required, best > wide.required ? best : wide.required, 1 + (wide.required / part) * 32 + (uint64_t)wide.ksplit * 1024};
 }
 
 // ... of the layer whose output is N wide and of the gated one of N / 2 outputs.
-static size_t linear_workspace(int32_t dtype, int32_t M, int32_t K, int32_t N, bool useful)
+static LinearSpace linear_workspace(int32_t dtype, int32_t M, int32_t K, int32_t N)
 {
     // the gated W_1 is planned on its F = N / 2 outputs; its slabs hold half as many outputs, so the
     // two plans need the same space and one query serves both calls
-    const size_t a = linear_need(dtype, FC_LIN_RESIDUAL, M, K, N, useful);
-    const size_t b = N % 2 == 0 ? linear_need(dtype, FC_LIN_GATE_UP, M, K, N / 2, useful) : 0;
-    return a > b ? a : b;
+    LinearSpace a = linear_need(dtype, FC_LIN_RESIDUAL, M, K, N);
+    if (N % 2 == 0) {
+        const LinearSpace b = linear_need(dtype, FC_LIN_GATE_UP, M, K, N / 2);
+        if (b.least > a.least) a.least = b.least;
+        if (b.useful > a.useful) a.useful = b.useful;
+        a.plan = a.plan << 1 | (b.plan != 0);  // (a gated layer is never cut into parts)
+    }
+    return a;
 }
 
 size_t fc_linear_workspace_bytes(int32_t dtype, int32_t M, int32_t K, int32_t N)
 {
     if ((dtype != FC_F32 && dtype != FC_BF16) || M < 1 || K < 1 || N < 1) return 0;
-    return linear_workspace(dtype, M, K, N, true);
+    return linear_workspace(dtype, M, K, N).useful;
 }
 
 // Small bf16 problems run in the tile kernel: it is one launch, and short as long as the products are few, where the
@@ -1054,9 +1067,9 @@ namespace {
 
 // Carve-up of the whole-layer workspace for M = B * A rows (every part 256-byte aligned).
 struct LayerWs {
-    size_t h, q, o, x2, act, lin, attn;  // attn: last, the attention takes what is left
+    size_t h, q, o, x2, act, lin, attn;  // attn: last
     size_t least;                        // bytes a call must bring
-    size_t useful;                       // bytes that all parts' best plans take
+    size_t lin_end, attn_end;            // where the best plans' partial sums and partial results end
 };
 
 struct LayerWsKey {
@@ -1065,9 +1078,24 @@ struct LayerWsKey {
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-LayerWs layer_ws(const fc_config &c, int32_t d_ff, int32_t A)
+// Space of the three linear layers together.
+LinearSpace layer_linear_space(const fc_config &c, int32_t d_ff, int32_t M)
 {
-    LayerWs w;
+    LinearSpace all = {0, 0, 0};
+    const int32_t E = c.n_q_heads * c.head_dim;
+    for (const LinearSpace &l : {linear_workspace(c.dtype, M, E, c.hidden), linear_workspace(c.dtype, M, c.hidden, 2 * d_ff),
+                                 linear_workspace(c.dtype, M, d_ff, c.hidden)}) {
+        if (l.least > all.least) all.least = l.least;
+        if (l.useful > all.useful) all.useful = l.useful;
+        all.plan = all.plan << 20 | l.plan;  // (17 bits each)
+    }
+    return all;
+}
+
+// The activations' places; `lin` is where they end.
+LayerWs layer_activations(const fc_config &c, int32_t d_ff, int32_t A)
+{
+    LayerWs w = {};
     const size_t es = esize_of(c.dtype);
     const size_t M = (size_t)c.batch * A, d = c.hidden, E = (size_t)c.n_q_heads * c.head_dim;
     size_t off = 0;
@@ -1081,18 +1109,74 @@ LayerWs layer_ws(const fc_config &c, int32_t d_ff, int32_t A)
     w.o = take(M * E * es);
     w.x2 = take(M * d * es);
     w.act = take(M * (size_t)d_ff * es);
-    // The linear layers' partial sums may run on over the attention's space, which is free again by then.
-    auto lin = [&](bool useful) {
-        const size_t l1 = linear_workspace(c.dtype, (int)M, (int)E, c.hidden, useful);
-        const size_t l2 = linear_workspace(c.dtype, (int)M, c.hidden, 2 * d_ff, useful);
-        const size_t l3 = linear_workspace(c.dtype, (int)M, d_ff, c.hidden, useful);
-        return l1 > l2 ? (l1 > l3 ? l1 : l3) : (l2 > l3 ? l2 : l3);
-    };
-    w.lin = take(lin(false));
-    w.attn = off;
-    w.least = off + align256(attn_workspace(c, A, false));
-    w.useful = w.lin + align256(lin(true));
+    w.lin = off;
     return w;
+}
+
+LayerWs layer_ws(const fc_config &c, int32_t d_ff, int32_t A)
+{
+    LayerWs w = layer_activations(c, d_ff, A);
+    // The linear layers' partial sums may run on over the attention's space, which is free again by then.
+    const LinearSpace lin = layer_linear_space(c, d_ff, c.batch * A);
+    w.attn = w.lin + align256(lin.least);
+    w.lin_end = w.lin + align256(lin.useful);
+    w.least = w.attn + align256(attn_workspace(c, A, false));
+    w.attn_end = w.attn + align256(attn_workspace(c, A, true));
+    return w;
+}
+
+// (planning it walks every window size up to A; a thread asks for the size and then calls)
+LayerWs layer_ws_of(const fc_config &c, int32_t d_ff, int32_t A)
+{
+    static thread_local Memo<LayerWsKey, LayerWs> memo;
+    const LayerWsKey key = {c.batch, c.hidden, c.n_q_heads, c.n_kv_heads, c.head_dim, c.max_seq, c.dtype, d_ff, A, fc_knobs().version};
+    return memo.get(key, [&] { return layer_ws(c, d_ff, A); });
+}
+
+// The most that a layer call of up to max_rows rows requires or makes use of.  Narrower windows may ask for more than wider ones, whose layers go
+// in fewer parts: 28 / 4 heads, d_ff 18944, 256 rows require 68 MB, 257 rows 50.  Between two multiples of 64 rows the number of tiles is the same
+// in every shape, so that the estimate of a number of parts is a constant and a term of rows x parts: the cheapest number does not rise
+// with the rows, and where it is the same at both ends of an interval the widest window takes the most.
+size_t layer_workspace_most(const fc_config &c, int32_t d_ff, int32_t max_rows)
+{
+    const LayerWs widest = layer_ws_of(c, d_ff, max_rows);
+    const size_t attn = align256(attn_workspace(c, max_rows, false));  // at least that of any narrower window
+    size_t most = widest.lin_end > widest.attn_end ? widest.lin_end : widest.attn_end;
+    auto take = [&](int32_t A, const LinearSpace &lin) {
+        const size_t at = layer_activations(c, d_ff, A).lin, least = at + align256(lin.least) + attn, useful = at + align256(lin.useful);
+        if (least > most) most = least;
+        if (useful > most) most = useful;
+    };
+    auto space = [&](int32_t A) { return layer_linear_space(c, d_ff, c.batch * A); };
+    struct Interval {
+        int32_t lo, hi;
+        LinearSpace at_lo, at_hi;
+    } todo[32];  // (halved each time, at most 64 windows wide)
+    for (int64_t last = (int64_t)c.batch * max_rows; last >= 1;) {
+        const int64_t before = last > 64 ? (last - 1) / 64 * 64 : last > 32 ? 32 : last > 16 ? 16 : 0;  // rows before + 1 .. last
+        const int32_t lo = (int32_t)(before / c.batch + 1), hi = (int32_t)(last / c.batch);
+        last = before;
+        if (lo > hi) continue;
+        // 256 compute units' partial sums of 256 x 256 are 64 MB; beyond that only the slice-wise kernel goes, which rises with the rows
+        if (layer_activations(c, d_ff, hi).lin + ((size_t)64 << 20) + attn <= most) break;
+        int n = 0;
+        todo[n++] = Interval{lo, hi, space(lo), space(hi)};
+        take(hi, todo[0].at_hi);
+        while (n > 0) {
+            const Interval v = todo[--n];
+            if (v.at_lo.plan == v.at_hi.plan) continue;  // (the wider end is taken already)
+            if (v.hi - v.lo <= 1) {
+                take(v.lo, v.at_lo);
+                continue;
+            }
+            const int32_t mid = v.lo + (v.hi - v.lo) / 2;
+            const LinearSpace at_mid = space(mid);
+            take(mid, at_mid);
+            todo[n++] = Interval{v.lo, mid, v.at_lo, at_mid};
+            todo[n++] = Interval{mid, v.hi, at_mid, v.at_hi};
+        }
+    }
+    return most;
 }
 
 }  // namespace
@@ -1101,9 +1185,10 @@ size_t fc_full_layer_workspace_bytes(const fc_config *cfg, int32_t d_ff, int32_t
 {
     if (check_config(cfg) != FC_OK || d_ff < 1 || max_rows < 1 || (int64_t)max_rows * cfg->batch > (1 << 24))
         return 0;
-    const LayerWs w = layer_ws(*cfg, d_ff, max_rows);
-    const size_t attn = w.attn + align256(attn_workspace(*cfg, max_rows, true));
-    return attn > w.useful ? attn : w.useful;
+    static thread_local Memo<LayerWsKey, size_t> memo;
+    const LayerWsKey key = {cfg->batch, cfg->hidden, cfg->n_q_heads, cfg->n_kv_heads, cfg->head_dim, cfg->max_seq, cfg->dtype, d_ff, max_rows,
+                            fc_knobs().version};
+    return memo.get(key, [&] { return layer_workspace_most(*cfg, d_ff, max_rows); });
 }
 
 fc_status fc_full_layer_step(fc_cache *cache, int32_t layer, const fc_layer_weights *wt, const void *x,
@@ -1125,9 +1210,7 @@ fc_status fc_full_layer_step(fc_cache *cache, int32_t layer, const fc_layer_weig
         return fail(FC_ERR_BOUNDS, "window [%d, %d+%d) outside the cache of %d rows", win_start, win_start, A,
                     c.max_seq);
     if (kv_len < 1 || kv_len > c.max_seq) return fail(FC_ERR_BOUNDS, "kv_len %d outside [1, %d]", kv_len, c.max_seq);
-    static thread_local Memo<LayerWsKey, LayerWs> memo;  // (planning it walks every window size up to A)
-    const LayerWsKey key = {c.batch, c.hidden, c.n_q_heads, c.n_kv_heads, c.head_dim, c.max_seq, c.dtype, wt->d_ff, A, fc_knobs().version};
-    const LayerWs w = memo.get(key, [&] { return layer_ws(c, wt->d_ff, A); });
+    const LayerWs w = layer_ws_of(c, wt->d_ff, A);
     if (!workspace || workspace_bytes < w.least)
         return fail(FC_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", w.least,
                     workspace ? workspace_bytes : (size_t)0);
