@@ -235,14 +235,17 @@ fc_status fc_refresh(fc_cache *cache, int32_t layer, const void *x, const void *
 fc_status fc_rmsnorm(int32_t dtype, const void *x, const void *weight, float eps, int32_t rows,
                      int32_t hidden, void *out, void *stream);
 
-/* Workspace bytes of fc_linear_residual for this shape (cross-workgroup partial sums); for
- * fc_ffn_gate_up pass N = 2 F.  0 on bad arguments or when none is needed. */
+/* Workspace bytes that are of use to fc_linear_residual at this shape (cross-workgroup partial sums);
+ * for fc_ffn_gate_up pass N = 2 F.  0 on bad arguments or when none is.  A call takes less, down to
+ * what some shapes require (WORKSPACE says how much; often nothing), and then sums the hidden
+ * dimension in fewer parts.  Results are the same bit for bit from call to call where the calls
+ * bring the same number of bytes, or no less than this query's. */
 size_t fc_linear_workspace_bytes(int32_t dtype, int32_t M, int32_t K, int32_t N);
 
 /* out[m][n] = residual[m][n] + sum_k x[m][k] w[n][k], rounded once (W_out and W_2 of Table 1, each
  * with the residual connection folded in).
  *   x  device [M][K];  w  device [N][K];  residual  device [M][N] or NULL;  out  device [M][N]
- *   (out may be residual);  workspace  device, >= fc_linear_workspace_bytes(dtype, M, K, N) bytes.
+ *   (out may be residual);  workspace  device, fc_linear_workspace_bytes(dtype, M, K, N) bytes.
  * Errors: INVALID_ARG, UNSUPPORTED (K not a multiple of 8), WORKSPACE, HIP. */
 fc_status fc_linear_residual(int32_t dtype, const void *x, const void *w, const void *residual,
                              int32_t M, int32_t K, int32_t N, void *out, void *workspace,
@@ -251,7 +254,7 @@ fc_status fc_linear_residual(int32_t dtype, const void *x, const void *w, const 
 /* out[m][f] = silu(sum_k x[m][k] w_gate[f][k]) * (sum_k x[m][k] w_up[f][k]), silu(t) = t / (1 + e^-t)
  * (the gated form of W_1 of Table 1); the two products stay in fp32, one rounding.
  *   x  device [M][K];  w_gate, w_up  device [F][K];  out  device [M][F];
- *   workspace  device, >= fc_linear_workspace_bytes(dtype, M, K, 2 F) bytes.
+ *   workspace  device, fc_linear_workspace_bytes(dtype, M, K, 2 F) bytes.
  * Errors: as fc_linear_residual. */
 fc_status fc_ffn_gate_up(int32_t dtype, const void *x, const void *w_gate, const void *w_up, int32_t M,
                          int32_t K, int32_t F, void *out, void *workspace, size_t workspace_bytes,
@@ -271,9 +274,10 @@ typedef struct {
     float eps;           /* RMSNorm epsilon */
 } fc_layer_weights;
 
-/* Workspace bytes of fc_full_layer_step for windows of up to max_rows rows per sequence
- * (intermediate activations of B * max_rows rows, partial sums, the attention workspace; of the last a
- * call requires no more than fc_active_attention does). */
+/* Workspace bytes of fc_full_layer_step for windows of up to max_rows rows per sequence: the most that
+ * any of them makes use of (intermediate activations, partial sums, the attention workspace).  Calls
+ * require less, of the last two no more than the calls they are made of; with this much or more the
+ * results are those of the chain of calls, each with the workspace of its own query, bit for bit. */
 size_t fc_full_layer_workspace_bytes(const fc_config *cfg, int32_t d_ff, int32_t max_rows);
 
 /* One cached step of the whole layer on the window rows (section 3.2.1 applied to every module of

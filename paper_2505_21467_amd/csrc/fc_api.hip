@@ -1218,7 +1218,9 @@ fc_status fc_full_layer_step(fc_cache *cache, int32_t layer, const fc_layer_weig
     char *ws = (char *)workspace;
     const int M = c.batch * A, d = c.hidden, E = c.n_q_heads * c.head_dim;
     void *h = ws + w.h, *q = ws + w.q, *o = ws + w.o, *x2 = ws + w.x2, *act = ws + w.act;
-    const size_t attn_bytes = workspace_bytes - w.attn, lin_bytes = workspace_bytes - w.lin;
+    // (no more than what is of use, so that what a caller has to spare changes no plan, and with it no rounding)
+    const size_t attn_bytes = (workspace_bytes < w.attn_end ? workspace_bytes : w.attn_end) - w.attn;
+    const size_t lin_bytes = (workspace_bytes < w.lin_end ? workspace_bytes : w.lin_end) - w.lin;
     void *lin = lin_bytes ? ws + w.lin : nullptr, *attn = attn_bytes ? ws + w.attn : nullptr;
 
     const bool once = fc_read_once(fc_pass_bytes(c, wt->d_ff, kv_len));
