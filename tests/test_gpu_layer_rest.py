@@ -390,6 +390,33 @@ def test_full_layer_step_takes_what_it_requires():
     assert_close(y[1], y[0], "f32", "layer output with less workspace")
 
 
+def test_full_layer_step_partial_sums_over_the_attentions_space():
+    """W_2 in six parts where a call must bring space for three: the partial sums run on over the attention's space.  Against the oracle and the
+    chain; what lies behind the given size is left alone, and what a caller has to spare changes no bit, at any length."""
+    w = inputs.Workload("parts", "bf16", 1, 2176, 17, 17, 128, 0, 0, d_ff=8192)
+    L, A = 60, 433
+    part = 4 * A * w.hidden
+    assert fc.fc_linear_workspace_bytes("bf16", A, w.d_ff, w.hidden) == 6 * part
+    _run_full_layer(w, L, A, seed=12, std=0.02)
+    layer, X = FullLayer(w, 13), inputs.hidden_states(w, 13, A)
+    g = GpuLayerCache("bf16", 1, w.hidden, 17, 17, 128, 4 * (L + A), max_rows=A)
+    K, V = inputs.kv_fill(w, 13, 4 * (L + A))
+    g.write_rows(0, K, V, 0)
+    need = fc.fc_full_layer_workspace_bytes(g.cfg, w.d_ff, A)
+    for S in (L + A, 4 * (L + A)):
+        y = []
+        for given in (need, need + (1 << 20), need + (64 << 20), need - 2 * part):
+            ws = torch.full((need + (64 << 20) + 4096,), 0x5A, dtype=torch.uint8, device=DEV)
+            out = torch.full((1, A, w.hidden), float("nan"), dtype=torch.bfloat16, device=DEV)
+            fc.fc_full_layer_step(g.handle, 0, layer.handle, _dev(X), L, A, None, S, out, ws, given)
+            torch.cuda.synchronize()
+            assert bool((ws[min(given, need):] == 0x5A).all()), given
+            y.append(out)
+        assert torch.equal(y[0], y[1]) and torch.equal(y[0], y[2])
+        assert_close(inputs.as_oracle(y[3]), inputs.as_oracle(y[0]), "bf16", "fewer parts")
+    g.close()
+
+
 def test_full_layer_step_small_bf16_generic_shapes():
     # shapes none of the matrix-core kernels cover: every module runs on the plain kernels
     w = inputs.Workload("small", "bf16", 2, 136, 6, 2, 64, 0, 0, d_ff=200)
