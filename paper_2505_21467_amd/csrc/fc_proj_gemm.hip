@@ -1081,7 +1081,7 @@ int plan_pieces(int slots, int M, int K, bool allow_half, bool allow_dealt, Gemm
     double best = 1e30;
     int n = 1;
     for (int sh = 0; sh < N_SHAPES; ++sh) {
-        if ((shape_half(sh) && !allow_half) || (shape_dealt(sh) && !allow_dealt) || (no64 && sh >= 9)) continue;
+        if ((shape_half(sh) && !allow_half) || (shape_dealt(sh) && !allow_dealt) || (no64 && (sh == 9 || sh == 10))) continue;
         const double c = launch_cost(sh, slots, M);
         if (c < best) {
             best = c;

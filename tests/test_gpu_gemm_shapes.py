@@ -1,6 +1,8 @@
 """GPU parity of the tiled GEMM's 256 x 256 tile (two slabs, one wave per SIMD) and of problems
 cut into two launches, at the edges: an odd number of slabs, ragged rows, one and few stages, parts of the
 hidden dimension."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -271,3 +273,35 @@ def test_parts_as_the_space_allows(M, K, N):
         fc.fc_linear_residual("bf16", xd, wd, rd, M, K, N, out, space, n)
         torch.cuda.synchronize()
         assert_close(inputs.as_oracle(out), ref, "bf16", "%d bytes of workspace" % n)
+
+
+def _launches(call):
+    """(workgroups, threads of one) of every kernel that `call(stream)` enqueues, from a captured graph that is not run."""
+    class Params(ctypes.Structure):  # hipKernelNodeParams
+        _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint * 3),
+                    ("args", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+    call(torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    graph, stream = torch.cuda.CUDAGraph(keep_graph=True), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=stream):
+        call(stream.cuda_stream)
+    hip = ctypes.CDLL("libamdhip64.so")
+    raw, n = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(n)) == 0
+    out = []
+    for node in nodes:
+        p = Params()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        out.append((p.grid[0], p.block[0]))
+    return out
+
+
+# One round of 256 x 96-pair tiles, above 512 rows too and at hidden sizes above 4096, where tiles of 64 rows are not taken.
+@pytest.mark.parametrize("M,K,slots", [(740, 4608, 108), (558, 6144, 108), (740, 4096, 108)])
+def test_runs_of_96_pairs_where_they_fill_a_round(M, K, slots):
+    print("[case] 96 pairs", M, K, slots, flush=True)
+    x, w, o = (torch.zeros(s, dtype=torch.bfloat16, device=DEV) for s in ((M, K), (slots * 64, K), (M, slots * 64)))
+    got = _launches(lambda s: fc.fc_ffn_gate_up("bf16", x, w, w, M, K, slots * 64, o, None, 0, s))
+    assert got == [(72 * 3, 256)], got
