@@ -532,7 +532,7 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
     const int rest = (g1 - g0) % TW;
     const bool halves = LDS && F32 && rest >= 1 && rest <= TW / 2;
     const int rounds = (g1 - g0) / TW, last0 = g0 + rounds * TW;
-    const int n = rounds + (halves ? 32 * last0 + 16 * wave < p.kv_len : wave < rest);
+    const int n = rounds + (halves ? 32 * last0 + 16 * wave < min(p.kv_len, 32 * g1) : wave < rest);
     auto group_of = [&](int i) { return halves && i == rounds ? last0 + (wave >> 1) : g0 + wave + i * TW; };
     // key of row i of 16-key half h: fp32 in order; bf16 so that register pairs of the two halves are 8 keys in a row
     auto key_of = [&](int h, int i) { return F32 ? 16 * h + i : 8 * (i >> 2) + 4 * h + (i & 3); };
