@@ -161,8 +161,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x4 (&acc)[MT
         if (has_v) {
             // Value rows go to the transposed tiles.  Where these 64 rows are consecutive positions of one sequence by way of LDS, [weight
             // row][window row], rounded, as far from a multiple of eight there as in the tile: they leave in pieces of eight keys, 16 bytes, and
-            // single keys at both ends.  Otherwise straight from the accumulators, lanes along the keys (32 rows of 128 x 80-pair tiles
-            // by way of LDS: 6 x 100 rows 28.7 -> 29.5 us).
+            // single keys at both ends: eight of 64 rows, eight weight rows at a time (by sixteens, half of the lanes idle, a start off a
+            // multiple of eight cost 2 us: 1280 rows of 36 slots from 67 on 44.0 -> 42.8, 2304 rows 69.3 -> 67.9; 1581 rows of 96 slots, hidden
+            // 4096, 153.8 -> 151.8, straight from the accumulators 151.2).  Otherwise straight from the accumulators, lanes along the keys
+            // (32 rows of 128 x 80-pair tiles by way of LDS: 6 x 100 rows 28.7 -> 29.5 us).
             constexpr int VPITCH = ROWS * 2 + 16, GROUPS = ROWS / 8;
             const int64_t per_head = (int64_t)G.spad * 128;
             const int n_in = min(ROWS, p.m_end - m_i), r_l = lane % ROWS;
@@ -202,12 +204,12 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, f32x4 (&acc)[MT
                         if (o >= 0 && c < c_hi) *(uint4 *)(vb + o + at) = v8;
                     }
                 }
-                const int before = c_lo - shift, single = before + shift + n_in - c_hi;  // at most 7 + 7
+                const int before = c_lo - shift, single = before + shift + n_in - c_hi;  // 8 of 64 rows, at most 7 + 7 of fewer
                 if (single) {
-                    const int e = lane & 15, c = e < before ? shift + e : c_hi + e - before;
+                    const int wide = single > 8 ? 4 : 3, e = lane & ((1 << wide) - 1), c = e < before ? shift + e : c_hi + e - before;
                     const int64_t at = key_at(base + c);
-#pragma unroll 2
-                    for (int j = lane >> 4; j < 16 * NT; j += 4) {
+#pragma unroll 4
+                    for (int j = lane >> wide; j < 16 * NT; j += 64 >> wide) {
                         const uint16_t v1 = *(const uint16_t *)(area + j * VPITCH + 2 * min(c, ROWS + 7));
                         const int64_t o = offset_of(j);
                         if (o >= 0 && e < single) vb[o + at] = v1;

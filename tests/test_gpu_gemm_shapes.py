@@ -145,6 +145,7 @@ def test_few_row_tiles_projection(shape, B, d, Hq, Hkv, A, knob):
     (1, 0, 80, False),    # a last step of 16 rows, the fewest that are taken in pieces
     (1, 5, 79, False),    # and of 15
     (3, 61, 192, False),  # every step one sequence's, two row tiles
+    (1, 1, 86, False),    # a last step of 22 with seven single keys at either end, more than eight
     (2, 33, 128, True),   # lists: a step of consecutive positions, one with gaps, padded rows
 ])
 def test_value_rows_of_the_wide_tiles(shape, B, L, A, listed, knob):
@@ -173,7 +174,7 @@ def test_value_rows_of_the_wide_tiles(shape, B, L, A, listed, knob):
 
 
 # The tile of 256 rows x 96 dealt pairs (shape 11): value rows as above, gated layers whose last run is short, and the non-temporal hint.
-@pytest.mark.parametrize("B,L,A,listed", [(1, 40, 64, False), (2, 43, 131, False), (1, 5, 79, False), (3, 61, 192, False), (2, 33, 128, True)])
+@pytest.mark.parametrize("B,L,A,listed", [(1, 40, 64, False), (2, 43, 131, False), (1, 5, 79, False), (3, 61, 192, False), (1, 1, 86, False), (2, 33, 128, True)])
 def test_runs_of_96_pairs_projection(B, L, A, listed, knob):
     test_value_rows_of_the_wide_tiles(11, B, L, A, listed, knob)
 
