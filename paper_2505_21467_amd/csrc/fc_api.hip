@@ -301,10 +301,10 @@ ForcedTiles forced_tiles(int64_t pairs, int row_tiles, int64_t by_len)
 // Bytes of partial results per row tile and key range: 32 x 128 half floats and 32 x 4 floats of row state.
 constexpr size_t ATTN_PART_BYTES = 32 * (128 * 2 + 4 * sizeof(float));
 
-// Workspace a call must bring (bytes): the partial results of one round of workgroups with the tiles by the row count
-// (a cache too short for 256 eight-wave workgroups of four tiles: 512 four-wave workgroups of two), or those of the plan
-// that a tuning knob forces.  What the planner does with it is its own affair: it often takes fewer ranges, and more only
-// where the caller brings more (fc_workspace_bytes says how much is of use).
+// Workspace a call must bring (bytes), a bound that callers rely on: the partial results of 256 units of two, four or eight
+// 32-row tiles by the row count, of 512 units of two where the cache is too short to give 256 of four, or those of the plan that a
+// tuning knob forces.  It is not the launch (every shape there puts one workgroup on a compute unit): the planner often takes
+// fewer ranges, and more only where the caller brings more (fc_workspace_bytes says how much is of use).
 size_t attn_required(const fc_config &cfg, int A, int kv_len)
 {
     if (cfg.dtype != FC_BF16 || cfg.head_dim != 128) return 0;  // those cut the keys only where there is space for it

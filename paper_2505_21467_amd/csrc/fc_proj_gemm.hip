@@ -660,11 +660,11 @@ __global__ __launch_bounds__((NW + NL) * 64) __attribute__((amdgpu_waves_per_eu(
 // 128 x 80 or 64 x 128).
 //
 // One wave per SIMD keeps up to 256 accumulators and reads the fewest operand bytes from LDS: 131 KB per 64 hidden
-// elements of a 256 x 256 tile against 196 KB with eight waves of 64 x 128, which together with the 64 KB of loads is
-// as much as LDS moves in the time of the multiplies.  v_mfma 16x16x32 instead of 32x32x16: under the power limit, multiplies
-// alone, 2024 against 1780 TFLOP/s (the accumulators are read and written half as often).  A stage of 64 hidden elements is two
-// phases of MT * NT multiplies; between them go the fragment reads of the next phase and the loads of later stages, one every
-// few multiplies, so nothing is waited for but the stage's barrier in the middle:
+// elements of a 256 x 256 tile against 196 KB with eight waves of 64 x 128, beside 64 KB of loads (free of conflicts LDS gives
+// 240 to 250 B per clock: 540 and 800 clocks of reads beside 2048 of multiplies).  v_mfma 16x16x32 instead of 32x32x16: under the
+// power limit, multiplies alone, 2024 against 1780 TFLOP/s (the accumulators are read and written half as often).  A stage of 64
+// hidden elements is two phases of MT * NT multiplies; between them go the fragment reads of the next phase and the loads of later
+// stages, one every few multiplies, so nothing is waited for but the stage's barrier in the middle:
 //
 //   barrier(s)   stage s+1 has arrived, every wave has read all of stage s: its slots are free
 //   phase B(s)   multiplies the second half of stage s; reads the first half of stage s+1, issues the first loads of batch s
@@ -1189,8 +1189,9 @@ double part_cost(const PartCost &c, int64_t tiles, int64_t M, int64_t K, int64_t
 // 101; 12288 x 4096, 360 / 760 rows 75 / 113 and 57 / 86; 1200 rows, more than one round of any tile, 256 x 256 in three parts 144 -> 113.  The
 // estimate of the uncut launches is that of plan_pieces, or that of one round here where it is the larger; it has to be beaten by 7 %,
 // and where a round would be less than three quarters full may be missed by 5 %.  Against parts for fewer than 192 workgroups
-// of 128 rows x half a slab, by fill rates (the rule that says what space a call must bring), over 390 problems not of the fit: 1.06 x in
-// the mean, up to 1.64 x, a few sizes slower by up to 8 % (13824 x 5120, 120 rows 37.8 -> 40.7); 2 % from the best measured in the mean.
+// of 128 rows x half a slab, by fill rates (the rule that says what space a call must bring), over 211 drawn problems where the two
+// differ: 1.14 x in the mean, up to 1.64 x, 21 slower by more than 3 % (worst: 5120 x 6144, 99 rows 23.1 -> 25.6; 13824 x 5120, 120 rows
+// 37.0 -> 39.7).  The better of both by measurement would be 1.147 x; a fit to these as well leaves 16 slower at the same mean.
 void choose_parts(FcWidePlan &p, int M, int K, int N, size_t cap)
 {
     const int64_t units = N / 128;
