@@ -613,173 +613,183 @@ __global__ __launch_bounds__(TW * 64) void k_attn_tile(AttnTileArgs p)
         m[u] = -INFINITY;
         l[u] = 0.f;
     }
-    for (int i = 0; i < n; ++i) {
-        const int g = group_of(i), half = halves && i == rounds ? wave & 1 : -1;  // -1: both
-        const bool more = i + 1 < n;
-        if constexpr (!LDS) {
-            const T *vt = vc + (size_t)(g >> 1) * (FC_VTILE * DH) + 32 * (g & 1);
-#pragma unroll
-            for (int d = 0; d < ND; ++d)
-#pragma unroll
-                for (int h = 0; h < NV; ++h)
-                    vd[d][h] = *(const frag *)(vt + (dv0 + 16 * d + rho) * FC_VTILE + (F32 ? 16 * h : 0) + KB * q);
-        }
-        f32x4 s[QT][2];
-#pragma unroll
-        for (int u = 0; u < QT; ++u)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) s[u][h] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if constexpr (LDS) {
-#pragma unroll
-            for (int part = 0; part < 32 / L::KG; ++part) {
-                if (part == 0) fc_wait_vm<L::NVL>();  // these keys are here; the values behind them may stay in flight
-                else fc_wait_vm<0>();
-                __builtin_amdgcn_sched_barrier(0);
-                frag kf[L::KG / 16][NKB];
-#pragma unroll
-                for (int h = 0; h < L::KG / 16; ++h)
-#pragma unroll
-                    for (int k = 0; k < NKB; ++k)
-                        kf[h][k] = *(const frag *)(kbuf + (16 * h + rho) * L::KROW + 16 * ((4 * k + q) ^ L::template swizzle<L::KROW>(16 * h + rho)));
-                fc_wait_lds();  // lgkmcnt(0): the area may be overwritten
-                __builtin_amdgcn_sched_barrier(0);
-                if (part + 1 < 32 / L::KG) issue_k(i, part + 1);
-                else if (more) issue_k(i + 1, 0);
-                __builtin_amdgcn_sched_barrier(0);
-                auto scores = [&](auto first, auto last) {  // 16-key halves first .. last - 1 of the part
-#pragma unroll
-                    for (int k = 0; k < NKB; ++k)
-#pragma unroll
-                        for (int u = 0; u < QT; ++u)
-#pragma unroll
-                            for (int h = decltype(first)::value; h < decltype(last)::value; ++h)
-                                s[u][part * (L::KG / 16) + h] = O::mfma(kf[h][k], qf[u][k], s[u][part * (L::KG / 16) + h]);
-                };
-                const std::integral_constant<int, 0> c0;
-                const std::integral_constant<int, 1> c1;
-                const std::integral_constant<int, L::KG / 16> c2;
-                if (!F32 || half < 0) scores(c0, c2);
-                else if (L::KG == 16) {
-                    if (half == part) scores(c0, c1);
-                } else if (half == 0) scores(c0, c1);
-                else scores(c1, c2);
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < QT; ++u)
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-#pragma unroll
-                    for (int k = 0; k < NKB; ++k) s[u][h] = O::mfma(kd[h][k], qf[u][k], s[u][h]);
-            if (more) load_k(g + TW);  // the next group's keys travel behind the softmax and the output products
-        }
-        if (F32 && LDS && half >= 0) {
-#pragma unroll
-            for (int u = 0; u < QT; ++u)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    if (half == 1) s[u][0][r] = -INFINITY;
-                    else s[u][1][r] = -INFINITY;
-                }
-        }
-        const bool past = 32 * g + 32 > p.kv_len;  // keys past the end may hold anything: no score, and zero values (0 * V stays 0)
-        if (past) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (32 * g + key_of(h, 4 * q + r) >= p.kv_len) {
-#pragma unroll
-                        for (int u = 0; u < QT; ++u) s[u][h][r] = -INFINITY;
-                    }
-        }
-        frag pf[QT][F32 ? NV : NP];
-#pragma unroll
-        for (int u = 0; u < QT; ++u) {
-            float mx = s[u][0][0];
-#pragma unroll
-            for (int r = 1; r < 8; ++r) mx = fmaxf(mx, s[u][r >> 2][r & 3]);
-            const float m_new = fmaxf(m[u], max_rows(mx));
-            const float alpha = __builtin_amdgcn_exp2f((m[u] - m_new) * p.c);
-            m[u] = m_new;
-            l[u] *= alpha;
-            float pr[8];
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                pr[r] = __builtin_amdgcn_exp2f((s[u][r >> 2][r & 3] - m_new) * p.c);
-                l[u] += pr[r];
-            }
-#pragma unroll
-            for (int d = 0; d < ND; ++d)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) o[u][d][r] *= alpha;
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                if constexpr (F32) {
-                    pf[u][r >> 2][r & 3] = pr[r];
-                } else {
-#pragma unroll
-                    for (int h = 0; h < NP; ++h) {
-                        pf[u][h][r] = (__bf16)pr[r];
-                        pr[r] -= (float)pf[u][h][r];  // (exact)
-                    }
-                }
-            }
-        }
-        if constexpr (LDS) {
-#pragma unroll
-            for (int part = 0; part < 32 / L::VG; ++part) {
-                if (part == 0 && more) fc_wait_vm<L::NK>();  // these values are here; the next keys may stay in flight
-                else fc_wait_vm<0>();
-                __builtin_amdgcn_sched_barrier(0);
-                constexpr int NVP = NV * L::VG / 32;  // fragments per 16 rows
-                frag vf[ND][NVP];
-#pragma unroll
-                for (int d = 0; d < ND; ++d)
-#pragma unroll
-                    for (int h = 0; h < NVP; ++h)
-                        vf[d][h] = *(const frag *)(vbuf + (16 * d + rho) * L::VROW + 16 * ((4 * h + q) ^ L::template swizzle<L::VROW>(16 * d + rho)));
-                fc_wait_lds();
-                __builtin_amdgcn_sched_barrier(0);
-                if (part + 1 < 32 / L::VG) issue_v(i, part + 1);
-                else if (more) issue_v(i + 1, 0);
-                __builtin_amdgcn_sched_barrier(0);
-                if (past) {
-#pragma unroll
-                    for (int d = 0; d < ND; ++d)
-#pragma unroll
-                        for (int h = 0; h < NVP; ++h)
-#pragma unroll
-                            for (int e = 0; e < KB; ++e)
-                                if (32 * g + L::VG * part + (F32 ? 16 * h : 0) + KB * q + e >= p.kv_len) vf[d][h][e] = {};
-                }
-#pragma unroll
-                for (int h = 0; h < (F32 ? NVP : NP); ++h) {
-                    if (F32 && half >= 0 && half != NVP * part + h) continue;
-#pragma unroll
-                    for (int u = 0; u < QT; ++u)
-#pragma unroll
-                        for (int d = 0; d < ND; ++d) o[u][d] = O::mfma(vf[d][F32 ? h : 0], pf[u][F32 ? NVP * part + h : h], o[u][d]);
-                }
-            }
-        } else {
-            if (past) {
+    // The wave's groups from .. to - 1, WHOLE or the HALF of one that it got, in a loop of their own: with tests for halves among the matrix
+    // instructions those no longer go beside the softmax (fp32 rows of 128, two layers, us before / with the tests / now: 16 / 4 heads, 92 rows,
+    // 1969 keys 91 / 96.6 / 90.5, 60 rows 62.4 / 56.5 / 57.2; 16 / 8 heads, 400 rows, 1900 keys 234 / 244 / 234).
+    constexpr int WHOLE = 0, HALF = 1;
+    auto take = [&](int from, int to, auto form) {
+        constexpr int FORM = decltype(form)::value;
+        for (int i = from; i < to; ++i) {
+            const int g = group_of(i), half = FORM == HALF ? wave & 1 : -1;  // -1: both
+            const bool more = FORM == WHOLE && i + 1 < n;
+            if constexpr (!LDS) {
+                const T *vt = vc + (size_t)(g >> 1) * (FC_VTILE * DH) + 32 * (g & 1);
 #pragma unroll
                 for (int d = 0; d < ND; ++d)
 #pragma unroll
                     for (int h = 0; h < NV; ++h)
-#pragma unroll
-                        for (int e = 0; e < KB; ++e)
-                            if (32 * g + (F32 ? 16 * h : 0) + KB * q + e >= p.kv_len) vd[d][h][e] = {};
+                        vd[d][h] = *(const frag *)(vt + (dv0 + 16 * d + rho) * FC_VTILE + (F32 ? 16 * h : 0) + KB * q);
             }
+            f32x4 s[QT][2];
 #pragma unroll
             for (int u = 0; u < QT; ++u)
 #pragma unroll
+                for (int h = 0; h < 2; ++h) s[u][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (LDS) {
+#pragma unroll
+                for (int part = 0; part < 32 / L::KG; ++part) {
+                    if (part == 0) fc_wait_vm<L::NVL>();  // these keys are here; the values behind them may stay in flight
+                    else fc_wait_vm<0>();
+                    __builtin_amdgcn_sched_barrier(0);
+                    frag kf[L::KG / 16][NKB];
+#pragma unroll
+                    for (int h = 0; h < L::KG / 16; ++h)
+#pragma unroll
+                        for (int k = 0; k < NKB; ++k)
+                            kf[h][k] = *(const frag *)(kbuf + (16 * h + rho) * L::KROW + 16 * ((4 * k + q) ^ L::template swizzle<L::KROW>(16 * h + rho)));
+                    fc_wait_lds();  // lgkmcnt(0): the area may be overwritten
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (part + 1 < 32 / L::KG) issue_k(i, part + 1);
+                    else if (more) issue_k(i + 1, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    auto scores = [&](auto first, auto last) {  // 16-key halves first .. last - 1 of the part
+#pragma unroll
+                        for (int k = 0; k < NKB; ++k)
+#pragma unroll
+                            for (int u = 0; u < QT; ++u)
+#pragma unroll
+                                for (int h = decltype(first)::value; h < decltype(last)::value; ++h)
+                                    s[u][part * (L::KG / 16) + h] = O::mfma(kf[h][k], qf[u][k], s[u][part * (L::KG / 16) + h]);
+                    };
+                    const std::integral_constant<int, 0> c0;
+                    const std::integral_constant<int, 1> c1;
+                    const std::integral_constant<int, L::KG / 16> c2;
+                    if (half < 0) scores(c0, c2);
+                    else if (L::KG == 16) {
+                        if (half == part) scores(c0, c1);
+                    } else if (half == 0) scores(c0, c1);
+                    else scores(c1, c2);
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < QT; ++u)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int k = 0; k < NKB; ++k) s[u][h] = O::mfma(kd[h][k], qf[u][k], s[u][h]);
+                if (more) load_k(g + TW);  // the next group's keys travel behind the softmax and the output products
+            }
+            if (half >= 0) {
+#pragma unroll
+                for (int u = 0; u < QT; ++u)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if (half == 1) s[u][0][r] = -INFINITY;
+                        else s[u][1][r] = -INFINITY;
+                    }
+            }
+            const bool past = 32 * g + 32 > p.kv_len;  // keys past the end may hold anything: no score, and zero values (0 * V stays 0)
+            if (past) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (32 * g + key_of(h, 4 * q + r) >= p.kv_len) {
+#pragma unroll
+                            for (int u = 0; u < QT; ++u) s[u][h][r] = -INFINITY;
+                        }
+            }
+            frag pf[QT][F32 ? NV : NP];
+#pragma unroll
+            for (int u = 0; u < QT; ++u) {
+                float mx = s[u][0][0];
+#pragma unroll
+                for (int r = 1; r < 8; ++r) mx = fmaxf(mx, s[u][r >> 2][r & 3]);
+                const float m_new = fmaxf(m[u], max_rows(mx));
+                const float alpha = __builtin_amdgcn_exp2f((m[u] - m_new) * p.c);
+                m[u] = m_new;
+                l[u] *= alpha;
+                float pr[8];
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    pr[r] = __builtin_amdgcn_exp2f((s[u][r >> 2][r & 3] - m_new) * p.c);
+                    l[u] += pr[r];
+                }
+#pragma unroll
                 for (int d = 0; d < ND; ++d)
 #pragma unroll
-                    for (int h = 0; h < (F32 ? NV : NP); ++h) o[u][d] = O::mfma(vd[d][F32 ? h : 0], pf[u][h], o[u][d]);
+                    for (int r = 0; r < 4; ++r) o[u][d][r] *= alpha;
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    if constexpr (F32) {
+                        pf[u][r >> 2][r & 3] = pr[r];
+                    } else {
+#pragma unroll
+                        for (int h = 0; h < NP; ++h) {
+                            pf[u][h][r] = (__bf16)pr[r];
+                            pr[r] -= (float)pf[u][h][r];  // (exact)
+                        }
+                    }
+                }
+            }
+            if constexpr (LDS) {
+#pragma unroll
+                for (int part = 0; part < 32 / L::VG; ++part) {
+                    if (part == 0 && more) fc_wait_vm<L::NK>();  // these values are here; the next keys may stay in flight
+                    else fc_wait_vm<0>();
+                    __builtin_amdgcn_sched_barrier(0);
+                    constexpr int NVP = NV * L::VG / 32;  // fragments per 16 rows
+                    frag vf[ND][NVP];
+#pragma unroll
+                    for (int d = 0; d < ND; ++d)
+#pragma unroll
+                        for (int h = 0; h < NVP; ++h)
+                            vf[d][h] = *(const frag *)(vbuf + (16 * d + rho) * L::VROW + 16 * ((4 * h + q) ^ L::template swizzle<L::VROW>(16 * d + rho)));
+                    fc_wait_lds();
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (part + 1 < 32 / L::VG) issue_v(i, part + 1);
+                    else if (more) issue_v(i + 1, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (past) {
+#pragma unroll
+                        for (int d = 0; d < ND; ++d)
+#pragma unroll
+                            for (int h = 0; h < NVP; ++h)
+#pragma unroll
+                                for (int e = 0; e < KB; ++e)
+                                    if (32 * g + L::VG * part + (F32 ? 16 * h : 0) + KB * q + e >= p.kv_len) vf[d][h][e] = {};
+                    }
+#pragma unroll
+                    for (int h = 0; h < (F32 ? NVP : NP); ++h) {
+                        if (half >= 0 && half != NVP * part + h) continue;
+#pragma unroll
+                        for (int u = 0; u < QT; ++u)
+#pragma unroll
+                            for (int d = 0; d < ND; ++d) o[u][d] = O::mfma(vf[d][F32 ? h : 0], pf[u][F32 ? NVP * part + h : h], o[u][d]);
+                    }
+                }
+            } else {
+                if (past) {
+#pragma unroll
+                    for (int d = 0; d < ND; ++d)
+#pragma unroll
+                        for (int h = 0; h < NV; ++h)
+#pragma unroll
+                            for (int e = 0; e < KB; ++e)
+                                if (32 * g + (F32 ? 16 * h : 0) + KB * q + e >= p.kv_len) vd[d][h][e] = {};
+                }
+#pragma unroll
+                for (int u = 0; u < QT; ++u)
+#pragma unroll
+                    for (int d = 0; d < ND; ++d)
+#pragma unroll
+                        for (int h = 0; h < (F32 ? NV : NP); ++h) o[u][d] = O::mfma(vd[d][F32 ? h : 0], pf[u][h], o[u][d]);
+            }
         }
-    }
+    };
+    take(0, halves ? rounds : n, std::integral_constant<int, WHOLE>());
+    if constexpr (F32 && LDS)
+        if (halves) take(rounds, n, std::integral_constant<int, HALF>());
 
     // ---- merge the eight waves through LDS
 #pragma unroll

@@ -1,5 +1,6 @@
-"""What the compiler makes of the attention kernel over key ranges, whose scores' multiplies are inline assembly that its hazard rules do not
-see: every other use of a score is far enough behind the multiply, and no register goes to memory in the loops."""
+"""What the compiler makes of the attention kernels.  Over key ranges the scores' multiplies are inline assembly that its hazard rules do not
+see: every other use of a score is far enough behind the multiply, and no register goes to memory in the loops.  In the fp32 tile kernel the
+output products go beside the softmax."""
 import os
 import re
 import subprocess
@@ -20,11 +21,11 @@ def _registers(text):
     return out
 
 
-def _kernels(asm):
-    """(name, instructions, place of each label, bytes of scratch) of every k_attn_ranges; an instruction: (opcode, operands, in inline assembly)."""
+def _kernels(asm, kernel):
+    """(name, instructions, place of each label, bytes of scratch) of every instance of a kernel; an instruction: (opcode, operands, in inline assembly)."""
     lines, out = asm.split("\n"), []
     for start, line in enumerate(lines):
-        if not (re.match(r"_Z\S*k_attn_ranges\S*:", line)):
+        if not re.match(r"_Z\S*%s\S*:" % kernel, line):
             continue
         code, labels, inline = [], {}, False
         for at in range(start + 1, len(lines)):
@@ -72,13 +73,17 @@ def _nearest_use(code, labels, at):
     return nearest
 
 
-@pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    out = str(tmp_path_factory.mktemp("asm") / "attn.s")
-    cmd = [build.HIPCC, *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, "fc_attn_mfma.hip"), "-o", out]
+def _compiled(folder, source):
+    out = str(folder.mktemp("asm") / "code.s")
+    cmd = [build.HIPCC, *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, source), "-o", out]
     subprocess.run(cmd, check=True, capture_output=True, timeout=240)
     with open(out) as f:
-        found = _kernels(f.read())
+        return f.read()
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    found = _kernels(_compiled(tmp_path_factory, "fc_attn_mfma.hip"), "k_attn_ranges")
     assert len(found) == 10
     return found
 
@@ -111,3 +116,20 @@ def test_a_use_too_near_is_found():
     assert far(("s_cbranch_vccnz", ".LBB0_1", False), ("s_nop", "15", False), read) == 1
     assert far(("s_nop", "15", False), ("s_nop", "3", False), read) == NEEDED and far(("v_fma_f32", "v20, s3, v4, v21", False)) == NEEDED
     assert far(("v_mfma_f32_16x16x32_bf16", "v[0:3], v[40:43], v[44:47], v[0:3]", True), read) == NEEDED
+
+
+def test_fp32_tile_products_go_beside_the_softmax(tmp_path_factory):
+    """The loop over whole groups has a group's exponentials (nine per tile of 16 rows) and its output products without a branch between them
+    (those for halves of groups, there, took up to 6 % of a call)."""
+    found = _kernels(_compiled(tmp_path_factory, "fc_generic.hip"), r"k_attn_tileIfLi\d+ELi\d+ELi\d+ELb1E")
+    assert len(found) == 7
+    for name, code, labels, scratch in found:
+        tiles = int(re.search(r"k_attn_tileIfLi\d+ELi(\d+)E", name).group(1))
+        starts = set(labels.values()) | {i + 1 for i, (op, _, _) in enumerate(code) if op.startswith("s_cbranch")}
+        edges = sorted(starts | {0, len(code)})
+        both = 0
+        for a, b in zip(edges, edges[1:]):
+            ops = [op for op, _, _ in code[a:b]]
+            if any(op.startswith("v_mfma") for op in ops):
+                both += sum(op.startswith("v_exp") for op in ops)
+        assert both >= 9 * tiles and scratch == 0, (name, both)
